@@ -2,6 +2,7 @@
 #include <mutex>
 
 #include "qmoe_dev.h"
+#include "qmoe_encode.h"
 
 namespace qmoe {
 
@@ -423,6 +424,13 @@ qmoe_status qmoe_dict_upload(qmoe_dict *d, void *dev_buf, size_t dev_bytes, void
         QMOE_HIP_TRY(hipMemcpyAsync(b + kDevTrieCodeOffset, d->code.data(), sizeof(int32_t) * d->code.size(),
                                     hipMemcpyHostToDevice, s));
     }
+    if (!d->rc_depth.empty()) {  // (after the trie: the run coder's tables lie in space its nodes do not reach)
+        QMOE_HIP_TRY(hipMemcpyAsync(b + kDevRcDepthOffset, d->rc_depth.data(), d->rc_depth.size(), hipMemcpyHostToDevice, s));
+        QMOE_HIP_TRY(hipMemcpyAsync(b + kDevRcFirstOffset, d->rc_first.data(), sizeof(uint32_t) * d->rc_first.size(),
+                                    hipMemcpyHostToDevice, s));
+        QMOE_HIP_TRY(hipMemcpyAsync(b + kDevRcCodesOffset, d->rc_codes.data(), sizeof(uint16_t) * d->rc_codes.size(),
+                                    hipMemcpyHostToDevice, s));
+    }
     d->dev = dev_buf;
     return QMOE_OK;
 }
@@ -434,7 +442,11 @@ qmoe_status qmoe_encode_device(const qmoe_dict *d, const int8_t *ternary, int ro
     if (!d->dev) return QMOE_E_NO_DEVICE_DICT;
     if (d->code.empty() || d->code.size() > (size_t)kMaxTrieNodes) return QMOE_E_LIMIT;
     const unsigned char *base = static_cast<const unsigned char *>(d->dev);
-    EncodeArgs a{};
+    DeviceInfo di;
+    const qmoe_status st = device_info(&di);
+    if (st != QMOE_OK) return st;
+    RunCoderArgs ra{};
+    EncodeArgs &a = ra.e;
     a.tern = ternary;
     a.rows = rows;
     a.cols = cols;
@@ -444,7 +456,15 @@ qmoe_status qmoe_encode_device(const qmoe_dict *d, const int8_t *ternary, int ro
     a.codes = codes;
     a.codes_cap = codes_cap;
     a.status = status;
-    return launch_encode(a, static_cast<hipStream_t>(stream));
+    if (!d->rc_depth.empty()) {
+        ra.depth = reinterpret_cast<const uint32_t *>(base + kDevRcDepthOffset);
+        ra.first = reinterpret_cast<const uint32_t *>(base + kDevRcFirstOffset);
+        ra.codes = reinterpret_cast<const uint16_t *>(base + kDevRcCodesOffset);
+        ra.depth0 = d->rc_depth0;
+    }
+    ra.cus = di.cus;
+    ra.max_lds = di.max_lds;
+    return launch_encode(ra, static_cast<hipStream_t>(stream));
 }
 
 qmoe_status qmoe_decode_matvec(const qmoe_dict *d, const qmoe_matrix *W, const uint16_t *x_bf16, int batch,

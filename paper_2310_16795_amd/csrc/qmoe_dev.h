@@ -7,7 +7,8 @@
 //   qmoe_product_mm.hip                  decode once, multiply on the matrix cores; decompression
 //   qmoe_matvec.hip                      one matrix, a few tokens: 16 lanes per row; decode-only hook
 //   qmoe_dispatch.hip                    tokens grouped by expert, work lists
-//   qmoe_misc.hip                        device encoder, bf16 comparator, copy, renumbering
+//   qmoe_encode.hip                      device encoder (its arguments: qmoe_encode.h)
+//   qmoe_misc.hip                        bf16 comparator, copy, renumbering
 //   qmoe_api.hip                         launch planning and the C ABI
 // Not part of the C ABI.
 #pragma once
@@ -109,16 +110,6 @@ struct DispatchArgs {
     int d_model;
 };
 
-struct EncodeArgs {
-    const int8_t *tern;   // [rows][cols], values -1 / 0 / +1
-    int rows, cols;
-    const int32_t *child, *code;
-    uint32_t *row_off;    // [rows+1]
-    uint16_t *codes;
-    unsigned long long codes_cap;
-    int *status;          // [2]: first error (qmoe_status, 0 = none), a row it happened in
-};
-
 struct DenseArgs {
     const uint16_t *const *mats;  // device array of row-major bf16 matrices, by expert
     const Item *items;
@@ -181,8 +172,7 @@ qmoe_status launch_matvec_rows(const ProductArgs &a, bool run, bool minmax, int 
                                hipStream_t s);                                                      // qmoe_matvec.hip
 qmoe_status launch_decode_dense(const ProductArgs &a, bool run, int8_t *out, int grid, hipStream_t s);
 qmoe_status launch_dispatch_kernel(const DispatchArgs &da, hipStream_t s);                          // qmoe_dispatch.hip
-qmoe_status launch_encode(const EncodeArgs &a, hipStream_t s);                                      // qmoe_misc.hip
-qmoe_status launch_dense_bf16(const DenseArgs &a, const ProductPlan &p, hipStream_t s);
+qmoe_status launch_dense_bf16(const DenseArgs &a, const ProductPlan &p, hipStream_t s);             // qmoe_misc.hip
 qmoe_status launch_stream_copy(void *dst, const void *src, size_t n16, int grid, hipStream_t s);
 qmoe_status launch_renumber(uint16_t *codes, size_t n, const uint16_t *map, int grid, hipStream_t s);
 

@@ -55,6 +55,31 @@ constexpr size_t kDevOrderMapOffset = kDevOrderTableOffset + sizeof(uint32_t) * 
 constexpr int kMaxTrieNodes = 1 << 17;
 constexpr size_t kDevTrieChildOffset = (kDevOrderMapOffset + sizeof(uint16_t) * kTableEntries + 255) / 256 * 256;
 constexpr size_t kDevTrieCodeOffset = kDevTrieChildOffset + sizeof(int32_t) * 9 * kMaxTrieNodes;
+
+// Run coder: the longest dictionary prefix of a position found from the places of its next non-zeros,
+// without walking the trie pair by pair.  For dictionaries whose entries hold at most three non-zeros
+// and whose every prefix of an entry is an entry (the paper's table).  Take the next 28 values of a row:
+// non-zeros at p1 < p2 < p3 < ... with sign bits s (1 = negative).  The entries that start like this and
+// hold exactly the first k of those non-zeros are one pattern; they differ only in their number of pairs,
+// which runs without gaps from p_k / 2 + 1 to the pattern's depth.  So the longest match is, over
+// k = 0..3, the largest min(depth of pattern k, p_{k+1} / 2, pairs left in the row) that is above p_k / 2.
+// Patterns are numbered by the combinatorial number system, C(p3,3) + C(p2,2) + p1 and so on:
+constexpr int kRcThree = 0;                        // + 8 * (C(p3,3) + C(p2,2) + p1) + (s1 | s2 << 1 | s3 << 2)
+constexpr int kRcTwo = 8 * 3276;                   // + 4 * (C(p2,2) + p1) + (s1 | s2 << 1)
+constexpr int kRcOne = kRcTwo + 4 * 378;           // + 2 * p1 + s1
+constexpr int kRcZero = kRcOne + 2 * 28;           // no non-zero
+constexpr int kRcPatterns = kRcZero + 1;
+// Depth tables: depth3, four bits a pattern of three (two sign variants a byte), then (at kRcDepth3Bytes) depth2 |
+// depth1 << 4, a byte by pattern of two, where positions 28 and 29 stand for non-zeros that are not there.
+constexpr int kRcDepth3Bytes = kRcTwo / 2 + 16;    // the last 16 bytes are 0: index of everything with p3 >= 28
+constexpr int kRcDepth2Bytes = (4 * 435 + 15) / 16 * 16;
+constexpr int kRcDepthBytes = kRcDepth3Bytes + kRcDepth2Bytes;
+// A dictionary with a run coder has at most kTableEntries + 1 trie nodes (each but the root is an entry), so
+// its tables take the unused half of the child table's space.
+constexpr size_t kDevRcDepthOffset = (kDevTrieChildOffset + sizeof(int32_t) * 9 * (kTableEntries + 1) + 255) / 256 * 256;
+constexpr size_t kDevRcFirstOffset = (kDevRcDepthOffset + kRcDepthBytes + 255) / 256 * 256;  // uint32 by pattern
+constexpr size_t kDevRcCodesOffset = (kDevRcFirstOffset + sizeof(uint32_t) * kRcPatterns + 255) / 256 * 256;
+static_assert(kDevRcCodesOffset + sizeof(uint16_t) * kTableEntries <= kDevTrieCodeOffset, "run-coder tables fit");
 constexpr size_t kDevDictBytes = kDevTrieCodeOffset + sizeof(int32_t) * kMaxTrieNodes;
 
 struct Tuning {
@@ -89,5 +114,11 @@ struct qmoe_dict {
     // trie over the entries: child[node * 9 + pair] (-1 = none), code[node] (-1 = no entry ends here)
     std::vector<int32_t> child;
     std::vector<int32_t> code;
+    // run coder (empty when the dictionary does not qualify): codeword of pattern i with D pairs is
+    // rc_codes[rc_first[i] + D] (modulo 2^32); the depth tables as laid out above; depth of the empty pattern
+    std::vector<uint8_t> rc_depth;
+    std::vector<uint32_t> rc_first;
+    std::vector<uint16_t> rc_codes;
+    int rc_depth0 = 0;
     const void *dev = nullptr;  // bound by qmoe_dict_upload
 };

@@ -1,109 +1,9 @@
-// Kernels around the hot path: the encoder on the device, the uncompressed bf16
-// comparator, a plain copy (bandwidth yardstick) and the load-time renumbering of a stream.
+// Kernels around the hot path: the uncompressed bf16 comparator, a plain copy (bandwidth
+// yardstick) and the load-time renumbering of a stream.
 #include "qmoe_dev.h"
 
 namespace qmoe {
 namespace {
-
-// exclusive prefix sum of one int per thread over the workgroup; `tmp` holds >= 32 ints
-__device__ __forceinline__ int block_exclusive_scan(int v, int *tmp, int &total)
-{
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwaves = (blockDim.x + 63) >> 6;
-    int incl = v;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int up = __shfl_up(incl, d, 64);
-        if (lane >= d) incl += up;
-    }
-    if (lane == 63) tmp[wave] = incl;
-    __syncthreads();
-    if (wave == 0) {
-        int w = lane < nwaves ? tmp[lane] : 0;
-        int wi = w;
-#pragma unroll
-        for (int d = 1; d < 16; d <<= 1) {
-            const int up = __shfl_up(wi, d, 64);
-            if (lane >= d) wi += up;
-        }
-        if (lane < nwaves) tmp[lane] = wi - w;  // exclusive per wave
-        if (lane == nwaves - 1) tmp[16] = wi;   // grand total
-    }
-    __syncthreads();
-    const int base = tmp[wave];
-    total = tmp[16];
-    __syncthreads();
-    return base + incl - v;
-}
-
-// ---------------------------------------------------------------- encoder
-//
-// Longest-prefix coding of ternary rows with the dictionary's trie (Section 4.3.3
-// "Encoding"), one row per lane: walk pairs from the root while a child exists, emit the
-// codeword of the deepest node that ends an entry, continue after that entry.  Three
-// launches: count codewords per row, turn the counts into row offsets (one workgroup), write
-// the codewords.  Same stream as qmoe_encode_host, codeword for codeword.
-
-
-__global__ void k_encode_clear(int *status)
-{
-    if (threadIdx.x < 2) status[threadIdx.x] = 0;
-}
-
-template <bool WRITE>
-__global__ __launch_bounds__(256) void k_encode(const EncodeArgs a)
-{
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= a.rows) return;
-    if (WRITE && a.status[0] != 0) return;
-    const int8_t *row = a.tern + (size_t)r * a.cols;
-    const int np = a.cols / 2;
-    const size_t out = WRITE ? (size_t)a.row_off[r] : 0;
-    uint32_t n = 0;
-    int bad = 0;
-    int i = 0;
-    while (i < np) {
-        int node = 0, best = -1, best_len = 0, depth = 0;
-        while (i + depth < np) {
-            const int va = row[2 * (i + depth)], vb = row[2 * (i + depth) + 1];
-            if (va < -1 || va > 1 || vb < -1 || vb > 1) { bad = QMOE_E_BAD_SYMBOL; break; }
-            // value -> symbol: 0 -> 0, -1 -> 1, +1 -> 2; pair index = 3 * first + second
-            const int sa = va == 0 ? 0 : (va < 0 ? 1 : 2), sb = vb == 0 ? 0 : (vb < 0 ? 1 : 2);
-            const int nx = a.child[(size_t)node * 9 + 3 * sa + sb];
-            if (nx < 0) break;
-            node = nx;
-            depth++;
-            const int c = a.code[node];
-            if (c >= 0) { best = c; best_len = depth; }
-        }
-        if (bad) break;
-        if (best < 0) { bad = QMOE_E_UNENCODABLE; break; }
-        if (WRITE) a.codes[out + n] = (uint16_t)best;
-        n++;
-        i += best_len;
-    }
-    if (bad) {
-        if (atomicCAS(&a.status[0], 0, bad) == 0) a.status[1] = r;
-        n = 0;
-    }
-    if (!WRITE) a.row_off[r + 1] = n;
-}
-
-// counts in row_off[1..rows] -> offsets; one workgroup
-__global__ __launch_bounds__(1024) void k_encode_offsets(const EncodeArgs a)
-{
-    __shared__ int tmp[32];
-    unsigned long long base = 0;
-    if (threadIdx.x == 0) a.row_off[0] = 0;
-    for (int r0 = 0; r0 < a.rows; r0 += (int)blockDim.x) {
-        const int r = r0 + (int)threadIdx.x;
-        const int c = r < a.rows ? (int)a.row_off[r + 1] : 0;
-        int total;
-        const int excl = block_exclusive_scan(c, tmp, total);
-        if (r < a.rows) a.row_off[r + 1] = (uint32_t)(base + (unsigned long long)(excl + c));
-        base += (unsigned long long)total;
-    }
-    if (threadIdx.x == 0 && (base > a.codes_cap || base > 0xFFFFFFFFull)) atomicCAS(&a.status[0], 0, QMOE_E_BUFFER_TOO_SMALL);
-}
 
 // ---------------------------------------------------------------- uncompressed bf16 comparator
 
@@ -258,18 +158,6 @@ __global__ __launch_bounds__(256) void k_renumber(uint16_t *codes, size_t n, con
 }
 
 }  // namespace
-
-qmoe_status launch_encode(const EncodeArgs &a, hipStream_t s)
-{
-    const int grid = (a.rows + 255) / 256;
-    // the status words are cleared by a kernel, not a memset node, so the call can be captured into a HIP graph
-    hipLaunchKernelGGL(k_encode_clear, dim3(1), dim3(64), 0, s, a.status);
-    hipLaunchKernelGGL(k_encode<false>, dim3(grid), dim3(256), 0, s, a);
-    hipLaunchKernelGGL(k_encode_offsets, dim3(1), dim3(1024), 0, s, a);
-    hipLaunchKernelGGL(k_encode<true>, dim3(grid), dim3(256), 0, s, a);
-    QMOE_HIP_TRY(hipGetLastError());
-    return QMOE_OK;
-}
 
 qmoe_status launch_dense_bf16(const DenseArgs &a, const ProductPlan &p, hipStream_t s)
 {

@@ -1,0 +1,92 @@
+"""The encoders' run coder (longest dictionary prefix from the places of the next non-zeros) against the oracle's
+trie: widths around its 16-value, 32-pair and segment edges, rows that no group of four or wavefront divides,
+all-zero and zero-free rows, and a dictionary that lacks phrases."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2310_16795_amd as q
+from paper_2310_16795_amd import device as dev
+from paper_2310_16795_amd import synth
+
+SHAPES = [(1, 2, 0.5), (5, 14, 0.9), (3, 16, 0.3), (65, 62, 0.9), (64, 64, 0.9), (66, 66, 0.97), (7, 1022, 0.885),
+          (513, 770, 0.3), (200, 2080, 0.0), (100, 1030, 1.0), (3, 30000, 0.93), (700, 4100, 0.92)]
+
+
+def _check(got, ref):
+    assert np.array_equal(got[1], ref[1]) and np.array_equal(got[0], ref[0])
+
+
+@pytest.mark.parametrize("rows,cols,p0", SHAPES)
+def test_host_encoder_equals_the_oracle_stream(oracle_dict, rows, cols, p0):
+    d = q.qmoe_dict_from_words(oracle_dict.words)
+    tern = synth.ternary(rows + cols, rows, cols, p0)
+    _check(q.qmoe_encode_host(d, tern), oracle.encode(oracle_dict, tern))
+    q.qmoe_dict_destroy(d)
+
+
+def _small_dictionary():
+    """The 40 most probable phrases: prefix-closed, but without a phrase for two neighbouring non-zeros."""
+    return oracle.Dictionary(p0=0.9, n_entries=40)
+
+
+def test_host_encoder_with_missing_phrases():
+    od = _small_dictionary()
+    d = q.qmoe_dict_from_words(od.words)
+    tern = np.zeros((9, 200), dtype=np.int8)
+    tern[:, 31::40] = 1
+    _check(q.qmoe_encode_host(d, tern), oracle.encode(od, tern))
+    tern[4, 100:102] = 1
+    with pytest.raises(q.QmoeError) as ei:
+        q.qmoe_encode_host(d, tern)
+    assert ei.value.status == -7  # UNENCODABLE
+    tern[4, 150] = 2  # behind it: the first error of the row counts
+    with pytest.raises(q.QmoeError) as ei:
+        q.qmoe_encode_host(d, tern)
+    assert ei.value.status == -7
+    tern[4, 20] = 2
+    with pytest.raises(q.QmoeError) as ei:
+        q.qmoe_encode_host(d, tern)
+    assert ei.value.status == -3  # BAD_SYMBOL
+    q.qmoe_dict_destroy(d)
+
+
+def _on_device(dd, tern, capacity):
+    codes = torch.full((capacity,), -1, dtype=torch.int16, device="cuda:0")
+    off = torch.empty(tern.shape[0] + 1, dtype=torch.int32, device="cuda:0")
+    status = torch.full((2,), 99, dtype=torch.int32, device="cuda:0")
+    q.qmoe_encode_device(dd.handle, torch.from_numpy(tern).to("cuda:0"), codes, off, status)
+    torch.cuda.synchronize()
+    return codes.cpu().numpy().view(np.uint16), off.cpu().numpy().view(np.uint32), status.tolist()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,cols,p0", SHAPES + [(20000, 130, 0.9), (40, 6146, 0.92)])
+def test_device_encoder_equals_the_oracle_stream(oracle_dict, rows, cols, p0):
+    dd = dev.DeviceDict(q.qmoe_dict_from_words(oracle_dict.words))
+    tern = synth.ternary(rows + cols, rows, cols, p0)
+    codes_ref, off_ref = oracle.encode(oracle_dict, tern)
+    codes, off, status = _on_device(dd, tern, codes_ref.size + 8)
+    assert status[0] == 0
+    _check((codes[:codes_ref.size], off), (codes_ref, off_ref))
+    assert (codes[codes_ref.size:] == 0xFFFF).all()  # nothing behind the stream
+    dd.close()
+
+
+@pytest.mark.gpu
+def test_device_encoder_with_missing_phrases():
+    od = _small_dictionary()
+    dd = dev.DeviceDict(q.qmoe_dict_from_words(od.words))
+    tern = np.zeros((70, 1200), dtype=np.int8)
+    tern[:, 31::40] = 1
+    codes_ref, off_ref = oracle.encode(od, tern)
+    codes, off, status = _on_device(dd, tern, codes_ref.size)
+    assert status[0] == 0
+    _check((codes, off), (codes_ref, off_ref))
+    for at, value, want in ((600, 1, -7), (900, 2, -7), (20, 2, -3)):
+        tern[41, at] = value
+        if at == 600:
+            tern[41, 601] = 1
+        assert _on_device(dd, tern, codes_ref.size)[2] == [want, 41]
+    dd.close()
