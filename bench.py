@@ -400,7 +400,7 @@ def main():
                    "zero_fraction": "0.80-0.97 per row" if w.p0_spread else w.p0,
                    "code_order": "interchange" if args.interchange_order else "device",
                    "stream_layout": (f"lane-interleaved ({layer.lanes['wi']} / {layer.lanes['wo']} lanes per matrix)"
-                                     if lanes_layout else "rows back to back"),
+                                     if layer.lanes["wi"] else "rows back to back"),
                    "grid": "{w_min,0,w_max}, bf16 pair per row" if minmax else "{-s,0,+s}, binary16 scale per row",
                    "dict_entries": args.dict_entries, "dict_max_pairs": args.dict_max_pairs},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBPS, "unit": "GB/s",

@@ -30,7 +30,7 @@
  *    (qmoe_set_tuning); per device, created on first use and kept until the process
  *    ends: the device's compute-unit count and LDS size, two events and -- only if a
  *    layer call brings no second stream of its own -- one stream (qmoe_moe_layer_forward),
- *    and the address of the 8 MiB scratch array of qmoe_moe_layer_forward_static.
+ *    and the address of the scratch array of qmoe_moe_layer_forward_static.
  */
 #ifndef QMOE_H
 #define QMOE_H
@@ -241,6 +241,13 @@ qmoe_status qmoe_lane_layout_unpack(const uint16_t *pieces /*host*/, const uint3
  * LDS size); 0 on error.  Build the lane-interleaved layout of that projection for this count.
  */
 int qmoe_plan_lanes(const qmoe_dict *d, int rows, int cols, int n_experts, int n_tokens);
+/*
+ * Which stream layout calls over n_experts experts and about n_tokens tokens read fastest
+ * (device numbering; needs the GPU): 1 = rows back to back, as encoded -- small calls share
+ * every row between several lanes and read the rows' pieces in order --, 0 = lane-interleaved
+ * (also on error).  Every call reads both layouts.
+ */
+int qmoe_plan_row_layout(const qmoe_dict *d, int d_model, int d_ff, int n_experts, int n_tokens);
 
 /*
  * Format bits for the calls whose matrix descriptors live in device memory (the host
@@ -274,9 +281,10 @@ qmoe_status qmoe_codes_to_device_order(const qmoe_dict *d, uint16_t *codes /*dev
  * W: host struct holding device pointers.  x: device bf16 [batch][cols].
  * y: device fp32 [batch][rows], overwritten.  fp32 accumulation.
  * One launch.  A small batch runs on a kernel that puts 16 lanes on every row (latency of a
- * single product); from a few dozen tokens on (device-order stream, cols divisible by 8, x
- * 16-byte aligned; the switch is a cost estimate, "mfma_min_tokens" overrides it) the matrix
- * is decoded once per 64 tokens and multiplied on the matrix cores.
+ * single product); more work (device-order stream) on one that stages the table in LDS; and from
+ * some hundred tokens on (also cols divisible by 8, x 16-byte aligned) the matrix is decoded once
+ * per 64 tokens and multiplied on the matrix cores.  The switches are cost estimates;
+ * "mfma_min_tokens" overrides the last one.
  * Errors: INVALID_ARG (NULL, batch<1, odd cols), NO_DEVICE_DICT, LIMIT
  * (cols > 32768, or four tokens' activations, 8 bytes per column, do not fit the LDS: cols
  * above 20448 on a GPU with 160 KB), HIP.
@@ -354,6 +362,9 @@ size_t qmoe_moe_layer_workspace(int n_experts, int d_model, int d_ff, int n_toke
  * may hold anything).  code_order: QMOE_FORMAT_* bits: the numbering of every expert's
  * stream (bit 0, as in qmoe_matrix) and whether the experts are on the asymmetric grid
  * (QMOE_FORMAT_GRID_MINMAX; the descriptors live in device memory, so the host is told).
+ * A call of fewer tokens than four per compute unit on experts of at least 2^18 weights
+ * (device order, rows back to back) enqueues one kernel per product, the first of which
+ * groups the tokens itself where it can (up to 512 tokens).  Otherwise:
  * Enqueues a dispatch kernel and, per product, the scalar kernel for experts with few
  * tokens and (device-order streams, widths divisible by 8, x 16-byte aligned) the
  * matrix-core kernel for crowded ones: an expert's matrix is decoded once per tile of up
@@ -386,7 +397,7 @@ qmoe_status qmoe_moe_layer_forward(const qmoe_dict *d, const qmoe_matrix *wi /*d
  * holds its copy until the process ends).  All kernels are enqueued on `stream`, one after
  * the other (no second stream, no events); the call allocates nothing and creates nothing.
  * Limit: qmoe_moe_layer_workspace(n_experts, d_model, d_ff, n_tokens) must not exceed
- * qmoe_static_workspace_bytes(), else QMOE_E_LIMIT (e.g. 512 tokens at d_ff = 4096 fit,
+ * qmoe_static_workspace_bytes() by more than 32 KiB, else QMOE_E_LIMIT (e.g. 512 tokens at d_ff = 4096 fit,
  * 2048 tokens at d_ff = 6144 do not).  Every call on a GPU shares that GPU's array and
  * finds the previous call's contents there (the dispatch kernel rewrites all it reads);
  * calls that overlap on one GPU -- two streams, two host threads -- race.

@@ -54,6 +54,7 @@ EXPORTS = [
     "qmoe_bf16_layer_forward", "qmoe_set_tuning", "qmoe_stream_copy", "qmoe_dict_device_order",
     "qmoe_codes_to_device_order", "qmoe_decompress", "qmoe_encode_device", "qmoe_hook_set", "qmoe_static_workspace_bytes", "qmoe_moe_layer_forward_static",
     "qmoe_lane_layout_size", "qmoe_lane_layout_build", "qmoe_lane_layout_unpack", "qmoe_plan_lanes",
+    "qmoe_plan_row_layout",
 ]
 
 
@@ -102,6 +103,7 @@ def lib():
         L.qmoe_lane_layout_build.argtypes = [vp, vp, i, i, vp, sz, vp]
         L.qmoe_lane_layout_unpack.argtypes = [vp, vp, vp, i, i, vp, sz]
         L.qmoe_plan_lanes.argtypes = [vp, i, i, i, i]
+        L.qmoe_plan_row_layout.argtypes = [vp, i, i, i, i]
         L.qmoe_hook_set.argtypes = [c_char_p, i]
         L.qmoe_stream_copy.argtypes = [vp, vp, sz, vp]
         _lib = L
@@ -335,6 +337,11 @@ def qmoe_plan_lanes(d: int, rows: int, cols: int, n_experts: int, n_tokens: int)
     if n <= 0:
         raise QmoeError(-1, "qmoe_plan_lanes")
     return n
+
+
+def qmoe_plan_row_layout(d: int, d_model: int, d_ff: int, n_experts: int, n_tokens: int) -> bool:
+    """True: layer calls of this size read rows back to back fastest; False: the lane-interleaved layout."""
+    return lib().qmoe_plan_row_layout(d, d_model, d_ff, n_experts, n_tokens) == 1
 
 
 def qmoe_lane_layout_build(codes: np.ndarray, row_off: np.ndarray, rows: int, lanes: int):

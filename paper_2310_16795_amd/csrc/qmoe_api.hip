@@ -78,8 +78,9 @@ qmoe_status side_stream(hipStream_t callers, SideStream *out)
 // library's own device image, so that the call allocates nothing.  Each GPU holds its own
 // copy at its own address; host code uses the address hipGetSymbolAddress returns for the
 // current device, never the array's name.
+constexpr size_t kShareRecords = kRowsShareBytes * kRowsMaxGrid;  // k_rows' part of a workspace, on top of what callers look at
 constexpr size_t kStaticWsBytes = (size_t)8 << 20;
-__device__ __align__(256) unsigned char g_static_ws[kStaticWsBytes];
+__device__ __align__(256) unsigned char g_static_ws[kStaticWsBytes + kShareRecords];
 
 qmoe_status static_workspace(void **out)
 {
@@ -304,6 +305,34 @@ qmoe_status plan_mm(const qmoe_dict *d, int code_order, int d_model, int d_ff, i
     return QMOE_OK;
 }
 
+// Do the experts with few tokens of a layer call take the kernel with several lanes per row, and how?
+struct RowsPlan {
+    bool on = false;
+    int slots_wi = 0, slots_wo = 0, grid = 0, max_lds = 0;
+};
+
+RowsPlan rows_plan(const qmoe_dict *d, int code_order, int lanes, int d_model, int d_ff, int n_tokens, int tb)
+{
+    RowsPlan p;
+    const int n_order = (int)d->order_table.size();
+    DeviceInfo di;
+    if (code_order != 1 || lanes || !n_order || d->max_nonzeros > kRunMaxNonzeros || tuning().rows < 0 || device_info(&di) != QMOE_OK)
+        return p;
+    p.max_lds = di.max_lds;
+    p.slots_wi = rows_tile_slots(d_model, tb, n_order, di.max_lds);
+    p.slots_wo = rows_tile_slots(d_ff, tb, n_order, di.max_lds);
+    p.grid = std::min(di.cus, kRowsMaxGrid);
+    // Calls of fewer than four tokens per compute unit (the line below which the matrix-core kernel stays off): the lanes
+    // of the other kernel own too few rows then, or there are too few of them (128 tokens on 128 experts of 768 x 3072:
+    // 68 -> 46 us; 512 on 128 of 1024 x 4096: 167 -> 120 us; one token, 2080 x 6144: 73 -> 22 us).  In larger calls that
+    // kernel's hand-out of items, next to the matrix-core kernel's workgroups, is the better one (2048 tokens on 2048
+    // experts: 0.97 ms against 1.03).  Matrices of less than a quarter of a million weights are launch latency either way
+    // and stay on the kernel that reads both stream layouts.
+    const bool small = n_tokens < 4 * di.cus && (long long)d_model * d_ff >= 1 << 18;
+    p.on = p.slots_wi && p.slots_wo && (small || tuning().rows > 0);
+    return p;
+}
+
 qmoe_status check_matrix_args(const qmoe_dict *d, const qmoe_matrix *W)
 {
     if (!d || !W) return QMOE_E_INVALID_ARG;
@@ -361,6 +390,7 @@ struct LayerPtrs {
     int *tok_off, *perm, *counters;
     Item *items_wi, *items_wo, *items_mm;
     uint16_t *hidden;
+    int *shares;  // k_rows: a record per workgroup
 };
 
 LayerPtrs layer_ptrs(void *ws, const qmoe_ws_layout &l)
@@ -369,11 +399,12 @@ LayerPtrs layer_ptrs(void *ws, const qmoe_ws_layout &l)
     return LayerPtrs{reinterpret_cast<int *>(b + l.tok_off), reinterpret_cast<int *>(b + l.perm),
                      reinterpret_cast<int *>(b + l.counters), reinterpret_cast<Item *>(b + l.items_wi),
                      reinterpret_cast<Item *>(b + l.items_wo), reinterpret_cast<Item *>(b + l.items_mm),
-                     reinterpret_cast<uint16_t *>(b + l.hidden)};
+                     reinterpret_cast<uint16_t *>(b + l.hidden),
+                     reinterpret_cast<int *>(b + l.total - kShareRecords)};
 }
 
-qmoe_status launch_dispatch(const int32_t *expert_idx, int n_tokens, int n_experts, int d_model,
-                            const LayerPtrs &lp, int tb_wi, int tb_wo, int mm_min, float *y, hipStream_t s)
+DispatchArgs dispatch_args(const int32_t *expert_idx, int n_tokens, int n_experts, int d_model, const LayerPtrs &lp, int tb_wi,
+                           int tb_wo, int mm_min, float *y)
 {
     DispatchArgs da;
     da.expert_idx = expert_idx;
@@ -390,7 +421,7 @@ qmoe_status launch_dispatch(const int32_t *expert_idx, int n_tokens, int n_exper
     da.mm_min = mm_min;
     da.y = y;
     da.d_model = d_model;
-    return launch_dispatch_kernel(da, s);
+    return da;
 }
 }  // namespace
 }  // namespace qmoe
@@ -499,38 +530,48 @@ qmoe_status qmoe_decode_matvec(const qmoe_dict *d, const qmoe_matrix *W, const u
     a.cols = W->cols;
     a.tb_max = tb;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    // Many tokens: the matrix-core kernel decodes the matrix once per 64 tokens instead of once
-    // per 8.  Its unit of work is 64 rows of a token tile, taken by one wavefront (a unit's time is
-    // set by the length of a row, not by how many units there are).
-    {
-        const Tuning &tu = tuning();
-        const int n_order = (int)d->order_table.size();
-        if (code_order == 1 && run && n_order > 0 && tu.mfma_min_tokens >= 0 && W->cols % 8 == 0 &&
-            reinterpret_cast<uintptr_t>(x_bf16) % 16 == 0 && mm_lds_bytes(n_order) <= (size_t)di.max_lds) {
-            const int tiles = (batch + kMmTokens - 1) / kMmTokens;
-            const int waves = kMmThreads / 64;
-            const long long units = (long long)tiles * ((W->rows + 63) / 64);
-            const long long blocks = (units + waves - 1) / waves;  // workgroups with every wavefront busy
-            // Measured on this GPU (microseconds): a round of the matrix-core kernel (every wavefront of
-            // every compute unit with one unit of 64 tokens) takes about 8 + 0.0148 per column; the other
-            // kernel works through tiles of eight tokens at 1.3 million weights per microsecond with one
-            // workgroup resident per compute unit (long rows: the tile's activations fill the LDS) and
-            // about three times that with three or more.
-            const double rounds = std::ceil((double)blocks / di.cus);
-            const double t_mm = rounds * (8.0 + 0.0148 * W->cols);
-            const int resident = (int)std::max<size_t>(1, std::min<size_t>(3, (size_t)di.max_lds / xs_bytes(8)));
-            const double rate = 1.3e6 * resident;
-            const double t_rows = std::max(8.5, 4.0 + std::ceil(batch / 8.0) * (double)W->rows * W->cols / rate);
-            const bool take = tu.mfma_min_tokens > 0 ? batch >= tu.mfma_min_tokens : t_mm < t_rows;
-            if (take) {
-                a.minmax = W->minmax_bf16 ? 1 : 0;
-                a.epilogue = 0;
-                MmPlan mp;
-                mp.smem = mm_lds_bytes(n_order);
-                mp.grid = (int)std::min<long long>(units, di.cus);  // a unit per compute unit before a second per compute unit
-                return launch_product_mm(a, mp, s);
-            }
-        }
+    // Three kernels: 16 lanes per row with the table in L2 (the shortest start), several lanes per row with the table
+    // in LDS, and the matrix cores, which decode the matrix once per 64 tokens (their unit of work is 64 rows of a token
+    // tile, taken by one wavefront: a unit's time is set by the length of a row, not by how many units there are).  The
+    // one with the lowest estimate is taken; measured on this GPU, microseconds a call (back-to-back calls are bound by
+    // the launch rate, about 7.5):
+    //  - 16 lanes per row: tiles of eight tokens at 1.3 million weights per microsecond with one workgroup resident
+    //    per compute unit (long rows: the tile's activations fill the LDS), about three times that with three or more;
+    //  - several lanes per row: 8.8 (10.5 on the asymmetric grid) and 48 million weights times tokens per microsecond, from
+    //    768 x 3072 to 2080 x 6144 and from 8 to 500 tokens;
+    //  - matrix cores: a round (every wavefront of every compute unit with one unit of 64 tokens) about 8 + 0.0148 per column.
+    const Tuning &tu = tuning();
+    const int n_order = (int)d->order_table.size();
+    const double weights = (double)W->rows * W->cols;
+    const int resident = (int)std::max<size_t>(1, std::min<size_t>(3, (size_t)di.max_lds / xs_bytes(8)));
+    const double t_matvec = std::max(7.5, 4.0 + std::ceil(batch / 8.0) * weights / (1.3e6 * resident));
+    double t_rows = 1e30, t_mm = 1e30;
+    int slots = 0;
+    if (code_order == 1 && run && n_order > 0 && tu.rows >= 0 && tu.token_tile == 0) {
+        slots = rows_tile_slots(W->cols, 4, n_order, di.max_lds);
+        if (slots) t_rows = tu.rows > 0 ? 0.0 : (W->minmax_bf16 ? 10.5 : 8.8) + weights * batch / 48e6;
+    }
+    const int tiles = (batch + kMmTokens - 1) / kMmTokens, waves = kMmThreads / 64;
+    const long long units = (long long)tiles * ((W->rows + 63) / 64);
+    if (code_order == 1 && run && n_order > 0 && tu.mfma_min_tokens >= 0 && W->cols % 8 == 0 &&
+        reinterpret_cast<uintptr_t>(x_bf16) % 16 == 0 && mm_lds_bytes(n_order) <= (size_t)di.max_lds) {
+        const long long blocks = (units + waves - 1) / waves;  // workgroups with every wavefront busy
+        t_mm = std::ceil((double)blocks / di.cus) * (8.0 + 0.0148 * W->cols);
+        if (tu.mfma_min_tokens > 0) t_mm = batch >= tu.mfma_min_tokens ? -1.0 : 1e30;
+    }
+    if (t_mm < std::min(t_rows, t_matvec)) {
+        a.minmax = W->minmax_bf16 ? 1 : 0;
+        a.epilogue = 0;
+        MmPlan mp;
+        mp.smem = mm_lds_bytes(n_order);
+        mp.grid = (int)std::min<long long>(units, di.cus);  // a unit per compute unit before a second per compute unit
+        return launch_product_mm(a, mp, s);
+    }
+    if (t_rows < t_matvec) {
+        a.tb_max = batch > 2 ? 4 : batch;
+        a.minmax = W->minmax_bf16 ? 1 : 0;
+        a.epilogue = 0;
+        return launch_rows(a, slots, nullptr, 0, 0, std::min(di.cus, kRowsMaxGrid), di.max_lds, s);
     }
     const int threads = 256;  // 16 rows at a time
     const long long items = (long long)((batch + tb - 1) / tb) * ((W->rows + threads / 16 - 1) / (threads / 16));
@@ -612,6 +653,7 @@ qmoe_status qmoe_moe_layer_ws_layout(int n_experts, int d_model, int d_ff, int n
     out->items_wo = off; off = align_up(off + sizeof(Item) * (size_t)n_tokens, 256);
     out->items_mm = off; off = align_up(off + sizeof(Item) * (size_t)n_tokens, 256);
     out->hidden = off;   off = align_up(off + sizeof(uint16_t) * (size_t)n_tokens * (size_t)d_ff, 256);
+    off += kShareRecords;  // (behind the parts that callers look at: see layer_ptrs)
     out->total = off;
     return QMOE_OK;
 }
@@ -650,8 +692,8 @@ qmoe_status qmoe_moe_dispatch(const qmoe_dict *d, int code_order, const int32_t 
                            (d_model % 8 == 0 && tuning().stage_out >= 0) ? 4 : 0, minmax, lanes_wo)) != QMOE_OK)
         return st;
     if ((st = plan_mm(d, code_order, d_model, d_ff, n_tokens, true, &mp)) != QMOE_OK) return st;
-    return launch_dispatch(expert_idx, n_tokens, n_experts, d_model, layer_ptrs(workspace, l), pwi.tb_max,
-                           pwo.tb_max, mp.min_tokens, nullptr, static_cast<hipStream_t>(stream));
+    return launch_dispatch_kernel(dispatch_args(expert_idx, n_tokens, n_experts, d_model, layer_ptrs(workspace, l), pwi.tb_max,
+                                                pwo.tb_max, mp.min_tokens, nullptr), static_cast<hipStream_t>(stream));
 }
 
 namespace {
@@ -693,10 +735,13 @@ qmoe_status layer_forward(const qmoe_dict *d, const qmoe_matrix *wi, const qmoe_
     hipStream_t s = static_cast<hipStream_t>(stream);
     const LayerPtrs lp = layer_ptrs(workspace, l);
     const int phases = tuning().phases > 0 ? tuning().phases : 31;
-    if (phases & 1)
-        if ((st = launch_dispatch(expert_idx, n_tokens, n_experts, d_model, lp, pwi.tb_max, pwo.tb_max,
-                                  mp.min_tokens, y, s)) != QMOE_OK)
-            return st;
+    RowsPlan rp;
+    if (pwi.tb_max == pwo.tb_max) rp = rows_plan(d, code_order, lanes_wi, d_model, d_ff, n_tokens, pwi.tb_max);
+    // In a small call the kernel with several lanes per row groups the tokens itself.
+    const bool grouping = rp.on && !mm && rows_can_dispatch(n_experts, n_tokens, rp.grid);
+    const DispatchArgs da = dispatch_args(expert_idx, n_tokens, n_experts, d_model, lp, pwi.tb_max, pwo.tb_max, mp.min_tokens, y);
+    if ((phases & 1) && !grouping)
+        if ((st = launch_dispatch_kernel(da, s)) != QMOE_OK) return st;
 
     // The experts with few tokens and the crowded ones are two independent chains of two
     // kernels (each second product reads only the hidden rows its own first product wrote).
@@ -782,8 +827,11 @@ qmoe_status layer_forward(const qmoe_dict *d, const qmoe_matrix *wi, const qmoe_
     a1.lds_dict_entries = pwi.lds_dict_entries;
     a1.stage_out = pwi.stage_out;
     a1.work_counter = lp.counters + 5;
+    a1.class_counts = a2.class_counts = lp.counters + 10;
+    a1.shares = a2.shares = grouping ? lp.shares : nullptr;
     if (phases & 2)
-        if ((st = launch_product(a1, pwi, run, s_sc)) != QMOE_OK) return st;
+        if ((st = rp.on ? launch_rows(a1, rp.slots_wi, grouping ? &da : nullptr, d_model, rp.slots_wo, rp.grid, rp.max_lds, s_sc)
+                        : launch_product(a1, pwi, run, s_sc)) != QMOE_OK) return st;
     a2.items = lp.items_wo;
     a2.n_items_dev = lp.counters + 4;
     a2.rows_per_item = pwo.rows_per_item;
@@ -793,7 +841,8 @@ qmoe_status layer_forward(const qmoe_dict *d, const qmoe_matrix *wi, const qmoe_
     a2.stage_out = pwo.stage_out && reinterpret_cast<uintptr_t>(y) % 16 == 0;
     a2.work_counter = lp.counters + 6;
     if (phases & 4)
-        if ((st = launch_product(a2, pwo, run, s_sc)) != QMOE_OK) return st;
+        if ((st = rp.on ? launch_rows(a2, rp.slots_wo, nullptr, 0, 0, rp.grid, rp.max_lds, s_sc) : launch_product(a2, pwo, run, s_sc)) != QMOE_OK)
+            return st;
     if (overlap) {
         QMOE_HIP_TRY(hipEventRecord(ss.join, ss.stream));
         QMOE_HIP_TRY(hipStreamWaitEvent(s, ss.join, 0));
@@ -823,6 +872,12 @@ int qmoe_plan_lanes(const qmoe_dict *d, int rows, int cols, int n_experts, int n
     return p.threads * p.blocks_per_pass;
 }
 
+int qmoe_plan_row_layout(const qmoe_dict *d, int d_model, int d_ff, int n_experts, int n_tokens)
+{
+    if (!d || layer_limits(n_experts, d_model, d_ff, n_tokens) != QMOE_OK) return 0;
+    return rows_plan(d, 1, 0, d_model, d_ff, n_tokens, 4).on ? 1 : 0;
+}
+
 size_t qmoe_static_workspace_bytes(void) { return kStaticWsBytes; }
 
 qmoe_status qmoe_moe_layer_forward_static(const qmoe_dict *d, const qmoe_matrix *wi, const qmoe_matrix *wo,
@@ -835,13 +890,13 @@ qmoe_status qmoe_moe_layer_forward_static(const qmoe_dict *d, const qmoe_matrix 
     if (st != QMOE_OK) return st;
     if (!d || !wi || !wo || !x_bf16 || !expert_idx || !y) return QMOE_E_INVALID_ARG;
     if (!d->dev) return QMOE_E_NO_DEVICE_DICT;
-    if (l.total > kStaticWsBytes) return QMOE_E_LIMIT;
+    if (l.total > kStaticWsBytes + kShareRecords) return QMOE_E_LIMIT;
     void *ws = nullptr;
     const qmoe_status wst = static_workspace(&ws);
     if (wst != QMOE_OK) return wst;
     // one stream, no events: nothing here creates a stream, an event or memory
     return layer_forward(d, wi, wo, code_order, n_experts, d_model, d_ff, x_bf16, expert_idx, gate, n_tokens, y, ws,
-                         kStaticWsBytes, stream, 0, nullptr);
+                         kStaticWsBytes + kShareRecords, stream, 0, nullptr);
 }
 
 qmoe_status qmoe_bf16_layer_forward(const uint16_t *const *wi_dense, const uint16_t *const *wo_dense,
@@ -863,8 +918,8 @@ qmoe_status qmoe_bf16_layer_forward(const uint16_t *const *wi_dense, const uint1
     const LayerPtrs lp = layer_ptrs(workspace, l);
     const int phases = tuning().phases > 0 ? tuning().phases : 7;
     if (phases & 1)
-        if ((st = launch_dispatch(expert_idx, n_tokens, n_experts, d_model, lp, pwi.tb_max, pwo.tb_max,
-                                  0x7FFFFFFF, y, s)) != QMOE_OK)
+        if ((st = launch_dispatch_kernel(dispatch_args(expert_idx, n_tokens, n_experts, d_model, lp, pwi.tb_max, pwo.tb_max,
+                                                       0x7FFFFFFF, y), s)) != QMOE_OK)
             return st;
     DenseArgs a{};
     a.n_experts = n_experts;

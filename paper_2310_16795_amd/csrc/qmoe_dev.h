@@ -4,6 +4,7 @@
 // Section 4.3.3 of the paper defines what the kernels compute; the mapping onto gfx950
 // (CDNA4, wave64) is this library's own and is described where each kernel is defined:
 //   qmoe_product.h / qmoe_product_*.hip  fused decode + product, a lane per row range
+//   qmoe_rows.hip                        the same with several lanes per row: few items, single matrices
 //   qmoe_product_mm.hip                  decode once, multiply on the matrix cores; decompression
 //   qmoe_matvec.hip                      one matrix, a few tokens: 16 lanes per row; decode-only hook
 //   qmoe_dispatch.hip                    tokens grouped by expert, work lists
@@ -73,6 +74,8 @@ struct ProductArgs {
     int tb_max;
     int lds_dict_entries;     // leading run entries copied to LDS (0 = none)
     int stage_out;            // first product: results of a block staged in LDS and written as whole lines (LDS after the table)
+    int *shares;              // k_rows: a record per workgroup, written by the first product for the second, or nullptr
+    const int *class_counts;  // items with more than four tokens, three or four, two, one (the list's order), or nullptr
     int *work_counter;        // device counter (zeroed by the dispatch kernel) for handing out items, or nullptr
     const uint32_t *order_table;  // device-order table (n_order entries, the first n_groups are groups)
     int n_groups, n_order;
@@ -148,6 +151,8 @@ struct MmPlan {
 
 // matrix-core kernel: shape constants the planner needs
 constexpr int kProductMaxThreads = 768;  // largest workgroup of k_product
+constexpr int kRowsMaxGrid = 512;        // workgroups of k_rows that a workspace has share records for
+constexpr size_t kRowsShareBytes = 64;   // a record
 constexpr int kMmThreads = 512;
 constexpr int kMmTokens = 64;                  // tokens per tile
 constexpr int kMmMinTokensDefault = 8;         // experts with fewer tokens stay on the scalar kernel
@@ -170,6 +175,11 @@ qmoe_status launch_decompress(const DecompressArgs &a, int out_kind, bool minmax
 size_t decompress_lds_bytes(int n_order, int n_mats);  // table, rings, windows, one bit per matrix
 qmoe_status launch_matvec_rows(const ProductArgs &a, bool run, bool minmax, int grid, int threads, size_t smem,
                                hipStream_t s);                                                      // qmoe_matvec.hip
+int rows_tile_slots(int cols, int tb, int n_order, int max_lds);                                     // qmoe_rows.hip
+bool rows_can_dispatch(int n_experts, int n_tokens, int grid);
+// da: the launch groups the tokens itself and leaves records for the second product (rows2, x_slots2)
+qmoe_status launch_rows(const ProductArgs &a, int x_slots, const DispatchArgs *da, int rows2, int x_slots2, int grid, int max_lds,
+                        hipStream_t s);
 qmoe_status launch_decode_dense(const ProductArgs &a, bool run, int8_t *out, int grid, hipStream_t s);
 qmoe_status launch_dispatch_kernel(const DispatchArgs &da, hipStream_t s);                          // qmoe_dispatch.hip
 qmoe_status launch_dense_bf16(const DenseArgs &a, const ProductPlan &p, hipStream_t s);             // qmoe_misc.hip
@@ -204,6 +214,58 @@ __device__ __forceinline__ float row_sum16_to_last(float v)
     v += __int_as_float(dpp0<kRowShr1>(__float_as_int(v)));
     return v;
 }
+
+// Inclusive prefix sum over the 64 lanes of a wavefront with data-parallel-primitive adds (no trip
+// through the LDS crossbar): the row scan, then lane 15 of a row added to the whole next row, then
+// lane 31 to the upper half.
+template <int CTRL, int ROW_MASK = 0xf>
+__device__ __forceinline__ int dpp_add(int x)
+{
+    return x + __builtin_amdgcn_update_dpp(0, x, CTRL, ROW_MASK, 0xf, false);  // lanes without a source add 0
+}
+__device__ __forceinline__ int wave_inclusive_scan(int x)
+{
+    x = row_scan16(x);
+    x = dpp_add<0x142, 0xa>(x);  // row_bcast:15 into rows 1 and 3
+    x = dpp_add<0x143, 0xc>(x);  // row_bcast:31 into rows 2 and 3
+    return x;
+}
+
+// Exclusive prefix sums of N ints per thread over the workgroup (up to 16 wavefronts), all at
+// once (three barriers).  `tmp` holds >= 17 * N ints: [value][wavefront], then the N totals.
+template <int N>
+__device__ __forceinline__ void block_exclusive_scan_n(const int (&v)[N], int *tmp, int (&excl)[N], int (&total)[N])
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwaves = (blockDim.x + 63) >> 6;
+    int incl[N];
+#pragma unroll
+    for (int k = 0; k < N; k++) {
+        incl[k] = wave_inclusive_scan(v[k]);
+        if (lane == 63) tmp[k * 16 + wave] = incl[k];
+    }
+    __syncthreads();
+    if (wave == 0) {
+        // a row of 16 lanes per value: lane w of the row holds wavefront w's sum; four values a turn
+        for (int k0 = 0; k0 < N; k0 += 4) {
+            const int k = k0 + (lane >> 4), w = lane & 15;
+            const bool live = k < N && w < nwaves;
+            const int mine = live ? tmp[k * 16 + w] : 0;
+            const int run = row_scan16(mine);
+            if (live) tmp[k * 16 + w] = run - mine;
+            if (k < N && w == 15) tmp[16 * N + k] = run;  // wavefronts that do not exist added 0
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < N; k++) {
+        excl[k] = tmp[k * 16 + wave] + incl[k] - v[k];
+        total[k] = tmp[16 * N + k];
+    }
+    __syncthreads();
+}
+
+// classes of token tiles in the order the work lists hold them: more than four tokens, three or four, two, one
+__device__ __forceinline__ int tile_class(int n) { return n > 4 ? 0 : (n > 2 ? 1 : (n == 2 ? 2 : 3)); }
 
 __device__ __forceinline__ float bf16_bits_to_float(uint32_t b) { return __uint_as_float(b << 16); }
 
@@ -257,10 +319,11 @@ __device__ __forceinline__ void stage_words(uint32_t *dst_lds, const uint32_t *s
 // loads and stores one value at a time waits for every load in turn.
 //
 // One token: 8-byte records {0, +x, 0, -x} (with_neg) or {0, x, 0, 0}; columns cols ..
-// cols + kPadCols - 1, and everything when `live` is false, are zero records.
+// cols + PAD - 1, and everything when `live` is false, are zero records.
+template <int PAD = kPadCols>
 __device__ __forceinline__ void stage_x_one(uint16_t *xs_w, const uint16_t *xrow, int cols, bool live, bool with_neg)
 {
-    const int n = cols + kPadCols, step = (int)blockDim.x;
+    const int n = cols + PAD, step = (int)blockDim.x;
     gp_u16 x = (gp_u16)xrow;
     for (int c0 = (int)threadIdx.x; c0 < n; c0 += 8 * step) {
         uint32_t v[8];
@@ -280,11 +343,11 @@ __device__ __forceinline__ void stage_x_one(uint16_t *xs_w, const uint16_t *xrow
 
 // TBI tokens (2, 4, 8): bf16 [column][TBI]; token t of the tile is row x_rows[t] of x (tokens
 // from ntok on are zeros).  x_rows holds at least one valid row.
-template <int TBI, typename RowOf>
+template <int TBI, int PAD = kPadCols, typename RowOf>
 __device__ __forceinline__ void stage_x_tile(uint16_t *xs_w, const uint16_t *xbase, RowOf row_of, int ntok, int ldx,
                                              int cols)
 {
-    const int n = cols + kPadCols, step = (int)blockDim.x;
+    const int n = cols + PAD, step = (int)blockDim.x;
     gp_u16 x = (gp_u16)xbase;
     size_t off[TBI];
 #pragma unroll
@@ -557,6 +620,30 @@ __device__ __forceinline__ void accumulate(const Entry &e, uint32_t xs_addr, uin
                 }
             }
         }
+    }
+}
+
+// One token, activations as records {0, +x, 0, -x}: acc[0] += the three values an entry's fields selected (signs applied by
+// the place they were read from), by packed dot products against (1, 1): two values share a register, no widening.
+// ASYM: acc[1] takes the same inputs with their own sign: a value read from a -x slot has its sign bit flipped back (the
+// field's negative bit says which; three instructions more in place of three more reads of the LDS).
+template <int ASYM>
+__device__ __forceinline__ void add_one_token(const uint32_t *x, uint32_t e, float (&acc)[1 + ASYM])
+{
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    auto dot1 = [](uint32_t v, float c) -> float {
+        const uint32_t one2 = 0x3F803F80u;
+        bf16x2 a, ones;
+        __builtin_memcpy(&a, &v, 4);
+        __builtin_memcpy(&ones, &one2, 4);
+        return __builtin_amdgcn_fdot2_f32_bf16(a, ones, c, false);
+    };
+    const uint32_t pair = x[1] | (x[2] << 16);
+    acc[0] = dot1(x[0], dot1(pair, acc[0]));
+    if constexpr (ASYM) {
+        const uint32_t up = e << 5;  // bit 15: field 0 negative, bit 31: field 2 negative; field 1: bit 18 of e
+        const uint32_t pair_a = pair ^ ((up & 0x80000000u) | ((e >> 3) & 0x8000u));
+        acc[1] = dot1(x[0] ^ (up & 0x8000u), dot1(pair_a, acc[1]));
     }
 }
 

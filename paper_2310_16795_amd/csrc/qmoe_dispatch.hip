@@ -8,55 +8,6 @@ namespace {
 // ---------------------------------------------------------------- dispatch
 
 
-// Inclusive prefix sum over the 64 lanes of a wavefront with data-parallel-primitive adds (no trip
-// through the LDS crossbar): the row scan, then lane 15 of a row added to the whole next row, then
-// lane 31 to the upper half.
-template <int CTRL, int ROW_MASK = 0xf>
-__device__ __forceinline__ int dpp_add(int x)
-{
-    return x + __builtin_amdgcn_update_dpp(0, x, CTRL, ROW_MASK, 0xf, false);  // lanes without a source add 0
-}
-__device__ __forceinline__ int wave_inclusive_scan(int x)
-{
-    x = row_scan16(x);
-    x = dpp_add<0x142, 0xa>(x);  // row_bcast:15 into rows 1 and 3
-    x = dpp_add<0x143, 0xc>(x);  // row_bcast:31 into rows 2 and 3
-    return x;
-}
-
-// Exclusive prefix sums of N ints per thread over the workgroup (up to 16 wavefronts), all at
-// once (three barriers).  `tmp` holds >= 17 * N ints: [value][wavefront], then the N totals.
-template <int N>
-__device__ __forceinline__ void block_exclusive_scan_n(const int (&v)[N], int *tmp, int (&excl)[N], int (&total)[N])
-{
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwaves = (blockDim.x + 63) >> 6;
-    int incl[N];
-#pragma unroll
-    for (int k = 0; k < N; k++) {
-        incl[k] = wave_inclusive_scan(v[k]);
-        if (lane == 63) tmp[k * 16 + wave] = incl[k];
-    }
-    __syncthreads();
-    if (wave == 0) {
-        // a row of 16 lanes per value: lane w of the row holds wavefront w's sum; four values a turn
-        for (int k0 = 0; k0 < N; k0 += 4) {
-            const int k = k0 + (lane >> 4), w = lane & 15;
-            const bool live = k < N && w < nwaves;
-            const int mine = live ? tmp[k * 16 + w] : 0;
-            const int run = row_scan16(mine);
-            if (live) tmp[k * 16 + w] = run - mine;
-            if (k < N && w == 15) tmp[16 * N + k] = run;  // wavefronts that do not exist added 0
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < N; k++) {
-        excl[k] = tmp[k * 16 + wave] + incl[k] - v[k];
-        total[k] = tmp[16 * N + k];
-    }
-    __syncthreads();
-}
-
 // One workgroup of 1024 threads groups the tokens by expert (stable) and writes
 // the work lists of both products.
 __global__ __launch_bounds__(1024) void k_dispatch(const DispatchArgs a)
@@ -105,10 +56,8 @@ __global__ __launch_bounds__(1024) void k_dispatch(const DispatchArgs a)
     // each thread owns a contiguous chunk of experts
     const int chunk = (E + nthr - 1) / nthr;
     const int e0 = min(E, tid * chunk), e1 = min(E, e0 + chunk);
-    // Work items of the scalar products are listed longest first (tiles of more than four
-    // tokens, then of three or four, of two, of one): handed out in that order, the last
-    // workgroups to finish are busy with short items.
-    auto tile_class = [](int n) { return n > 4 ? 0 : (n > 2 ? 1 : (n == 2 ? 2 : 3)); };
+    // Work items of the scalar products are listed longest first (by tile_class): handed out in that
+    // order, the last workgroups to finish are busy with short items.
     int s_tok = 0, s_act = 0, s_mm = 0;
     int s_wi[4] = {0, 0, 0, 0}, s_wo[4] = {0, 0, 0, 0};
     for (int e = e0; e < e1; e++) {
@@ -168,7 +117,8 @@ __global__ __launch_bounds__(1024) void k_dispatch(const DispatchArgs a)
         a.counters[5] = 0; a.counters[6] = 0;  // work hand-out of the two scalar products
         a.counters[7] = tot_mm;
         a.counters[8] = 0; a.counters[9] = 0;  // work hand-out of the two matrix-core products
-        for (int i = 10; i < kLayerCounters; i++) a.counters[i] = 0;
+        for (int k = 0; k < 4; k++) a.counters[10 + k] = all[4 + k];  // items_wi by class
+        a.counters[14] = 0; a.counters[15] = 0;
     }
     __syncthreads();
 

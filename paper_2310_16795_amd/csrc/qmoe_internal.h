@@ -91,6 +91,7 @@ struct Tuning {
     int host_threads = 0;
     int blocks_first = 0;   // forced blocks per matrix pass, first / single product
     int blocks_second = 0;  // same, second product of a layer
+    int rows = 0;       // several lanes per row in layer calls: 1 = always, -1 = never, 0 = the planner's choice
     int stage_out = 0;  // -1 = the first product writes its hidden values straight to global memory
     int overlap = 0;  // -1 = all kernels of a layer on the caller's stream, one after the other
     int mfma_min_tokens = 0;  // 0 = heuristic, -1 = never use the matrix-core kernel

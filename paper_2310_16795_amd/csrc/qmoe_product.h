@@ -171,43 +171,19 @@ __device__ __forceinline__ void consume8(const ProductArgs &a, LaneState<TBI, AS
     st.pos8 = p;
     float part[8][NA];  // the sums after each of the eight
     if constexpr (TBI == 1) {
-        // the three bf16 values of a codeword are added with two packed dot products
-        // against (1, 1): two of them share a register, no widening shifts
         uint32_t x[24];
-        uint32_t xa[ASYM ? 24 : 1];  // asymmetric grid: the same inputs with their own sign (+x of each record)
 #pragma unroll
         for (int j = 0; j < 8; j++) {
             const uint32_t rec = pos[j];  // the activations begin at LDS address 0 (the caller checks)
 #pragma unroll
-            for (int z = 0; z < 3; z++) {
-                const uint32_t addr = rec + ((e[j].e0 >> (8 + 8 * z)) & 0xFFu);
-                x[3 * j + z] = (uint32_t)(*(lp_u16)(uintptr_t)addr);
-                // the -x slot is 4 bytes after the +x slot; an unused field stays on the zero slot
-                if constexpr (ASYM) xa[3 * j + z] = (uint32_t)(*(lp_u16)(uintptr_t)(addr & ~4u));
-            }
+            for (int z = 0; z < 3; z++)
+                x[3 * j + z] = (uint32_t)(*(lp_u16)(uintptr_t)(rec + ((e[j].e0 >> (8 + 8 * z)) & 0xFFu)));
         }
-        typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-        const uint32_t one2 = 0x3F803F80u;
-        bf16x2 ones;
-        __builtin_memcpy(&ones, &one2, 4);
 #pragma unroll
         for (int j = 0; j < 8; j++) {
-            const uint32_t pair = x[3 * j] | (x[3 * j + 1] << 16);
-            bf16x2 p2, p1;
-            __builtin_memcpy(&p2, &pair, 4);
-            __builtin_memcpy(&p1, &x[3 * j + 2], 4);
-            st.acc[0] = __builtin_amdgcn_fdot2_f32_bf16(p2, ones, st.acc[0], false);
-            st.acc[0] = __builtin_amdgcn_fdot2_f32_bf16(p1, ones, st.acc[0], false);
-            part[j][0] = st.acc[0];
-            if constexpr (ASYM) {
-                const uint32_t pair_a = xa[3 * j] | (xa[3 * j + 1] << 16);
-                bf16x2 a2, a1;
-                __builtin_memcpy(&a2, &pair_a, 4);
-                __builtin_memcpy(&a1, &xa[3 * j + 2], 4);
-                st.acc[NA - 1] = __builtin_amdgcn_fdot2_f32_bf16(a2, ones, st.acc[NA - 1], false);
-                st.acc[NA - 1] = __builtin_amdgcn_fdot2_f32_bf16(a1, ones, st.acc[NA - 1], false);
-                part[j][NA - 1] = st.acc[NA - 1];
-            }
+            add_one_token<ASYM>(x + 3 * j, e[j].e0, st.acc);
+#pragma unroll
+            for (int t = 0; t < NA; t++) part[j][t] = st.acc[t];
         }
     } else {
 #pragma unroll

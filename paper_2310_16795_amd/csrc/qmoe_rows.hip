@@ -1,0 +1,757 @@
+// Fused decode + product with the rows of a matrix shared by several lanes each: the form for
+// calls whose items are too few, or whose rows are too long, to give every lane rows of its own
+// (qmoe_product.h), and for single matrices.
+#include "qmoe_dev.h"
+
+namespace qmoe {
+namespace {
+
+// ---------------------------------------------------------------- a row per L lanes
+//
+// L lanes (1 .. 64, a power of two) share a matrix row.  Each takes a whole 16-byte piece of the row's codewords
+// (eight) at a time, looks the eight entries up, adds their run lengths, and finds the column where its piece
+// starts from a prefix sum over the row's lanes (data-parallel-primitive adds) -- one scan for eight codewords.  Then
+// it applies its entries as the lane-per-row-range kernel does, without that kernel's bookkeeping for rows that end
+// inside a piece, and the lanes' sums are added at the end of the row.
+//
+// The work of a launch -- every row of every item, weighted by what a row of a tile of that many tokens
+// costs -- is cut into one contiguous share per workgroup, on the device, where the number of items is known: no
+// hand-out, no last round that is nearly empty, and one or two tiles of activations to stage per workgroup.  L is
+// chosen there too: as few lanes as keep the sixteen wavefronts of a workgroup at work.
+constexpr int kRowsThreads = 1024;
+constexpr int kRowsPadCols = 8 * 28 + 4;  // zeros behind the activations: a piece that starts past the row's end (corrupt
+                                          // stream) reads at most this far
+
+
+// Workgroup barrier for LDS traffic only: loads from global memory stay in flight across it (__syncthreads waits for them).
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// inclusive prefix sum over the L lanes of a row (lane `sub` of it); L is the same in every lane
+template <typename T>
+__device__ __forceinline__ T lanes_scan(T v, int L, int sub)
+{
+    auto add = [&](auto ctrl, auto row_mask, bool take) {
+        int bits;
+        __builtin_memcpy(&bits, &v, 4);
+        bits = __builtin_amdgcn_update_dpp(0, bits, decltype(ctrl)::value, decltype(row_mask)::value, 0xf, false);
+        bits = take ? bits : 0;  // (all zero bits: 0 as an integer and as a float)
+        T w;
+        __builtin_memcpy(&w, &bits, 4);
+        v += w;
+    };
+    using std::integral_constant;
+    using full = integral_constant<int, 0xf>;
+    if (L > 1) add(integral_constant<int, kRowShr1>{}, full{}, sub >= 1);
+    if (L > 2) add(integral_constant<int, kRowShr2>{}, full{}, sub >= 2);
+    if (L > 4) add(integral_constant<int, kRowShr4>{}, full{}, sub >= 4);
+    if (L > 8) add(integral_constant<int, kRowShr8>{}, full{}, sub >= 8);
+    if (L > 16) add(integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{}, true);  // row_bcast:15 into rows 1 and 3
+    if (L > 32) add(integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{}, true);  // row_bcast:31 into rows 2 and 3
+    return v;
+}
+
+typedef u32x4 u32x4_any __attribute__((aligned(2)));
+using gp_u32x4_any = const __attribute__((address_space(1))) u32x4_any *;
+
+// How the rows of a launch are cut into shares: made by the host.
+struct RowsSplit {
+    int rows, x_slots;   // rows of a matrix; token tiles whose activations fit the LDS at once (1 or 2)
+    double inv_item[4];  // 1 / (cost of a whole item of class k)
+    double inv_grid;
+};
+
+struct RowsTile {
+    int ntok, slot0;
+    const __attribute__((address_space(3))) int *tok_ids;
+    const __attribute__((address_space(3))) float *gate_s;
+};
+
+// What a lane needs to begin a group of 64 / L rows: three dependent trips to memory (descriptor, offsets, first piece), asked
+// for before the activations are staged for a wavefront's first group, and during the group before for the others.
+struct GroupHead {
+    uint32_t K0, K1, raw;  // the row's first codeword, the next row's, scale (or grid pair) as stored
+    u32x4 v;               // the lane's first piece
+};
+
+template <int ASYM>
+__device__ __forceinline__ void head_offsets(const qmoe_matrix &M, int r1, int row, GroupHead &h)
+{
+    const int rr = min(row, r1 - 1);
+    gp_u32 row_off = (gp_u32)M.row_off;
+    h.K0 = row_off[rr];
+    h.K1 = row_off[rr + 1];
+    if constexpr (ASYM) h.raw = M.minmax_bf16 ? ((gp_u32)M.minmax_bf16)[rr] : 0u;  // no pair array: decodes to zeros
+    else h.raw = ((gp_u16)M.scale_f16)[rr];
+}
+
+// Piece q holds codewords 8 q .. 8 q + 7 of a row of n codewords that begins at codeword K0.  Rows begin anywhere in the
+// stream, so a piece's address is a multiple of 2 only; a piece that would reach past the stream's last 16-byte boundary is
+// read that much earlier and its first slots are somebody else's.
+struct RowPieces {
+    uint32_t K0, k_last;
+    int n;
+    uintptr_t codes;
+    __device__ __forceinline__ RowPieces(const qmoe_matrix &M, const GroupHead &h, bool live)
+    {
+        const uint32_t cap = min(M.n_codes, kMaxCodes), end = min(h.K1, cap);
+        K0 = min(h.K0, end);
+        n = live ? (int)(end - K0) : 0;
+        k_last = max((cap + 7u) & ~7u, 8u) - 8u;
+        codes = reinterpret_cast<uintptr_t>(M.codes);
+    }
+    __device__ __forceinline__ uint32_t slot0(int q) const { return K0 + 8u * (uint32_t)min(q, max((n - 1) >> 3, 0)); }
+    __device__ __forceinline__ u32x4 load(int q) const { return *(gp_u32x4_any)(codes + 2u * (uintptr_t)min(slot0(q), k_last)); }
+};
+
+// Rows r0 .. r1 of M for a tile whose activations are staged at LDS address xs_addr: the groups of 64 / L rows numbered
+// `group`, `group` + wavefronts of the workgroup, ...  `head`: of group `group`, if `have`.
+template <int TBI, int EPI, int ASYM>
+__device__ __forceinline__ void rows_block(const ProductArgs &a, const qmoe_matrix &M, int r0, int r1, int group, int log2L,
+                                           uint32_t xs_addr, const RowsTile &tile, lp_u32 table, GroupHead head, bool have)
+{
+    constexpr int NA = TBI * (1 + ASYM);
+    const int lane = threadIdx.x & 63, waves = (int)blockDim.x >> 6, L = 1 << log2L;
+    const int sub = lane & (L - 1), mine = lane >> log2L, R = 64 >> log2L;
+    const uint32_t n_groups3 = 3u * (uint32_t)a.n_groups, last = (uint32_t)a.n_order - 1u, cols8 = 8u * (uint32_t)a.cols;
+    for (int rg = r0 + group * R; rg < r1; rg += waves * R) {
+        const int row = rg + mine;
+        const bool live = row < r1;
+        if (!have) {
+            head_offsets<ASYM>(M, r1, row, head);
+            head.v = RowPieces(M, head, live).load(sub);
+        }
+        const RowPieces rp(M, head, live);
+        const int n = rp.n;
+        const uint32_t raw = head.raw;
+        u32x4 v = head.v;
+        head_offsets<ASYM>(M, r1, row + waves * R, head);
+        have = true;
+        float acc[NA];
+#pragma unroll
+        for (int t = 0; t < NA; t++) acc[t] = 0.0f;
+        uint32_t base8 = 0u;  // 8 * column where the row's pieces of this step begin
+        for (int q = sub; __any(8 * q < n); q += L) {
+            const u32x4 v_next = rp.load(q + L);
+            uint32_t e[8];
+#pragma unroll
+            for (int j = 0; j < 4; j++) order_entry2(table, v[j], n_groups3, last, e[2 * j], e[2 * j + 1]);
+            // slots that are not the row's codewords become empty entries
+            const uint32_t at = rp.slot0(q);
+            const int from = (int)(at - min(at, rp.k_last)), to = from + n - 8 * q;  // the row's slots of this piece
+            if (!__all(from == 0 && to >= 8)) {
+                const uint32_t keep = (0xFFu << from) & (to <= 0 ? 0u : (1u << min(to, 8)) - 1u);
+#pragma unroll
+                for (int j = 0; j < 8; j++) e[j] &= (uint32_t)__builtin_amdgcn_sbfe((int)keep, j, 1);
+            }
+            uint32_t len8 = 0u;
+#pragma unroll
+            for (int j = 0; j < 8; j++) len8 += e[j] & 0xFFu;
+            const uint32_t incl = lanes_scan(len8, L, sub);
+            uint32_t pos = (TBI == 1 ? xs_addr : 0u) + min(base8 + incl - len8, cols8);
+            base8 += (uint32_t)__shfl((int)incl, lane | (L - 1), 64);
+            if constexpr (TBI == 1) {
+                uint32_t x[24];
+#pragma unroll
+                for (int j = 0; j < 8; j++) {
+#pragma unroll
+                    for (int z = 0; z < 3; z++) x[3 * j + z] = (uint32_t)(*(lp_u16)(uintptr_t)(pos + ((e[j] >> (8 + 8 * z)) & 0xFFu)));
+                    pos += e[j] & 0xFFu;
+                }
+#pragma unroll
+                for (int j = 0; j < 8; j++) add_one_token<ASYM>(x + 3 * j, e[j], acc);
+            } else {
+#pragma unroll
+                for (int j = 0; j < 8; j++) {
+                    accumulate_tile<TBI, ASYM>(e[j], xs_addr, pos, acc);  // sums doubled
+                    pos += e[j] & 0xFFu;
+                }
+            }
+            v = v_next;
+        }
+        head.v = RowPieces(M, head, row + waves * R < r1).load(sub);
+#pragma unroll
+        for (int t = 0; t < NA; t++) acc[t] = lanes_scan(acc[t], L, sub);
+        if (live && sub == L - 1) {
+            float scale, mid = 0.0f;  // y = scale * (signed sum) + mid * (sum under |weight|)
+            if constexpr (ASYM) {
+                const float w_min = __uint_as_float(raw << 16), w_max = __uint_as_float(raw & 0xFFFF0000u);
+                scale = 0.5f * (w_max - w_min);
+                mid = 0.5f * (w_max + w_min);
+            } else {
+                scale = half_bits_to_float((uint16_t)raw);
+            }
+            if constexpr (TBI != 1) {
+                scale *= 0.5f;
+                mid *= 0.5f;
+            }
+#pragma unroll
+            for (int t = 0; t < TBI; t++) {
+                if (t < tile.ntok) {
+                    float y = acc[t] * scale;
+                    if constexpr (ASYM) y = fmaf(acc[NA - TBI + t], mid, y);
+                    if constexpr (EPI == 0)
+                        ((__attribute__((address_space(1))) float *)a.out)[(size_t)tile.tok_ids[t] * a.ld_out + row] = tile.gate_s[t] * y;
+                    else
+                        ((__attribute__((address_space(1))) uint16_t *)a.out)[(size_t)(tile.slot0 + t) * a.ld_out + row] =
+                            float_to_bf16_bits(y > 0.0f ? y : 0.0f);
+                }
+            }
+        }
+    }
+}
+
+// What a row of a tile costs by the tile's class (more than four tokens, three or four, two, one): nanoseconds per row
+// of 1024 columns and workgroup, measured 17.3, 12.5 and 9.8 for the last three.
+constexpr int kRowCost[4] = {56, 31, 22, 17};
+
+// A workgroup's share of a launch: from row r0 of item i0 to row r1 of item i1.
+struct RowsShare {
+    int i0, r0, i1, r1;
+};
+
+// Share `b` of `n` of all rows of the items, cls[k] of them of class k.  (Double precision in place of 64-bit integer
+// divisions, each of which is a hundred instructions: a place is the same function of its cost for the share that
+// ends there and the one that begins there, so rounding moves a boundary by a few rows at most and loses none.)
+__device__ __forceinline__ RowsShare rows_share(const int (&cls)[4], const RowsSplit &sp, int n, int b)
+{
+    const int n_items = cls[0] + cls[1] + cls[2] + cls[3], rows = sp.rows, eights = (rows + 7) >> 3;
+    RowsShare s{0, 0, -1, 0};
+    if (n_items < 1) return s;
+    double total = 0.0;  // in costs of eight rows
+#pragma unroll
+    for (int k = 0; k < 4; k++) total += (double)cls[k] * (double)(kRowCost[k] * eights);
+    // With fewer items than workgroups every workgroup can have a part of one item: a tile of class k is cut into
+    // ceil(cost[k] / t) parts, t the smallest cost of a part for which the parts of all items fit the grid.
+    int g = 0, parts[4] = {0, 0, 0, 0}, used = 0, top_cost = 1;
+    if (n_items <= n) {
+        int top = 1;  // how many there are of the costliest class present
+#pragma unroll
+        for (int k = 3; k >= 0; k--) {
+            top_cost = cls[k] ? kRowCost[k] : top_cost;
+            top = cls[k] ? cls[k] : top;
+        }
+        const float inv_cost = 1.0f / (float)top_cost;
+        // (an even split of the cost would give it this many; rounding up needs fewer, rarely by more than a few)
+        g = min((int)((float)n / (float)top), (int)((float)(top_cost * eights) * (float)n / (float)total) + 1);
+        for (; g >= 1; g--) {
+            used = 0;
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                parts[k] = (int)ceilf((float)(kRowCost[k] * g) * inv_cost - 1e-3f);
+                used += parts[k] * cls[k];
+            }
+            if (used <= n) break;
+        }
+    }
+    // That is uneven when there are nearly as many items as workgroups; equal shares of the whole list begin and
+    // end inside items, so most workgroups have two items to stage and work on -- side by side if the activations of
+    // both fit the LDS (then a few per cent are worth it), one after the other otherwise, each with too few rows for
+    // all wavefronts.
+    if (g >= 1 && (float)(top_cost * eights) * (float)n <= (sp.x_slots > 1 ? 1.08f : 1.25f) * (float)total * (float)g) {
+        if (b >= used) return s;
+        int item = 0, p = 1, at = -1, left = b;
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            const int here = cls[k] * parts[k];
+            if (at < 0) {
+                if (left < here) {
+                    p = parts[k];
+                    const int whole = (int)(((float)left + 0.5f) / (float)p);
+                    item += whole;
+                    at = left - whole * p;
+                } else {
+                    left -= here;
+                    item += cls[k];
+                }
+            }
+        }
+        const float step = (float)eights / (float)p;
+        s.i0 = s.i1 = item;
+        s.r0 = 8 * (int)((float)at * step);
+        s.r1 = at + 1 == p ? rows : 8 * (int)((float)(at + 1) * step);
+    } else {
+        // the place in the list where the first `c` units of cost end; rows in eights
+        auto place = [&](double c, int &item, int &row) {
+            item = 0;
+            row = 0;
+            bool found = false;
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                const double per = (double)(kRowCost[k] * eights), here = (double)cls[k] * per;
+                if (!found) {
+                    if (c < here) {
+                        const int i = min((int)(c * sp.inv_item[k]), cls[k] - 1);
+                        const double in_item = c - (double)i * per;
+                        item += i;
+                        row = 8 * max(0, min((int)((float)in_item * (1.0f / (float)kRowCost[k])), eights));
+                        found = true;
+                    } else {
+                        c -= here;
+                        item += cls[k];
+                    }
+                }
+            }
+        };
+        place(floor(total * sp.inv_grid * (double)b), s.i0, s.r0);
+        if (b + 1 == n) {
+            s.i1 = n_items - 1;
+            s.r1 = rows;
+        } else {
+            place(floor(total * sp.inv_grid * (double)(b + 1)), s.i1, s.r1);
+            s.r1 = min(s.r1, rows);
+        }
+        if (s.i0 >= n_items) s.i1 = -1;
+    }
+    return s;
+}
+
+// The items of a share, in LDS: what a wavefront needs to know of each is read where it is needed (kept in registers for
+// several items, it is more than the scalar registers hold).
+constexpr int kKeptSegments = 6;  // items of a share looked at together
+struct RowsSegment {
+    int expert, slot0, ntok, ra, rb;  // rows ra .. rb of the item
+    int tok[kMaxTokenTile];           // its tokens
+};
+using lp_segment = const __attribute__((address_space(3))) RowsSegment *;
+
+// A record of a workgroup's share for the second product, written by the same workgroup of the first: the share, and
+// {expert, slot0 | tokens << 16} of the items it begins with.
+static_assert(kRowsShareBytes == 4 * (4 + 2 * kKeptSegments), "record size");
+constexpr int kShareInts = 4 + 2 * kKeptSegments;
+
+// ---- grouping the tokens by expert inside the first product
+//
+// In a small call (rows_can_dispatch) the grouping is a few thousand operations, less than the launch of a kernel for it and
+// the trips to memory for its results: every workgroup does it for itself, in LDS.  A bit per token and expert gives a
+// token's rank among its expert's tokens and the expert's count; experts in order give slots and items (longest class
+// first), the same lists k_dispatch writes.
+constexpr int kInlineTokens = 512;
+constexpr size_t kInlineMaskBytes = 64 * 1024;
+
+struct InlineLists {
+    int cls[4];
+    lp_u32 items;              // [n] {expert, slot0 | ntok << 16}
+    const __attribute__((address_space(3))) int *perm;  // [T]
+};
+
+__device__ __forceinline__ size_t inline_mask_words(int E, int T) { return (size_t)E * ((T + 31) >> 5); }
+
+// `scratch`: LDS of inline_lds_bytes(E, T); `e` the expert of token threadIdx.x (-1: none).  Workgroup 0 also writes the lists
+// to the workspace and clears the output rows of tokens without an expert.
+__device__ __forceinline__ InlineLists group_tokens(const DispatchArgs &d, int e, unsigned char *scratch)
+{
+    const int T = d.n_tokens, E = d.n_experts, tid = threadIdx.x, nthr = blockDim.x;
+    const int mw = (T + 31) >> 5;
+    uint32_t *mask = reinterpret_cast<uint32_t *>(scratch);
+    int *off = reinterpret_cast<int *>(mask + inline_mask_words(E, T));  // [E] first slot
+    int *perm = off + E;                                                  // [T]
+    uint32_t *items = reinterpret_cast<uint32_t *>(perm + T);             // [2 T]
+    int *tmp = reinterpret_cast<int *>(items + 2 * T);                    // [17 * 3] scan scratch
+    for (int i = tid; i < E * mw; i += nthr) mask[i] = 0u;
+    __syncthreads();
+    if (e >= 0) atomicOr(&mask[e * mw + (tid >> 5)], 1u << (tid & 31));
+    __syncthreads();
+    const int chunk = (E + nthr - 1) / nthr, e0 = min(E, tid * chunk), e1 = min(E, e0 + chunk);
+    auto count = [&](int x) {
+        int n = 0;
+        for (int w = 0; w < mw; w++) n += __popc(mask[x * mw + w]);
+        return n;
+    };
+    int sums[3] = {0, 0, 0};  // two 16-bit counts each: tokens | class 0, class 1 | class 2, class 3 | experts with tokens
+    for (int x = e0; x < e1; x++) {
+        const int n = count(x);
+        if (n) {
+            const int whole = n / d.tb_wi, rest = n % d.tb_wi, kw = tile_class(d.tb_wi), kr = rest ? tile_class(rest) : -1;
+            auto of = [&](int k) { return (k == kw ? whole : 0) + (k == kr ? 1 : 0); };
+            sums[0] += n | of(0) << 16;
+            sums[1] += of(1) | of(2) << 16;
+            sums[2] += of(3) | 1 << 16;
+        }
+    }
+    int before[3], all[3];
+    block_exclusive_scan_n<3>(sums, tmp, before, all);
+    InlineLists r;
+    r.cls[0] = all[0] >> 16;
+    r.cls[1] = all[1] & 0xFFFF;
+    r.cls[2] = all[1] >> 16;
+    r.cls[3] = all[2] & 0xFFFF;
+    int slot = before[0] & 0xFFFF;
+    int at[4] = {before[0] >> 16, r.cls[0] + (before[1] & 0xFFFF), r.cls[0] + r.cls[1] + (before[1] >> 16),
+                 r.cls[0] + r.cls[1] + r.cls[2] + (before[2] & 0xFFFF)};
+    const bool record = blockIdx.x == 0;
+    for (int x = e0; x < e1; x++) {
+        const int n = count(x);
+        off[x] = slot;
+        if (record) d.tok_off[x] = slot;
+        for (int i = 0; i < n; i += d.tb_wi) {
+            const int m = min(d.tb_wi, n - i), k = tile_class(m);
+            int to = 0;
+#pragma unroll
+            for (int c = 0; c < 4; c++)
+                if (c == k) to = at[c]++;
+            items[2 * to] = (uint32_t)x;
+            items[2 * to + 1] = (uint32_t)(slot + i) | (uint32_t)m << 16;
+            if (record) d.items_wi[to] = d.items_wo[to] = Item{x, slot + i, m, 0};
+        }
+        slot += n;
+    }
+    __syncthreads();
+    if (e >= 0) {
+        int rank = 0;
+        for (int w = 0; w < (tid >> 5); w++) rank += __popc(mask[e * mw + w]);
+        rank += __popc(mask[e * mw + (tid >> 5)] & ((1u << (tid & 31)) - 1u));
+        perm[off[e] + rank] = tid;
+        if (record) d.perm[off[e] + rank] = tid;
+    }
+    if (record) {
+        const int kept = all[0] & 0xFFFF;
+        if (tid < kLayerCounters) {
+            const int n = r.cls[0] + r.cls[1] + r.cls[2] + r.cls[3];
+            int v = 0;
+            v = tid == 0 ? kept : v;
+            v = tid == 1 ? T - kept : v;
+            v = tid == 2 ? all[2] >> 16 : v;
+            v = tid == 3 || tid == 4 ? n : v;
+            v = tid >= 10 && tid < 14 ? r.cls[(tid - 10) & 3] : v;
+            d.counters[tid] = v;
+        }
+        if (tid == 0) d.tok_off[E] = kept;
+        if (d.y && tid < T && e < 0)
+            for (int c = 0; c < d.d_model; c++) d.y[(size_t)tid * d.d_model + c] = 0.0f;
+    }
+    __syncthreads();
+    r.items = (lp_u32)items;
+    r.perm = (const __attribute__((address_space(3))) int *)perm;
+    return r;
+}
+
+// Activations of a tile on their way to LDS: column pairs threadIdx.x, + 1024, ... of up to four tokens.  All loads are
+// issued before the first store (a loop that loads and stores a piece at a time waits for every load in turn: 4 us for
+// four tokens of 3072 columns).
+struct XPairs {
+    static constexpr int kPieces = 4;  // 8192 columns; wider tiles go round again
+    uint32_t v[kPieces][4];
+};
+typedef uint32_t u32_any __attribute__((aligned(2)));
+using gp_u32_any = const __attribute__((address_space(1))) u32_any *;
+
+template <typename RowOf>
+__device__ __forceinline__ void x_load(XPairs &p, const uint16_t *x, RowOf row_of, int ntok, int ldx, int cols, int base)
+{
+    uintptr_t src[4];
+#pragma unroll
+    for (int t = 0; t < 4; t++) src[t] = reinterpret_cast<uintptr_t>(x) + 2 * (size_t)row_of(min(t, ntok - 1)) * (size_t)ldx;
+#pragma unroll
+    for (int k = 0; k < XPairs::kPieces; k++) {
+        const int c = 2 * (base + k * kRowsThreads + (int)threadIdx.x);
+        const uintptr_t at = 2 * (uintptr_t)min(c, cols - 2);
+        if (2 * (base + k * kRowsThreads) < cols) {  // (uniform)
+            p.v[k][0] = *(gp_u32_any)(src[0] + at);
+            if (ntok > 1) {
+#pragma unroll
+                for (int t = 1; t < 4; t++) p.v[k][t] = *(gp_u32_any)(src[t] + at);
+            }
+        }
+    }
+}
+
+__device__ __forceinline__ void x_store(const XPairs &p, unsigned char *xs, int ntok, int cols, int base)
+{
+    const int n = cols + kRowsPadCols;
+#pragma unroll
+    for (int k = 0; k < XPairs::kPieces; k++) {
+        const int c = 2 * (base + k * kRowsThreads + (int)threadIdx.x);
+        if (c < n) {
+            const bool in = c < cols;
+            u32x4 o{0u, 0u, 0u, 0u};
+            if (ntok <= 1) {  // records {0, +x, 0, -x}
+                const uint32_t v = in ? p.v[k][0] : 0u, flip = in ? 0x80000000u : 0u;
+                o.x = v << 16;
+                o.y = (v << 16) ^ flip;
+                o.z = v & 0xFFFF0000u;
+                o.w = (v & 0xFFFF0000u) ^ flip;
+            } else if (in) {  // four tokens a column; those that are not there are zeros
+                const uint32_t v1 = p.v[k][1], v2 = ntok > 2 ? p.v[k][2] : 0u, v3 = ntok > 3 ? p.v[k][3] : 0u;
+                o.x = __builtin_amdgcn_perm(v1, p.v[k][0], 0x05040100u);
+                o.y = __builtin_amdgcn_perm(v3, v2, 0x05040100u);
+                o.z = __builtin_amdgcn_perm(v1, p.v[k][0], 0x07060302u);
+                o.w = __builtin_amdgcn_perm(v3, v2, 0x07060302u);
+            }
+            *reinterpret_cast<u32x4 *>(xs + 8 * (size_t)c) = o;
+        }
+    }
+}
+
+// LDS of the shares, segments and gates
+constexpr int kRowsSmallBytes = (4 * 8 + (int)sizeof(RowsSegment) * kKeptSegments + 4 * 2 * kMaxTokenTile + 15) / 16 * 16;
+
+// GROUP: the launch groups the tokens itself (first product of a small call); split2: of the second product, for whose
+// shares it leaves records.
+template <int EPI, int ASYM, bool GROUP>
+__global__ __launch_bounds__(kRowsThreads) void k_rows(const ProductArgs a, const DispatchArgs d, const RowsSplit split, const RowsSplit split2)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    // LDS: table | shares and segments | gates of the tiles in work | activations of one or two tiles (before that, the lists
+    // of the grouping)
+    uint32_t *table_w = reinterpret_cast<uint32_t *>(smem);
+    const size_t table_bytes = ((size_t)a.n_order * 4 + 15) & ~(size_t)15;
+    int *share_s = reinterpret_cast<int *>(smem + table_bytes);                       // [2][4]
+    RowsSegment *seg_s = reinterpret_cast<RowsSegment *>(share_s + 8);                // [kKeptSegments]
+    float *gate_s = reinterpret_cast<float *>(seg_s + kKeptSegments);                 // [2][kMaxTokenTile]
+    unsigned char *xs0 = smem + table_bytes + kRowsSmallBytes;
+    const size_t xs_bytes = (size_t)(a.cols + kRowsPadCols) * max(a.tb_max, 4) * sizeof(uint16_t);
+    const int wave = (int)threadIdx.x >> 6, lane = (int)threadIdx.x & 63;
+    constexpr int waves = kRowsThreads / 64;
+
+    // ---- this workgroup's share of the rows
+    InlineLists lists;
+    if constexpr (GROUP) {
+        int e = -1;
+        if ((int)threadIdx.x < d.n_tokens) {
+            e = d.expert_idx[threadIdx.x];
+            if (e < 0 || e >= d.n_experts) e = -1;
+        }
+        stage_words(table_w, a.order_table, a.n_order);
+        lists = group_tokens(d, e, xs0);
+    }
+    // (wavefront 0; with GROUP wavefront 1 does the same for the second product)
+    if (wave < (GROUP ? 2 : 1)) {
+        RowsShare sh;
+        if constexpr (GROUP) {
+            sh = rows_share(lists.cls, wave ? split2 : split, (int)gridDim.x, (int)blockIdx.x);
+        } else if (a.shares) {
+            const int *p = a.shares + blockIdx.x * kShareInts;
+            sh = RowsShare{p[0], p[1], p[2], p[3]};
+        } else {
+            int cls[4];
+            if (a.items) {
+#pragma unroll
+                for (int k = 0; k < 4; k++) cls[k] = a.class_counts[k];
+            } else {
+                const int n = (a.batch + a.tb_max - 1) / a.tb_max;
+                cls[0] = a.tb_max > 4 ? n : 0;
+                cls[1] = a.tb_max > 2 && a.tb_max <= 4 ? n : 0;
+                cls[2] = a.tb_max == 2 ? n : 0;
+                cls[3] = a.tb_max == 1 ? n : 0;
+            }
+            sh = rows_share(cls, split, (int)gridDim.x, (int)blockIdx.x);
+        }
+        if (lane == 0) {
+            share_s[4 * wave] = sh.i0;
+            share_s[4 * wave + 1] = sh.r0;
+            share_s[4 * wave + 2] = sh.i1;
+            share_s[4 * wave + 3] = sh.r1;
+        }
+    }
+    if constexpr (!GROUP) stage_words(table_w, a.order_table, a.n_order);
+    __syncthreads();
+    if constexpr (GROUP) {
+        if (threadIdx.x < (unsigned)kShareInts) {
+            const int k = threadIdx.x, n = lists.cls[0] + lists.cls[1] + lists.cls[2] + lists.cls[3];
+            const int i = min(share_s[4] + ((k - 4) >> 1), n - 1);
+            a.shares[blockIdx.x * kShareInts + k] = k < 4 ? share_s[4 + k] : (n ? (int)lists.items[2 * i + (k & 1)] : 0);
+        }
+    }
+    const int i1 = __builtin_amdgcn_readfirstlane(share_s[2]);
+    int i_base = __builtin_amdgcn_readfirstlane(share_s[0]);
+    if (i_base > i1 || (i_base == i1 && share_s[1] >= share_s[3])) return;
+
+    // lanes per row for so many rows: the fewest for which the rounds of the workgroup's wavefronts, each as long as a
+    // row's pieces over its lanes plus the round's own start and end (about two more), are shortest
+    auto lanes_log2 = [&](int rows_here) -> int {
+        const int pieces = a.cols / 176 + 1;
+        int best = 0x7FFFFFFF, log2L = 0;
+        for (int l = 0; l <= 6; l++) {
+            const int rounds = ((rows_here << l) + kRowsThreads - 1) / kRowsThreads;
+            const int cost = rounds * (((pieces + (1 << l) - 1) >> l) + 2 + (l > 0));
+            if (cost < best) {
+                best = cost;
+                log2L = l;
+            }
+        }
+        return log2L;
+    };
+    for (; i_base <= i1; i_base += kKeptSegments) {
+        // ---- the next items of the share: eight lanes for each, a token apiece
+        if (threadIdx.x < kKeptSegments * kMaxTokenTile) {
+            const int k = threadIdx.x / kMaxTokenTile, t = threadIdx.x % kMaxTokenTile, i = i_base + k;
+            int expert = -1, slot0 = 0, ntok = 0, tok = 0;
+            if (i <= i1) {
+                if constexpr (GROUP) {
+                    expert = (int)lists.items[2 * i];
+                    slot0 = (int)(lists.items[2 * i + 1] & 0xFFFFu);
+                    ntok = (int)(lists.items[2 * i + 1] >> 16);
+                } else if (a.shares) {  // (such a share is looked at in one go)
+                    const int *p = a.shares + blockIdx.x * kShareInts + 4 + 2 * k;
+                    expert = p[0];
+                    slot0 = p[1] & 0xFFFF;
+                    ntok = p[1] >> 16;
+                } else if (a.items) {
+                    const Item it = a.items[i];
+                    expert = it.expert;
+                    slot0 = it.slot0;
+                    ntok = it.ntok;
+                } else {
+                    expert = 0;
+                    slot0 = i * a.tb_max;
+                    ntok = a.batch - slot0;
+                }
+            }
+            ntok = min(ntok, a.tb_max);
+            const bool ok = expert >= 0 && expert < a.n_experts && ntok > 0;
+            if (ok) {
+                const int at = slot0 + min(t, ntok - 1);
+                if constexpr (GROUP) tok = lists.perm[at];
+                else tok = a.perm ? a.perm[at] : at;
+            }
+            RowsSegment &g = seg_s[k];
+            if (t == 0) {
+                g.expert = ok ? expert : 0;
+                g.slot0 = slot0;
+                g.ntok = ntok;
+                g.ra = i == share_s[0] ? share_s[1] : 0;
+                g.rb = !ok ? g.ra : (i == i1 ? share_s[3] : a.rows);
+            }
+            g.tok[t] = tok;
+        }
+        __syncthreads();
+        for (int k0 = 0; k0 < kKeptSegments && i_base + k0 <= i1; k0 += split.x_slots) {
+            // ---- a batch of one or two of them
+            lp_segment g0 = (lp_segment)(seg_s + k0), g1 = (lp_segment)(seg_s + min(k0 + 1, kKeptSegments - 1));
+            const bool two = split.x_slots > 1 && k0 + 1 < kKeptSegments && i_base + k0 + 1 <= i1;
+            const int ra0 = __builtin_amdgcn_readfirstlane(g0->ra), rb0 = __builtin_amdgcn_readfirstlane(g0->rb);
+            const int ra1 = __builtin_amdgcn_readfirstlane(g1->ra), rb1 = two ? __builtin_amdgcn_readfirstlane(g1->rb) : ra1;
+            const int log2L = lanes_log2((rb0 - ra0) + (rb1 - ra1)), R = 64 >> log2L;
+            const int groups0 = (rb0 - ra0 + R - 1) >> (6 - log2L);
+            // the wavefront's first group of rows (in segment head_k): its offsets are asked for first
+            const int head_k = wave < groups0 ? 0 : 1;
+            const int head_rb = head_k ? rb1 : rb0, head_r = head_k ? ra1 + (wave - groups0) * R : ra0 + wave * R;
+            const bool have = head_r < head_rb;
+            GroupHead head{0u, 0u, 0u, u32x4{0u, 0u, 0u, 0u}};
+            if (have) {
+                const int expert = __builtin_amdgcn_readfirstlane(head_k ? g1->expert : g0->expert);
+                const qmoe_matrix M = a.mats ? a.mats[expert] : a.single;
+                head_offsets<ASYM>(M, head_rb, head_r + (lane >> log2L), head);
+            }
+            if (k0 || i_base != __builtin_amdgcn_readfirstlane(share_s[0]) || GROUP) lds_barrier();  // the tiles before (the lists) are done with
+#pragma unroll
+            for (int k = 0; k < 2; k++) {
+                if (k ? ra1 >= rb1 : ra0 >= rb0) continue;
+                lp_segment g = k ? g1 : g0;
+                unsigned char *xs = xs0 + (k ? xs_bytes : 0);
+                const int ntok = __builtin_amdgcn_readfirstlane(g->ntok), slot0 = __builtin_amdgcn_readfirstlane(g->slot0);
+                auto row_of = [&](int t) { return a.x_by_slot ? slot0 + t : __builtin_amdgcn_readfirstlane(g->tok[t]); };
+                if (ntok <= 4) {
+                    for (int base = 0; 2 * base < a.cols + kRowsPadCols; base += XPairs::kPieces * kRowsThreads) {
+                        XPairs px;
+                        x_load(px, a.x, row_of, ntok, a.ldx, a.cols, base);
+                        x_store(px, xs, ntok, a.cols, base);
+                    }
+                } else {
+                    stage_x_tile<8, kRowsPadCols>(reinterpret_cast<uint16_t *>(xs), a.x, row_of, ntok, a.ldx, a.cols);
+                }
+            }
+            if (have) {
+                const int expert = __builtin_amdgcn_readfirstlane(head_k ? g1->expert : g0->expert);
+                const qmoe_matrix M = a.mats ? a.mats[expert] : a.single;
+                head.v = RowPieces(M, head, head_r + (lane >> log2L) < head_rb).load(lane & ((1 << log2L) - 1));
+            }
+            if (EPI == 0 && threadIdx.x < 2 * kMaxTokenTile) {
+                const int tok = threadIdx.x < kMaxTokenTile ? g0->tok[threadIdx.x] : g1->tok[threadIdx.x - kMaxTokenTile];
+                gate_s[threadIdx.x] = a.gate ? a.gate[tok] : 1.0f;
+            }
+            lds_barrier();
+            int group = wave;  // the wavefront's first group of rows of the segment
+            for (int k = 0; k < 2; k++) {
+                const int ra = k ? ra1 : ra0, rb = k ? rb1 : rb0;
+                if (ra >= rb) continue;
+                lp_segment g = k ? g1 : g0;
+                const int expert = __builtin_amdgcn_readfirstlane(g->expert);
+                const qmoe_matrix M = a.mats ? a.mats[expert] : a.single;
+                const bool first = have && k == head_k;
+                RowsTile tile;
+                tile.ntok = __builtin_amdgcn_readfirstlane(g->ntok);
+                tile.slot0 = __builtin_amdgcn_readfirstlane(g->slot0);
+                tile.tok_ids = g->tok;
+                tile.gate_s = (const __attribute__((address_space(3))) float *)(gate_s + k * kMaxTokenTile);
+                const uint32_t xs_addr = (uint32_t)(uintptr_t)(lp_u16)(uint16_t *)(xs0 + (k ? xs_bytes : 0));
+                if (tile.ntok <= 1) rows_block<1, EPI, ASYM>(a, M, ra, rb, group, log2L, xs_addr, tile, (lp_u32)table_w, head, first);
+                else if (tile.ntok <= 2) rows_block<2, EPI, ASYM>(a, M, ra, rb, group, log2L, xs_addr, tile, (lp_u32)table_w, head, first);
+                else if (tile.ntok <= 4) rows_block<4, EPI, ASYM>(a, M, ra, rb, group, log2L, xs_addr, tile, (lp_u32)table_w, head, first);
+                else rows_block<8, EPI, ASYM>(a, M, ra, rb, group, log2L, xs_addr, tile, (lp_u32)table_w, head, first);
+                group = (group - groups0) & (waves - 1);  // the second segment's groups go on where the first one's end
+            }
+        }
+        if (i_base + kKeptSegments <= i1) __syncthreads();  // the segments are done with
+    }
+}
+
+size_t rows_fixed_bytes(int n_order) { return (((size_t)n_order * 4 + 15) & ~(size_t)15) + kRowsSmallBytes; }
+size_t rows_tile_bytes(int cols, int tb) { return (size_t)(cols + kRowsPadCols) * 2 * (size_t)std::max(tb, 4); }
+size_t inline_lds_bytes(int E, int T)
+{
+    return 4 * ((size_t)E * ((T + 31) / 32) + (size_t)E + 3 * (size_t)T + 64);
+}
+
+}  // namespace
+
+int rows_tile_slots(int cols, int tb, int n_order, int max_lds)
+{
+    const size_t fixed = rows_fixed_bytes(n_order), tile = rows_tile_bytes(cols, tb);
+    return fixed + 2 * tile <= (size_t)max_lds ? 2 : (fixed + tile <= (size_t)max_lds ? 1 : 0);
+}
+
+bool rows_can_dispatch(int n_experts, int n_tokens, int grid)
+{
+    // (a share then spans at most n_tokens / grid + 2 items: all items cost at least what one token's does)
+    return n_tokens <= kInlineTokens && n_tokens <= (kKeptSegments - 2) * grid && 4 * (size_t)n_experts * ((n_tokens + 31) / 32) <= kInlineMaskBytes;
+}
+
+RowsSplit rows_split(int rows, int x_slots, int grid)
+{
+    RowsSplit sp;
+    sp.rows = rows;
+    sp.x_slots = x_slots;
+    for (int k = 0; k < 4; k++) sp.inv_item[k] = 1.0 / (double)(kRowCost[k] * ((rows + 7) / 8));
+    sp.inv_grid = 1.0 / grid;
+    return sp;
+}
+
+qmoe_status launch_rows(const ProductArgs &a, int x_slots, const DispatchArgs *da, int rows2, int x_slots2, int grid, int max_lds,
+                        hipStream_t s)
+{
+    size_t tiles = rows_tile_bytes(a.cols, a.tb_max) * (size_t)x_slots;
+    if (da) tiles = std::max(tiles, inline_lds_bytes(da->n_experts, da->n_tokens));
+    const size_t smem = rows_fixed_bytes(a.n_order) + tiles;
+    if (smem > (size_t)max_lds) return QMOE_E_LIMIT;
+    DispatchArgs d{};
+    RowsSplit split2{};
+    if (da) {
+        d = *da;
+        split2 = rows_split(rows2, x_slots2, grid);
+    }
+    const RowsSplit split = rows_split(a.rows, x_slots, grid);
+    auto launch = [&](auto kernel) -> qmoe_status {
+        const qmoe_status st = allow_lds(kernel, smem);
+        if (st != QMOE_OK) return st;
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(kRowsThreads), smem, s, a, d, split, split2);
+        return QMOE_OK;
+    };
+    qmoe_status st;
+    if (da)
+        st = a.minmax ? launch(k_rows<1, 1, true>) : launch(k_rows<1, 0, true>);
+    else if (a.minmax)
+        st = a.epilogue ? launch(k_rows<1, 1, false>) : launch(k_rows<0, 1, false>);
+    else
+        st = a.epilogue ? launch(k_rows<1, 0, false>) : launch(k_rows<0, 0, false>);
+    if (st != QMOE_OK) return st;
+    QMOE_HIP_TRY(hipGetLastError());
+    return QMOE_OK;
+}
+
+}  // namespace qmoe

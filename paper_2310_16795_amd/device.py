@@ -80,12 +80,17 @@ class DeviceLayer:
     def finalize(self, device_order_of: "DeviceDict | None" = None, lanes_for_tokens: int = 0):
         """Upload everything; with device_order_of, renumber the streams for that dictionary; with
         lanes_for_tokens (a typical token count of the calls to come; needs device_order_of), re-pack
-        every stream into the lane-interleaved layout for the lane count the planner picks."""
+        every stream into the lane-interleaved layout for the lane count the planner picks -- unless
+        calls of that size read rows back to back faster (qmoe_plan_row_layout)."""
         self.code_order = 0 if device_order_of is None else 1
         self.format = self.code_order | (B.FORMAT_GRID_MINMAX if self.minmax else 0)
         per_row = 2 if self.minmax else 1  # 16-bit values of scale data per row
         self.bufs, self.desc_dev, self.desc_host = {}, {}, {}
         self.lanes = {"wi": 0, "wo": 0}
+        if lanes_for_tokens > 0:
+            assert device_order_of is not None
+            if B.qmoe_plan_row_layout(device_order_of.handle, self.d_model, self.d_ff, self.n_experts, lanes_for_tokens):
+                lanes_for_tokens = 0
         for which in ("wi", "wo"):
             rows = self.d_ff if which == "wi" else self.d_model
             cols = self.d_model if which == "wi" else self.d_ff
@@ -93,7 +98,6 @@ class DeviceLayer:
             lanes = 0
             wave_off = None
             if lanes_for_tokens > 0:
-                assert device_order_of is not None
                 lanes = B.qmoe_plan_lanes(device_order_of.handle, rows, cols, self.n_experts, lanes_for_tokens)
                 self.lanes[which] = lanes
                 wave_off = np.zeros((self.n_experts, lanes // 64 + 1), dtype=np.uint32)

@@ -1,0 +1,94 @@
+"""The kernel that shares a row between several lanes, against the oracle, at the edges of its branches: calls of
+one item and of more items than workgroups, tiles of every size, the largest call that groups its tokens itself and
+the smallest that does not, rows that no eight and no group of lanes divides, more columns than one round of staging."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2310_16795_amd as q
+from paper_2310_16795_amd import device as dev
+from paper_2310_16795_amd import synth
+from test_gpu_parity import _build_layer, _check_layer, _check_product, _run_layer, _to_dev16, _upload
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def gpu():
+    if not torch.cuda.is_available():
+        pytest.fail("the GPU tests need a GPU: the HIP path has no fallback")
+    return "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def ddict(gpu, oracle_dict):
+    dd = dev.DeviceDict(q.qmoe_dict_from_words(oracle_dict.words), gpu)
+    yield dd
+    dd.close()
+
+
+@pytest.fixture(autouse=True)
+def always_this_kernel():
+    q.qmoe_hook_set("rows", 1)
+    yield
+    q.qmoe_hook_set("rows", 0)
+
+
+@pytest.mark.parametrize("minmax", [False, True])
+@pytest.mark.parametrize("E,d_model,d_ff,T", [
+    (3, 8, 20, 1),        # fewer rows than lanes, one piece per row
+    (5, 30, 2, 9),        # two rows
+    (40, 258, 130, 1),    # one item on the whole GPU
+    (7, 520, 514, 33),    # rows that no eight divides
+    (600, 72, 96, 512),   # more items than workgroups, the largest call that groups its tokens itself
+    (600, 72, 96, 513),   # ... and the smallest that does not
+    (1, 264, 136, 510),   # every tile on one expert
+    (4, 64, 8400, 6),     # more columns than one round of staging
+])
+def test_layer_every_tile(gpu, ddict, oracle_dict, E, d_model, d_ff, T, minmax):
+    w = synth.WORKLOADS["switch_base128"].scaled(n_experts=E, d_model=d_model, d_ff=d_ff, n_tokens=T)
+    idx, x = w.expert_idx(), w.tokens()
+    if T > 8 and E > 4:
+        idx[0], idx[T // 2] = -1, E    # tokens without an expert
+        idx[1:8] = [2, 2, 2, 2, 3, 3, 3]
+    layer = _build_layer(w, oracle_dict, gpu, order_of=ddict, minmax=minmax)
+    gate = np.random.default_rng(5).uniform(0.2, 1.0, T)
+    y, wsout = _run_layer(layer, ddict, x, idx, gpu, gate)
+    valid = [t for t in range(T) if 0 <= idx[t] < E]
+    tok_off, perm = oracle.dispatch(idx, E)
+    assert np.array_equal(wsout["tok_off"], tok_off) and np.array_equal(wsout["perm"][:len(valid)], perm)
+    assert wsout["counters"][0] == len(valid) and wsout["counters"][2] == len({int(idx[t]) for t in valid})
+    covered = np.zeros(len(valid), dtype=int)
+    for e, slot0, ntok, _ in wsout["items_wi"][:wsout["counters"][3]]:
+        assert tok_off[e] <= slot0 and slot0 + ntok <= tok_off[e + 1]
+        covered[slot0:slot0 + ntok] += 1
+    n_items = wsout["counters"][3]
+    assert (covered == 1).all() and np.array_equal(wsout["items_wi"][:n_items], wsout["items_wo"][:wsout["counters"][4]])
+    _check_layer(w, idx, x, y, wsout, valid if len(valid) < 60 else valid[:30] + valid[-30:], gate, asym=minmax)
+    assert not y[[t for t in range(T) if not 0 <= idx[t] < E]].any()
+    y2, _ = _run_layer(layer, ddict, x, idx, gpu, gate)
+    assert np.array_equal(y, y2)
+    for tile in (1, 8) if d_ff < 5000 else (1,):  # (eight tokens of 8400 columns do not fit the LDS)
+        q.qmoe_set_tuning("token_tile", tile)
+        try:
+            yt, wst = _run_layer(layer, ddict, x, idx, gpu, gate)
+        finally:
+            q.qmoe_set_tuning("token_tile", 0)
+        _check_layer(w, idx, x, yt, wst, valid[:20], gate, asym=minmax)
+
+
+@pytest.mark.parametrize("rows,cols,p0,batch", [(1, 2, 0.5, 1), (3, 16, 0.9, 2), (9, 226, 0.8, 3), (2080, 6144, 0.9, 5),
+                                                (4001, 130, 0.97, 37), (600, 2080, 0.0, 1), (50, 8194, 1.0, 4), (31, 12000, 0.9, 9)])
+@pytest.mark.parametrize("minmax", [False, True])
+def test_single_matrix(gpu, ddict, oracle_dict, rows, cols, p0, batch, minmax):
+    tern = synth.ternary(rows + cols, rows, cols, p0)
+    scale = None if minmax else synth.uniform_f16(1, (rows,), 0.01, 0.1)
+    pairs = synth.minmax_bf16(2, rows, 0.01, 0.1) if minmax else None
+    x = synth.normal_bf16(3, (batch, cols))
+    M = _upload(oracle_dict, tern, scale, gpu, ddict, minmax=pairs)
+    y = torch.full((batch, rows), float("nan"), dtype=torch.float32, device=gpu)
+    q.qmoe_decode_matvec(ddict.handle, M.desc, _to_dev16(x, gpu), y)
+    torch.cuda.synchronize()
+    y_ref, bound = oracle.matvec(tern, scale, x, with_bound=True, minmax_bf16=pairs)
+    _check_product(y.cpu().numpy(), y_ref, bound, f"{rows}x{cols}")
