@@ -315,7 +315,7 @@ qmoe_status qmoe_decode_dense(const qmoe_dict *d, const qmoe_matrix *W /*host*/,
  * aligned, NULL = skip that matrix.  cols must be a multiple of 8.  One launch for all
  * matrices; nothing is allocated.
  * Errors: INVALID_ARG, NO_DEVICE_DICT, LIMIT (no device order; cols > 32768; more matrices in
- * one call than the kernel's LDS has a bit for: about 20000 with the paper's table), HIP.
+ * one call than the kernel's LDS has a bit for: about 120000 with the paper's table), HIP.
  */
 qmoe_status qmoe_decompress(const qmoe_dict *d, const qmoe_matrix *mats /*device*/, int code_order,
                             int n_mats, int rows, int cols, int out_kind,

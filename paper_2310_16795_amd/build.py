@@ -18,7 +18,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(CSRC, "_build")
 LIB = os.path.join(CSRC, "libqmoe.so")
 UNITS = ["qmoe_host.cpp", "qmoe_api.hip", "qmoe_product_sym.hip", "qmoe_product_asym.hip", "qmoe_product_mm.hip",
-         "qmoe_rows.hip", "qmoe_matvec.hip", "qmoe_dispatch.hip", "qmoe_encode.hip", "qmoe_misc.hip"]
+         "qmoe_rows.hip", "qmoe_decompress.hip", "qmoe_matvec.hip", "qmoe_dispatch.hip", "qmoe_encode.hip", "qmoe_misc.hip"]
 HEADERS = [os.path.join(ROOT, "include", "qmoe.h"), os.path.join(ROOT, "include", "qmoe_hooks.h"),
            os.path.join(CSRC, "qmoe_internal.h"), os.path.join(CSRC, "qmoe_dev.h"), os.path.join(CSRC, "qmoe_product.h"),
            os.path.join(CSRC, "qmoe_encode.h")]

@@ -5,7 +5,8 @@
 // (CDNA4, wave64) is this library's own and is described where each kernel is defined:
 //   qmoe_product.h / qmoe_product_*.hip  fused decode + product, a lane per row range
 //   qmoe_rows.hip                        the same with several lanes per row: few items, single matrices
-//   qmoe_product_mm.hip                  decode once, multiply on the matrix cores; decompression
+//   qmoe_product_mm.hip                  decode once, multiply on the matrix cores
+//   qmoe_decompress.hip                  whole matrices back to int8 or bf16
 //   qmoe_matvec.hip                      one matrix, a few tokens: 16 lanes per row; decode-only hook
 //   qmoe_dispatch.hip                    tokens grouped by expert, work lists
 //   qmoe_encode.hip                      device encoder (its arguments: qmoe_encode.h)
@@ -95,7 +96,7 @@ struct DecompressArgs {
     const qmoe_matrix *mats;  // device array
     void *const *out;         // device array of destinations (row-major rows x cols), nullptr = skip
     int n_mats, rows, cols;
-    int rows_per_block, row_blocks;
+    int slots;                // units of rows per matrix (set by launch_decompress)
     const uint32_t *order_table;
     int n_groups, n_order;
 };
@@ -170,9 +171,8 @@ qmoe_status launch_product_sym(const ProductArgs &a, const ProductPlan &p, bool 
 qmoe_status launch_product_asym(const ProductArgs &a, const ProductPlan &p, bool run, hipStream_t s);
 size_t mm_lds_bytes(int n_order);                                                                   // qmoe_product_mm.hip
 qmoe_status launch_product_mm(ProductArgs a, const MmPlan &mp, hipStream_t s);
-void mm_rows(int rows, int *row_blocks, int *rows_per_block);
-qmoe_status launch_decompress(const DecompressArgs &a, int out_kind, bool minmax, int grid, size_t smem, hipStream_t s);
-size_t decompress_lds_bytes(int n_order, int n_mats);  // table, rings, windows, one bit per matrix
+qmoe_status launch_decompress(DecompressArgs a, int out_kind, bool minmax, int cus, size_t smem, hipStream_t s);  // qmoe_decompress.hip
+size_t decompress_lds_bytes(int n_order, int n_mats);  // table, rings, one bit per matrix
 qmoe_status launch_matvec_rows(const ProductArgs &a, bool run, bool minmax, int grid, int threads, size_t smem,
                                hipStream_t s);                                                      // qmoe_matvec.hip
 int rows_tile_slots(int cols, int tb, int n_order, int max_lds);                                     // qmoe_rows.hip
@@ -202,6 +202,30 @@ __device__ __forceinline__ int row_scan16(int v)
     v += dpp0<kRowShr2>(v);
     v += dpp0<kRowShr4>(v);
     v += dpp0<kRowShr8>(v);
+    return v;
+}
+
+// inclusive prefix sum over groups of L lanes (1 .. 64, a power of two, the same in every lane); `sub`: lane of the group
+template <typename T>
+__device__ __forceinline__ T lanes_scan(T v, int L, int sub)
+{
+    auto add = [&](auto ctrl, auto row_mask, bool take) {
+        int bits;
+        __builtin_memcpy(&bits, &v, 4);
+        bits = __builtin_amdgcn_update_dpp(0, bits, decltype(ctrl)::value, decltype(row_mask)::value, 0xf, false);
+        bits = take ? bits : 0;  // (all zero bits: 0 as an integer and as a float)
+        T w;
+        __builtin_memcpy(&w, &bits, 4);
+        v += w;
+    };
+    using std::integral_constant;
+    using full = integral_constant<int, 0xf>;
+    if (L > 1) add(integral_constant<int, kRowShr1>{}, full{}, sub >= 1);
+    if (L > 2) add(integral_constant<int, kRowShr2>{}, full{}, sub >= 2);
+    if (L > 4) add(integral_constant<int, kRowShr4>{}, full{}, sub >= 4);
+    if (L > 8) add(integral_constant<int, kRowShr8>{}, full{}, sub >= 8);
+    if (L > 16) add(integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{}, true);  // row_bcast:15 into rows 1 and 3
+    if (L > 32) add(integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{}, true);  // row_bcast:31 into rows 2 and 3
     return v;
 }
 
@@ -292,6 +316,19 @@ using gp_u64 = const __attribute__((address_space(1))) unsigned long long *;
 using gp_u32x4 = const __attribute__((address_space(1))) u32x4 *;
 using lp_u32 = const __attribute__((address_space(3))) uint32_t *;
 using lp_u16 = const __attribute__((address_space(3))) uint16_t *;
+
+// Asymmetric grid: byte selectors (0: zero, 2: w_max, 6: w_min), eight of them in d0, d1, pick the row's own bf16 grid
+// points out of lo = w_max << 16, hi = w_min << 16 (bytes 0..3 of the permute's source are lo, 4..7 hi; selector b
+// takes the value's low byte, b + 1 its high byte).
+__device__ __forceinline__ u32x4 select_minmax(uint32_t d0, uint32_t d1, uint32_t hi, uint32_t lo)
+{
+    u32x4 o;
+    o.x = __builtin_amdgcn_perm(hi, lo, __builtin_amdgcn_perm(0u, d0, 0x01010000u) + 0x01000100u);
+    o.y = __builtin_amdgcn_perm(hi, lo, __builtin_amdgcn_perm(0u, d0, 0x03030202u) + 0x01000100u);
+    o.z = __builtin_amdgcn_perm(hi, lo, __builtin_amdgcn_perm(0u, d1, 0x01010000u) + 0x01000100u);
+    o.w = __builtin_amdgcn_perm(hi, lo, __builtin_amdgcn_perm(0u, d1, 0x03030202u) + 0x01000100u);
+    return o;
+}
 
 // Copy n 32-bit words from global memory to LDS with the whole workgroup (both 16-byte
 // aligned): 16 bytes per lane and up to eight loads in flight per lane before the first

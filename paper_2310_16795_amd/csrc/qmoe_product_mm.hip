@@ -1,6 +1,5 @@
-// Kernels built on the ring decoder: the matrix-core product for crowded experts
-// (Section 5.3 of the paper proposes decoding once for several tokens) and the
-// decompression of whole matrices (Section 4.3.3 mentions it as a variant).
+// The matrix-core product for crowded experts (Section 5.3 of the paper proposes decoding once for
+// several tokens).
 #include "qmoe_dev.h"
 
 namespace qmoe {
@@ -46,24 +45,14 @@ __device__ __forceinline__ bf16x8 mm_expand(uint32_t d0, uint32_t d1)
     return r;
 }
 
-// Asymmetric grid: the ring holds byte selectors (0: zero, 2: w_max, 6: w_min) and eight of
-// them pick the row's own bf16 grid points out of lo = w_max << 16, hi = w_min << 16 (bytes
-// 0..3 of the permute's source are lo, 4..7 hi; selector b takes the value's low byte,
-// b + 1 its high byte).
 __device__ __forceinline__ bf16x8 mm_expand_minmax(uint32_t d0, uint32_t d1, uint32_t hi, uint32_t lo)
 {
-    u32x4 o;
-    o.x = __builtin_amdgcn_perm(hi, lo, __builtin_amdgcn_perm(0u, d0, 0x01010000u) + 0x01000100u);
-    o.y = __builtin_amdgcn_perm(hi, lo, __builtin_amdgcn_perm(0u, d0, 0x03030202u) + 0x01000100u);
-    o.z = __builtin_amdgcn_perm(hi, lo, __builtin_amdgcn_perm(0u, d1, 0x01010000u) + 0x01000100u);
-    o.w = __builtin_amdgcn_perm(hi, lo, __builtin_amdgcn_perm(0u, d1, 0x03030202u) + 0x01000100u);
+    const u32x4 o = select_minmax(d0, d1, hi, lo);
     bf16x8 r;
     __builtin_memcpy(&r, &o, 16);
     return r;
 }
 
-using gw_u64 = __attribute__((address_space(1))) unsigned long long *;
-using gw_u32x4 = __attribute__((address_space(1))) u32x4 *;
 using lw_u8 = __attribute__((address_space(3))) unsigned char *;
 using lw_u64 = __attribute__((address_space(3))) unsigned long long *;
 using lw_u32x4 = __attribute__((address_space(3))) u32x4 *;
@@ -72,7 +61,7 @@ using lp_u32x4 = const __attribute__((address_space(3))) u32x4 *;
 using lp_i32 = const __attribute__((address_space(3))) int *;
 using lp_f32 = const __attribute__((address_space(3))) float *;
 
-// ---- the ring decoder shared by the matrix-core product and the decompression kernel ----
+// ---- the ring decoder ----
 //
 // One lane = one row.  A lane's codewords pass through a window of two 16-byte pieces (sixteen
 // codewords) in LDS, the next piece is in flight in a register; the codeword two places ahead
@@ -171,15 +160,11 @@ __device__ __forceinline__ void ring_prime(RingDecoder &d, lp_u32 table, uint32_
 // reads are issued first, unconditional, from addresses chosen so that a lane that sat out
 // reads again what it already holds, and are used a round later; the entry of ci + 1 is kept
 // as read, next to the sign flips of its code's two low bits.
-//
-// `shift8` = 8 * (columns by which this lane's steps begin early, 0..63): the lane's step covers
-// columns kc - shift .. kc - shift + 63 (the decompression kernel lets every row's steps end on
-// line boundaries of the row's destination; the product passes 0).
 template <int ASYM, class AfterWait>
 __device__ __forceinline__ void ring_decode_step(RingDecoder &d, lp_u32 table, uint32_t n_groups, uint32_t n_order, int kc,
-                                                 uint32_t shift8, AfterWait &&after_wait)
+                                                 AfterWait &&after_wait)
 {
-    const uint32_t lim8 = 8u * (uint32_t)(kc + kMmAhead) - shift8, end8 = 8u * (uint32_t)(kc + kMmKc) - shift8;
+    const uint32_t lim8 = 8u * (uint32_t)(kc + kMmAhead), end8 = 8u * (uint32_t)(kc + kMmKc);
     bool first = true;
     do {
         // Slide the window by one piece where its first piece is used up (once per step as a
@@ -351,7 +336,7 @@ __device__ __forceinline__ void mm_item(const ProductArgs &a, const qmoe_matrix 
         // ---- decode until every lane has passed column kc + 64; the next step's activations are
         // fetched right after the window's wait, a whole step ahead
         u32x4 xn[MB][2];
-        ring_decode_step<ASYM>(dec, table, n_groups, n_order, kc, 0u, [&]() {
+        ring_decode_step<ASYM>(dec, table, n_groups, n_order, kc, [&]() {
             int k_next = kc + kMmKc;
             asm volatile("" : "+s"(k_next));
 #pragma unroll
@@ -533,188 +518,12 @@ __global__ __launch_bounds__(kMmThreads) void k_product_mm(const ProductArgs a)
     }
 }
 
-// ---------------------------------------------------------------- decompression of whole matrices
-//
-// The codec without the product: dense ternary (int8) or scaled bf16 copies of compressed
-// matrices, for consumers that want a plain matrix (a library GEMM, a check).  The ring
-// decoder of the matrix-core product: a workgroup of 512 lanes owns up to 512 rows, one lane
-// per row; after each 64-column step a wavefront writes out the 64 x 64 tile its own lanes
-// decoded, 8 rows per store instruction with 8 lanes covering a row's 64 columns, so that
-// the stores are whole 64- or 128-byte runs.  Wavefronts never wait for each other.
-
-// OUT 0: int8 in {-1, 0, +1}; 1: bf16(scale of the row) with the weight's sign, or 0;
-// 2: the row's bf16 grid point w_max or w_min, or 0 (asymmetric grid)
-template <int OUT>
-__global__ __launch_bounds__(kMmThreads) void k_decompress(const DecompressArgs a)
-{
-    extern __shared__ __align__(16) unsigned char smem[];
-    const size_t table_bytes = ((size_t)a.n_order * 4 + 15) & ~(size_t)15;
-    uint32_t *table_w = reinterpret_cast<uint32_t *>(smem);
-    stage_words(table_w, a.order_table, a.n_order);
-    __syncthreads();
-    lp_u32 table = (lp_u32)table_w;
-    const uint32_t wt = (uint32_t)(uintptr_t)(lw_u8)(smem + table_bytes);               // [512][kMmWRowBytes] rings
-    const uint32_t win = wt + (uint32_t)(kMmThreads * kMmWRowBytes);                     // [512][kMmWinBytes] codeword windows
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int seg = lane & 7, sub_row = lane >> 3;  // write-out role: columns 8*seg.., rows sub_row + 8*i
-    const uint32_t n_groups = (uint32_t)a.n_groups, n_order = (uint32_t)a.n_order;
-    // A row's 64-column steps begin early by as many columns as it takes for their ends to fall on
-    // 128-byte (bf16) or 64-byte (int8) boundaries of the row's destination: a matrix whose rows are no
-    // multiple of that long would otherwise have every run of every other row straddle two lines.
-    // (Destinations are 16-byte aligned and cols is a multiple of 8, so a shift is a multiple of 8 columns.)
-    constexpr int kBpe = OUT == 0 ? 1 : 2, kRunBytes = kMmKc * kBpe;
-    const bool shifted = ((size_t)a.cols * kBpe) % kRunBytes != 0;
-    const int nsteps = (a.cols + kMmKc - 1) / kMmKc + (shifted ? 1 : 0);
-
-    // Which matrices have a destination: one bit each, so that the workgroups share the matrices that
-    // are asked for evenly (dealt out over all matrices, a workgroup's share of those would be a matter of luck).
-    using lw_mask = __attribute__((address_space(3))) unsigned long long *;
-    lw_mask mask = (lw_mask)(uintptr_t)(win + (uint32_t)(kMmThreads * kMmWinBytes));  // [(n_mats + 63) / 64]
-    const int mask_words = (a.n_mats + 63) / 64;
-    for (int w = wave; w < mask_words; w += kMmThreads / 64) {
-        const int m = 64 * w + lane;
-        const unsigned long long bits = __ballot(m < a.n_mats && a.out[m] != nullptr);
-        if (lane == 0) mask[w] = bits;
-    }
-    __syncthreads();
-    long long n_wanted = 0;
-    for (int w = 0; w < mask_words; w++) n_wanted += __popcll(mask[w]);
-    const long long total = n_wanted * a.row_blocks;
-
-    for (long long g = blockIdx.x; g < total; g += gridDim.x) {
-        const int nth = (int)(g / a.row_blocks);  // which of the wanted matrices
-        const int blk = (int)(g - (long long)nth * a.row_blocks);
-        int m;
-        {
-            int w = 0, rem = nth;
-            for (;; w++) {
-                const int n = __popcll(mask[w]);
-                if (rem < n) break;
-                rem -= n;
-            }
-            unsigned long long bits = mask[w];
-            for (int i = 0; i < rem; i++) bits &= bits - 1ull;
-            // (the same in every lane; said so, the matrix descriptor is read into scalar registers)
-            m = __builtin_amdgcn_readfirstlane(64 * w + (int)__ffsll((long long)bits) - 1);
-        }
-        // (a pointer read from memory is a generic one to the compiler; stores through it would go out as
-        // generic-address stores, which count as LDS traffic too and make every wait of the decoder a full one)
-        const uintptr_t out = reinterpret_cast<uintptr_t>(a.out[m]);
-        // columns by which row r's steps begin early
-        auto row_shift = [&](int r) -> int {
-            const int lead = (int)((out + (uintptr_t)kBpe * (uintptr_t)r * (uintptr_t)a.cols) % kRunBytes);  // bytes past a boundary
-            return lead / kBpe;  // = (64 - columns up to the row's first boundary) mod 64
-        };
-        const qmoe_matrix M = a.mats[m];
-        const int r0 = blk * a.rows_per_block;
-        const int row = r0 + tid;
-        const bool row_live = tid < a.rows_per_block && row < a.rows;
-        RingDecoder dec;
-        ring_setup(dec, M, row, row_live, wt + (uint32_t)(tid * kMmWRowBytes), win + (uint32_t)(tid * kMmWinBytes));
-
-        // the eight rows this lane writes out: which of them exist, and their bf16 scale in both
-        // halves of a register (OUT 2: the (w_min, w_max) pair as stored, w_min in the low half)
-        bool r_ok[8];
-        uint32_t s2[8];
-        int sh[8];  // the shifts of those rows
-        const uint32_t shift8 = shifted && row_live ? 8u * (uint32_t)row_shift(row) : 0u;  // this lane's own row
-#pragma unroll
-        for (int i = 0; i < 8; i++) {
-            const int rl = 64 * wave + sub_row + 8 * i;
-            r_ok[i] = rl < a.rows_per_block && r0 + rl < a.rows;
-            sh[i] = shifted && r_ok[i] ? row_shift(r0 + rl) : 0;
-            // (loads without a branch, from row r0 where there is no row: the eight are in flight together)
-            const int rr = r_ok[i] ? r0 + rl : min(r0, a.rows - 1);
-            s2[i] = 0u;
-            if constexpr (OUT == 2) {
-                if (M.minmax_bf16) {
-                    const uint32_t pair = ((gp_u32)M.minmax_bf16)[rr];
-                    s2[i] = r_ok[i] ? pair : 0u;
-                }
-            }
-            if constexpr (OUT == 1) {
-                const uint32_t b = float_to_bf16_bits(half_bits_to_float(((gp_u16)M.scale_f16)[rr]));
-                s2[i] = r_ok[i] ? (b | (b << 16)) : 0u;
-            }
-        }
-        ring_prime(dec, table, n_groups, n_order);
-
-        for (int c = 0; c < nsteps; c++) {
-            const int kc = c * kMmKc;
-            ring_decode_step<OUT == 2>(dec, table, n_groups, n_order, kc, shift8, []() {});
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            // the eight reads first (every lane reads, from inside the workgroup's rings), then the stores
-            unsigned long long d[8];
-#pragma unroll
-            for (int i = 0; i < 8; i++) {
-                const int rl = 64 * wave + sub_row + 8 * i;
-                const uint32_t ring_col = (uint32_t)(kc - sh[i] + 8 * seg) & (uint32_t)(kMmRing - 1);  // 8-aligned: no wrap inside
-                d[i] = *(lp_u64)(uintptr_t)(wt + (uint32_t)(rl * kMmWRowBytes) + ring_col);
-            }
-#pragma unroll
-            for (int i = 0; i < 8; i++) {
-                const int r = r0 + 64 * wave + sub_row + 8 * i;
-                const int k = kc - sh[i] + 8 * seg;
-                if (r_ok[i] && k >= 0 && k + 8 <= a.cols) {
-                    const uint32_t w0 = (uint32_t)d[i], w1 = (uint32_t)(d[i] >> 32);
-                    const size_t at = (size_t)r * a.cols + k;
-                    if constexpr (OUT == 0) {
-                        // ring byte 0x40 -> 0x01, 0xC0 -> 0xFF, 0 -> 0
-                        const uint32_t o0 = ((w0 >> 6) & 0x01010101u) | (((w0 >> 7) & 0x01010101u) * 0xFEu);
-                        const uint32_t o1 = ((w1 >> 6) & 0x01010101u) | (((w1 >> 7) & 0x01010101u) * 0xFEu);
-                        *(gw_u64)(out + at) = (unsigned long long)o0 | ((unsigned long long)o1 << 32);
-                    } else if constexpr (OUT == 2) {
-                        const bf16x8 v = mm_expand_minmax(w0, w1, s2[i] << 16, s2[i] & 0xFFFF0000u);
-                        u32x4 o;
-                        __builtin_memcpy(&o, &v, 16);
-                        *(gw_u32x4)(out + 2 * at) = o;
-                    } else {
-                        u32x4 o;
-#pragma unroll
-                        for (int h = 0; h < 4; h++) {
-                            // two ring bytes -> the high bytes of two 16-bit halves: 0x4000 / 0xC000 / 0
-                            const uint32_t e = __builtin_amdgcn_perm(0u, h < 2 ? w0 : w1, (h & 1) ? 0x030c020cu : 0x010c000cu);
-                            const uint32_t present = ((e >> 14) & 0x00010001u) * 0xFFFFu;
-                            o[h] = ((e & 0x80008000u) | s2[i]) & present;
-                        }
-                        *(gw_u32x4)(out + 2 * at) = o;
-                    }
-                }
-            }
-            // the 64 columns of this lane's ring that held its step are cleared for the step after next:
-            // after the reads above
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int j = 0; j < kMmKc / 8; j++) {
-                const uint32_t ring_col = ((uint32_t)(8 * kc + 64 * j) - shift8) >> 3 & (uint32_t)(kMmRing - 1);
-                *(lw_u64)(uintptr_t)(dec.wrow + ring_col) = 0ull;
-            }
-        }
-    }
-}
-
 }  // namespace
 
 size_t mm_lds_bytes(int n_order)
 {
     return (((size_t)n_order * 4 + 15) & ~(size_t)15) + (size_t)kMmThreads * kMmWRowBytes +
            (size_t)kMmThreads * kMmWinBytes + 16;
-}
-
-size_t decompress_lds_bytes(int n_order, int n_mats)
-{
-    return (((size_t)n_order * 4 + 15) & ~(size_t)15) + (size_t)kMmThreads * kMmWRowBytes +
-           (size_t)kMmThreads * kMmWinBytes + 8 * (((size_t)n_mats + 63) / 64);
-}
-
-void mm_rows(int rows, int *row_blocks, int *rows_per_block)
-{
-    const int nb = (rows + kMmThreads - 1) / kMmThreads;
-    const int per = (rows + nb - 1) / nb;
-    *row_blocks = nb;
-    *rows_per_block = std::min(kMmThreads, (per + 63) / 64 * 64);
 }
 
 qmoe_status launch_product_mm(ProductArgs a, const MmPlan &mp, hipStream_t s)
@@ -732,24 +541,6 @@ qmoe_status launch_product_mm(ProductArgs a, const MmPlan &mp, hipStream_t s)
     else
         st = a.epilogue ? launch(k_product_mm<1, 0>) : launch(k_product_mm<0, 0>);
     if (st != QMOE_OK) return st;
-    QMOE_HIP_TRY(hipGetLastError());
-    return QMOE_OK;
-}
-
-
-qmoe_status launch_decompress(const DecompressArgs &a, int out_kind, bool minmax, int grid, size_t smem, hipStream_t s)
-{
-    qmoe_status st;
-    if (out_kind == 0) {
-        if ((st = allow_lds(k_decompress<0>, smem)) != QMOE_OK) return st;
-        hipLaunchKernelGGL(k_decompress<0>, dim3(grid), dim3(kMmThreads), smem, s, a);
-    } else if (minmax) {
-        if ((st = allow_lds(k_decompress<2>, smem)) != QMOE_OK) return st;
-        hipLaunchKernelGGL(k_decompress<2>, dim3(grid), dim3(kMmThreads), smem, s, a);
-    } else {
-        if ((st = allow_lds(k_decompress<1>, smem)) != QMOE_OK) return st;
-        hipLaunchKernelGGL(k_decompress<1>, dim3(grid), dim3(kMmThreads), smem, s, a);
-    }
     QMOE_HIP_TRY(hipGetLastError());
     return QMOE_OK;
 }

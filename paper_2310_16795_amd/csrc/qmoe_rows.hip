@@ -31,30 +31,6 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// inclusive prefix sum over the L lanes of a row (lane `sub` of it); L is the same in every lane
-template <typename T>
-__device__ __forceinline__ T lanes_scan(T v, int L, int sub)
-{
-    auto add = [&](auto ctrl, auto row_mask, bool take) {
-        int bits;
-        __builtin_memcpy(&bits, &v, 4);
-        bits = __builtin_amdgcn_update_dpp(0, bits, decltype(ctrl)::value, decltype(row_mask)::value, 0xf, false);
-        bits = take ? bits : 0;  // (all zero bits: 0 as an integer and as a float)
-        T w;
-        __builtin_memcpy(&w, &bits, 4);
-        v += w;
-    };
-    using std::integral_constant;
-    using full = integral_constant<int, 0xf>;
-    if (L > 1) add(integral_constant<int, kRowShr1>{}, full{}, sub >= 1);
-    if (L > 2) add(integral_constant<int, kRowShr2>{}, full{}, sub >= 2);
-    if (L > 4) add(integral_constant<int, kRowShr4>{}, full{}, sub >= 4);
-    if (L > 8) add(integral_constant<int, kRowShr8>{}, full{}, sub >= 8);
-    if (L > 16) add(integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{}, true);  // row_bcast:15 into rows 1 and 3
-    if (L > 32) add(integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{}, true);  // row_bcast:31 into rows 2 and 3
-    return v;
-}
-
 typedef u32x4 u32x4_any __attribute__((aligned(2)));
 using gp_u32x4_any = const __attribute__((address_space(1))) u32x4_any *;
 
