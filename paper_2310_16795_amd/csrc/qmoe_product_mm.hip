@@ -21,6 +21,15 @@ namespace {
 // zero), expanded to bf16 by a byte permute when a fragment is read; the factor 2
 // is taken out again, exactly, when a row is written.
 // Only device-order streams (whole table in LDS) take this path.
+//
+// What bounds it: nothing alone.  For 64 codewords the vector units issue 79 instructions and the LDS works 87 cycles, of
+// the 136 a compute unit takes (rows of 2080 columns, sparsities mixed); the LDS holds two wavefronts per SIMD (ring,
+// window and table), too few to hide each other's waits altogether.  A step's activations are loaded straight into the registers the
+// product reads, a codeword piece only by the lanes that need one (asking again for what is there costs a line per lane), a
+// lane's tests are one limit each: 98 instructions before, and 1119 us instead of 1236 for 256 experts of 2080 x 6144 with
+// 1-32 tokens each, 268 instead of 296 us for 128 experts of 768 x 3072 with 31 tokens each.
+// (Slower, measured: two lanes per row with rings of 256 columns, two codewords a round, a ring stored by columns and read
+// transposed, codewords four by four in the window.)
 
 constexpr int kMmKc = 64;                      // columns per step
 constexpr int kMmRing = 2 * kMmKc;             // columns a lane's ring holds
@@ -29,8 +38,6 @@ constexpr int kMmAhead = kMmRing - 28 - 1;     // a codeword may start this far 
 constexpr int kMmWRowBytes = kMmRing + 16;     // 36 banks per row: 16 consecutive rows read 16 bytes each (two lanes, 8 bytes apiece) without conflict
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-
 
 // eight ring bytes (high bytes of bf16) -> eight bf16
 __device__ __forceinline__ bf16x8 mm_expand(uint32_t d0, uint32_t d1)
@@ -74,11 +81,13 @@ using lp_f32 = const __attribute__((address_space(3))) float *;
 //
 // (A struct of plain scalars and free functions that are always inlined: the state stays in
 // registers.)
+constexpr uint32_t kMmWinAhead = 13;  // the window holds 16 codewords, and a round reads two ahead of the one it applies
 constexpr int kMmWinBytes = 40;   // a lane's window: two 16-byte pieces, padded so that the 64 slots spread over the banks
 
 struct RingDecoder {
-    uint32_t left;              // codewords to go
     uint32_t ci;                // index of the next codeword, counted from the lane's first piece
+    uint32_t end;               // index past the row's last codeword
+    uint32_t lim;               // the lane may go on while ci < lim: codewords are left, and the window reaches two past them
     uint32_t wbase;             // index of the first codeword of the window's first piece (a multiple of 8)
     uint32_t pos8;              // 8 * (column where the next run starts)
     uint32_t ent, ent_n, flips_n, c1, c2;  // the pipeline: entry of codeword ci, entry of ci + 1 as read and the
@@ -90,7 +99,7 @@ struct RingDecoder {
 
 __device__ __forceinline__ u32x4 ring_piece_at(const RingDecoder &d, uintptr_t at)
 {
-    // pieces past the lane's last one re-read the last (never used: `left` runs out first)
+    // pieces past the lane's last one re-read the last (never used: `end` comes first)
     return *(gp_u32x4)(at < d.last ? at : d.last);
 }
 
@@ -106,9 +115,23 @@ __device__ __forceinline__ uint32_t ring_code_at(const RingDecoder &d, uint32_t 
     return (uint32_t)(*(lp_u16)(uintptr_t)(d.slot + 2u * (i & 15u)));
 }
 
-__device__ __forceinline__ uint32_t ring_entry_index(uint32_t code, uint32_t n_groups, uint32_t n_order)
+// table index of a code, as order_entry2 takes it, and what the code's two low bits flip in the entry (bits 18 and 26 of the result; the
+// other bits are left to the caller's mask)
+__device__ __forceinline__ uint32_t ring_entry_index(uint32_t code, uint32_t n_groups3, uint32_t last)
 {
-    return min(max(code >> 2, __builtin_elementwise_sub_sat(code, 3u * n_groups)), n_order - 1u);
+    uint32_t i;
+    asm("v_med3_u32 %0, %1, %2, %3" : "=v"(i) : "v"(code >> 2), "v"(__builtin_elementwise_sub_sat(code, n_groups3)), "s"(last));
+    return i;
+}
+
+constexpr uint32_t kMmFlips = 0x04040000u;
+
+__device__ __forceinline__ uint32_t ring_flips(uint32_t code)
+{
+    const uint32_t two = code & 3u;
+    uint32_t f;
+    asm("v_lshl_or_b32 %0, %1, 25, %2" : "=v"(f) : "v"(two), "v"(two << 18));
+    return f;
 }
 
 // The lane's row (none: an empty stream), its window filled, its ring cleared.
@@ -116,7 +139,8 @@ __device__ __forceinline__ void ring_setup(RingDecoder &d, const qmoe_matrix &M,
                                            uint32_t slot)
 {
     const RowStream rst = row_stream(M, row, row_live);
-    d.left = rst.left;
+    d.end = rst.sub + rst.left;
+    d.lim = min(d.end, kMmWinAhead);
     d.pp = rst.pp;
     d.last = rst.last;
     d.pstr = rst.pstride;
@@ -137,14 +161,15 @@ __device__ __forceinline__ void ring_setup(RingDecoder &d, const qmoe_matrix &M,
 
 // Fill the pipeline.  Nothing is in flight afterwards, so that the wait at the top of a round is
 // for the two reads of the round before and not for the three stores issued after them.
-__device__ __forceinline__ void ring_prime(RingDecoder &d, lp_u32 table, uint32_t n_groups, uint32_t n_order)
+__device__ __forceinline__ void ring_prime(RingDecoder &d, lp_u32 table, uint32_t n_groups3, uint32_t last)
 {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    const uint32_t c0 = ring_code_at(d, d.ci);
     d.c1 = ring_code_at(d, d.ci + 1u);
     d.c2 = ring_code_at(d, d.ci + 2u);
-    d.ent = order_entry(table, ring_code_at(d, d.ci), n_groups, n_order);
-    d.ent_n = table[ring_entry_index(d.c1, n_groups, n_order)];
-    d.flips_n = order_flips(d.c1);
+    d.ent = table[ring_entry_index(c0, n_groups3, last)] ^ (ring_flips(c0) & kMmFlips);
+    d.ent_n = table[ring_entry_index(d.c1, n_groups3, last)];
+    d.flips_n = ring_flips(d.c1);
     asm volatile("" : "+v"(d.ent_n), "+v"(d.c1), "+v"(d.c2), "+v"(d.ent));
 }
 
@@ -153,7 +178,7 @@ __device__ __forceinline__ void ring_prime(RingDecoder &d, lp_u32 table, uint32_
 // then ends below column kc + 128, the first one that shares a ring byte with the step), so
 // the lanes of a wavefront, whose codewords end at different columns, seldom wait for each
 // other.  `after_wait` runs once, right after the step's wait for global memory: the place
-// to issue loads that should stay in flight for a whole step.
+// to issue loads that are wanted when the step has been decoded.
 //
 // The pipeline: nothing that was just read is used in the round that reads it (a select or a
 // sign flip on a fresh value would make the wavefront wait for it on the spot): a round's two
@@ -161,30 +186,33 @@ __device__ __forceinline__ void ring_prime(RingDecoder &d, lp_u32 table, uint32_
 // reads again what it already holds, and are used a round later; the entry of ci + 1 is kept
 // as read, next to the sign flips of its code's two low bits.
 template <int ASYM, class AfterWait>
-__device__ __forceinline__ void ring_decode_step(RingDecoder &d, lp_u32 table, uint32_t n_groups, uint32_t n_order, int kc,
+__device__ __forceinline__ void ring_decode_step(RingDecoder &d, lp_u32 table, uint32_t n_groups3, uint32_t last, int kc,
                                                  AfterWait &&after_wait)
 {
     const uint32_t lim8 = 8u * (uint32_t)(kc + kMmAhead), end8 = 8u * (uint32_t)(kc + kMmKc);
     bool first = true;
     do {
-        // Slide the window by one piece where its first piece is used up (once per step as a
-        // rule).  The other lanes fetch the piece they already wait for again, so that the
-        // load is unconditional and stays in flight until the next slide.
+        // Slide the window by one piece where its first piece is used up (a third of the lanes in a step, as a
+        // rule), and ask for the next one there.
         {
             const bool s8 = d.ci - d.wbase >= 8u;
-            if (s8) ring_store_piece(d, 2u * (d.wbase & 8u), d.fut);
-            d.wbase += s8 ? 8u : 0u;
-            d.pp += s8 ? d.pstr : (uintptr_t)0;
-            d.fut = ring_piece_at(d, d.pp + 2u * d.pstr);
-        }
-        if (first) {
-            first = false;
-            after_wait();
+            asm volatile("" : "+v"(d.fut));  // (the wait belongs here, ahead of after_wait's loads)
+            if (first) {
+                first = false;
+                after_wait();
+            }
+            if (s8) {
+                ring_store_piece(d, 2u * (d.wbase & 8u), d.fut);
+                d.wbase += 8u;
+                d.pp += d.pstr;
+                d.fut = ring_piece_at(d, d.pp + 2u * d.pstr);
+            }
+            d.lim = min(d.end, d.wbase + kMmWinAhead);
         }
         // (a loop with its test at the end: with the test in front the compiler keeps two copies of the
         // decoder's state and moves all of it from one to the other every round)
-        if (__any(d.left != 0u && d.pos8 < end8 && d.ci - d.wbase <= 12u)) do {
-            const bool go = d.left != 0u && d.pos8 <= lim8 && d.ci - d.wbase <= 12u;
+        if (__any(d.ci < d.lim && d.pos8 < end8)) do {
+            const bool go = d.ci < d.lim && d.pos8 <= lim8;
             // The entry this round applies; a lane that sits out applies an empty one, which stores
             // three zeros at the column where its next run starts: nothing was written there yet, and
             // it is never a column of the step being completed (kMmAhead keeps a lane's position below
@@ -193,10 +221,10 @@ __device__ __forceinline__ void ring_decode_step(RingDecoder &d, lp_u32 table, u
             // move on to codeword ci + go: its entry is the one read a round ago (go) or still e0,
             // the code after it c2 (go) or still c1; this round's reads go out before anything else
             const uint32_t csel = go ? d.c2 : d.c1;
-            d.ent = go ? (d.ent_n ^ d.flips_n) : d.ent;
+            d.ent = go ? (d.ent_n ^ (d.flips_n & kMmFlips)) : d.ent;
             d.ci += go ? 1u : 0u;
-            d.ent_n = table[ring_entry_index(csel, n_groups, n_order)];
-            d.flips_n = order_flips(csel);
+            d.ent_n = table[ring_entry_index(csel, n_groups3, last)];
+            d.flips_n = ring_flips(csel);
             d.c1 = csel;
             d.c2 = ring_code_at(d, d.ci + 2u);
             __builtin_amdgcn_sched_barrier(0);  // the round's two reads go out before the rest of its work
@@ -209,9 +237,8 @@ __device__ __forceinline__ void ring_decode_step(RingDecoder &d, lp_u32 table, u
                 *(lw_u8)(uintptr_t)(d.wrow + col) = (unsigned char)(ASYM ? (t & 6u) : (t << 5));
             }
             d.pos8 += e0 & 0xFFu;
-            d.left -= go ? 1u : 0u;
-        } while (__any(d.left != 0u && d.pos8 < end8 && d.ci - d.wbase <= 12u));
-    } while (__any(d.left != 0u && d.pos8 < end8));
+        } while (__any(d.ci < d.lim && d.pos8 < end8));
+    } while (__any(d.ci < d.end && d.pos8 < end8));
 }
 
 // The half of the ring that held step c becomes columns kc + 128 .. kc + 191: cleared after
@@ -263,42 +290,45 @@ __device__ __forceinline__ void mm_item(const ProductArgs &a, const qmoe_matrix 
 
     // ---- this lane's part of the activations: token 16 * mb + l16, columns 8 * lg .. 8 * lg + 7 of every 32
     uintptr_t xsrc[MB];
-    uint32_t xmul[MB];  // bytes from one column's value to the next column's, in units of 2: 1, or (tiled) the block's tokens
-    bool x_ok[MB];
+    uint32_t xmul2[MB];  // bytes from one column's value to the next column's: 2, or (tiled) 2 * the block's tokens
     const bool x_col = 8 * lg + 8 <= a.cols;
 #pragma unroll
     for (int mb = 0; mb < MB; mb++) {
         const int t = 16 * mb + l16;
-        x_ok[mb] = t < ntok;
-        xmul[mb] = 1u;
+        const bool x_ok = t < ntok;
+        xmul2[mb] = 2u;
         // (a lane whose columns do not exist -- fewer than 8 * lg + 8 columns -- reads column 0 and drops it;
         // a lane without a token reads the block's first token, or row 0)
         const size_t col0 = x_col ? 8 * (size_t)lg : (size_t)0;
-        if (a.x_tiled) {
+        if (EPI == 0 && a.x_tiled) {
             const int tb = min(16, ntok - 16 * mb);  // tokens in this block (<= 0: no such block)
             const size_t block0 = tb > 0 ? (size_t)(slot0 + 16 * mb) : (size_t)slot0;
-            const size_t j = x_ok[mb] ? (size_t)l16 : (size_t)0;
-            xmul[mb] = (uint32_t)max(tb, 1);
-            xsrc[mb] = reinterpret_cast<uintptr_t>(a.x) + 2 * (block0 * (size_t)a.ldx + col0 * (size_t)xmul[mb] + 8 * j);
+            const size_t j = x_ok ? (size_t)l16 : (size_t)0;
+            xmul2[mb] = 2u * (uint32_t)__builtin_amdgcn_readfirstlane(max(tb, 1));
+            xsrc[mb] = reinterpret_cast<uintptr_t>(a.x) + 2 * (block0 * (size_t)a.ldx + 8 * j) + col0 * (size_t)xmul2[mb];
         } else {
             size_t xrow = 0;
-            if (x_ok[mb]) {
+            if (x_ok) {
                 const int tok = a.perm ? a.perm[slot0 + t] : slot0 + t;
                 xrow = a.x_by_slot ? (size_t)(slot0 + t) : (size_t)tok;
             }
             xsrc[mb] = reinterpret_cast<uintptr_t>(a.x) + 2 * (xrow * (size_t)a.ldx + col0);
         }
-        x_ok[mb] = x_ok[mb] && x_col;
     }
-    // Loads are unconditional (a lane without a token, or past the last column, reads a valid
-    // address -- column 8 * lg of some row -- and drops the value): a load under a branch would
-    // be waited for at the end of the branch instead of staying in flight.
+    // A step's activations are asked for before its weights are decoded and arrive meanwhile.  What a lane without a token brings is some other row's and multiplies into a result nobody writes.
+    // Only a last step of fewer than 64 columns looks at its columns: a lane past the last one reads column 8 * lg and
+    // drops it.
     const int x_last = x_col ? a.cols - 8 * lg - 8 : 0;  // last column offset this lane may read at
-    auto load_x = [&](int mb, int k) -> u32x4 {
-        return *(gp_u32x4)(xsrc[mb] + 2 * (uintptr_t)xmul[mb] * (uintptr_t)min(k, x_last));
-    };
-    auto keep_x = [&](int mb, const u32x4 &v, int k) -> u32x4 {
-        return (x_ok[mb] && k <= x_last) ? v : u32x4{0u, 0u, 0u, 0u};
+    u32x4 xa[MB][2];
+    uint32_t x_end[MB];  // x_last in bytes
+#pragma unroll
+    for (int mb = 0; mb < MB; mb++) x_end[mb] = (uint32_t)x_last * xmul2[mb];
+    auto fetch_x = [&](int k) {
+#pragma unroll
+        for (int mb = 0; mb < MB; mb++)
+#pragma unroll
+            for (int ks = 0; ks < 2; ks++)
+                xa[mb][ks] = *(gp_u32x4)(xsrc[mb] + (uintptr_t)min((uint32_t)(k + 32 * ks) * xmul2[mb], x_end[mb]));
     };
 
     f32x4 acc[MB][4];
@@ -321,32 +351,25 @@ __device__ __forceinline__ void mm_item(const ProductArgs &a, const qmoe_matrix 
     }
     const uint32_t wfrag = wt + (uint32_t)((64 * wave + l16) * kMmWRowBytes + 8 * lg);
     const int nsteps = (a.cols + kMmKc - 1) / kMmKc;
-    const uint32_t n_groups = (uint32_t)a.n_groups, n_order = (uint32_t)a.n_order;
+    const uint32_t n_groups3 = 3u * (uint32_t)a.n_groups, last = (uint32_t)a.n_order - 1u;
 
-    ring_prime(dec, table, n_groups, n_order);
-
-    u32x4 xa[MB][2];
-#pragma unroll
-    for (int mb = 0; mb < MB; mb++)
-#pragma unroll
-        for (int ks = 0; ks < 2; ks++) xa[mb][ks] = keep_x(mb, load_x(mb, 32 * ks), 32 * ks);
+    ring_prime(dec, table, n_groups3, last);
 
     for (int c = 0; c < nsteps; c++) {
         const int kc = c * kMmKc;
-        // ---- decode until every lane has passed column kc + 64; the next step's activations are
-        // fetched right after the window's wait, a whole step ahead
-        u32x4 xn[MB][2];
-        ring_decode_step<ASYM>(dec, table, n_groups, n_order, kc, [&]() {
-            int k_next = kc + kMmKc;
-            asm volatile("" : "+s"(k_next));
-#pragma unroll
-            for (int mb = 0; mb < MB; mb++)
-#pragma unroll
-                for (int ks = 0; ks < 2; ks++) xn[mb][ks] = load_x(mb, k_next + 32 * ks);
-        });
+        // ---- decode until every lane has passed column kc + 64
+        ring_decode_step<ASYM>(dec, table, n_groups3, last, kc, [&]() { fetch_x(kc); });
         // the rows this wavefront multiplies are the ones its own lanes wrote
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
+
+        if (kc + kMmKc > a.cols) {
+            asm volatile("");  // (a branch, not selects in every step)
+#pragma unroll
+            for (int mb = 0; mb < MB; mb++)
+#pragma unroll
+                for (int ks = 0; ks < 2; ks++) xa[mb][ks] = x_col && kc + 32 * ks <= x_last ? xa[mb][ks] : u32x4{0u, 0u, 0u, 0u};
+        }
 
         // ---- multiply step c
         const uint32_t wf = wfrag + (uint32_t)((c & 1) * kMmKc);
@@ -372,10 +395,6 @@ __device__ __forceinline__ void mm_item(const ProductArgs &a, const qmoe_matrix 
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
         ring_clear_half(dec, c);
-#pragma unroll
-        for (int mb = 0; mb < MB; mb++)
-#pragma unroll
-            for (int ks = 0; ks < 2; ks++) xa[mb][ks] = keep_x(mb, xn[mb][ks], kc + kMmKc + 32 * ks);
     }
 
     // accumulator v of lane l: token 16 * mb + 4 * (l / 16) + v, row 16 * nb + l % 16 of the wavefront's 64

@@ -1,0 +1,39 @@
+"""The matrix-core product at the edges of its steps: columns that do not fill a step of 64, token tiles
+of one block, of two, of four and their remainders, rows that end inside a wavefront's 64, rows without codewords to
+spare and rows of very different lengths next to each other."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2310_16795_amd as q
+from paper_2310_16795_amd import device as dev
+from paper_2310_16795_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("cols", [8, 24, 32, 56, 64, 72, 128, 200, 1000])
+@pytest.mark.parametrize("minmax", [False, True])
+def test_partial_steps_and_tiles(oracle_dict, cols, minmax):
+    gpu = "cuda:0"
+    rows = 70
+    tern = np.concatenate([synth.ternary(51, 24, cols, 0.3), synth.ternary(52, 23, cols, 0.9), synth.ternary(53, 23, cols, 1.0)])
+    tern = tern[np.random.default_rng(5).permutation(rows)]
+    scale = None if minmax else synth.uniform_f16(54, (rows,), 0.01, 0.1)
+    mm = synth.minmax_bf16(55, rows, 0.01, 0.1) if minmax else None
+    codes, row_off = oracle.encode(oracle_dict, tern)
+    dd = dev.DeviceDict(q.qmoe_dict_from_words(oracle_dict.words), gpu)
+    M = dev.DeviceMatrix(codes, row_off, scale, rows, cols, device=gpu, device_order_of=dd, minmax_bf16=mm)
+    q.qmoe_set_tuning("mfma_min_tokens", 1)
+    try:
+        for batch in (1, 15, 17, 32, 33, 63, 64, 130):
+            x = synth.normal_bf16(56 + batch, (batch, cols))
+            y = torch.full((batch, rows), float("nan"), dtype=torch.float32, device=gpu)
+            q.qmoe_decode_matvec(dd.handle, M.desc, torch.from_numpy(x.view(np.int16).copy()).to(gpu), y)
+            torch.cuda.synchronize()
+            y_ref, bound = oracle.matvec(tern, scale, x, with_bound=True, minmax_bf16=mm)
+            assert (np.abs(y.cpu().numpy().astype(np.float64) - y_ref) <= 1e-3 * bound + 1e-30).all(), batch
+    finally:
+        q.qmoe_set_tuning("mfma_min_tokens", 0)
+        dd.close()
