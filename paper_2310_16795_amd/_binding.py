@@ -33,6 +33,8 @@ class qmoe_matrix(Structure):
                 ("minmax_bf16", c_void_p), ("wave_off", c_void_p), ("lanes", c_uint32), ("reserved", c_uint32)]
 
 
+_MATRIX_BYTES = ctypes.sizeof(qmoe_matrix)
+
 FORMAT_DEVICE_ORDER = 1
 FORMAT_GRID_MINMAX = 2
 
@@ -133,9 +135,22 @@ def _dev_ptr(t) -> int:
 
 def _stream_ptr(stream) -> int:
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        return _current_stream()
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
+
+
+def _current_stream() -> int:
+    """The current stream of the current GPU.  torch.cuda.current_stream() builds an object around it, 2.8 us, a third of
+    the shortest call; its handle alone is asked for where this torch has the function."""
+    global _current_stream
+    import torch
+    ptr = torch.cuda.current_stream().cuda_stream  # (also makes sure that torch has started the GPU)
+    raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+    if raw and device:
+        _current_stream = lambda: raw(device())
+    else:
+        _current_stream = lambda: torch.cuda.current_stream().cuda_stream
+    return ptr
 
 
 # ------------------------------------------------------------------ dictionary
@@ -226,8 +241,9 @@ def qmoe_validate_host(d: int, codes: np.ndarray, row_off: np.ndarray, rows: int
 
 def qmoe_decode_matvec(d: int, W: qmoe_matrix, x_bf16, y, stream=None) -> None:
     """x_bf16: device int16/uint16/bfloat16 [batch, cols]; y: device float32 [batch, rows]."""
-    batch = x_bf16.shape[0]
-    if x_bf16.shape[1] != W.cols or tuple(y.shape) != (batch, W.rows):
+    shape = x_bf16.shape
+    batch = shape[0]
+    if shape[1] != W.cols or y.shape != (batch, W.rows):
         raise ValueError("shape mismatch")
     if x_bf16.element_size() != 2 or y.element_size() != 4:
         raise ValueError("x must be 16-bit, y 32-bit")
@@ -252,10 +268,11 @@ def qmoe_moe_layer_workspace(n_experts: int, d_model: int, d_ff: int, n_tokens: 
 
 
 def _layer_shapes(wi_dev, wo_dev, n_experts, d_model, x_bf16, expert_idx, y) -> int:
-    n_tokens = x_bf16.shape[0]
-    if x_bf16.shape[1] != d_model or tuple(y.shape) != (n_tokens, d_model) or expert_idx.numel() != n_tokens:
+    shape = x_bf16.shape
+    n_tokens = shape[0]
+    if shape[1] != d_model or y.shape != (n_tokens, d_model) or expert_idx.numel() != n_tokens:
         raise ValueError("shape mismatch")
-    need = ctypes.sizeof(qmoe_matrix) * n_experts
+    need = _MATRIX_BYTES * n_experts
     if wi_dev.numel() * wi_dev.element_size() < need or wo_dev.numel() * wo_dev.element_size() < need:
         raise ValueError("expert descriptor arrays too small")
     return n_tokens
@@ -278,12 +295,7 @@ def qmoe_moe_layer_forward(d: int, wi_dev, wo_dev, code_order: int, n_experts: i
                            x_bf16, expert_idx, gate, y, workspace, stream=None, side_stream=None) -> None:
     """wi_dev / wo_dev: device byte tensors holding n_experts qmoe_matrix structs.
     side_stream: a second stream of the caller's for the scalar kernels (None: the library's own)."""
-    n_tokens = x_bf16.shape[0]
-    if x_bf16.shape[1] != d_model or tuple(y.shape) != (n_tokens, d_model) or expert_idx.numel() != n_tokens:
-        raise ValueError("shape mismatch")
-    need = ctypes.sizeof(qmoe_matrix) * n_experts
-    if wi_dev.numel() * wi_dev.element_size() < need or wo_dev.numel() * wo_dev.element_size() < need:
-        raise ValueError("expert descriptor arrays too small")
+    n_tokens = _layer_shapes(wi_dev, wo_dev, n_experts, d_model, x_bf16, expert_idx, y)
     _check(lib().qmoe_moe_layer_forward(d, _dev_ptr(wi_dev), _dev_ptr(wo_dev), code_order, n_experts, d_model, d_ff,
                                         _dev_ptr(x_bf16), _dev_ptr(expert_idx), _dev_ptr(gate), n_tokens,
                                         _dev_ptr(y), _dev_ptr(workspace),

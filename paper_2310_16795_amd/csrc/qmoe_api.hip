@@ -8,10 +8,28 @@ namespace qmoe {
 
 std::atomic<int> g_last_hip_error{0};
 
+// The permission belongs to the function on the current GPU and lasts: the runtime is asked only when a kernel wants more
+// than it was given before (asking costs the host as much as planning a call does).
 qmoe_status allow_lds_bytes(const void *kernel, size_t smem)
 {
-    if (smem > 48 * 1024)
-        QMOE_HIP_TRY(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
+    if (smem <= 48 * 1024) return QMOE_OK;
+    struct Allowed {
+        const void *kernel;
+        int dev;
+        size_t bytes;
+    };
+    static std::vector<Allowed> allowed;  // an entry per kernel and GPU, a few dozen at most
+    static std::mutex mu;
+    int dev = 0;
+    QMOE_HIP_TRY(hipGetDevice(&dev));
+    std::lock_guard<std::mutex> lock(mu);
+    Allowed *mine = nullptr;
+    for (Allowed &a : allowed)
+        if (a.kernel == kernel && a.dev == dev) mine = &a;
+    if (mine && mine->bytes >= smem) return QMOE_OK;
+    QMOE_HIP_TRY(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
+    if (mine) mine->bytes = smem;
+    else allowed.push_back({kernel, dev, smem});
     return QMOE_OK;
 }
 
@@ -534,7 +552,7 @@ qmoe_status qmoe_decode_matvec(const qmoe_dict *d, const qmoe_matrix *W, const u
     // in LDS, and the matrix cores, which decode the matrix once per 64 tokens (their unit of work is 64 rows of a token
     // tile, taken by one wavefront: a unit's time is set by the length of a row, not by how many units there are).  The
     // one with the lowest estimate is taken; measured on this GPU, microseconds a call (back-to-back calls are bound by
-    // the launch rate, about 7.5):
+    // the launch rate, about 4.5):
     //  - 16 lanes per row: tiles of eight tokens at 1.3 million weights per microsecond with one workgroup resident
     //    per compute unit (long rows: the tile's activations fill the LDS), about three times that with three or more;
     //  - several lanes per row: 8.8 (10.5 on the asymmetric grid) and 48 million weights times tokens per microsecond, from
@@ -544,7 +562,7 @@ qmoe_status qmoe_decode_matvec(const qmoe_dict *d, const qmoe_matrix *W, const u
     const int n_order = (int)d->order_table.size();
     const double weights = (double)W->rows * W->cols;
     const int resident = (int)std::max<size_t>(1, std::min<size_t>(3, (size_t)di.max_lds / xs_bytes(8)));
-    const double t_matvec = std::max(7.5, 4.0 + std::ceil(batch / 8.0) * weights / (1.3e6 * resident));
+    const double t_matvec = 4.0 + std::ceil(batch / 8.0) * weights / (1.3e6 * resident);
     double t_rows = 1e30, t_mm = 1e30;
     int slots = 0;
     if (code_order == 1 && run && n_order > 0 && tu.rows >= 0 && tu.token_tile == 0) {
