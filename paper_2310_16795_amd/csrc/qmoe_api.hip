@@ -751,7 +751,7 @@ qmoe_status layer_forward(const qmoe_dict *d, const qmoe_matrix *wi, const qmoe_
     RowsPlan rp;
     if (pwi.tb_max == pwo.tb_max) rp = rows_plan(d, code_order, lanes_wi, d_model, d_ff, n_tokens, pwi.tb_max);
     // In a small call the kernel with several lanes per row groups the tokens itself.
-    const bool grouping = rp.on && !mm && rows_can_dispatch(n_experts, n_tokens, rp.grid);
+    const bool grouping = rp.on && !mm && rows_can_dispatch(n_experts, n_tokens, rp.grid, n_order, rp.max_lds);
     const DispatchArgs da = dispatch_args(expert_idx, n_tokens, n_experts, d_model, lp, pwi.tb_max, pwo.tb_max, mp.min_tokens, y);
     if ((phases & 1) && !grouping)
         if ((st = launch_dispatch_kernel(da, s)) != QMOE_OK) return st;

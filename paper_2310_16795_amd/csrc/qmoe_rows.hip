@@ -682,10 +682,13 @@ int rows_tile_slots(int cols, int tb, int n_order, int max_lds)
     return fixed + 2 * tile <= (size_t)max_lds ? 2 : (fixed + tile <= (size_t)max_lds ? 1 : 0);
 }
 
-bool rows_can_dispatch(int n_experts, int n_tokens, int grid)
+bool rows_can_dispatch(int n_experts, int n_tokens, int grid, int n_order, int max_lds)
 {
     // (a share then spans at most n_tokens / grid + 2 items: all items cost at least what one token's does)
-    return n_tokens <= kInlineTokens && n_tokens <= (kKeptSegments - 2) * grid && 4 * (size_t)n_experts * ((n_tokens + 31) / 32) <= kInlineMaskBytes;
+    if (n_tokens > kInlineTokens || n_tokens > (kKeptSegments - 2) * grid) return false;
+    // The table is in LDS already when the lists are made: with the paper's they fit up to about 12000 experts and 32 tokens.
+    return 4 * (size_t)n_experts * ((n_tokens + 31) / 32) <= kInlineMaskBytes &&
+           rows_fixed_bytes(n_order) + inline_lds_bytes(n_experts, n_tokens) <= (size_t)max_lds;
 }
 
 RowsSplit rows_split(int rows, int x_slots, int grid)
