@@ -46,7 +46,10 @@ __global__ __launch_bounds__(64 * kDcMaxWaves) void k_decompress(const Decompres
     const uint32_t ring = rings + (uint32_t)((wave * kDcRows + mine) * kDcRowBytes);  // this lane's row
     for (uint32_t i = 8u * (uint32_t)tid; i < (uint32_t)(waves * kDcRows * kDcRowBytes); i += 8u * blockDim.x)
         *(lw_u64)(uintptr_t)(rings + i) = 0ull;
-    const uint32_t n_groups3 = 3u * (uint32_t)a.n_groups, last = (uint32_t)a.n_order - 1u;
+    const uint32_t n_groups3 = 3u * (uint32_t)a.n_groups, last = (uint32_t)a.n_order - 1u, cols8 = 8u * (uint32_t)a.cols;
+    // (a table too small for the index of every codeword: an unknown one may read other bytes as an entry, whose weights
+    // need not lie inside its run)
+    const bool any_entry = last < 0xFFFFu >> 2;
 
     // Which matrices have a destination: one bit each, so that the units of those that are asked for are dealt out.
     using lw_mask = __attribute__((address_space(3))) unsigned long long *;
@@ -117,7 +120,7 @@ __global__ __launch_bounds__(64 * kDcMaxWaves) void k_decompress(const Decompres
                 return *(gp_u32)(rs.pp + rs.pstride * (uintptr_t)(at >> 2) + 4u * (uintptr_t)(at & 3));
             };
             uint32_t v = load(sub);
-            bool more = true;
+            bool more = true, over = false;  // over: the row's stream (a corrupt one) has run past its width
             for (int h0 = 0; more; h0 += kDcLanes) {
                 const int h = h0 + sub;
                 const uint32_t v_next = load(h + kDcLanes);
@@ -132,6 +135,7 @@ __global__ __launch_bounds__(64 * kDcMaxWaves) void k_decompress(const Decompres
                 const uint32_t incl = lanes_scan(len8, kDcLanes, sub);
                 uint32_t p = pos8 + incl - len8;
                 pos8 += (uint32_t)__shfl((int)incl, lane | (kDcLanes - 1), 64);
+                over |= pos8 > cols8;
 #pragma unroll
                 for (int j = 0; j < 2; j++) {
                     // (an entry's unused fields come first and store a zero at the run's first column, ahead of its weights)
@@ -182,6 +186,12 @@ __global__ __launch_bounds__(64 * kDcMaxWaves) void k_decompress(const Decompres
                         }
                     }
                 }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+            }
+            // What such a row left in its ring behind its last column would be weights of the ring's next row.
+            if (any_entry || __any(over)) {
+                for (int i = 8 * sub; i < kDcRing; i += 8 * kDcLanes) *(lw_u64)(uintptr_t)(ring + (uint32_t)i) = 0ull;
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
                 __builtin_amdgcn_wave_barrier();
             }

@@ -50,3 +50,38 @@ def test_edges(rows, cols, p0, lanes):
         assert np.array_equal(got if kind == 0 else got.view(np.uint16), want[kind])
         assert (host[:at] == 77).all() and (host[at + rows * cols:] == 77).all()
     dd.close()
+
+
+@pytest.mark.parametrize("kind", [0, 1, 2])
+def test_stream_past_its_width_spoils_no_other_row(kind):
+    """Two matrices whose every row runs on to ten times the width they are described with, and two sound ones that the same
+    wavefronts take after them: the sound ones come out whole."""
+    gpu, rows, cols = "cuda:0", 4096, 64
+    dd = dev.DeviceDict(device=gpu)
+    long = synth.ternary(3, rows, 10 * cols, 0.9)
+    sound = synth.ternary(4, rows, cols, 0.9)
+    scale, pairs = synth.uniform_f16(6, (rows,), 0.01, 0.1), synth.minmax_bf16(5, rows, 0.01, 0.1)
+    desc, keep = (q.qmoe_matrix * 4)(), []
+    for i, tern in ((0, long), (2, sound)):
+        codes, off = q.qmoe_encode_host(dd.handle, tern)
+        M = dev.DeviceMatrix(codes, off, None if kind == 2 else scale, rows, cols, device=gpu, device_order_of=dd,
+                             minmax_bf16=pairs if kind == 2 else None)
+        desc[i] = desc[i + 1] = M.desc
+        keep.append(M)
+    d_desc = torch.from_numpy(np.frombuffer(bytes(desc), dtype=np.uint8).copy()).to(gpu)
+    out = torch.full((6, rows, cols), 77, dtype=torch.int8 if kind == 0 else torch.int16, device=gpu)
+    ptrs = torch.tensor([out[i].data_ptr() for i in range(1, 5)], dtype=torch.int64, device=gpu)
+    print(f"kind {kind}", flush=True)
+    q.qmoe_decompress(dd.handle, d_desc, q.FORMAT_DEVICE_ORDER | (q.FORMAT_GRID_MINMAX if kind == 2 else 0), 4, rows, cols, min(kind, 1),
+                      ptrs)
+    torch.cuda.synchronize()
+    host = out.cpu().numpy()
+    sb = scale.view(np.float16).astype(np.float32).view(np.uint32)
+    sb = ((sb + 0x7FFF + ((sb >> 16) & 1)) >> 16).astype(np.uint16)[:, None]
+    want = (sound if kind == 0 else
+            np.where(sound == 0, 0, np.where(sound > 0, sb, sb | 0x8000)).astype(np.uint16) if kind == 1 else
+            np.where(sound == 0, 0, np.where(sound > 0, pairs[:, 1:2], pairs[:, 0:1])).astype(np.uint16))
+    for i in (3, 4):
+        assert np.array_equal(host[i].view(want.dtype), want), i
+    assert (host[0] == 77).all() and (host[5] == 77).all()
+    dd.close()
