@@ -92,3 +92,23 @@ def test_single_matrix(gpu, ddict, oracle_dict, rows, cols, p0, batch, minmax):
     torch.cuda.synchronize()
     y_ref, bound = oracle.matvec(tern, scale, x, with_bound=True, minmax_bf16=pairs)
     _check_product(y.cpu().numpy(), y_ref, bound, f"{rows}x{cols}")
+
+
+@pytest.mark.parametrize("T,d_model", [(1, 40), (33, 258), (512, 130), (511, 2050)])
+@pytest.mark.parametrize("keep", [0, 5])
+def test_tokens_without_an_expert(gpu, ddict, oracle_dict, T, d_model, keep):
+    """Nearly all of a call's tokens, and all of them: zero rows, and the others as ever."""
+    E = 6
+    w = synth.WORKLOADS["switch_base128"].scaled(n_experts=E, d_model=d_model, d_ff=96, n_tokens=T)
+    x = w.tokens()
+    idx = np.where(np.arange(T) % 2, -1, E).astype(np.int32)
+    idx[::max(1, T // keep) if keep else T + 1] = 2
+    if keep == 0:
+        idx[0] = 2 ** 31 - 1
+    layer = _build_layer(w, oracle_dict, gpu, order_of=ddict)
+    print(f"{T} tokens of {d_model}, {keep}", flush=True)
+    y, wsout = _run_layer(layer, ddict, x, idx, gpu)
+    kept = [t for t in range(T) if idx[t] == 2]
+    assert len(kept) <= 6 and wsout["counters"][0] == len(kept) and wsout["counters"][1] == T - len(kept)
+    assert not y[[t for t in range(T) if idx[t] != 2]].any()  # (the output held NaN before the call)
+    _check_layer(w, idx, x, y, wsout, kept)
