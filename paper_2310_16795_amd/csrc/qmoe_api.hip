@@ -363,6 +363,54 @@ qmoe_status check_matrix_args(const qmoe_dict *d, const qmoe_matrix *W)
     return QMOE_OK;
 }
 
+// What a single-matrix call costs on each of its three kernels, in microseconds (back-to-back calls; below about 4.8 they
+// are bound by the launch rate): 16 lanes per row with the table in L2, the shortest start; several lanes per row with the
+// table in LDS; and the matrix cores, which decode the matrix once per 64 tokens.  What a kernel has to do goes by codewords,
+// not by weights: a row of 6144 columns has 265 at 90 % zeros and 431 at 80 %.
+// Fitted to all three kernels' times at 5766 points (88 shapes from 500 x 500 to 6200 x 6200, 80, 88.5, 90 and 92 % zeros and
+// rows of mixed sparsity, both grids, 1 to 500 tokens) so that the choice, rather than the time, comes out right: the kernel
+// taken is within 5 % of the fastest at 98.5 % of them.  (Estimates by weights, calibrated at 90 % zeros: at 89 %, and up to
+// 39 % slower than 16 lanes per row where those are the better kernel.)
+struct MatvecCosts {
+    double lanes16, rows, mm;
+};
+
+MatvecCosts matvec_costs(const qmoe_matrix &W, int batch, int tile, const DeviceInfo &di)
+{
+    const double cus = di.cus, codes = (double)W.n_codes, per_row = codes / W.rows, cols = W.cols;
+    MatvecCosts c;
+    {
+        // An item is 16 rows of a tile of up to eight tokens: its activations are staged, its rows decoded, and its time is
+        // a latency, a little longer the more of them share a compute unit.  They run in rounds of as many workgroups as
+        // are resident (LDS of a tile's activations, in the hardware's steps of 1280 bytes; six at most), which mix.  A last
+        // tile of one token is done between the others.
+        const size_t lds = ((size_t)(W.cols + kPadCols) * 2 * (size_t)std::max(tile, 4) + 1279) / 1280 * 1280;
+        const double resident = (double)std::max<size_t>(1, std::min<size_t>(6, (size_t)di.max_lds / lds));
+        const double row_blocks = (W.rows + 15) / 16;
+        const int whole = batch / tile, rest = batch % tile;
+        const double items = row_blocks * (whole ? whole + (rest > 1 ? 1 : 0) : 1.0);
+        const double x = items / (cus * resident), rounds = x <= 1.0 ? 1.0 : 0.5 * (x + std::ceil(x));
+        const double share = std::min(resident, std::ceil(items / cus));
+        const double small = batch <= 1 ? 0.49 : (batch <= 4 ? 0.8 : 1.0);
+        const double item = (0.0305 * per_row + 0.00123 * cols) * small + share * (0.001 * per_row + 0.000066 * cols);
+        c.lanes16 = 2.7 + item * rounds + 4.5 * (rounds - 1.0);
+    }
+    {
+        // the table's way to LDS, then codewords times tiles of four tokens, evenly over the compute units
+        const double tiles = batch > 2 ? std::ceil(batch / 4.0) : 1.0;
+        const double start = batch <= 1 ? 9.15 : 9.8;
+        const double code = batch <= 1 ? 0.0002 : (batch <= 2 ? 0.00041 : 0.00054);
+        c.rows = start + (W.minmax_bf16 ? 2.7 : 0.0) + code * codes * tiles / cus;
+    }
+    {
+        // a unit of 64 rows and 64 tokens on one wavefront: the length of a row, longer the more wavefronts share a compute unit
+        const double units = std::ceil((double)batch / kMmTokens) * ((W.rows + 63) / 64), waves = kMmThreads / 64;
+        const double per_cu = std::ceil(units / cus), rounds = std::ceil(per_cu / waves), share = std::min(per_cu, waves);
+        c.mm = 5.4 + rounds * (per_row * (0.1135 + 0.0177 * share) + cols * (0.0075 + 0.0014 * share)) * (W.minmax_bf16 ? 1.05 : 1.0);
+    }
+    return c;
+}
+
 void fill_tables(const qmoe_dict *d, ProductArgs *a, int code_order)
 {
     const unsigned char *base = static_cast<const unsigned char *>(d->dev);
@@ -548,36 +596,23 @@ qmoe_status qmoe_decode_matvec(const qmoe_dict *d, const qmoe_matrix *W, const u
     a.cols = W->cols;
     a.tb_max = tb;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    // Three kernels: 16 lanes per row with the table in L2 (the shortest start), several lanes per row with the table
-    // in LDS, and the matrix cores, which decode the matrix once per 64 tokens (their unit of work is 64 rows of a token
-    // tile, taken by one wavefront: a unit's time is set by the length of a row, not by how many units there are).  The
-    // one with the lowest estimate is taken; measured on this GPU, microseconds a call (back-to-back calls are bound by
-    // the launch rate, about 4.5):
-    //  - 16 lanes per row: tiles of eight tokens at 1.3 million weights per microsecond with one workgroup resident
-    //    per compute unit (long rows: the tile's activations fill the LDS), about three times that with three or more;
-    //  - several lanes per row: 8.8 (10.5 on the asymmetric grid) and 48 million weights times tokens per microsecond, from
-    //    768 x 3072 to 2080 x 6144 and from 8 to 500 tokens;
-    //  - matrix cores: a round (every wavefront of every compute unit with one unit of 64 tokens) about 8 + 0.0148 per column.
     const Tuning &tu = tuning();
     const int n_order = (int)d->order_table.size();
-    const double weights = (double)W->rows * W->cols;
-    const int resident = (int)std::max<size_t>(1, std::min<size_t>(3, (size_t)di.max_lds / xs_bytes(8)));
-    const double t_matvec = 4.0 + std::ceil(batch / 8.0) * weights / (1.3e6 * resident);
+    const bool ordered = code_order == 1 && run && n_order > 0;
+    const MatvecCosts cost = matvec_costs(*W, batch, tb, di);
     double t_rows = 1e30, t_mm = 1e30;
     int slots = 0;
-    if (code_order == 1 && run && n_order > 0 && tu.rows >= 0 && tu.token_tile == 0) {
+    if (ordered && tu.rows >= 0 && tu.token_tile == 0) {
         slots = rows_tile_slots(W->cols, 4, n_order, di.max_lds);
-        if (slots) t_rows = tu.rows > 0 ? 0.0 : (W->minmax_bf16 ? 10.5 : 8.8) + weights * batch / 48e6;
+        if (slots) t_rows = tu.rows > 0 ? 0.0 : cost.rows;
     }
-    const int tiles = (batch + kMmTokens - 1) / kMmTokens, waves = kMmThreads / 64;
-    const long long units = (long long)tiles * ((W->rows + 63) / 64);
-    if (code_order == 1 && run && n_order > 0 && tu.mfma_min_tokens >= 0 && W->cols % 8 == 0 &&
-        reinterpret_cast<uintptr_t>(x_bf16) % 16 == 0 && mm_lds_bytes(n_order) <= (size_t)di.max_lds) {
-        const long long blocks = (units + waves - 1) / waves;  // workgroups with every wavefront busy
-        t_mm = std::ceil((double)blocks / di.cus) * (8.0 + 0.0148 * W->cols);
+    const long long units = (long long)((batch + kMmTokens - 1) / kMmTokens) * ((W->rows + 63) / 64);
+    if (ordered && tu.mfma_min_tokens >= 0 && W->cols % 8 == 0 && reinterpret_cast<uintptr_t>(x_bf16) % 16 == 0 &&
+        mm_lds_bytes(n_order) <= (size_t)di.max_lds) {
+        t_mm = cost.mm;
         if (tu.mfma_min_tokens > 0) t_mm = batch >= tu.mfma_min_tokens ? -1.0 : 1e30;
     }
-    if (t_mm < std::min(t_rows, t_matvec)) {
+    if (t_mm < std::min(t_rows, cost.lanes16)) {
         a.minmax = W->minmax_bf16 ? 1 : 0;
         a.epilogue = 0;
         MmPlan mp;
@@ -585,7 +620,7 @@ qmoe_status qmoe_decode_matvec(const qmoe_dict *d, const qmoe_matrix *W, const u
         mp.grid = (int)std::min<long long>(units, di.cus);  // a unit per compute unit before a second per compute unit
         return launch_product_mm(a, mp, s);
     }
-    if (t_rows < t_matvec) {
+    if (t_rows < cost.lanes16) {
         a.tb_max = batch > 2 ? 4 : batch;
         a.minmax = W->minmax_bf16 ? 1 : 0;
         a.epilogue = 0;

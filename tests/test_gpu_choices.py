@@ -7,7 +7,7 @@ import oracle
 import paper_2310_16795_amd as q
 from paper_2310_16795_amd import device as dev
 from paper_2310_16795_amd import synth
-from test_gpu_parity import _build_layer, _check_layer, _run_layer
+from test_gpu_parity import _build_layer, _check_layer, _check_product, _run_layer, _to_dev16, _upload
 
 pytestmark = pytest.mark.gpu
 
@@ -44,3 +44,30 @@ def test_many_experts(gpu, ddict, oracle_dict, E, T):
     assert np.array_equal(wsout["tok_off"], tok_off) and np.array_equal(wsout["perm"][:len(valid)], perm)
     _check_layer(w, idx, x, y, wsout, valid[:12])
     assert not y[[t for t in range(T) if idx[t] >= E]].any()
+
+
+# Batches on both sides of the lines between the single-matrix call's three kernels (256 compute units): 16 lanes per row to
+# several, several to the matrix cores, 16 lanes to the matrix cores; widths where a tile's activations are resident
+# three times, twice and once, and a width no multiple of eight, which the matrix cores do not take.
+@pytest.mark.parametrize("rows,cols,p0,batches", [
+    (1040, 2080, 0.80, (1, 249, 250, 377, 378, 412, 413)), (2080, 1040, 0.90, (8, 9, 249, 250, 273, 274)), (2000, 512, 0.80, (193, 194, 201, 202)),
+    (1040, 2082, 0.80, (249, 413)), (600, 5096, 0.80, (1, 2, 64)), (300, 3400, 0.92, (4, 5, 65)), (40, 10300, 0.90, (4, 5, 9))])
+@pytest.mark.parametrize("minmax", [False, True])
+def test_single_matrix(gpu, ddict, oracle_dict, rows, cols, p0, batches, minmax):
+    tern = synth.ternary(rows + cols, rows, cols, p0)
+    scale = None if minmax else synth.uniform_f16(1, (rows,), 0.01, 0.1)
+    pairs = synth.minmax_bf16(2, rows, 0.01, 0.1) if minmax else None
+    M = _upload(oracle_dict, tern, scale, gpu, ddict, minmax=pairs)
+    x = synth.normal_bf16(3, (max(batches), cols))
+    some = sorted({0, 1, 7, 63, 64, 248, 249, *(b - 1 for b in batches)} & set(range(max(batches))))
+    y_ref, bound = oracle.matvec(tern, scale, x[some], with_bound=True, minmax_bf16=pairs)
+    for b in batches:
+        print(f"{rows}x{cols}, {b} tokens", flush=True)
+        y = torch.full((b, rows), float("nan"), dtype=torch.float32, device=gpu)
+        q.qmoe_decode_matvec(ddict.handle, M.desc, _to_dev16(x[:b], gpu), y)
+        torch.cuda.synchronize()
+        y = y.cpu().numpy()
+        assert np.isfinite(y).all()
+        for i, t in enumerate(some):
+            if t < b:
+                _check_product(y[t][None, :], y_ref[i][None, :], bound[i][None, :], f"{rows}x{cols} token {t} of {b}")
