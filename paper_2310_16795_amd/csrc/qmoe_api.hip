@@ -683,9 +683,8 @@ qmoe_status qmoe_decompress(const qmoe_dict *d, const qmoe_matrix *mats, int cod
     a.order_table = reinterpret_cast<const uint32_t *>(static_cast<const unsigned char *>(d->dev) + kDevOrderTableOffset);
     a.n_groups = d->n_groups;
     a.n_order = (int)d->order_table.size();
-    const size_t smem = decompress_lds_bytes(a.n_order, n_mats);
-    if (smem > (size_t)di.max_lds) return QMOE_E_LIMIT;  // (the paper's table leaves room for about 120000 matrices a call)
-    return launch_decompress(a, out_kind, minmax, di.cus, smem, static_cast<hipStream_t>(stream));
+    if (decompress_lds_bytes(a.n_order, n_mats) > (size_t)di.max_lds) return QMOE_E_LIMIT;  // (the paper's table leaves room for about 120000 matrices a call)
+    return launch_decompress(a, out_kind, minmax, di.cus, di.max_lds, static_cast<hipStream_t>(stream));
 }
 
 qmoe_status qmoe_moe_layer_ws_layout(int n_experts, int d_model, int d_ff, int n_tokens, qmoe_ws_layout *out)

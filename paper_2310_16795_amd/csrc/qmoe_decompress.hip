@@ -5,25 +5,28 @@
 namespace qmoe {
 namespace {
 
-// A wavefront takes two rows, 32 lanes each.  In a step every lane decodes a quarter of a 16-byte piece of its row (two
-// codewords; the column where they start by a prefix sum over the row's lanes) and stores the weights, one byte a
-// column, into the row's ring in LDS.  Whole 256-column groups then leave the ring: the lanes of a row write its 256
-// columns, 512 bytes in a run (int8: 256), and clear them.  A row's groups begin early by as many columns as it takes
-// for their ends to fall on multiples of that run in the row's destination.
+// A wavefront takes two rows, 32 lanes each (narrow matrices: eight rows of eight lanes each).  In a step every lane decodes
+// a quarter of a 16-byte piece of its row (two codewords; the column where they start by a prefix sum over the row's
+// lanes) and stores the weights, one byte a column, into the row's ring in LDS.  Whole groups of columns, eight a lane, then
+// leave the ring: the lanes of a row write its 256 columns, 512 bytes in a run (int8: 256), and clear them.  A row's groups
+// begin early by as many columns as it takes for their ends to fall on multiples of that run in the row's destination.
 //
 // Bound: the stores.  Per 64 codewords a compute unit has about 330 cycles of HBM write time (bf16) and the wavefront
 // about 150 of vector issue, so what counts is that every compute unit has rows to write all the time, to the end (small
 // units, the number of wavefronts chosen so that they divide evenly), and how the stores reach memory: runs of 128
 // bytes 3.4 TB/s, marked non-temporal (the matrices do not fit the caches, and the lines are whole) 4.0, runs of 512 bytes 4.3.
 // 12 experts of 2080 x 6144, both projections, to bf16 (613 MB; a fill takes 95 us): 331 us with the kernel before, which
-// gave a lane a row and a workgroup 512 rows (60 workgroups for the one projection, 144 for the other), now 136.
-constexpr int kDcLanes = 32;                      // lanes per row
-constexpr int kDcRows = 64 / kDcLanes;            // rows of a wavefront
-constexpr int kDcGroup = 8 * kDcLanes;            // columns the lanes of a row write at once
-// columns a row's ring holds: what is left of a group (kDcGroup - 1) and two codewords a lane (56 columns)
-constexpr int kDcRing = 64 * kDcLanes;
-constexpr int kDcRowBytes = kDcRing + 16;
+// gave a lane a row and a workgroup 512 rows (60 workgroups for the one projection, 144 for the other), now 134.
 constexpr int kDcMaxWaves = 16;
+constexpr int kDcWide = 32, kDcNarrow = 8;        // lanes per row
+template <int LANES>
+struct DcShape {
+    static constexpr int kRows = 64 / LANES;      // rows of a wavefront
+    static constexpr int kGroup = 8 * LANES;      // columns the lanes of a row write at once
+    // columns a row's ring holds: what is left of a group (kGroup - 1) and two codewords a lane (56 columns)
+    static constexpr int kRing = 64 * LANES;
+    static constexpr int kRowBytes = kRing + 16;
+};
 
 using lw_u8 = __attribute__((address_space(3))) unsigned char *;
 using lw_u64 = __attribute__((address_space(3))) unsigned long long *;
@@ -32,15 +35,17 @@ using gw_u32x4 = __attribute__((address_space(1))) u32x4 *;
 
 // OUT 0: int8 in {-1, 0, +1}; 1: bf16(scale of the row) with the weight's sign, or 0;
 // 2: the row's bf16 grid point w_max or w_min, or 0 (asymmetric grid)
-template <int OUT>
+template <int OUT, int kDcLanes>
 __global__ __launch_bounds__(64 * kDcMaxWaves) void k_decompress(const DecompressArgs a)
 {
+    constexpr int kDcRows = DcShape<kDcLanes>::kRows, kDcGroup = DcShape<kDcLanes>::kGroup, kDcRing = DcShape<kDcLanes>::kRing,
+                  kDcRowBytes = DcShape<kDcLanes>::kRowBytes;
     extern __shared__ __align__(16) unsigned char smem[];
     const size_t table_bytes = ((size_t)a.n_order * 4 + 15) & ~(size_t)15;
     uint32_t *table_w = reinterpret_cast<uint32_t *>(smem);
     stage_words(table_w, a.order_table, a.n_order);
     lp_u32 table = (lp_u32)table_w;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, waves = (int)blockDim.x >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), waves = (int)blockDim.x >> 6;
     const int sub = lane & (kDcLanes - 1), mine = lane / kDcLanes;
     const uint32_t rings = (uint32_t)(uintptr_t)(lw_u8)(smem + table_bytes);
     const uint32_t ring = rings + (uint32_t)((wave * kDcRows + mine) * kDcRowBytes);  // this lane's row
@@ -61,28 +66,49 @@ __global__ __launch_bounds__(64 * kDcMaxWaves) void k_decompress(const Decompres
         if (lane == 0) mask[w] = bits;
     }
     __syncthreads();
-    long long n_wanted = 0;
-    for (int w = 0; w < mask_words; w++) n_wanted += __popcll(mask[w]);
+    int n_wanted = 0;
+    for (int w = 0; w < mask_words; w += 64) n_wanted += w + lane < mask_words ? __popcll(mask[w + lane]) : 0;
+    n_wanted = __builtin_amdgcn_readlane(wave_inclusive_scan(n_wanted), 63);
     // Units of a matrix: kDcRows consecutive rows, or, in the lane-interleaved layout, the i-th rows of as many consecutive
     // lanes' row ranges (their pieces lie next to each other).  A wavefront takes every a.slots-th unit of a matrix: one, but
     // for the lane-interleaved layout of a matrix with rows that its lanes do not divide.
-    const long long total = n_wanted * a.slots;
     constexpr int kBpe = OUT == 0 ? 1 : 2, kRunBytes = kDcGroup * kBpe;
 
-    for (long long g = (long long)blockIdx.x * waves + wave; g < total; g += (long long)gridDim.x * waves) {
-        const int nth = (int)(g / a.slots), slot = (int)(g - (long long)nth * a.slots);
-        int m;
+    // The units of all wanted matrices are dealt out round robin.  A wavefront's next unit is `stride` units on: so many matrices
+    // and so many slots, known once, and the matrix is found from the place of the last one (with thousands of
+    // small matrices, a walk from the mask's first word and a division for every unit are most of a unit's time).
+    const int stride = (int)gridDim.x * waves;
+    const long long first = (long long)blockIdx.x * waves + wave;
+    const int d_nth = stride / a.slots, d_slot = stride - d_nth * a.slots;
+    int nth = (int)min(first / a.slots, (long long)n_wanted), slot = (int)(first - (long long)nth * a.slots);
+    int word = 0, skip = nth;                 // the matrix is the skip-th of the bits left in this word and the words after it
+    auto word_bits = [&](int w) -> unsigned long long {  // the same in every lane
+        const unsigned long long b = mask[w];
+        return (unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b) |
+               (unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32)) << 32;
+    };
+    unsigned long long bits = word_bits(0);
+    while (nth < n_wanted) {
+        for (;;) {
+            const int n = __popcll(bits);
+            if (skip < n) break;
+            skip -= n;
+            bits = word_bits(++word);
+        }
+        int m = 64 * word;
         {
-            int w = 0, rem = nth;
-            for (;; w++) {
-                const int n = __popcll(mask[w]);
-                if (rem < n) break;
-                rem -= n;
+            int at = 0;
+            unsigned long long rest = bits;
+#pragma unroll
+            for (int half = 32; half >= 1; half >>= 1) {
+                const int n = __popcll(rest & ((1ull << half) - 1ull));
+                const bool up = skip >= n;
+                skip -= up ? n : 0;
+                at += up ? half : 0;
+                rest >>= up ? half : 0;
             }
-            unsigned long long bits = mask[w];
-            for (int i = 0; i < rem; i++) bits &= bits - 1ull;
-            // (the same in every lane; said so, the matrix descriptor is read into scalar registers)
-            m = __builtin_amdgcn_readfirstlane(64 * w + (int)__ffsll((long long)bits) - 1);
+            bits &= ~0ull << at;              // this matrix and those after it
+            m = __builtin_amdgcn_readfirstlane(m + at);  // (the same in every lane; said so, its descriptor is read into scalar registers)
         }
         const uintptr_t out = reinterpret_cast<uintptr_t>(a.out[m]);
         const qmoe_matrix M = a.mats[m];
@@ -196,19 +222,33 @@ __global__ __launch_bounds__(64 * kDcMaxWaves) void k_decompress(const Decompres
                 __builtin_amdgcn_wave_barrier();
             }
         }
+        slot += d_slot;
+        skip = d_nth;
+        if (slot >= a.slots) {
+            slot -= a.slots;
+            skip++;
+        }
+        nth += skip;
     }
 }
 
 }  // namespace
 
-size_t decompress_lds_bytes(int n_order, int n_mats)
+template <int LANES>
+static size_t dc_lds_bytes(int n_order, int n_mats)
 {
-    return (((size_t)n_order * 4 + 15) & ~(size_t)15) + (size_t)kDcMaxWaves * kDcRows * kDcRowBytes + 8 * (((size_t)n_mats + 63) / 64);
+    return (((size_t)n_order * 4 + 15) & ~(size_t)15) + (size_t)kDcMaxWaves * DcShape<LANES>::kRows * DcShape<LANES>::kRowBytes +
+           8 * (((size_t)n_mats + 63) / 64);
 }
 
-qmoe_status launch_decompress(DecompressArgs a, int out_kind, bool minmax, int cus, size_t smem, hipStream_t s)
+size_t decompress_lds_bytes(int n_order, int n_mats) { return dc_lds_bytes<kDcWide>(n_order, n_mats); }
+
+template <int LANES>
+static qmoe_status launch_dc(DecompressArgs a, int out_kind, bool minmax, int cus, hipStream_t s)
 {
-    a.slots = (a.rows + kDcRows - 1) / kDcRows;
+    constexpr int kRows = DcShape<LANES>::kRows;
+    const size_t smem = dc_lds_bytes<LANES>(a.n_order, a.n_mats);
+    a.slots = (a.rows + kRows - 1) / kRows;
     // as few wavefronts as take the units in the same number of rounds
     const long long total = (long long)a.n_mats * a.slots, most = (long long)cus * kDcMaxWaves, rounds = (total + most - 1) / most;
     const int waves = (int)std::max(1LL, std::min<long long>(kDcMaxWaves, (total + cus * rounds - 1) / (cus * rounds)));
@@ -219,10 +259,24 @@ qmoe_status launch_decompress(DecompressArgs a, int out_kind, bool minmax, int c
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * waves), smem, s, a);
         return QMOE_OK;
     };
-    const qmoe_status st = out_kind == 0 ? launch(k_decompress<0>) : (minmax ? launch(k_decompress<2>) : launch(k_decompress<1>));
+    const qmoe_status st =
+        out_kind == 0 ? launch(k_decompress<0, LANES>) : (minmax ? launch(k_decompress<2, LANES>) : launch(k_decompress<1, LANES>));
     if (st != QMOE_OK) return st;
     QMOE_HIP_TRY(hipGetLastError());
     return QMOE_OK;
+}
+
+qmoe_status launch_decompress(const DecompressArgs &a, int out_kind, bool minmax, int cus, int max_lds, hipStream_t s)
+{
+    // A row of some hundred columns is one step of 32 lanes, most of them without a codeword, and a unit's trips to memory are
+    // most of its time: eight rows a wavefront, eight lanes each, make them a quarter as many.  To int8, 256 rows a matrix,
+    // wide and narrow: 2048 of 256 columns 131 and 60 us, 1024 of 512 columns 75 and 42, 682 of 768 columns 57 and 48, 512
+    // of 1024 columns 47 and 46; in a single round a row's length counts, and the lines cross at 384 to 512 columns (42
+    // matrices of 384: 7.7 and 7.2 us, 32 of 512: 6.8 and 7.8).
+    const bool rounds = (long long)a.n_mats * ((a.rows + 1) / 2) >= 4LL * cus * kDcMaxWaves;
+    if (a.cols <= (rounds ? 768 : 384) && dc_lds_bytes<kDcNarrow>(a.n_order, a.n_mats) <= (size_t)max_lds)
+        return launch_dc<kDcNarrow>(a, out_kind, minmax, cus, s);
+    return launch_dc<kDcWide>(a, out_kind, minmax, cus, s);
 }
 
 }  // namespace qmoe

@@ -171,7 +171,7 @@ qmoe_status launch_product_sym(const ProductArgs &a, const ProductPlan &p, bool 
 qmoe_status launch_product_asym(const ProductArgs &a, const ProductPlan &p, bool run, hipStream_t s);
 size_t mm_lds_bytes(int n_order);                                                                   // qmoe_product_mm.hip
 qmoe_status launch_product_mm(ProductArgs a, const MmPlan &mp, hipStream_t s);
-qmoe_status launch_decompress(DecompressArgs a, int out_kind, bool minmax, int cus, size_t smem, hipStream_t s);  // qmoe_decompress.hip
+qmoe_status launch_decompress(const DecompressArgs &a, int out_kind, bool minmax, int cus, int max_lds, hipStream_t s);  // qmoe_decompress.hip
 size_t decompress_lds_bytes(int n_order, int n_mats);  // table, rings, one bit per matrix
 qmoe_status launch_matvec_rows(const ProductArgs &a, bool run, bool minmax, int grid, int threads, size_t smem,
                                hipStream_t s);                                                      // qmoe_matvec.hip

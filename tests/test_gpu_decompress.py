@@ -12,6 +12,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("rows,cols,p0", [(1, 8, 0.9), (3, 248, 0.9), (5, 256, 0.0), (130, 264, 0.97), (67, 2048, 0.885), (65, 2056, 1.0),
+                                          (9, 384, 0.9), (9, 392, 0.9), (2, 512, 0.0), (33, 1000, 0.9),
                                           (9, 20000, 0.9)])
 @pytest.mark.parametrize("lanes", [0, 64, 192])
 def test_edges(rows, cols, p0, lanes):
@@ -49,6 +50,35 @@ def test_edges(rows, cols, p0, lanes):
         got = host[at: at + rows * cols].reshape(rows, cols)
         assert np.array_equal(got if kind == 0 else got.view(np.uint16), want[kind])
         assert (host[:at] == 77).all() and (host[at + rows * cols:] == 77).all()
+    dd.close()
+
+
+@pytest.mark.parametrize("n_mats,rows,cols", [(1500, 24, 40), (1800, 20, 768), (1800, 20, 776), (70, 3, 400), (5000, 2, 8)])
+@pytest.mark.parametrize("wanted", ["all", "some"])
+def test_many_matrices(n_mats, rows, cols, wanted):
+    """A wavefront goes from matrix to matrix through the ones that have a destination: many of them, none for hundreds in a row,
+    rows that no unit divides, widths on both sides of the lines between eight and 32 lanes per row."""
+    gpu, made = "cuda:0", 7
+    dd = dev.DeviceDict(device=gpu)
+    scale = synth.uniform_f16(6, (rows,), 0.01, 0.1)
+    terns = [synth.ternary(40 + i, rows, cols, 0.85) for i in range(made)]
+    mats = [dev.DeviceMatrix(*q.qmoe_encode_host(dd.handle, t), scale, rows, cols, device=gpu, device_order_of=dd) for t in terns]
+    desc = (q.qmoe_matrix * n_mats)(*[mats[m % made].desc for m in range(n_mats)])
+    rng = np.random.default_rng(n_mats)
+    want = np.ones(n_mats, bool) if wanted == "all" else rng.random(n_mats) < 0.3
+    if wanted == "some":
+        want[n_mats // 5: n_mats // 2] = False
+        want[-1] = True
+    at = np.flatnonzero(want)
+    out = torch.full((at.size + 1, rows, cols), 77, dtype=torch.int8, device=gpu)
+    ptrs = np.zeros(n_mats, dtype=np.int64)
+    ptrs[at] = out.data_ptr() + np.arange(at.size) * rows * cols
+    d_desc = torch.from_numpy(np.frombuffer(bytes(desc), dtype=np.uint8).copy()).to(gpu)
+    print(f"{n_mats} of {rows}x{cols}", flush=True)
+    q.qmoe_decompress(dd.handle, d_desc, q.FORMAT_DEVICE_ORDER, n_mats, rows, cols, 0, torch.from_numpy(ptrs).to(gpu))
+    torch.cuda.synchronize()
+    host = out.cpu().numpy()
+    assert np.array_equal(host[:-1], np.stack(terns)[at % made]) and (host[-1] == 77).all()
     dd.close()
 
 
