@@ -218,7 +218,7 @@ qmoe_status plan_product(int rows, int cols, bool run_table, long long max_passe
         };
         const int want_b = best_b;
         best_b = 0;
-        for (int d = 0; d <= force_lanes / 64 && !best_b; d++) {
+        for (int d = 0; d <= std::max(force_lanes / 64, want_b) && !best_b; d++) {
             if (fits(want_b + d)) best_b = want_b + d;
             else if (fits(want_b - d)) best_b = want_b - d;
         }

@@ -46,6 +46,17 @@ def test_many_experts(gpu, ddict, oracle_dict, E, T):
     assert not y[[t for t in range(T) if idx[t] >= E]].any()
 
 
+# Few lanes per matrix (256 and 192 here), and calls so small that their matrices would be split over more workgroups than that.
+@pytest.mark.parametrize("T", [1, 5, 40])
+def test_lanes_of_a_large_call_in_a_small_one(gpu, ddict, oracle_dict, T):
+    w = synth.WORKLOADS["switch_base128"].scaled(n_experts=2, d_model=520, d_ff=3002, n_tokens=T)
+    idx, x = w.expert_idx(), w.tokens()
+    layer = _build_layer(w, oracle_dict, gpu, order_of=ddict, lanes_for_tokens=4096)
+    print(f"{T} tokens, {layer.lanes} lanes", flush=True)
+    y, wsout = _run_layer(layer, ddict, x, idx, gpu)
+    _check_layer(w, idx, x, y, wsout, list(range(min(T, 8))))
+
+
 # Batches on both sides of the lines between the single-matrix call's three kernels (256 compute units): 16 lanes per row to
 # several, several to the matrix cores, 16 lanes to the matrix cores; widths where a tile's activations are resident
 # three times, twice and once, and a width no multiple of eight, which the matrix cores do not take.
