@@ -318,9 +318,7 @@ struct InlineLists {
 __device__ __forceinline__ size_t inline_mask_words(int E, int T) { return (size_t)E * ((T + 31) >> 5); }
 
 // `scratch`: LDS of inline_lds_bytes(E, T); `e` the expert of token threadIdx.x (-1: none).  Workgroup 0 also writes the lists
-// to the workspace.  The output rows of tokens without an expert are cleared by all workgroups, a row at a time and in whole
-// lines: a rank that holds a part of the experts has mostly such tokens (512 tokens, 448 of them without an expert, on experts
-// of 768 x 3072: 230 us when a thread of workgroup 0 cleared a row, 38 us now; 2080 x 6144: 559 and 89 us).
+// to the workspace.
 __device__ __forceinline__ InlineLists group_tokens(const DispatchArgs &d, int e, unsigned char *scratch)
 {
     const int T = d.n_tokens, E = d.n_experts, tid = threadIdx.x, nthr = blockDim.x;
@@ -329,7 +327,7 @@ __device__ __forceinline__ InlineLists group_tokens(const DispatchArgs &d, int e
     int *off = reinterpret_cast<int *>(mask + inline_mask_words(E, T));  // [E] first slot
     int *perm = off + E;                                                  // [T]
     uint32_t *items = reinterpret_cast<uint32_t *>(perm + T);             // [2 T]
-    int *tmp = reinterpret_cast<int *>(items + 2 * T);  // [17 * 3] scan scratch, then a bit per token without an expert
+    int *tmp = reinterpret_cast<int *>(items + 2 * T);                    // [17 * 3] scan scratch
     for (int i = tid; i < E * mw; i += nthr) mask[i] = 0u;
     __syncthreads();
     if (e >= 0) atomicOr(&mask[e * mw + (tid >> 5)], 1u << (tid & 31));
@@ -353,8 +351,6 @@ __device__ __forceinline__ InlineLists group_tokens(const DispatchArgs &d, int e
     }
     int before[3], all[3];
     block_exclusive_scan_n<3>(sums, tmp, before, all);
-    const unsigned long long none = __ballot(tid < T && e < 0);
-    if ((tid & 31) == 0 && tid < T) tmp[tid >> 5] = (int)(uint32_t)(none >> (tid & 32));
     InlineLists r;
     r.cls[0] = all[0] >> 16;
     r.cls[1] = all[1] & 0xFFFF;
@@ -403,9 +399,6 @@ __device__ __forceinline__ InlineLists group_tokens(const DispatchArgs &d, int e
         if (tid == 0) d.tok_off[E] = kept;
     }
     __syncthreads();
-    for (int t = (int)blockIdx.x; t < T; t += (int)gridDim.x)
-        if ((tmp[t >> 5] >> (t & 31)) & 1)
-            for (int c = tid; c < d.d_model; c += nthr) ((__attribute__((address_space(1))) float *)d.y)[(size_t)t * d.d_model + c] = 0.0f;
     r.items = (lp_u32)items;
     r.perm = (const __attribute__((address_space(3))) int *)perm;
     return r;
@@ -498,6 +491,16 @@ __global__ __launch_bounds__(kRowsThreads) void k_rows(const ProductArgs a, cons
             if (e < 0 || e >= d.n_experts) e = -1;
         }
         stage_words(table_w, a.order_table, a.n_order);
+        // The output rows of tokens without an expert are cleared by all workgroups, a row at a time and in whole lines: a rank
+        // that holds a part of the experts has mostly such tokens (512 tokens, 448 of them without an expert, on experts of
+        // 768 x 3072: 230 us when a thread of workgroup 0 cleared a row, 38 us now; 2080 x 6144: 559 and 89 us).  Here,
+        // among the first loads: behind the grouping it cost calls on the asymmetric grid 0.7 us.
+        for (int t = (int)blockIdx.x; t < d.n_tokens; t += (int)gridDim.x) {
+            const int et = d.expert_idx[t];
+            if (et < 0 || et >= d.n_experts)
+                for (int c = (int)threadIdx.x; c < d.d_model; c += kRowsThreads)
+                    ((__attribute__((address_space(1))) float *)d.y)[(size_t)t * d.d_model + c] = 0.0f;
+        }
         lists = group_tokens(d, e, xs0);
     }
     // (wavefront 0; with GROUP wavefront 1 does the same for the second product)
