@@ -329,12 +329,12 @@ struct RowsPlan {
     int slots_wi = 0, slots_wo = 0, grid = 0, max_lds = 0;
 };
 
-RowsPlan rows_plan(const qmoe_dict *d, int code_order, int lanes, int d_model, int d_ff, int n_tokens, int tb)
+RowsPlan rows_plan(const qmoe_dict *d, int code_order, int d_model, int d_ff, int n_tokens, int tb)
 {
     RowsPlan p;
     const int n_order = (int)d->order_table.size();
     DeviceInfo di;
-    if (code_order != 1 || lanes || !n_order || d->max_nonzeros > kRunMaxNonzeros || tuning().rows < 0 || device_info(&di) != QMOE_OK)
+    if (code_order != 1 || !n_order || d->max_nonzeros > kRunMaxNonzeros || tuning().rows < 0 || device_info(&di) != QMOE_OK)
         return p;
     p.max_lds = di.max_lds;
     p.slots_wi = rows_tile_slots(d_model, tb, n_order, di.max_lds);
@@ -344,8 +344,9 @@ RowsPlan rows_plan(const qmoe_dict *d, int code_order, int lanes, int d_model, i
     // of the other kernel own too few rows then, or there are too few of them (128 tokens on 128 experts of 768 x 3072:
     // 68 -> 46 us; 512 on 128 of 1024 x 4096: 167 -> 120 us; one token, 2080 x 6144: 73 -> 22 us).  In larger calls that
     // kernel's hand-out of items, next to the matrix-core kernel's workgroups, is the better one (2048 tokens on 2048
-    // experts: 0.97 ms against 1.03).  Matrices of less than a quarter of a million weights are launch latency either way
-    // and stay on the kernel that reads both stream layouts.
+    // experts: 0.97 ms against 1.03).  Matrices of less than a quarter of a million weights are launch latency either way.
+    // Both layouts of the streams: on a layer re-packed for large calls, one token takes 22 us instead of 155 (2080 x 6144), 512
+    // tokens 375 instead of 560.
     const bool small = n_tokens < 4 * di.cus && (long long)d_model * d_ff >= 1 << 18;
     p.on = p.slots_wi && p.slots_wo && (small || tuning().rows > 0);
     return p;
@@ -783,7 +784,7 @@ qmoe_status layer_forward(const qmoe_dict *d, const qmoe_matrix *wi, const qmoe_
     const LayerPtrs lp = layer_ptrs(workspace, l);
     const int phases = tuning().phases > 0 ? tuning().phases : 31;
     RowsPlan rp;
-    if (pwi.tb_max == pwo.tb_max) rp = rows_plan(d, code_order, lanes_wi, d_model, d_ff, n_tokens, pwi.tb_max);
+    if (pwi.tb_max == pwo.tb_max) rp = rows_plan(d, code_order, d_model, d_ff, n_tokens, pwi.tb_max);
     // In a small call the kernel with several lanes per row groups the tokens itself.
     const bool grouping = rp.on && !mm && rows_can_dispatch(n_experts, n_tokens, rp.grid, n_order, rp.max_lds);
     const DispatchArgs da = dispatch_args(expert_idx, n_tokens, n_experts, d_model, lp, pwi.tb_max, pwo.tb_max, mp.min_tokens, y);
@@ -875,6 +876,8 @@ qmoe_status layer_forward(const qmoe_dict *d, const qmoe_matrix *wi, const qmoe_
     a1.stage_out = pwi.stage_out;
     a1.work_counter = lp.counters + 5;
     a1.class_counts = a2.class_counts = lp.counters + 10;
+    a1.lanes = lanes_wi;
+    a2.lanes = lanes_wo;
     a1.shares = a2.shares = grouping ? lp.shares : nullptr;
     if (phases & 2)
         if ((st = rp.on ? launch_rows(a1, rp.slots_wi, grouping ? &da : nullptr, d_model, rp.slots_wo, rp.grid, rp.max_lds, s_sc)
@@ -922,7 +925,7 @@ int qmoe_plan_lanes(const qmoe_dict *d, int rows, int cols, int n_experts, int n
 int qmoe_plan_row_layout(const qmoe_dict *d, int d_model, int d_ff, int n_experts, int n_tokens)
 {
     if (!d || layer_limits(n_experts, d_model, d_ff, n_tokens) != QMOE_OK) return 0;
-    return rows_plan(d, 1, 0, d_model, d_ff, n_tokens, 4).on ? 1 : 0;
+    return rows_plan(d, 1, d_model, d_ff, n_tokens, 4).on ? 1 : 0;
 }
 
 size_t qmoe_static_workspace_bytes(void) { return kStaticWsBytes; }

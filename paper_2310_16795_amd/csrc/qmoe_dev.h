@@ -76,6 +76,7 @@ struct ProductArgs {
     int lds_dict_entries;     // leading run entries copied to LDS (0 = none)
     int stage_out;            // first product: results of a block staged in LDS and written as whole lines (LDS after the table)
     int *shares;              // k_rows: a record per workgroup, written by the first product for the second, or nullptr
+    int lanes;                // k_rows: lane count of the lane-interleaved layout, 0 = rows back to back
     const int *class_counts;  // items with more than four tokens, three or four, two, one (the list's order), or nullptr
     int *work_counter;        // device counter (zeroed by the dispatch kernel) for handing out items, or nullptr
     const uint32_t *order_table;  // device-order table (n_order entries, the first n_groups are groups)

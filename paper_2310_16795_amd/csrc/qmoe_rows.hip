@@ -39,6 +39,9 @@ struct RowsSplit {
     int rows, x_slots;   // rows of a matrix; token tiles whose activations fit the LDS at once (1 or 2)
     double inv_item[4];  // 1 / (cost of a whole item of class k)
     double inv_grid;
+    // lane-interleaved layout: 1 / lanes, and the even split of the rows over the lanes (`lane_extra` lanes own a row more)
+    float inv_lanes;
+    int lanes, lane_rows, lane_extra;
 };
 
 struct RowsTile {
@@ -51,43 +54,107 @@ struct RowsTile {
 // for before the activations are staged for a wavefront's first group, and during the group before for the others.
 struct GroupHead {
     uint32_t K0, K1, raw;  // the row's first codeword, the next row's, scale (or grid pair) as stored
+    uint32_t Ka, wave, at; // lane-interleaved layout: first codeword of the row's lane, first piece of its group of lanes, place there
     u32x4 v;               // the lane's first piece
 };
 
-template <int ASYM>
-__device__ __forceinline__ void head_offsets(const qmoe_matrix &M, int r1, int row, GroupHead &h)
+// Rows are numbered in the order in which they are worked on.  Back to back: as they are.  Lane-interleaved: the first rows of
+// all lanes of the layout, then their second rows and so on, so that neighbours, whose pieces the lanes of a wavefront read
+// together, are neighbours in memory.  Row number n -> the matrix's row, and the first row of its lane.
+// (Against rows back to back, us: one token 21.1 and 22.1, 64 tokens 83 and 85, 512 tokens 374 and 375 on 256 experts of
+// 2080 x 6144; 512 tokens on 128 experts of 768 x 3072 88 and 96.  Not loading `Ka` where every lane has one row: slower, the
+// branch waits for the loads before it.)
+template <int LANES>
+__device__ __forceinline__ int numbered_row(const RowsSplit &sp, int n, int &lane_of, int &lane_row)
 {
-    const int rr = min(row, r1 - 1);
+    if constexpr (!LANES) {
+        return n;
+    } else {
+        const int i = (int)(((float)n + 0.5f) * sp.inv_lanes);  // n / lanes (exact: rows and lanes are below 2^16)
+        lane_of = n - i * sp.lanes;
+        lane_row = lane_of * sp.lane_rows + min(lane_of, sp.lane_extra);
+        return lane_row + i;
+    }
+}
+
+template <int ASYM, int LANES>
+__device__ __forceinline__ void head_offsets(const RowsSplit &sp, const qmoe_matrix &M, int r1, int number, GroupHead &h)
+{
+    int lane_of = 0, lane_row = 0;
+    const int rr = numbered_row<LANES>(sp, min(number, r1 - 1), lane_of, lane_row);
     gp_u32 row_off = (gp_u32)M.row_off;
     h.K0 = row_off[rr];
     h.K1 = row_off[rr + 1];
+    if constexpr (LANES) {
+        h.Ka = row_off[lane_row];
+        h.wave = ((gp_u32)M.wave_off)[lane_of >> 6];
+        h.at = (uint32_t)(lane_of & 63);
+    }
     if constexpr (ASYM) h.raw = M.minmax_bf16 ? ((gp_u32)M.minmax_bf16)[rr] : 0u;  // no pair array: decodes to zeros
     else h.raw = ((gp_u16)M.scale_f16)[rr];
 }
 
-// Piece q holds codewords 8 q .. 8 q + 7 of a row of n codewords that begins at codeword K0.  Rows begin anywhere in the
-// stream, so a piece's address is a multiple of 2 only; a piece that would reach past the stream's last 16-byte boundary is
-// read that much earlier and its first slots are somebody else's.
+// The 16-byte pieces of a row of n codewords.  `end` bounds the codewords' places in the row's pieces: piece q holds places
+// 8 q .. 8 q + 7, and slots [from, to) of it are codewords of the row.
+//
+// Back to back: places count from the row's first codeword.  Rows begin anywhere in the stream, so a piece's address is a
+// multiple of 2 only; a piece that would reach past the stream's last 16-byte boundary is read that much earlier and its
+// first slots are somebody else's.
+template <int LANES>
 struct RowPieces {
     uint32_t K0, k_last;
-    int n;
+    int n, end;
     uintptr_t codes;
     __device__ __forceinline__ RowPieces(const qmoe_matrix &M, const GroupHead &h, bool live)
     {
-        const uint32_t cap = min(M.n_codes, kMaxCodes), end = min(h.K1, cap);
-        K0 = min(h.K0, end);
-        n = live ? (int)(end - K0) : 0;
+        const uint32_t cap = min(M.n_codes, kMaxCodes), K1 = min(h.K1, cap);
+        K0 = min(h.K0, K1);
+        end = n = live ? (int)(K1 - K0) : 0;
         k_last = max((cap + 7u) & ~7u, 8u) - 8u;
         codes = reinterpret_cast<uintptr_t>(M.codes);
     }
     __device__ __forceinline__ uint32_t slot0(int q) const { return K0 + 8u * (uint32_t)min(q, max((n - 1) >> 3, 0)); }
     __device__ __forceinline__ u32x4 load(int q) const { return *(gp_u32x4_any)(codes + 2u * (uintptr_t)min(slot0(q), k_last)); }
+    __device__ __forceinline__ void slots(int q, int &from, int &to) const
+    {
+        const uint32_t at = slot0(q);
+        from = (int)(at - min(at, k_last));
+        to = from + n - 8 * q;
+    }
 };
 
-// Rows r0 .. r1 of M for a tile whose activations are staged at LDS address xs_addr: the groups of 64 / L rows numbered
+// Lane-interleaved: a row is a part of its lane's stream, whose pieces lie 64 apart; places count from the start of the
+// piece that holds the row's first codeword.
+template <>
+struct RowPieces<1> {
+    uint32_t piece, last;
+    int lead, n, end;
+    uintptr_t codes;
+    __device__ __forceinline__ RowPieces(const qmoe_matrix &M, const GroupHead &h, bool live)
+    {
+        const uint32_t cap = min(M.n_codes, kMaxCodes), K1 = min(h.K1, cap), K0 = min(h.K0, K1), before = K0 - min(h.Ka, K0);
+        n = live ? (int)(K1 - K0) : 0;
+        lead = (int)(before & 7u);
+        end = n ? lead + n : 0;
+        piece = h.wave + h.at + 64u * (before >> 3);
+        last = max(cap >> 3, 1u) - 1u;  // (the buffer's last piece: offsets that are no offsets stay inside it)
+        codes = reinterpret_cast<uintptr_t>(M.codes);
+    }
+    __device__ __forceinline__ u32x4 load(int q) const
+    {
+        return *(gp_u32x4)(codes + 16u * (uintptr_t)min(piece + 64u * (uint32_t)min(q, max((end - 1) >> 3, 0)), last));
+    }
+    __device__ __forceinline__ void slots(int q, int &from, int &to) const
+    {
+        from = q == 0 ? lead : 0;
+        to = end - 8 * q;
+    }
+};
+
+// Rows number r0 .. r1 of M for a tile whose activations are staged at LDS address xs_addr: the groups of 64 / L rows numbered
 // `group`, `group` + wavefronts of the workgroup, ...  `head`: of group `group`, if `have`.
-template <int TBI, int EPI, int ASYM>
-__device__ __forceinline__ void rows_block(const ProductArgs &a, const qmoe_matrix &M, int r0, int r1, int group, int log2L,
+template <int TBI, int EPI, int ASYM, int LANES>
+__device__ __forceinline__ void rows_block(const ProductArgs &a, const RowsSplit &sp, const qmoe_matrix &M, int r0, int r1, int group, int log2L,
                                            uint32_t xs_addr, const RowsTile &tile, lp_u32 table, GroupHead head, bool have)
 {
     constexpr int NA = TBI * (1 + ASYM);
@@ -95,30 +162,30 @@ __device__ __forceinline__ void rows_block(const ProductArgs &a, const qmoe_matr
     const int sub = lane & (L - 1), mine = lane >> log2L, R = 64 >> log2L;
     const uint32_t n_groups3 = 3u * (uint32_t)a.n_groups, last = (uint32_t)a.n_order - 1u, cols8 = 8u * (uint32_t)a.cols;
     for (int rg = r0 + group * R; rg < r1; rg += waves * R) {
-        const int row = rg + mine;
-        const bool live = row < r1;
+        const int number = rg + mine;
+        const bool live = number < r1;
         if (!have) {
-            head_offsets<ASYM>(M, r1, row, head);
-            head.v = RowPieces(M, head, live).load(sub);
+            head_offsets<ASYM, LANES>(sp, M, r1, number, head);
+            head.v = RowPieces<LANES>(M, head, live).load(sub);
         }
-        const RowPieces rp(M, head, live);
-        const int n = rp.n;
+        const RowPieces<LANES> rp(M, head, live);
+        const int end = rp.end;
         const uint32_t raw = head.raw;
         u32x4 v = head.v;
-        head_offsets<ASYM>(M, r1, row + waves * R, head);
+        head_offsets<ASYM, LANES>(sp, M, r1, number + waves * R, head);
         have = true;
         float acc[NA];
 #pragma unroll
         for (int t = 0; t < NA; t++) acc[t] = 0.0f;
         uint32_t base8 = 0u;  // 8 * column where the row's pieces of this step begin
-        for (int q = sub; __any(8 * q < n); q += L) {
+        for (int q = sub; __any(8 * q < end); q += L) {
             const u32x4 v_next = rp.load(q + L);
             uint32_t e[8];
 #pragma unroll
             for (int j = 0; j < 4; j++) order_entry2(table, v[j], n_groups3, last, e[2 * j], e[2 * j + 1]);
             // slots that are not the row's codewords become empty entries
-            const uint32_t at = rp.slot0(q);
-            const int from = (int)(at - min(at, rp.k_last)), to = from + n - 8 * q;  // the row's slots of this piece
+            int from, to;
+            rp.slots(q, from, to);
             if (!__all(from == 0 && to >= 8)) {
                 const uint32_t keep = (0xFFu << from) & (to <= 0 ? 0u : (1u << min(to, 8)) - 1u);
 #pragma unroll
@@ -149,7 +216,7 @@ __device__ __forceinline__ void rows_block(const ProductArgs &a, const qmoe_matr
             }
             v = v_next;
         }
-        head.v = RowPieces(M, head, row + waves * R < r1).load(sub);
+        head.v = RowPieces<LANES>(M, head, number + waves * R < r1).load(sub);
 #pragma unroll
         for (int t = 0; t < NA; t++) acc[t] = lanes_scan(acc[t], L, sub);
         if (live && sub == L - 1) {
@@ -165,6 +232,8 @@ __device__ __forceinline__ void rows_block(const ProductArgs &a, const qmoe_matr
                 scale *= 0.5f;
                 mid *= 0.5f;
             }
+            int lane_of, lane_row;
+            const int row = numbered_row<LANES>(sp, number, lane_of, lane_row);
 #pragma unroll
             for (int t = 0; t < TBI; t++) {
                 if (t < tile.ntok) {
@@ -466,7 +535,7 @@ constexpr int kRowsSmallBytes = (4 * 8 + (int)sizeof(RowsSegment) * kKeptSegment
 
 // GROUP: the launch groups the tokens itself (first product of a small call); split2: of the second product, for whose
 // shares it leaves records.
-template <int EPI, int ASYM, bool GROUP>
+template <int EPI, int ASYM, bool GROUP, int LANES>
 __global__ __launch_bounds__(kRowsThreads) void k_rows(const ProductArgs a, const DispatchArgs d, const RowsSplit split, const RowsSplit split2)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -616,11 +685,11 @@ __global__ __launch_bounds__(kRowsThreads) void k_rows(const ProductArgs a, cons
             const int head_k = wave < groups0 ? 0 : 1;
             const int head_rb = head_k ? rb1 : rb0, head_r = head_k ? ra1 + (wave - groups0) * R : ra0 + wave * R;
             const bool have = head_r < head_rb;
-            GroupHead head{0u, 0u, 0u, u32x4{0u, 0u, 0u, 0u}};
+            GroupHead head{};
             if (have) {
                 const int expert = __builtin_amdgcn_readfirstlane(head_k ? g1->expert : g0->expert);
                 const qmoe_matrix M = a.mats ? a.mats[expert] : a.single;
-                head_offsets<ASYM>(M, head_rb, head_r + (lane >> log2L), head);
+                head_offsets<ASYM, LANES>(split, M, head_rb, head_r + (lane >> log2L), head);
             }
             if (k0 || i_base != __builtin_amdgcn_readfirstlane(share_s[0]) || GROUP) lds_barrier();  // the tiles before (the lists) are done with
 #pragma unroll
@@ -643,7 +712,7 @@ __global__ __launch_bounds__(kRowsThreads) void k_rows(const ProductArgs a, cons
             if (have) {
                 const int expert = __builtin_amdgcn_readfirstlane(head_k ? g1->expert : g0->expert);
                 const qmoe_matrix M = a.mats ? a.mats[expert] : a.single;
-                head.v = RowPieces(M, head, head_r + (lane >> log2L) < head_rb).load(lane & ((1 << log2L) - 1));
+                head.v = RowPieces<LANES>(M, head, head_r + (lane >> log2L) < head_rb).load(lane & ((1 << log2L) - 1));
             }
             if (EPI == 0 && threadIdx.x < 2 * kMaxTokenTile) {
                 const int tok = threadIdx.x < kMaxTokenTile ? g0->tok[threadIdx.x] : g1->tok[threadIdx.x - kMaxTokenTile];
@@ -664,10 +733,10 @@ __global__ __launch_bounds__(kRowsThreads) void k_rows(const ProductArgs a, cons
                 tile.tok_ids = g->tok;
                 tile.gate_s = (const __attribute__((address_space(3))) float *)(gate_s + k * kMaxTokenTile);
                 const uint32_t xs_addr = (uint32_t)(uintptr_t)(lp_u16)(uint16_t *)(xs0 + (k ? xs_bytes : 0));
-                if (tile.ntok <= 1) rows_block<1, EPI, ASYM>(a, M, ra, rb, group, log2L, xs_addr, tile, (lp_u32)table_w, head, first);
-                else if (tile.ntok <= 2) rows_block<2, EPI, ASYM>(a, M, ra, rb, group, log2L, xs_addr, tile, (lp_u32)table_w, head, first);
-                else if (tile.ntok <= 4) rows_block<4, EPI, ASYM>(a, M, ra, rb, group, log2L, xs_addr, tile, (lp_u32)table_w, head, first);
-                else rows_block<8, EPI, ASYM>(a, M, ra, rb, group, log2L, xs_addr, tile, (lp_u32)table_w, head, first);
+                if (tile.ntok <= 1) rows_block<1, EPI, ASYM, LANES>(a, split, M, ra, rb, group, log2L, xs_addr, tile, (lp_u32)table_w, head, first);
+                else if (tile.ntok <= 2) rows_block<2, EPI, ASYM, LANES>(a, split, M, ra, rb, group, log2L, xs_addr, tile, (lp_u32)table_w, head, first);
+                else if (tile.ntok <= 4) rows_block<4, EPI, ASYM, LANES>(a, split, M, ra, rb, group, log2L, xs_addr, tile, (lp_u32)table_w, head, first);
+                else rows_block<8, EPI, ASYM, LANES>(a, split, M, ra, rb, group, log2L, xs_addr, tile, (lp_u32)table_w, head, first);
                 group = (group - groups0) & (waves - 1);  // the second segment's groups go on where the first one's end
             }
         }
@@ -699,13 +768,17 @@ bool rows_can_dispatch(int n_experts, int n_tokens, int grid, int n_order, int m
            rows_fixed_bytes(n_order) + inline_lds_bytes(n_experts, n_tokens) <= (size_t)max_lds;
 }
 
-RowsSplit rows_split(int rows, int x_slots, int grid)
+RowsSplit rows_split(int rows, int lanes, int x_slots, int grid)
 {
     RowsSplit sp;
     sp.rows = rows;
     sp.x_slots = x_slots;
     for (int k = 0; k < 4; k++) sp.inv_item[k] = 1.0 / (double)(kRowCost[k] * ((rows + 7) / 8));
     sp.inv_grid = 1.0 / grid;
+    sp.lanes = lanes;
+    sp.inv_lanes = lanes ? 1.0f / (float)lanes : 0.0f;
+    sp.lane_rows = lanes ? rows / lanes : 0;
+    sp.lane_extra = lanes ? rows % lanes : 0;
     return sp;
 }
 
@@ -720,22 +793,22 @@ qmoe_status launch_rows(const ProductArgs &a, int x_slots, const DispatchArgs *d
     RowsSplit split2{};
     if (da) {
         d = *da;
-        split2 = rows_split(rows2, x_slots2, grid);
+        split2 = rows_split(rows2, 0, x_slots2, grid);  // (its shares only)
     }
-    const RowsSplit split = rows_split(a.rows, x_slots, grid);
+    const RowsSplit split = rows_split(a.rows, a.lanes, x_slots, grid);
     auto launch = [&](auto kernel) -> qmoe_status {
         const qmoe_status st = allow_lds(kernel, smem);
         if (st != QMOE_OK) return st;
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(kRowsThreads), smem, s, a, d, split, split2);
         return QMOE_OK;
     };
-    qmoe_status st;
-    if (da)
-        st = a.minmax ? launch(k_rows<1, 1, true>) : launch(k_rows<1, 0, true>);
-    else if (a.minmax)
-        st = a.epilogue ? launch(k_rows<1, 1, false>) : launch(k_rows<0, 1, false>);
-    else
-        st = a.epilogue ? launch(k_rows<1, 0, false>) : launch(k_rows<0, 0, false>);
+    auto choose = [&](auto lanes) -> qmoe_status {
+        constexpr int LANES = decltype(lanes)::value;
+        if (da) return a.minmax ? launch(k_rows<1, 1, true, LANES>) : launch(k_rows<1, 0, true, LANES>);
+        if (a.minmax) return a.epilogue ? launch(k_rows<1, 1, false, LANES>) : launch(k_rows<0, 1, false, LANES>);
+        return a.epilogue ? launch(k_rows<1, 0, false, LANES>) : launch(k_rows<0, 0, false, LANES>);
+    };
+    const qmoe_status st = a.lanes ? choose(std::integral_constant<int, 1>{}) : choose(std::integral_constant<int, 0>{});
     if (st != QMOE_OK) return st;
     QMOE_HIP_TRY(hipGetLastError());
     return QMOE_OK;

@@ -79,9 +79,10 @@ class DeviceLayer:
 
     def finalize(self, device_order_of: "DeviceDict | None" = None, lanes_for_tokens: int = 0):
         """Upload everything; with device_order_of, renumber the streams for that dictionary; with
-        lanes_for_tokens (a typical token count of the calls to come; needs device_order_of), re-pack
+        lanes_for_tokens (the token count of the largest calls to come; needs device_order_of), re-pack
         every stream into the lane-interleaved layout for the lane count the planner picks -- unless
-        calls of that size read rows back to back faster (qmoe_plan_row_layout)."""
+        calls of that size are better served by rows back to back (qmoe_plan_row_layout).  Calls of
+        any size read either layout."""
         self.code_order = 0 if device_order_of is None else 1
         self.format = self.code_order | (B.FORMAT_GRID_MINMAX if self.minmax else 0)
         per_row = 2 if self.minmax else 1  # 16-bit values of scale data per row

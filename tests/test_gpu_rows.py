@@ -112,3 +112,31 @@ def test_tokens_without_an_expert(gpu, ddict, oracle_dict, T, d_model, keep):
     assert len(kept) <= 6 and wsout["counters"][0] == len(kept) and wsout["counters"][1] == T - len(kept)
     assert not y[[t for t in range(T) if idx[t] != 2]].any()  # (the output held NaN before the call)
     _check_layer(w, idx, x, y, wsout, kept)
+
+
+@pytest.mark.parametrize("minmax", [False, True])
+@pytest.mark.parametrize("E,d_model,d_ff,T,loaded_for", [
+    (3, 8, 20, 1, 1),          # fewer rows than the layout's lanes
+    (4, 258, 130, 9, 1),       # a row or two per lane, some lanes with one more
+    (4, 200, 1030, 33, 1),     # two rows per lane, a few lanes with three
+    (2, 520, 3002, 5, 4096),   # many rows per lane that the lanes do not divide
+    (40, 258, 516, 1, 1),      # one item on the whole GPU
+    (600, 72, 200, 512, 4096),  # more items than workgroups, tokens grouped inside the first product
+    (600, 72, 200, 513, 1),    # ... and by the dispatch kernel
+    (2, 64, 8400, 6, 1),       # more columns than one round of staging
+])
+def test_lane_interleaved_layers(gpu, ddict, oracle_dict, monkeypatch, E, d_model, d_ff, T, loaded_for, minmax):
+    monkeypatch.setattr(dev.B, "qmoe_plan_row_layout", lambda *a: False)
+    w = synth.WORKLOADS["switch_base128"].scaled(n_experts=E, d_model=d_model, d_ff=d_ff, n_tokens=T)
+    idx, x = w.expert_idx(), w.tokens()
+    if T > 8 and E > 4:
+        idx[0], idx[T // 2] = -1, E
+        idx[1:8] = [2, 2, 2, 2, 3, 3, 3]
+    layer = _build_layer(w, oracle_dict, gpu, order_of=ddict, minmax=minmax, lanes_for_tokens=loaded_for)
+    assert layer.lanes["wi"] >= 64 and layer.lanes["wo"] >= 64
+    gate = np.random.default_rng(5).uniform(0.2, 1.0, T)
+    print(f"{layer.lanes} lanes", flush=True)
+    y, wsout = _run_layer(layer, ddict, x, idx, gpu, gate)
+    valid = [t for t in range(T) if 0 <= idx[t] < E]
+    _check_layer(w, idx, x, y, wsout, valid if len(valid) < 60 else valid[:30] + valid[-30:], gate, asym=minmax)
+    assert not y[[t for t in range(T) if not 0 <= idx[t] < E]].any()
