@@ -14,7 +14,7 @@ namespace {
 // Bound: the stores.  Per 64 codewords a compute unit has about 330 cycles of HBM write time (bf16) and the wavefront
 // about 150 of vector issue, so what counts is that every compute unit has rows to write all the time, to the end (small
 // units, the number of wavefronts chosen so that they divide evenly), and how the stores reach memory: runs of 128
-// bytes 3.4 TB/s, marked non-temporal (matrices that do not fit the caches; the lines are whole) 4.0, runs of 512 bytes 4.3.
+// bytes 3.4 TB/s, marked non-temporal (the matrices do not fit the caches, and the lines are whole) 4.0, runs of 512 bytes 4.3.
 // 12 experts of 2080 x 6144, both projections, to bf16 (613 MB; a fill takes 95 us): 331 us with the kernel before, which
 // gave a lane a row and a workgroup 512 rows (60 workgroups for the one projection, 144 for the other), now 134.
 constexpr int kDcMaxWaves = 16;
@@ -32,24 +32,6 @@ using lw_u8 = __attribute__((address_space(3))) unsigned char *;
 using lw_u64 = __attribute__((address_space(3))) unsigned long long *;
 using gw_u64 = __attribute__((address_space(1))) unsigned long long *;
 using gw_u32x4 = __attribute__((address_space(1))) u32x4 *;
-
-// Results that the last-level cache (256 MB) holds are stored so that it does, for the product that reads them next, larger ones
-// past it.  Decompression to bf16 and then torch.matmul of every matrix with 64 tokens, us, stored past the caches and plainly:
-// one of 768 x 3072 23.1 and 22.9, 12 (57 MB) 156 and 132, 48 (226 MB) 600 and 489; 8 of 2080 x 6144 (204 MB) 201 and 152, 12
-// (307 MB) 304 and 336.  The call alone: 10.1 and 10.1, 16.3 and 18.3, 52 and 43; 49 and 38, 72 and 71.
-constexpr unsigned long long kDcCachedBytes = 230ull * 1000 * 1000;
-
-template <typename P, typename V>
-__device__ __forceinline__ void dc_store(P at, V v, bool cached)
-{
-    if (cached) {
-        asm volatile("");  // (before and after it: the compiler makes one unmarked store of the two otherwise)
-        *at = v;
-        asm volatile("");
-    } else {
-        __builtin_nontemporal_store(v, at);
-    }
-}
 
 // OUT 0: int8 in {-1, 0, +1}; 1: bf16(scale of the row) with the weight's sign, or 0;
 // 2: the row's bf16 grid point w_max or w_min, or 0 (asymmetric grid)
@@ -91,7 +73,6 @@ __global__ __launch_bounds__(64 * kDcMaxWaves) void k_decompress(const Decompres
     // lanes' row ranges (their pieces lie next to each other).  A wavefront takes every a.slots-th unit of a matrix: one, but
     // for the lane-interleaved layout of a matrix with rows that its lanes do not divide.
     constexpr int kBpe = OUT == 0 ? 1 : 2, kRunBytes = kDcGroup * kBpe;
-    const bool cached = (unsigned long long)n_wanted * (unsigned long long)a.rows * (unsigned long long)(a.cols * kBpe) <= kDcCachedBytes;
 
     // The units of all wanted matrices are dealt out round robin.  A wavefront's next unit is `stride` units on: so many matrices
     // and so many slots, known once, and the matrix is found from the place of the last one (with thousands of
@@ -214,9 +195,9 @@ __global__ __launch_bounds__(64 * kDcMaxWaves) void k_decompress(const Decompres
                                 // ring byte 0x40 -> 0x01, 0xC0 -> 0xFF, 0 -> 0
                                 const uint32_t n0 = (w0 >> 7) & 0x01010101u, n1 = (w1 >> 7) & 0x01010101u;
                                 const uint32_t o0 = ((w0 >> 6) & 0x01010101u) | ((n0 << 8) - n0), o1 = ((w1 >> 6) & 0x01010101u) | ((n1 << 8) - n1);
-                                dc_store((gw_u64)(dst + (uintptr_t)k), (unsigned long long)o0 | ((unsigned long long)o1 << 32), cached);
+                                __builtin_nontemporal_store((unsigned long long)o0 | ((unsigned long long)o1 << 32), (gw_u64)(dst + (uintptr_t)k));
                             } else if constexpr (OUT == 2) {
-                                dc_store((gw_u32x4)(dst + 2 * (uintptr_t)k), select_minmax(w0, w1, s2 << 16, s2 & 0xFFFF0000u), cached);
+                                __builtin_nontemporal_store(select_minmax(w0, w1, s2 << 16, s2 & 0xFFFF0000u), (gw_u32x4)(dst + 2 * (uintptr_t)k));
                             } else {
                                 u32x4 o;
 #pragma unroll
@@ -226,7 +207,7 @@ __global__ __launch_bounds__(64 * kDcMaxWaves) void k_decompress(const Decompres
                                     const uint32_t ones = (b >> 14) & 0x00010001u;
                                     o[i] = ((b & 0x80008000u) | s2) & ((ones << 16) - ones);
                                 }
-                                dc_store((gw_u32x4)(dst + 2 * (uintptr_t)k), o, cached);
+                                __builtin_nontemporal_store(o, (gw_u32x4)(dst + 2 * (uintptr_t)k));
                             }
                         }
                     }

@@ -115,26 +115,3 @@ def test_stream_past_its_width_spoils_no_other_row(kind):
         assert np.array_equal(host[i].view(want.dtype), want), i
     assert (host[0] == 77).all() and (host[5] == 77).all()
     dd.close()
-
-
-@pytest.mark.parametrize("kind", [0, 1, 2])
-def test_more_than_the_caches_hold(kind):
-    """Results of more than 230 MB leave past the caches, smaller ones do not: the same bytes."""
-    gpu, rows, cols, n = "cuda:0", 2080, 6144, 20 if kind == 0 else 10
-    dd = dev.DeviceDict(device=gpu)
-    tern = synth.ternary(3, rows, cols, 0.9)
-    codes, off = q.qmoe_encode_host(dd.handle, tern)
-    M = dev.DeviceMatrix(codes, off, None if kind == 2 else synth.uniform_f16(6, (rows,), 0.01, 0.1), rows, cols, device=gpu,
-                         device_order_of=dd, minmax_bf16=synth.minmax_bf16(5, rows, 0.01, 0.1) if kind == 2 else None)
-    out = torch.full((n + 1, rows, cols), 77, dtype=torch.int8 if kind == 0 else torch.int16, device=gpu)
-    d_desc = torch.from_numpy(np.frombuffer(bytes((q.qmoe_matrix * n)(*[M.desc] * n)), dtype=np.uint8).copy()).to(gpu)
-    ptrs = torch.tensor([out[i].data_ptr() for i in range(n)], dtype=torch.int64, device=gpu)
-    fmt = q.FORMAT_DEVICE_ORDER | (q.FORMAT_GRID_MINMAX if kind == 2 else 0)
-    print(f"kind {kind}", flush=True)
-    q.qmoe_decompress(dd.handle, d_desc, fmt, n, rows, cols, min(kind, 1), ptrs)
-    q.qmoe_decompress(dd.handle, d_desc, fmt, 1, rows, cols, min(kind, 1), torch.tensor([out[n].data_ptr()], dtype=torch.int64, device=gpu))
-    torch.cuda.synchronize()
-    assert torch.equal(out[:n], out[n].expand(n, rows, cols))
-    sign = torch.sign((out[n] if kind == 0 else out[n].view(torch.bfloat16)).float()).to(torch.int8)
-    assert torch.equal(sign.cpu(), torch.from_numpy(tern))
-    dd.close()
