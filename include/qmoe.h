@@ -360,9 +360,9 @@ size_t qmoe_moe_layer_workspace(int n_experts, int d_model, int d_ff, int n_toke
  * device int32 [n_tokens].  gate: device fp32 [n_tokens] or NULL (= 1).
  * y: device fp32 [n_tokens][d_model], overwritten; a token whose expert index
  * is outside [0, n_experts) gets a zero row.  workspace: device, 256-byte
- * aligned, >= qmoe_moe_layer_workspace(...) bytes, contents need not be
- * initialised.  Experts without tokens are never touched (their qmoe_matrix
- * may hold anything).  code_order: QMOE_FORMAT_* bits: the numbering of every expert's
+ * aligned, >= qmoe_moe_layer_workspace(...) bytes (32 KiB less will do, for half a microsecond
+ * more in small calls), contents need not be initialised.  Experts without tokens are never
+ * touched (their qmoe_matrix may hold anything).  code_order: QMOE_FORMAT_* bits: the numbering of every expert's
  * stream (bit 0, as in qmoe_matrix) and whether the experts are on the asymmetric grid
  * (QMOE_FORMAT_GRID_MINMAX; the descriptors live in device memory, so the host is told).
  * A call of fewer tokens than four per compute unit on experts of at least 2^18 weights

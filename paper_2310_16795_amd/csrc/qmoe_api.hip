@@ -96,7 +96,9 @@ qmoe_status side_stream(hipStream_t callers, SideStream *out)
 // library's own device image, so that the call allocates nothing.  Each GPU holds its own
 // copy at its own address; host code uses the address hipGetSymbolAddress returns for the
 // current device, never the array's name.
-constexpr size_t kShareRecords = kRowsShareBytes * kRowsMaxGrid;  // k_rows' part of a workspace, on top of what callers look at
+// k_rows' part of a workspace, behind what callers look at: the second product of a small call finds its shares there (0.5 us
+// of 21 for one token); in a workspace without it, as long as calls needed before there were such records, it works them out again
+constexpr size_t kShareRecords = kRowsShareBytes * kRowsMaxGrid;
 constexpr size_t kStaticWsBytes = (size_t)8 << 20;
 __device__ __align__(256) unsigned char g_static_ws[kStaticWsBytes + kShareRecords];
 
@@ -720,7 +722,7 @@ qmoe_status qmoe_moe_dispatch(const qmoe_dict *d, int code_order, const int32_t 
     qmoe_status st = qmoe_moe_layer_ws_layout(n_experts, d_model, d_ff, n_tokens, &l);
     if (st != QMOE_OK) return st;
     if (!d || !expert_idx) return QMOE_E_INVALID_ARG;
-    if (!workspace || reinterpret_cast<uintptr_t>(workspace) % 256 || workspace_bytes < l.total)
+    if (!workspace || reinterpret_cast<uintptr_t>(workspace) % 256 || workspace_bytes < l.total - kShareRecords)
         return QMOE_E_WORKSPACE;
     bool minmax = false;
     int lanes_wi = 0, lanes_wo = 0;
@@ -758,7 +760,7 @@ qmoe_status layer_forward(const qmoe_dict *d, const qmoe_matrix *wi, const qmoe_
     if (st != QMOE_OK) return st;
     if (!d || !wi || !wo || !x_bf16 || !expert_idx || !y) return QMOE_E_INVALID_ARG;
     if (!d->dev) return QMOE_E_NO_DEVICE_DICT;
-    if (!workspace || reinterpret_cast<uintptr_t>(workspace) % 256 || workspace_bytes < l.total)
+    if (!workspace || reinterpret_cast<uintptr_t>(workspace) % 256 || workspace_bytes < l.total - kShareRecords)
         return QMOE_E_WORKSPACE;
     bool minmax = false;
     int lanes_wi = 0, lanes_wo = 0;
@@ -878,7 +880,7 @@ qmoe_status layer_forward(const qmoe_dict *d, const qmoe_matrix *wi, const qmoe_
     a1.class_counts = a2.class_counts = lp.counters + 10;
     a1.lanes = lanes_wi;
     a2.lanes = lanes_wo;
-    a1.shares = a2.shares = grouping ? lp.shares : nullptr;
+    a1.shares = a2.shares = grouping && workspace_bytes >= l.total ? lp.shares : nullptr;
     if (phases & 2)
         if ((st = rp.on ? launch_rows(a1, rp.slots_wi, grouping ? &da : nullptr, d_model, rp.slots_wo, rp.grid, rp.max_lds, s_sc)
                         : launch_product(a1, pwi, run, s_sc)) != QMOE_OK) return st;
@@ -959,7 +961,7 @@ qmoe_status qmoe_bf16_layer_forward(const uint16_t *const *wi_dense, const uint1
     if (st != QMOE_OK) return st;
     if (!wi_dense || !wo_dense || !x_bf16 || !expert_idx || !y) return QMOE_E_INVALID_ARG;
     if ((d_model % 8) || (d_ff % 8)) return QMOE_E_INVALID_ARG;  // 16-byte row loads
-    if (!workspace || reinterpret_cast<uintptr_t>(workspace) % 256 || workspace_bytes < l.total)
+    if (!workspace || reinterpret_cast<uintptr_t>(workspace) % 256 || workspace_bytes < l.total - kShareRecords)
         return QMOE_E_WORKSPACE;
     ProductPlan pwi, pwo;
     if ((st = plan_dense(d_ff, d_model, n_tokens, &pwi)) != QMOE_OK) return st;

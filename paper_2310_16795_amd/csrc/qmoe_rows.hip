@@ -604,7 +604,7 @@ __global__ __launch_bounds__(kRowsThreads) void k_rows(const ProductArgs a, cons
     if constexpr (!GROUP) stage_words(table_w, a.order_table, a.n_order);
     __syncthreads();
     if constexpr (GROUP) {
-        if (threadIdx.x < (unsigned)kShareInts) {
+        if (a.shares && threadIdx.x < (unsigned)kShareInts) {
             const int k = threadIdx.x, n = lists.cls[0] + lists.cls[1] + lists.cls[2] + lists.cls[3];
             const int i = min(share_s[4] + ((k - 4) >> 1), n - 1);
             a.shares[blockIdx.x * kShareInts + k] = k < 4 ? share_s[4 + k] : (n ? (int)lists.items[2 * i + (k & 1)] : 0);

@@ -82,3 +82,26 @@ def test_single_matrix(gpu, ddict, oracle_dict, rows, cols, p0, batches, minmax)
         for i, t in enumerate(some):
             if t < b:
                 _check_product(y[t][None, :], y_ref[i][None, :], bound[i][None, :], f"{rows}x{cols} token {t} of {b}")
+
+
+# A workspace without the 32 KiB behind the parts that callers look at, in which the second product of a small call finds its
+# shares of the work: accepted by all calls, nothing written behind it, the same results; shorter ones are refused.
+@pytest.mark.parametrize("T,d_ff", [(1, 600), (70, 600), (600, 600), (40, 64)])
+def test_workspace_without_records(gpu, ddict, oracle_dict, T, d_ff):
+    w = synth.WORKLOADS["switch_base128"].scaled(n_experts=6, d_model=520, d_ff=d_ff, n_tokens=T)
+    x, idx = _to_dev16(w.tokens(), gpu), torch.from_numpy(w.expert_idx()).to(gpu)
+    layer = _build_layer(w, oracle_dict, gpu, order_of=ddict)
+    full = layer.workspace(T)
+    less = full.numel() - 32768
+    pool = torch.full((full.numel(),), 0x5A, dtype=torch.uint8, device=gpu)
+    ys = [torch.full((T, w.d_model), float("nan"), dtype=torch.float32, device=gpu) for _ in range(2)]
+    print(f"{T} tokens, {less} bytes", flush=True)
+    layer.forward(ddict, x, idx, ys[0], full)
+    layer.forward(ddict, x, idx, ys[1], pool[:less])
+    torch.cuda.synchronize()
+    assert torch.equal(ys[0], ys[1]) and bool((pool[less:] == 0x5A).all())
+    q.qmoe_moe_dispatch(ddict.handle, 1, idx, 6, w.d_model, d_ff, pool[:less])
+    with pytest.raises(q.QmoeError):
+        layer.forward(ddict, x, idx, ys[1], pool[:less - 1])
+    torch.cuda.synchronize()
+    assert torch.equal(ys[0], ys[1]) and bool((pool[less:] == 0x5A).all())
