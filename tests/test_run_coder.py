@@ -90,3 +90,30 @@ def test_device_encoder_with_missing_phrases():
             tern[41, 601] = 1
         assert _on_device(dd, tern, codes_ref.size)[2] == [want, 41]
     dd.close()
+
+
+def test_host_encoder_without_vector_instructions(oracle_dict, tmp_path):
+    """The host code built for a processor without SSE2 gives the same streams."""
+    import ctypes
+    import os
+    import subprocess
+
+    root = os.path.dirname(os.path.dirname(os.path.abspath(q.__file__)))
+    lib = str(tmp_path / "libqmoe_host.so")
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-fPIC", "-shared", "-pthread", "-U__SSE2__", "-D_EMMINTRIN_H_INCLUDED", "-I", os.path.join(root, "include"),
+                           "-I", os.path.join(root, "paper_2310_16795_amd", "csrc"),
+                           os.path.join(root, "paper_2310_16795_amd", "csrc", "qmoe_host.cpp"), "-o", lib])
+    L, vp = ctypes.CDLL(lib), ctypes.c_void_p
+    words, d = np.ascontiguousarray(oracle_dict.words, dtype=np.uint32), vp()
+    assert L.qmoe_dict_from_words(vp(words.ctypes.data), words.size // 2, ctypes.byref(d)) == 0
+    for rows, cols, p0 in SHAPES:
+        tern = synth.ternary(rows + cols, rows, cols, p0)
+        ref, ref_off = oracle.encode(oracle_dict, tern)
+        codes, off, n = np.zeros(ref.size, np.uint16), np.zeros(rows + 1, np.uint32), ctypes.c_size_t()
+        assert L.qmoe_encode_host(d, vp(tern.ctypes.data), rows, cols, vp(codes.ctypes.data), ctypes.c_size_t(codes.size),
+                                  vp(off.ctypes.data), ctypes.byref(n)) == 0
+        assert n.value == ref.size and np.array_equal(codes, ref) and np.array_equal(off, ref_off)
+        tern[rows // 2, cols // 2] = 2
+        assert L.qmoe_encode_host(d, vp(tern.ctypes.data), rows, cols, vp(codes.ctypes.data), ctypes.c_size_t(codes.size),
+                                  vp(off.ctypes.data), ctypes.byref(n)) == -3
+    L.qmoe_dict_destroy(d)
