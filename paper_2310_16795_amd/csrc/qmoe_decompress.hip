@@ -144,7 +144,8 @@ __global__ __launch_bounds__(64 * kDcMaxWaves) void k_decompress(const Decompres
             const int n = (int)rs.left, lead = (int)rs.sub;
             uint32_t pos8 = 0u;  // 8 * column the row has reached
             // quarter-piece h of the row: codewords 2 h - lead and 2 h - lead + 1
-            const int quarters = n ? (lead + n + 1) >> 1 : 0;
+            int quarters = n ? (lead + n + 1) >> 1 : 0;
+            if (lanes) quarters = min(quarters, 4 * (int)((rs.last - rs.pp) >> 10) + 4);  // (none behind `last`)
             auto load = [&](int h) -> uint32_t {
                 const int at = max(min(h, quarters - 1), 0);
                 return *(gp_u32)(rs.pp + rs.pstride * (uintptr_t)(at >> 2) + 4u * (uintptr_t)(at & 3));

@@ -426,6 +426,13 @@ struct RowStream {
     uint32_t left, sub;
 };
 
+// Address of a lane-interleaved stream's last piece.  Pieces of a lane lie 64 apart, so offsets that are no offsets reach far
+// past the stream even when they are clamped to its length: no piece behind this one is read.
+__device__ __forceinline__ uintptr_t last_piece_of(const qmoe_matrix &M)
+{
+    return reinterpret_cast<uintptr_t>(M.codes) + 16u * (uintptr_t)(max(min(M.n_codes, kMaxCodes) >> 3, 1u) - 1u);
+}
+
 __device__ __forceinline__ RowStream row_stream(const qmoe_matrix &M, int row, bool live)
 {
     RowStream r;
@@ -463,6 +470,11 @@ __device__ __forceinline__ RowStream row_stream(const qmoe_matrix &M, int row, b
     }
     r.sub = lead >> 1;
     r.last = r.pp + r.pstride * (uintptr_t)(((lead + 2u * r.left + 15u) >> 4) - 1u);
+    if (M.lanes) {
+        const uintptr_t end = last_piece_of(M);
+        r.pp = r.pp < end ? r.pp : end;
+        r.last = r.last < end ? r.last : end;
+    }
     return r;
 }
 

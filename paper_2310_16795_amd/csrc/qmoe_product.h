@@ -287,7 +287,7 @@ __device__ __forceinline__ void product_block(const ProductArgs &a, const qmoe_m
         first_byte = reinterpret_cast<uintptr_t>(M.codes) +
                      16u * ((uintptr_t)((gp_u32)M.wave_off)[gl >> 6] + (uintptr_t)(gl & 63));
     const uint32_t lead = (uint32_t)(first_byte & 15u);
-    const uintptr_t chunk = first_byte - lead;
+    uintptr_t chunk = first_byte - lead;
     const uintptr_t pstride = interleaved ? 1024u : 16u;  // from a piece of the lane to its next
     const int rel = -(int)(lead >> 1);
     const int my_pieces = n ? (int)((lead + 2u * n + 15u) >> 4) : 0;
@@ -307,7 +307,12 @@ __device__ __forceinline__ void product_block(const ProductArgs &a, const qmoe_m
 
     // Piece p + 2 is being loaded and the entries of piece p + 1 looked up while piece p
     // is applied.
-    const uintptr_t last_piece = chunk + pstride * (uintptr_t)max(my_pieces - 1, 0);
+    uintptr_t last_piece = chunk + pstride * (uintptr_t)max(my_pieces - 1, 0);
+    if (interleaved) {
+        const uintptr_t end = last_piece_of(M);
+        chunk = chunk < end ? chunk : end;
+        last_piece = last_piece < end ? last_piece : end;
+    }
     auto load_piece = [&](int p) -> u32x4 {
         // lanes past their own end re-read their last piece (its slots are masked out below)
         const uintptr_t at = chunk + pstride * (uintptr_t)p;

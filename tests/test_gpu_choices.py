@@ -105,3 +105,37 @@ def test_workspace_without_records(gpu, ddict, oracle_dict, T, d_ff):
         layer.forward(ddict, x, idx, ys[1], pool[:less - 1])
     torch.cuda.synchronize()
     assert torch.equal(ys[0], ys[1]) and bool((pool[less:] == 0x5A).all())
+
+
+# Offsets that are no offsets, in the lane-interleaved layout, whose pieces lie 1 KiB apart: wrong numbers for that expert, no
+# access outside its stream, and the other experts' results as ever.  The calls read the layout with each of the kernels that do.
+@pytest.mark.parametrize("T,min_tokens", [(3, 0), (1100, -1), (1100, 8)])
+@pytest.mark.parametrize("kind", ["large", "random", "falling"])
+def test_corrupt_offsets_in_the_lane_layout(gpu, ddict, oracle_dict, T, min_tokens, kind):
+    w = synth.WORKLOADS["switch_base128"].scaled(n_experts=3, d_model=264, d_ff=1024, n_tokens=T)
+    idx, x = w.expert_idx(), w.tokens()
+    idx[:3] = [0, 1, 2]
+    layer = _build_layer(w, oracle_dict, gpu, order_of=ddict, lanes_for_tokens=4096)
+    assert layer.lanes["wi"]
+    q.qmoe_set_tuning("mfma_min_tokens", min_tokens)
+    try:
+        y, wsout = _run_layer(layer, ddict, x, idx, gpu)
+        rng = np.random.default_rng(3)
+        for which in ("wi", "wo"):
+            off = layer.bufs[which][1]  # [experts][rows + 1]
+            n = off.shape[1]
+            bad = {"large": np.full(n, 0xFFFFFFFF), "random": rng.integers(0, 2 ** 32, n), "falling": np.arange(n)[::-1] * 40}[kind]
+            off[1] = torch.from_numpy(bad.astype(np.uint32).view(np.int32)).to(gpu)
+        print(f"{kind} offsets, {T} tokens", flush=True)
+        y2, _ = _run_layer(layer, ddict, x, idx, gpu)
+    finally:
+        q.qmoe_set_tuning("mfma_min_tokens", 0)
+    sound = [t for t in range(T) if idx[t] != 1]
+    assert np.array_equal(y[sound], y2[sound])
+    _check_layer(w, idx, x, y, wsout, sound[:4])
+    out = torch.full((3, w.d_ff, w.d_model), 77, dtype=torch.int8, device=gpu)
+    ptrs = torch.tensor([out[e].data_ptr() for e in range(3)], dtype=torch.int64, device=gpu)
+    q.qmoe_decompress(ddict.handle, layer.desc_dev["wi"], layer.format, 3, w.d_ff, w.d_model, 0, ptrs)
+    torch.cuda.synchronize()
+    for e in (0, 2):
+        assert np.array_equal(out[e].cpu().numpy(), w.wi_ternary(e))
