@@ -139,3 +139,20 @@ def test_corrupt_offsets_in_the_lane_layout(gpu, ddict, oracle_dict, T, min_toke
     torch.cuda.synchronize()
     for e in (0, 2):
         assert np.array_equal(out[e].cpu().numpy(), w.wi_ternary(e))
+
+
+# Layer calls on both sides of their lines: tokens grouped inside the first product up to 512, several lanes per row below four
+# tokens per compute unit (1024) where a matrix has 2^18 weights, both layouts.
+@pytest.mark.parametrize("d_model,d_ff", [(512, 512), (510, 512), (512, 520)])
+@pytest.mark.parametrize("T", [512, 513, 1023, 1024])
+@pytest.mark.parametrize("loaded_for", [0, 4096])
+def test_layer(gpu, ddict, oracle_dict, d_model, d_ff, T, loaded_for):
+    w = synth.WORKLOADS["switch_base128"].scaled(n_experts=24, d_model=d_model, d_ff=d_ff, n_tokens=T)
+    idx, x = w.expert_idx(), w.tokens()
+    idx[3], idx[5] = -1, 24
+    layer = _build_layer(w, oracle_dict, gpu, order_of=ddict, lanes_for_tokens=loaded_for, minmax=bool(T & 1))
+    print(f"{d_model}x{d_ff}, {T} tokens, {layer.lanes}", flush=True)
+    gate = np.random.default_rng(5).uniform(0.2, 1.0, T)
+    y, wsout = _run_layer(layer, ddict, x, idx, gpu, gate)
+    _check_layer(w, idx, x, y, wsout, [0, 1, 2, T // 2, T - 1], gate, asym=bool(T & 1))
+    assert np.isfinite(y).all() and not y[[3, 5]].any()
