@@ -82,9 +82,9 @@ __global__ __launch_bounds__(64 * kDcMaxWaves) void k_decompress(const Decompres
     // and so many slots, known once, and the matrix is found from the place of the last one (with thousands of
     // small matrices, a walk from the mask's first word and a division for every unit are most of a unit's time).
     const int stride = (int)gridDim.x * waves;
-    const long long first = (long long)blockIdx.x * waves + wave;
+    const int first = (int)blockIdx.x * waves + wave;
     const int d_nth = stride / a.slots, d_slot = stride - d_nth * a.slots;
-    int nth = (int)min(first / a.slots, (long long)n_wanted), slot = (int)(first - (long long)nth * a.slots);
+    int nth = first / a.slots, slot = first - nth * a.slots;
     int word = 0, skip = nth;                 // the matrix is the skip-th of the bits left in this word and the words after it
     auto word_bits = [&](int w) -> unsigned long long {  // the same in every lane
         const unsigned long long b = mask[w];
@@ -151,7 +151,7 @@ __global__ __launch_bounds__(64 * kDcMaxWaves) void k_decompress(const Decompres
                 return *(gp_u32)(rs.pp + rs.pstride * (uintptr_t)(at >> 2) + 4u * (uintptr_t)(at & 3));
             };
             uint32_t v = load(sub);
-            bool more = true, over = false;  // over: the row's stream (a corrupt one) has run past its width
+            bool more = true;
             for (int h0 = 0; more; h0 += kDcLanes) {
                 const int h = h0 + sub;
                 const uint32_t v_next = load(h + kDcLanes);
@@ -166,7 +166,6 @@ __global__ __launch_bounds__(64 * kDcMaxWaves) void k_decompress(const Decompres
                 const uint32_t incl = lanes_scan(len8, kDcLanes, sub);
                 uint32_t p = pos8 + incl - len8;
                 pos8 += (uint32_t)__shfl((int)incl, lane | (kDcLanes - 1), 64);
-                over |= pos8 > cols8;
 #pragma unroll
                 for (int j = 0; j < 2; j++) {
                     // (an entry's unused fields come first and store a zero at the run's first column, ahead of its weights)
@@ -220,8 +219,9 @@ __global__ __launch_bounds__(64 * kDcMaxWaves) void k_decompress(const Decompres
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
                 __builtin_amdgcn_wave_barrier();
             }
-            // What such a row left in its ring behind its last column would be weights of the ring's next row.
-            if (any_entry || __any(over)) {
+            // A (corrupt) stream that ran past the row's width -- or has more codewords than columns, so many that the column may
+            // have wrapped -- left weights in the ring behind its last column, which would be weights of the ring's next row.
+            if (any_entry || __any(pos8 > cols8 || n > a.cols)) {
                 for (int i = 8 * sub; i < kDcRing; i += 8 * kDcLanes) *(lw_u64)(uintptr_t)(ring + (uint32_t)i) = 0ull;
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
                 __builtin_amdgcn_wave_barrier();

@@ -156,3 +156,47 @@ def test_layer(gpu, ddict, oracle_dict, d_model, d_ff, T, loaded_for):
     y, wsout = _run_layer(layer, ddict, x, idx, gpu, gate)
     _check_layer(w, idx, x, y, wsout, [0, 1, 2, T // 2, T - 1], gate, asym=bool(T & 1))
     assert np.isfinite(y).all() and not y[[3, 5]].any()
+
+
+# Small calls and decompression in a HIP graph: replays with other work between them, and with other tokens in the same buffers.
+@pytest.mark.parametrize("loaded_for", [0, 4096])
+@pytest.mark.parametrize("T", [1, 100, 600])
+def test_small_calls_in_a_graph(gpu, ddict, oracle_dict, T, loaded_for):
+    w = synth.WORKLOADS["switch_base128"].scaled(n_experts=6, d_model=520, d_ff=520, n_tokens=T)
+    layer = _build_layer(w, oracle_dict, gpu, order_of=ddict, lanes_for_tokens=loaded_for)
+    x, idx = _to_dev16(w.tokens(), gpu), torch.from_numpy(w.expert_idx()).to(gpu)
+    y, ws = torch.zeros((T, w.d_model), dtype=torch.float32, device=gpu), layer.workspace(T)
+    out = torch.zeros((6, w.d_ff, w.d_model), dtype=torch.int8, device=gpu)
+    ptrs = torch.tensor([out[e].data_ptr() for e in range(6)], dtype=torch.int64, device=gpu)
+
+    def work(stream):
+        layer.forward(ddict, x, idx, y, ws, stream=stream)
+        q.qmoe_decompress(ddict.handle, layer.desc_dev["wi"], layer.format, 6, w.d_ff, w.d_model, 0, ptrs, stream=stream)
+
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    print(f"{T} tokens, {layer.lanes}", flush=True)
+    with torch.cuda.stream(side):
+        work(side.cuda_stream)
+        torch.cuda.synchronize()
+        eager, dense = y.clone(), out.clone()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            work(side.cuda_stream)
+    torch.cuda.synchronize()
+    for rep in range(3):
+        y.fill_(float("nan"))
+        out.fill_(5)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, eager) and torch.equal(out, dense), f"replay {rep}"
+        (y * 2).sum().item()
+    x.copy_(_to_dev16(w.scaled(cfg_id=97).tokens(), gpu))
+    idx.copy_(torch.from_numpy(np.roll(w.expert_idx(), 1) if T > 1 else (w.expert_idx() + 1) % 6))
+    graph.replay()
+    torch.cuda.synchronize()
+    got = y.clone()
+    work(torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert torch.equal(got, y) and not torch.equal(got, eager)
