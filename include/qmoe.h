@@ -159,7 +159,7 @@ qmoe_status qmoe_validate_host(const qmoe_dict *d, const uint16_t *codes /*host*
                                const uint32_t *row_off /*host [rows+1]*/, int rows, int cols);
 
 /*
- * The same encoder on the device (Section 4.3.3 "Encoding"), one matrix row per lane:
+ * The same encoder on the device (Section 4.3.3 "Encoding"):
  * ternary (device, row-major int8 [rows][cols], values -1/0/+1) is coded into codes
  * (device, capacity codes_cap codewords, interchange numbering -- run
  * qmoe_codes_to_device_order on it afterwards for the device numbering) and row_off
@@ -286,8 +286,8 @@ qmoe_status qmoe_codes_to_device_order(const qmoe_dict *d, uint16_t *codes /*dev
  * One launch.  A small batch runs on a kernel that puts 16 lanes on every row (latency of a
  * single product); more work (device-order stream) on one that stages the table in LDS; and from
  * some hundred tokens on (also cols divisible by 8, x 16-byte aligned) the matrix is decoded once
- * per 64 tokens and multiplied on the matrix cores.  The switches are cost estimates;
- * "mfma_min_tokens" overrides the last one.
+ * per 64 tokens and multiplied on the matrix cores.  The switches are cost estimates from W's rows, cols and
+ * n_codes and the batch; "mfma_min_tokens" overrides the last one.
  * Errors: INVALID_ARG (NULL, batch<1, odd cols), NO_DEVICE_DICT, LIMIT
  * (cols > 32768, or four tokens' activations, 8 bytes per column, do not fit the LDS: cols
  * above 20448 on a GPU with 160 KB), HIP.

@@ -20,6 +20,8 @@ extern "C" {
  *              matrix-core kernel of the first / second product; 0 = all (the default)
  *  "stage_out" -1 = the products write their results straight to global memory instead of
  *              staging a block's results in LDS; 0 = default
+ *  "rows"      1 = layer calls and single matrices use the kernel with several lanes per row
+ *              wherever it can run, -1 = never, 0 = the planner's choice (the default)
  * Unknown key: QMOE_E_INVALID_ARG.
  */
 qmoe_status qmoe_hook_set(const char *key, int value);
