@@ -261,6 +261,18 @@ inline int pair_of(int8_t a, int8_t b)
 bool row_bits(const int8_t *row, int cols, uint8_t *nz, uint8_t *neg)
 {
     int c = 0, bad = 0;
+    auto up_to_16 = [&] {
+        uint16_t n = 0, m = 0;
+        for (int j = 0; j < 16 && c + j < cols; j++) {
+            const int v = row[c + j];
+            bad |= v < -1 || v > 1;
+            n |= (uint16_t)((v != 0) << j);
+            m |= (uint16_t)((v < 0) << j);
+        }
+        std::memcpy(nz + c / 8, &n, 2);
+        std::memcpy(neg + c / 8, &m, 2);
+        c += 16;
+    };
 #if defined(__SSE2__)
     for (; c + 16 <= cols; c += 16) {
         const __m128i v = _mm_loadu_si128(reinterpret_cast<const __m128i *>(row + c));
@@ -271,18 +283,10 @@ bool row_bits(const int8_t *row, int cols, uint8_t *nz, uint8_t *neg)
         std::memcpy(nz + c / 8, &n, 2);
         std::memcpy(neg + c / 8, &m, 2);
     }
+    if (c < cols) up_to_16();
+#else
+    while (c < cols) up_to_16();
 #endif
-    for (; c < cols; c += 16) {
-        uint16_t n = 0, m = 0;
-        for (int j = 0; j < 16 && c + j < cols; j++) {
-            const int v = row[c + j];
-            bad |= v < -1 || v > 1;
-            n |= (uint16_t)((v != 0) << j);
-            m |= (uint16_t)((v < 0) << j);
-        }
-        std::memcpy(nz + c / 8, &n, 2);
-        std::memcpy(neg + c / 8, &m, 2);
-    }
     std::memset(nz + c / 8, 0, 8);
     std::memset(neg + c / 8, 0, 8);
     return bad == 0;
