@@ -78,13 +78,11 @@ __global__ __launch_bounds__(64 * kDcMaxWaves) void k_decompress(const Decompres
     // for the lane-interleaved layout of a matrix with rows that its lanes do not divide.
     constexpr int kBpe = OUT == 0 ? 1 : 2, kRunBytes = kDcGroup * kBpe;
 
-    // The units of all wanted matrices are dealt out round robin.  A wavefront's next unit is `stride` units on: so many matrices
-    // and so many slots, known once, and the matrix is found from the place of the last one (with thousands of
-    // small matrices, a walk from the mask's first word and a division for every unit are most of a unit's time).
-    const int stride = (int)gridDim.x * waves;
-    const int first = (int)blockIdx.x * waves + wave;
-    const int d_nth = stride / a.slots, d_slot = stride - d_nth * a.slots;
-    int nth = first / a.slots, slot = first - nth * a.slots;
+    // The units of all wanted matrices are dealt out round robin.  A wavefront's next unit is as many units on as there are
+    // wavefronts: so many matrices and so many slots, known to the host, and the matrix is found from the place of the last one
+    // (with thousands of small matrices, a walk from the mask's first word and a division for every unit are most of a unit's time).
+    const int first = (int)blockIdx.x * waves + wave;  // (below 2^16)
+    int nth = (int)(((float)first + 0.5f) * a.inv_slots), slot = first - nth * a.slots;
     int word = 0, skip = nth;                 // the matrix is the skip-th of the bits left in this word and the words after it
     auto word_bits = [&](int w) -> unsigned long long {  // the same in every lane
         const unsigned long long b = mask[w];
@@ -227,8 +225,8 @@ __global__ __launch_bounds__(64 * kDcMaxWaves) void k_decompress(const Decompres
                 __builtin_amdgcn_wave_barrier();
             }
         }
-        slot += d_slot;
-        skip = d_nth;
+        slot += a.next_slot;
+        skip = a.next_nth;
         if (slot >= a.slots) {
             slot -= a.slots;
             skip++;
@@ -258,6 +256,9 @@ static qmoe_status launch_dc(DecompressArgs a, int out_kind, bool minmax, int cu
     const long long total = (long long)a.n_mats * a.slots, most = (long long)cus * kDcMaxWaves, rounds = (total + most - 1) / most;
     const int waves = (int)std::max(1LL, std::min<long long>(kDcMaxWaves, (total + cus * rounds - 1) / (cus * rounds)));
     const int grid = (int)std::min<long long>((total + waves - 1) / waves, (long long)cus);
+    a.next_nth = grid * waves / a.slots;
+    a.next_slot = grid * waves % a.slots;
+    a.inv_slots = 1.0f / (float)a.slots;
     auto launch = [&](auto kernel) -> qmoe_status {
         const qmoe_status st = allow_lds(kernel, smem);
         if (st != QMOE_OK) return st;

@@ -97,7 +97,9 @@ struct DecompressArgs {
     const qmoe_matrix *mats;  // device array
     void *const *out;         // device array of destinations (row-major rows x cols), nullptr = skip
     int n_mats, rows, cols;
-    int slots;                // units of rows per matrix (set by launch_decompress)
+    int slots;                // units of rows per matrix; the next three with it (set by launch_decompress)
+    int next_nth, next_slot;  // from a wavefront's unit to its next: matrices on, slots on
+    float inv_slots;          // 1 / slots
     const uint32_t *order_table;
     int n_groups, n_order;
 };
