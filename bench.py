@@ -356,8 +356,8 @@ def main():
         return mat_bytes("wo", w.d_model, experts) + toks * w.d_ff * 2 + toks * w.d_model * 4
     dict_mode = "0|1" if args.interchange_order else "3"  # template argument: where the table is read from
     g = 1 if minmax else 0                                # template argument: the grid
-    # small calls share a row between several lanes (the library's own rule, from which its layout advice follows)
-    several = not args.interchange_order and q.qmoe_plan_row_layout(dd.handle, w.d_model, w.d_ff, w.n_experts, T)
+    # which kernel the experts with few tokens take is the library's own rule
+    several = q.qmoe_hook_several_lanes(dd.handle, layer.format, w.n_experts, w.d_model, w.d_ff, T)
     few_name = [f"k_rows<{epi}, {g}, ...>" if several else f"k_product<{dict_mode}, {epi}, {g}>" for epi in (0, 1)]
     kernels = {
         "first_product_scalar": (f"{few_name[1]} (first product, experts with few tokens)", kernel_bytes("wi", few)),

@@ -219,9 +219,9 @@ typedef struct qmoe_matrix {
  * its meaning (codeword counts), codes points to the pieces, n_codes is 8 * n_pieces.  The
  * padding is part of the compressed size: report 16 * n_pieces bytes, not 2 * row_off[rows].
  * Only the layer calls and qmoe_decompress read this layout: pass the lane counts in the format
- * argument (QMOE_FORMAT_LANES).  Larger layer calls launch exactly `lanes` lanes per matrix then, so
- * build it for them -- qmoe_plan_lanes gives the count the planner would pick --; small calls
- * and qmoe_decompress read it whatever the count.
+ * argument (QMOE_FORMAT_LANES).  Larger layer calls whose kernel gives a lane a row range launch exactly `lanes`
+ * lanes per matrix then, so build it for them -- qmoe_plan_lanes gives the count the planner would
+ * pick --; the other kernels and qmoe_decompress read it whatever the count.
  *   qmoe_lane_layout_size    number of 16-byte pieces the layout takes
  *   qmoe_lane_layout_build   codes (host, interchange or device numbering) -> out (host, 8 *
  *                            out_pieces codewords), wave_off (host [lanes/64 + 1])
@@ -248,7 +248,7 @@ int qmoe_plan_lanes(const qmoe_dict *d, int rows, int cols, int n_experts, int n
  * every row between several lanes, are up to 7 % faster on it, and it has no padding --, 0 =
  * lane-interleaved (also on error).  Every call reads both layouts; a layer that serves calls of
  * both kinds is best laid out for its largest ones (2080 x 6144, 256 experts, one token: 21.1 us
- * rows back to back, 22.1 us lane-interleaved; 1024 tokens: 590 and 578 us).
+ * rows back to back, 22.1 us lane-interleaved; 1024 tokens: 496 and 491 us).
  */
 int qmoe_plan_row_layout(const qmoe_dict *d, int d_model, int d_ff, int n_experts, int n_tokens);
 
@@ -366,10 +366,11 @@ size_t qmoe_moe_layer_workspace(int n_experts, int d_model, int d_ff, int n_toke
  * stream (bit 0, as in qmoe_matrix) and whether the experts are on the asymmetric grid
  * (QMOE_FORMAT_GRID_MINMAX; the descriptors live in device memory, so the host is told).
  * A call of fewer tokens than four per compute unit on experts of at least 2^18 weights
- * (device order) enqueues one kernel per product, the first of which
+ * (device order) enqueues one kernel per product, in which several lanes share a row; the first
  * groups the tokens itself where it can (up to 512 tokens).  Otherwise:
  * Enqueues a dispatch kernel and, per product, the scalar kernel for experts with few
- * tokens and (device-order streams, widths divisible by 8, x 16-byte aligned) the
+ * tokens (by the experts that the call can reach, their widths and the layout: the one in which several
+ * lanes share a row, or the one with a row range per lane) and (device-order streams, widths divisible by 8, x 16-byte aligned) the
  * matrix-core kernel for crowded ones: an expert's matrix is decoded once per tile of up
  * to 64 tokens there, instead of once per 4.  When both kinds of experts are present the
  * two kernels of one kind run on a second stream that forks from `stream` after the dispatch and

@@ -26,6 +26,13 @@ extern "C" {
  */
 qmoe_status qmoe_hook_set(const char *key, int value);
 
+/*
+ * 1 if a layer call of this size gives its experts with few tokens to the kernel with several lanes per
+ * row, 0 if to the one with a row range per lane (also on error): the name of the kernel that a profile
+ * shows (widths whose activations leave room for tiles of four tokens).  format: QMOE_FORMAT_* bits.
+ */
+int qmoe_hook_several_lanes(const qmoe_dict *d, int format, int n_experts, int d_model, int d_ff, int n_tokens);
+
 #ifdef __cplusplus
 }
 #endif

@@ -56,7 +56,7 @@ EXPORTS = [
     "qmoe_bf16_layer_forward", "qmoe_set_tuning", "qmoe_stream_copy", "qmoe_dict_device_order",
     "qmoe_codes_to_device_order", "qmoe_decompress", "qmoe_encode_device", "qmoe_hook_set", "qmoe_static_workspace_bytes", "qmoe_moe_layer_forward_static",
     "qmoe_lane_layout_size", "qmoe_lane_layout_build", "qmoe_lane_layout_unpack", "qmoe_plan_lanes",
-    "qmoe_plan_row_layout",
+    "qmoe_plan_row_layout", "qmoe_hook_several_lanes",
 ]
 
 
@@ -107,6 +107,7 @@ def lib():
         L.qmoe_plan_lanes.argtypes = [vp, i, i, i, i]
         L.qmoe_plan_row_layout.argtypes = [vp, i, i, i, i]
         L.qmoe_hook_set.argtypes = [c_char_p, i]
+        L.qmoe_hook_several_lanes.argtypes = [vp, i, i, i, i, i]
         L.qmoe_stream_copy.argtypes = [vp, vp, sz, vp]
         _lib = L
     return _lib
@@ -382,6 +383,11 @@ def qmoe_lane_layout_unpack(pieces: np.ndarray, wave_off: np.ndarray, row_off: n
 def qmoe_hook_set(key: str, value: int) -> None:
     """Measurement hooks (include/qmoe_hooks.h): not part of the product ABI."""
     _check(lib().qmoe_hook_set(key.encode(), int(value)), "qmoe_hook_set")
+
+
+def qmoe_hook_several_lanes(d: int, fmt: int, n_experts: int, d_model: int, d_ff: int, n_tokens: int) -> bool:
+    """Which kernel a layer call's experts with few tokens take (include/qmoe_hooks.h)."""
+    return lib().qmoe_hook_several_lanes(d, fmt, n_experts, d_model, d_ff, n_tokens) == 1
 
 
 def qmoe_stream_copy(dst, src, stream=None) -> None:

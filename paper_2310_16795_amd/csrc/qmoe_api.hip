@@ -327,11 +327,11 @@ qmoe_status plan_mm(const qmoe_dict *d, int code_order, int d_model, int d_ff, i
 
 // Do the experts with few tokens of a layer call take the kernel with several lanes per row, and how?
 struct RowsPlan {
-    bool on = false;
+    bool on = false, small = false;
     int slots_wi = 0, slots_wo = 0, grid = 0, max_lds = 0;
 };
 
-RowsPlan rows_plan(const qmoe_dict *d, int code_order, int d_model, int d_ff, int n_tokens, int tb)
+RowsPlan rows_plan(const qmoe_dict *d, int code_order, int n_experts, bool lanes, int d_model, int d_ff, int n_tokens, int tb)
 {
     RowsPlan p;
     const int n_order = (int)d->order_table.size();
@@ -342,15 +342,24 @@ RowsPlan rows_plan(const qmoe_dict *d, int code_order, int d_model, int d_ff, in
     p.slots_wi = rows_tile_slots(d_model, tb, n_order, di.max_lds);
     p.slots_wo = rows_tile_slots(d_ff, tb, n_order, di.max_lds);
     p.grid = std::min(di.cus, kRowsMaxGrid);
-    // Calls of fewer than four tokens per compute unit (the line below which the matrix-core kernel stays off): the lanes
+    // Small calls, fewer than four tokens per compute unit (the line below which the matrix-core kernel stays off): the lanes
     // of the other kernel own too few rows then, or there are too few of them (128 tokens on 128 experts of 768 x 3072:
-    // 68 -> 46 us; 512 on 128 of 1024 x 4096: 167 -> 120 us; one token, 2080 x 6144: 73 -> 22 us).  In larger calls that
-    // kernel's hand-out of items, next to the matrix-core kernel's workgroups, is the better one (2048 tokens on 2048
-    // experts: 0.97 ms against 1.03).  Matrices of less than a quarter of a million weights are launch latency either way.
+    // 68 -> 46 us; 512 on 128 of 1024 x 4096: 167 -> 120 us; one token, 2080 x 6144: 73 -> 22 us).
+    p.small = n_tokens < 4 * di.cus;
+    // Larger calls, for the experts with few tokens next to the matrix-core kernel: the same holds while there are not many more
+    // items than compute units, and beyond that while a share that begins in one item and ends in the next has room for both
+    // tiles in LDS (widths up to about 5800).  Layer, us, other kernel / this one, Zipf routing and uniform: 128 experts of
+    // 768 x 3072, 1024 tokens 182 / 156 and 222 / 215; 256 of 2080 x 6144, 1024 tokens 598 / 496 and 849 / 732, 4000 tokens 911 /
+    // 892 and 997 / 1003; 512 of 512 x 2048, 2048 tokens 227 / 148 and 357 / 207; 2048 of 768 x 3072, 2048 tokens 304 / 278 and
+    // 562 / 400.  Not so: 1024 of 2080 x 6144, 2048 tokens 885 / 922 and 1590 / 1690 -- and with few experts each, but the matrices of
+    // 2^22 weights lane-interleaved, 512 of 1024 x 4096, 1500 tokens 299 / 314 and 477 / 458: left as it was.
+    const double active = n_experts * (1.0 - std::exp(-(double)n_tokens / n_experts));
+    const bool two_tiles = p.slots_wi > 1 && p.slots_wo > 1;
+    const long long weights = (long long)d_model * d_ff;
+    const bool large = active <= 1.25 * di.cus || (two_tiles && (!lanes || weights < 1 << 22));
     // Both layouts of the streams: on a layer re-packed for large calls, one token takes 22 us instead of 155 (2080 x 6144), 512
-    // tokens 375 instead of 560.
-    const bool small = n_tokens < 4 * di.cus && (long long)d_model * d_ff >= 1 << 18;
-    p.on = p.slots_wi && p.slots_wo && (small || tuning().rows > 0);
+    // tokens 375 instead of 560.  Matrices of less than a quarter of a million weights are launch latency either way.
+    p.on = p.slots_wi && p.slots_wo && ((weights >= 1 << 18 && (p.small || large)) || tuning().rows > 0);
     return p;
 }
 
@@ -786,7 +795,7 @@ qmoe_status layer_forward(const qmoe_dict *d, const qmoe_matrix *wi, const qmoe_
     const LayerPtrs lp = layer_ptrs(workspace, l);
     const int phases = tuning().phases > 0 ? tuning().phases : 31;
     RowsPlan rp;
-    if (pwi.tb_max == pwo.tb_max) rp = rows_plan(d, code_order, d_model, d_ff, n_tokens, pwi.tb_max);
+    if (pwi.tb_max == pwo.tb_max) rp = rows_plan(d, code_order, n_experts, lanes_wi != 0, d_model, d_ff, n_tokens, pwi.tb_max);
     // In a small call the kernel with several lanes per row groups the tokens itself.
     const bool grouping = rp.on && !mm && rows_can_dispatch(n_experts, n_tokens, rp.grid, n_order, rp.max_lds);
     const DispatchArgs da = dispatch_args(expert_idx, n_tokens, n_experts, d_model, lp, pwi.tb_max, pwo.tb_max, mp.min_tokens, y);
@@ -927,7 +936,16 @@ int qmoe_plan_lanes(const qmoe_dict *d, int rows, int cols, int n_experts, int n
 int qmoe_plan_row_layout(const qmoe_dict *d, int d_model, int d_ff, int n_experts, int n_tokens)
 {
     if (!d || layer_limits(n_experts, d_model, d_ff, n_tokens) != QMOE_OK) return 0;
-    return rows_plan(d, 1, d_model, d_ff, n_tokens, 4).on ? 1 : 0;
+    const RowsPlan p = rows_plan(d, 1, n_experts, false, d_model, d_ff, n_tokens, 4);
+    return p.on && p.small ? 1 : 0;
+}
+
+int qmoe_hook_several_lanes(const qmoe_dict *d, int format, int n_experts, int d_model, int d_ff, int n_tokens)
+{
+    int code_order, lanes = 0;
+    bool minmax;
+    if (!d || layer_limits(n_experts, d_model, d_ff, n_tokens) != QMOE_OK || split_format(format, &code_order, &minmax, &lanes) != QMOE_OK) return 0;
+    return rows_plan(d, code_order, n_experts, lanes != 0, d_model, d_ff, n_tokens, 4).on ? 1 : 0;
 }
 
 size_t qmoe_static_workspace_bytes(void) { return kStaticWsBytes; }

@@ -200,3 +200,41 @@ def test_small_calls_in_a_graph(gpu, ddict, oracle_dict, T, loaded_for):
     work(torch.cuda.current_stream().cuda_stream)
     torch.cuda.synchronize()
     assert torch.equal(got, y) and not torch.equal(got, eager)
+
+
+# Calls of 1024 tokens, next to the matrix cores: the experts with few tokens take several lanes per row up to 1.25 active experts
+# per compute unit (320, which 335 experts do not reach and 336 do), beyond that where two tiles fit the LDS and, lane-interleaved,
+# below 2^22 weights.  One to seven tokens, and tiles of one block and of several; eagerly and in a graph.
+@pytest.mark.parametrize("E,d_model,d_ff,loaded_for,several", [
+    (335, 64, 5900, 0, True), (336, 64, 5900, 0, False), (335, 5900, 64, 4096, True), (336, 5900, 64, 4096, False),
+    (700, 64, -2, 0, True), (700, 64, 0, 0, False), (700, -2, 64, 4096, True), (700, 0, 64, 4096, False),
+    (700, 2048, 2040, 4096, True), (700, 2048, 2048, 4096, False), (700, 2048, 2048, 0, True), (6, 510, 514, 0, False), (6, 510, 516, 0, True)])
+def test_few_tokens_next_to_the_matrix_cores(gpu, ddict, oracle_dict, E, d_model, d_ff, loaded_for, several):
+    line = next(c for c in range(5000, 6500, 2) if not q.qmoe_hook_several_lanes(ddict.handle, 1, 700, 64, c, 1024))
+    d_model, d_ff = (d if d > 0 else line + d for d in (d_model, d_ff))  # 0: the first width without room for two tiles, -2: the last with
+    T, asym = 1024, bool(E & 1)
+    w = synth.WORKLOADS["switch_base128"].scaled(n_experts=E, d_model=d_model, d_ff=d_ff, n_tokens=T)
+    x, counts = w.tokens(), {0: 1, E - 1: 3, 2: 7, 3: 20, 4: 100}
+    idx = np.full(T, -1, dtype=np.int32)
+    idx[np.random.default_rng(4).permutation(T)[:131]] = np.repeat(list(counts), list(counts.values()))
+    layer = _build_layer(w, oracle_dict, gpu, encoder="library", lib_dict=ddict.handle, experts=list(counts), order_of=ddict, minmax=asym,
+                         lanes_for_tokens=loaded_for)
+    assert bool(layer.lanes["wi"]) == bool(loaded_for)
+    assert q.qmoe_hook_several_lanes(ddict.handle, layer.format, E, d_model, d_ff, T) == several
+    print(f"{E} experts of {d_model} x {d_ff}, {layer.lanes}", flush=True)
+    y, wsout = _run_layer(layer, ddict, x, idx, gpu)
+    some = [int(np.flatnonzero(idx == e)[k]) for e, n in counts.items() for k in {0, n - 1}]
+    _check_layer(w, idx, x, y, wsout, some, asym=asym)
+    assert np.isfinite(y).all() and not y[idx < 0].any()
+    xd, idxd, yd, ws = _to_dev16(x, gpu), torch.from_numpy(idx).to(gpu), torch.zeros((T, d_model), dtype=torch.float32, device=gpu), layer.workspace(T)
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=streams[0]):
+        layer.forward(ddict, xd, idxd, yd, ws, stream=streams[0].cuda_stream, side_stream=streams[1].cuda_stream)
+    for rep in range(3):
+        yd.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(yd.cpu().numpy(), y), f"replay {rep}"
