@@ -70,9 +70,6 @@ __global__ __launch_bounds__(64 * kDcMaxWaves) void k_decompress(const Decompres
         if (lane == 0) mask[w] = bits;
     }
     __syncthreads();
-    int n_wanted = 0;
-    for (int w = 0; w < mask_words; w += 64) n_wanted += w + lane < mask_words ? __popcll(mask[w + lane]) : 0;
-    n_wanted = __builtin_amdgcn_readlane(wave_inclusive_scan(n_wanted), 63);
     // Units of a matrix: kDcRows consecutive rows, or, in the lane-interleaved layout, the i-th rows of as many consecutive
     // lanes' row ranges (their pieces lie next to each other).  A wavefront takes every a.slots-th unit of a matrix: one, but
     // for the lane-interleaved layout of a matrix with rows that its lanes do not divide.
@@ -82,7 +79,7 @@ __global__ __launch_bounds__(64 * kDcMaxWaves) void k_decompress(const Decompres
     // wavefronts: so many matrices and so many slots, known to the host, and the matrix is found from the place of the last one
     // (with thousands of small matrices, a walk from the mask's first word and a division for every unit are most of a unit's time).
     const int first = (int)blockIdx.x * waves + wave;  // (below 2^16)
-    int nth = (int)(((float)first + 0.5f) * a.inv_slots), slot = first - nth * a.slots;
+    int nth = __builtin_amdgcn_readfirstlane((int)(((float)first + 0.5f) * a.inv_slots)), slot = first - nth * a.slots;
     int word = 0, skip = nth;                 // the matrix is the skip-th of the bits left in this word and the words after it
     auto word_bits = [&](int w) -> unsigned long long {  // the same in every lane
         const unsigned long long b = mask[w];
@@ -90,6 +87,12 @@ __global__ __launch_bounds__(64 * kDcMaxWaves) void k_decompress(const Decompres
                (unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32)) << 32;
     };
     unsigned long long bits = word_bits(0);
+    int n_wanted = __popcll(bits);
+    if (mask_words > 1) {
+        n_wanted = 0;
+        for (int w = 0; w < mask_words; w += 64) n_wanted += w + lane < mask_words ? __popcll(mask[w + lane]) : 0;
+        n_wanted = __builtin_amdgcn_readlane(wave_inclusive_scan(n_wanted), 63);
+    }
     while (nth < n_wanted) {
         for (;;) {
             const int n = __popcll(bits);
