@@ -351,8 +351,8 @@ RowsPlan rows_plan(const qmoe_dict *d, int code_order, int n_experts, bool lanes
     // tiles in LDS (widths up to about 5800).  Layer, us, other kernel / this one, Zipf routing and uniform: 128 experts of
     // 768 x 3072, 1024 tokens 182 / 156 and 222 / 215; 256 of 2080 x 6144, 1024 tokens 598 / 496 and 849 / 732, 4000 tokens 911 /
     // 892 and 997 / 1003; 512 of 512 x 2048, 2048 tokens 227 / 148 and 357 / 207; 2048 of 768 x 3072, 2048 tokens 304 / 278 and
-    // 562 / 400.  Not so: 1024 of 2080 x 6144, 2048 tokens 885 / 922 and 1590 / 1690 -- and with few experts each, but the matrices of
-    // 2^22 weights lane-interleaved, 512 of 1024 x 4096, 1500 tokens 299 / 314 and 477 / 458: left as it was.
+    // 562 / 400.  Not so: 1024 of 2080 x 6144, 2048 tokens 885 / 922 and 1590 / 1690; lane-interleaved, with 2^22 weights and more,
+    // 512 of 1024 x 4096, 1500 tokens 299 / 314 and 477 / 458.
     const double active = n_experts * (1.0 - std::exp(-(double)n_tokens / n_experts));
     const bool two_tiles = p.slots_wi > 1 && p.slots_wo > 1;
     const long long weights = (long long)d_model * d_ff;

@@ -238,3 +238,18 @@ def test_few_tokens_next_to_the_matrix_cores(gpu, ddict, oracle_dict, E, d_model
         graph.replay()
         torch.cuda.synchronize()
         assert np.array_equal(yd.cpu().numpy(), y), f"replay {rep}"
+
+
+# Thousands of items for several lanes per row: widths that the matrix cores do not take, shares of many items.
+@pytest.mark.parametrize("loaded_for", [0, 4096])
+def test_many_tokens_without_the_matrix_cores(gpu, ddict, oracle_dict, loaded_for):
+    T, E = 20003, 3
+    w = synth.WORKLOADS["switch_base128"].scaled(n_experts=E, d_model=510, d_ff=518, n_tokens=T)
+    idx, x = w.expert_idx(), w.tokens()
+    idx[[5, 12345]] = -1, E
+    layer = _build_layer(w, oracle_dict, gpu, order_of=ddict, lanes_for_tokens=loaded_for)
+    assert q.qmoe_hook_several_lanes(ddict.handle, layer.format, E, 510, 518, T)
+    print(f"{T} tokens, {layer.lanes}", flush=True)
+    y, wsout = _run_layer(layer, ddict, x, idx, gpu)
+    _check_layer(w, idx, x, y, wsout, [0, 1, 5000, 9999, T // 2, T - 2, T - 1])
+    assert np.isfinite(y).all() and not y[[5, 12345]].any() and (y != 0).any(axis=1).sum() == T - 2
