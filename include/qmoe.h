@@ -248,7 +248,7 @@ int qmoe_plan_lanes(const qmoe_dict *d, int rows, int cols, int n_experts, int n
  * every row between several lanes, are up to 7 % faster on it, and it has no padding --, 0 =
  * lane-interleaved (also on error).  Every call reads both layouts; a layer that serves calls of
  * both kinds is best laid out for its largest ones (2080 x 6144, 256 experts, one token: 21.1 us
- * rows back to back, 22.1 us lane-interleaved; 1024 tokens: 496 and 491 us).
+ * rows back to back, 22.1 us lane-interleaved; 1024 tokens: 492 and 476 us).
  */
 int qmoe_plan_row_layout(const qmoe_dict *d, int d_model, int d_ff, int n_experts, int n_tokens);
 
