@@ -109,15 +109,16 @@ def test_workspace_without_records(gpu, ddict, oracle_dict, T, d_ff):
 
 # Offsets that are no offsets, in the lane-interleaved layout, whose pieces lie 1 KiB apart: wrong numbers for that expert, no
 # access outside its stream, and the other experts' results as ever.  The calls read the layout with each of the kernels that do.
-@pytest.mark.parametrize("T,min_tokens", [(3, 0), (1100, -1), (1100, 8)])
+@pytest.mark.parametrize("T,min_tokens,rows", [(3, 0, 0), (1100, -1, 1), (1100, -1, -1), (1100, 8, 0)])
 @pytest.mark.parametrize("kind", ["large", "random", "falling"])
-def test_corrupt_offsets_in_the_lane_layout(gpu, ddict, oracle_dict, T, min_tokens, kind):
+def test_corrupt_offsets_in_the_lane_layout(gpu, ddict, oracle_dict, T, min_tokens, rows, kind):
     w = synth.WORKLOADS["switch_base128"].scaled(n_experts=3, d_model=264, d_ff=1024, n_tokens=T)
     idx, x = w.expert_idx(), w.tokens()
     idx[:3] = [0, 1, 2]
     layer = _build_layer(w, oracle_dict, gpu, order_of=ddict, lanes_for_tokens=4096)
     assert layer.lanes["wi"]
     q.qmoe_set_tuning("mfma_min_tokens", min_tokens)
+    q.qmoe_hook_set("rows", rows)
     try:
         y, wsout = _run_layer(layer, ddict, x, idx, gpu)
         rng = np.random.default_rng(3)
@@ -130,6 +131,7 @@ def test_corrupt_offsets_in_the_lane_layout(gpu, ddict, oracle_dict, T, min_toke
         y2, _ = _run_layer(layer, ddict, x, idx, gpu)
     finally:
         q.qmoe_set_tuning("mfma_min_tokens", 0)
+        q.qmoe_hook_set("rows", 0)
     sound = [t for t in range(T) if idx[t] != 1]
     assert np.array_equal(y[sound], y2[sound])
     _check_layer(w, idx, x, y, wsout, sound[:4])
@@ -141,8 +143,8 @@ def test_corrupt_offsets_in_the_lane_layout(gpu, ddict, oracle_dict, T, min_toke
         assert np.array_equal(out[e].cpu().numpy(), w.wi_ternary(e))
 
 
-# Layer calls on both sides of their lines: tokens grouped inside the first product up to 512, several lanes per row below four
-# tokens per compute unit (1024) where a matrix has 2^18 weights, both layouts.
+# Layer calls on both sides of their lines: tokens grouped inside the first product up to 512, the matrix cores from four
+# tokens per compute unit (1024) on, several lanes per row where a matrix has 2^18 weights, both layouts.
 @pytest.mark.parametrize("d_model,d_ff", [(512, 512), (510, 512), (512, 520)])
 @pytest.mark.parametrize("T", [512, 513, 1023, 1024])
 @pytest.mark.parametrize("loaded_for", [0, 4096])
