@@ -501,6 +501,13 @@ DispatchArgs dispatch_args(const int32_t *expert_idx, int n_tokens, int n_expert
     da.d_model = d_model;
     return da;
 }
+
+qmoe_status launch_dispatch(const DispatchArgs &da, hipStream_t s)
+{
+    DeviceInfo di;
+    const qmoe_status st = device_info(&di);
+    return st != QMOE_OK ? st : launch_dispatch_kernel(da, di.max_lds, s);
+}
 }  // namespace
 }  // namespace qmoe
 
@@ -751,7 +758,7 @@ qmoe_status qmoe_moe_dispatch(const qmoe_dict *d, int code_order, const int32_t 
                            (d_model % 8 == 0 && tuning().stage_out >= 0) ? 4 : 0, minmax, lanes_wo)) != QMOE_OK)
         return st;
     if ((st = plan_mm(d, code_order, d_model, d_ff, n_tokens, true, &mp)) != QMOE_OK) return st;
-    return launch_dispatch_kernel(dispatch_args(expert_idx, n_tokens, n_experts, d_model, layer_ptrs(workspace, l), pwi.tb_max,
+    return launch_dispatch(dispatch_args(expert_idx, n_tokens, n_experts, d_model, layer_ptrs(workspace, l), pwi.tb_max,
                                                 pwo.tb_max, mp.min_tokens, nullptr), static_cast<hipStream_t>(stream));
 }
 
@@ -800,7 +807,7 @@ qmoe_status layer_forward(const qmoe_dict *d, const qmoe_matrix *wi, const qmoe_
     const bool grouping = rp.on && !mm && rows_can_dispatch(n_experts, n_tokens, rp.grid, n_order, rp.max_lds);
     const DispatchArgs da = dispatch_args(expert_idx, n_tokens, n_experts, d_model, lp, pwi.tb_max, pwo.tb_max, mp.min_tokens, y);
     if ((phases & 1) && !grouping)
-        if ((st = launch_dispatch_kernel(da, s)) != QMOE_OK) return st;
+        if ((st = launch_dispatch(da, s)) != QMOE_OK) return st;
 
     // The experts with few tokens and the crowded ones are two independent chains of two
     // kernels (each second product reads only the hidden rows its own first product wrote).
@@ -988,7 +995,7 @@ qmoe_status qmoe_bf16_layer_forward(const uint16_t *const *wi_dense, const uint1
     const LayerPtrs lp = layer_ptrs(workspace, l);
     const int phases = tuning().phases > 0 ? tuning().phases : 7;
     if (phases & 1)
-        if ((st = launch_dispatch_kernel(dispatch_args(expert_idx, n_tokens, n_experts, d_model, lp, pwi.tb_max, pwo.tb_max,
+        if ((st = launch_dispatch(dispatch_args(expert_idx, n_tokens, n_experts, d_model, lp, pwi.tb_max, pwo.tb_max,
                                                        0x7FFFFFFF, y), s)) != QMOE_OK)
             return st;
     DenseArgs a{};

@@ -184,7 +184,7 @@ bool rows_can_dispatch(int n_experts, int n_tokens, int grid, int n_order, int m
 qmoe_status launch_rows(const ProductArgs &a, int x_slots, const DispatchArgs *da, int rows2, int x_slots2, int grid, int max_lds,
                         hipStream_t s);
 qmoe_status launch_decode_dense(const ProductArgs &a, bool run, int8_t *out, int grid, hipStream_t s);
-qmoe_status launch_dispatch_kernel(const DispatchArgs &da, hipStream_t s);                          // qmoe_dispatch.hip
+qmoe_status launch_dispatch_kernel(const DispatchArgs &da, int max_lds, hipStream_t s);             // qmoe_dispatch.hip
 qmoe_status launch_dense_bf16(const DenseArgs &a, const ProductPlan &p, hipStream_t s);             // qmoe_misc.hip
 qmoe_status launch_stream_copy(void *dst, const void *src, size_t n16, int grid, hipStream_t s);
 qmoe_status launch_renumber(uint16_t *codes, size_t n, const uint16_t *map, int grid, hipStream_t s);

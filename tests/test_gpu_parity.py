@@ -500,8 +500,8 @@ def test_layer_with_every_token_dropped(gpu, ddict, oracle_dict):
 
 
 def test_layer_with_thousands_of_dropped_tokens(gpu, ddict, oracle_dict):
-    """More dropped tokens than the dispatch kernel's list of them holds (2048): the rest are cleared one
-    row per thread; the kept tokens, scattered among them, still come out right."""
+    """Thousands of tokens without an expert, their rows cleared by the dispatch kernel's other workgroups; the kept
+    tokens, scattered among them, still come out right."""
     w = synth.WORKLOADS["switch_base128"].scaled(n_experts=4, d_model=72, d_ff=96, n_tokens=5000)
     x = w.tokens()
     idx = np.full(5000, -1, dtype=np.int32)
@@ -514,6 +514,38 @@ def test_layer_with_thousands_of_dropped_tokens(gpu, ddict, oracle_dict):
     dropped[keep] = False
     assert not y[dropped].any()
     _check_layer(w, idx, x, y, wsout, sorted(int(t) for t in keep))
+
+
+@pytest.mark.parametrize("E,T", [(1, 64), (31, 65), (32, 128), (33, 129), (64, 1023), (2, 1025), (2048, 2049), (4095, 4160),
+                                 (8192, 700), (16384, 3000)])
+def test_dispatch_parts(gpu, E, T):
+    """The dispatch kernel's parts of the tokens: full and ragged last ones, fewer parts where the counts of many experts fill
+    the LDS; a run of equal tokens across the parts' edges, crowded and lone experts."""
+    rng = np.random.default_rng(E + T)
+    idx = np.minimum((rng.pareto(0.8, T)).astype(np.int64), E - 1).astype(np.int32)
+    idx[T // 3:T // 3 + 70] = E - 1
+    idx[[0, T - 1]] = -1, E
+    dd = dev.DeviceDict(device=gpu)
+    ws = torch.empty(q.qmoe_moe_layer_workspace(E, 64, 128, T), dtype=torch.uint8, device=gpu)
+    q.qmoe_moe_dispatch(dd.handle, 1, torch.from_numpy(idx).to(gpu), E, 64, 128, ws)
+    torch.cuda.synchronize()
+    got = dev.read_workspace(ws, E, 64, 128, T)
+    tok_off, perm = oracle.dispatch(idx, E)
+    n = int(tok_off[-1])
+    assert np.array_equal(got["tok_off"], tok_off) and np.array_equal(got["perm"][:n], perm)
+    assert got["counters"][0] == n and got["counters"][1] == T - n
+    covered = np.zeros(n, dtype=np.int32)
+    for items, k in (("items_mm", 7), ("items_wi", 3)):
+        for e, slot0, ntok, _ in got[items][:got["counters"][k]]:
+            assert tok_off[e] <= slot0 and slot0 + ntok <= tok_off[e + 1]
+            covered[slot0:slot0 + ntok] += 1
+    assert (covered == 1).all()
+    assert np.array_equal(got["items_wi"][:got["counters"][3]], got["items_wo"][:got["counters"][4]])
+    sizes = got["items_wi"][:got["counters"][3], 2]
+    by_class = [int(((sizes > 4)).sum()), int(((sizes > 2) & (sizes <= 4)).sum()), int((sizes == 2).sum()), int((sizes == 1).sum())]
+    assert list(got["counters"][10:14]) == by_class
+    assert (np.diff(np.where(sizes > 2, 3, sizes)) <= 0).all()  # longest first
+    dd.close()
 
 
 def test_dispatch_many_tokens(gpu):
