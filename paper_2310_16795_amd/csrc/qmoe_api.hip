@@ -802,7 +802,11 @@ qmoe_status layer_forward(const qmoe_dict *d, const qmoe_matrix *wi, const qmoe_
     const LayerPtrs lp = layer_ptrs(workspace, l);
     const int phases = tuning().phases > 0 ? tuning().phases : 31;
     RowsPlan rp;
-    if (pwi.tb_max == pwo.tb_max) rp = rows_plan(d, code_order, n_experts, lanes_wi != 0, d_model, d_ff, n_tokens, pwi.tb_max);
+    if (pwi.tb_max == pwo.tb_max) {
+        const int tb = std::min(pwi.tb_max, kRowsTokenTile);
+        rp = rows_plan(d, code_order, n_experts, lanes_wi != 0, d_model, d_ff, n_tokens, tb);
+        if (rp.on) pwi.tb_max = pwo.tb_max = tb;
+    }
     // In a small call the kernel with several lanes per row groups the tokens itself.
     const bool grouping = rp.on && !mm && rows_can_dispatch(n_experts, n_tokens, rp.grid, n_order, rp.max_lds);
     const DispatchArgs da = dispatch_args(expert_idx, n_tokens, n_experts, d_model, lp, pwi.tb_max, pwo.tb_max, mp.min_tokens, y);

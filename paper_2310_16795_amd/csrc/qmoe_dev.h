@@ -155,6 +155,7 @@ struct MmPlan {
 
 // matrix-core kernel: shape constants the planner needs
 constexpr int kProductMaxThreads = 768;  // largest workgroup of k_product
+constexpr int kRowsTokenTile = 4;        // largest token tile of k_rows (with tiles of eight it had twice the instructions to fetch, and registers spilled)
 constexpr int kRowsMaxGrid = 512;        // workgroups of k_rows that a workspace has share records for
 constexpr size_t kRowsShareBytes = 64;   // a record
 constexpr int kMmThreads = 512;

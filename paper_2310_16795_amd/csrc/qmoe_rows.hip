@@ -259,7 +259,7 @@ struct RowsShare {
     int i0, r0, i1, r1;
 };
 
-// Share `b` of `n` of all rows of the items, cls[k] of them of class k.  (Double precision in place of 64-bit integer
+// Share `b` of `n` of all rows of the items, cls[k] of them of class k; by a whole wavefront.  (Double precision in place of 64-bit integer
 // divisions, each of which is a hundred instructions: a place is the same function of its cost for the share that
 // ends there and the one that begins there, so rounding moves a boundary by a few rows at most and loses none.)
 __device__ __forceinline__ RowsShare rows_share(const int (&cls)[4], const RowsSplit &sp, int n, int b)
@@ -281,16 +281,22 @@ __device__ __forceinline__ RowsShare rows_share(const int (&cls)[4], const RowsS
             top = cls[k] ? cls[k] : top;
         }
         const float inv_cost = 1.0f / (float)top_cost;
-        // (an even split of the cost would give it this many; rounding up needs fewer, rarely by more than a few)
-        g = min((int)((float)n / (float)top), (int)((float)(top_cost * eights) * (float)n / (float)total) + 1);
-        for (; g >= 1; g--) {
-            used = 0;
+        auto parts_of = [&](int k, int g_) { return (int)ceilf((float)(kRowCost[k] * g_) * inv_cost - 1e-3f); };
+        // (An even split of the cost would give it this many; rounding up needs fewer, rarely by more than a few.  A lane tries
+        // each: the first that fits.)
+        const int most = min((int)((float)n / (float)top), (int)((float)(top_cost * eights) * (float)n / (float)total) + 1);
+        for (int from = most; from >= 1 && g == 0; from -= 64) {
+            const int mine = from - (int)(threadIdx.x & 63u);
+            int need = 0;
 #pragma unroll
-            for (int k = 0; k < 4; k++) {
-                parts[k] = (int)ceilf((float)(kRowCost[k] * g) * inv_cost - 1e-3f);
-                used += parts[k] * cls[k];
-            }
-            if (used <= n) break;
+            for (int k = 0; k < 4; k++) need += parts_of(k, mine) * cls[k];
+            const unsigned long long fits = __ballot(mine >= 1 && need <= n);
+            if (fits) g = from - __builtin_ctzll(fits);
+        }
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            parts[k] = parts_of(k, g);
+            used += parts[k] * cls[k];
         }
     }
     // That is uneven when there are nearly as many items as workgroups; equal shares of the whole list begin and
@@ -320,35 +326,34 @@ __device__ __forceinline__ RowsShare rows_share(const int (&cls)[4], const RowsS
         s.r0 = 8 * (int)((float)at * step);
         s.r1 = at + 1 == p ? rows : 8 * (int)((float)(at + 1) * step);
     } else {
-        // the place in the list where the first `c` units of cost end; rows in eights
-        auto place = [&](double c, int &item, int &row) {
-            item = 0;
-            row = 0;
-            bool found = false;
+        // The places in the list where the first `c` units of cost end, rows in eights: even lanes where the share begins, odd
+        // ones where it ends.
+        double c = floor(total * sp.inv_grid * (double)(b + (int)(threadIdx.x & 1u)));
+        int item = 0, row = 0;
+        bool found = false;
 #pragma unroll
-            for (int k = 0; k < 4; k++) {
-                const double per = (double)(kRowCost[k] * eights), here = (double)cls[k] * per;
-                if (!found) {
-                    if (c < here) {
-                        const int i = min((int)(c * sp.inv_item[k]), cls[k] - 1);
-                        const double in_item = c - (double)i * per;
-                        item += i;
-                        row = 8 * max(0, min((int)((float)in_item * (1.0f / (float)kRowCost[k])), eights));
-                        found = true;
-                    } else {
-                        c -= here;
-                        item += cls[k];
-                    }
+        for (int k = 0; k < 4; k++) {
+            const double per = (double)(kRowCost[k] * eights), here = (double)cls[k] * per;
+            if (!found) {
+                if (c < here) {
+                    const int i = min((int)(c * sp.inv_item[k]), cls[k] - 1);
+                    const double in_item = c - (double)i * per;
+                    item += i;
+                    row = 8 * max(0, min((int)((float)in_item * (1.0f / (float)kRowCost[k])), eights));
+                    found = true;
+                } else {
+                    c -= here;
+                    item += cls[k];
                 }
             }
-        };
-        place(floor(total * sp.inv_grid * (double)b), s.i0, s.r0);
+        }
+        s.i0 = __builtin_amdgcn_readlane(item, 0);
+        s.r0 = __builtin_amdgcn_readlane(row, 0);
+        s.i1 = __builtin_amdgcn_readlane(item, 1);
+        s.r1 = min(__builtin_amdgcn_readlane(row, 1), rows);
         if (b + 1 == n) {
             s.i1 = n_items - 1;
             s.r1 = rows;
-        } else {
-            place(floor(total * sp.inv_grid * (double)(b + 1)), s.i1, s.r1);
-            s.r1 = min(s.r1, rows);
         }
         if (s.i0 >= n_items) s.i1 = -1;
     }
@@ -372,125 +377,246 @@ constexpr int kShareInts = 4 + 2 * kKeptSegments;
 // ---- grouping the tokens by expert inside the first product
 //
 // In a small call (rows_can_dispatch) the grouping is a few thousand operations, less than the launch of a kernel for it and
-// the trips to memory for its results: every workgroup does it for itself, in LDS.  A bit per token and expert gives a
-// token's rank among its expert's tokens and the expert's count; experts in order give slots and items (longest class
-// first), the same lists k_dispatch writes.
+// the trips to memory for its results: every workgroup does it for itself, in LDS, and leaves its part of the lists that
+// k_dispatch would write in the workspace.
 constexpr int kInlineTokens = 512;
 constexpr size_t kInlineMaskBytes = 64 * 1024;
 
 struct InlineLists {
-    int cls[4];
-    lp_u32 items;              // [n] {expert, slot0 | ntok << 16}
-    const __attribute__((address_space(3))) int *perm;  // [T]
+    int cls[4], kept, experts;  // items by class, tokens with an expert, experts with tokens
+    lp_u32 items;               // [n] {expert, slot0 | ntok << 16}
+    const __attribute__((address_space(3))) int *perm;  // [kept]
+    const __attribute__((address_space(3))) int *off;   // [E] first slot of every expert, or (few tokens) ...
+    lp_u32 sorted;                                      // ... nullptr, and [kept] the slots' experts
 };
 
 __device__ __forceinline__ size_t inline_mask_words(int E, int T) { return (size_t)E * ((T + 31) >> 5); }
 
-// `scratch`: LDS of inline_lds_bytes(E, T); `e` the expert of token threadIdx.x (-1: none).  Workgroup 0 also writes the lists
-// to the workspace.
-__device__ __forceinline__ InlineLists group_tokens(const DispatchArgs &d, int e, unsigned char *scratch)
+// Up to 64 tokens: all of it in the registers of wavefront 0, a lane a token.  A ballot per bit of the experts tells a lane
+// which tokens have the same expert and which a smaller one.  `e` the lane's expert (-1: none).
+__device__ __forceinline__ void group_few(const DispatchArgs &d, int e, int *perm, uint32_t *items, uint32_t *sorted, int *totals)
 {
-    const int T = d.n_tokens, E = d.n_experts, tid = threadIdx.x, nthr = blockDim.x;
+    const int E = d.n_experts, lane = (int)threadIdx.x;
+    const bool valid = e >= 0;
+    const int key = valid ? e : E;  // (behind all experts)
+    uint32_t eq[2] = {~0u, ~0u}, less[2] = {0u, 0u};
+    for (int b = 31 - __builtin_clz(E); b >= 0; b--) {
+        const uint32_t one = (uint32_t)__builtin_amdgcn_sbfe(key, (uint32_t)b, 1u);  // 0 or all ones
+        const unsigned long long ones = __ballot(one != 0u);
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+            const uint32_t o = (uint32_t)(ones >> (32 * h));
+            less[h] |= eq[h] & ~o & one;
+            eq[h] &= ~(o ^ one);
+        }
+    }
+    const int rank = (int)__builtin_amdgcn_mbcnt_hi(eq[1], __builtin_amdgcn_mbcnt_lo(eq[0], 0u));
+    const int slot = __popc(less[0]) + __popc(less[1]) + rank, left = __popc(eq[0]) + __popc(eq[1]) - rank;
+    const int kept = __popcll(__ballot(valid));
+    // into the slots' order: experts in order, an expert's tokens in theirs; a tile begins at every d.tb_wi-th (a power of two)
+    if (valid) {
+        const bool head = (rank & (d.tb_wi - 1)) == 0;
+        perm[slot] = lane;
+        items[slot] = (uint32_t)e | (head ? (uint32_t)min(left, d.tb_wi) << 16 : 0u) | (rank == 0 ? 1u << 24 : 0u);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const uint32_t v = lane < kept ? items[lane] : 0u;
+    const int expert = (int)(v & 0xFFFFu), m = (int)((v >> 16) & 0xFFu);
+    if (lane < kept) sorted[lane] = (uint32_t)expert;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    int base = 0, to = 0;
+#pragma unroll
+    for (int c = 0; c < 4; c++) {
+        const bool here = m > 0 && tile_class(m) == c;
+        const unsigned long long all = __ballot(here);
+        if (here) to = base + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(all >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)all, 0u));
+        base += __popcll(all);
+        if (lane == c) totals[c] = __popcll(all);
+    }
+    if (m > 0) {
+        items[2 * to] = (uint32_t)expert;
+        items[2 * to + 1] = (uint32_t)lane | (uint32_t)m << 16;
+    }
+    const int experts = __popcll(__ballot((v >> 24) != 0u));
+    if (lane == 0) {
+        totals[4] = kept;
+        totals[5] = experts;
+    }
+}
+
+// More tokens: a bit per token and expert gives a token's rank among its expert's tokens and the expert's count; experts in
+// order give slots and items (longest class first).  `e` the expert of token threadIdx.x.  Barriers wait for LDS only.
+__device__ __forceinline__ void group_many(const DispatchArgs &d, int e, uint32_t *mask, int *off, int *perm, uint32_t *items, int *tmp,
+                                           int *totals)
+{
+    const int T = d.n_tokens, E = d.n_experts, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int mw = (T + 31) >> 5;
-    uint32_t *mask = reinterpret_cast<uint32_t *>(scratch);
-    int *off = reinterpret_cast<int *>(mask + inline_mask_words(E, T));  // [E] first slot
-    int *perm = off + E;                                                  // [T]
-    uint32_t *items = reinterpret_cast<uint32_t *>(perm + T);             // [2 T]
-    int *tmp = reinterpret_cast<int *>(items + 2 * T);                    // [17 * 3] scan scratch
-    for (int i = tid; i < E * mw; i += nthr) mask[i] = 0u;
-    __syncthreads();
+    for (int i = tid; i < E * mw; i += kRowsThreads) mask[i] = 0u;
+    lds_barrier();
     if (e >= 0) atomicOr(&mask[e * mw + (tid >> 5)], 1u << (tid & 31));
-    __syncthreads();
-    const int chunk = (E + nthr - 1) / nthr, e0 = min(E, tid * chunk), e1 = min(E, e0 + chunk);
+    lds_barrier();
+    const int chunk = (E + kRowsThreads - 1) / kRowsThreads, e0 = min(E, tid * chunk), e1 = min(E, e0 + chunk);
     auto count = [&](int x) {
         int n = 0;
         for (int w = 0; w < mw; w++) n += __popc(mask[x * mw + w]);
         return n;
     };
+    const int kw = tile_class(d.tb_wi), log2_tb = __builtin_ctz(d.tb_wi);
     int sums[3] = {0, 0, 0};  // two 16-bit counts each: tokens | class 0, class 1 | class 2, class 3 | experts with tokens
+    int n_first = 0;
     for (int x = e0; x < e1; x++) {
         const int n = count(x);
+        if (x == e0) n_first = n;
         if (n) {
-            const int whole = n / d.tb_wi, rest = n % d.tb_wi, kw = tile_class(d.tb_wi), kr = rest ? tile_class(rest) : -1;
+            const int whole = n >> log2_tb, rest = n & (d.tb_wi - 1), kr = rest ? tile_class(rest) : -1;
             auto of = [&](int k) { return (k == kw ? whole : 0) + (k == kr ? 1 : 0); };
             sums[0] += n | of(0) << 16;
             sums[1] += of(1) | of(2) << 16;
             sums[2] += of(3) | 1 << 16;
         }
     }
+    // prefix sums: within the wavefronts, then every wavefront adds up the totals of those before it
+    constexpr int waves = kRowsThreads / 64;
     int before[3], all[3];
-    block_exclusive_scan_n<3>(sums, tmp, before, all);
-    InlineLists r;
-    r.cls[0] = all[0] >> 16;
-    r.cls[1] = all[1] & 0xFFFF;
-    r.cls[2] = all[1] >> 16;
-    r.cls[3] = all[2] & 0xFFFF;
-    int slot = before[0] & 0xFFFF;
-    int at[4] = {before[0] >> 16, r.cls[0] + (before[1] & 0xFFFF), r.cls[0] + r.cls[1] + (before[1] >> 16),
-                 r.cls[0] + r.cls[1] + r.cls[2] + (before[2] & 0xFFFF)};
-    const bool record = blockIdx.x == 0;
-    for (int x = e0; x < e1; x++) {
-        const int n = count(x);
-        off[x] = slot;
-        if (record) d.tok_off[x] = slot;
-        for (int i = 0; i < n; i += d.tb_wi) {
-            const int m = min(d.tb_wi, n - i), k = tile_class(m);
-            int to = 0;
 #pragma unroll
-            for (int c = 0; c < 4; c++)
-                if (c == k) to = at[c]++;
-            items[2 * to] = (uint32_t)x;
-            items[2 * to + 1] = (uint32_t)(slot + i) | (uint32_t)m << 16;
-            if (record) d.items_wi[to] = d.items_wo[to] = Item{x, slot + i, m, 0};
+    for (int k = 0; k < 3; k++) {
+        before[k] = wave_inclusive_scan(sums[k]);
+        if (lane == 63) tmp[k * waves + wave] = before[k];
+        before[k] -= sums[k];
+    }
+    lds_barrier();
+#pragma unroll
+    for (int k = 0; k < 3; k++) {
+        const int run = row_scan16(lane < waves ? tmp[k * waves + lane] : 0);
+        all[k] = __builtin_amdgcn_readlane(run, waves - 1);
+        before[k] += wave ? __builtin_amdgcn_readlane(run, __builtin_amdgcn_readfirstlane(wave) - 1) : 0;
+    }
+    const int cls[4] = {all[0] >> 16, all[1] & 0xFFFF, all[1] >> 16, all[2] & 0xFFFF};
+    int slot = before[0] & 0xFFFF;
+    int at[4] = {before[0] >> 16, cls[0] + (before[1] & 0xFFFF), cls[0] + cls[1] + (before[1] >> 16),
+                 cls[0] + cls[1] + cls[2] + (before[2] & 0xFFFF)};
+    for (int x = e0; x < e1; x++) {
+        const int n = x == e0 ? n_first : count(x);
+        off[x] = slot;
+        const int whole = n >> log2_tb, rest = n & (d.tb_wi - 1), kr = tile_class(rest);
+        int first = 0, last = 0;
+#pragma unroll
+        for (int c = 0; c < 4; c++) {
+            if (c == kw) {
+                first = at[c];
+                at[c] += whole;
+            }
+            if (c == kr && rest) last = at[c]++;
+        }
+        for (int i = 0; i < whole; i++) {
+            items[2 * (first + i)] = (uint32_t)x;
+            items[2 * (first + i) + 1] = (uint32_t)(slot + (i << log2_tb)) | (uint32_t)d.tb_wi << 16;
+        }
+        if (rest) {
+            items[2 * last] = (uint32_t)x;
+            items[2 * last + 1] = (uint32_t)(slot + (whole << log2_tb)) | (uint32_t)rest << 16;
         }
         slot += n;
     }
-    __syncthreads();
+    if (tid < 4) totals[tid] = tid == 0 ? cls[0] : (tid == 1 ? cls[1] : (tid == 2 ? cls[2] : cls[3]));
+    if (tid == 4) totals[4] = all[0] & 0xFFFF;
+    if (tid == 5) totals[5] = all[2] >> 16;
+    lds_barrier();
     if (e >= 0) {
         int rank = 0;
         for (int w = 0; w < (tid >> 5); w++) rank += __popc(mask[e * mw + w]);
         rank += __popc(mask[e * mw + (tid >> 5)] & ((1u << (tid & 31)) - 1u));
         perm[off[e] + rank] = tid;
-        if (record) d.perm[off[e] + rank] = tid;
     }
-    if (record) {
-        const int kept = all[0] & 0xFFFF;
-        if (tid < kLayerCounters) {
-            const int n = r.cls[0] + r.cls[1] + r.cls[2] + r.cls[3];
-            int v = 0;
-            v = tid == 0 ? kept : v;
-            v = tid == 1 ? T - kept : v;
-            v = tid == 2 ? all[2] >> 16 : v;
-            v = tid == 3 || tid == 4 ? n : v;
-            v = tid >= 10 && tid < 14 ? r.cls[(tid - 10) & 3] : v;
-            d.counters[tid] = v;
-        }
-        if (tid == 0) d.tok_off[E] = kept;
+}
+
+// `scratch`: LDS of inline_lds_bytes(E, T); `e` the expert of token threadIdx.x (-1: none).
+__device__ __forceinline__ InlineLists group_tokens(const DispatchArgs &d, int e, unsigned char *scratch)
+{
+    const int T = d.n_tokens, E = d.n_experts;
+    const bool few = T <= 64;
+    int *totals = reinterpret_cast<int *>(scratch);                      // [8]
+    uint32_t *mask = reinterpret_cast<uint32_t *>(totals + 8);           // (few tokens: none)
+    int *off = reinterpret_cast<int *>(mask + (few ? 0 : inline_mask_words(E, T)));  // [E] first slot; few tokens: [T] experts by slot
+    int *perm = off + (few ? T : E);                                     // [T]
+    uint32_t *items = reinterpret_cast<uint32_t *>(perm + T);            // [2 T]
+    int *tmp = reinterpret_cast<int *>(items + 2 * T);                   // [3 * 16] scan scratch
+    if (few) {
+        if (threadIdx.x < 64) group_few(d, e, perm, items, reinterpret_cast<uint32_t *>(off), totals);
+    } else {
+        group_many(d, e, mask, off, perm, items, tmp, totals);
     }
-    __syncthreads();
+    lds_barrier();
+    InlineLists r;
+#pragma unroll
+    for (int k = 0; k < 4; k++) r.cls[k] = __builtin_amdgcn_readfirstlane(totals[k]);
+    r.kept = __builtin_amdgcn_readfirstlane(totals[4]);
+    r.experts = __builtin_amdgcn_readfirstlane(totals[5]);
     r.items = (lp_u32)items;
     r.perm = (const __attribute__((address_space(3))) int *)perm;
+    r.off = few ? nullptr : (const __attribute__((address_space(3))) int *)off;
+    r.sorted = (lp_u32)(uint32_t *)off;
     return r;
+}
+
+// The lists as k_dispatch leaves them in the workspace, a part by every workgroup (one that wrote them all would be the last
+// to begin its rows).
+__device__ __forceinline__ void record_lists(const DispatchArgs &d, const InlineLists &r)
+{
+    const int i0 = (int)(threadIdx.x * gridDim.x + blockIdx.x), step = kRowsThreads * (int)gridDim.x;
+    const int n = r.cls[0] + r.cls[1] + r.cls[2] + r.cls[3], E = d.n_experts;
+    for (int i = i0; i <= E; i += step) {
+        int slot = r.kept;  // slots below expert i
+        if (i < E) {
+            if (r.off) {
+                slot = r.off[i];
+            } else {
+                int lo = 0;
+                for (int half = 64; half >= 1; half >>= 1)
+                    if (lo + half <= r.kept && (int)r.sorted[lo + half - 1] < i) lo += half;
+                slot = lo;
+            }
+        }
+        d.tok_off[i] = slot;
+    }
+    if (i0 < n) {
+        const uint32_t v = r.items[2 * i0 + 1];
+        d.items_wi[i0] = d.items_wo[i0] = Item{(int)r.items[2 * i0], (int)(v & 0xFFFFu), (int)(v >> 16), 0};
+    }
+    if (i0 < r.kept) d.perm[i0] = r.perm[i0];
+    if (blockIdx.x == 0 && threadIdx.x < kLayerCounters) {
+        const int k = (int)threadIdx.x;
+        int v = 0;
+        v = k == 0 ? r.kept : v;
+        v = k == 1 ? d.n_tokens - r.kept : v;
+        v = k == 2 ? r.experts : v;
+        v = k == 3 || k == 4 ? n : v;
+        v = k == 10 ? r.cls[0] : (k == 11 ? r.cls[1] : (k == 12 ? r.cls[2] : (k == 13 ? r.cls[3] : v)));
+        d.counters[k] = v;
+    }
 }
 
 // Activations of a tile on their way to LDS: column pairs threadIdx.x, + 1024, ... of up to four tokens.  All loads are
 // issued before the first store (a loop that loads and stores a piece at a time waits for every load in turn: 4 us for
 // four tokens of 3072 columns).
+template <int PIECES = 4>  // 8192 columns
 struct XPairs {
-    static constexpr int kPieces = 4;  // 8192 columns; wider tiles go round again
+    static constexpr int kPieces = PIECES;
     uint32_t v[kPieces][4];
 };
 typedef uint32_t u32_any __attribute__((aligned(2)));
 using gp_u32_any = const __attribute__((address_space(1))) u32_any *;
 
-template <typename RowOf>
-__device__ __forceinline__ void x_load(XPairs &p, const uint16_t *x, RowOf row_of, int ntok, int ldx, int cols, int base)
+template <int PIECES, typename RowOf>
+__device__ __forceinline__ void x_load(XPairs<PIECES> &p, const uint16_t *x, RowOf row_of, int ntok, int ldx, int cols, int base)
 {
     uintptr_t src[4];
 #pragma unroll
     for (int t = 0; t < 4; t++) src[t] = reinterpret_cast<uintptr_t>(x) + 2 * (size_t)row_of(min(t, ntok - 1)) * (size_t)ldx;
 #pragma unroll
-    for (int k = 0; k < XPairs::kPieces; k++) {
+    for (int k = 0; k < PIECES; k++) {
         const int c = 2 * (base + k * kRowsThreads + (int)threadIdx.x);
         const uintptr_t at = 2 * (uintptr_t)min(c, cols - 2);
         if (2 * (base + k * kRowsThreads) < cols) {  // (uniform)
@@ -503,11 +629,12 @@ __device__ __forceinline__ void x_load(XPairs &p, const uint16_t *x, RowOf row_o
     }
 }
 
-__device__ __forceinline__ void x_store(const XPairs &p, unsigned char *xs, int ntok, int cols, int base)
+template <int PIECES>
+__device__ __forceinline__ void x_store(const XPairs<PIECES> &p, unsigned char *xs, int ntok, int cols, int base)
 {
     const int n = cols + kRowsPadCols;
 #pragma unroll
-    for (int k = 0; k < XPairs::kPieces; k++) {
+    for (int k = 0; k < PIECES; k++) {
         const int c = 2 * (base + k * kRowsThreads + (int)threadIdx.x);
         if (c < n) {
             const bool in = c < cols;
@@ -533,8 +660,43 @@ __device__ __forceinline__ void x_store(const XPairs &p, unsigned char *xs, int 
 // LDS of the shares, segments and gates
 constexpr int kRowsSmallBytes = (4 * 8 + (int)sizeof(RowsSegment) * kKeptSegments + 4 * 2 * kMaxTokenTile + 15) / 16 * 16;
 
+// The table on its way to LDS: asked for first of all, stored when the loads that the rows wait for are on their way.  (Pieces of
+// 16 bytes, the last one perhaps reaching into the space behind the table's last entry: the blob reserves kMaxOrderTable entries.)
+struct TablePieces {
+    static constexpr int kPieces = (kMaxOrderTable / 4 + kRowsThreads - 1) / kRowsThreads;
+    u32x4 v[kPieces];
+};
+
+__device__ __forceinline__ void table_load(TablePieces &p, const uint32_t *table, int n)
+{
+    const int n4 = (n + 3) >> 2;
+#pragma unroll
+    for (int k = 0; k < TablePieces::kPieces; k++) p.v[k] = ((gp_u32x4)table)[min(k * kRowsThreads + (int)threadIdx.x, n4 - 1)];
+}
+
+__device__ __forceinline__ void table_store(const TablePieces &p, uint32_t *table_lds, int n)
+{
+    const int n4 = (n + 3) >> 2;
+#pragma unroll
+    for (int k = 0; k < TablePieces::kPieces; k++) {
+        const int i = k * kRowsThreads + (int)threadIdx.x;
+        if (i < n4) reinterpret_cast<u32x4 *>(table_lds)[i] = p.v[k];
+    }
+}
+
+// The items of a batch (one or two, worked on side by side), the same in every lane.
+struct RowsBatchItem {
+    int expert, slot0, ntok, ra, rb;
+};
+
 // GROUP: the launch groups the tokens itself (first product of a small call); split2: of the second product, for whose
 // shares it leaves records.
+//
+// Small calls are bound by the way to the first codeword: share -> descriptor -> row offsets -> codewords, each a trip to
+// memory, with the table, the activations and the grouping beside them.  So the table is asked for first and stored last, a
+// second product's record is read by every wavefront itself, what wavefront 0 works out goes round with one barrier, and no
+// barrier waits for a load or a store of global memory (__syncthreads does).  One token on 2048 experts of 2080 x 6144: 21.5 -> 18.4 us;
+// 128 on 128 of 768 x 3072: 45.6 -> 42.7; 512 on 128 of 1024 x 4096: 119.8 -> 116.8.
 template <int EPI, int ASYM, bool GROUP, int LANES>
 __global__ __launch_bounds__(kRowsThreads) void k_rows(const ProductArgs a, const DispatchArgs d, const RowsSplit split, const RowsSplit split2)
 {
@@ -543,7 +705,7 @@ __global__ __launch_bounds__(kRowsThreads) void k_rows(const ProductArgs a, cons
     // of the grouping)
     uint32_t *table_w = reinterpret_cast<uint32_t *>(smem);
     const size_t table_bytes = ((size_t)a.n_order * 4 + 15) & ~(size_t)15;
-    int *share_s = reinterpret_cast<int *>(smem + table_bytes);                       // [2][4]
+    int *share_s = reinterpret_cast<int *>(smem + table_bytes);                       // [8]
     RowsSegment *seg_s = reinterpret_cast<RowsSegment *>(share_s + 8);                // [kKeptSegments]
     float *gate_s = reinterpret_cast<float *>(seg_s + kKeptSegments);                 // [2][kMaxTokenTile]
     unsigned char *xs0 = smem + table_bytes + kRowsSmallBytes;
@@ -557,16 +719,22 @@ __global__ __launch_bounds__(kRowsThreads) void k_rows(const ProductArgs a, cons
     if constexpr (!GROUP) {
         if (a.items && !a.shares && (a.class_counts[0] | a.class_counts[1] | a.class_counts[2] | a.class_counts[3]) == 0) return;
     }
+    const bool recorded = !GROUP && a.shares && a.x_by_slot;  // the share is in a record of the first product's
+
+    // ---- the first loads, in the order in which they are wanted
+    int e = -1, record = 0;
+    if constexpr (GROUP) {
+        if ((int)threadIdx.x < d.n_tokens) e = d.expert_idx[threadIdx.x];
+    } else if (recorded) {
+        record = a.shares[blockIdx.x * kShareInts + (lane & (kShareInts - 1))];
+    }
+    TablePieces tp;
+    table_load(tp, a.order_table, a.n_order);
 
     // ---- this workgroup's share of the rows
     InlineLists lists;
     if constexpr (GROUP) {
-        int e = -1;
-        if ((int)threadIdx.x < d.n_tokens) {
-            e = d.expert_idx[threadIdx.x];
-            if (e < 0 || e >= d.n_experts) e = -1;
-        }
-        stage_words(table_w, a.order_table, a.n_order);
+        if (e < 0 || e >= d.n_experts) e = -1;
         // The output rows of tokens without an expert are cleared by all workgroups, a row at a time and in whole lines: a rank
         // that holds a part of the experts has mostly such tokens (512 tokens, 448 of them without an expert, on experts of
         // 768 x 3072: 230 us when a thread of workgroup 0 cleared a row, 38 us now; 2080 x 6144: 559 and 89 us).  Here,
@@ -579,47 +747,105 @@ __global__ __launch_bounds__(kRowsThreads) void k_rows(const ProductArgs a, cons
         }
         lists = group_tokens(d, e, xs0);
     }
-    // (wavefront 0; with GROUP wavefront 1 does the same for the second product)
-    if (wave < (GROUP ? 2 : 1)) {
-        RowsShare sh;
-        if constexpr (GROUP) {
-            sh = rows_share(lists.cls, wave ? split2 : split, (int)gridDim.x, (int)blockIdx.x);
-        } else if (a.shares) {
-            const int *p = a.shares + blockIdx.x * kShareInts;
-            sh = RowsShare{p[0], p[1], p[2], p[3]};
-        } else {
-            int cls[4];
-            if (a.items) {
-#pragma unroll
-                for (int k = 0; k < 4; k++) cls[k] = a.class_counts[k];
+    // The items a share has at `i_base` and behind it, into LDS: by wavefront 0, eight lanes for each item, a token apiece.
+    struct SegmentPart {
+        int expert, slot0, ntok, tok;
+        bool ok;
+    };
+    const int seg_k = lane / kMaxTokenTile, seg_t = lane % kMaxTokenTile;
+    auto load_segments = [&](const RowsShare &sh, int i_base) -> SegmentPart {
+        const int i = i_base + seg_k;
+        SegmentPart p{-1, 0, 0, 0, false};
+        const int rec_expert = GROUP ? 0 : __shfl(record, 4 + 2 * seg_k, 64), rec_at = GROUP ? 0 : __shfl(record, 5 + 2 * seg_k, 64);
+        if (i <= sh.i1 && seg_k < kKeptSegments) {
+            if constexpr (GROUP) {
+                p.expert = (int)lists.items[2 * i];
+                p.slot0 = (int)(lists.items[2 * i + 1] & 0xFFFFu);
+                p.ntok = (int)(lists.items[2 * i + 1] >> 16);
+            } else if (recorded) {  // (such a share is looked at in one go)
+                p.expert = rec_expert;
+                p.slot0 = rec_at & 0xFFFF;
+                p.ntok = rec_at >> 16;
+            } else if (a.items) {
+                const Item it = a.items[i];
+                p.expert = it.expert;
+                p.slot0 = it.slot0;
+                p.ntok = it.ntok;
             } else {
-                const int n = (a.batch + a.tb_max - 1) / a.tb_max;
-                cls[0] = a.tb_max > 4 ? n : 0;
-                cls[1] = a.tb_max > 2 && a.tb_max <= 4 ? n : 0;
-                cls[2] = a.tb_max == 2 ? n : 0;
-                cls[3] = a.tb_max == 1 ? n : 0;
+                p.expert = 0;
+                p.slot0 = i * a.tb_max;
+                p.ntok = a.batch - p.slot0;
             }
-            sh = rows_share(cls, split, (int)gridDim.x, (int)blockIdx.x);
         }
-        if (lane == 0) {
-            share_s[4 * wave] = sh.i0;
-            share_s[4 * wave + 1] = sh.r0;
-            share_s[4 * wave + 2] = sh.i1;
-            share_s[4 * wave + 3] = sh.r1;
+        p.ntok = min(p.ntok, a.tb_max);
+        p.ok = p.expert >= 0 && p.expert < a.n_experts && p.ntok > 0;
+        if (p.ok) {
+            const int at = p.slot0 + min(seg_t, p.ntok - 1);
+            if constexpr (GROUP) p.tok = lists.perm[at];
+            else p.tok = a.perm ? a.perm[at] : at;
         }
+        return p;
+    };
+    auto store_segments = [&](const SegmentPart &p, const RowsShare &sh, int i_base) {
+        const int i = i_base + seg_k;
+        if (seg_k >= kKeptSegments) return;
+        RowsSegment &g = seg_s[seg_k];
+        if (seg_t == 0) {
+            g.expert = p.ok ? p.expert : 0;
+            g.slot0 = p.slot0;
+            g.ntok = p.ntok;
+            g.ra = i == sh.i0 ? sh.r0 : 0;
+            g.rb = !p.ok ? g.ra : (i == sh.i1 ? sh.r1 : a.rows);
+        }
+        g.tok[seg_t] = p.tok;
+    };
+    SegmentPart seg_own{};  // (recorded: stored with the table)
+    RowsShare sh;
+    if (recorded) {
+        sh = RowsShare{__builtin_amdgcn_readlane(record, 0), __builtin_amdgcn_readlane(record, 1), __builtin_amdgcn_readlane(record, 2),
+                       __builtin_amdgcn_readlane(record, 3)};
+        if (wave == 0) seg_own = load_segments(sh, sh.i0);
+    } else {
+        if (wave == 0) {
+            if constexpr (GROUP) {
+                sh = rows_share(lists.cls, split, (int)gridDim.x, (int)blockIdx.x);
+            } else {
+                int cls[4];
+                if (a.items) {
+#pragma unroll
+                    for (int k = 0; k < 4; k++) cls[k] = a.class_counts[k];
+                } else {
+                    const int n = (a.batch + a.tb_max - 1) / a.tb_max;
+                    cls[0] = a.tb_max > 4 ? n : 0;
+                    cls[1] = a.tb_max > 2 && a.tb_max <= 4 ? n : 0;
+                    cls[2] = a.tb_max == 2 ? n : 0;
+                    cls[3] = a.tb_max == 1 ? n : 0;
+                }
+                sh = rows_share(cls, split, (int)gridDim.x, (int)blockIdx.x);
+            }
+            if (lane == 0) {
+                share_s[0] = sh.i0;
+                share_s[1] = sh.r0;
+                share_s[2] = sh.i1;
+                share_s[3] = sh.r1;
+            }
+            store_segments(load_segments(sh, sh.i0), sh, sh.i0);
+        }
+        if constexpr (GROUP) {
+            if (wave == 1 && a.shares) {  // the second product's share
+                const RowsShare s2 = rows_share(lists.cls, split2, (int)gridDim.x, (int)blockIdx.x);
+                const int n = lists.cls[0] + lists.cls[1] + lists.cls[2] + lists.cls[3], i = min(s2.i0 + ((lane - 4) >> 1), n - 1);
+                const int place = lane == 0 ? s2.i0 : (lane == 1 ? s2.r0 : (lane == 2 ? s2.i1 : s2.r1));
+                if (lane < kShareInts)
+                    a.shares[blockIdx.x * kShareInts + lane] = lane < 4 ? place : (n ? (int)lists.items[2 * i + (lane & 1)] : 0);
+            }
+            record_lists(d, lists);
+        }
+        lds_barrier();
+        sh = RowsShare{__builtin_amdgcn_readfirstlane(share_s[0]), __builtin_amdgcn_readfirstlane(share_s[1]),
+                       __builtin_amdgcn_readfirstlane(share_s[2]), __builtin_amdgcn_readfirstlane(share_s[3])};
     }
-    if constexpr (!GROUP) stage_words(table_w, a.order_table, a.n_order);
-    __syncthreads();
-    if constexpr (GROUP) {
-        if (a.shares && threadIdx.x < (unsigned)kShareInts) {
-            const int k = threadIdx.x, n = lists.cls[0] + lists.cls[1] + lists.cls[2] + lists.cls[3];
-            const int i = min(share_s[4] + ((k - 4) >> 1), n - 1);
-            a.shares[blockIdx.x * kShareInts + k] = k < 4 ? share_s[4 + k] : (n ? (int)lists.items[2 * i + (k & 1)] : 0);
-        }
-    }
-    const int i1 = __builtin_amdgcn_readfirstlane(share_s[2]);
-    int i_base = __builtin_amdgcn_readfirstlane(share_s[0]);
-    if (i_base > i1 || (i_base == i1 && share_s[1] >= share_s[3])) return;
+    if (sh.i0 > sh.i1 || (sh.i0 == sh.i1 && sh.r0 >= sh.r1)) return;
 
     // lanes per row for so many rows: the fewest for which the rounds of the workgroup's wavefronts, each as long as a
     // row's pieces over its lanes plus the round's own start and end (about two more), are shortest
@@ -636,118 +862,121 @@ __global__ __launch_bounds__(kRowsThreads) void k_rows(const ProductArgs a, cons
         }
         return log2L;
     };
-    for (; i_base <= i1; i_base += kKeptSegments) {
-        // ---- the next items of the share: eight lanes for each, a token apiece
-        if (threadIdx.x < kKeptSegments * kMaxTokenTile) {
-            const int k = threadIdx.x / kMaxTokenTile, t = threadIdx.x % kMaxTokenTile, i = i_base + k;
-            int expert = -1, slot0 = 0, ntok = 0, tok = 0;
-            if (i <= i1) {
-                if constexpr (GROUP) {
-                    expert = (int)lists.items[2 * i];
-                    slot0 = (int)(lists.items[2 * i + 1] & 0xFFFFu);
-                    ntok = (int)(lists.items[2 * i + 1] >> 16);
-                } else if (a.shares) {  // (such a share is looked at in one go)
-                    const int *p = a.shares + blockIdx.x * kShareInts + 4 + 2 * k;
-                    expert = p[0];
-                    slot0 = p[1] & 0xFFFF;
-                    ntok = p[1] >> 16;
-                } else if (a.items) {
-                    const Item it = a.items[i];
-                    expert = it.expert;
-                    slot0 = it.slot0;
-                    ntok = it.ntok;
-                } else {
-                    expert = 0;
-                    slot0 = i * a.tb_max;
-                    ntok = a.batch - slot0;
-                }
-            }
-            ntok = min(ntok, a.tb_max);
-            const bool ok = expert >= 0 && expert < a.n_experts && ntok > 0;
-            if (ok) {
-                const int at = slot0 + min(t, ntok - 1);
-                if constexpr (GROUP) tok = lists.perm[at];
-                else tok = a.perm ? a.perm[at] : at;
-            }
-            RowsSegment &g = seg_s[k];
-            if (t == 0) {
-                g.expert = ok ? expert : 0;
-                g.slot0 = slot0;
-                g.ntok = ntok;
-                g.ra = i == share_s[0] ? share_s[1] : 0;
-                g.rb = !ok ? g.ra : (i == i1 ? share_s[3] : a.rows);
-            }
-            g.tok[t] = tok;
-        }
-        __syncthreads();
-        for (int k0 = 0; k0 < kKeptSegments && i_base + k0 <= i1; k0 += split.x_slots) {
-            // ---- a batch of one or two of them
-            lp_segment g0 = (lp_segment)(seg_s + k0), g1 = (lp_segment)(seg_s + min(k0 + 1, kKeptSegments - 1));
-            const bool two = split.x_slots > 1 && k0 + 1 < kKeptSegments && i_base + k0 + 1 <= i1;
-            const int ra0 = __builtin_amdgcn_readfirstlane(g0->ra), rb0 = __builtin_amdgcn_readfirstlane(g0->rb);
-            const int ra1 = __builtin_amdgcn_readfirstlane(g1->ra), rb1 = two ? __builtin_amdgcn_readfirstlane(g1->rb) : ra1;
-            const int log2L = lanes_log2((rb0 - ra0) + (rb1 - ra1)), R = 64 >> log2L;
-            const int groups0 = (rb0 - ra0 + R - 1) >> (6 - log2L);
-            // the wavefront's first group of rows (in segment head_k): its offsets are asked for first
-            const int head_k = wave < groups0 ? 0 : 1;
-            const int head_rb = head_k ? rb1 : rb0, head_r = head_k ? ra1 + (wave - groups0) * R : ra0 + wave * R;
-            const bool have = head_r < head_rb;
-            GroupHead head{};
-            if (have) {
-                const int expert = __builtin_amdgcn_readfirstlane(head_k ? g1->expert : g0->expert);
-                const qmoe_matrix M = a.mats ? a.mats[expert] : a.single;
-                head_offsets<ASYM, LANES>(split, M, head_rb, head_r + (lane >> log2L), head);
-            }
-            if (k0 || i_base != __builtin_amdgcn_readfirstlane(share_s[0]) || GROUP) lds_barrier();  // the tiles before (the lists) are done with
+    RowsBatchItem b[2];
+    int log2L = 0, groups0 = 0, head_k = 0;
+    bool have = false;  // the wavefront has rows in the batch: its first group (of item head_k), begun in `head`
+    GroupHead head{};
+    // ---- a batch of one or two items: activations and the wavefront's first rows asked for, in this order; `meanwhile` runs
+    // ahead of what has to wait for the row offsets
+    auto stage = [&](lp_segment g0, lp_segment g1, auto meanwhile) {
+        auto row_of = [&](int k, int t) { return a.x_by_slot ? b[k].slot0 + t : __builtin_amdgcn_readfirstlane((k ? g1 : g0)->tok[t]); };
+        log2L = lanes_log2((b[0].rb - b[0].ra) + (b[1].rb - b[1].ra));
+        const int R = 64 >> log2L;
+        groups0 = (b[0].rb - b[0].ra + R - 1) >> (6 - log2L);
+        head_k = wave < groups0 ? 0 : 1;
+        const int head_rb = head_k ? b[1].rb : b[0].rb, head_r = head_k ? b[1].ra + (wave - groups0) * R : b[0].ra + wave * R;
+        have = head_r < head_rb;
+        XPairs<> px[2];
 #pragma unroll
-            for (int k = 0; k < 2; k++) {
-                if (k ? ra1 >= rb1 : ra0 >= rb0) continue;
-                lp_segment g = k ? g1 : g0;
-                unsigned char *xs = xs0 + (k ? xs_bytes : 0);
-                const int ntok = __builtin_amdgcn_readfirstlane(g->ntok), slot0 = __builtin_amdgcn_readfirstlane(g->slot0);
-                auto row_of = [&](int t) { return a.x_by_slot ? slot0 + t : __builtin_amdgcn_readfirstlane(g->tok[t]); };
-                if (ntok <= 4) {
-                    for (int base = 0; 2 * base < a.cols + kRowsPadCols; base += XPairs::kPieces * kRowsThreads) {
-                        XPairs px;
-                        x_load(px, a.x, row_of, ntok, a.ldx, a.cols, base);
-                        x_store(px, xs, ntok, a.cols, base);
-                    }
-                } else {
-                    stage_x_tile<8, kRowsPadCols>(reinterpret_cast<uint16_t *>(xs), a.x, row_of, ntok, a.ldx, a.cols);
-                }
-            }
-            if (have) {
-                const int expert = __builtin_amdgcn_readfirstlane(head_k ? g1->expert : g0->expert);
-                const qmoe_matrix M = a.mats ? a.mats[expert] : a.single;
-                head.v = RowPieces<LANES>(M, head, head_r + (lane >> log2L) < head_rb).load(lane & ((1 << log2L) - 1));
-            }
-            if (EPI == 0 && threadIdx.x < 2 * kMaxTokenTile) {
-                const int tok = threadIdx.x < kMaxTokenTile ? g0->tok[threadIdx.x] : g1->tok[threadIdx.x - kMaxTokenTile];
-                gate_s[threadIdx.x] = a.gate ? a.gate[tok] : 1.0f;
-            }
-            lds_barrier();
-            int group = wave;  // the wavefront's first group of rows of the segment
-            for (int k = 0; k < 2; k++) {
-                const int ra = k ? ra1 : ra0, rb = k ? rb1 : rb0;
-                if (ra >= rb) continue;
-                lp_segment g = k ? g1 : g0;
-                const int expert = __builtin_amdgcn_readfirstlane(g->expert);
-                const qmoe_matrix M = a.mats ? a.mats[expert] : a.single;
-                const bool first = have && k == head_k;
-                RowsTile tile;
-                tile.ntok = __builtin_amdgcn_readfirstlane(g->ntok);
-                tile.slot0 = __builtin_amdgcn_readfirstlane(g->slot0);
-                tile.tok_ids = g->tok;
-                tile.gate_s = (const __attribute__((address_space(3))) float *)(gate_s + k * kMaxTokenTile);
-                const uint32_t xs_addr = (uint32_t)(uintptr_t)(lp_u16)(uint16_t *)(xs0 + (k ? xs_bytes : 0));
-                if (tile.ntok <= 1) rows_block<1, EPI, ASYM, LANES>(a, split, M, ra, rb, group, log2L, xs_addr, tile, (lp_u32)table_w, head, first);
-                else if (tile.ntok <= 2) rows_block<2, EPI, ASYM, LANES>(a, split, M, ra, rb, group, log2L, xs_addr, tile, (lp_u32)table_w, head, first);
-                else if (tile.ntok <= 4) rows_block<4, EPI, ASYM, LANES>(a, split, M, ra, rb, group, log2L, xs_addr, tile, (lp_u32)table_w, head, first);
-                else rows_block<8, EPI, ASYM, LANES>(a, split, M, ra, rb, group, log2L, xs_addr, tile, (lp_u32)table_w, head, first);
-                group = (group - groups0) & (waves - 1);  // the second segment's groups go on where the first one's end
+        for (int k = 0; k < 2; k++)
+            if (b[k].ra < b[k].rb) x_load(px[k], a.x, [&](int t) { return row_of(k, t); }, b[k].ntok, a.ldx, a.cols, 0);
+        const int expert = head_k ? b[1].expert : b[0].expert;
+        if (have) {
+            const qmoe_matrix M = a.mats ? a.mats[expert] : a.single;
+            head_offsets<ASYM, LANES>(split, M, head_rb, head_r + (lane >> log2L), head);
+        }
+        meanwhile();
+        if (have) {
+            const qmoe_matrix M = a.mats ? a.mats[expert] : a.single;
+            head.v = RowPieces<LANES>(M, head, head_r + (lane >> log2L) < head_rb).load(lane & ((1 << log2L) - 1));
+        }
+#pragma unroll
+        for (int k = 0; k < 2; k++) {
+            if (b[k].ra >= b[k].rb) continue;
+            unsigned char *xs = xs0 + (k ? xs_bytes : 0);
+            x_store(px[k], xs, b[k].ntok, a.cols, 0);
+            for (int base = XPairs<>::kPieces * kRowsThreads; 2 * base < a.cols + kRowsPadCols; base += kRowsThreads) {  // wide tiles
+                XPairs<1> more;
+                x_load(more, a.x, [&](int t) { return row_of(k, t); }, b[k].ntok, a.ldx, a.cols, base);
+                x_store(more, xs, b[k].ntok, a.cols, base);
             }
         }
-        if (i_base + kKeptSegments <= i1) __syncthreads();  // the segments are done with
+        if (EPI == 0 && wave == 0 && lane < 2 * kMaxTokenTile) {
+            const int tok = lane < kMaxTokenTile ? g0->tok[lane] : g1->tok[lane - kMaxTokenTile];
+            gate_s[lane] = a.gate ? a.gate[tok] : 1.0f;
+        }
+    };
+    // (Another fill of the segments than the first only in large calls: small ones have few items a share.)
+    int i = sh.i0, i_base = sh.i0;
+    auto segment = [&](int k) { return (lp_segment)(seg_s + min(i - i_base + k, kKeptSegments - 1)); };
+    auto batch_of = [&]() {
+#pragma unroll
+        for (int k = 0; k < 2; k++) {
+            lp_segment g = segment(k);
+            b[k].expert = __builtin_amdgcn_readfirstlane(g->expert);
+            b[k].slot0 = __builtin_amdgcn_readfirstlane(g->slot0);
+            b[k].ntok = __builtin_amdgcn_readfirstlane(g->ntok);
+            b[k].ra = __builtin_amdgcn_readfirstlane(g->ra);
+            b[k].rb = __builtin_amdgcn_readfirstlane(g->rb);
+        }
+    };
+    auto one_or_two = [&]() {
+        if (split.x_slots < 2 || i + 1 > sh.i1) b[1].rb = b[1].ra;
+    };
+    if (recorded) {
+        // (not from LDS: wavefront 0 puts it there below)
+#pragma unroll
+        for (int k = 0; k < 2; k++) {
+            const int expert = __builtin_amdgcn_readlane(record, 4 + 2 * k), at = __builtin_amdgcn_readlane(record, 5 + 2 * k);
+            const int ntok = min(at >> 16, a.tb_max);
+            const bool ok = expert >= 0 && expert < a.n_experts && ntok > 0;
+            b[k].expert = ok ? expert : 0;
+            b[k].slot0 = at & 0xFFFF;
+            b[k].ntok = ntok;
+            b[k].ra = k ? 0 : sh.r0;
+            b[k].rb = !ok ? b[k].ra : (sh.i0 + k == sh.i1 ? sh.r1 : a.rows);
+        }
+    } else {
+        batch_of();
+    }
+    one_or_two();
+    stage(segment(0), segment(1), [&]() {
+        table_store(tp, table_w, a.n_order);
+        if (recorded && wave == 0) store_segments(seg_own, sh, sh.i0);
+    });
+    for (;;) {
+        lds_barrier();
+        int group = wave;  // the wavefront's first group of rows of the item
+        for (int k = 0; k < 2; k++) {
+            const RowsBatchItem &it = k ? b[1] : b[0];
+            if (it.ra >= it.rb) continue;
+            lp_segment g = segment(k);
+            const qmoe_matrix M = a.mats ? a.mats[it.expert] : a.single;
+            const bool first = have && k == head_k;
+            RowsTile tile;
+            tile.ntok = it.ntok;
+            tile.slot0 = it.slot0;
+            tile.tok_ids = g->tok;
+            tile.gate_s = (const __attribute__((address_space(3))) float *)(gate_s + k * kMaxTokenTile);
+            const uint32_t xs_addr = (uint32_t)(uintptr_t)(lp_u16)(uint16_t *)(xs0 + (k ? xs_bytes : 0));
+            if (tile.ntok <= 1) rows_block<1, EPI, ASYM, LANES>(a, split, M, it.ra, it.rb, group, log2L, xs_addr, tile, (lp_u32)table_w, head, first);
+            else if (tile.ntok <= 2) rows_block<2, EPI, ASYM, LANES>(a, split, M, it.ra, it.rb, group, log2L, xs_addr, tile, (lp_u32)table_w, head, first);
+            else rows_block<4, EPI, ASYM, LANES>(a, split, M, it.ra, it.rb, group, log2L, xs_addr, tile, (lp_u32)table_w, head, first);
+            group = (group - groups0) & (waves - 1);  // the second item's groups go on where the first one's end
+        }
+        i += split.x_slots;
+        if (i > sh.i1) break;
+        lds_barrier();  // the tiles (and the segments) before are done with
+        if constexpr (!GROUP) {
+            if (i - i_base >= kKeptSegments) {
+                i_base += kKeptSegments;
+                if (wave == 0) store_segments(load_segments(sh, i_base), sh, i_base);
+                lds_barrier();
+            }
+        }
+        batch_of();
+        one_or_two();
+        stage(segment(0), segment(1), []() {});
     }
 }
 
@@ -755,7 +984,7 @@ size_t rows_fixed_bytes(int n_order) { return (((size_t)n_order * 4 + 15) & ~(si
 size_t rows_tile_bytes(int cols, int tb) { return (size_t)(cols + kRowsPadCols) * 2 * (size_t)std::max(tb, 4); }
 size_t inline_lds_bytes(int E, int T)
 {
-    return 4 * ((size_t)E * ((T + 31) / 32) + (size_t)E + 3 * (size_t)T + 64);
+    return 4 * std::max((size_t)E * ((T + 31) / 32) + (size_t)E + 3 * (size_t)T + 64, 4 * (size_t)T + 8);
 }
 
 }  // namespace
@@ -792,6 +1021,7 @@ RowsSplit rows_split(int rows, int lanes, int x_slots, int grid)
 qmoe_status launch_rows(const ProductArgs &a, int x_slots, const DispatchArgs *da, int rows2, int x_slots2, int grid, int max_lds,
                         hipStream_t s)
 {
+    if (a.tb_max > kRowsTokenTile) return QMOE_E_LIMIT;
     size_t tiles = rows_tile_bytes(a.cols, a.tb_max) * (size_t)x_slots;
     if (da) tiles = std::max(tiles, inline_lds_bytes(da->n_experts, da->n_tokens));
     const size_t smem = rows_fixed_bytes(a.n_order) + tiles;

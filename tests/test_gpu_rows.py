@@ -140,3 +140,36 @@ def test_lane_interleaved_layers(gpu, ddict, oracle_dict, monkeypatch, E, d_mode
     valid = [t for t in range(T) if 0 <= idx[t] < E]
     _check_layer(w, idx, x, y, wsout, valid if len(valid) < 60 else valid[:30] + valid[-30:], gate, asym=minmax)
     assert not y[[t for t in range(T) if not 0 <= idx[t] < E]].any()
+
+
+@pytest.mark.parametrize("E,T", [(1, 64), (2, 63), (3, 65), (2048, 64), (2047, 1), (5000, 33), (300, 300), (1100, 512), (33, 2)])
+@pytest.mark.parametrize("drop", [False, True])
+def test_tokens_grouped_in_the_first_product(gpu, ddict, oracle_dict, E, T, drop):
+    """Up to 64 tokens in one wavefront's registers, more by masks in LDS: the lists in the workspace are the ones the
+    dispatch kernel writes, and the second product finds its shares."""
+    w = synth.WORKLOADS["switch_base128"].scaled(n_experts=E, d_model=48, d_ff=80, n_tokens=T)
+    x, rng = w.tokens(), np.random.default_rng(E + T)
+    idx = np.minimum(rng.pareto(0.7, T).astype(np.int64), E - 1).astype(np.int32)
+    idx[-(T // 3):] = E - 1
+    if drop:
+        idx[rng.integers(0, T, 1 + T // 4)] = np.int32(-1 if T % 2 else E)
+    layer = dev.DeviceLayer(E, 48, 80, gpu)
+    used = sorted({int(e) for e in idx if 0 <= e < E})
+    for e in used:
+        for which, tern, scale in (("wi", w.wi_ternary(e), w.wi_scale(e)), ("wo", w.wo_ternary(e), w.wo_scale(e))):
+            layer.set_expert(e, which, *q.qmoe_encode_host(ddict.handle, tern), scale)
+    layer.finalize(device_order_of=ddict)
+    print(f"{E} experts, {T} tokens", flush=True)
+    y, got = _run_layer(layer, ddict, x, idx, gpu)
+    tok_off, perm = oracle.dispatch(idx, E)
+    n = int(tok_off[-1])
+    assert np.array_equal(got["tok_off"], tok_off) and np.array_equal(got["perm"][:n], perm)
+    counts = np.diff(tok_off)
+    assert list(got["counters"][:3]) == [n, T - n, int((counts > 0).sum())]
+    tiles = [(e, int(tok_off[e]) + i, min(4, int(counts[e]) - i)) for e in used for i in range(0, int(counts[e]), 4)]
+    expect = [t for k in ((3, 4), (2,), (1,)) for t in tiles if t[2] in k]
+    for items, k in (("items_wi", 3), ("items_wo", 4)):
+        assert got["counters"][k] == len(expect) and [tuple(r[:3]) for r in got[items][:len(expect)].tolist()] == expect
+    assert list(got["counters"][10:14]) == [0] + [sum(t[2] in k for t in tiles) for k in ((3, 4), (2,), (1,))]
+    _check_layer(w, idx, x, y, got, [t for t in range(T) if 0 <= idx[t] < E][:24])
+    assert not y[[t for t in range(T) if not 0 <= idx[t] < E]].any()
