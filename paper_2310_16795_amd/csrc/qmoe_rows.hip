@@ -34,11 +34,34 @@ __device__ __forceinline__ void lds_barrier()
 typedef u32x4 u32x4_any __attribute__((aligned(2)));
 using gp_u32x4_any = const __attribute__((address_space(1))) u32x4_any *;
 
+// The descriptor of an expert's matrix, in scalar registers (nothing writes it during the launch; `expert` the same in every
+// lane): as a vector load it was waited for together with the table and the activations.
+__device__ __forceinline__ qmoe_matrix matrix_of(const ProductArgs &a, int expert)
+{
+    typedef const __attribute__((address_space(4))) qmoe_matrix *cp_matrix;
+    if (!a.mats) return a.single;
+    qmoe_matrix m;
+    cp_matrix p = (cp_matrix)(uintptr_t)(a.mats + expert);
+    m.codes = p->codes;
+    m.row_off = p->row_off;
+    m.scale_f16 = p->scale_f16;
+    m.rows = p->rows;
+    m.cols = p->cols;
+    m.n_codes = p->n_codes;
+    m.code_order = p->code_order;
+    m.minmax_bf16 = p->minmax_bf16;
+    m.wave_off = p->wave_off;
+    m.lanes = p->lanes;
+    m.reserved = 0u;
+    return m;
+}
+
 // How the rows of a launch are cut into shares: made by the host.
 struct RowsSplit {
     int rows, x_slots;   // rows of a matrix; token tiles whose activations fit the LDS at once (1 or 2)
     double inv_item[4];  // 1 / (cost of a whole item of class k)
     double inv_grid;
+    uint32_t round_cost[7];  // of a round of the wavefronts with 2^l lanes per row: the pieces of a row over its lanes, and about two more
     // lane-interleaved layout: 1 / lanes, and the even split of the rows over the lanes (`lane_extra` lanes own a row more)
     float inv_lanes;
     int lanes, lane_rows, lane_extra;
@@ -250,9 +273,9 @@ __device__ __forceinline__ void rows_block(const ProductArgs &a, const RowsSplit
     }
 }
 
-// What a row of a tile costs by the tile's class (more than four tokens, three or four, two, one): nanoseconds per row
-// of 1024 columns and workgroup, measured 17.3, 12.5 and 9.8 for the last three.
-constexpr int kRowCost[4] = {56, 31, 22, 17};
+// What a row of a tile costs by the tile's class (none, as tiles have at most four tokens; three or four, two, one): nanoseconds
+// per row of 1024 columns and workgroup, measured 17.3, 12.5 and 9.8.
+constexpr int kRowCost[4] = {0, 31, 22, 17};
 
 // A workgroup's share of a launch: from row r0 of item i0 to row r1 of item i1.
 struct RowsShare {
@@ -264,37 +287,39 @@ struct RowsShare {
 // ends there and the one that begins there, so rounding moves a boundary by a few rows at most and loses none.)
 __device__ __forceinline__ RowsShare rows_share(const int (&cls)[4], const RowsSplit &sp, int n, int b)
 {
-    const int n_items = cls[0] + cls[1] + cls[2] + cls[3], rows = sp.rows, eights = (rows + 7) >> 3;
+    const int n_items = cls[1] + cls[2] + cls[3], rows = sp.rows, eights = (rows + 7) >> 3;
     RowsShare s{0, 0, -1, 0};
     if (n_items < 1) return s;
     double total = 0.0;  // in costs of eight rows
 #pragma unroll
-    for (int k = 0; k < 4; k++) total += (double)cls[k] * (double)(kRowCost[k] * eights);
+    for (int k = 1; k < 4; k++) total += (double)cls[k] * (double)(kRowCost[k] * eights);
     // With fewer items than workgroups every workgroup can have a part of one item: a tile of class k is cut into
     // ceil(cost[k] / t) parts, t the smallest cost of a part for which the parts of all items fit the grid.
     int g = 0, parts[4] = {0, 0, 0, 0}, used = 0, top_cost = 1;
     if (n_items <= n) {
         int top = 1;  // how many there are of the costliest class present
 #pragma unroll
-        for (int k = 3; k >= 0; k--) {
+        for (int k = 3; k >= 1; k--) {
             top_cost = cls[k] ? kRowCost[k] : top_cost;
             top = cls[k] ? cls[k] : top;
         }
-        const float inv_cost = 1.0f / (float)top_cost;
+        // (reciprocals to the last bit but one: every workgroup has the same ones, and whole quotients are rounded up first)
+        const float inv_cost = __builtin_amdgcn_rcpf((float)top_cost);
         auto parts_of = [&](int k, int g_) { return (int)ceilf((float)(kRowCost[k] * g_) * inv_cost - 1e-3f); };
         // (An even split of the cost would give it this many; rounding up needs fewer, rarely by more than a few.  A lane tries
         // each: the first that fits.)
-        const int most = min((int)((float)n / (float)top), (int)((float)(top_cost * eights) * (float)n / (float)total) + 1);
+        const int most = min((int)((float)n * __builtin_amdgcn_rcpf((float)top) + 1e-3f),
+                             (int)((float)(top_cost * eights) * (float)n * __builtin_amdgcn_rcpf((float)total)) + 1);
         for (int from = most; from >= 1 && g == 0; from -= 64) {
             const int mine = from - (int)(threadIdx.x & 63u);
             int need = 0;
 #pragma unroll
-            for (int k = 0; k < 4; k++) need += parts_of(k, mine) * cls[k];
+            for (int k = 1; k < 4; k++) need += parts_of(k, mine) * cls[k];
             const unsigned long long fits = __ballot(mine >= 1 && need <= n);
             if (fits) g = from - __builtin_ctzll(fits);
         }
 #pragma unroll
-        for (int k = 0; k < 4; k++) {
+        for (int k = 1; k < 4; k++) {
             parts[k] = parts_of(k, g);
             used += parts[k] * cls[k];
         }
@@ -307,12 +332,12 @@ __device__ __forceinline__ RowsShare rows_share(const int (&cls)[4], const RowsS
         if (b >= used) return s;
         int item = 0, p = 1, at = -1, left = b;
 #pragma unroll
-        for (int k = 0; k < 4; k++) {
+        for (int k = 1; k < 4; k++) {
             const int here = cls[k] * parts[k];
             if (at < 0) {
                 if (left < here) {
                     p = parts[k];
-                    const int whole = (int)(((float)left + 0.5f) / (float)p);
+                    const int whole = (int)(((float)left + 0.5f) * __builtin_amdgcn_rcpf((float)p));
                     item += whole;
                     at = left - whole * p;
                 } else {
@@ -321,7 +346,7 @@ __device__ __forceinline__ RowsShare rows_share(const int (&cls)[4], const RowsS
                 }
             }
         }
-        const float step = (float)eights / (float)p;
+        const float step = (float)eights * __builtin_amdgcn_rcpf((float)p);
         s.i0 = s.i1 = item;
         s.r0 = 8 * (int)((float)at * step);
         s.r1 = at + 1 == p ? rows : 8 * (int)((float)(at + 1) * step);
@@ -332,7 +357,7 @@ __device__ __forceinline__ RowsShare rows_share(const int (&cls)[4], const RowsS
         int item = 0, row = 0;
         bool found = false;
 #pragma unroll
-        for (int k = 0; k < 4; k++) {
+        for (int k = 1; k < 4; k++) {
             const double per = (double)(kRowCost[k] * eights), here = (double)cls[k] * per;
             if (!found) {
                 if (c < here) {
@@ -458,11 +483,19 @@ __device__ __forceinline__ void group_many(const DispatchArgs &d, int e, uint32_
     if (e >= 0) atomicOr(&mask[e * mw + (tid >> 5)], 1u << (tid & 31));
     lds_barrier();
     const int chunk = (E + kRowsThreads - 1) / kRowsThreads, e0 = min(E, tid * chunk), e1 = min(E, e0 + chunk);
-    auto count = [&](int x) {
+    // bits of words [0, to) of an expert's mask: four reads in flight
+    auto bits = [&](int x, int to) {
         int n = 0;
-        for (int w = 0; w < mw; w++) n += __popc(mask[x * mw + w]);
+        for (int w = 0; w < to; w += 4) {
+            uint32_t v[4];
+#pragma unroll
+            for (int k = 0; k < 4; k++) v[k] = mask[x * mw + min(w + k, mw - 1)];
+#pragma unroll
+            for (int k = 0; k < 4; k++) n += w + k < to ? __popc(v[k]) : 0;
+        }
         return n;
     };
+    auto count = [&](int x) { return bits(x, mw); };
     const int kw = tile_class(d.tb_wi), log2_tb = __builtin_ctz(d.tb_wi);
     int sums[3] = {0, 0, 0};  // two 16-bit counts each: tokens | class 0, class 1 | class 2, class 3 | experts with tokens
     int n_first = 0;
@@ -525,8 +558,7 @@ __device__ __forceinline__ void group_many(const DispatchArgs &d, int e, uint32_
     if (tid == 5) totals[5] = all[2] >> 16;
     lds_barrier();
     if (e >= 0) {
-        int rank = 0;
-        for (int w = 0; w < (tid >> 5); w++) rank += __popc(mask[e * mw + w]);
+        int rank = bits(e, tid >> 5);
         rank += __popc(mask[e * mw + (tid >> 5)] & ((1u << (tid & 31)) - 1u));
         perm[off[e] + rank] = tid;
     }
@@ -609,52 +641,58 @@ struct XPairs {
 typedef uint32_t u32_any __attribute__((aligned(2)));
 using gp_u32_any = const __attribute__((address_space(1))) u32_any *;
 
-template <int PIECES, typename RowOf>
-__device__ __forceinline__ void x_load(XPairs<PIECES> &p, const uint16_t *x, RowOf row_of, int ntok, int ldx, int cols, int base)
+template <int PIECES>
+__device__ __forceinline__ void x_load(XPairs<PIECES> &p, const uint16_t *x, const int (&row)[4], int ntok, int ldx, int cols, int base)
 {
     uintptr_t src[4];
 #pragma unroll
-    for (int t = 0; t < 4; t++) src[t] = reinterpret_cast<uintptr_t>(x) + 2 * (size_t)row_of(min(t, ntok - 1)) * (size_t)ldx;
+    for (int t = 0; t < 4; t++) src[t] = reinterpret_cast<uintptr_t>(x) + 2u * ((uintptr_t)(uint32_t)row[t] * (uint32_t)ldx);
 #pragma unroll
     for (int k = 0; k < PIECES; k++) {
         const int c = 2 * (base + k * kRowsThreads + (int)threadIdx.x);
-        const uintptr_t at = 2 * (uintptr_t)min(c, cols - 2);
+        const uintptr_t at = 2 * (uintptr_t)(uint32_t)min(c, cols - 2);
         if (2 * (base + k * kRowsThreads) < cols) {  // (uniform)
             p.v[k][0] = *(gp_u32_any)(src[0] + at);
-            if (ntok > 1) {
-#pragma unroll
-                for (int t = 1; t < 4; t++) p.v[k][t] = *(gp_u32_any)(src[t] + at);
+            if (ntok > 1) p.v[k][1] = *(gp_u32_any)(src[1] + at);
+            if (ntok > 2) {
+                p.v[k][2] = *(gp_u32_any)(src[2] + at);
+                p.v[k][3] = *(gp_u32_any)(src[3] + at);
             }
         }
     }
 }
 
+// One token: records {0, +x, 0, -x}; more: four tokens a column (a tile of two is read as two, and what stands behind the last
+// token of three is its neighbour's: sums that nobody writes).
 template <int PIECES>
 __device__ __forceinline__ void x_store(const XPairs<PIECES> &p, unsigned char *xs, int ntok, int cols, int base)
 {
-    const int n = cols + kRowsPadCols;
 #pragma unroll
     for (int k = 0; k < PIECES; k++) {
+        if (2 * (base + k * kRowsThreads) >= cols) break;  // (uniform)
         const int c = 2 * (base + k * kRowsThreads + (int)threadIdx.x);
-        if (c < n) {
-            const bool in = c < cols;
-            u32x4 o{0u, 0u, 0u, 0u};
-            if (ntok <= 1) {  // records {0, +x, 0, -x}
-                const uint32_t v = in ? p.v[k][0] : 0u, flip = in ? 0x80000000u : 0u;
-                o.x = v << 16;
-                o.y = (v << 16) ^ flip;
-                o.z = v & 0xFFFF0000u;
-                o.w = (v & 0xFFFF0000u) ^ flip;
-            } else if (in) {  // four tokens a column; those that are not there are zeros
-                const uint32_t v1 = p.v[k][1], v2 = ntok > 2 ? p.v[k][2] : 0u, v3 = ntok > 3 ? p.v[k][3] : 0u;
-                o.x = __builtin_amdgcn_perm(v1, p.v[k][0], 0x05040100u);
-                o.y = __builtin_amdgcn_perm(v3, v2, 0x05040100u);
-                o.z = __builtin_amdgcn_perm(v1, p.v[k][0], 0x07060302u);
-                o.w = __builtin_amdgcn_perm(v3, v2, 0x07060302u);
-            }
-            *reinterpret_cast<u32x4 *>(xs + 8 * (size_t)c) = o;
+        u32x4 o;
+        if (ntok <= 1) {
+            const uint32_t v = p.v[k][0];
+            o.x = v << 16;
+            o.y = o.x ^ 0x80000000u;
+            o.z = v & 0xFFFF0000u;
+            o.w = o.z ^ 0x80000000u;
+        } else {
+            o.x = __builtin_amdgcn_perm(p.v[k][1], p.v[k][0], 0x05040100u);
+            o.y = __builtin_amdgcn_perm(p.v[k][3], p.v[k][2], 0x05040100u);
+            o.z = __builtin_amdgcn_perm(p.v[k][1], p.v[k][0], 0x07060302u);
+            o.w = __builtin_amdgcn_perm(p.v[k][3], p.v[k][2], 0x07060302u);
         }
+        if (c < cols) *reinterpret_cast<u32x4 *>(xs + 8 * (size_t)c) = o;
     }
+}
+
+// zeros behind a tile's last column
+__device__ __forceinline__ void x_pad(unsigned char *xs, int cols)
+{
+    static_assert(kRowsPadCols % 2 == 0 && kRowsPadCols / 2 <= kRowsThreads, "a pair a thread");
+    if ((int)threadIdx.x < kRowsPadCols / 2) *reinterpret_cast<u32x4 *>(xs + 8 * (size_t)(cols + 2 * (int)threadIdx.x)) = u32x4{0u, 0u, 0u, 0u};
 }
 
 // LDS of the shares, segments and gates
@@ -695,8 +733,11 @@ struct RowsBatchItem {
 // Small calls are bound by the way to the first codeword: share -> descriptor -> row offsets -> codewords, each a trip to
 // memory, with the table, the activations and the grouping beside them.  So the table is asked for first and stored last, a
 // second product's record is read by every wavefront itself, what wavefront 0 works out goes round with one barrier, and no
-// barrier waits for a load or a store of global memory (__syncthreads does).  One token on 2048 experts of 2080 x 6144: 21.5 -> 18.4 us;
-// 128 on 128 of 768 x 3072: 45.6 -> 42.7; 512 on 128 of 1024 x 4096: 119.8 -> 116.8.
+// barrier waits for a load or a store of global memory (__syncthreads does).  One token on 2048 experts of 2080 x 6144: 21.5 -> 17.3 us;
+// 128 on 128 of 768 x 3072: 45.6 -> 41.7; 512 on 128 of 1024 x 4096: 119.5 -> 114.8.
+// (Tried and slower: eight wavefronts, 45.3 us for the second; the table straight into LDS with one copy of the staging code, for which
+// registers spill, 47.9; what follows the grouping in one copy more of the code: the two kernels of a call do not fit the 64 KB of
+// the instruction cache together then.)
 template <int EPI, int ASYM, bool GROUP, int LANES>
 __global__ __launch_bounds__(kRowsThreads) void k_rows(const ProductArgs a, const DispatchArgs d, const RowsSplit split, const RowsSplit split2)
 {
@@ -710,7 +751,7 @@ __global__ __launch_bounds__(kRowsThreads) void k_rows(const ProductArgs a, cons
     float *gate_s = reinterpret_cast<float *>(seg_s + kKeptSegments);                 // [2][kMaxTokenTile]
     unsigned char *xs0 = smem + table_bytes + kRowsSmallBytes;
     const size_t xs_bytes = (size_t)(a.cols + kRowsPadCols) * max(a.tb_max, 4) * sizeof(uint16_t);
-    const int wave = (int)threadIdx.x >> 6, lane = (int)threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = (int)threadIdx.x & 63;
     constexpr int waves = kRowsThreads / 64;
 
     // A large call whose experts all have many tokens: nothing to do, and the matrix-core kernel waits for the compute units.  Seen
@@ -816,8 +857,8 @@ __global__ __launch_bounds__(kRowsThreads) void k_rows(const ProductArgs a, cons
                     for (int k = 0; k < 4; k++) cls[k] = a.class_counts[k];
                 } else {
                     const int n = (a.batch + a.tb_max - 1) / a.tb_max;
-                    cls[0] = a.tb_max > 4 ? n : 0;
-                    cls[1] = a.tb_max > 2 && a.tb_max <= 4 ? n : 0;
+                    cls[0] = 0;
+                    cls[1] = a.tb_max > 2 ? n : 0;
                     cls[2] = a.tb_max == 2 ? n : 0;
                     cls[3] = a.tb_max == 1 ? n : 0;
                 }
@@ -849,16 +890,14 @@ __global__ __launch_bounds__(kRowsThreads) void k_rows(const ProductArgs a, cons
 
     // lanes per row for so many rows: the fewest for which the rounds of the workgroup's wavefronts, each as long as a
     // row's pieces over its lanes plus the round's own start and end (about two more), are shortest
-    auto lanes_log2 = [&](int rows_here) -> int {
-        const int pieces = a.cols / 176 + 1;
-        int best = 0x7FFFFFFF, log2L = 0;
+    auto lanes_log2 = [&](uint32_t rows_here) -> int {
+        uint32_t best = 0xFFFFFFFFu;
+        int log2L = 0;
+#pragma unroll
         for (int l = 0; l <= 6; l++) {
-            const int rounds = ((rows_here << l) + kRowsThreads - 1) / kRowsThreads;
-            const int cost = rounds * (((pieces + (1 << l) - 1) >> l) + 2 + (l > 0));
-            if (cost < best) {
-                best = cost;
-                log2L = l;
-            }
+            const uint32_t cost = (((rows_here << l) + (uint32_t)kRowsThreads - 1u) / (uint32_t)kRowsThreads) * split.round_cost[l];
+            log2L = cost < best ? l : log2L;
+            best = min(best, cost);
         }
         return log2L;
     };
@@ -867,10 +906,26 @@ __global__ __launch_bounds__(kRowsThreads) void k_rows(const ProductArgs a, cons
     bool have = false;  // the wavefront has rows in the batch: its first group (of item head_k), begun in `head`
     GroupHead head{};
     // ---- a batch of one or two items: activations and the wavefront's first rows asked for, in this order; `meanwhile` runs
-    // ahead of what has to wait for the row offsets
+    // ahead of what has to wait for the row offsets (and says which token a lane of wavefront 0 holds, -1: ask the segments)
     auto stage = [&](lp_segment g0, lp_segment g1, auto meanwhile) {
-        auto row_of = [&](int k, int t) { return a.x_by_slot ? b[k].slot0 + t : __builtin_amdgcn_readfirstlane((k ? g1 : g0)->tok[t]); };
-        log2L = lanes_log2((b[0].rb - b[0].ra) + (b[1].rb - b[1].ra));
+        // the input rows of the tiles (of tokens past a tile's last: the last's again)
+        int xrow[2][4];
+#pragma unroll
+        for (int k = 0; k < 2; k++) {
+            if (b[k].ra >= b[k].rb) continue;
+            if (a.x_by_slot) {
+#pragma unroll
+                for (int t = 0; t < 4; t++) xrow[k][t] = b[k].slot0 + min(t, b[k].ntok - 1);
+            } else {
+                lp_segment g = k ? g1 : g0;
+                int tok[4];
+#pragma unroll
+                for (int t = 0; t < 4; t++) tok[t] = g->tok[t];
+#pragma unroll
+                for (int t = 0; t < 4; t++) xrow[k][t] = __builtin_amdgcn_readfirstlane(tok[t]);
+            }
+        }
+        log2L = lanes_log2((uint32_t)((b[0].rb - b[0].ra) + (b[1].rb - b[1].ra)));
         const int R = 64 >> log2L;
         groups0 = (b[0].rb - b[0].ra + R - 1) >> (6 - log2L);
         head_k = wave < groups0 ? 0 : 1;
@@ -879,15 +934,19 @@ __global__ __launch_bounds__(kRowsThreads) void k_rows(const ProductArgs a, cons
         XPairs<> px[2];
 #pragma unroll
         for (int k = 0; k < 2; k++)
-            if (b[k].ra < b[k].rb) x_load(px[k], a.x, [&](int t) { return row_of(k, t); }, b[k].ntok, a.ldx, a.cols, 0);
+            if (b[k].ra < b[k].rb) x_load(px[k], a.x, xrow[k], b[k].ntok, a.ldx, a.cols, 0);
         const int expert = head_k ? b[1].expert : b[0].expert;
         if (have) {
-            const qmoe_matrix M = a.mats ? a.mats[expert] : a.single;
+            const qmoe_matrix M = matrix_of(a, expert);
             head_offsets<ASYM, LANES>(split, M, head_rb, head_r + (lane >> log2L), head);
         }
-        meanwhile();
+        // (wavefront 0: the gates of the tiles' tokens)
+        const bool gates = EPI == 0 && wave == 0 && lane < 2 * kMaxTokenTile;
+        const int own = meanwhile();
+        float gate = 1.0f;
+        if (gates && a.gate) gate = a.gate[own >= 0 ? own : (lane < kMaxTokenTile ? g0 : g1)->tok[lane % kMaxTokenTile]];
         if (have) {
-            const qmoe_matrix M = a.mats ? a.mats[expert] : a.single;
+            const qmoe_matrix M = matrix_of(a, expert);
             head.v = RowPieces<LANES>(M, head, head_r + (lane >> log2L) < head_rb).load(lane & ((1 << log2L) - 1));
         }
 #pragma unroll
@@ -895,16 +954,14 @@ __global__ __launch_bounds__(kRowsThreads) void k_rows(const ProductArgs a, cons
             if (b[k].ra >= b[k].rb) continue;
             unsigned char *xs = xs0 + (k ? xs_bytes : 0);
             x_store(px[k], xs, b[k].ntok, a.cols, 0);
-            for (int base = XPairs<>::kPieces * kRowsThreads; 2 * base < a.cols + kRowsPadCols; base += kRowsThreads) {  // wide tiles
+            x_pad(xs, a.cols);
+            for (int base = XPairs<>::kPieces * kRowsThreads; 2 * base < a.cols; base += kRowsThreads) {  // wide tiles
                 XPairs<1> more;
-                x_load(more, a.x, [&](int t) { return row_of(k, t); }, b[k].ntok, a.ldx, a.cols, base);
+                x_load(more, a.x, xrow[k], b[k].ntok, a.ldx, a.cols, base);
                 x_store(more, xs, b[k].ntok, a.cols, base);
             }
         }
-        if (EPI == 0 && wave == 0 && lane < 2 * kMaxTokenTile) {
-            const int tok = lane < kMaxTokenTile ? g0->tok[lane] : g1->tok[lane - kMaxTokenTile];
-            gate_s[lane] = a.gate ? a.gate[tok] : 1.0f;
-        }
+        if (gates) gate_s[lane] = gate;
     };
     // (Another fill of the segments than the first only in large calls: small ones have few items a share.)
     int i = sh.i0, i_base = sh.i0;
@@ -943,6 +1000,7 @@ __global__ __launch_bounds__(kRowsThreads) void k_rows(const ProductArgs a, cons
     stage(segment(0), segment(1), [&]() {
         table_store(tp, table_w, a.n_order);
         if (recorded && wave == 0) store_segments(seg_own, sh, sh.i0);
+        return recorded ? seg_own.tok : -1;
     });
     for (;;) {
         lds_barrier();
@@ -951,7 +1009,7 @@ __global__ __launch_bounds__(kRowsThreads) void k_rows(const ProductArgs a, cons
             const RowsBatchItem &it = k ? b[1] : b[0];
             if (it.ra >= it.rb) continue;
             lp_segment g = segment(k);
-            const qmoe_matrix M = a.mats ? a.mats[it.expert] : a.single;
+            const qmoe_matrix M = matrix_of(a, it.expert);
             const bool first = have && k == head_k;
             RowsTile tile;
             tile.ntok = it.ntok;
@@ -976,7 +1034,7 @@ __global__ __launch_bounds__(kRowsThreads) void k_rows(const ProductArgs a, cons
         }
         batch_of();
         one_or_two();
-        stage(segment(0), segment(1), []() {});
+        stage(segment(0), segment(1), []() { return -1; });
     }
 }
 
@@ -1004,13 +1062,15 @@ bool rows_can_dispatch(int n_experts, int n_tokens, int grid, int n_order, int m
            rows_fixed_bytes(n_order) + inline_lds_bytes(n_experts, n_tokens) <= (size_t)max_lds;
 }
 
-RowsSplit rows_split(int rows, int lanes, int x_slots, int grid)
+RowsSplit rows_split(int rows, int cols, int lanes, int x_slots, int grid)
 {
     RowsSplit sp;
     sp.rows = rows;
     sp.x_slots = x_slots;
-    for (int k = 0; k < 4; k++) sp.inv_item[k] = 1.0 / (double)(kRowCost[k] * ((rows + 7) / 8));
+    sp.inv_item[0] = 0.0;
+    for (int k = 1; k < 4; k++) sp.inv_item[k] = 1.0 / (double)(kRowCost[k] * ((rows + 7) / 8));
     sp.inv_grid = 1.0 / grid;
+    for (int l = 0; l <= 6; l++) sp.round_cost[l] = (uint32_t)(((cols / 176 + (1 << l)) >> l) + 2 + (l > 0));
     sp.lanes = lanes;
     sp.inv_lanes = lanes ? 1.0f / (float)lanes : 0.0f;
     sp.lane_rows = lanes ? rows / lanes : 0;
@@ -1030,9 +1090,9 @@ qmoe_status launch_rows(const ProductArgs &a, int x_slots, const DispatchArgs *d
     RowsSplit split2{};
     if (da) {
         d = *da;
-        split2 = rows_split(rows2, 0, x_slots2, grid);  // (its shares only)
+        split2 = rows_split(rows2, 0, 0, x_slots2, grid);  // (its shares only)
     }
-    const RowsSplit split = rows_split(a.rows, a.lanes, x_slots, grid);
+    const RowsSplit split = rows_split(a.rows, a.cols, a.lanes, x_slots, grid);
     auto launch = [&](auto kernel) -> qmoe_status {
         const qmoe_status st = allow_lds(kernel, smem);
         if (st != QMOE_OK) return st;
