@@ -167,7 +167,8 @@ qmoe_status qmoe_validate_host(const qmoe_dict *d, const uint16_t *codes /*host*
  * stream qmoe_encode_host produces.  Nothing is read back: status (device int32[2]) holds
  * 0 or the first error (BAD_SYMBOL, UNENCODABLE, BUFFER_TOO_SMALL) and a row it happened
  * in once the work on `stream` is done; with an error the contents of codes are
- * undefined.  Enqueues four kernels (the first clears status), no memset.
+ * undefined.  Until that work is done row_off and status hold what its kernels tell each other.  Enqueues three kernels (for
+ * each 2^31 values or so), four with a dictionary that has no run coder; no memset.
  * Errors at the call: INVALID_ARG, NO_DEVICE_DICT, LIMIT (the table's trie has more than
  * 131072 nodes), HIP.
  */

@@ -25,8 +25,12 @@ struct RunCoderArgs {
     // launch shape, set by launch_encode
     int lanes_log2;          // lanes per row
     int seg_pairs;           // pairs a lane parses (a multiple of 32)
+    int row0, row_end;       // rows of the launch: whole groups of 64 >> lanes_log2, but for the last
+    int groups, groups_per_wg, groups_extra;  // (the first groups_extra tickets stand for a group more)
     int bit_words, mask_words, row_lds;  // LDS of a row: (non-zero, sign) words, boundary words, bytes together
 };
+
+constexpr int kRcTicketBytes = 16;  // LDS behind the depth tables: the workgroup's ticket
 
 qmoe_status launch_encode(const RunCoderArgs &a, hipStream_t s);
 

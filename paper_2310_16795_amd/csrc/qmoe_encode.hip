@@ -1,6 +1,7 @@
 // The encoder on the device (Section 4.3.3 "Encoding"): longest-prefix coding of ternary rows, codeword
-// for codeword the stream of qmoe_encode_host.  Count codewords per row, turn the counts into row
-// offsets (one workgroup), write the codewords.
+// for codeword the stream of qmoe_encode_host.  With the run coder a row is parsed once: the wavefronts tell each other how
+// many codewords come before theirs.  By the trie: count codewords per row, turn the counts into row offsets (one
+// workgroup), write the codewords.
 #include "qmoe_encode.h"
 
 namespace qmoe {
@@ -111,13 +112,23 @@ __global__ __launch_bounds__(256) void k_encode(const EncodeArgs a)
 // sequential -- an entry's end is the next one's start -- but a parse that starts in the wrong place falls into
 // step with the right one after a few entries, so every lane parses a segment of the row from the
 // segment's first pair and marks where entries begin; then it starts again from where the lane before it
-// really ended and goes on until it meets a mark of its first parse.  (Where it meets none before the
-// segment's end, the next lane's start has moved and that lane goes again: after j rounds lane j is
-// right.)  Wavefronts share nothing but the depth tables; no barrier after those are staged.
+// ended and goes on until it meets a mark of its first parse.  The last few lanes of a wavefront that have met none after
+// that many steps are helped by all the others (91 us to the end of the slowest wavefront's parse without, 76 with).  Wavefronts share
+// the depth tables; no barrier after those are staged.
+//
+// Where a row's codewords go depends on all rows before it.  A wavefront's rows are a group; when it has parsed them it
+// publishes their number of codewords, looks at the groups before it -- 64 at a time, back to one that knows all before
+// itself -- and publishes the sum.  The words for that are the row offsets that end the groups, which a last kernel turns into
+// plain offsets.  A wavefront waits for lower groups only, and groups are given out by a ticket that a workgroup draws when
+// it runs, so whatever is waited for is in work on some compute unit and waits for nobody above it.
 //
 // Bound: the chain of an entry (about 900 cycles) times the entries a wavefront goes through, with the two or
-// three wavefronts per SIMD that the row strings leave room for.  16640 x 6144 values, 90 % zeros: 89 us to
-// count and 101 us to write, 2680 us each by the trie (a row per lane, a dependent read of L2 per pair).
+// three wavefronts per SIMD that the row strings leave room for.  16640 x 6144 values, 90 % zeros: 207 us
+// with every row parsed twice, to count and to write, 112 now (23 packed, 13 and 17 the two parses, up to 45 in the last
+// wavefront, 20 looked up, 9 copied out), 2680 us a pass by the trie (a row per lane, a dependent read of L2 per pair).
+
+constexpr int kRcAlone = 16;  // entries of the second parse that the lanes take on their own, at least
+constexpr int kRcHelp = 12;   // lanes of a wavefront that are helped, at most
 
 struct Bits {
     uint32_t nz, neg;  // 28 values from a pair on
@@ -203,7 +214,80 @@ __device__ __forceinline__ void pack16(const u32x4 &v, uint32_t &nz, uint32_t &n
     }
 }
 
-template <bool WRITE>
+// The number of codewords that a group's state says, and what it is the number of: all codewords up to the group's end, or
+// the group's own (0: not known yet).
+constexpr uint32_t kEncAll = 0x40000000u, kEncOwn = 0x80000000u, kEncCount = kEncAll - 1u;
+
+__device__ __forceinline__ uint32_t *group_state(const RunCoderArgs &a, int group)
+{
+    return a.e.row_off + min(a.row0 + (long long)(group + 1) * (64 >> a.lanes_log2), (long long)a.row_end);
+}
+
+__device__ __forceinline__ void publish(uint32_t *state, uint32_t v)
+{
+    if ((threadIdx.x & 63) == 0) __hip_atomic_store(state, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Codewords of the groups below `group` (by a whole wavefront): lane i looks at group - 1 - i.
+__device__ __forceinline__ uint32_t codewords_before(const RunCoderArgs &a, int group)
+{
+    const int lane = threadIdx.x & 63;
+    uint32_t sum = 0u;
+    for (int at = group - 1; at >= 0;) {
+        uint32_t v = kEncAll;
+        if (at - lane >= 0) v = __hip_atomic_load(group_state(a, at - lane), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const unsigned long long all = __ballot((v & kEncAll) != 0u), unknown = __ballot(v == 0u);
+        const int last = all ? __builtin_ctzll(all) : 63;
+        if (unknown & (~0ull >> (63 - last))) {
+            __builtin_amdgcn_s_sleep(2);
+            continue;
+        }
+        sum += (uint32_t)__builtin_amdgcn_readlane(wave_inclusive_scan(lane <= last ? (int)(v & kEncCount) : 0), 63);
+        if (all) break;
+        at -= 64;
+    }
+    return sum;
+}
+
+// status[0] the first error, status[1] (while the encoder runs) the tickets drawn, row_off[0] (until its end) the error's row + 1
+__device__ __forceinline__ void report_row(const EncodeArgs &e, int error, int row)
+{
+    if (atomicCAS(&e.row_off[0], 0u, (uint32_t)row + 1u) == 0u) e.status[0] = error;
+}
+
+// Clears what the chunk's groups publish in, the tickets and, ahead of the first chunk, the errors.
+__global__ void k_encode_begin(const RunCoderArgs a)
+{
+    const int g = blockIdx.x * blockDim.x + threadIdx.x;
+    if (g < a.groups) *group_state(a, g) = 0u;
+    if (g == 0) {
+        a.e.status[1] = 0;
+        if (a.row0 == 0) {
+            a.e.status[0] = 0;
+            a.e.row_off[0] = 0u;
+        }
+    }
+}
+
+// The groups' last offsets as plain offsets; behind the last chunk the error's row in its place.
+__global__ __launch_bounds__(1024) void k_encode_end(const RunCoderArgs a)
+{
+    const unsigned long long base = a.row0 ? a.e.row_off[a.row0] : 0u;
+    const int g = blockIdx.x * blockDim.x + threadIdx.x;
+    if (g >= a.groups) return;
+    uint32_t *state = group_state(a, g);
+    const unsigned long long at = base + (*state & kEncCount);
+    *state = (uint32_t)at;
+    if (g != a.groups - 1) return;
+    // (a chunk whose offsets do not fit ends with an error that stays, so what comes behind it does not matter)
+    if (a.e.status[0] == 0 && (at > a.e.codes_cap || at > 0xFFFFFFFFull)) a.e.status[0] = QMOE_E_BUFFER_TOO_SMALL;
+    if (a.row_end == a.e.rows) {
+        const uint32_t row = a.e.row_off[0];
+        a.e.status[1] = row ? (int)(row - 1u) : 0;
+        a.e.row_off[0] = 0u;
+    }
+}
+
 __global__ __launch_bounds__(1024) void k_encode_runs(const RunCoderArgs a)
 {
     typedef __attribute__((address_space(3))) uint32_t *lw_u32;
@@ -212,19 +296,24 @@ __global__ __launch_bounds__(1024) void k_encode_runs(const RunCoderArgs a)
     typedef const __attribute__((address_space(1))) u32x4_any *gp_u32x4_any;
     extern __shared__ __align__(16) unsigned char smem[];
     const EncodeArgs &e = a.e;
-    if (WRITE && e.status[0] != 0) return;
+    int *ticket_s = reinterpret_cast<int *>(smem + kRcDepthBytes);
+    if (threadIdx.x == 0) *ticket_s = atomicAdd(&e.status[1], 1);
+    const unsigned long long codes_base = a.row0 ? e.row_off[a.row0] : 0u;
     stage_words(reinterpret_cast<uint32_t *>(smem), a.depth, kRcDepthBytes / 4);
     __syncthreads();
     const uint32_t depth_lds = (uint32_t)(uintptr_t)(lw_u16)(uint16_t *)smem;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
     const int L = 1 << a.lanes_log2, R = 64 >> a.lanes_log2;  // lanes per row, rows per wavefront
     const int sub = lane & (L - 1), mine = lane >> a.lanes_log2;
-    const uint32_t rows_lds = depth_lds + (uint32_t)kRcDepthBytes + (uint32_t)(wave * R * a.row_lds);
+    const uint32_t rows_lds = depth_lds + (uint32_t)(kRcDepthBytes + kRcTicketBytes) + (uint32_t)(wave * R * a.row_lds);
     const int np = e.cols / 2;
     const int seg0 = sub * a.seg_pairs, seg1 = min(seg0 + a.seg_pairs, np);
 
-    for (int group = (int)blockIdx.x * waves + wave; (long long)group * R < e.rows; group += (int)gridDim.x * waves) {
-        const int row0 = group * R, row = row0 + mine;
+    // a workgroup's groups follow each other
+    const int ticket = __builtin_amdgcn_readfirstlane(*ticket_s), first_group = ticket * a.groups_per_wg + min(ticket, a.groups_extra);
+    const int end_group = first_group + a.groups_per_wg + (ticket < a.groups_extra ? 1 : 0);
+    for (int group = first_group + wave; group < end_group; group += waves) {
+        const int row0 = a.row0 + group * R, row = row0 + mine;
         uint32_t tail_wrong = 0u;
         auto put = [&](int r, int c, uint32_t nz, uint32_t neg) {
             lw_u16 w = (lw_u16)(uintptr_t)(rows_lds + (uint32_t)(r * a.row_lds) + 8u * (uint32_t)(c >> 5) + (uint32_t)((c >> 3) & 2));
@@ -234,7 +323,7 @@ __global__ __launch_bounds__(1024) void k_encode_runs(const RunCoderArgs a)
         // ---- the wavefront's rows as bit strings (zeros behind the last value), boundary marks cleared
         // (a row is cut into pieces of 1024 values; eight pieces are asked for at a time, also across rows)
         uint32_t bad = 0u;
-        const int pieces = (32 * a.bit_words + 1023) >> 10, n_rows = min(R, e.rows - row0);
+        const int pieces = (32 * a.bit_words + 1023) >> 10, n_rows = min(R, a.row_end - row0);
         for (int i0 = 0; i0 < n_rows * pieces; i0 += 8) {
             u32x4 v[8];
 #pragma unroll
@@ -250,7 +339,7 @@ __global__ __launch_bounds__(1024) void k_encode_runs(const RunCoderArgs a)
                 uint32_t nz, neg, wrong = 0u;
                 pack16(v[k], nz, neg, wrong);
                 if (r < n_rows && c < 32 * a.bit_words) put(r, c, nz, neg);
-                if (!WRITE && __any(wrong != 0u) && mine == r) bad = 1u;
+                if (__any(wrong != 0u) && mine == r) bad = 1u;
             }
         }
         if ((e.cols & 15) && lane < n_rows) {  // the values after a row's last whole sixteen
@@ -264,7 +353,7 @@ __global__ __launch_bounds__(1024) void k_encode_runs(const RunCoderArgs a)
             put(lane, c, nz, neg);
             tail_wrong = wrong;
         }
-        if (!WRITE && (__ballot(tail_wrong != 0u) >> mine & 1ull)) bad = 1u;
+        if (__ballot(tail_wrong != 0u) >> mine & 1ull) bad = 1u;
         for (int i = lane; i < n_rows * a.mask_words; i += 64) {
             const int r = i / a.mask_words;
             *(lw_u32)(uintptr_t)(rows_lds + (uint32_t)(r * a.row_lds) + 8u * (uint32_t)a.bit_words + 4u * (uint32_t)(i - r * a.mask_words)) = 0u;
@@ -272,7 +361,7 @@ __global__ __launch_bounds__(1024) void k_encode_runs(const RunCoderArgs a)
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
 
-        const bool live = row < e.rows && seg0 < np;
+        const bool live = row < a.row_end && seg0 < np;
         const uint32_t bits = rows_lds + (uint32_t)(mine * a.row_lds);
         lw_u32 marks = (lw_u32)(uintptr_t)(bits + 8u * (uint32_t)a.bit_words);
         bool odd = false;  // a position where no entry fits was met (perhaps only by a parse from the wrong place)
@@ -296,97 +385,244 @@ __global__ __launch_bounds__(1024) void k_encode_runs(const RunCoderArgs a)
             }
             marks[word] = set;
         }
-        // ---- again from where the lane before really ended, until the two parses meet
-        int start = seg0;
-        bool moved;
-        do {
-            const int before = __shfl_up(end, 1, 64);
-            const int from = sub == 0 ? 0 : before;
-            moved = false;
-            if (live && from != start) {
-                // (an entry reaches at most 13 pairs into the segment)
-                marks[seg0 >> 5] &= ~((1u << (from - seg0)) - 1u);
-                int t = from;
-                bool met = false;
-                while (t < seg1) {
-                    const int w = t >> 5, b = t & 31;
-                    uint32_t m = marks[w];
-                    if ((m >> b) & 1u) {
-                        met = true;
+        // ---- again from where the lane before ended, until the two parses meet
+        const int before_end = __shfl_up(end, 1, 64), from = sub == 0 ? 0 : before_end;
+        const bool again = live && from != seg0;
+        bool met = false;
+        int t = from;
+        auto step = [&]() {  // an entry of the second parse: its mark in the place of the first parse's up to its end
+            const int w = t >> 5, b = t & 31;
+            const uint32_t m = marks[w];
+            if ((m >> b) & 1u) {
+                met = true;
+                return;
+            }
+            int len = longest_run(depth_lds, a.depth0, row_window(bits, t), np - t);
+            odd |= len < 1;
+            len = max(len, 1);
+            const unsigned long long span = ((1ull << len) - 1ull) << b;
+            marks[w] = (m & ~(uint32_t)span) | (1u << b);
+            if ((uint32_t)(span >> 32) && 32 * (w + 1) < seg1) marks[w + 1] &= ~(uint32_t)(span >> 32);
+            t += len;
+        };
+        // (an entry reaches at most 13 pairs into the segment)
+        if (again) marks[seg0 >> 5] &= ~((1u << (from - seg0)) - 1u);
+        for (int k = 0;; k++) {
+            const bool on = again && !met && t < seg1, moved = again && !met && t >= seg1 && t != end;
+            const int n_on = __popcll(__ballot(on));
+            if (n_on == 0) break;
+            // Most lanes meet their first parse after a few entries, one of 64 after fifty: the last ones are better off with the
+            // whole wavefront's help.  (Sixteen steps at least: whoever is left is past the pairs that the lane before may
+            // reach into the segment.)
+            if (k >= kRcAlone && n_on <= 4 && __popcll(__ballot(on || moved)) <= kRcHelp) break;
+            if (on) step();
+        }
+        bool pending = again && !met && t != end;
+        if (__popcll(__ballot(pending)) > kRcHelp) {
+            // rows whose parses hardly ever meet (long runs of zeros): every lane whose start has moved goes again, until none has;
+            // after j rounds lane j is right
+            int start = seg0;
+            if (again) {
+                start = from;
+                if (!met) end = t;
+            }
+            bool moved;
+            do {
+                const int ahead = __shfl_up(end, 1, 64), now = sub == 0 ? 0 : ahead;
+                moved = false;
+                if (live && now != start) {
+                    marks[seg0 >> 5] &= ~((1u << (now - seg0)) - 1u);
+                    t = now;
+                    met = false;
+                    while (t < seg1 && !met) step();
+                    if (!met) {
+                        moved = t != end;
+                        end = t;
+                    }
+                    start = now;
+                }
+            } while (__any(moved));
+        } else if (__any(pending)) {
+            // A window of 64 pairs at a time: every lane finds the entry that would begin at its pair, and the wavefront goes through
+            // those that do, on into the next segments where it has to.  What is left to a lane begins at a mark.
+            if (pending && t >= seg1) atomicAnd((uint32_t *)(marks + (seg1 >> 5)), ~((1u << (t - seg1)) - 1u));
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            pending = pending && t < np && !((marks[min(t, np - 1) >> 5] >> (t & 31)) & 1u);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            if (pending) atomicOr((uint32_t *)(marks + (t >> 5)), 1u << (t & 31));
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            unsigned long long todo = __ballot(pending);
+            while (todo) {
+                const int l = __builtin_ctzll(todo), its_row = l >> a.lanes_log2;
+                const uint32_t its_bits = rows_lds + (uint32_t)(its_row * a.row_lds);
+                lw_u32 its_marks = (lw_u32)(uintptr_t)(its_bits + 8u * (uint32_t)a.bit_words);
+                int pos = __builtin_amdgcn_readlane(t, l), ended = np;
+                for (bool first = true; pos < np; first = false) {
+                    const int at = min(pos + lane, np - 1), width = min(64, np - pos);
+                    const int run = longest_run(depth_lds, a.depth0, row_window(its_bits, at), np - at);
+                    unsigned long long old = __ballot(lane < width && ((its_marks[at >> 5] >> (at & 31)) & 1u));
+                    if (first) old &= ~1ull;
+                    unsigned long long begun = 0ull;
+                    int off = 0;
+                    while (off < width && !((old >> off) & 1ull)) {
+                        begun |= 1ull << off;
+                        off += max(__builtin_amdgcn_readlane(run, off), 1);
+                    }
+                    if (__ballot(run < 1) & begun) odd |= mine == its_row;
+                    const int stop = min(off, width);  // pairs of the window that are settled
+                    const unsigned long long settled = stop == 64 ? ~0ull : (1ull << stop) - 1ull;
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    const int rel = 32 * ((pos >> 5) + lane) - pos;  // of a word's first pair in the window
+                    if (lane < 3 && rel < 64) {
+                        const uint32_t mask = rel >= 0 ? (uint32_t)(settled >> rel) : (uint32_t)(settled << -rel);
+                        const uint32_t set = rel >= 0 ? (uint32_t)(begun >> rel) : (uint32_t)(begun << -rel);
+                        if (mask) its_marks[(pos >> 5) + lane] = (its_marks[(pos >> 5) + lane] & ~mask) | (set & mask);
+                    }
+                    const int next = pos + off;
+                    const bool joined = off < width;
+                    // (the last entry may reach past the window)
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    const int behind = pos + 64 + lane;
+                    if (!joined && behind < min(next, np)) atomicAnd((uint32_t *)(its_marks + (behind >> 5)), ~(1u << (behind & 31)));
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    pos = next;
+                    if (joined) {
+                        ended = next;
                         break;
                     }
-                    int len = longest_run(depth_lds, a.depth0, row_window(bits, t), np - t);
-                    odd |= len < 1;
-                    len = max(len, 1);
-                    const unsigned long long span = ((1ull << len) - 1ull) << b;
-                    marks[w] = (m & ~(uint32_t)span) | (1u << b);
-                    if ((uint32_t)(span >> 32) && 32 * (w + 1) < seg1) marks[w + 1] &= ~(uint32_t)(span >> 32);
-                    t += len;
                 }
-                if (!met) {
-                    moved = t != end;
-                    end = t;
-                }
-                start = from;
+                // (lanes that this parse went past have nothing left to do)
+                todo &= todo - 1ull;
+                todo &= ~__ballot(pending && lane > l && mine == its_row && t < ended);
             }
-        } while (__any(moved));
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
 
         // ---- codewords of the segment, and of the row's segments before it
         int count = 0;
         if (live)
             for (int w = seg0 >> 5; 32 * w < seg1; w++) count += __popc(marks[w]);
-        int incl = count;
-        for (int d = 1; d < L; d <<= 1) {
-            const int up = __shfl_up(incl, d, 64);
-            if (sub >= d) incl += up;
-        }
-        if constexpr (!WRITE) {
-            // Rows with something odd in them are walked by the trie: it says whether that is an error, and
-            // which comes first in the row.
+        // Rows with something odd in them are walked by the trie: it says whether that is an error, and
+        // which comes first in the row.  (Such a row has no codewords.)
+        if (__any(odd || bad != 0u)) {
             const unsigned long long odd_lanes = __ballot(odd || bad != 0u);
             const unsigned long long row_lanes = L == 64 ? ~0ull : ((1ull << L) - 1ull) << (mine * L);
-            int total = incl;
-            if (sub == L - 1 && row < e.rows) {
-                if (odd_lanes & row_lanes) {
-                    uint32_t n = 0;
-                    const int error = walk_row(e, row, &n, [](uint32_t, int) {});
-                    if (error) {
-                        report(e, error, row);
-                        total = 0;
-                    }
-                }
-                e.row_off[row + 1] = (uint32_t)total;
+            int error = 0;
+            if (sub == L - 1 && row < a.row_end && (odd_lanes & row_lanes)) {
+                uint32_t n = 0;
+                error = walk_row(e, row, &n, [](uint32_t, int) {});
+                if (error) report_row(e, error, row);
             }
-        } else if (live) {
-            // four entries at a time: their trips to the two code tables overlap
-            uint16_t *out = e.codes + (size_t)e.row_off[row] + (size_t)(incl - count);
+            if (__ballot(error != 0) & row_lanes) count = 0;
+        }
+        const int incl = wave_inclusive_scan(count), rel = incl - count;
+        const uint32_t own = (uint32_t)__builtin_amdgcn_readlane(incl, 63);
+        uint32_t *state = group_state(a, group);
+        if (group > 0) publish(state, kEncOwn | own);
+
+        // ---- the segment's codewords, kAtOnce at a time (their trips to the two code tables overlap): put(n, c) takes entries n
+        // .. n + kAtOnce - 1, those of the segment among them
+        constexpr int kAtOnce = 8;
+        auto codewords = [&](auto &&put) {
+            // the segment's last entry ends where the next segment's first one begins, or with the row
+            int last_end = np;
+            if (seg1 < np) {
+                const uint32_t ahead = marks[seg1 >> 5] & 0x3FFFu;
+                last_end = ahead ? seg1 + __builtin_ctz(ahead) : np;
+            }
             int w = seg0 >> 5;
             uint32_t set = marks[w];
             auto next = [&]() -> int {  // the next mark of the segment, or its end
                 while (set == 0u && 32 * (w + 1) < seg1) set = marks[++w];
-                if (set == 0u) return end;
+                if (set == 0u) return last_end;
                 const int t = 32 * w + __builtin_ctz(set);
                 set &= set - 1u;
                 return t;
             };
             int at = next();
-            for (int n = 0; n < count; n += 4) {
-                uint32_t i[4];
+            for (int n = 0; n < count; n += kAtOnce) {
+                uint32_t i[kAtOnce];
 #pragma unroll
-                for (int k = 0; k < 4; k++) {
+                for (int k = 0; k < kAtOnce; k++) {
                     const int to = n + k < count ? next() : at;
                     const int len = max(to - at, 1);
                     const Bits v = row_window(bits, min(at, np - 1));
                     i[k] = ((gp_u32)a.first)[pattern_of(v, min(len, 14))] + (uint32_t)len;
                     at = to;
                 }
+                uint16_t c[kAtOnce];
+#pragma unroll
+                for (int k = 0; k < kAtOnce; k++) c[k] = ((gp_u16)a.codes)[min(i[k], (uint32_t)kTableEntries - 1u)];
+                put(n, c);
+            }
+        };
+        // Before the groups before are all there, the codewords can be put into LDS, over the segment's bits that have been read:
+        // from 8 bytes on (the lane before reads that far into the segment), 16 pairs of bits in 8 bytes.  They must never reach
+        // what is still to be read, so entry n = 8, 16, ... has to begin in a word of 32 pairs, w of the segment, with
+        // 8 + 2 n <= 16 w: always so where entries are longer than four pairs or so.
+        bool early = 8 + 2 * ((count + kAtOnce - 1) / kAtOnce * kAtOnce) <= 8 * ((seg1 - seg0) >> 4) || count == 0;
+        if (live) {
+            int n = 0;
+            for (int w = 0; 32 * w < seg1 - seg0; w++) {
+                n += __popc(marks[(seg0 >> 5) + w]);
+                const int eighth = (n - 1) & ~(kAtOnce - 1);  // the last n = 8, 16, ... in this word or before it
+                early &= eighth < kAtOnce || 8 + 2 * eighth <= 16 * w;
+            }
+        }
+        const bool in_lds = __all(early || !live);
+        const uint32_t codes_lds = bits + 8u * (uint32_t)(seg0 >> 4) + 8u;
+        if (in_lds && live) {
+            codewords([&](int n, const uint16_t (&c)[kAtOnce]) {
+                typedef __attribute__((address_space(3))) unsigned long long *lw_u64;
+                lw_u64 to = (lw_u64)(uintptr_t)(codes_lds + 2u * (uint32_t)n);
+#pragma unroll
+                for (int h = 0; h < 2; h++)
+                    to[h] = (unsigned long long)((uint32_t)c[4 * h] | (uint32_t)c[4 * h + 1] << 16) |
+                            (unsigned long long)((uint32_t)c[4 * h + 2] | (uint32_t)c[4 * h + 3] << 16) << 32;
+            });
+        }
+        // ---- codewords of the groups before
+        const uint32_t before = group > 0 ? codewords_before(a, group) : 0u;
+        publish(state, kEncAll | (before + own));
+        if (sub == L - 1 && mine + 1 < n_rows) e.row_off[row + 1] = (uint32_t)(codes_base + before + (uint32_t)incl);
+        const unsigned long long place = codes_base + before;  // of the group
+        const int fit = (int)min((unsigned long long)own, e.codes_cap - min(place, e.codes_cap));
+        typedef __attribute__((address_space(1))) uint16_t *gw_u16;
+        gw_u16 out = (gw_u16)(e.codes + place);
+        if (in_lds) {
+            // a segment at a time, in whole lines
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            for (int l0 = 0; l0 < 64; l0 += 4) {
                 uint16_t c[4];
 #pragma unroll
-                for (int k = 0; k < 4; k++) c[k] = ((gp_u16)a.codes)[min(i[k], (uint32_t)kTableEntries - 1u)];
+                for (int k = 0; k < 4; k++) {
+                    const uint32_t from = (uint32_t)__builtin_amdgcn_readlane((int)codes_lds, l0 + k);
+                    const int n = __builtin_amdgcn_readlane(count, l0 + k);
+                    c[k] = lane < n ? *(const __attribute__((address_space(3))) uint16_t *)(uintptr_t)(from + 2u * (uint32_t)lane) : (uint16_t)0;
+                }
 #pragma unroll
-                for (int k = 0; k < 4; k++)
-                    if (n + k < count) ((__attribute__((address_space(1))) uint16_t *)out)[n + k] = c[k];
+                for (int k = 0; k < 4; k++) {
+                    const int n = __builtin_amdgcn_readlane(count, l0 + k), at = __builtin_amdgcn_readlane(rel, l0 + k);
+                    if (lane < n && at + lane < fit) out[at + lane] = c[k];
+                    for (int j = 64 + lane; j < n; j += 64)  // (dense rows)
+                        if (at + j < fit)
+                            out[at + j] = *(const __attribute__((address_space(3))) uint16_t *)(uintptr_t)((uint32_t)__builtin_amdgcn_readlane((int)codes_lds, l0 + k) + 2u * (uint32_t)j);
+                }
             }
+        } else if (live) {
+            codewords([&](int n, const uint16_t (&c)[kAtOnce]) {
+#pragma unroll
+                for (int k = 0; k < kAtOnce; k++)
+                    if (n + k < count && rel + n + k < fit) out[rel + n + k] = c[k];
+            });
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -437,17 +673,17 @@ qmoe_status launch_encode(const RunCoderArgs &args, hipStream_t s)
     a.mask_words = (np + 31) / 32 + 1;
     a.row_lds = (8 * a.bit_words + 4 * a.mask_words + 15) / 16 * 16;
     // Lanes per row.  A wavefront's time is its entries one after the other: those of a segment (about 11.5
-    // pairs each), and those of the second parse until the slowest of its lanes has fallen into step -- about
-    // 45 (simulated at 80-92 % zeros: half the lanes need 2-9, one in a hundred 30-64), spread over several
-    // rounds, each up to a segment, where segments are shorter than that.  An entry takes about 900 cycles
+    // pairs each), and those of the second parse until its lanes have fallen into step -- about
+    // 45 (simulated at 80-92 % zeros: half the lanes need 2-9, one in a hundred 30-64; with the wavefront's help for the last
+    // ones somewhat fewer, and never many more).  An entry takes about 900 cycles
     // from end to end and 340 of its SIMD's issue.  A wavefront's row strings have to fit the LDS next to the
-    // depth tables.  (16640 x 6144 values: 89 us a pass
+    // depth tables.  (16640 x 6144 values, a pass of an earlier form: 89 us
     // with 8 lanes per row, as chosen; 156 us with 32, 170 us with 4.)
-    int best_waves = 0, best_log2 = 0, best_grid = 1;
+    int best_waves = 0, best_log2 = 0;
     double best = 0.0;
     for (int l = 0; l <= 6; l++) {
         const int R = 64 >> l;
-        const int fit = std::min(16, (a.max_lds - kRcDepthBytes) / (R * a.row_lds));
+        const int fit = std::min(16, (a.max_lds - kRcDepthBytes - kRcTicketBytes) / (R * a.row_lds));
         if (fit < 1 || !a.depth) continue;
         const int seg = (((np + (1 << l) - 1) >> l) + 31) / 32 * 32;
         const long long groups = (e.rows + R - 1) / R, rounds = (groups + (long long)a.cus * fit - 1) / ((long long)a.cus * fit);
@@ -458,31 +694,41 @@ qmoe_status launch_encode(const RunCoderArgs &args, hipStream_t s)
             best = cost;
             best_log2 = l;
             best_waves = waves;
-            best_grid = (int)std::min<long long>(a.cus, (groups + waves - 1) / waves);
         }
     }
     a.lanes_log2 = best_log2;
     a.seg_pairs = (((np + (1 << best_log2) - 1) >> best_log2) + 31) / 32 * 32;
-    const size_t smem = (size_t)kRcDepthBytes + (size_t)best_waves * (64 >> best_log2) * a.row_lds;
+    if (best_waves) {
+        const size_t smem = (size_t)kRcDepthBytes + kRcTicketBytes + (size_t)best_waves * (64 >> best_log2) * a.row_lds;
+        const qmoe_status st = allow_lds(k_encode_runs, smem);
+        if (st != QMOE_OK) return st;
+        // Rows in chunks whose codewords (at most one a pair) a state can count: one, but for matrices of 2^31 values and more.
+        const int R = 64 >> best_log2;
+        const long long chunk = std::max<long long>(R, (long long)(kEncCount / (uint32_t)np) / R * R);
+        for (long long r0 = 0; r0 < e.rows; r0 += chunk) {
+            a.row0 = (int)r0;
+            a.row_end = (int)std::min<long long>(e.rows, r0 + chunk);
+            a.groups = (a.row_end - a.row0 + R - 1) / R;
+            const int grid = std::min(a.cus, a.groups);  // (not as few workgroups as have a group for every wavefront: 117.9 us, 112)
+            a.groups_per_wg = a.groups / grid;
+            a.groups_extra = a.groups % grid;
+            const int small = (a.groups + 255) / 256;
+            hipLaunchKernelGGL(k_encode_begin, dim3(small), dim3(256), 0, s, a);
+            hipLaunchKernelGGL(k_encode_runs, dim3(grid), dim3(64 * best_waves), smem, s, a);
+            hipLaunchKernelGGL(k_encode_end, dim3(small), dim3(256), 0, s, a);
+        }
+        QMOE_HIP_TRY(hipGetLastError());
+        return QMOE_OK;
+    }
     // the status words are cleared by a kernel, not a memset node, so the call can be captured into a HIP graph
     hipLaunchKernelGGL(k_encode_clear, dim3(1), dim3(64), 0, s, e.status);
     const int grid = (e.rows + 255) / 256;
-    if (best_waves) {
-        qmoe_status st = allow_lds(k_encode_runs<false>, smem);
-        if (st == QMOE_OK) st = allow_lds(k_encode_runs<true>, smem);
-        if (st != QMOE_OK) return st;
-        hipLaunchKernelGGL(k_encode_runs<false>, dim3(best_grid), dim3(64 * best_waves), smem, s, a);
-    } else {
-        hipLaunchKernelGGL(k_encode<false>, dim3(grid), dim3(256), 0, s, e);
-    }
+    hipLaunchKernelGGL(k_encode<false>, dim3(grid), dim3(256), 0, s, e);
     if (np < 100000)
         hipLaunchKernelGGL(k_encode_offsets<20>, dim3(1), dim3(1024), 0, s, e);
     else
         hipLaunchKernelGGL(k_encode_offsets<1>, dim3(1), dim3(1024), 0, s, e);
-    if (best_waves)
-        hipLaunchKernelGGL(k_encode_runs<true>, dim3(best_grid), dim3(64 * best_waves), smem, s, a);
-    else
-        hipLaunchKernelGGL(k_encode<true>, dim3(grid), dim3(256), 0, s, e);
+    hipLaunchKernelGGL(k_encode<true>, dim3(grid), dim3(256), 0, s, e);
     QMOE_HIP_TRY(hipGetLastError());
     return QMOE_OK;
 }

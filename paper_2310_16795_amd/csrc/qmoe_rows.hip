@@ -61,7 +61,7 @@ struct RowsSplit {
     int rows, x_slots;   // rows of a matrix; token tiles whose activations fit the LDS at once (1 or 2)
     double inv_item[4];  // 1 / (cost of a whole item of class k)
     double inv_grid;
-    uint32_t round_cost[7];  // of a round of the wavefronts with 2^l lanes per row: the pieces of a row over its lanes, and about two more
+    uint32_t round_cost[7];  // of a round of the wavefronts with 2^l lanes per row: twice the pieces of a row over its lanes, and two or three more
     // lane-interleaved layout: 1 / lanes, and the even split of the rows over the lanes (`lane_extra` lanes own a row more)
     float inv_lanes;
     int lanes, lane_rows, lane_extra;
@@ -889,7 +889,7 @@ __global__ __launch_bounds__(kRowsThreads) void k_rows(const ProductArgs a, cons
     if (sh.i0 > sh.i1 || (sh.i0 == sh.i1 && sh.r0 >= sh.r1)) return;
 
     // lanes per row for so many rows: the fewest for which the rounds of the workgroup's wavefronts, each as long as a
-    // row's pieces over its lanes plus the round's own start and end (about two more), are shortest
+    // row's pieces over its lanes plus the round's own start and end (one or one and a half more), are shortest
     auto lanes_log2 = [&](uint32_t rows_here) -> int {
         uint32_t best = 0xFFFFFFFFu;
         int log2L = 0;
@@ -1070,7 +1070,7 @@ RowsSplit rows_split(int rows, int cols, int lanes, int x_slots, int grid)
     sp.inv_item[0] = 0.0;
     for (int k = 1; k < 4; k++) sp.inv_item[k] = 1.0 / (double)(kRowCost[k] * ((rows + 7) / 8));
     sp.inv_grid = 1.0 / grid;
-    for (int l = 0; l <= 6; l++) sp.round_cost[l] = (uint32_t)(((cols / 176 + (1 << l)) >> l) + 2 + (l > 0));
+    for (int l = 0; l <= 6; l++) sp.round_cost[l] = (uint32_t)(2 * ((cols / 176 + (1 << l)) >> l) + 2 + (l > 0));
     sp.lanes = lanes;
     sp.inv_lanes = lanes ? 1.0f / (float)lanes : 0.0f;
     sp.lane_rows = lanes ? rows / lanes : 0;

@@ -117,3 +117,24 @@ def test_host_encoder_without_vector_instructions(oracle_dict, tmp_path):
         assert L.qmoe_encode_host(d, vp(tern.ctypes.data), rows, cols, vp(codes.ctypes.data), ctypes.c_size_t(codes.size),
                                   vp(off.ctypes.data), ctypes.byref(n)) == -3
     L.qmoe_dict_destroy(d)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,cols,p0", [(2100, 6144, 0.9), (300, 6144, 0.96), (130, 6144, 0.98), (90, 8190, 0.995), (17, 16384, 0.9),
+                                          (5000, 258, 0.9), (20000, 66, 0.85), (9, 6144, 0.3), (1030, 3000, 0.93)])
+def test_device_encoder_many_groups(oracle_dict, rows, cols, p0):
+    """Groups of rows that wait for each other's counts, and parses that meet late: lanes helped by their wavefront, or (few
+    non-zeros) round after round.  Rows alternate between two densities, so that some wavefronts are done long before others."""
+    dd = dev.DeviceDict(q.qmoe_dict_from_words(oracle_dict.words), "cuda:0")
+    tern = synth.ternary(rows * 3 + cols, rows, cols, p0)
+    tern[::5] *= synth.ternary(7, len(tern[::5]), cols, 0.3) != 0
+    codes, off = q.qmoe_encode_host(dd.handle, tern)
+    print(f"{rows} x {cols}, {p0}", flush=True)
+    for _ in range(3):  # (the offsets are where the groups publish: a second call finds the first one's)
+        got = _on_device(dd, tern, codes.size)
+        assert got[2] == [0, 0]
+        _check(got[:2], (codes, off))
+    assert _on_device(dd, tern, codes.size - 1)[2] == [-2, 0]  # BUFFER_TOO_SMALL
+    tern[rows // 2, cols // 3] = 5
+    assert _on_device(dd, tern, codes.size)[2] == [-3, rows // 2]  # BAD_SYMBOL
+    dd.close()
