@@ -707,9 +707,11 @@ __device__ __forceinline__ void add_one_token(const uint32_t *x, uint32_t e, flo
 // (bit 14 = non-zero, bit 15 = negative: 0x4000 / 0xC000): the sums come out doubled, exactly,
 // and the caller halves the row scale.  Field 0 takes a dot product with (weight, 0) and
 // (0, weight).  Per codeword: three gathers, TBI / 2 * 2 permutes and 2 * TBI dot products.
-template <int TBI, int ASYM = 0>
+// SHARED: a field 0 without a weight reads the zeroed column at zero8 (8 * cols) instead of the
+// run's first one; see consume8 for what that is worth and where.
+template <int TBI, int ASYM = 0, bool SHARED = false>
 __device__ __forceinline__ void accumulate_tile(uint32_t e0, uint32_t xs_addr, uint32_t pos8,
-                                                float (&acc)[TBI * (1 + ASYM)])
+                                                float (&acc)[TBI * (1 + ASYM)], uint32_t zero8 = 0)
 {
     static_assert(TBI == 2 || TBI == 4 || TBI == 8, "tile sizes");
     typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -724,7 +726,8 @@ __device__ __forceinline__ void accumulate_tile(uint32_t e0, uint32_t xs_addr, u
     uint32_t g[3][NW];
 #pragma unroll
     for (int z = 0; z < 3; z++) {
-        const uint32_t at = pos8 + ((ec >> (8 + 8 * z)) & 0xFFu);
+        uint32_t at = pos8 + ((ec >> (8 + 8 * z)) & 0xFFu);
+        if (SHARED && z == 0) at = (e0 & 0xFF00u) ? at : zero8;
         p32 p = (p32)(uintptr_t)(xs_addr + (TBI == 8 ? 2u * at : at));
 #pragma unroll
         for (int k = 0; k < NW; k++) g[z][k] = p[k];

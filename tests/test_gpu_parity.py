@@ -113,6 +113,29 @@ def test_matvec_integer_inputs_are_exact(gpu, ddict, oracle_dict):
     assert np.array_equal(y.cpu().numpy().astype(np.float64), oracle.matvec(tern, one, x))
 
 
+@pytest.mark.parametrize("batch", [1, 2, 3, 5, 8, 19])
+@pytest.mark.parametrize("cols", [30, 280, 2080])
+def test_unused_fields_read_no_live_activation(gpu, ddict, oracle_dict, batch, cols):
+    """Rows that begin (0, w), (w, w) and leave column 0 without a weight, and an infinite activation there: entries with
+    fewer than three weights point their first field at a zero, so nothing reads that column and integer inputs stay exact."""
+    rows = 200
+    tern = synth.ternary(331, rows, cols, 0.93)
+    tern[:, :4] = synth.ternary(332, rows, 4, 0.0)
+    tern[:, 0] = 0
+    one = np.full(rows, np.float16(1.0).view(np.uint16), dtype=np.uint16)
+    xi = np.random.default_rng(cols + batch).integers(-4, 5, (batch, cols)).astype(np.float32)
+    xi[:, 0] = 0.0
+    bits = torch.from_numpy(xi).to(torch.bfloat16).view(torch.int16).numpy().view(np.uint16)
+    want = oracle.matvec(tern, one, bits)
+    bits = bits.copy()
+    bits[:, 0] = 0x7F80
+    M = _upload(oracle_dict, tern, one, gpu)
+    y = torch.empty((batch, rows), dtype=torch.float32, device=gpu)
+    q.qmoe_decode_matvec(ddict.handle, M.desc, _to_dev16(bits, gpu), y)
+    torch.cuda.synchronize()
+    assert np.array_equal(y.cpu().numpy().astype(np.float64), want)
+
+
 def test_general_dictionary_with_many_nonzeros_per_entry(gpu):
     """A table whose entries hold up to six non-zeros cannot use run entries: the
     kernels must fall back to reading the interchange words, with the same results."""
