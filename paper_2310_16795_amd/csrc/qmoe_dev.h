@@ -337,8 +337,9 @@ __device__ __forceinline__ u32x4 select_minmax(uint32_t d0, uint32_t d1, uint32_
 // Copy n 32-bit words from global memory to LDS with the whole workgroup (both 16-byte
 // aligned): 16 bytes per lane and up to eight loads in flight per lane before the first
 // store.  (A plain word-by-word loop waits for every load before it issues the next; for the
-// 65 KB table that was 20-60 us at the start of every workgroup.)
-__device__ __forceinline__ void stage_words(uint32_t *dst_lds, const uint32_t *src, int n)
+// 65 KB table that was 20-60 us at the start of every workgroup.)  `map` is applied to each word.
+template <class Map>
+__device__ __forceinline__ void stage_words(uint32_t *dst_lds, const uint32_t *src, int n, Map &&map)
 {
     const int n4 = n >> 2;  // whole 16-byte pieces
     gp_u32x4 s4 = (gp_u32x4)src;
@@ -350,9 +351,14 @@ __device__ __forceinline__ void stage_words(uint32_t *dst_lds, const uint32_t *s
         for (int k = 0; k < 8; k++) v[k] = s4[min(i0 + k * step, n4 - 1)];
 #pragma unroll
         for (int k = 0; k < 8; k++)
-            if (i0 + k * step < n4) d4[i0 + k * step] = v[k];
+            if (i0 + k * step < n4) d4[i0 + k * step] = u32x4{map(v[k].x), map(v[k].y), map(v[k].z), map(v[k].w)};
     }
-    for (int i = 4 * n4 + (int)threadIdx.x; i < n; i += step) dst_lds[i] = ((gp_u32)src)[i];
+    for (int i = 4 * n4 + (int)threadIdx.x; i < n; i += step) dst_lds[i] = map(((gp_u32)src)[i]);
+}
+
+__device__ __forceinline__ void stage_words(uint32_t *dst_lds, const uint32_t *src, int n)
+{
+    stage_words(dst_lds, src, n, [](uint32_t w) { return w; });
 }
 
 // ---- activations of a tile into LDS (whole workgroup).  The loads of eight columns (one

@@ -22,12 +22,13 @@ namespace {
 // is taken out again, exactly, when a row is written.
 // Only device-order streams (whole table in LDS) take this path.
 //
-// What bounds it: nothing alone.  For 64 codewords the vector units issue 79 instructions and the LDS works 87 cycles, of
-// the 136 a compute unit takes (rows of 2080 columns, sparsities mixed); the LDS holds two wavefronts per SIMD (ring,
-// window and table), too few to hide each other's waits altogether.  A step's activations are loaded straight into the registers the
-// product reads, a codeword piece only by the lanes that need one (asking again for what is there costs a line per lane), a
-// lane's tests are one limit each: 98 instructions before, and 1119 us instead of 1236 for 256 experts of 2080 x 6144 with
-// 1-32 tokens each, 268 instead of 296 us for 128 experts of 768 x 3072 with 31 tokens each.
+// What bounds it: nothing alone.  Of a wavefront's step 48 % goes by in the decoder's rounds (about 4.5 of them, 270 cycles
+// each, with 24 vector instructions and about 35 cycles of the LDS that eight wavefronts share), 30 % in the multiply (a quarter of
+// that waiting for activations), the rest at the window, the set-up and the results (rows of 2080 and 6144 columns, sparsities mixed); the
+// LDS holds two wavefronts per SIMD (ring, window and table), too few to hide each other's waits altogether.  A step's activations are loaded
+// straight into the registers the product reads, a codeword piece only by the lanes that need one (asking again for what is there
+// costs a line per lane).  (Activations asked for a step ahead: 1164 us instead of 1000 where the wait for the window's piece then
+// waits for them too, 1013 where it is moved behind the multiply.)
 // (Slower, measured: two lanes per row with rings of 256 columns, two codewords a round, a ring stored by columns and read
 // transposed, codewords four by four in the window.)
 
@@ -81,17 +82,20 @@ using lp_f32 = const __attribute__((address_space(3))) float *;
 //
 // (A struct of plain scalars and free functions that are always inlined: the state stays in
 // registers.)
-constexpr uint32_t kMmWinAhead = 13;  // the window holds 16 codewords, and a round reads two ahead of the one it applies
-constexpr int kMmWinBytes = 40;   // a lane's window: two 16-byte pieces, padded so that the 64 slots spread over the banks
+constexpr uint32_t kMmWinAhead = 2 * 15;  // the window holds 16 codewords (32 bytes), and a round reads two ahead of the one it applies
+constexpr int kMmWinBytes = 32;   // a lane's window: two 16-byte pieces, on 32 bytes
+
+// The table comes first in the LDS, at address 0, and what follows it begins on 32 bytes (see the windows).
+__host__ __device__ inline size_t mm_table_bytes(int n_order) { return ((size_t)n_order * 4 + 31) & ~(size_t)31; }
 
 struct RingDecoder {
-    uint32_t ci;                // index of the next codeword, counted from the lane's first piece
-    uint32_t end;               // index past the row's last codeword
-    uint32_t lim;               // the lane may go on while ci < lim: codewords are left, and the window reaches two past them
-    uint32_t wbase;             // index of the first codeword of the window's first piece (a multiple of 8)
+    // (bytes into the lane's codewords, counted from its first piece)
+    uint32_t ci;                // one past the next codeword
+    uint32_t end;               // one past the row's last codeword's end
+    uint32_t lim;               // the lane may go on while ci < lim: codewords are left, and the window reaches one past them
+    uint32_t wbase;             // first codeword of the window's first piece (a multiple of 16)
     uint32_t pos8;              // 8 * (column where the next run starts)
-    uint32_t ent, ent_n, flips_n, c1, c2;  // the pipeline: entry of codeword ci, entry of ci + 1 as read and the
-                                           // sign flips of its code, codes of ci + 1 and ci + 2
+    uint32_t ent, flips, code;  // the pipeline: entry of the next codeword as read, the sign flips of its code, code of the one after
     uintptr_t pp, last, pstr;   // first piece of the window, the lane's last piece, bytes from a piece to the next
     u32x4 fut;                  // the piece after the window, in flight
     uint32_t wrow, slot;        // LDS byte addresses of the lane's ring and window
@@ -110,27 +114,31 @@ __device__ __forceinline__ void ring_store_piece(const RingDecoder &d, uint32_t 
     w[1] = (unsigned long long)v.z | ((unsigned long long)v.w << 32);
 }
 
-__device__ __forceinline__ uint32_t ring_code_at(const RingDecoder &d, uint32_t i)
+__device__ __forceinline__ uint32_t ring_code_at(const RingDecoder &d, uint32_t at)
 {
-    return (uint32_t)(*(lp_u16)(uintptr_t)(d.slot + 2u * (i & 15u)));
+    return (uint32_t)(*(lp_u16)(uintptr_t)(d.slot + (at & 30u)));
 }
 
-// table index of a code, as order_entry2 takes it, and what the code's two low bits flip in the entry (bits 18 and 26 of the result; the
-// other bits are left to the caller's mask)
-__device__ __forceinline__ uint32_t ring_entry_index(uint32_t code, uint32_t n_groups3, uint32_t last)
+// LDS byte offset of a code's table entry: the index that order_entry2 takes, times four.  (Signed, so that the second candidate
+// needs no saturation: below the crossing it is the smaller one, and the median with the last entry is then the first.)
+__device__ __forceinline__ uint32_t ring_entry_at(uint32_t code, int minus_groups12, int last4)
 {
-    uint32_t i;
-    asm("v_med3_u32 %0, %1, %2, %3" : "=v"(i) : "v"(code >> 2), "v"(__builtin_elementwise_sub_sat(code, n_groups3)), "s"(last));
-    return i;
+    int at;
+    asm("v_med3_i32 %0, %1, %2, %3" : "=v"(at) : "v"(code & ~3u), "v"((int)(code << 2) + minus_groups12), "s"(last4));
+    return (uint32_t)at;
 }
 
-constexpr uint32_t kMmFlips = 0x04040000u;
+// The table in LDS has its entries' bytes in another order than the one in memory: field 1, field 0, field 2, length.  What the two
+// low bits of a code flip, the signs of fields 1 and 2, is then bits 2 and 18, and one product of the code's low byte
+// puts both there (its other bits are left to the caller's mask).
+__device__ __forceinline__ uint32_t ring_entry_bytes(uint32_t e) { return __builtin_amdgcn_perm(e, e, 0x00030102u); }
+constexpr uint32_t kMmFlips = 0x00040004u;
 
 __device__ __forceinline__ uint32_t ring_flips(uint32_t code)
 {
-    const uint32_t two = code & 3u;
     uint32_t f;
-    asm("v_lshl_or_b32 %0, %1, 25, %2" : "=v"(f) : "v"(two), "v"(two << 18));
+    asm("v_mul_u32_u24_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_0 src1_sel:DWORD"
+        : "=v"(f) : "v"(code), "s"(0x00020004u));
     return f;
 }
 
@@ -139,12 +147,12 @@ __device__ __forceinline__ void ring_setup(RingDecoder &d, const qmoe_matrix &M,
                                            uint32_t slot)
 {
     const RowStream rst = row_stream(M, row, row_live);
-    d.end = rst.sub + rst.left;
+    d.end = 2u * (rst.sub + rst.left) + 2u;
     d.lim = min(d.end, kMmWinAhead);
     d.pp = rst.pp;
     d.last = rst.last;
     d.pstr = rst.pstride;
-    d.ci = rst.sub;
+    d.ci = 2u * rst.sub + 2u;
     d.wrow = wrow;
     d.slot = slot;
     {
@@ -161,16 +169,84 @@ __device__ __forceinline__ void ring_setup(RingDecoder &d, const qmoe_matrix &M,
 
 // Fill the pipeline.  Nothing is in flight afterwards, so that the wait at the top of a round is
 // for the two reads of the round before and not for the three stores issued after them.
-__device__ __forceinline__ void ring_prime(RingDecoder &d, lp_u32 table, uint32_t n_groups3, uint32_t last)
+__device__ __forceinline__ void ring_prime(RingDecoder &d, int minus_groups12, int last4)
 {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    const uint32_t c0 = ring_code_at(d, d.ci);
-    d.c1 = ring_code_at(d, d.ci + 1u);
-    d.c2 = ring_code_at(d, d.ci + 2u);
-    d.ent = table[ring_entry_index(c0, n_groups3, last)] ^ (ring_flips(c0) & kMmFlips);
-    d.ent_n = table[ring_entry_index(d.c1, n_groups3, last)];
-    d.flips_n = ring_flips(d.c1);
-    asm volatile("" : "+v"(d.ent_n), "+v"(d.c1), "+v"(d.c2), "+v"(d.ent));
+    const uint32_t c0 = ring_code_at(d, d.ci - 2u);
+    d.code = ring_code_at(d, d.ci);
+    d.ent = *(lp_u32)(uintptr_t)ring_entry_at(c0, minus_groups12, last4);
+    d.flips = ring_flips(c0);
+    asm volatile("" : "+v"(d.ent), "+v"(d.code));
+}
+
+// Rounds of one codeword per lane, until no lane of the wavefront that may go on (ci < lim) is before column end8 / 8.  A lane
+// that sits out -- its codewords in the window used up, or too far ahead (pos8 > lim8) -- does so for the rest of the call.
+//
+// The pipeline: a round's two reads, the code two codewords ahead and the entry one ahead, go out before its stores and are
+// used in the next round, the code first (it makes an address, the entry waits behind it).  The LDS works in order, so that
+// lgkmcnt(3) is the wait for them and not for the three stores issued after them.
+//
+// In assembly because lanes leave by the execution mask, which only shrinks: the compiler's loop either selects old
+// or new state for every lane that sat out (four instructions, and the lane's reads and stores are done in vain) or rebuilds the mask by
+// scalar instructions and branches.  24 vector instructions, 5 of the LDS and 3 others; 32, 5 and 4 before: 256 experts of 2080 x 6144
+// with 1-32 tokens each 1071 -> 1001 us, 128 experts of 768 x 3072 with 31 tokens each 224 -> 219 us.  (The same instructions field
+// after field, not side by side: 1016 us.  Fields without a weight kept from storing: 1028 us.)
+template <int ASYM>
+__device__ __forceinline__ void ring_rounds(RingDecoder &d, int minus_groups12, int last4, uint32_t lim8, uint32_t end8)
+{
+    uint32_t e, t0, t1, t2, w0, w1, w2;
+    unsigned long long all;
+#define QMOE_ROUNDS(value) \
+    asm volatile("s_mov_b64 %[all], exec\n\t" \
+                 "v_cmpx_lt_u32_e32 vcc, %[ci], %[lim]\n\t" \
+                 "v_cmpx_ge_u32_e32 vcc, %[lim8], %[pos]\n\t" \
+                 "0:\n\t" \
+                 "s_waitcnt lgkmcnt(4)\n\t" \
+                 "v_and_b32_e32 %[t0], -4, %[code]\n\t" \
+                 "v_lshl_add_u32 %[t1], %[code], 2, %[k12]\n\t" \
+                 "v_add_u32_e32 %[ci], 2, %[ci]\n\t" \
+                 "v_med3_i32 %[t0], %[t0], %[t1], %[last4]\n\t" \
+                 "v_and_or_b32 %[t1], %[ci], 30, %[slot]\n\t" \
+                 "s_waitcnt lgkmcnt(3)\n\t" \
+                 "v_bitop3_b32 %[e], %[flips], %[ent], %[mask] bitop3:0x6c\n\t" \
+                 "v_mul_u32_u24_sdwa %[flips], %[code], %[mul] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_0 src1_sel:DWORD\n\t" \
+                 "ds_read_u16 %[code], %[t1]\n\t" \
+                 "ds_read_b32 %[ent], %[t0]\n\t" \
+                 "v_add_u32_sdwa %[t0], %[e], %[pos] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_1 src1_sel:DWORD\n\t" \
+                 "v_add_u32_sdwa %[t1], %[e], %[pos] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_0 src1_sel:DWORD\n\t" \
+                 "v_add_u32_sdwa %[t2], %[e], %[pos] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_2 src1_sel:DWORD\n\t" \
+                 "v_add_u32_sdwa %[pos], %[e], %[pos] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_3 src1_sel:DWORD\n\t" \
+                 "v_bfe_u32 %[w0], %[t0], 3, 7\n\t" \
+                 "v_bfe_u32 %[w1], %[t1], 3, 7\n\t" \
+                 "v_bfe_u32 %[w2], %[t2], 3, 7\n\t" \
+                 value("%[t0]") \
+                 value("%[t1]") \
+                 value("%[t2]") \
+                 "v_add_u32_e32 %[w0], %[w0], %[ring]\n\t" \
+                 "v_add_u32_e32 %[w1], %[w1], %[ring]\n\t" \
+                 "v_add_u32_e32 %[w2], %[w2], %[ring]\n\t" \
+                 "ds_write_b8 %[w0], %[t0]\n\t" \
+                 "ds_write_b8 %[w1], %[t1]\n\t" \
+                 "ds_write_b8 %[w2], %[t2]\n\t" \
+                 "v_cmpx_lt_u32_e32 vcc, %[ci], %[lim]\n\t" \
+                 "v_cmpx_ge_u32_e32 vcc, %[lim8], %[pos]\n\t" \
+                 "v_cmp_gt_u32_e32 vcc, %[end8], %[pos]\n\t" \
+                 "s_cbranch_vccnz 0b\n\t" \
+                 "s_waitcnt lgkmcnt(3)\n\t" \
+                 "s_mov_b64 exec, %[all]\n\t" \
+                 : [ci] "+v"(d.ci), [pos] "+v"(d.pos8), [ent] "+v"(d.ent), [flips] "+v"(d.flips), [code] "+v"(d.code), \
+                   [e] "=&v"(e), [t0] "=&v"(t0), [t1] "=&v"(t1), [t2] "=&v"(t2), [w0] "=&v"(w0), [w1] "=&v"(w1), [w2] "=&v"(w2), \
+                   [all] "=&s"(all) \
+                 : [lim] "v"(d.lim), [ring] "v"(d.wrow), [slot] "v"(d.slot), [lim8] "s"(lim8), [end8] "s"(end8), \
+                   [k12] "s"(minus_groups12), [last4] "s"(last4), [mask] "s"(kMmFlips), [mul] "s"(0x00020004u) \
+                 : "vcc", "memory")
+#define QMOE_AS_IS(t) "v_and_b32_e32 " t ", 6, " t "\n\t"
+#define QMOE_ON_TOP(t) "v_lshlrev_b32_e32 " t ", 5, " t "\n\t"
+    if constexpr (ASYM) QMOE_ROUNDS(QMOE_AS_IS);
+    else QMOE_ROUNDS(QMOE_ON_TOP);
+#undef QMOE_AS_IS
+#undef QMOE_ON_TOP
+#undef QMOE_ROUNDS
 }
 
 // Decode until every lane of the wavefront has passed column kc + 64.  A lane that is there
@@ -179,14 +255,8 @@ __device__ __forceinline__ void ring_prime(RingDecoder &d, lp_u32 table, uint32_
 // the lanes of a wavefront, whose codewords end at different columns, seldom wait for each
 // other.  `after_wait` runs once, right after the step's wait for global memory: the place
 // to issue loads that are wanted when the step has been decoded.
-//
-// The pipeline: nothing that was just read is used in the round that reads it (a select or a
-// sign flip on a fresh value would make the wavefront wait for it on the spot): a round's two
-// reads are issued first, unconditional, from addresses chosen so that a lane that sat out
-// reads again what it already holds, and are used a round later; the entry of ci + 1 is kept
-// as read, next to the sign flips of its code's two low bits.
 template <int ASYM, class AfterWait>
-__device__ __forceinline__ void ring_decode_step(RingDecoder &d, lp_u32 table, uint32_t n_groups3, uint32_t last, int kc,
+__device__ __forceinline__ void ring_decode_step(RingDecoder &d, int minus_groups12, int last4, int kc,
                                                  AfterWait &&after_wait)
 {
     const uint32_t lim8 = 8u * (uint32_t)(kc + kMmAhead), end8 = 8u * (uint32_t)(kc + kMmKc);
@@ -195,49 +265,21 @@ __device__ __forceinline__ void ring_decode_step(RingDecoder &d, lp_u32 table, u
         // Slide the window by one piece where its first piece is used up (a third of the lanes in a step, as a
         // rule), and ask for the next one there.
         {
-            const bool s8 = d.ci - d.wbase >= 8u;
+            const bool s8 = d.ci - d.wbase >= 16u;  // (not below the new first piece afterwards, so that the next such test holds)
             asm volatile("" : "+v"(d.fut));  // (the wait belongs here, ahead of after_wait's loads)
             if (first) {
                 first = false;
                 after_wait();
             }
             if (s8) {
-                ring_store_piece(d, 2u * (d.wbase & 8u), d.fut);
-                d.wbase += 8u;
+                ring_store_piece(d, d.wbase & 16u, d.fut);
+                d.wbase += 16u;
                 d.pp += d.pstr;
                 d.fut = ring_piece_at(d, d.pp + 2u * d.pstr);
             }
             d.lim = min(d.end, d.wbase + kMmWinAhead);
         }
-        // (a loop with its test at the end: with the test in front the compiler keeps two copies of the
-        // decoder's state and moves all of it from one to the other every round)
-        if (__any(d.ci < d.lim && d.pos8 < end8)) do {
-            const bool go = d.ci < d.lim && d.pos8 <= lim8;
-            // The entry this round applies; a lane that sits out applies an empty one, which stores
-            // three zeros at the column where its next run starts: nothing was written there yet, and
-            // it is never a column of the step being completed (kMmAhead keeps a lane's position below
-            // kc + 128), so the loop body has no branch and the stores need not be waited for.
-            const uint32_t e0 = go ? d.ent : 0u;
-            // move on to codeword ci + go: its entry is the one read a round ago (go) or still e0,
-            // the code after it c2 (go) or still c1; this round's reads go out before anything else
-            const uint32_t csel = go ? d.c2 : d.c1;
-            d.ent = go ? (d.ent_n ^ (d.flips_n & kMmFlips)) : d.ent;
-            d.ci += go ? 1u : 0u;
-            d.ent_n = table[ring_entry_index(csel, n_groups3, last)];
-            d.flips_n = ring_flips(csel);
-            d.c1 = csel;
-            d.c2 = ring_code_at(d, d.ci + 2u);
-            __builtin_amdgcn_sched_barrier(0);  // the round's two reads go out before the rest of its work
-#pragma unroll
-            for (int z = 0; z < kRunMaxNonzeros; z++) {
-                const uint32_t t = d.pos8 + ((e0 >> (8 + 8 * z)) & 0xFFu);  // 8 * column + the field's low three bits
-                const uint32_t col = (t >> 3) & (uint32_t)(kMmRing - 1);
-                // value bits of the field (2: +1, 6: -1): as they are (asymmetric grid: byte selectors), or
-                // at the top of the byte (0x40 / 0xC0; the store keeps the low eight bits)
-                *(lw_u8)(uintptr_t)(d.wrow + col) = (unsigned char)(ASYM ? (t & 6u) : (t << 5));
-            }
-            d.pos8 += e0 & 0xFFu;
-        } while (__any(d.ci < d.lim && d.pos8 < end8));
+        if (__any(d.ci < d.lim && d.pos8 < end8)) ring_rounds<ASYM>(d, minus_groups12, last4, lim8, end8);
     } while (__any(d.ci < d.end && d.pos8 < end8));
 }
 
@@ -265,7 +307,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 template <int MB, int EPI, int ASYM>
 __device__ __forceinline__ void mm_item(const ProductArgs &a, const qmoe_matrix &M, int rblk, int slot0, int ntok,
-                                        lp_u32 table, uint32_t wt, uint32_t win)
+                                        uint32_t wt, uint32_t win)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l16 = lane & 15, lg = lane >> 4;
@@ -351,14 +393,14 @@ __device__ __forceinline__ void mm_item(const ProductArgs &a, const qmoe_matrix 
     }
     const uint32_t wfrag = wt + (uint32_t)((64 * wave + l16) * kMmWRowBytes + 8 * lg);
     const int nsteps = (a.cols + kMmKc - 1) / kMmKc;
-    const uint32_t n_groups3 = 3u * (uint32_t)a.n_groups, last = (uint32_t)a.n_order - 1u;
+    const int minus_groups12 = -12 * a.n_groups, last4 = 4 * (a.n_order - 1);
 
-    ring_prime(dec, table, n_groups3, last);
+    ring_prime(dec, minus_groups12, last4);
 
     for (int c = 0; c < nsteps; c++) {
         const int kc = c * kMmKc;
         // ---- decode until every lane has passed column kc + 64
-        ring_decode_step<ASYM>(dec, table, n_groups3, last, kc, [&]() { fetch_x(kc); });
+        ring_decode_step<ASYM>(dec, minus_groups12, last4, kc, [&]() { fetch_x(kc); });
         // the rows this wavefront multiplies are the ones its own lanes wrote
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -446,7 +488,7 @@ template <int EPI, int ASYM>
 __global__ __launch_bounds__(kMmThreads) void k_product_mm(const ProductArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    const size_t table_bytes = ((size_t)a.n_order * 4 + 15) & ~(size_t)15;
+    const size_t table_bytes = mm_table_bytes(a.n_order);
     uint32_t *table_w = reinterpret_cast<uint32_t *>(smem);
     unsigned char *wt = smem + table_bytes;                           // [512][kMmWRowBytes] rings
     unsigned char *win = wt + (size_t)kMmThreads * kMmWRowBytes;      // [512][kMmWinBytes] codeword windows
@@ -469,7 +511,7 @@ __global__ __launch_bounds__(kMmThreads) void k_product_mm(const ProductArgs a)
     int *next_base = reinterpret_cast<int *>(win + (size_t)kMmThreads * kMmWinBytes);  // [1], in-step hand-out only
     int *tok_sums = next_base + 1;                                                      // [2]
     if (threadIdx.x < 2) tok_sums[threadIdx.x] = 0;
-    stage_words(table_w, a.order_table, a.n_order);
+    stage_words(table_w, a.order_table, a.n_order, ring_entry_bytes);
     __syncthreads();
     // In step or each wavefront for itself (see the loop)?  In step when most of the tokens sit in tiles of
     // more than 32: those read 4-8 KB of activations per wavefront and step.
@@ -529,11 +571,11 @@ __global__ __launch_bounds__(kMmThreads) void k_product_mm(const ProductArgs a)
         if (expert < 0 || expert >= a.n_experts || ntok < 1) continue;
         const qmoe_matrix M = a.mats ? a.mats[expert] : a.single;
         if (ntok <= 16)
-            mm_item<1, EPI, ASYM>(a, M, rblk, slot0, ntok, (lp_u32)table_w, wt_addr, win_addr);
+            mm_item<1, EPI, ASYM>(a, M, rblk, slot0, ntok, wt_addr, win_addr);
         else if (ntok <= 32)
-            mm_item<2, EPI, ASYM>(a, M, rblk, slot0, ntok, (lp_u32)table_w, wt_addr, win_addr);
+            mm_item<2, EPI, ASYM>(a, M, rblk, slot0, ntok, wt_addr, win_addr);
         else
-            mm_item<4, EPI, ASYM>(a, M, rblk, slot0, ntok, (lp_u32)table_w, wt_addr, win_addr);
+            mm_item<4, EPI, ASYM>(a, M, rblk, slot0, ntok, wt_addr, win_addr);
     }
 }
 
@@ -541,7 +583,7 @@ __global__ __launch_bounds__(kMmThreads) void k_product_mm(const ProductArgs a)
 
 size_t mm_lds_bytes(int n_order)
 {
-    return (((size_t)n_order * 4 + 15) & ~(size_t)15) + (size_t)kMmThreads * kMmWRowBytes +
+    return mm_table_bytes(n_order) + (size_t)kMmThreads * kMmWRowBytes +
            (size_t)kMmThreads * kMmWinBytes + 16;
 }
 

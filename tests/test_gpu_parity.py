@@ -1020,6 +1020,25 @@ def test_decode_matvec_large_batch_on_the_matrix_cores(gpu, ddict, oracle_dict, 
 # The activations of a tile sit in LDS (160 KB), 8 bytes per column for up to four tokens, next to
 # the table when the stream uses the device numbering; beyond that the calls refuse (LIMIT).
 
+@pytest.mark.parametrize("cols", [58, 130, 2080])
+@pytest.mark.parametrize("minmax", [False, True])
+def test_matrix_core_rows_of_very_different_density(gpu, ddict, oracle_dict, cols, minmax):
+    """Rows of up to a codeword per pair next to rows of zeros: some lanes of a wavefront use up several pieces of their
+    stream in a step of 64 columns while others, far ahead, use none."""
+    rows = 150
+    p0 = np.tile([0.0, 1.0, 0.9, 0.3, 0.97], rows)[:rows]
+    tern = np.concatenate([synth.ternary(500 + r, 1, cols, float(p0[r])) for r in range(rows)])
+    one = np.full(rows, np.float16(1.0).view(np.uint16), dtype=np.uint16)
+    ends = torch.tensor([[-1.0, 1.0]] * rows).to(torch.bfloat16).view(torch.int16).numpy().view(np.uint16)
+    xi = np.random.default_rng(cols).integers(-4, 5, (64, cols)).astype(np.float32)
+    x = torch.from_numpy(xi).to(torch.bfloat16).view(torch.int16).numpy().view(np.uint16)
+    M = _upload(oracle_dict, tern, None if minmax else one, gpu, ddict, minmax=ends if minmax else None)
+    y = torch.empty((64, rows), dtype=torch.float32, device=gpu)
+    q.qmoe_decode_matvec(ddict.handle, M.desc, _to_dev16(x, gpu), y)
+    torch.cuda.synchronize()
+    assert np.array_equal(y.cpu().numpy().astype(np.float64), oracle.matvec(tern, one, x))
+
+
 @pytest.mark.parametrize("order", [0, 1])
 def test_decode_matvec_at_the_widest_row(gpu, ddict, oracle_dict, order):
     rows, cols = 24, 20448
