@@ -405,6 +405,17 @@ __device__ __forceinline__ void mm_item(const ProductArgs &a, const qmoe_matrix 
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
 
+        // (all of the step's weights are asked for before the first is used: 1000 us, 988 now for 256 experts of 2080 x 6144)
+        unsigned long long wd[2][4];
+        {
+            const uint32_t wf = wfrag + (uint32_t)((c & 1) * kMmKc);
+#pragma unroll
+            for (int ks = 0; ks < 2; ks++)
+#pragma unroll
+                for (int nb = 0; nb < 4; nb++) wd[ks][nb] = *(lp_u64)(uintptr_t)(wf + (uint32_t)(nb * 16 * kMmWRowBytes + 32 * ks));
+            __builtin_amdgcn_sched_barrier(0);
+        }
+
         if (kc + kMmKc > a.cols) {
             asm volatile("");  // (a branch, not selects in every step)
 #pragma unroll
@@ -414,13 +425,12 @@ __device__ __forceinline__ void mm_item(const ProductArgs &a, const qmoe_matrix 
         }
 
         // ---- multiply step c
-        const uint32_t wf = wfrag + (uint32_t)((c & 1) * kMmKc);
 #pragma unroll
         for (int ks = 0; ks < 2; ks++) {
             bf16x8 bw[4], ax[MB];
 #pragma unroll
             for (int nb = 0; nb < 4; nb++) {
-                const unsigned long long d = *(lp_u64)(uintptr_t)(wf + (uint32_t)(nb * 16 * kMmWRowBytes + 32 * ks));
+                const unsigned long long d = wd[ks][nb];
                 if constexpr (ASYM)
                     bw[nb] = mm_expand_minmax((uint32_t)d, (uint32_t)(d >> 32), g_hi[nb], g_lo[nb]);
                 else
