@@ -33,6 +33,14 @@ qmoe_status qmoe_hook_set(const char *key, int value);
  */
 int qmoe_hook_several_lanes(const qmoe_dict *d, int format, int n_experts, int d_model, int d_ff, int n_tokens);
 
+/*
+ * How the kernel with several lanes per row cuts a launch into one share per workgroup, computed on the host (no GPU needed):
+ * items[0], [1], [2] token tiles of three or four, two, one tokens, in this order, of matrices of `rows` rows; tiles_at_once: 1, or
+ * 2 where the activations of two tiles fit the LDS.  Share b goes from row out[4 b + 1] of item out[4 b] to row out[4 b + 3] of
+ * item out[4 b + 2], and is empty if that is a lower item.  out: int[4 * groups].
+ */
+qmoe_status qmoe_hook_rows_shares(int rows, const int items[3], int tiles_at_once, int groups, int *out);
+
 #ifdef __cplusplus
 }
 #endif

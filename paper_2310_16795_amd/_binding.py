@@ -56,7 +56,7 @@ EXPORTS = [
     "qmoe_bf16_layer_forward", "qmoe_set_tuning", "qmoe_stream_copy", "qmoe_dict_device_order",
     "qmoe_codes_to_device_order", "qmoe_decompress", "qmoe_encode_device", "qmoe_hook_set", "qmoe_static_workspace_bytes", "qmoe_moe_layer_forward_static",
     "qmoe_lane_layout_size", "qmoe_lane_layout_build", "qmoe_lane_layout_unpack", "qmoe_plan_lanes",
-    "qmoe_plan_row_layout", "qmoe_hook_several_lanes",
+    "qmoe_plan_row_layout", "qmoe_hook_several_lanes", "qmoe_hook_rows_shares",
 ]
 
 
@@ -108,6 +108,7 @@ def lib():
         L.qmoe_plan_row_layout.argtypes = [vp, i, i, i, i]
         L.qmoe_hook_set.argtypes = [c_char_p, i]
         L.qmoe_hook_several_lanes.argtypes = [vp, i, i, i, i, i]
+        L.qmoe_hook_rows_shares.argtypes = [i, vp, i, i, vp]
         L.qmoe_stream_copy.argtypes = [vp, vp, sz, vp]
         _lib = L
     return _lib
@@ -388,6 +389,14 @@ def qmoe_hook_set(key: str, value: int) -> None:
 def qmoe_hook_several_lanes(d: int, fmt: int, n_experts: int, d_model: int, d_ff: int, n_tokens: int) -> bool:
     """Which kernel a layer call's experts with few tokens take (include/qmoe_hooks.h)."""
     return lib().qmoe_hook_several_lanes(d, fmt, n_experts, d_model, d_ff, n_tokens) == 1
+
+
+def qmoe_hook_rows_shares(rows: int, items, tiles_at_once: int, groups: int = 256) -> np.ndarray:
+    """The shares of a launch of the kernel with several lanes per row (include/qmoe_hooks.h): int32 [groups, 4]."""
+    n = np.ascontiguousarray(items, dtype=np.int32)
+    out = np.empty((groups, 4), dtype=np.int32)
+    _check(lib().qmoe_hook_rows_shares(rows, _host_ptr(n), tiles_at_once, groups, _host_ptr(out)), "qmoe_hook_rows_shares")
+    return out
 
 
 def qmoe_stream_copy(dst, src, stream=None) -> None:

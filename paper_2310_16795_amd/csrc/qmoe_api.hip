@@ -959,6 +959,19 @@ int qmoe_hook_several_lanes(const qmoe_dict *d, int format, int n_experts, int d
     return rows_plan(d, code_order, n_experts, lanes != 0, d_model, d_ff, n_tokens, 4).on ? 1 : 0;
 }
 
+qmoe_status qmoe_hook_rows_shares(int rows, const int items[3], int tiles_at_once, int groups, int *out)
+{
+    if (rows < 1 || rows > kMaxCols || !items || groups < 1 || groups > kRowsMaxGrid || (tiles_at_once != 1 && tiles_at_once != 2) || !out)
+        return QMOE_E_INVALID_ARG;
+    int cls[4] = {0, 0, 0, 0};
+    for (int k = 0; k < 3; k++) {
+        if (items[k] < 0 || items[k] > kMaxTokens) return QMOE_E_INVALID_ARG;
+        cls[k + 1] = items[k];
+    }
+    rows_shares(rows, cls, tiles_at_once, groups, out);
+    return QMOE_OK;
+}
+
 size_t qmoe_static_workspace_bytes(void) { return kStaticWsBytes; }
 
 qmoe_status qmoe_moe_layer_forward_static(const qmoe_dict *d, const qmoe_matrix *wi, const qmoe_matrix *wo,

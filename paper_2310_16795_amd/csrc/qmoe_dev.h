@@ -181,6 +181,7 @@ qmoe_status launch_matvec_rows(const ProductArgs &a, bool run, bool minmax, int 
                                hipStream_t s);                                                      // qmoe_matvec.hip
 int rows_tile_slots(int cols, int tb, int n_order, int max_lds);                                     // qmoe_rows.hip
 bool rows_can_dispatch(int n_experts, int n_tokens, int grid, int n_order, int max_lds);
+void rows_shares(int rows, const int (&cls)[4], int x_slots, int grid, int *out);  // all shares of a launch: {i0, r0, i1, r1} each
 // da: the launch groups the tokens itself and leaves records for the second product (rows2, x_slots2)
 qmoe_status launch_rows(const ProductArgs &a, int x_slots, const DispatchArgs *da, int rows2, int x_slots2, int grid, int max_lds,
                         hipStream_t s);

@@ -277,15 +277,42 @@ __device__ __forceinline__ void rows_block(const ProductArgs &a, const RowsSplit
 // per row of 1024 columns and workgroup, measured 17.3, 12.5 and 9.8.
 constexpr int kRowCost[4] = {0, 31, 22, 17};
 
-// A workgroup's share of a launch: from row r0 of item i0 to row r1 of item i1.
+// A workgroup's share of a launch: from row r0 of item i0 to row r1 of item i1 (none of it: i1 < i0).  r0 is a row of item i0.
 struct RowsShare {
     int i0, r0, i1, r1;
 };
 
-// Share `b` of `n` of all rows of the items, cls[k] of them of class k; by a whole wavefront.  (Double precision in place of 64-bit integer
-// divisions, each of which is a hundred instructions: a place is the same function of its cost for the share that
-// ends there and the one that begins there, so rounding moves a boundary by a few rows at most and loses none.)
-__device__ __forceinline__ RowsShare rows_share(const int (&cls)[4], const RowsSplit &sp, int n, int b)
+// (reciprocals to the last bit but one: every workgroup has the same ones, and whole quotients are rounded up first)
+__host__ __device__ __forceinline__ float near_rcp(float v)
+{
+#ifdef __HIP_DEVICE_COMPILE__
+    return __builtin_amdgcn_rcpf(v);
+#else
+    return 1.0f / v;
+#endif
+}
+
+// The largest number from `most` down to 1 that fits, 0 if none does: a lane tries each.
+template <class Fits>
+__host__ __device__ __forceinline__ int largest_that(int most, Fits &&fits)
+{
+#ifdef __HIP_DEVICE_COMPILE__
+    for (int from = most; from >= 1; from -= 64) {
+        const int mine = from - (int)(threadIdx.x & 63u);
+        const unsigned long long yes = __ballot(mine >= 1 && fits(mine));
+        if (yes) return from - __builtin_ctzll(yes);
+    }
+#else
+    for (int g = most; g >= 1; g--)
+        if (fits(g)) return g;
+#endif
+    return 0;
+}
+
+// Share `b` of `n` of all rows of the items, cls[k] of them of class k; by a whole wavefront (on the host: for qmoe_hook_rows_shares).
+// (Double precision in place of 64-bit integer divisions, each of which is a hundred instructions: a place is the same function of its
+// cost for the share that ends there and the one that begins there, so rounding moves a boundary by a few rows at most and loses none.)
+__host__ __device__ __forceinline__ RowsShare rows_share(const int (&cls)[4], const RowsSplit &sp, int n, int b)
 {
     const int n_items = cls[1] + cls[2] + cls[3], rows = sp.rows, eights = (rows + 7) >> 3;
     RowsShare s{0, 0, -1, 0};
@@ -303,21 +330,17 @@ __device__ __forceinline__ RowsShare rows_share(const int (&cls)[4], const RowsS
             top_cost = cls[k] ? kRowCost[k] : top_cost;
             top = cls[k] ? cls[k] : top;
         }
-        // (reciprocals to the last bit but one: every workgroup has the same ones, and whole quotients are rounded up first)
-        const float inv_cost = __builtin_amdgcn_rcpf((float)top_cost);
+        const float inv_cost = near_rcp((float)top_cost);
         auto parts_of = [&](int k, int g_) { return (int)ceilf((float)(kRowCost[k] * g_) * inv_cost - 1e-3f); };
-        // (An even split of the cost would give it this many; rounding up needs fewer, rarely by more than a few.  A lane tries
-        // each: the first that fits.)
-        const int most = min((int)((float)n * __builtin_amdgcn_rcpf((float)top) + 1e-3f),
-                             (int)((float)(top_cost * eights) * (float)n * __builtin_amdgcn_rcpf((float)total)) + 1);
-        for (int from = most; from >= 1 && g == 0; from -= 64) {
-            const int mine = from - (int)(threadIdx.x & 63u);
+        // (an even split of the cost would give it this many; rounding up needs fewer, rarely by more than a few)
+        const int most = min((int)((float)n * near_rcp((float)top) + 1e-3f),
+                             (int)((float)(top_cost * eights) * (float)n * near_rcp((float)total)) + 1);
+        g = largest_that(most, [&](int g_) {
             int need = 0;
 #pragma unroll
-            for (int k = 1; k < 4; k++) need += parts_of(k, mine) * cls[k];
-            const unsigned long long fits = __ballot(mine >= 1 && need <= n);
-            if (fits) g = from - __builtin_ctzll(fits);
-        }
+            for (int k = 1; k < 4; k++) need += parts_of(k, g_) * cls[k];
+            return need <= n;
+        });
 #pragma unroll
         for (int k = 1; k < 4; k++) {
             parts[k] = parts_of(k, g);
@@ -337,7 +360,7 @@ __device__ __forceinline__ RowsShare rows_share(const int (&cls)[4], const RowsS
             if (at < 0) {
                 if (left < here) {
                     p = parts[k];
-                    const int whole = (int)(((float)left + 0.5f) * __builtin_amdgcn_rcpf((float)p));
+                    const int whole = (int)(((float)left + 0.5f) * near_rcp((float)p));
                     item += whole;
                     at = left - whole * p;
                 } else {
@@ -346,36 +369,50 @@ __device__ __forceinline__ RowsShare rows_share(const int (&cls)[4], const RowsS
                 }
             }
         }
-        const float step = (float)eights * __builtin_amdgcn_rcpf((float)p);
+        const float step = (float)eights * near_rcp((float)p);
         s.i0 = s.i1 = item;
         s.r0 = 8 * (int)((float)at * step);
         s.r1 = at + 1 == p ? rows : 8 * (int)((float)(at + 1) * step);
     } else {
-        // The places in the list where the first `c` units of cost end, rows in eights: even lanes where the share begins, odd
-        // ones where it ends.
-        double c = floor(total * sp.inv_grid * (double)(b + (int)(threadIdx.x & 1u)));
-        int item = 0, row = 0;
-        bool found = false;
+        // the place in the list where the first b_ shares end; rows in eights
+        auto place = [&](int b_, int &item, int &row) {
+            double c = floor(total * sp.inv_grid * (double)b_);
+            item = row = 0;
+            bool found = false;
 #pragma unroll
-        for (int k = 1; k < 4; k++) {
-            const double per = (double)(kRowCost[k] * eights), here = (double)cls[k] * per;
-            if (!found) {
-                if (c < here) {
-                    const int i = min((int)(c * sp.inv_item[k]), cls[k] - 1);
-                    const double in_item = c - (double)i * per;
-                    item += i;
-                    row = 8 * max(0, min((int)((float)in_item * (1.0f / (float)kRowCost[k])), eights));
-                    found = true;
-                } else {
-                    c -= here;
-                    item += cls[k];
+            for (int k = 1; k < 4; k++) {
+                const double per = (double)(kRowCost[k] * eights), here = (double)cls[k] * per;
+                if (!found) {
+                    if (c < here) {
+                        const int i = min((int)(c * sp.inv_item[k]), cls[k] - 1);
+                        const double in_item = c - (double)i * per;
+                        item += i;
+                        row = 8 * max(0, min((int)((float)in_item * (1.0f / (float)kRowCost[k])), eights));
+                        found = true;
+                    } else {
+                        c -= here;
+                        item += cls[k];
+                    }
                 }
             }
-        }
+        };
+#ifdef __HIP_DEVICE_COMPILE__
+        int item, row;  // even lanes where the share begins, odd ones where it ends
+        place(b + (int)(threadIdx.x & 1u), item, row);
         s.i0 = __builtin_amdgcn_readlane(item, 0);
         s.r0 = __builtin_amdgcn_readlane(row, 0);
         s.i1 = __builtin_amdgcn_readlane(item, 1);
-        s.r1 = min(__builtin_amdgcn_readlane(row, 1), rows);
+        s.r1 = __builtin_amdgcn_readlane(row, 1);
+#else
+        place(b, s.i0, s.r0);
+        place(b + 1, s.i1, s.r1);
+#endif
+        s.r1 = min(s.r1, rows);
+        // (A whole item's cost times its reciprocal may fall short of one: the place is then behind that item's last row.)
+        if (s.r0 >= rows) {
+            s.i0++;
+            s.r0 = 0;
+        }
         if (b + 1 == n) {
             s.i1 = n_items - 1;
             s.r1 = rows;
@@ -1076,6 +1113,16 @@ RowsSplit rows_split(int rows, int cols, int lanes, int x_slots, int grid)
     sp.lane_rows = lanes ? rows / lanes : 0;
     sp.lane_extra = lanes ? rows % lanes : 0;
     return sp;
+}
+
+void rows_shares(int rows, const int (&cls)[4], int x_slots, int grid, int *out)
+{
+    const RowsSplit sp = rows_split(rows, 0, 0, x_slots, grid);
+    for (int b = 0; b < grid; b++) {
+        const RowsShare s = rows_share(cls, sp, grid, b);
+        const int v[4] = {s.i0, s.r0, s.i1, s.r1};
+        std::copy(v, v + 4, out + 4 * b);
+    }
 }
 
 qmoe_status launch_rows(const ProductArgs &a, int x_slots, const DispatchArgs *da, int rows2, int x_slots2, int grid, int max_lds,

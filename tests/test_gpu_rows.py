@@ -173,3 +173,20 @@ def test_tokens_grouped_in_the_first_product(gpu, ddict, oracle_dict, E, T, drop
     assert list(got["counters"][10:14]) == [0] + [sum(t[2] in k for t in tiles) for k in ((3, 4), (2,), (1,))]
     _check_layer(w, idx, x, y, got, [t for t in range(T) if 0 <= idx[t] < E][:24])
     assert not y[[t for t in range(T) if not 0 <= idx[t] < E]].any()
+
+
+# Uneven shares (nearly as many items as workgroups) of matrices whose rows no eight divides: a share's beginning may fall behind
+# the last row of an item, and the wavefronts of that workgroup go on with the item after it, 16 and more lanes to a row.
+@pytest.mark.parametrize("d_model,d_ff,pairs,singles", [(354, 2048, 0, 26), (394, 2048, 0, 44), (396, 4714, 17, 18), (2048, 468, 0, 26)])
+@pytest.mark.parametrize("minmax", [False, True])
+@pytest.mark.parametrize("lanes", [False, True])
+def test_shares_that_begin_behind_an_item(gpu, ddict, oracle_dict, monkeypatch, d_model, d_ff, pairs, singles, minmax, lanes):
+    if lanes:
+        monkeypatch.setattr(dev.B, "qmoe_plan_row_layout", lambda *a: False)
+    E, T = pairs + singles, 2 * pairs + singles
+    w = synth.WORKLOADS["switch_base128"].scaled(n_experts=E, d_model=d_model, d_ff=d_ff, n_tokens=T)
+    x = w.tokens()
+    idx = np.concatenate([np.repeat(np.arange(pairs), 2), np.arange(pairs, E)]).astype(np.int32)
+    layer = _build_layer(w, oracle_dict, gpu, "library", ddict.handle, order_of=ddict, minmax=minmax, lanes_for_tokens=T if lanes else 0)
+    y, wsout = _run_layer(layer, ddict, x, idx, gpu)
+    _check_layer(w, idx, x, y, wsout, list(range(T)), asym=minmax)

@@ -329,3 +329,31 @@ def test_lane_layout_round_trip_and_placement(lib_dict):
     assert L.qmoe_lane_layout_build(c.ctypes.data, ro.ctypes.data, 2, 64, out.ctypes.data, 64, wo.ctypes.data) == 0
     assert out[:3].tolist() == [0, 1, 2] and out[8:10].tolist() == [3, 4]  # lane 0 owns row 0, lane 1 row 1
     assert L.qmoe_plan_lanes(None, 8, 16, 4, 4) == 0
+
+
+@pytest.mark.parametrize("groups", [256, 80, 1])
+def test_shares_of_the_rows_cover_each_row_once(groups):
+    """Every share begins at a row of its first item, ends where the next one begins, and together they are all rows of all items;
+    rows that no eight divides, items from one to several a workgroup, in mixed classes."""
+    rng = np.random.default_rng(groups)
+    mixes = [(0, 0, 26), (0, 0, 44), (0, 17, 18), (0, 26, 0), (1, 0, 0), (0, 0, 1), (0, 0, 256), (256, 0, 0), (3, 30, 479)]
+    mixes += [tuple(int(v) for v in rng.integers(0, hi, 3)) for hi in (4, 30, 100, 300) for _ in range(6)]
+    for rows in (1, 7, 8, 9, 346, 354, 358, 386, 394, 396, 452, 468, 530, 730, 768, 1003, 2080, 6144):
+        for mix in mixes:
+            n = sum(mix)
+            for tiles in (1, 2):
+                s = q.qmoe_hook_rows_shares(rows, mix, tiles, groups).astype(np.int64)
+                begin, end = s[:, 0] * rows + s[:, 1], s[:, 2] * rows + s[:, 3]
+                s, begin, end = (v[(s[:, 2] > s[:, 0]) | ((s[:, 2] == s[:, 0]) & (s[:, 3] > s[:, 1]))] for v in (s, begin, end))
+                where = f"{rows} rows, {mix}, {tiles}"
+                if n == 0:
+                    assert not len(s), where
+                    continue
+                assert (s[:, 1] >= 0).all() and (s[:, 1] < rows).all() and (s[:, 3] >= 0).all() and (s[:, 3] <= rows).all(), where
+                assert begin[0] == 0 and end[-1] == n * rows and np.array_equal(begin[1:], end[:-1]), where
+                tokens = 4 * mix[0] + 2 * mix[1] + mix[2]
+                if tokens <= 4 * groups:  # (such calls keep a share's items in a record of six)
+                    assert (s[:, 2] - s[:, 0] < 6).all(), where
+    for bad in ((0, (1, 0, 0), 1), (8, (-1, 0, 0), 1), (8, (1, 0, 0), 3)):
+        with pytest.raises(q.QmoeError):
+            q.qmoe_hook_rows_shares(*bad, groups)
