@@ -699,8 +699,8 @@ __device__ __forceinline__ void x_load(XPairs<PIECES> &p, const uint16_t *x, con
     }
 }
 
-// One token: records {0, +x, 0, -x}; more: four tokens a column (a tile of two is read as two, and what stands behind the last
-// token of three is its neighbour's: sums that nobody writes).
+// One token: records {0, +x, 0, -x}; more: four tokens a column (a tile of two is read as two).  Behind the last token of three
+// stand zeros: a field's dot product takes the neighbour in with a weight of zero, and an infinity would make that a NaN.
 template <int PIECES>
 __device__ __forceinline__ void x_store(const XPairs<PIECES> &p, unsigned char *xs, int ntok, int cols, int base)
 {
@@ -716,10 +716,11 @@ __device__ __forceinline__ void x_store(const XPairs<PIECES> &p, unsigned char *
             o.z = v & 0xFFFF0000u;
             o.w = o.z ^ 0x80000000u;
         } else {
+            const uint32_t fourth = ntok > 3 ? p.v[k][3] : 0u;
             o.x = __builtin_amdgcn_perm(p.v[k][1], p.v[k][0], 0x05040100u);
-            o.y = __builtin_amdgcn_perm(p.v[k][3], p.v[k][2], 0x05040100u);
+            o.y = __builtin_amdgcn_perm(fourth, p.v[k][2], 0x05040100u);
             o.z = __builtin_amdgcn_perm(p.v[k][1], p.v[k][0], 0x07060302u);
-            o.w = __builtin_amdgcn_perm(p.v[k][3], p.v[k][2], 0x07060302u);
+            o.w = __builtin_amdgcn_perm(fourth, p.v[k][2], 0x07060302u);
         }
         if (c < cols) *reinterpret_cast<u32x4 *>(xs + 8 * (size_t)c) = o;
     }

@@ -190,3 +190,24 @@ def test_shares_that_begin_behind_an_item(gpu, ddict, oracle_dict, monkeypatch, 
     layer = _build_layer(w, oracle_dict, gpu, "library", ddict.handle, order_of=ddict, minmax=minmax, lanes_for_tokens=T if lanes else 0)
     y, wsout = _run_layer(layer, ddict, x, idx, gpu)
     _check_layer(w, idx, x, y, wsout, list(range(T)), asym=minmax)
+
+
+@pytest.mark.parametrize("minmax", [False, True])
+@pytest.mark.parametrize("batch", [3, 7])
+def test_three_tokens_like_four(gpu, ddict, oracle_dict, batch, minmax):
+    """A tile of three tokens computes what it computes with a fourth token of zeros, infinities among the activations included."""
+    rows, cols = 130, 600
+    tern = synth.ternary(41, rows, cols, 0.7)
+    scale = None if minmax else synth.uniform_f16(1, (rows,), 0.01, 0.1)
+    pairs = synth.minmax_bf16(2, rows, 0.01, 0.1) if minmax else None
+    x = synth.normal_bf16(3, (batch + 1, cols))
+    x[batch - 1, [7, 301]] = 0x7F80
+    x[batch] = 0
+    M = _upload(oracle_dict, tern, scale, gpu, ddict, minmax=pairs)
+    got = []
+    for b in (batch, batch + 1):
+        y = torch.empty((b, rows), dtype=torch.float32, device=gpu)
+        q.qmoe_decode_matvec(ddict.handle, M.desc, _to_dev16(x[:b], gpu), y)
+        torch.cuda.synchronize()
+        got.append(y.cpu().numpy()[:batch])
+    assert np.isinf(got[1]).any() and np.array_equal(got[0], got[1], equal_nan=True)
