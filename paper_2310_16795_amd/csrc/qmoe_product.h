@@ -171,9 +171,9 @@ __device__ __forceinline__ void consume8(const ProductArgs &a, LaneState<TBI, AS
     st.pos8 = p;
     float part[8][NA];  // the sums after each of the eight
     // The gathers bound this loop: 64 lanes that read at random take 7.1 cycles of the CU's LDS, and
-    // lanes that read one and the same word share an access.  Field 0 is the last that an entry
-    // fills, so most codewords carry no weight there: those lanes all read one zero (the empty slot
-    // of column 0's record; in tiles the zeroed column past the last).  c2048, 2048 tokens, both
+    // lanes that read one and the same word share an access.  Field 0 is the last that an entry of
+    // the device order fills, so most codewords carry no weight there: those lanes all read one zero
+    // (the empty slot of column 0's record; in tiles the zeroed column past the last).  c2048, 2048 tokens, both
     // products: 921 -> 845 us.  The same for field 1, which more codewords use, costs its two
     // instructions and gains nothing (1.068x against 1.076x for field 0 alone); in k_rows, which
     // waits for latency and not for the LDS, it loses 1 to 6 %.

@@ -116,8 +116,8 @@ def test_matvec_integer_inputs_are_exact(gpu, ddict, oracle_dict):
 @pytest.mark.parametrize("batch", [1, 2, 3, 5, 8, 19])
 @pytest.mark.parametrize("cols", [30, 280, 2080])
 def test_unused_fields_read_no_live_activation(gpu, ddict, oracle_dict, batch, cols):
-    """Rows that begin (0, w), (w, w) and leave column 0 without a weight, and an infinite activation there: entries with
-    fewer than three weights point their first field at a zero, so nothing reads that column and integer inputs stay exact."""
+    """Rows that begin (0, w), (w, w) and leave column 0 without a weight, and an infinite activation there: the first entry has
+    its three weights, nothing reads that column, and integer inputs stay exact."""
     rows = 200
     tern = synth.ternary(331, rows, cols, 0.93)
     tern[:, :4] = synth.ternary(332, rows, 4, 0.0)
@@ -134,6 +134,50 @@ def test_unused_fields_read_no_live_activation(gpu, ddict, oracle_dict, batch, c
     q.qmoe_decode_matvec(ddict.handle, M.desc, _to_dev16(bits, gpu), y)
     torch.cuda.synchronize()
     assert np.array_equal(y.cpu().numpy().astype(np.float64), want)
+
+
+# Tiles of up to four, two, eight tokens and of one; the table in LDS, in L2 (-1), its head in LDS.  (Interchange numbering: an
+# entry's weights begin with the first field, and tiles multiply the column by the zero weights of the others.)
+@pytest.mark.parametrize("order,tile,table", [(1, 0, 0), (1, 2, 0), (1, 8, 0), (1, 0, -1), (1, 1, 0), (0, 1, 0), (0, 1, 8192)])
+@pytest.mark.parametrize("minmax", [False, True])
+def test_shared_zero_of_unused_first_fields(gpu, ddict, oracle_dict, minmax, order, tile, table):
+    """Infinite activations at the columns where entries with two weights begin, none of them on the column itself: the
+    lane-per-row kernel reads a zero for the field that such an entry leaves unused, so the hidden vectors of integer inputs stay
+    exact.  All rows are alike, so that nothing else reads those columns."""
+    d_model, d_ff, counts = 280, 40, (1, 2, 3, 4, 9)
+    idx = np.repeat(np.arange(len(counts)), counts).astype(np.int32)
+    tern = np.repeat(synth.ternary(341, 1, d_model, 0.9), d_ff, axis=0)
+    codes, row_off = oracle.encode(oracle_dict, tern)
+    row = codes[:row_off[1]]
+    begins = np.cumsum(2 * oracle_dict.npairs[row].astype(int)) - 2 * oracle_dict.npairs[row]
+    # (not column 0: slots of a lane's first and last piece that are not its codewords stand there)
+    two = [c for c, code in zip(begins, row) if c > 0 and (oracle_dict.syms[code] != 0).sum() == 2 and tern[0, c] == 0]
+    assert len(two) >= 2
+    one = np.full(d_ff, np.float16(1.0).view(np.uint16), dtype=np.uint16)
+    pair = np.tile(np.array([0xBF80, 0x4040], dtype=np.uint16), (d_ff, 1))  # (-1, 3): signed sum twice, and the sum under |weight|
+    wo, wo_off = oracle.encode(oracle_dict, synth.ternary(343, d_model, d_ff, 0.9))
+    layer = dev.DeviceLayer(len(counts), d_model, d_ff, gpu, minmax=minmax)
+    for e in range(len(counts)):
+        layer.set_expert(e, "wi", codes, row_off, pair if minmax else one)
+        layer.set_expert(e, "wo", wo, wo_off, np.zeros((d_model, 2) if minmax else d_model, dtype=np.uint16))
+    layer.finalize(device_order_of=ddict if order else None)
+    x = np.random.default_rng(7).integers(-2, 3, (idx.size, d_model)).astype(np.float32)
+    x[:, two] = 0.0
+    bits = torch.from_numpy(x).to(torch.bfloat16).view(torch.int16).numpy().view(np.uint16).copy()
+    want = np.maximum(oracle.matvec(tern, None if minmax else one, bits, minmax_bf16=pair if minmax else None), 0.0)
+    assert 0 < want.max() <= 256  # (exact in bf16)
+    bits[:, two] = 0x7F80
+    for key, value in (("mfma_min_tokens", -1), ("token_tile", tile), ("lds_dict_entries", table)):
+        q.qmoe_set_tuning(key, value)
+    q.qmoe_hook_set("rows", -1)
+    try:
+        _, got = _run_layer(layer, ddict, bits, idx, gpu)
+    finally:
+        q.qmoe_hook_set("rows", 0)
+        for key in ("mfma_min_tokens", "token_tile", "lds_dict_entries"):
+            q.qmoe_set_tuning(key, 0)
+    hidden = torch.from_numpy(got["hidden"].view(np.int16)).view(torch.bfloat16).double().numpy()
+    assert np.array_equal(hidden, want[got["perm"]])
 
 
 def test_general_dictionary_with_many_nonzeros_per_entry(gpu):
