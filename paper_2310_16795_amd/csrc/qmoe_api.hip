@@ -10,9 +10,9 @@ std::atomic<int> g_last_hip_error{0};
 
 // The permission belongs to the function on the current GPU and lasts: the runtime is asked only when a kernel wants more
 // than it was given before (asking costs the host as much as planning a call does).
-qmoe_status allow_lds_bytes(const void *kernel, size_t smem)
+qmoe_status allow_lds_bytes(const void *kernel, size_t smem, bool from_zero)
 {
-    if (smem <= 48 * 1024) return QMOE_OK;
+    if (smem <= 48 * 1024 && !from_zero) return QMOE_OK;
     struct Allowed {
         const void *kernel;
         int dev;
@@ -27,6 +27,11 @@ qmoe_status allow_lds_bytes(const void *kernel, size_t smem)
     for (Allowed &a : allowed)
         if (a.kernel == kernel && a.dev == dev) mine = &a;
     if (mine && mine->bytes >= smem) return QMOE_OK;
+    if (from_zero && !mine) {
+        hipFuncAttributes f;
+        QMOE_HIP_TRY(hipFuncGetAttributes(&f, kernel));
+        if (f.sharedSizeBytes) return QMOE_E_LIMIT;
+    }
     QMOE_HIP_TRY(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
     if (mine) mine->bytes = smem;
     else allowed.push_back({kernel, dev, smem});

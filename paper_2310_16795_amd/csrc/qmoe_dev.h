@@ -164,11 +164,12 @@ constexpr int kMmMinTokensDefault = 8;         // experts with fewer tokens stay
 
 // ---------------------------------------------------------------- launch functions (one per kernel family)
 // Each enqueues on `s` and returns QMOE_OK or QMOE_E_HIP; the callers have checked the arguments.
-qmoe_status allow_lds_bytes(const void *kernel, size_t smem);
+// from_zero: the kernel takes the launch's LDS to begin at address 0, so it may have none of a fixed size (QMOE_E_LIMIT if it does)
+qmoe_status allow_lds_bytes(const void *kernel, size_t smem, bool from_zero);
 template <typename K>
-inline qmoe_status allow_lds(K kernel, size_t smem)
+inline qmoe_status allow_lds(K kernel, size_t smem, bool from_zero = false)
 {
-    return allow_lds_bytes(reinterpret_cast<const void *>(kernel), smem);
+    return allow_lds_bytes(reinterpret_cast<const void *>(kernel), smem, from_zero);
 }
 qmoe_status launch_product(const ProductArgs &a, const ProductPlan &p, bool run, hipStream_t s);   // qmoe_product_*.hip
 qmoe_status launch_product_sym(const ProductArgs &a, const ProductPlan &p, bool run, hipStream_t s);

@@ -85,7 +85,10 @@ using lp_f32 = const __attribute__((address_space(3))) float *;
 constexpr uint32_t kMmWinAhead = 2 * 15;  // the window holds 16 codewords (32 bytes), and a round reads two ahead of the one it applies
 constexpr int kMmWinBytes = 32;   // a lane's window: two 16-byte pieces, on 32 bytes
 
-// The table comes first in the LDS, at address 0, and what follows it begins on 32 bytes (see the windows).
+// The table comes first in the LDS, at address 0 (launch_product_mm sees to that), and what follows it begins on 32 bytes: a window's
+// address takes the place in it by an OR.
+static_assert(kMmWinBytes == 32 && kMmThreads * kMmWRowBytes % kMmWinBytes == 0, "windows on their own size: ring_rounds and ring_code_at keep bits 1..4");
+static_assert(kMmRing == 1 << 7, "ring_rounds takes seven bits of a column");
 __host__ __device__ inline size_t mm_table_bytes(int n_order) { return ((size_t)n_order * 4 + 31) & ~(size_t)31; }
 
 struct RingDecoder {
@@ -601,7 +604,7 @@ qmoe_status launch_product_mm(ProductArgs a, const MmPlan &mp, hipStream_t s)
 {
     a.mm_row_blocks = (a.rows + 63) / 64;  // units of 64 rows, one wavefront each
     auto launch = [&](auto kernel) -> qmoe_status {
-        const qmoe_status st = allow_lds(kernel, mp.smem);
+        const qmoe_status st = allow_lds(kernel, mp.smem, true);
         if (st != QMOE_OK) return st;
         hipLaunchKernelGGL(kernel, dim3(mp.grid), dim3(kMmThreads), mp.smem, s, a);
         return QMOE_OK;
