@@ -53,6 +53,14 @@ __device__ __forceinline__ uint32_t row_scale_raw(const RowSink &rs, int i)
     else return (uint32_t)rs.scale_s[i];
 }
 
+// ... of the lane's current row; behind its rows the last one's, for a lane without rows the block's first (the scales may be the
+// last thing in the workgroup's LDS)
+template <int ASYM>
+__device__ __forceinline__ uint32_t lane_scale_raw(const RowSink &rs, int row, int rb)
+{
+    return row_scale_raw<ASYM>(rs, max(min(row, rb - 1) - rs.r0, 0));
+}
+
 template <int TBI, int EPI, int ASYM = 0>
 __device__ __forceinline__ void write_row(const ProductArgs &a, const LaneState<TBI, ASYM> &st,
                                           const float (&sum)[TBI * (1 + ASYM)], const RowSink &rs)
@@ -113,7 +121,7 @@ __device__ __forceinline__ void consume1(const ProductArgs &a, LaneState<TBI, AS
             for (int t = 0; t < TBI * (1 + ASYM); t++) st.acc[t] = 0.0f;
             st.pos8 -= cols8;
             st.row += 1;
-            if constexpr (TBI == 1) st.sraw = row_scale_raw<ASYM>(rs, min(st.row, st.rb) - rs.r0);
+            if constexpr (TBI == 1) st.sraw = lane_scale_raw<ASYM>(rs, st.row, st.rb);
         }
     }
 }
@@ -226,7 +234,7 @@ __device__ __forceinline__ void consume8(const ProductArgs &a, LaneState<TBI, AS
             }
             st.row += 1;
             // the next row's scale is asked for now and not needed before that row ends
-            if constexpr (TBI == 1) st.sraw = row_scale_raw<ASYM>(rs, min(st.row, st.rb) - rs.r0);
+            if constexpr (TBI == 1) st.sraw = lane_scale_raw<ASYM>(rs, st.row, st.rb);
         }
     }
 }
@@ -312,7 +320,7 @@ __device__ __forceinline__ void product_block(const ProductArgs &a, const qmoe_m
     st.row = ra;
     st.rb = rb;
     st.sraw = 0u;
-    if constexpr (TBI == 1) st.sraw = row_scale_raw<ASYM>(rs, min(ra, rb) - rs.r0);
+    if constexpr (TBI == 1) st.sraw = lane_scale_raw<ASYM>(rs, ra, rb);
 
     // Piece p + 2 is being loaded and the entries of piece p + 1 looked up while piece p
     // is applied.
