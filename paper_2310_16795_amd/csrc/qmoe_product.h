@@ -119,7 +119,7 @@ __device__ __forceinline__ void consume1(const ProductArgs &a, LaneState<TBI, AS
             if (st.row < st.rb) write_row<TBI, EPI, ASYM>(a, st, st.acc, rs);
 #pragma unroll
             for (int t = 0; t < TBI * (1 + ASYM); t++) st.acc[t] = 0.0f;
-            st.pos8 -= cols8;
+            st.pos8 = min(st.pos8 - cols8, cols8);  // (0, but in a corrupt stream: a row narrower than a run would fall behind for good)
             st.row += 1;
             if constexpr (TBI == 1) st.sraw = lane_scale_raw<ASYM>(rs, st.row, st.rb);
         }

@@ -18,7 +18,7 @@ def library(tmp_path_factory):
     return build(str(tmp_path_factory.mktemp("lanes")))
 
 
-@pytest.mark.parametrize("kind,count", [("layer", 60), ("single", 60), ("single_corrupt", 18), ("encode", 60)])
+@pytest.mark.parametrize("kind,count", [("layer", 60), ("layer_corrupt", 24), ("single", 60), ("single_corrupt", 18), ("encode", 60)])
 def test_every_access_is_inside(library, kind, count):
     cmd = [sys.executable, os.path.join(HERE, "lanes", "cases.py"), kind, "1", str(count)]
     r = subprocess.run(cmd, env={**os.environ, "QMOE_LIBRARY": library}, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300)
