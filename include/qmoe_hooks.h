@@ -22,6 +22,8 @@ extern "C" {
  *              staging a block's results in LDS; 0 = default
  *  "rows"      1 = layer calls and single matrices use the kernel with several lanes per row
  *              wherever it can run, -1 = never, 0 = the planner's choice (the default)
+ *  "encode_rows" n = the device encoder takes at most n rows (in whole groups of its wavefronts) in a round of its three
+ *              kernels, as it does by itself from 2^31 values on; 0 = default
  * Unknown key: QMOE_E_INVALID_ARG.
  */
 qmoe_status qmoe_hook_set(const char *key, int value);

@@ -611,10 +611,10 @@ __global__ __launch_bounds__(1024) void k_encode_runs(const RunCoderArgs a)
 #pragma unroll
                 for (int k = 0; k < 4; k++) {
                     const int n = __builtin_amdgcn_readlane(count, l0 + k), at = __builtin_amdgcn_readlane(rel, l0 + k);
+                    const uint32_t from = (uint32_t)__builtin_amdgcn_readlane((int)codes_lds, l0 + k);
                     if (lane < n && at + lane < fit) out[at + lane] = c[k];
                     for (int j = 64 + lane; j < n; j += 64)  // (dense rows)
-                        if (at + j < fit)
-                            out[at + j] = *(const __attribute__((address_space(3))) uint16_t *)(uintptr_t)((uint32_t)__builtin_amdgcn_readlane((int)codes_lds, l0 + k) + 2u * (uint32_t)j);
+                        if (at + j < fit) out[at + j] = *(const __attribute__((address_space(3))) uint16_t *)(uintptr_t)(from + 2u * (uint32_t)j);
                 }
             }
         } else if (live) {
@@ -704,7 +704,8 @@ qmoe_status launch_encode(const RunCoderArgs &args, hipStream_t s)
         if (st != QMOE_OK) return st;
         // Rows in chunks whose codewords (at most one a pair) a state can count: one, but for matrices of 2^31 values and more.
         const int R = 64 >> best_log2;
-        const long long chunk = std::max<long long>(R, (long long)(kEncCount / (uint32_t)np) / R * R);
+        long long chunk = std::max<long long>(R, (long long)(kEncCount / (uint32_t)np) / R * R);
+        if (tuning().encode_rows > 0) chunk = std::min<long long>(chunk, std::max(R, tuning().encode_rows / R * R));
         for (long long r0 = 0; r0 < e.rows; r0 += chunk) {
             a.row0 = (int)r0;
             a.row_end = (int)std::min<long long>(e.rows, r0 + chunk);

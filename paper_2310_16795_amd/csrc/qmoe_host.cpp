@@ -736,6 +736,7 @@ qmoe_status qmoe_hook_set(const char *key, int value)
     if (!std::strcmp(key, "phases")) t.phases = value;
     else if (!std::strcmp(key, "stage_out")) t.stage_out = value;
     else if (!std::strcmp(key, "rows")) t.rows = value;
+    else if (!std::strcmp(key, "encode_rows")) t.encode_rows = value;
     else return QMOE_E_INVALID_ARG;
     return QMOE_OK;
 }

@@ -95,6 +95,7 @@ struct Tuning {
     int stage_out = 0;  // -1 = the first product writes its hidden values straight to global memory
     int overlap = 0;  // -1 = all kernels of a layer on the caller's stream, one after the other
     int mfma_min_tokens = 0;  // 0 = heuristic, -1 = never use the matrix-core kernel
+    int encode_rows = 0;  // rows of a round of the device encoder's kernels at most, 0 = as many as their states can count
     int phases = 0;  // kernels of a layer call to enqueue: bit 0 dispatch, bits 1 / 2 scalar kernel of the first / second
                      // product, bits 3 / 4 matrix-core kernel of the first / second product; 0 = all
 };

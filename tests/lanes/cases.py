@@ -134,7 +134,8 @@ def single(rng, i, corrupt):
 def encode(rng, i, bad):
     """The device encoder; bad: a value that is none, or too little room."""
     rows, cols, p0 = int(np.exp(rng.uniform(0, 5.5))), 2 * int(np.exp(rng.uniform(0, 6.5))), float(rng.choice([0.0, 0.3, 0.6, 0.8, 0.9, 0.95, 0.98, 1.0]))
-    print(f"encode {i}: {rows} x {cols}, {p0} zeros", flush=True)
+    a_round = int(rng.choice([0, 1, 64, 100]))  # rows
+    print(f"encode {i}: {rows} x {cols}, {p0} zeros, {a_round} rows a round", flush=True)
     tern = synth.ternary(int(rng.integers(1 << 20)), rows, cols, p0)
     if i % 3 == 0:
         tern[::3] = synth.ternary(5, len(tern[::3]), cols, 0.4)
@@ -143,6 +144,7 @@ def encode(rng, i, bad):
     if bad == 1:
         tern[rows // 2, cols // 3] = 5
     m = Memory(i % 2)
+    q.qmoe_hook_set("encode_rows", a_round)
     at, at_off, status = m.new(2 * room, 2), m.new(4 * (rows + 1)), m.new(8)
     assert L.qmoe_encode_device(D, m.put(tern), rows, cols, at, room, at_off, status, None) == 0
     status = read(status, 2, np.int32).tolist()

@@ -75,6 +75,33 @@ def test_device_encoder_equals_the_oracle_stream(oracle_dict, rows, cols, p0):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("rows,cols,p0,a_round", [(700, 4100, 0.92, 64), (513, 770, 0.3, 1), (5000, 258, 0.9, 2048), (65, 62, 0.9, 64)])
+def test_device_encoder_in_rounds(oracle_dict, rows, cols, p0, a_round):
+    """The rows in several rounds of the encoder's kernels, as matrices of 2^31 values and more are taken: offsets go on where the round
+    before ended, and an error of an early round stays."""
+    dd = dev.DeviceDict(q.qmoe_dict_from_words(oracle_dict.words))
+    tern = synth.ternary(rows + cols, rows, cols, p0)
+    codes_ref, off_ref = oracle.encode(oracle_dict, tern)
+    q.qmoe_hook_set("encode_rows", a_round)
+    try:
+        for _ in range(2):
+            codes, off, status = _on_device(dd, tern, codes_ref.size + 8)
+            assert status == [0, 0]
+            _check((codes[:codes_ref.size], off), (codes_ref, off_ref))
+            assert (codes[codes_ref.size:] == 0xFFFF).all()
+        assert _on_device(dd, tern, codes_ref.size - 1)[2] == [-2, 0]  # BUFFER_TOO_SMALL in the last round
+        assert _on_device(dd, tern, 10)[2] == [-2, 0]                  # ... and in the first
+        tern[1, cols // 3] = 5
+        assert _on_device(dd, tern, codes_ref.size)[2] == [-3, 1]      # BAD_SYMBOL
+        assert _on_device(dd, tern, 10)[2] == [-3, 1]
+        tern[1, cols // 3], tern[rows - 1, cols // 3] = 0, 5
+        assert _on_device(dd, tern, tern.size)[2] == [-3, rows - 1]
+    finally:
+        q.qmoe_hook_set("encode_rows", 0)
+    dd.close()
+
+
+@pytest.mark.gpu
 def test_device_encoder_with_missing_phrases():
     od = _small_dictionary()
     dd = dev.DeviceDict(q.qmoe_dict_from_words(od.words))
