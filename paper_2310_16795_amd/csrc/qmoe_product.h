@@ -181,10 +181,13 @@ __device__ __forceinline__ void consume8(const ProductArgs &a, LaneState<TBI, AS
     // The gathers bound this loop: 64 lanes that read at random take 7.1 cycles of the CU's LDS, and
     // lanes that read one and the same word share an access.  Field 0 is the last that an entry of
     // the device order fills, so most codewords carry no weight there: those lanes all read one zero
-    // (the empty slot of column 0's record; in tiles the zeroed column past the last).  c2048, 2048 tokens, both
-    // products: 921 -> 845 us.  The same for field 1, which more codewords use, costs its two
-    // instructions and gains nothing (1.068x against 1.076x for field 0 alone); in k_rows, which
-    // waits for latency and not for the LDS, it loses 1 to 6 %.
+    // (the empty slot of column 0's record; in tiles the zeroed column past the last).  c2048, 2048
+    // tokens, both products: 921 -> 845 us.  (Interchange numbering fills field 0 first: 256 tokens on
+    // 256 experts of 2080 x 6144, asymmetric grid, 1166 us with the shared zero, 1087 without.)  The
+    // same for field 1, which more codewords use, costs its two instructions and gains nothing (1.068x
+    // against 1.076x for field 0 alone); in k_rows, which waits for latency and not for the LDS, it
+    // loses 1 to 6 %.
+    constexpr bool kShared = DICT == kDictOrder || DICT == kDictOrderL2;
     if constexpr (TBI == 1) {
         uint32_t x[24];
 #pragma unroll
@@ -193,7 +196,7 @@ __device__ __forceinline__ void consume8(const ProductArgs &a, LaneState<TBI, AS
 #pragma unroll
             for (int z = 0; z < 3; z++) {
                 const uint32_t f = (e[j].e0 >> (8 + 8 * z)) & 0xFFu;
-                x[3 * j + z] = (uint32_t)(*(lp_u16)(uintptr_t)(z == 0 && f == 0u ? 0u : rec + f));
+                x[3 * j + z] = (uint32_t)(*(lp_u16)(uintptr_t)(kShared && z == 0 && f == 0u ? 0u : rec + f));
             }
         }
 #pragma unroll
@@ -205,7 +208,7 @@ __device__ __forceinline__ void consume8(const ProductArgs &a, LaneState<TBI, AS
     } else {
 #pragma unroll
         for (int j = 0; j < 8; j++) {
-            if constexpr (DICT != kDictWords) accumulate_tile<TBI, ASYM, true>(e[j].e0, xs_addr, pos[j], st.acc, cols8);
+            if constexpr (DICT != kDictWords) accumulate_tile<TBI, ASYM, kShared>(e[j].e0, xs_addr, pos[j], st.acc, cols8);
             else accumulate<TBI, DICT, ASYM>(e[j], xs_addr, pos[j], st.acc);
 #pragma unroll
             for (int t = 0; t < NA; t++) part[j][t] = st.acc[t];

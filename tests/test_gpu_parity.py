@@ -137,7 +137,8 @@ def test_unused_fields_read_no_live_activation(gpu, ddict, oracle_dict, batch, c
 
 
 # Tiles of up to four, two, eight tokens and of one; the table in LDS, in L2 (-1), its head in LDS.  (Interchange numbering: an
-# entry's weights begin with the first field, and tiles multiply the column by the zero weights of the others.)
+# entry's weights begin with the first field; one token's unused fields read the empty slot of their run's first record, tiles multiply
+# the column by zero weights.)
 @pytest.mark.parametrize("order,tile,table", [(1, 0, 0), (1, 2, 0), (1, 8, 0), (1, 0, -1), (1, 1, 0), (0, 1, 0), (0, 1, 8192)])
 @pytest.mark.parametrize("minmax", [False, True])
 def test_shared_zero_of_unused_first_fields(gpu, ddict, oracle_dict, minmax, order, tile, table):
