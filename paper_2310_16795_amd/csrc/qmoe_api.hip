@@ -764,7 +764,7 @@ qmoe_status qmoe_moe_dispatch(const qmoe_dict *d, int code_order, const int32_t 
         return st;
     if ((st = plan_mm(d, code_order, d_model, d_ff, n_tokens, true, &mp)) != QMOE_OK) return st;
     return launch_dispatch(dispatch_args(expert_idx, n_tokens, n_experts, d_model, layer_ptrs(workspace, l), pwi.tb_max,
-                                                pwo.tb_max, mp.min_tokens, nullptr), static_cast<hipStream_t>(stream));
+                                         pwo.tb_max, mp.min_tokens, nullptr), static_cast<hipStream_t>(stream));
 }
 
 namespace {
@@ -1018,7 +1018,7 @@ qmoe_status qmoe_bf16_layer_forward(const uint16_t *const *wi_dense, const uint1
     const int phases = tuning().phases > 0 ? tuning().phases : 7;
     if (phases & 1)
         if ((st = launch_dispatch(dispatch_args(expert_idx, n_tokens, n_experts, d_model, lp, pwi.tb_max, pwo.tb_max,
-                                                       0x7FFFFFFF, y), s)) != QMOE_OK)
+                                                0x7FFFFFFF, y), s)) != QMOE_OK)
             return st;
     DenseArgs a{};
     a.n_experts = n_experts;

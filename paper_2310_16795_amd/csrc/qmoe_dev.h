@@ -513,7 +513,8 @@ __device__ __forceinline__ uint32_t order_entry(TablePtr table, uint32_t code, u
 // the index is the median of the two candidates and the last entry: the larger of the
 // two for every code the table knows; for a code it does not know, the last entry or the
 // smaller candidate (at most code >> 2 < 16384, inside the space reserved for the table in
-// the device blob; in LDS, at worst other bytes of the workgroup's own allocation).
+// the device blob; in LDS, where only a table of fewer entries than that can be left behind,
+// other bytes of the workgroup's allocation or, past its end, the zero that such a read gives).
 template <typename TablePtr>
 __device__ __forceinline__ void order_entry2(TablePtr table, uint32_t w, uint32_t n_groups3, uint32_t last,
                                              uint32_t &e_lo, uint32_t &e_hi)

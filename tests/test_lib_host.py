@@ -336,7 +336,7 @@ def test_shares_of_the_rows_cover_each_row_once(groups):
     """Every share begins at a row of its first item, ends where the next one begins, and together they are all rows of all items;
     rows that no eight divides, items from one to several a workgroup, in mixed classes."""
     rng = np.random.default_rng(groups)
-    mixes = [(0, 0, 26), (0, 0, 44), (0, 17, 18), (0, 26, 0), (1, 0, 0), (0, 0, 1), (0, 0, 256), (256, 0, 0), (3, 30, 479)]
+    mixes = [(0, 0, 26), (0, 0, 44), (0, 17, 18), (0, 26, 0), (1, 0, 0), (0, 0, 1), (0, 0, 256), (256, 0, 0), (3, 30, 479), (20001, 30000, 50002)]
     mixes += [tuple(int(v) for v in rng.integers(0, hi, 3)) for hi in (4, 30, 100, 300) for _ in range(6)]
     for rows in (1, 7, 8, 9, 346, 354, 358, 386, 394, 396, 452, 468, 530, 730, 768, 1003, 2080, 6144):
         for mix in mixes:
