@@ -716,11 +716,14 @@ __device__ __forceinline__ void x_store(const XPairs<PIECES> &p, unsigned char *
             o.z = v & 0xFFFF0000u;
             o.w = o.z ^ 0x80000000u;
         } else {
-            const uint32_t fourth = ntok > 3 ? p.v[k][3] : 0u;
             o.x = __builtin_amdgcn_perm(p.v[k][1], p.v[k][0], 0x05040100u);
-            o.y = __builtin_amdgcn_perm(fourth, p.v[k][2], 0x05040100u);
+            o.y = __builtin_amdgcn_perm(p.v[k][3], p.v[k][2], 0x05040100u);
             o.z = __builtin_amdgcn_perm(p.v[k][1], p.v[k][0], 0x07060302u);
-            o.w = __builtin_amdgcn_perm(fourth, p.v[k][2], 0x07060302u);
+            o.w = __builtin_amdgcn_perm(p.v[k][3], p.v[k][2], 0x07060302u);
+            if (ntok == 3) {
+                o.y &= 0xFFFFu;
+                o.w &= 0xFFFFu;
+            }
         }
         if (c < cols) *reinterpret_cast<u32x4 *>(xs + 8 * (size_t)c) = o;
     }
