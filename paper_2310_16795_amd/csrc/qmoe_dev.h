@@ -418,6 +418,28 @@ __device__ __forceinline__ void stage_x_tile(uint16_t *xs_w, const uint16_t *xba
     }
 }
 
+// The descriptor of an expert's matrix, in scalar registers (nothing writes it during the launch; `expert` the same in every
+// lane): as a vector load it was waited for together with the table and the activations.
+__device__ __forceinline__ qmoe_matrix matrix_of(const ProductArgs &a, int expert)
+{
+    typedef const __attribute__((address_space(4))) qmoe_matrix *cp_matrix;
+    if (!a.mats) return a.single;
+    qmoe_matrix m;
+    cp_matrix p = (cp_matrix)(uintptr_t)(a.mats + expert);
+    m.codes = p->codes;
+    m.row_off = p->row_off;
+    m.scale_f16 = p->scale_f16;
+    m.rows = p->rows;
+    m.cols = p->cols;
+    m.n_codes = p->n_codes;
+    m.code_order = p->code_order;
+    m.minmax_bf16 = p->minmax_bf16;
+    m.wave_off = p->wave_off;
+    m.lanes = p->lanes;
+    m.reserved = 0u;
+    return m;
+}
+
 // Entry of a device-order code from the group/single table (see qmoe_internal.h):
 // codes below 4 * n_groups share table[code >> 2], the rest are single entries at
 // table[code - 3 * n_groups]; the index is the larger of the two expressions (the

@@ -11,287 +11,391 @@ namespace {
 // in hand: y[token][row] = sum_k x[token][k] * W[row][k].  The scalar kernel
 // would decode the matrix again for every few tokens; this one decodes it once per
 // tile of up to 64 tokens.  A wavefront owns 64 rows (one lane per row) and walks
-// the columns 64 at a time.  Every lane keeps a ring of 128 one-byte columns of its
-// row in LDS and decodes its codewords into it sequentially, as far ahead as the
+// the columns 64 at a time.  Every lane keeps a ring of 256 columns of its
+// row in LDS, four bits a column, and decodes its codewords into it, as far ahead as the
 // ring allows (so the lanes of a wavefront, whose codewords end at different
 // columns, seldom wait for each other); then the wavefront multiplies the 64
 // columns that are complete, for the 64 rows its lanes decoded, with the tokens'
 // activations on the matrix cores, fp32 accumulators in registers.  The
-// ring holds the weights as the high byte of bf16 +-2.0 (0x40 / 0xC0, low byte
-// zero), expanded to bf16 by a byte permute when a fragment is read; the factor 2
+// ring holds the weights as fp4 numbers (+-2.0), which one instruction widens to bf16, two at a time; the factor 2
 // is taken out again, exactly, when a row is written.
 // Only device-order streams (whole table in LDS) take this path.
 //
-// What bounds it: nothing alone.  Of a wavefront's step 48 % goes by in the decoder's rounds (about 4.5 of them, 270 cycles
-// each, with 24 vector instructions and about 35 cycles of the LDS that eight wavefronts share), 30 % in the multiply (a quarter of
-// that waiting for activations), the rest at the window, the set-up and the results (rows of 2080 and 6144 columns, sparsities mixed); the
-// LDS holds two wavefronts per SIMD (ring, window and table), too few to hide each other's waits altogether.  A step's activations are loaded
-// straight into the registers the product reads, a codeword piece only by the lanes that need one (asking again for what is there
-// costs a line per lane).  (Activations asked for a step ahead: 1164 us instead of 1000 where the wait for the window's piece then
-// waits for them too, 1013 where it is moved behind the multiply.)
-// (Slower, measured: two lanes per row with rings of 256 columns, two codewords a round, a ring stored by columns and read
-// transposed, codewords four by four in the window.)
+// What bounds it: the length of a step on a wavefront, of which the LDS holds two per SIMD (rings, windows and table); they do
+// not hide each other's waits altogether.  256 experts of 2080 x 6144 with 16 tokens each, first / second product, 394 / 348 us
+// when this was measured: without the rounds 318 / 242, without the multiply 355 / 291, without rounds, multiply and stream loads
+// 209 / 113, one step a unit 121 / 67; all rows of a wavefront the same (one line a load) and without the rounds 266 / 216.
+// Vector units issue on 58 % of the cycles (142 instructions a step), the LDS works 45 %.
+//
+// (Four codewords a round and four bits a column: with one codeword a round and a byte a column, three byte stores a codeword and the
+// ring cleared by stores, the same layer took 449 / 420 us with the units handed out by tickets, 430 / 361 this way; rows of mixed sparsity
+// 498 / 475 and 493 / 435; on the asymmetric grid 495 / 469 and 480 / 419.  Slower or no different, measured: the trips to memory of the
+// next unit during the present one, 905 -> 930 us for 256 experts with 1 to 32 tokens; the activations of 64-token tiles a step ahead, 765 -> 785.)
 
 constexpr int kMmKc = 64;                      // columns per step
-constexpr int kMmRing = 2 * kMmKc;             // columns a lane's ring holds
-constexpr int kMmAhead = kMmRing - 28 - 1;     // a codeword may start this far past the step's first column (its run then ends
-                                               // below column kc + 128, the first one that shares a ring byte with the step)
-constexpr int kMmWRowBytes = kMmRing + 16;     // 36 banks per row: 16 consecutive rows read 16 bytes each (two lanes, 8 bytes apiece) without conflict
+constexpr int kMmRing = 256;                   // columns a lane's ring holds
+constexpr int kMmGroup = 4;                    // codewords a lane decodes in a round
+constexpr int kMmAhead = kMmRing - 28 * kMmGroup;  // a round may start this far past the step's first column (its runs then end
+                                                   // below the first column that shares a place in the ring with the step)
+constexpr int kMmRowBytes = kMmRing / 2;       // four bits a column
+constexpr int kMmWindow = 16;                  // codewords of a lane's window: two pieces of eight
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-// eight ring bytes (high bytes of bf16) -> eight bf16
-__device__ __forceinline__ bf16x8 mm_expand(uint32_t d0, uint32_t d1)
+// eight columns of four bits (0x4: +2, 0xC: -2 as an fp4 number) -> eight bf16
+__device__ __forceinline__ bf16x8 mm_expand(uint32_t d)
 {
-    u32x4 o;
-    o.x = __builtin_amdgcn_perm(0u, d0, 0x010c000cu);
-    o.y = __builtin_amdgcn_perm(0u, d0, 0x030c020cu);
-    o.z = __builtin_amdgcn_perm(0u, d1, 0x010c000cu);
-    o.w = __builtin_amdgcn_perm(0u, d1, 0x030c020cu);
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    bf16x2 o[4];
+    o[0] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(d, 1.0f, 0);
+    o[1] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(d, 1.0f, 1);
+    o[2] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(d, 1.0f, 2);
+    o[3] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(d, 1.0f, 3);
     bf16x8 r;
-    __builtin_memcpy(&r, &o, 16);
+    __builtin_memcpy(&r, o, 16);
     return r;
 }
 
-__device__ __forceinline__ bf16x8 mm_expand_minmax(uint32_t d0, uint32_t d1, uint32_t hi, uint32_t lo)
+// The same on the asymmetric grid: byte selectors (0: zero, 2: w_max, 6: w_min) of the even and of the odd columns pick the
+// row's own bf16 grid points out of lo = w_max << 16, hi = w_min << 16 (see select_minmax).
+__device__ __forceinline__ bf16x8 mm_expand_minmax(uint32_t d, uint32_t hi, uint32_t lo)
 {
-    const u32x4 o = select_minmax(d0, d1, hi, lo);
+    const uint32_t even = (d >> 1) & 0x06060606u, odd = (d >> 5) & 0x06060606u;
+    u32x4 o;
+    o.x = __builtin_amdgcn_perm(hi, lo, __builtin_amdgcn_perm(odd, even, 0x04040000u) + 0x01000100u);
+    o.y = __builtin_amdgcn_perm(hi, lo, __builtin_amdgcn_perm(odd, even, 0x05050101u) + 0x01000100u);
+    o.z = __builtin_amdgcn_perm(hi, lo, __builtin_amdgcn_perm(odd, even, 0x06060202u) + 0x01000100u);
+    o.w = __builtin_amdgcn_perm(hi, lo, __builtin_amdgcn_perm(odd, even, 0x07070303u) + 0x01000100u);
     bf16x8 r;
     __builtin_memcpy(&r, &o, 16);
     return r;
 }
 
 using lw_u8 = __attribute__((address_space(3))) unsigned char *;
+using lw_u32 = __attribute__((address_space(3))) uint32_t *;
 using lw_u64 = __attribute__((address_space(3))) unsigned long long *;
 using lw_u32x4 = __attribute__((address_space(3))) u32x4 *;
 using lp_u64 = const __attribute__((address_space(3))) unsigned long long *;
-using lp_u32x4 = const __attribute__((address_space(3))) u32x4 *;
-using lp_i32 = const __attribute__((address_space(3))) int *;
-using lp_f32 = const __attribute__((address_space(3))) float *;
 
 // ---- the ring decoder ----
 //
-// One lane = one row.  A lane's codewords pass through a window of two 16-byte pieces (sixteen
-// codewords) in LDS, the next piece is in flight in a register; the codeword two places ahead
-// is read from the window and the table entry one place ahead is looked up while the current
-// entry is applied.  Applying an entry is three one-byte stores into the lane's ring of 128
-// columns: field z goes to ring column (column + position) mod 128 with the value bits of the
-// field shifted to the top of the byte (0x40: +2.0, 0xC0: -2.0 as the high byte of bf16) or, for
-// the asymmetric grid, as they are (byte selectors 2 / 6); an unused field (0) comes first and
-// writes its zero at the run's first column before any real weight of the same run.
+// One lane = one row.  A lane's codewords pass through a window of two 16-byte pieces (four groups of four codewords) in LDS.
+// A round takes one group: four table entries are looked up side by side and their
+// fields put into the lane's ring by ORs (a field without a weight ORs zero), which cost the LDS what stores of a byte do.  A step's operand read
+// takes the weights out by exchanges with zero, so that nothing is cleared.
 //
-// (A struct of plain scalars and free functions that are always inlined: the state stays in
-// registers.)
-constexpr uint32_t kMmWinAhead = 2 * 15;  // the window holds 16 codewords (32 bytes), and a round reads two ahead of the one it applies
-constexpr int kMmWinBytes = 32;   // a lane's window: two 16-byte pieces, on 32 bytes
+// The LDS begins with the table (at address 0; launch_product_mm sees to that), then the rings, then the windows.  A ring is 32 words
+// of eight columns; the rings of eight rows lie word by word, [8 rows][32 words][row of the eight], so that a place -- four times a column, plus
+// a constant -- has the word's address in its upper bits as it stands and the shift inside the word in its lower five.
+__host__ __device__ inline size_t mm_table_bytes(int n_order) { return ((size_t)n_order * 4 + 2047) & ~(size_t)2047; }
+constexpr size_t kMmWindowBytes = 2 * kMmWindow;  // a lane's
+constexpr uint32_t kMmWord = 0x3E0;               // bits of a place that are the word's address
+static_assert(kMmRing == 256 && kMmRowBytes == 128, "32 words of eight columns, 32 bytes from one to the next");
 
-// The table comes first in the LDS, at address 0 (launch_product_mm sees to that), and what follows it begins on 32 bytes: a window's
-// address takes the place in it by an OR.
-static_assert(kMmWinBytes == 32 && kMmThreads * kMmWRowBytes % kMmWinBytes == 0, "windows on their own size: ring_rounds and ring_code_at keep bits 1..4");
-static_assert(kMmRing == 1 << 7, "ring_rounds takes seven bits of a column");
-__host__ __device__ inline size_t mm_table_bytes(int n_order) { return ((size_t)n_order * 4 + 31) & ~(size_t)31; }
+// The rings of rows 8 .. 15 of 16 begin four words on: the 16 rows x 4 words of an operand read fall on 64 banks.
+__device__ __forceinline__ uint32_t ring_begin(uint32_t row) { return 128u * ((row >> 3) & 1u); }
+
+// The table in LDS has its entries' bytes in another order than the one in memory, each halved: field 1, field 0, field 2,
+// length.  A byte is 4 * position | weight as two signed bits; what the two low bits of a code flip, the signs of fields 1 and
+// 2, is then bits 1 and 17, and one product of the code's low byte puts both there (its other bits are left to the mask).
+__device__ __forceinline__ uint32_t ring_entry_bytes(uint32_t e)
+{
+    return (__builtin_amdgcn_perm(e, e, 0x00030102u) >> 1) & 0x7F7F7F7Fu;
+}
+constexpr uint32_t kMmFlipMul = 0x00010002u, kMmFlips = 0x00020002u, kMmPlaces = 0x7C7C7C7Cu, kMmWeights = 0x03030303u;
 
 struct RingDecoder {
-    // (bytes into the lane's codewords, counted from its first piece)
-    uint32_t ci;                // one past the next codeword
-    uint32_t end;               // one past the row's last codeword's end
-    uint32_t lim;               // the lane may go on while ci < lim: codewords are left, and the window reaches one past them
-    uint32_t wbase;             // first codeword of the window's first piece (a multiple of 16)
-    uint32_t pos8;              // 8 * (column where the next run starts)
-    uint32_t ent, flips, code;  // the pipeline: entry of the next codeword as read, the sign flips of its code, code of the one after
-    uintptr_t pp, last, pstr;   // first piece of the window, the lane's last piece, bytes from a piece to the next
-    u32x4 fut;                  // the piece after the window, in flight
-    uint32_t wrow, slot;        // LDS byte addresses of the lane's ring and window
+    // (codewords counted from the first of the row's first piece)
+    uint32_t ci;               // the next group's first codeword
+    uint32_t n, n4;            // one past the row's last codeword; that down to whole groups
+    uint32_t have, asked;      // one past the last codeword in the window, and past the last one asked for
+    uint32_t pos;              // place of the column where the next run starts
+    uintptr_t next;            // the next piece to ask for
+    uint32_t pstr;             // bytes from a piece to the next
+    uint32_t wrow, slot;       // LDS byte addresses of the lane's ring and window
 };
 
-__device__ __forceinline__ u32x4 ring_piece_at(const RingDecoder &d, uintptr_t at)
+// A piece on its way to the window.
+struct RingPiece {
+    u32x4 v;
+    bool live;
+};
+
+// Asks for a lane's next piece where the window has room for it.  All lanes load, those that ask for nothing the matrix's first
+// piece: what is in flight at any point of the program is then known to the compiler, whose waits for the activations would
+// otherwise be waits for the stream too.
+__device__ __forceinline__ void ring_ask(RingDecoder &d, const void *codes, RingPiece &p)
 {
-    // pieces past the lane's last one re-read the last (never used: `end` comes first)
-    return *(gp_u32x4)(at < d.last ? at : d.last);
+    p.live = (int)(d.asked - d.ci) <= kMmWindow / 2 && d.asked < d.n;  // (at first ci may be ahead, in the middle of the first piece)
+    p.v = *(gp_u32x4)(p.live ? d.next : reinterpret_cast<uintptr_t>(codes));
+    d.next += p.live ? d.pstr : 0u;
+    d.asked += p.live ? 8u : 0u;
 }
 
-__device__ __forceinline__ void ring_store_piece(const RingDecoder &d, uint32_t half_bytes, const u32x4 &v)
+// The window is kept by groups, [group][lane]: a wavefront's reads do not meet in a bank.
+__device__ __forceinline__ void ring_arrive(RingDecoder &d, RingPiece &p)
 {
-    lw_u64 w = (lw_u64)(uintptr_t)(d.slot + half_bytes);
-    w[0] = (unsigned long long)v.x | ((unsigned long long)v.y << 32);
-    w[1] = (unsigned long long)v.z | ((unsigned long long)v.w << 32);
+    asm volatile("" ::"v"(p.v));  // (the wait belongs here, whether a lane asked or not)
+    if (p.live) {
+        lw_u64 w = (lw_u64)(uintptr_t)(((d.have << 7) & 1024u) | d.slot);
+        w[0] = (unsigned long long)p.v.x | ((unsigned long long)p.v.y << 32);
+        w[64] = (unsigned long long)p.v.z | ((unsigned long long)p.v.w << 32);
+        d.have += 8u;
+    }
+    p.live = false;
 }
 
-__device__ __forceinline__ uint32_t ring_code_at(const RingDecoder &d, uint32_t at)
+__device__ __forceinline__ uint32_t byte_of(uint32_t v, int k) { return (v >> (8 * k)) & 0xFFu; }
+
+struct RingTable {
+    uint32_t groups3, last;  // 3 * groups and the last entry's index, twice each, side by side
+};
+
+__device__ __forceinline__ unsigned long long ring_codes_at(const RingDecoder &d, uint32_t at)
 {
-    return (uint32_t)(*(lp_u16)(uintptr_t)(d.slot + (at & 30u)));
+    return *(lp_u64)(uintptr_t)(((at << 7) & 0x600u) | d.slot);
 }
 
-// LDS byte offset of a code's table entry: the index that order_entry2 takes, times four.  (Signed, so that the second candidate
-// needs no saturation: below the crossing it is the smaller one, and the median with the last entry is then the first.)
-__device__ __forceinline__ uint32_t ring_entry_at(uint32_t code, int minus_groups12, int last4)
+// LDS byte offsets of two codewords' table entries: the index that order_entry2 takes, times four.
+__device__ __forceinline__ void ring_entries_at(const RingTable &tab, uint32_t w, uint32_t &at0, uint32_t &at1)
 {
-    int at;
-    asm("v_med3_i32 %0, %1, %2, %3" : "=v"(at) : "v"(code & ~3u), "v"((int)(code << 2) + minus_groups12), "s"(last4));
-    return (uint32_t)at;
+    typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+    u16x2 c, g, l;
+    __builtin_memcpy(&c, &w, 4);
+    __builtin_memcpy(&g, &tab.groups3, 4);
+    __builtin_memcpy(&l, &tab.last, 4);
+    const u16x2 two = {2, 2};
+    const u16x2 i = __builtin_elementwise_min(__builtin_elementwise_max(c >> two, __builtin_elementwise_sub_sat(c, g)), l);
+    uint32_t both;
+    __builtin_memcpy(&both, &i, 4);
+    asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0" : "=v"(at0) : "s"(2), "v"(both));
+    asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1" : "=v"(at1) : "s"(2), "v"(both));
 }
 
-// The table in LDS has its entries' bytes in another order than the one in memory: field 1, field 0, field 2, length.  What the two
-// low bits of a code flip, the signs of fields 1 and 2, is then bits 2 and 18, and one product of the code's low byte
-// puts both there (its other bits are left to the caller's mask).
-__device__ __forceinline__ uint32_t ring_entry_bytes(uint32_t e) { return __builtin_amdgcn_perm(e, e, 0x00030102u); }
-constexpr uint32_t kMmFlips = 0x00040004u;
+// A group: its codewords and their entries as read.
+struct RingGroup {
+    uint32_t w[2], e[kMmGroup];
+};
 
-__device__ __forceinline__ uint32_t ring_flips(uint32_t code)
+__device__ __forceinline__ RingGroup ring_look_up(const RingTable &tab, unsigned long long four)
 {
-    uint32_t f;
-    asm("v_mul_u32_u24_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_0 src1_sel:DWORD"
-        : "=v"(f) : "v"(code), "s"(0x00020004u));
-    return f;
+    RingGroup g;
+    uint32_t at[kMmGroup];
+#pragma unroll
+    for (int h = 0; h < 2; h++) {
+        g.w[h] = (uint32_t)(four >> (32 * h));
+        ring_entries_at(tab, g.w[h], at[2 * h], at[2 * h + 1]);
+    }
+#pragma unroll
+    for (int j = 0; j < kMmGroup; j++) g.e[j] = *(lp_u32)(uintptr_t)at[j];
+    return g;
 }
 
-// The lane's row (none: an empty stream), its window filled, its ring cleared.
-__device__ __forceinline__ void ring_setup(RingDecoder &d, const qmoe_matrix &M, int row, bool row_live, uint32_t wrow,
-                                           uint32_t slot)
+// A group at one of the row's ends: of its codewords only those from `from` on and below n are the row's.
+__device__ __forceinline__ void ring_apply_part(RingDecoder &d, const RingGroup &g, uint32_t from)
+{
+#pragma unroll
+    for (int j = 0; j < kMmGroup; j++) {
+        const uint32_t k = d.ci + (uint32_t)j, flips = ((g.w[j >> 1] >> (16 * (j & 1))) & 0xFFu) * kMmFlipMul;
+        const bool own = k >= from && k < d.n;
+        const uint32_t places = own ? g.e[j] & kMmPlaces : 0u, weights = own ? (g.e[j] & kMmWeights) ^ (flips & kMmFlips) : 0u;
+#pragma unroll
+        for (int z = 0; z < 3; z++) {
+            const uint32_t t = d.pos + byte_of(places, z);
+            __hip_atomic_fetch_or((lw_u32)(uintptr_t)((t & kMmWord) | d.wrow), byte_of(weights, z) << (t & 31u), __ATOMIC_RELAXED,
+                                  __HIP_MEMORY_SCOPE_WAVEFRONT);
+        }
+        d.pos += places >> 24;
+    }
+    d.ci += kMmGroup;
+}
+
+// Rounds of one whole group per lane, until no lane of the wavefront that may go on (ci < stop) is before `end`.  A lane
+// that sits out -- no group left in the window, or too far ahead (pos > lim) -- does so for the rest of the call.  `g`: the
+// lanes' first groups.
+//
+// A group's codewords are read before the group ahead of it is applied, and looked up only if there is another round.  In assembly
+// because lanes leave by the execution mask, which only shrinks: the compiler keeps old and new state of every lane apart
+// and moves it back and forth (a round is 20 vector instructions a codeword here).
+__device__ __forceinline__ void ring_rounds(RingDecoder &d, const RingTable &tab, RingGroup g, uint32_t stop, uint32_t lim, uint32_t end)
+{
+    uint32_t f, wt, pl, t0, t1, t2, a0, a1, a2;
+    uint32_t n0, n1;
+    unsigned long long all;
+    asm volatile(
+                 "s_mov_b64 %[all], exec\n\t"
+                 "v_cmpx_lt_u32_e32 vcc, %[ci], %[stop]\n\t"
+                 "v_cmpx_ge_u32_e32 vcc, %[lim], %[pos]\n\t"
+                 "v_cmp_lt_u32_e32 vcc, %[pos], %[end]\n\t"
+                 "s_cbranch_vccz 1f\n\t"
+                 "0:\n\t"
+                 "v_add_u32_e32 %[ci], 4, %[ci]\n\t"
+                 "v_lshlrev_b32_e32 %[t0], 7, %[ci]\n\t"
+                 "v_and_or_b32 %[t0], %[t0], %[groups], %[slot]\n\t"
+                 "ds_read_b32 %[n0], %[t0]\n\t"
+                 "ds_read_b32 %[n1], %[t0] offset:4\n\t"
+                 "v_mul_u32_u24_sdwa %[f], %[w0], %[mul] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_0 src1_sel:DWORD\n\t"
+                 "v_and_b32_e32 %[wt], %[weights], %[e0]\n\t"
+                 "v_and_b32_e32 %[pl], %[places], %[e0]\n\t"
+                 "v_bitop3_b32 %[wt], %[f], %[wt], %[flips] bitop3:0x6c\n\t"
+                 "v_add_u32_sdwa %[t0], %[pl], %[pos] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_0 src1_sel:DWORD\n\t"
+                 "v_add_u32_sdwa %[t1], %[pl], %[pos] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_1 src1_sel:DWORD\n\t"
+                 "v_add_u32_sdwa %[t2], %[pl], %[pos] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_2 src1_sel:DWORD\n\t"
+                 "v_add_u32_sdwa %[pos], %[pl], %[pos] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_3 src1_sel:DWORD\n\t"
+                 "v_and_or_b32 %[a0], %[t0], %[word], %[ring]\n\t"
+                 "v_and_or_b32 %[a1], %[t1], %[word], %[ring]\n\t"
+                 "v_and_or_b32 %[a2], %[t2], %[word], %[ring]\n\t"
+                 "v_lshlrev_b32_sdwa %[t0], %[t0], %[wt] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_0\n\t"
+                 "v_lshlrev_b32_sdwa %[t1], %[t1], %[wt] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_1\n\t"
+                 "v_lshlrev_b32_sdwa %[t2], %[t2], %[wt] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_2\n\t"
+                 "ds_or_b32 %[a0], %[t0]\n\t"
+                 "ds_or_b32 %[a1], %[t1]\n\t"
+                 "ds_or_b32 %[a2], %[t2]\n\t"
+                 "v_mul_u32_u24_sdwa %[f], %[w0], %[mul] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_2 src1_sel:DWORD\n\t"
+                 "v_and_b32_e32 %[wt], %[weights], %[e1]\n\t"
+                 "v_and_b32_e32 %[pl], %[places], %[e1]\n\t"
+                 "v_bitop3_b32 %[wt], %[f], %[wt], %[flips] bitop3:0x6c\n\t"
+                 "v_add_u32_sdwa %[t0], %[pl], %[pos] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_0 src1_sel:DWORD\n\t"
+                 "v_add_u32_sdwa %[t1], %[pl], %[pos] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_1 src1_sel:DWORD\n\t"
+                 "v_add_u32_sdwa %[t2], %[pl], %[pos] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_2 src1_sel:DWORD\n\t"
+                 "v_add_u32_sdwa %[pos], %[pl], %[pos] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_3 src1_sel:DWORD\n\t"
+                 "v_and_or_b32 %[a0], %[t0], %[word], %[ring]\n\t"
+                 "v_and_or_b32 %[a1], %[t1], %[word], %[ring]\n\t"
+                 "v_and_or_b32 %[a2], %[t2], %[word], %[ring]\n\t"
+                 "v_lshlrev_b32_sdwa %[t0], %[t0], %[wt] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_0\n\t"
+                 "v_lshlrev_b32_sdwa %[t1], %[t1], %[wt] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_1\n\t"
+                 "v_lshlrev_b32_sdwa %[t2], %[t2], %[wt] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_2\n\t"
+                 "ds_or_b32 %[a0], %[t0]\n\t"
+                 "ds_or_b32 %[a1], %[t1]\n\t"
+                 "ds_or_b32 %[a2], %[t2]\n\t"
+                 "v_mul_u32_u24_sdwa %[f], %[w1], %[mul] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_0 src1_sel:DWORD\n\t"
+                 "v_and_b32_e32 %[wt], %[weights], %[e2]\n\t"
+                 "v_and_b32_e32 %[pl], %[places], %[e2]\n\t"
+                 "v_bitop3_b32 %[wt], %[f], %[wt], %[flips] bitop3:0x6c\n\t"
+                 "v_add_u32_sdwa %[t0], %[pl], %[pos] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_0 src1_sel:DWORD\n\t"
+                 "v_add_u32_sdwa %[t1], %[pl], %[pos] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_1 src1_sel:DWORD\n\t"
+                 "v_add_u32_sdwa %[t2], %[pl], %[pos] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_2 src1_sel:DWORD\n\t"
+                 "v_add_u32_sdwa %[pos], %[pl], %[pos] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_3 src1_sel:DWORD\n\t"
+                 "v_and_or_b32 %[a0], %[t0], %[word], %[ring]\n\t"
+                 "v_and_or_b32 %[a1], %[t1], %[word], %[ring]\n\t"
+                 "v_and_or_b32 %[a2], %[t2], %[word], %[ring]\n\t"
+                 "v_lshlrev_b32_sdwa %[t0], %[t0], %[wt] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_0\n\t"
+                 "v_lshlrev_b32_sdwa %[t1], %[t1], %[wt] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_1\n\t"
+                 "v_lshlrev_b32_sdwa %[t2], %[t2], %[wt] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_2\n\t"
+                 "ds_or_b32 %[a0], %[t0]\n\t"
+                 "ds_or_b32 %[a1], %[t1]\n\t"
+                 "ds_or_b32 %[a2], %[t2]\n\t"
+                 "v_mul_u32_u24_sdwa %[f], %[w1], %[mul] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_2 src1_sel:DWORD\n\t"
+                 "v_and_b32_e32 %[wt], %[weights], %[e3]\n\t"
+                 "v_and_b32_e32 %[pl], %[places], %[e3]\n\t"
+                 "v_bitop3_b32 %[wt], %[f], %[wt], %[flips] bitop3:0x6c\n\t"
+                 "v_add_u32_sdwa %[t0], %[pl], %[pos] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_0 src1_sel:DWORD\n\t"
+                 "v_add_u32_sdwa %[t1], %[pl], %[pos] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_1 src1_sel:DWORD\n\t"
+                 "v_add_u32_sdwa %[t2], %[pl], %[pos] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_2 src1_sel:DWORD\n\t"
+                 "v_add_u32_sdwa %[pos], %[pl], %[pos] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_3 src1_sel:DWORD\n\t"
+                 "v_and_or_b32 %[a0], %[t0], %[word], %[ring]\n\t"
+                 "v_and_or_b32 %[a1], %[t1], %[word], %[ring]\n\t"
+                 "v_and_or_b32 %[a2], %[t2], %[word], %[ring]\n\t"
+                 "v_lshlrev_b32_sdwa %[t0], %[t0], %[wt] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_0\n\t"
+                 "v_lshlrev_b32_sdwa %[t1], %[t1], %[wt] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_1\n\t"
+                 "v_lshlrev_b32_sdwa %[t2], %[t2], %[wt] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_2\n\t"
+                 "ds_or_b32 %[a0], %[t0]\n\t"
+                 "ds_or_b32 %[a1], %[t1]\n\t"
+                 "ds_or_b32 %[a2], %[t2]\n\t"
+                 "v_cmpx_lt_u32_e32 vcc, %[ci], %[stop]\n\t"
+                 "v_cmpx_ge_u32_e32 vcc, %[lim], %[pos]\n\t"
+                 "v_cmp_lt_u32_e32 vcc, %[pos], %[end]\n\t"
+                 "s_waitcnt lgkmcnt(12)\n\t"
+                 "s_cbranch_vccz 1f\n\t"
+                 "v_mov_b32_e32 %[w0], %[n0]\n\t"
+                 "v_mov_b32_e32 %[w1], %[n1]\n\t"
+                 "v_pk_lshrrev_b16 %[t0], 2, %[n0] op_sel_hi:[0,1]\n\t"
+                 "v_pk_sub_u16 %[t1], %[n0], %[g3] clamp\n\t"
+                 "v_pk_max_u16 %[t0], %[t0], %[t1]\n\t"
+                 "v_pk_min_u16 %[t0], %[t0], %[last]\n\t"
+                 "v_lshlrev_b32_sdwa %[a0], %[two], %[t0] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n\t"
+                 "v_lshlrev_b32_sdwa %[t2], %[two], %[t0] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n\t"
+                 "ds_read_b32 %[e0], %[a0]\n\t"
+                 "ds_read_b32 %[e1], %[t2]\n\t"
+                 "v_pk_lshrrev_b16 %[t0], 2, %[n1] op_sel_hi:[0,1]\n\t"
+                 "v_pk_sub_u16 %[t1], %[n1], %[g3] clamp\n\t"
+                 "v_pk_max_u16 %[t0], %[t0], %[t1]\n\t"
+                 "v_pk_min_u16 %[t0], %[t0], %[last]\n\t"
+                 "v_lshlrev_b32_sdwa %[a1], %[two], %[t0] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n\t"
+                 "v_lshlrev_b32_sdwa %[t2], %[two], %[t0] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n\t"
+                 "ds_read_b32 %[e2], %[a1]\n\t"
+                 "ds_read_b32 %[e3], %[t2]\n\t"
+                 "s_waitcnt lgkmcnt(0)\n\t"
+                 "s_branch 0b\n\t"
+                 "1:\n\t"
+                 "s_mov_b64 exec, %[all]\n\t"
+                 : [ci] "+v"(d.ci), [pos] "+v"(d.pos), [w0] "+v"(g.w[0]), [w1] "+v"(g.w[1]), [e0] "+v"(g.e[0]), [e1] "+v"(g.e[1]),
+                   [e2] "+v"(g.e[2]), [e3] "+v"(g.e[3]), [f] "=&v"(f), [wt] "=&v"(wt), [pl] "=&v"(pl), [t0] "=&v"(t0), [t1] "=&v"(t1),
+                   [t2] "=&v"(t2), [a0] "=&v"(a0), [a1] "=&v"(a1), [a2] "=&v"(a2), [n0] "=&v"(n0), [n1] "=&v"(n1), [all] "=&s"(all)
+                 : [stop] "v"(stop), [lim] "v"(lim), [end] "v"(end), [slot] "v"(d.slot), [ring] "v"(d.wrow), [groups] "s"(0x600u),
+                   [mul] "s"(kMmFlipMul), [flips] "s"(kMmFlips), [weights] "s"(kMmWeights), [places] "s"(kMmPlaces), [word] "s"(kMmWord),
+                   [g3] "s"(tab.groups3), [last] "s"(tab.last), [two] "s"(2)
+                 : "vcc", "memory");
+}
+
+// The lane's row (none: an empty stream), its window filled, its ring cleared, its first group decoded.
+__device__ __forceinline__ void ring_setup(RingDecoder &d, const RingTable &tab, const qmoe_matrix &M, int row, bool row_live, uint32_t lane,
+                                           uint32_t rings, uint32_t slot)
 {
     const RowStream rst = row_stream(M, row, row_live);
-    d.end = 2u * (rst.sub + rst.left) + 2u;
-    d.lim = min(d.end, kMmWinAhead);
-    d.pp = rst.pp;
-    d.last = rst.last;
-    d.pstr = rst.pstride;
-    d.ci = 2u * rst.sub + 2u;
-    d.wrow = wrow;
+    // (the row's pieces end with rst.last, which offsets that are none do not move behind the stream)
+    const uint32_t pieces = (uint32_t)((rst.last - rst.pp) >> (M.lanes ? 10 : 4)) + 1u;
+    d.n = rst.left ? min(rst.sub + rst.left, 8u * pieces) : rst.sub;
+    d.n4 = d.n & ~(uint32_t)(kMmGroup - 1);
+    d.ci = rst.sub & ~(uint32_t)(kMmGroup - 1);
+    d.next = rst.pp;
+    d.pstr = (uint32_t)rst.pstride;
+    d.wrow = rings + 1024u * (lane >> 3) + 4u * (lane & 7u);
     d.slot = slot;
-    {
-        const u32x4 p0 = ring_piece_at(d, d.pp), p1 = ring_piece_at(d, d.pp + d.pstr);
-        ring_store_piece(d, 0u, p0);
-        ring_store_piece(d, 16u, p1);
-    }
-    d.fut = ring_piece_at(d, d.pp + 2u * d.pstr);
-    d.wbase = 0;
-    d.pos8 = 0;
+    d.have = d.asked = 0u;
+    RingPiece p0, p1;
+    ring_ask(d, M.codes, p0);
+    ring_ask(d, M.codes, p1);
+    ring_arrive(d, p0);
+    ring_arrive(d, p1);
+    d.pos = ring_begin(lane) + 2u;
 #pragma unroll
-    for (int i = 0; i < kMmRing / 8; i++) ((lw_u64)(uintptr_t)wrow)[i] = 0ull;
-}
-
-// Fill the pipeline.  Nothing is in flight afterwards, so that the wait at the top of a round is
-// for the two reads of the round before and not for the three stores issued after them.
-__device__ __forceinline__ void ring_prime(RingDecoder &d, int minus_groups12, int last4)
-{
+    for (int i = 0; i < kMmRowBytes / 16; i++) ((lw_u32x4)(uintptr_t)rings)[64 * i + (int)lane] = u32x4{0u, 0u, 0u, 0u};
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    const uint32_t c0 = ring_code_at(d, d.ci - 2u);
-    d.code = ring_code_at(d, d.ci);
-    d.ent = *(lp_u32)(uintptr_t)ring_entry_at(c0, minus_groups12, last4);
-    d.flips = ring_flips(c0);
-    asm volatile("" : "+v"(d.ent), "+v"(d.code));
+    __builtin_amdgcn_wave_barrier();
+    if (__any(rst.sub & 3u)) {
+        if (d.ci < d.n) ring_apply_part(d, ring_look_up(tab, ring_codes_at(d, d.ci)), rst.sub);
+    }
 }
 
-// Rounds of one codeword per lane, until no lane of the wavefront that may go on (ci < lim) is before column end8 / 8.  A lane
-// that sits out -- its codewords in the window used up, or too far ahead (pos8 > lim8) -- does so for the rest of the call.
-//
-// The pipeline: a round's two reads, the code two codewords ahead and the entry one ahead, go out before its stores and are
-// used in the next round, the code first (it makes an address, the entry waits behind it).  The LDS works in order, so that
-// lgkmcnt(3) is the wait for them and not for the three stores issued after them.
-//
-// In assembly because lanes leave by the execution mask, which only shrinks: the compiler's loop either selects old
-// or new state for every lane that sat out (four instructions, and the lane's reads and stores are done in vain) or rebuilds the mask by
-// scalar instructions and branches.  24 vector instructions, 5 of the LDS and 3 others; 32, 5 and 4 before: 256 experts of 2080 x 6144
-// with 1-32 tokens each 1071 -> 1001 us, 128 experts of 768 x 3072 with 31 tokens each 224 -> 219 us.  (The same instructions field
-// after field, not side by side: 1016 us.  Fields without a weight kept from storing: 1028 us.)
-template <int ASYM>
-__device__ __forceinline__ void ring_rounds(RingDecoder &d, int minus_groups12, int last4, uint32_t lim8, uint32_t end8)
+// Decode until every lane of the wavefront has passed column kc + 64 (or its row's end).  A lane that is there
+// already keeps going as long as its next group's runs end before the first column that shares a
+// place in the ring with the step, so the lanes of a wavefront, whose codewords end at different columns, seldom wait for each
+// other.  A piece arrives two steps after it was asked for: `older` has
+// arrived and is asked for anew, `newer` is in flight.  `between` runs once, between the step's wait and its load of the stream.
+template <class Between>
+__device__ __forceinline__ void ring_decode_step(RingDecoder &d, const RingTable &tab, uint32_t first, const void *codes, RingPiece &older, RingPiece &newer,
+                                                 Between &&between)
 {
-    uint32_t e, t0, t1, t2, w0, w1, w2;
-    unsigned long long all;
-#define QMOE_ROUNDS(value) \
-    asm volatile("s_mov_b64 %[all], exec\n\t" \
-                 "v_cmpx_lt_u32_e32 vcc, %[ci], %[lim]\n\t" \
-                 "v_cmpx_ge_u32_e32 vcc, %[lim8], %[pos]\n\t" \
-                 "0:\n\t" \
-                 "s_waitcnt lgkmcnt(4)\n\t" \
-                 "v_and_b32_e32 %[t0], -4, %[code]\n\t" \
-                 "v_lshl_add_u32 %[t1], %[code], 2, %[k12]\n\t" \
-                 "v_add_u32_e32 %[ci], 2, %[ci]\n\t" \
-                 "v_med3_i32 %[t0], %[t0], %[t1], %[last4]\n\t" \
-                 "v_and_or_b32 %[t1], %[ci], 30, %[slot]\n\t" \
-                 "s_waitcnt lgkmcnt(3)\n\t" \
-                 "v_bitop3_b32 %[e], %[flips], %[ent], %[mask] bitop3:0x6c\n\t" \
-                 "v_mul_u32_u24_sdwa %[flips], %[code], %[mul] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_0 src1_sel:DWORD\n\t" \
-                 "ds_read_u16 %[code], %[t1]\n\t" \
-                 "ds_read_b32 %[ent], %[t0]\n\t" \
-                 "v_add_u32_sdwa %[t0], %[e], %[pos] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_1 src1_sel:DWORD\n\t" \
-                 "v_add_u32_sdwa %[t1], %[e], %[pos] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_0 src1_sel:DWORD\n\t" \
-                 "v_add_u32_sdwa %[t2], %[e], %[pos] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_2 src1_sel:DWORD\n\t" \
-                 "v_add_u32_sdwa %[pos], %[e], %[pos] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_3 src1_sel:DWORD\n\t" \
-                 "v_bfe_u32 %[w0], %[t0], 3, 7\n\t" \
-                 "v_bfe_u32 %[w1], %[t1], 3, 7\n\t" \
-                 "v_bfe_u32 %[w2], %[t2], 3, 7\n\t" \
-                 value("%[t0]") \
-                 value("%[t1]") \
-                 value("%[t2]") \
-                 "v_add_u32_e32 %[w0], %[w0], %[ring]\n\t" \
-                 "v_add_u32_e32 %[w1], %[w1], %[ring]\n\t" \
-                 "v_add_u32_e32 %[w2], %[w2], %[ring]\n\t" \
-                 "ds_write_b8 %[w0], %[t0]\n\t" \
-                 "ds_write_b8 %[w1], %[t1]\n\t" \
-                 "ds_write_b8 %[w2], %[t2]\n\t" \
-                 "v_cmpx_lt_u32_e32 vcc, %[ci], %[lim]\n\t" \
-                 "v_cmpx_ge_u32_e32 vcc, %[lim8], %[pos]\n\t" \
-                 "v_cmp_gt_u32_e32 vcc, %[end8], %[pos]\n\t" \
-                 "s_cbranch_vccnz 0b\n\t" \
-                 "s_waitcnt lgkmcnt(3)\n\t" \
-                 "s_mov_b64 exec, %[all]\n\t" \
-                 : [ci] "+v"(d.ci), [pos] "+v"(d.pos8), [ent] "+v"(d.ent), [flips] "+v"(d.flips), [code] "+v"(d.code), \
-                   [e] "=&v"(e), [t0] "=&v"(t0), [t1] "=&v"(t1), [t2] "=&v"(t2), [w0] "=&v"(w0), [w1] "=&v"(w1), [w2] "=&v"(w2), \
-                   [all] "=&s"(all) \
-                 : [lim] "v"(d.lim), [ring] "v"(d.wrow), [slot] "v"(d.slot), [lim8] "s"(lim8), [end8] "s"(end8), \
-                   [k12] "s"(minus_groups12), [last4] "s"(last4), [mask] "s"(kMmFlips), [mul] "s"(0x00020004u) \
-                 : "vcc", "memory")
-#define QMOE_AS_IS(t) "v_and_b32_e32 " t ", 6, " t "\n\t"
-#define QMOE_ON_TOP(t) "v_lshlrev_b32_e32 " t ", 5, " t "\n\t"
-    if constexpr (ASYM) QMOE_ROUNDS(QMOE_AS_IS);
-    else QMOE_ROUNDS(QMOE_ON_TOP);
-#undef QMOE_AS_IS
-#undef QMOE_ON_TOP
-#undef QMOE_ROUNDS
-}
-
-// Decode until every lane of the wavefront has passed column kc + 64.  A lane that is there
-// already keeps going as long as its next run starts at most kMmAhead columns past kc (its run
-// then ends below column kc + 128, the first one that shares a ring byte with the step), so
-// the lanes of a wavefront, whose codewords end at different columns, seldom wait for each
-// other.  `after_wait` runs once, right after the step's wait for global memory: the place
-// to issue loads that are wanted when the step has been decoded.
-template <int ASYM, class AfterWait>
-__device__ __forceinline__ void ring_decode_step(RingDecoder &d, int minus_groups12, int last4, int kc,
-                                                 AfterWait &&after_wait)
-{
-    const uint32_t lim8 = 8u * (uint32_t)(kc + kMmAhead), end8 = 8u * (uint32_t)(kc + kMmKc);
-    bool first = true;
-    do {
-        // Slide the window by one piece where its first piece is used up (a third of the lanes in a step, as a
-        // rule), and ask for the next one there.
-        {
-            const bool s8 = d.ci - d.wbase >= 16u;  // (not below the new first piece afterwards, so that the next such test holds)
-            asm volatile("" : "+v"(d.fut));  // (the wait belongs here, ahead of after_wait's loads)
-            if (first) {
-                first = false;
-                after_wait();
-            }
-            if (s8) {
-                ring_store_piece(d, d.wbase & 16u, d.fut);
-                d.wbase += 16u;
-                d.pp += d.pstr;
-                d.fut = ring_piece_at(d, d.pp + 2u * d.pstr);
-            }
-            d.lim = min(d.end, d.wbase + kMmWinAhead);
-        }
-        if (__any(d.ci < d.lim && d.pos8 < end8)) ring_rounds<ASYM>(d, minus_groups12, last4, lim8, end8);
-    } while (__any(d.ci < d.end && d.pos8 < end8));
-}
-
-// The half of the ring that held step c becomes columns kc + 128 .. kc + 191: cleared after
-// the step's reads.
-__device__ __forceinline__ void ring_clear_half(const RingDecoder &d, int c)
-{
-#pragma unroll
-    for (int i = 0; i < kMmKc / 8; i++) ((lw_u64)(uintptr_t)(d.wrow + (uint32_t)((c & 1) * kMmKc)))[i] = 0ull;
+    const uint32_t lim = first + 4u * kMmAhead, end = first + 4u * kMmKc;
+    ring_arrive(d, older);
+    const unsigned long long four = ring_codes_at(d, d.ci);
+    between();
+    const RingGroup g = ring_look_up(tab, four);
+    ring_ask(d, codes, older);
+    ring_rounds(d, tab, g, min(d.n4, d.have), lim, end);
+    if (__any(d.ci < d.n && d.pos < end)) {  // a lane is at its row's last few codewords, or the window is empty: everything that was asked for, and more
+        ring_arrive(d, newer);
+        ring_arrive(d, older);
+        do {
+            RingPiece now;
+            ring_ask(d, codes, now);
+            ring_arrive(d, now);
+            ring_rounds(d, tab, ring_look_up(tab, ring_codes_at(d, d.ci)), min(d.n4, d.have), lim, end);
+            if (d.ci == d.n4 && d.ci < min(d.n, d.have) && d.pos < end)
+                ring_apply_part(d, ring_look_up(tab, ring_codes_at(d, d.ci)), 0u);
+        } while (__any(d.ci < d.n && d.pos < end));
+    }
 }
 
 // ---- the matrix-core product ----
@@ -315,22 +419,21 @@ __device__ __forceinline__ void mm_item(const ProductArgs &a, const qmoe_matrix 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l16 = lane & 15, lg = lane >> 4;
 
-    // The second product writes to the tokens' own rows of the output, scaled by their gates.  Lane t asks
-    // for token t's row and gate now, among the other trips to memory of the set-up (two registers for the
-    // length of the item); the lanes swap them when the results are written.
-    int tok_own = 0;
+    // Lane t asks for token t now, and in the second product, which writes to the tokens' own rows of the output, scaled
+    // by their gates, for its gate, among the other trips to memory of the set-up (two registers for the
+    // length of the item); the lanes swap them when the activations are asked for and when the results are written.
+    const int at_own = slot0 + min(lane, ntok - 1);
+    const int tok_own = a.perm ? ((const __attribute__((address_space(1))) int *)a.perm)[at_own] : at_own;
     float gate_own = 1.0f;
-    if constexpr (EPI == 0) {
-        const int t = min(lane, ntok - 1);
-        tok_own = a.perm ? a.perm[slot0 + t] : slot0 + t;
-    }
 
     // ---- this lane's row (the wavefront's 64 rows are block `rblk` of the matrix) and its codewords
     const int r0 = rblk * 64;
     const int row = r0 + lane;
     const bool row_live = row < a.rows;
     RingDecoder dec;
-    ring_setup(dec, M, row, row_live, wt + (uint32_t)(tid * kMmWRowBytes), win + (uint32_t)(tid * kMmWinBytes));
+    const RingTable tab{(uint32_t)(3 * a.n_groups) * 0x10001u, (uint32_t)(a.n_order - 1) * 0x10001u};
+    const uint32_t rings = wt + (uint32_t)(wave * 64 * kMmRowBytes);
+    ring_setup(dec, tab, M, row, row_live, (uint32_t)lane, rings, win + (uint32_t)(wave * 64 * (int)kMmWindowBytes + lane * 8));
     if constexpr (EPI == 0) gate_own = a.gate ? a.gate[tok_own] : 1.0f;
 
     // ---- this lane's part of the activations: token 16 * mb + l16, columns 8 * lg .. 8 * lg + 7 of every 32
@@ -340,23 +443,19 @@ __device__ __forceinline__ void mm_item(const ProductArgs &a, const qmoe_matrix 
 #pragma unroll
     for (int mb = 0; mb < MB; mb++) {
         const int t = 16 * mb + l16;
-        const bool x_ok = t < ntok;
         xmul2[mb] = 2u;
         // (a lane whose columns do not exist -- fewer than 8 * lg + 8 columns -- reads column 0 and drops it;
-        // a lane without a token reads the block's first token, or row 0)
+        // a lane without a token reads the block's first token, or the tile's last)
         const size_t col0 = x_col ? 8 * (size_t)lg : (size_t)0;
         if (EPI == 0 && a.x_tiled) {
             const int tb = min(16, ntok - 16 * mb);  // tokens in this block (<= 0: no such block)
             const size_t block0 = tb > 0 ? (size_t)(slot0 + 16 * mb) : (size_t)slot0;
-            const size_t j = x_ok ? (size_t)l16 : (size_t)0;
+            const size_t j = t < ntok ? (size_t)l16 : (size_t)0;
             xmul2[mb] = 2u * (uint32_t)__builtin_amdgcn_readfirstlane(max(tb, 1));
             xsrc[mb] = reinterpret_cast<uintptr_t>(a.x) + 2 * (block0 * (size_t)a.ldx + 8 * j) + col0 * (size_t)xmul2[mb];
         } else {
-            size_t xrow = 0;
-            if (x_ok) {
-                const int tok = a.perm ? a.perm[slot0 + t] : slot0 + t;
-                xrow = a.x_by_slot ? (size_t)(slot0 + t) : (size_t)tok;
-            }
+            const int tok = __shfl(tok_own, t, 64);  // (where the tile has no such token, its last one)
+            const size_t xrow = a.x_by_slot ? (size_t)(slot0 + min(t, ntok - 1)) : (size_t)tok;
             xsrc[mb] = reinterpret_cast<uintptr_t>(a.x) + 2 * (xrow * (size_t)a.ldx + col0);
         }
     }
@@ -364,16 +463,26 @@ __device__ __forceinline__ void mm_item(const ProductArgs &a, const qmoe_matrix 
     // Only a last step of fewer than 64 columns looks at its columns: a lane past the last one reads column 8 * lg and
     // drops it.
     const int x_last = x_col ? a.cols - 8 * lg - 8 : 0;  // last column offset this lane may read at
-    u32x4 xa[MB][2];
+    constexpr int kAhead = MB == 4 ? 0 : 1;  // steps the activations are asked for ahead
+    u32x4 xa[kAhead + 1][MB][2];
     uint32_t x_end[MB];  // x_last in bytes
 #pragma unroll
     for (int mb = 0; mb < MB; mb++) x_end[mb] = (uint32_t)x_last * xmul2[mb];
-    auto fetch_x = [&](int k) {
+    auto fetch_x = [&](u32x4 (&to)[MB][2], int k) {
+        if (k + kMmKc <= a.cols) {
 #pragma unroll
-        for (int mb = 0; mb < MB; mb++)
+            for (int mb = 0; mb < MB; mb++) {
+                const uintptr_t at = xsrc[mb] + (uintptr_t)((uint32_t)k * xmul2[mb]);
+                to[mb][0] = *(gp_u32x4)at;
+                to[mb][1] = *(gp_u32x4)(at + 32u * xmul2[mb]);
+            }
+        } else {
 #pragma unroll
-            for (int ks = 0; ks < 2; ks++)
-                xa[mb][ks] = *(gp_u32x4)(xsrc[mb] + (uintptr_t)min((uint32_t)(k + 32 * ks) * xmul2[mb], x_end[mb]));
+            for (int mb = 0; mb < MB; mb++)
+#pragma unroll
+                for (int ks = 0; ks < 2; ks++)
+                    to[mb][ks] = *(gp_u32x4)(xsrc[mb] + (uintptr_t)min((uint32_t)(k + 32 * ks) * xmul2[mb], x_end[mb]));
+        }
     };
 
     f32x4 acc[MB][4];
@@ -382,9 +491,18 @@ __device__ __forceinline__ void mm_item(const ProductArgs &a, const qmoe_matrix 
 #pragma unroll
         for (int nb = 0; nb < 4; nb++) acc[mb][nb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 
-    // asymmetric grid: the grid points of the four rows whose weights this lane feeds to the matrix cores
+    // asymmetric grid, tiles of up to 32 tokens: a second sum under |weight|, the grid points are applied when a row is written; larger ones (no registers for
+    // that): the grid points of the four rows whose weights this lane feeds to the matrix cores
+    constexpr bool kTwoSums = ASYM && MB <= 2;
+    f32x4 acc_abs[kTwoSums ? MB : 1][4];
+    if constexpr (kTwoSums) {
+#pragma unroll
+        for (int mb = 0; mb < MB; mb++)
+#pragma unroll
+            for (int nb = 0; nb < 4; nb++) acc_abs[mb][nb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    }
     uint32_t g_hi[4] = {0u, 0u, 0u, 0u}, g_lo[4] = {0u, 0u, 0u, 0u};
-    if constexpr (ASYM) {
+    if constexpr (ASYM && !kTwoSums) {
 #pragma unroll
         for (int nb = 0; nb < 4; nb++) {
             const int rl = 16 * nb + l16;
@@ -394,37 +512,47 @@ __device__ __forceinline__ void mm_item(const ProductArgs &a, const qmoe_matrix 
             g_lo[nb] = pair & 0xFFFF0000u;
         }
     }
-    const uint32_t wfrag = wt + (uint32_t)((64 * wave + l16) * kMmWRowBytes + 8 * lg);
+    // operand reads: row l16 of a block of 16, word lg (+ 4 for the upper half) of the step's eight
+    const uint32_t wfrag = rings + 1024u * (uint32_t)(l16 >> 3) + 4u * (uint32_t)(l16 & 7);
+    uint32_t word = 32u * (uint32_t)lg + ring_begin((uint32_t)l16), first = ring_begin((uint32_t)lane) + 2u;
     const int nsteps = (a.cols + kMmKc - 1) / kMmKc;
-    const int minus_groups12 = -12 * a.n_groups, last4 = 4 * (a.n_order - 1);
 
-    ring_prime(dec, minus_groups12, last4);
-
-    for (int c = 0; c < nsteps; c++) {
+    RingPiece piece[2];
+#pragma unroll
+    for (int k = 0; k < 2; k++) {
+        piece[k].v = u32x4{0u, 0u, 0u, 0u};
+        piece[k].live = false;
+    }
+    if constexpr (kAhead) fetch_x(xa[0], 0);
+    auto step = [&](auto parity, int c) {
+        constexpr int P = decltype(parity)::value, X = P & kAhead;
         const int kc = c * kMmKc;
         // ---- decode until every lane has passed column kc + 64
-        ring_decode_step<ASYM>(dec, minus_groups12, last4, kc, [&]() { fetch_x(kc); });
+        ring_decode_step(dec, tab, first, M.codes, piece[P], piece[1 - P], [&]() { fetch_x(xa[kAhead ? 1 - P : 0], kc + kAhead * kMmKc); });
+        first += 4u * kMmKc;
         // the rows this wavefront multiplies are the ones its own lanes wrote
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
 
-        // (all of the step's weights are asked for before the first is used: 1000 us, 988 now for 256 experts of 2080 x 6144)
-        unsigned long long wd[2][4];
-        {
-            const uint32_t wf = wfrag + (uint32_t)((c & 1) * kMmKc);
+        // The step's weights are taken out of the rings, which leaves zeros for the columns that come there next.
+        uint32_t wd[2][4];
 #pragma unroll
-            for (int ks = 0; ks < 2; ks++)
+        for (int ks = 0; ks < 2; ks++) {
+            const uint32_t at = ((word + 128u * (uint32_t)ks) & kMmWord) | wfrag;
 #pragma unroll
-                for (int nb = 0; nb < 4; nb++) wd[ks][nb] = *(lp_u64)(uintptr_t)(wf + (uint32_t)(nb * 16 * kMmWRowBytes + 32 * ks));
-            __builtin_amdgcn_sched_barrier(0);
+            for (int nb = 0; nb < 4; nb++)
+                wd[ks][nb] = __hip_atomic_exchange((lw_u32)(uintptr_t)(at + (uint32_t)(nb * 16 * kMmRowBytes)), 0u, __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_WAVEFRONT);
         }
+        word += 4u * kMmKc;
+        __builtin_amdgcn_sched_barrier(0);
 
         if (kc + kMmKc > a.cols) {
             asm volatile("");  // (a branch, not selects in every step)
 #pragma unroll
             for (int mb = 0; mb < MB; mb++)
 #pragma unroll
-                for (int ks = 0; ks < 2; ks++) xa[mb][ks] = x_col && kc + 32 * ks <= x_last ? xa[mb][ks] : u32x4{0u, 0u, 0u, 0u};
+                for (int ks = 0; ks < 2; ks++) xa[X][mb][ks] = x_col && kc + 32 * ks <= x_last ? xa[X][mb][ks] : u32x4{0u, 0u, 0u, 0u};
         }
 
         // ---- multiply step c
@@ -433,24 +561,43 @@ __device__ __forceinline__ void mm_item(const ProductArgs &a, const qmoe_matrix 
             bf16x8 bw[4], ax[MB];
 #pragma unroll
             for (int nb = 0; nb < 4; nb++) {
-                const unsigned long long d = wd[ks][nb];
-                if constexpr (ASYM)
-                    bw[nb] = mm_expand_minmax((uint32_t)d, (uint32_t)(d >> 32), g_hi[nb], g_lo[nb]);
+                if constexpr (ASYM && !kTwoSums)
+                    bw[nb] = mm_expand_minmax(wd[ks][nb], g_hi[nb], g_lo[nb]);
                 else
-                    bw[nb] = mm_expand((uint32_t)d, (uint32_t)(d >> 32));
+                    bw[nb] = mm_expand(wd[ks][nb]);
             }
 #pragma unroll
-            for (int mb = 0; mb < MB; mb++) __builtin_memcpy(&ax[mb], &xa[mb][ks], 16);
+            for (int mb = 0; mb < MB; mb++) __builtin_memcpy(&ax[mb], &xa[X][mb][ks], 16);
 #pragma unroll
             for (int mb = 0; mb < MB; mb++)
 #pragma unroll
                 for (int nb = 0; nb < 4; nb++)
                     acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ax[mb], bw[nb], acc[mb][nb], 0, 0, 0);
+            if constexpr (kTwoSums) {
+#pragma unroll
+                for (int nb = 0; nb < 4; nb++) {
+                    u32x4 m;
+                    __builtin_memcpy(&m, &bw[nb], 16);
+                    m &= 0x7FFF7FFFu;
+                    __builtin_memcpy(&bw[nb], &m, 16);
+                }
+#pragma unroll
+                for (int mb = 0; mb < MB; mb++)
+#pragma unroll
+                    for (int nb = 0; nb < 4; nb++)
+                        acc_abs[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ax[mb], bw[nb], acc_abs[mb][nb], 0, 0, 0);
+            }
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
-        ring_clear_half(dec, c);
-    }
+    };
+    // (two steps a turn, so that what is in flight keeps its registers; an odd number of steps ends with one that has no columns)
+    int c = 0;
+    do {
+        step(std::integral_constant<int, 0>{}, c);
+        step(std::integral_constant<int, 1>{}, c + 1);
+        c += 2;
+    } while (c < nsteps);
 
     // accumulator v of lane l: token 16 * mb + 4 * (l / 16) + v, row 16 * nb + l % 16 of the wavefront's 64
     // (second product: output row and gate of each of the lane's tokens, from the lane that holds them)
@@ -470,15 +617,24 @@ __device__ __forceinline__ void mm_item(const ProductArgs &a, const qmoe_matrix 
     for (int nb = 0; nb < 4; nb++) {
         const int r = r0 + 16 * nb + l16;
         if (r < a.rows) {
-            // symmetric grid: the weights were +-2; asymmetric: they were the grid points themselves
-            const float scale = ASYM ? 1.0f : 0.5f * half_bits_to_float(((gp_u16)M.scale_f16)[r]);
+            // the weights were +-2, or the grid points themselves
+            float scale = 1.0f, mid = 0.0f;
+            if constexpr (kTwoSums) {  // y = (w_max - w_min) / 2 * signed sum + (w_max + w_min) / 2 * sum under |weight|
+                const uint32_t pair = M.minmax_bf16 ? ((gp_u32)M.minmax_bf16)[r] : 0u;  // (no pair array: zeros)
+                const float w_min = __uint_as_float(pair << 16), w_max = __uint_as_float(pair & 0xFFFF0000u);
+                scale = 0.25f * (w_max - w_min);
+                mid = 0.25f * (w_max + w_min);
+            } else if constexpr (!ASYM) {
+                scale = 0.5f * half_bits_to_float(((gp_u16)M.scale_f16)[r]);
+            }
 #pragma unroll
             for (int mb = 0; mb < MB; mb++) {
 #pragma unroll
                 for (int v = 0; v < 4; v++) {
                     const int t = 16 * mb + 4 * lg + v;
                     if (t < ntok) {
-                        const float val = acc[mb][nb][v] * scale;
+                        float val = acc[mb][nb][v] * scale;
+                        if constexpr (kTwoSums) val = fmaf(acc_abs[mb][nb][v], mid, val);
                         if constexpr (EPI == 0) {
                             reinterpret_cast<float *>(a.out)[(size_t)tok_of[mb][v] * a.ld_out + r] = gate_of[mb][v] * val;
                         } else {
@@ -503,8 +659,8 @@ __global__ __launch_bounds__(kMmThreads) void k_product_mm(const ProductArgs a)
     extern __shared__ __align__(16) unsigned char smem[];
     const size_t table_bytes = mm_table_bytes(a.n_order);
     uint32_t *table_w = reinterpret_cast<uint32_t *>(smem);
-    unsigned char *wt = smem + table_bytes;                           // [512][kMmWRowBytes] rings
-    unsigned char *win = wt + (size_t)kMmThreads * kMmWRowBytes;      // [512][kMmWinBytes] codeword windows
+    unsigned char *wt = smem + table_bytes;                           // [512][kMmRowBytes] rings
+    unsigned char *win = wt + (size_t)kMmThreads * kMmRowBytes;       // codeword windows: [wavefront][group][lane][4]
 
     // A unit of work is 64 rows of one (expert, token tile) item, and a wavefront takes it alone: after
     // the table is staged the wavefronts of a workgroup share nothing and meet at no barrier, so one
@@ -521,7 +677,7 @@ __global__ __launch_bounds__(kMmThreads) void k_product_mm(const ProductArgs a)
     // so one that runs half empty keeps the other kernels of a layer call off that compute unit); the
     // single-matrix call, which is after latency, spreads its units over as many compute units as it can.
     if (total <= 0 || (int)blockIdx.x >= (listed ? (total + waves - 1) / waves : total)) return;
-    int *next_base = reinterpret_cast<int *>(win + (size_t)kMmThreads * kMmWinBytes);  // [1], in-step hand-out only
+    int *next_base = reinterpret_cast<int *>(win + (size_t)kMmThreads * kMmWindowBytes);  // [1], in-step hand-out only
     int *tok_sums = next_base + 1;                                                      // [2]
     if (threadIdx.x < 2) tok_sums[threadIdx.x] = 0;
     stage_words(table_w, a.order_table, a.n_order, ring_entry_bytes);
@@ -545,10 +701,17 @@ __global__ __launch_bounds__(kMmThreads) void k_product_mm(const ProductArgs a)
     }
 
     const uint32_t wt_addr = (uint32_t)(uintptr_t)(lw_u8)wt, win_addr = (uint32_t)(uintptr_t)(lw_u8)win;
-    // (round robin over the workgroups first, then over their wavefronts: few units spread over many compute units)
-    int g_static = wave * (int)gridDim.x + (int)blockIdx.x;
+    // Which units: in a layer call seven eighths of them are dealt out, a workgroup's wavefronts taking consecutive ones (of
+    // the same tile, as a rule), and the rest handed out by the device counter.  (A ticket for every unit, and the counter bounds the
+    // kernel: it gives one in 13 ns, whoever asks, and 256 experts of 2080 x 6144 with 16 tokens each have 24576 units in the first
+    // product.  That product 436 -> 394 us; fifteen sixteenths, two thirds: no difference.)
+    // The single-matrix call deals all of them out, round robin over the workgroups first, then over their wavefronts: few units spread
+    // over many compute units.
+    const int all_waves = (int)gridDim.x * waves;
+    const int dealt = listed ? (total - total / 8) / all_waves * all_waves : total;
+    int g_dealt = listed ? (int)blockIdx.x * waves + wave : wave * (int)gridDim.x + (int)blockIdx.x;
     for (;;) {
-        int g = g_static;
+        int g = g_dealt;
         if (in_step) {
             // The wavefronts of a workgroup take eight consecutive units together and start them together:
             // where the activations are not stored by token blocks (the first product of a layer) their
@@ -562,18 +725,24 @@ __global__ __launch_bounds__(kMmThreads) void k_product_mm(const ProductArgs a)
             if (base >= total) break;
             g = base + wave;
             if (g >= total) continue;
-        } else if (listed) {
+        } else if (listed && g >= dealt) {
             int got = 0;
             if (lane == 0) got = atomicAdd(a.work_counter, 1);
-            g = __builtin_amdgcn_readfirstlane(got);
+            g = dealt + __builtin_amdgcn_readfirstlane(got);
+        } else {
+            g_dealt += all_waves;
         }
-        g_static += (int)gridDim.x * waves;
         if (g >= total) break;
         const int idx = g / a.mm_row_blocks;
         const int rblk = g - idx * a.mm_row_blocks;
         Item it;
         if (listed) {
-            it = a.items[idx];
+            // (scalar loads: nothing writes the list during the launch)
+            typedef const __attribute__((address_space(4))) Item *cp_item;
+            cp_item p = (cp_item)(uintptr_t)(a.items + idx);
+            it.expert = p->expert;
+            it.slot0 = p->slot0;
+            it.ntok = p->ntok;
         } else {
             it.expert = 0;
             it.slot0 = idx * kMmTokens;
@@ -582,7 +751,7 @@ __global__ __launch_bounds__(kMmThreads) void k_product_mm(const ProductArgs a)
         const int expert = it.expert, slot0 = it.slot0;
         const int ntok = min(it.ntok, kMmTokens);
         if (expert < 0 || expert >= a.n_experts || ntok < 1) continue;
-        const qmoe_matrix M = a.mats ? a.mats[expert] : a.single;
+        const qmoe_matrix M = matrix_of(a, expert);
         if (ntok <= 16)
             mm_item<1, EPI, ASYM>(a, M, rblk, slot0, ntok, wt_addr, win_addr);
         else if (ntok <= 32)
@@ -596,8 +765,7 @@ __global__ __launch_bounds__(kMmThreads) void k_product_mm(const ProductArgs a)
 
 size_t mm_lds_bytes(int n_order)
 {
-    return mm_table_bytes(n_order) + (size_t)kMmThreads * kMmWRowBytes +
-           (size_t)kMmThreads * kMmWinBytes + 16;
+    return mm_table_bytes(n_order) + (size_t)kMmThreads * (kMmRowBytes + kMmWindowBytes) + 16;
 }
 
 qmoe_status launch_product_mm(ProductArgs a, const MmPlan &mp, hipStream_t s)

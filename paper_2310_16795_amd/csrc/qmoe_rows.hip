@@ -34,28 +34,6 @@ __device__ __forceinline__ void lds_barrier()
 typedef u32x4 u32x4_any __attribute__((aligned(2)));
 using gp_u32x4_any = const __attribute__((address_space(1))) u32x4_any *;
 
-// The descriptor of an expert's matrix, in scalar registers (nothing writes it during the launch; `expert` the same in every
-// lane): as a vector load it was waited for together with the table and the activations.
-__device__ __forceinline__ qmoe_matrix matrix_of(const ProductArgs &a, int expert)
-{
-    typedef const __attribute__((address_space(4))) qmoe_matrix *cp_matrix;
-    if (!a.mats) return a.single;
-    qmoe_matrix m;
-    cp_matrix p = (cp_matrix)(uintptr_t)(a.mats + expert);
-    m.codes = p->codes;
-    m.row_off = p->row_off;
-    m.scale_f16 = p->scale_f16;
-    m.rows = p->rows;
-    m.cols = p->cols;
-    m.n_codes = p->n_codes;
-    m.code_order = p->code_order;
-    m.minmax_bf16 = p->minmax_bf16;
-    m.wave_off = p->wave_off;
-    m.lanes = p->lanes;
-    m.reserved = 0u;
-    return m;
-}
-
 // How the rows of a launch are cut into shares: made by the host.
 struct RowsSplit {
     int rows, x_slots;   // rows of a matrix; token tiles whose activations fit the LDS at once (1 or 2)
