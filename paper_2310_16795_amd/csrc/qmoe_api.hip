@@ -305,7 +305,7 @@ qmoe_status plan_dense(int rows, int cols, long long max_passes_hint, ProductPla
     return QMOE_OK;
 }
 
-qmoe_status plan_mm(const qmoe_dict *d, int code_order, int d_model, int d_ff, int n_tokens, bool x_aligned,
+qmoe_status plan_mm(const qmoe_dict *d, int code_order, int n_experts, int d_model, int d_ff, int n_tokens, bool x_aligned,
                     MmPlan *mp)
 {
     *mp = MmPlan{};
@@ -324,7 +324,15 @@ qmoe_status plan_mm(const qmoe_dict *d, int code_order, int d_model, int d_ff, i
     // unit anyway.  With few tokens in the call (measured: 512 tokens on 128 experts) the
     // scalar kernel finishes every expert in one round and the chain would be the critical path.
     if (tu.mfma_min_tokens == 0 && n_tokens < 4 * di.cus) return QMOE_OK;
-    mp->min_tokens = tu.mfma_min_tokens > 0 ? tu.mfma_min_tokens : kMmMinTokensDefault;
+    // A tile of eight or more tokens is better here anyhow, one of six or seven where most experts are crowded or nearly so (the
+    // few-token kernels need two passes for it).  Layers whose experts have few tokens keep those on the few-token kernels, which
+    // are their long chain, and so do very crowded ones, where only skewed routing has such experts and the crowded are the long chain.
+    // From eight / from six tokens on, us: 256 experts of 2080 x 6144, 1500 tokens 796 / 708, asymmetric grid 877 / 785; 512 of
+    // 1024 x 4096, 4000 tokens 623 / 592; 128 of 1024 x 4096, 1100 tokens 236 / 219; 256 of 2080 x 6144 with 1-32 tokens each
+    // 966 / 926.  Not so: 1500 of 600 x 1600, 4000 tokens 331 / 371; 2048 of 2080 x 6144, 2048 tokens 828 / 836; 128 of 768 x 3072,
+    // 4001 tokens, Zipf 207 / 210.
+    const bool six = n_tokens >= 4LL * n_experts && n_tokens < 24LL * n_experts;
+    mp->min_tokens = tu.mfma_min_tokens > 0 ? tu.mfma_min_tokens : (six ? kMmMinTokensCrowded : kMmMinTokensDefault);
     mp->grid = di.cus;
     mp->smem = mm_lds_bytes(n_order);
     return QMOE_OK;
@@ -762,7 +770,7 @@ qmoe_status qmoe_moe_dispatch(const qmoe_dict *d, int code_order, const int32_t 
                            tuning().blocks_second > 0 ? tuning().blocks_second : spread,
                            (d_model % 8 == 0 && tuning().stage_out >= 0) ? 4 : 0, minmax, lanes_wo)) != QMOE_OK)
         return st;
-    if ((st = plan_mm(d, code_order, d_model, d_ff, n_tokens, true, &mp)) != QMOE_OK) return st;
+    if ((st = plan_mm(d, code_order, n_experts, d_model, d_ff, n_tokens, true, &mp)) != QMOE_OK) return st;
     return launch_dispatch(dispatch_args(expert_idx, n_tokens, n_experts, d_model, layer_ptrs(workspace, l), pwi.tb_max,
                                          pwo.tb_max, mp.min_tokens, nullptr), static_cast<hipStream_t>(stream));
 }
@@ -800,7 +808,7 @@ qmoe_status layer_forward(const qmoe_dict *d, const qmoe_matrix *wi, const qmoe_
                            (d_model % 8 == 0 && tuning().stage_out >= 0) ? 4 : 0, minmax, lanes_wo)) != QMOE_OK)
         return st;
     MmPlan mp;
-    if ((st = plan_mm(d, code_order, d_model, d_ff, n_tokens, reinterpret_cast<uintptr_t>(x_bf16) % 16 == 0, &mp)) != QMOE_OK)
+    if ((st = plan_mm(d, code_order, n_experts, d_model, d_ff, n_tokens, reinterpret_cast<uintptr_t>(x_bf16) % 16 == 0, &mp)) != QMOE_OK)
         return st;
     const bool mm = mp.min_tokens <= n_tokens;  // otherwise no expert can reach the threshold
     hipStream_t s = static_cast<hipStream_t>(stream);
