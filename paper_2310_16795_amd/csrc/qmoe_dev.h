@@ -467,43 +467,36 @@ __device__ __forceinline__ uintptr_t last_piece_of(const qmoe_matrix &M)
     return reinterpret_cast<uintptr_t>(M.codes) + 16u * (uintptr_t)(max(min(M.n_codes, kMaxCodes) >> 3, 1u) - 1u);
 }
 
+// (No branch waits for a load before the next one is asked for: offsets and group of lanes are one trip to memory.)
 __device__ __forceinline__ RowStream row_stream(const qmoe_matrix &M, int row, bool live)
 {
     RowStream r;
-    r.pp = reinterpret_cast<uintptr_t>(M.codes);
-    r.last = r.pp;
-    r.pstride = M.lanes ? 1024u : 16u;
-    r.left = 0u;
-    r.sub = 0u;
-    if (!live) return r;
     gp_u32 row_off = (gp_u32)M.row_off;
+    const int at = live ? row : 0;
+    const uint32_t off1 = row_off[at + 1], off0 = row_off[at];
     const uint32_t cap = min(M.n_codes, kMaxCodes);
-    const uint32_t K1 = min(row_off[row + 1], cap);
-    const uint32_t K0 = min(row_off[row], K1);
-    r.left = K1 - K0;
-    if (r.left == 0u) return r;
-    uint32_t lead;  // bytes from the start of the first piece to the row's first codeword
     if (M.lanes) {
         const int lanes = (int)M.lanes, base = M.rows / lanes, extra = M.rows - base * lanes;
         const int split = extra * (base + 1);  // rows below it belong to lanes that own base + 1 rows
-        int g, ra;
-        if (row < split) {
-            g = row / (base + 1);
-            ra = g * (base + 1);
-        } else {
-            g = extra + (row - split) / max(base, 1);
-            ra = split + (g - extra) * base;
-        }
-        const uint32_t before = K0 - min(row_off[ra], K0);  // the lane's codewords ahead of this row
-        r.pp += 16u * ((uintptr_t)((gp_u32)M.wave_off)[g >> 6] + (uintptr_t)(g & 63) + 64u * (uintptr_t)(before >> 3));
-        lead = 2u * (before & 7u);
+        const int ra0 = at < split ? 0 : split, per = at < split ? base + 1 : max(base, 1);
+        const int own = (int)((uint32_t)(at - ra0) / (uint32_t)per), g = (at < split ? 0 : extra) + own;
+        const uint32_t first = row_off[ra0 + own * per], wave = ((gp_u32)M.wave_off)[g >> 6];
+        const uint32_t K1 = min(off1, cap), K0 = min(off0, K1), before = K0 - min(first, K0);  // the lane's codewords ahead of this row
+        r.left = live ? K1 - K0 : 0u;
+        r.pstride = 1024u;
+        r.pp = reinterpret_cast<uintptr_t>(M.codes);
+        if (r.left) r.pp += 16u * ((uintptr_t)wave + (uintptr_t)(g & 63) + 64u * (uintptr_t)(before >> 3));
+        r.sub = r.left ? before & 7u : 0u;
     } else {
-        const uintptr_t first_byte = r.pp + 2 * (uintptr_t)K0;
-        lead = (uint32_t)(first_byte & 15u);
+        const uint32_t K1 = min(off1, cap), K0 = min(off0, K1);
+        r.left = live ? K1 - K0 : 0u;
+        r.pstride = 16u;
+        const uintptr_t first_byte = reinterpret_cast<uintptr_t>(M.codes) + (r.left ? 2 * (uintptr_t)K0 : (uintptr_t)0);
+        const uint32_t lead = (uint32_t)(first_byte & 15u);
         r.pp = first_byte - lead;
+        r.sub = lead >> 1;
     }
-    r.sub = lead >> 1;
-    r.last = r.pp + r.pstride * (uintptr_t)(((lead + 2u * r.left + 15u) >> 4) - 1u);
+    r.last = r.pp + r.pstride * (uintptr_t)(r.left ? ((2u * (r.sub + r.left) + 15u) >> 4) - 1u : 0u);
     if (M.lanes) {
         const uintptr_t end = last_piece_of(M);
         r.pp = r.pp < end ? r.pp : end;

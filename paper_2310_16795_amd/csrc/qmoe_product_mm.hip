@@ -338,9 +338,11 @@ __device__ __forceinline__ void ring_rounds(RingDecoder &d, const RingTable &tab
                  : "vcc", "memory");
 }
 
-// The lane's row (none: an empty stream), its window filled, its ring cleared, its first group decoded.
+// The lane's row (none: an empty stream), its window filled, its ring cleared, its first group decoded.  `meanwhile` runs when the
+// window's pieces have been asked for: what it asks for is on its way together with them.
+template <class Meanwhile>
 __device__ __forceinline__ void ring_setup(RingDecoder &d, const RingTable &tab, const qmoe_matrix &M, int row, bool row_live, uint32_t lane,
-                                           uint32_t rings, uint32_t slot)
+                                           uint32_t rings, uint32_t slot, Meanwhile &&meanwhile)
 {
     const RowStream rst = row_stream(M, row, row_live);
     // (the row's pieces end with rst.last, which offsets that are none do not move behind the stream)
@@ -356,11 +358,12 @@ __device__ __forceinline__ void ring_setup(RingDecoder &d, const RingTable &tab,
     RingPiece p0, p1;
     ring_ask(d, M.codes, p0);
     ring_ask(d, M.codes, p1);
-    ring_arrive(d, p0);
-    ring_arrive(d, p1);
+    meanwhile();
     d.pos = ring_begin(lane) + 2u;
 #pragma unroll
     for (int i = 0; i < kMmRowBytes / 16; i++) ((lw_u32x4)(uintptr_t)rings)[64 * i + (int)lane] = u32x4{0u, 0u, 0u, 0u};
+    ring_arrive(d, p0);
+    ring_arrive(d, p1);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
     if (__any(rst.sub & 3u)) {
@@ -371,17 +374,12 @@ __device__ __forceinline__ void ring_setup(RingDecoder &d, const RingTable &tab,
 // Decode until every lane of the wavefront has passed column kc + 64 (or its row's end).  A lane that is there
 // already keeps going as long as its next group's runs end before the first column that shares a
 // place in the ring with the step, so the lanes of a wavefront, whose codewords end at different columns, seldom wait for each
-// other.  A piece arrives two steps after it was asked for: `older` has
-// arrived and is asked for anew, `newer` is in flight.  `between` runs once, between the step's wait and its load of the stream.
-template <class Between>
+// other.  `g`: the lanes' first groups, looked up during the multiply of the step before.  A piece arrives at the end of the step after the one it
+// was asked for in: `older` has arrived and is asked for anew, `newer` is in flight.
 __device__ __forceinline__ void ring_decode_step(RingDecoder &d, const RingTable &tab, uint32_t first, const void *codes, RingPiece &older, RingPiece &newer,
-                                                 Between &&between)
+                                                 const RingGroup &g)
 {
     const uint32_t lim = first + 4u * kMmAhead, end = first + 4u * kMmKc;
-    ring_arrive(d, older);
-    const unsigned long long four = ring_codes_at(d, d.ci);
-    between();
-    const RingGroup g = ring_look_up(tab, four);
     ring_ask(d, codes, older);
     ring_rounds(d, tab, g, min(d.n4, d.have), lim, end);
     if (__any(d.ci < d.n && d.pos < end)) {  // a lane is at its row's last few codewords, or the window is empty: everything that was asked for, and more
@@ -433,13 +431,13 @@ __device__ __forceinline__ void mm_item(const ProductArgs &a, const qmoe_matrix 
     RingDecoder dec;
     const RingTable tab{(uint32_t)(3 * a.n_groups) * 0x10001u, (uint32_t)(a.n_order - 1) * 0x10001u};
     const uint32_t rings = wt + (uint32_t)(wave * 64 * kMmRowBytes);
-    ring_setup(dec, tab, M, row, row_live, (uint32_t)lane, rings, win + (uint32_t)(wave * 64 * (int)kMmWindowBytes + lane * 8));
-    if constexpr (EPI == 0) gate_own = a.gate ? a.gate[tok_own] : 1.0f;
-
     // ---- this lane's part of the activations: token 16 * mb + l16, columns 8 * lg .. 8 * lg + 7 of every 32
     uintptr_t xsrc[MB];
     uint32_t xmul2[MB];  // bytes from one column's value to the next column's: 2, or (tiled) 2 * the block's tokens
     const bool x_col = 8 * lg + 8 <= a.cols;
+    const int x_last = x_col ? a.cols - 8 * lg - 8 : 0;  // last column offset this lane may read at
+    uint32_t x_end[MB];  // x_last in bytes
+    auto address_x = [&]() {
 #pragma unroll
     for (int mb = 0; mb < MB; mb++) {
         const int t = 16 * mb + l16;
@@ -458,16 +456,14 @@ __device__ __forceinline__ void mm_item(const ProductArgs &a, const qmoe_matrix 
             const size_t xrow = a.x_by_slot ? (size_t)(slot0 + min(t, ntok - 1)) : (size_t)tok;
             xsrc[mb] = reinterpret_cast<uintptr_t>(a.x) + 2 * (xrow * (size_t)a.ldx + col0);
         }
+        x_end[mb] = (uint32_t)x_last * xmul2[mb];
     }
+    };
     // A step's activations are asked for before its weights are decoded and arrive meanwhile.  What a lane without a token brings is some other row's and multiplies into a result nobody writes.
     // Only a last step of fewer than 64 columns looks at its columns: a lane past the last one reads column 8 * lg and
     // drops it.
-    const int x_last = x_col ? a.cols - 8 * lg - 8 : 0;  // last column offset this lane may read at
     constexpr int kAhead = MB == 4 ? 0 : 1;  // steps the activations are asked for ahead
     u32x4 xa[kAhead + 1][MB][2];
-    uint32_t x_end[MB];  // x_last in bytes
-#pragma unroll
-    for (int mb = 0; mb < MB; mb++) x_end[mb] = (uint32_t)x_last * xmul2[mb];
     auto fetch_x = [&](u32x4 (&to)[MB][2], int k) {
         if (k + kMmKc <= a.cols) {
 #pragma unroll
@@ -484,6 +480,11 @@ __device__ __forceinline__ void mm_item(const ProductArgs &a, const qmoe_matrix 
                     to[mb][ks] = *(gp_u32x4)(xsrc[mb] + (uintptr_t)min((uint32_t)(k + 32 * ks) * xmul2[mb], x_end[mb]));
         }
     };
+    ring_setup(dec, tab, M, row, row_live, (uint32_t)lane, rings, win + (uint32_t)(wave * 64 * (int)kMmWindowBytes + lane * 8), [&]() {
+        address_x();
+        if constexpr (kAhead) fetch_x(xa[0], 0);
+        if constexpr (EPI == 0) gate_own = a.gate ? a.gate[tok_own] : 1.0f;
+    });
 
     f32x4 acc[MB][4];
 #pragma unroll
@@ -523,12 +524,13 @@ __device__ __forceinline__ void mm_item(const ProductArgs &a, const qmoe_matrix 
         piece[k].v = u32x4{0u, 0u, 0u, 0u};
         piece[k].live = false;
     }
-    if constexpr (kAhead) fetch_x(xa[0], 0);
+    RingGroup group = ring_look_up(tab, ring_codes_at(dec, dec.ci));
     auto step = [&](auto parity, int c) {
         constexpr int P = decltype(parity)::value, X = P & kAhead;
         const int kc = c * kMmKc;
         // ---- decode until every lane has passed column kc + 64
-        ring_decode_step(dec, tab, first, M.codes, piece[P], piece[1 - P], [&]() { fetch_x(xa[kAhead ? 1 - P : 0], kc + kAhead * kMmKc); });
+        fetch_x(xa[kAhead ? 1 - P : 0], kc + kAhead * kMmKc);
+        ring_decode_step(dec, tab, first, M.codes, piece[P], piece[1 - P], group);
         first += 4u * kMmKc;
         // the rows this wavefront multiplies are the ones its own lanes wrote
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -545,6 +547,9 @@ __device__ __forceinline__ void mm_item(const ProductArgs &a, const qmoe_matrix 
                                                    __HIP_MEMORY_SCOPE_WAVEFRONT);
         }
         word += 4u * kMmKc;
+        // the next step's first groups, under this step's multiply
+        ring_arrive(dec, piece[1 - P]);
+        const unsigned long long four = ring_codes_at(dec, dec.ci);
         __builtin_amdgcn_sched_barrier(0);
 
         if (kc + kMmKc > a.cols) {
@@ -586,6 +591,10 @@ __device__ __forceinline__ void mm_item(const ProductArgs &a, const qmoe_matrix 
 #pragma unroll
                     for (int nb = 0; nb < 4; nb++)
                         acc_abs[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ax[mb], bw[nb], acc_abs[mb][nb], 0, 0, 0);
+            }
+            if (ks == 0) {
+                group = ring_look_up(tab, four);
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
