@@ -228,7 +228,8 @@ def qmoe_encode_host(d: int, tern: np.ndarray):
     codes = np.empty(max(cap, 1), dtype=np.uint16)
     _check(lib().qmoe_encode_host(d, _host_ptr(t), rows, cols, _host_ptr(codes), cap, _host_ptr(row_off),
                                   byref(n)), "qmoe_encode_host")
-    return codes[: n.value].copy(), row_off
+    codes.resize(n.value, refcheck=False)  # (in place: no second array to fault in and copy to)
+    return codes, row_off
 
 
 def qmoe_validate_host(d: int, codes: np.ndarray, row_off: np.ndarray, rows: int, cols: int) -> None:

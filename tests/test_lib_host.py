@@ -106,6 +106,31 @@ def test_encoder_thread_count_does_not_change_the_stream(lib_dict):
     assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
 
 
+@pytest.mark.parametrize("rows,threads", [(1, 1), (3, 5), (64, 2), (65, 2), (257, 5), (1023, 16), (4099, 3)])
+def test_encoder_pieces(lib_dict, rows, threads):
+    """The pieces that the threads take: the stream is one thread's, the error is that of the matrix's first bad row, a
+    buffer that is too small is left alone."""
+    t = synth.ternary(209, rows, 66, 0.85)
+    L, n = q.lib(), ctypes.c_size_t(0)
+    try:
+        q.qmoe_set_tuning("host_threads", 1)
+        codes, row_off = q.qmoe_encode_host(lib_dict, t)
+        q.qmoe_set_tuning("host_threads", threads)
+        again = q.qmoe_encode_host(lib_dict, t)
+        assert np.array_equal(again[0], codes) and np.array_equal(again[1], row_off)
+        assert again[0].flags["OWNDATA"] and again[0].dtype == np.uint16
+        out, ro = np.full(codes.size, 7, dtype=np.uint16), np.zeros(rows + 1, dtype=np.uint32)
+        call = lambda m, cap: L.qmoe_encode_host(lib_dict, m.ctypes.data, rows, 66, out.ctypes.data, cap,  # noqa: E731
+                                                 ro.ctypes.data, ctypes.byref(n))
+        assert call(t, codes.size - 1) == -2 and n.value == codes.size and (out == 7).all()
+        assert call(t, codes.size) == 0 and np.array_equal(out, codes)
+        bad = t.copy()
+        bad[rows // 2, 13] = bad[rows - 1, 0] = 2
+        assert call(bad, codes.size) == -3
+    finally:
+        q.qmoe_set_tuning("host_threads", 0)
+
+
 def test_encoder_with_small_dictionaries_equals_oracle():
     for p0, mp, n in ((0.6, 2, 20), (0.5, 3, 500)):
         d = q.qmoe_dict_create(p0, mp, n)
