@@ -107,42 +107,50 @@ constexpr uint32_t kMmFlipMul = 0x00010002u, kMmFlips = 0x00020002u, kMmPlaces =
 struct RingDecoder {
     // (codewords counted from the first of the row's first piece)
     uint32_t ci;               // the next group's first codeword
-    uint32_t n, n4;            // one past the row's last codeword; that down to whole groups
+    uint32_t n;                // one past the row's last group.  What follows the row's last codeword in that group is somebody else's: its
+                               // runs lie behind the row's last column, where the activations are zeros
     uint32_t have, asked;      // one past the last codeword in the window, and past the last one asked for
     uint32_t pos;              // place of the column where the next run starts
-    uintptr_t next;            // the next piece to ask for
-    uint32_t pstr;             // bytes from a piece to the next
+    uintptr_t first;           // the row's first piece
+    uint32_t step_log2;        // codeword -> bytes from the first piece: 1, or 7 where a lane's pieces lie 1024 bytes apart
     uint32_t wrow, slot;       // LDS byte addresses of the lane's ring and window
 };
 
 // A piece on its way to the window.
 struct RingPiece {
     u32x4 v;
-    bool live;
+    uint32_t at;  // its first codeword (kMmNoPiece: the lane asked for none)
 };
+constexpr uint32_t kMmNoPiece = ~0u;
 
-// Asks for a lane's next piece where the window has room for it.  All lanes load, those that ask for nothing the matrix's first
+// Asks for a lane's next piece where the window has room for it, or will have when the lane has used one more group, which it
+// nearly always has by the time that the piece arrives.  (Asked for only when there is room, a piece is late for rows with a codeword
+// for every 20 values or fewer: one step in eight of such a wavefront waited for it, and so for all that was in flight; one
+// in a hundred now.)  All lanes load, those that ask for nothing the matrix's first
 // piece: what is in flight at any point of the program is then known to the compiler, whose waits for the activations would
 // otherwise be waits for the stream too.
 __device__ __forceinline__ void ring_ask(RingDecoder &d, const void *codes, RingPiece &p)
 {
-    p.live = (int)(d.asked - d.ci) <= kMmWindow / 2 && d.asked < d.n;  // (at first ci may be ahead, in the middle of the first piece)
-    p.v = *(gp_u32x4)(p.live ? d.next : reinterpret_cast<uintptr_t>(codes));
-    d.next += p.live ? d.pstr : 0u;
-    d.asked += p.live ? 8u : 0u;
+    const bool ask = (int)(d.asked - d.ci) <= kMmWindow / 2 + kMmGroup && d.asked < d.n;  // (at first ci may be ahead, in the middle of the first piece)
+    p.v = *(gp_u32x4)(ask ? d.first + ((uintptr_t)(d.asked << d.step_log2)) : reinterpret_cast<uintptr_t>(codes));
+    p.at = ask ? d.asked : kMmNoPiece;
+    d.asked += ask ? 8u : 0u;
 }
 
-// The window is kept by groups, [group][lane]: a wavefront's reads do not meet in a bank.
+// The window is kept by groups, [group][lane]: a wavefront's reads do not meet in a bank.  A piece that comes too early is
+// dropped, and so is the one behind it, and asked for again.
 __device__ __forceinline__ void ring_arrive(RingDecoder &d, RingPiece &p)
 {
     asm volatile("" ::"v"(p.v));  // (the wait belongs here, whether a lane asked or not)
-    if (p.live) {
+    const bool next = p.at == d.have, room = (int)(d.have - d.ci) <= kMmWindow / 2;
+    d.asked = next && !room ? d.have : d.asked;
+    if (next && room) {
         lw_u64 w = (lw_u64)(uintptr_t)(((d.have << 7) & 1024u) | d.slot);
         w[0] = (unsigned long long)p.v.x | ((unsigned long long)p.v.y << 32);
         w[64] = (unsigned long long)p.v.z | ((unsigned long long)p.v.w << 32);
         d.have += 8u;
     }
-    p.live = false;
+    p.at = kMmNoPiece;
 }
 
 __device__ __forceinline__ uint32_t byte_of(uint32_t v, int k) { return (v >> (8 * k)) & 0xFFu; }
@@ -191,13 +199,13 @@ __device__ __forceinline__ RingGroup ring_look_up(const RingTable &tab, unsigned
     return g;
 }
 
-// A group at one of the row's ends: of its codewords only those from `from` on and below n are the row's.
+// A row's first group: of its codewords only those from `from` on are the row's.
 __device__ __forceinline__ void ring_apply_part(RingDecoder &d, const RingGroup &g, uint32_t from)
 {
 #pragma unroll
     for (int j = 0; j < kMmGroup; j++) {
         const uint32_t k = d.ci + (uint32_t)j, flips = ((g.w[j >> 1] >> (16 * (j & 1))) & 0xFFu) * kMmFlipMul;
-        const bool own = k >= from && k < d.n;
+        const bool own = k >= from;
         const uint32_t places = own ? g.e[j] & kMmPlaces : 0u, weights = own ? (g.e[j] & kMmWeights) ^ (flips & kMmFlips) : 0u;
 #pragma unroll
         for (int z = 0; z < 3; z++) {
@@ -347,11 +355,12 @@ __device__ __forceinline__ void ring_setup(RingDecoder &d, const RingTable &tab,
     const RowStream rst = row_stream(M, row, row_live);
     // (the row's pieces end with rst.last, which offsets that are none do not move behind the stream)
     const uint32_t pieces = (uint32_t)((rst.last - rst.pp) >> (M.lanes ? 10 : 4)) + 1u;
-    d.n = rst.left ? min(rst.sub + rst.left, 8u * pieces) : rst.sub;
-    d.n4 = d.n & ~(uint32_t)(kMmGroup - 1);
+    // (2^24: no row has as many, and a place in the stream counts its bytes in 32 bits)
+    const uint32_t n = rst.left ? min(min(rst.sub + rst.left, 8u * pieces), 1u << 24) : 0u;
+    d.n = (n + kMmGroup - 1) & ~(uint32_t)(kMmGroup - 1);
     d.ci = rst.sub & ~(uint32_t)(kMmGroup - 1);
-    d.next = rst.pp;
-    d.pstr = (uint32_t)rst.pstride;
+    d.first = rst.pp;
+    d.step_log2 = M.lanes ? 7u : 1u;
     d.wrow = rings + 1024u * (lane >> 3) + 4u * (lane & 7u);
     d.slot = slot;
     d.have = d.asked = 0u;
@@ -381,17 +390,15 @@ __device__ __forceinline__ void ring_decode_step(RingDecoder &d, const RingTable
 {
     const uint32_t lim = first + 4u * kMmAhead, end = first + 4u * kMmKc;
     ring_ask(d, codes, older);
-    ring_rounds(d, tab, g, min(d.n4, d.have), lim, end);
-    if (__any(d.ci < d.n && d.pos < end)) {  // a lane is at its row's last few codewords, or the window is empty: everything that was asked for, and more
+    ring_rounds(d, tab, g, min(d.n, d.have), lim, end);
+    if (__any(d.ci < d.n && d.pos < end)) {  // a lane's window is empty: everything that was asked for, and more
         ring_arrive(d, newer);
         ring_arrive(d, older);
         do {
             RingPiece now;
             ring_ask(d, codes, now);
             ring_arrive(d, now);
-            ring_rounds(d, tab, ring_look_up(tab, ring_codes_at(d, d.ci)), min(d.n4, d.have), lim, end);
-            if (d.ci == d.n4 && d.ci < min(d.n, d.have) && d.pos < end)
-                ring_apply_part(d, ring_look_up(tab, ring_codes_at(d, d.ci)), 0u);
+            ring_rounds(d, tab, ring_look_up(tab, ring_codes_at(d, d.ci)), min(d.n, d.have), lim, end);
         } while (__any(d.ci < d.n && d.pos < end));
     }
 }
@@ -522,7 +529,7 @@ __device__ __forceinline__ void mm_item(const ProductArgs &a, const qmoe_matrix 
 #pragma unroll
     for (int k = 0; k < 2; k++) {
         piece[k].v = u32x4{0u, 0u, 0u, 0u};
-        piece[k].live = false;
+        piece[k].at = kMmNoPiece;
     }
     RingGroup group = ring_look_up(tab, ring_codes_at(dec, dec.ci));
     auto step = [&](auto parity, int c) {
@@ -558,6 +565,12 @@ __device__ __forceinline__ void mm_item(const ProductArgs &a, const qmoe_matrix 
             for (int mb = 0; mb < MB; mb++)
 #pragma unroll
                 for (int ks = 0; ks < 2; ks++) xa[X][mb][ks] = x_col && kc + 32 * ks <= x_last ? xa[X][mb][ks] : u32x4{0u, 0u, 0u, 0u};
+            if constexpr (ASYM && !kTwoSums) {  // (a grid point may be infinite)
+#pragma unroll
+                for (int ks = 0; ks < 2; ks++)
+#pragma unroll
+                    for (int nb = 0; nb < 4; nb++) wd[ks][nb] = x_col && kc + 32 * ks <= x_last ? wd[ks][nb] : 0u;
+            }
         }
 
         // ---- multiply step c

@@ -37,3 +37,60 @@ def test_partial_steps_and_tiles(oracle_dict, cols, minmax):
     finally:
         q.qmoe_set_tuning("mfma_min_tokens", 0)
         dd.close()
+
+
+def _matvec(oracle_dict, tern, scale, mm, batches):
+    """The matrix-core kernel's result for every batch, with its activations."""
+    gpu, (rows, cols) = "cuda:0", tern.shape
+    codes, row_off = oracle.encode(oracle_dict, tern)
+    dd = dev.DeviceDict(q.qmoe_dict_from_words(oracle_dict.words), gpu)
+    M = dev.DeviceMatrix(codes, row_off, scale, rows, cols, device=gpu, device_order_of=dd, minmax_bf16=mm)
+    q.qmoe_set_tuning("mfma_min_tokens", 1)
+    try:
+        for batch in batches:
+            x = synth.normal_bf16(66 + batch, (batch, cols))
+            y = torch.full((batch, rows), float("nan"), dtype=torch.float32, device=gpu)
+            q.qmoe_decode_matvec(dd.handle, M.desc, torch.from_numpy(x.view(np.int16).copy()).to(gpu), y)
+            torch.cuda.synchronize()
+            yield batch, x, y.cpu().numpy().astype(np.float64)
+    finally:
+        q.qmoe_set_tuning("mfma_min_tokens", 0)
+        dd.close()
+
+
+@pytest.mark.parametrize("cols", [512, 1000, 2080])
+@pytest.mark.parametrize("minmax", [False, True])
+def test_lanes_far_apart(oracle_dict, cols, minmax):
+    """Rows that are dense in one half and nearly empty in the other, next to rows the other way round: lanes that run out of codewords
+    next to lanes that are so far ahead that their next piece comes too early."""
+    rows, half = 130, cols // 2 // 8 * 8
+    dense, thin = synth.ternary(61, rows, cols, 0.2), synth.ternary(62, rows, cols, 0.985)
+    tern = dense.copy()
+    for r in range(rows):
+        if r % 4 == 0:
+            tern[r, :half] = thin[r, :half]
+        elif r % 4 == 1:
+            tern[r, half:] = thin[r, half:]
+        elif r % 4 == 2:
+            tern[r] = thin[r]
+    scale = None if minmax else synth.uniform_f16(63, (rows,), 0.01, 0.1)
+    mm = synth.minmax_bf16(64, rows, 0.01, 0.1) if minmax else None
+    for batch, x, y in _matvec(oracle_dict, tern, scale, mm, (3, 20, 64, 65)):
+        y_ref, bound = oracle.matvec(tern, scale, x, with_bound=True, minmax_bf16=mm)
+        assert (np.abs(y - y_ref) <= 1e-3 * bound + 1e-30).all(), batch
+
+
+@pytest.mark.parametrize("cols", [8, 64, 72, 200])
+def test_unused_grid_point_is_not_read(oracle_dict, cols):
+    """What stands behind a row's last codeword multiplies with zeros: an infinite grid point that the row does not use leaves its
+    result alone (rows of negative weights only, rows of positive ones after them)."""
+    rows = 70
+    tern = -np.abs(synth.ternary(65, rows, cols, 0.6))
+    tern[1::2] *= -1
+    mm = synth.minmax_bf16(66, rows, 0.01, 0.1).copy()
+    ref = mm.copy()
+    mm[0::2, 1], mm[1::2, 0] = 0x7F80, 0xFF80  # w_max, w_min
+    for batch, x, y in _matvec(oracle_dict, tern.astype(np.int8), None, mm, (64, 100)):
+        y_ref, bound = oracle.matvec(tern.astype(np.int8), None, x, with_bound=True, minmax_bf16=ref)
+        big = slice(0, batch // 64 * 64)  # (tiles of more than 32 tokens multiply with the grid points themselves)
+        assert (np.abs(y - y_ref)[big] <= 1e-3 * bound[big] + 1e-30).all(), batch
