@@ -305,6 +305,27 @@ qmoe_status plan_dense(int rows, int cols, long long max_passes_hint, ProductPla
     return QMOE_OK;
 }
 
+// Tokens from which on a call of fewer than four per compute unit has its crowded experts multiplied on the matrix cores.
+//
+// The few-token kernels decode a matrix again for every four tokens: 0.18 us a pass and million weights of a matrix (both
+// products), behind a start of 15 us.  The matrix-core kernel decodes it once for 64, but a tile is walked column step by column step by one
+// wavefront per 64 rows, a chain of 1.1 us a step behind a start of 45, or, where that is more, 0.24 us an expert and million weights; and
+// experts with few tokens, left to the other kernel, come on top (70 us), unless there are hardly any.  Experts of the same size, few
+// tokens / matrix cores, us: 4 of 2080 x 6144, 200 tokens 196 / 195, 400 256 / 175, 1000 563 / 180; 64, 700 tokens 426 / 255; 8 of 1024 x
+// 4096, 700 tokens 154 / 125; 128 of 1024 x 4096, 700 tokens 167 / 205; 4 of 768 x 3072, 700 tokens 101 / 105.  Of 330 calls with 4 experts
+// to 130, 220 tokens to 990, six shapes, uniform and Zipf routing, 80 to 90 % zeros, this takes 112 to the matrix cores, in 0.59 of the
+// time on average and 0.97 at worst.
+// (On one stream: the two chains side by side, on two, were 7 % slower here.)
+int mm_from_tokens(int n_experts, int d_model, int d_ff)
+{
+    const double weights = 1e-6 * d_model * d_ff, steps = (d_model + d_ff) / 64.0;
+    const double chain = std::max(45.0 + 1.1 * steps, 25.0 + 0.24 * n_experts * weights);
+    // passes of four tokens, and for every expert three eighths of one that is not full
+    auto tokens = [&](double us) { return 4.0 * ((1.05 * us - 15.0) / (0.18 * weights) - 0.375 * n_experts); };
+    const double from = std::min(tokens(chain + 70.0), std::max(tokens(chain), 32.0 * n_experts));
+    return (int)std::min(std::max(from, 4.0 * n_experts), 2e9) + 1;
+}
+
 qmoe_status plan_mm(const qmoe_dict *d, int code_order, int n_experts, int d_model, int d_ff, int n_tokens, bool x_aligned,
                     MmPlan *mp)
 {
@@ -319,11 +340,11 @@ qmoe_status plan_mm(const qmoe_dict *d, int code_order, int n_experts, int d_mod
     if (code_order != 1 || n_order == 0 || d->max_nonzeros > kRunMaxNonzeros || !fits || (d_model % 8) ||
         (d_ff % 8) || !x_aligned || tu.mfma_min_tokens < 0)
         return QMOE_OK;
-    // A tile is walked column step by column step by one wavefront per 64 rows: a long chain
-    // that pays only when the scalar kernel would need several rounds of items per compute
-    // unit anyway.  With few tokens in the call (measured: 512 tokens on 128 experts) the
-    // scalar kernel finishes every expert in one round and the chain would be the critical path.
-    if (tu.mfma_min_tokens == 0 && n_tokens < 4 * di.cus) return QMOE_OK;
+    if (tu.mfma_min_tokens == 0 && n_tokens < 4 * di.cus) {
+        mp->from_tokens = mm_from_tokens(n_experts, d_model, d_ff);
+        mp->one_stream = true;
+        if (n_tokens < mp->from_tokens) return QMOE_OK;
+    }
     // A tile of eight or more tokens is better here anyhow, one of six or seven where most experts are crowded or nearly so (the
     // few-token kernels need two passes for it).  Layers whose experts have few tokens keep those on the few-token kernels, which
     // are their long chain, and so do very crowded ones, where only skewed routing has such experts and the crowded are the long chain.
@@ -495,7 +516,7 @@ LayerPtrs layer_ptrs(void *ws, const qmoe_ws_layout &l)
 }
 
 DispatchArgs dispatch_args(const int32_t *expert_idx, int n_tokens, int n_experts, int d_model, const LayerPtrs &lp, int tb_wi,
-                           int tb_wo, int mm_min, float *y)
+                           int tb_wo, const MmPlan &mp, float *y)
 {
     DispatchArgs da;
     da.expert_idx = expert_idx;
@@ -509,7 +530,8 @@ DispatchArgs dispatch_args(const int32_t *expert_idx, int n_tokens, int n_expert
     da.items_mm = lp.items_mm;
     da.tb_wi = tb_wi;
     da.tb_wo = tb_wo;
-    da.mm_min = mm_min;
+    da.mm_min = mp.min_tokens;
+    da.mm_from = mp.from_tokens;
     da.y = y;
     da.d_model = d_model;
     return da;
@@ -772,7 +794,7 @@ qmoe_status qmoe_moe_dispatch(const qmoe_dict *d, int code_order, const int32_t 
         return st;
     if ((st = plan_mm(d, code_order, n_experts, d_model, d_ff, n_tokens, true, &mp)) != QMOE_OK) return st;
     return launch_dispatch(dispatch_args(expert_idx, n_tokens, n_experts, d_model, layer_ptrs(workspace, l), pwi.tb_max,
-                                         pwo.tb_max, mp.min_tokens, nullptr), static_cast<hipStream_t>(stream));
+                                         pwo.tb_max, mp, nullptr), static_cast<hipStream_t>(stream));
 }
 
 namespace {
@@ -822,7 +844,7 @@ qmoe_status layer_forward(const qmoe_dict *d, const qmoe_matrix *wi, const qmoe_
     }
     // In a small call the kernel with several lanes per row groups the tokens itself.
     const bool grouping = rp.on && !mm && rows_can_dispatch(n_experts, n_tokens, rp.grid, n_order, rp.max_lds);
-    const DispatchArgs da = dispatch_args(expert_idx, n_tokens, n_experts, d_model, lp, pwi.tb_max, pwo.tb_max, mp.min_tokens, y);
+    const DispatchArgs da = dispatch_args(expert_idx, n_tokens, n_experts, d_model, lp, pwi.tb_max, pwo.tb_max, mp, y);
     if ((phases & 1) && !grouping)
         if ((st = launch_dispatch(da, s)) != QMOE_OK) return st;
 
@@ -840,7 +862,7 @@ qmoe_status layer_forward(const qmoe_dict *d, const qmoe_matrix *wi, const qmoe_
     // units in proportion to its work was worse than either (measured for shares from 1/4 to 7/8).
     // The host cannot see the routing, so it goes by the average: with four or more tokens per
     // expert most tokens sit in crowded experts.
-    const bool overlap = side && mm && tuning().overlap >= 0 && (phases & 6) && (phases & 24);
+    const bool overlap = side && mm && !mp.one_stream && tuning().overlap >= 0 && (phases & 6) && (phases & 24);
     const bool mm_first = (long long)n_tokens < 4LL * n_experts;
     hipStream_t s_mm = s, s_sc = s;
     SideStream ss;
@@ -1026,7 +1048,7 @@ qmoe_status qmoe_bf16_layer_forward(const uint16_t *const *wi_dense, const uint1
     const int phases = tuning().phases > 0 ? tuning().phases : 7;
     if (phases & 1)
         if ((st = launch_dispatch(dispatch_args(expert_idx, n_tokens, n_experts, d_model, lp, pwi.tb_max, pwo.tb_max,
-                                                0x7FFFFFFF, y), s)) != QMOE_OK)
+                                                MmPlan{}, y), s)) != QMOE_OK)
             return st;
     DenseArgs a{};
     a.n_experts = n_experts;

@@ -77,7 +77,9 @@ __global__ __launch_bounds__(1024) void k_dispatch(const DispatchArgs a)
     const int S = count_stride(E);
     int *cnt = sm;               // [PARTS][S] tokens of the part, later the slot of its next one; expert e at spread(e)
     int *tmp = sm + PARTS * S;   // [17 * 12] scan scratch
+    int *lost = tmp + 17 * 12;   // tokens without an expert
     for (int i = tid; i < PARTS * S; i += nthr) cnt[i] = 0;
+    if (tid == 0) *lost = 0;
     __syncthreads();
     int dropped = 0;
     for (int t0 = tid; t0 < T; t0 += 4 * nthr) {
@@ -92,7 +94,9 @@ __global__ __launch_bounds__(1024) void k_dispatch(const DispatchArgs a)
             else dropped++;
         }
     }
+    if (dropped) atomicAdd(lost, dropped);
     __syncthreads();
+    const int mm_min = T - *lost >= a.mm_from ? a.mm_min : 0x7FFFFFFF;
 
     // each thread owns a contiguous chunk of experts
     const int chunk = (E + nthr - 1) / nthr;
@@ -107,7 +111,7 @@ __global__ __launch_bounds__(1024) void k_dispatch(const DispatchArgs a)
         for (int p = 0; p < PARTS; p++) n += cnt[p * S + spread(e)];
         s_tok += n;
         s_act += n > 0;
-        if (n >= a.mm_min) {
+        if (n >= mm_min) {
             s_mm += (n + kMmTokens - 1) / kMmTokens;
         } else if (n > 0) {
             s_wi[tile_class(a.tb_wi)] += n / a.tb_wi;
@@ -141,7 +145,7 @@ __global__ __launch_bounds__(1024) void k_dispatch(const DispatchArgs a)
             n += here[p];
         }
         a.tok_off[e] = p_tok;
-        if (n >= a.mm_min) {
+        if (n >= mm_min) {
             for (int i = 0; i * kMmTokens < n; i++)
                 a.items_mm[p_mm++] = Item{e, p_tok + i * kMmTokens, min(kMmTokens, n - i * kMmTokens), 0};
         } else {
@@ -211,7 +215,7 @@ template <int PARTS>
 static qmoe_status launch_parts(const DispatchArgs &da, int threads, int max_lds, hipStream_t s)
 {
     // parts: a wavefront each, as many as the tokens fill and the LDS has counts for (two at 16384 experts)
-    const size_t smem = sizeof(int) * ((size_t)PARTS * (size_t)count_stride(da.n_experts) + 17 * 12);
+    const size_t smem = sizeof(int) * ((size_t)PARTS * (size_t)count_stride(da.n_experts) + 17 * 12 + 1);
     if constexpr (PARTS > 1) {
         if (PARTS > threads / 64 || 32 * PARTS >= da.n_tokens || smem > (size_t)max_lds)
             return launch_parts<PARTS / 2>(da, threads, max_lds, s);
