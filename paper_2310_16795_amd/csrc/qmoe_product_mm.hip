@@ -631,7 +631,7 @@ __device__ __forceinline__ void mm_item(const ProductArgs &a, const qmoe_matrix 
     typedef u32x4 u32x4_word __attribute__((aligned(4)));
     typedef __attribute__((address_space(1))) float *gw_f32;
     typedef __attribute__((address_space(1))) uint16_t *gw_u16;
-    float scale[4][4], mid[kTwoSums ? 4 : 1][4];
+    float scale[4][4], scale_neg[kTwoSums ? 4 : 1][4];
 #pragma unroll
     for (int nb = 0; nb < 4; nb++) {
 #pragma unroll
@@ -639,10 +639,9 @@ __device__ __forceinline__ void mm_item(const ProductArgs &a, const qmoe_matrix 
             // the weights were +-2, or the grid points themselves
             uint32_t raw = 0u;
             if constexpr (kTwoSums || !ASYM) raw = (uint32_t)__shfl((int)scale_own, 16 * nb + 4 * lg + v, 64);
-            if constexpr (kTwoSums) {  // y = (w_max - w_min) / 2 * signed sum + (w_max + w_min) / 2 * sum under |weight|
-                const float w_min = __uint_as_float(raw << 16), w_max = __uint_as_float(raw & 0xFFFF0000u);
-                scale[nb][v] = 0.25f * (w_max - w_min);
-                mid[nb][v] = 0.25f * (w_max + w_min);
+            if constexpr (kTwoSums) {
+                scale[nb][v] = 0.25f * __uint_as_float(raw & 0xFFFF0000u);  // w_max
+                scale_neg[nb][v] = 0.25f * __uint_as_float(raw << 16);      // w_min
             } else if constexpr (!ASYM) {
                 scale[nb][v] = 0.5f * half_bits_to_float((uint16_t)raw);
             } else {
@@ -677,8 +676,17 @@ __device__ __forceinline__ void mm_item(const ProductArgs &a, const qmoe_matrix 
                 float val[4];
 #pragma unroll
                 for (int v = 0; v < 4; v++) {
-                    val[v] = acc[mb][nb][v] * scale[nb][v];
-                    if constexpr (kTwoSums) val[v] = fmaf(acc_abs[mb][nb][v], mid[nb][v], val[v]);
+                    if constexpr (kTwoSums) {
+                        // Twice the activations under positive and under negative weights: exactly zero where a row has none of them,
+                        // so that a grid point that it does not use, which may be large or infinite, has no part in it.
+                        // (Half the sum and the difference of the grid points times the two sums: that point's rounding stays in the result.
+                        // A sum of its own for each sign in the matrix cores: 256 experts of 2080 x 6144 with 16 tokens each 880 -> 971 us.)
+                        const float pos = acc_abs[mb][nb][v] + acc[mb][nb][v], neg = acc_abs[mb][nb][v] - acc[mb][nb][v];
+                        const float of_pos = pos != 0.0f ? pos * scale[nb][v] : 0.0f;
+                        val[v] = neg != 0.0f ? fmaf(neg, scale_neg[nb][v], of_pos) : of_pos;
+                    } else {
+                        val[v] = acc[mb][nb][v] * scale[nb][v];
+                    }
                     if constexpr (EPI == 0) val[v] *= gate;
                     else val[v] = val[v] > 0.0f ? val[v] : 0.0f;
                 }

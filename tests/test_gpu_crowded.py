@@ -90,7 +90,21 @@ def test_unused_grid_point_is_not_read(oracle_dict, cols):
     mm = synth.minmax_bf16(66, rows, 0.01, 0.1).copy()
     ref = mm.copy()
     mm[0::2, 1], mm[1::2, 0] = 0x7F80, 0xFF80  # w_max, w_min
-    for batch, x, y in _matvec(oracle_dict, tern.astype(np.int8), None, mm, (64, 100)):
+    for batch, x, y in _matvec(oracle_dict, tern.astype(np.int8), None, mm, (5, 20, 32, 64, 100)):
         y_ref, bound = oracle.matvec(tern.astype(np.int8), None, x, with_bound=True, minmax_bf16=ref)
-        big = slice(0, batch // 64 * 64)  # (tiles of more than 32 tokens multiply with the grid points themselves)
-        assert (np.abs(y - y_ref)[big] <= 1e-3 * bound[big] + 1e-30).all(), batch
+        assert (np.abs(y - y_ref) <= 1e-3 * bound + 1e-30).all(), batch
+
+
+@pytest.mark.parametrize("batch", [5, 32, 64])
+def test_grid_points_far_apart(oracle_dict, batch):
+    """A row's small grid point keeps its share next to one that is 2^24 times as large: rows that use only the small one, with the large
+    one there, come out as precise as a sum in float32 of the products (2^-24 a sum, in a chain of at most `cols` sums)."""
+    rows, cols = 70, 520
+    tern = -np.abs(synth.ternary(67, rows, cols, 0.6)).astype(np.int8)
+    tern[1::2] *= -1
+    mm = synth.minmax_bf16(68, rows, 0.01, 0.1).copy()
+    mm[0::2, 1] += 24 << 7  # w_max of the rows of negative weights
+    mm[1::2, 0] += 24 << 7  # w_min of the others
+    for _, x, y in _matvec(oracle_dict, tern, None, mm, (batch,)):
+        y_ref, bound = oracle.matvec(tern, None, x, with_bound=True, minmax_bf16=mm)
+        assert (np.abs(y - y_ref) <= cols * 2.0 ** -24 * bound).all()
