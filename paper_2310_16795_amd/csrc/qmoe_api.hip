@@ -326,6 +326,8 @@ int mm_from_tokens(int n_experts, int d_model, int d_ff)
     return (int)std::min(std::max(from, 4.0 * n_experts), 2e9) + 1;
 }
 
+constexpr int kMmMinTokensMostly = 5;  // (see kMmMinTokensDefault) in layers whose experts mostly have a few tokens
+
 qmoe_status plan_mm(const qmoe_dict *d, int code_order, int n_experts, int d_model, int d_ff, int n_tokens, bool x_aligned,
                     MmPlan *mp)
 {
@@ -345,15 +347,21 @@ qmoe_status plan_mm(const qmoe_dict *d, int code_order, int n_experts, int d_mod
         mp->one_stream = true;
         if (n_tokens < mp->from_tokens) return QMOE_OK;
     }
-    // A tile of eight or more tokens is better here anyhow, one of six or seven where most experts are crowded or nearly so (the
+    // A tile of eight or more tokens is better here anyhow, one of five to seven where most experts are crowded or nearly so (the
     // few-token kernels need two passes for it).  Layers whose experts have few tokens keep those on the few-token kernels, which
     // are their long chain, and so do very crowded ones, where only skewed routing has such experts and the crowded are the long chain.
     // From eight / from six tokens on, us: 256 experts of 2080 x 6144, 1500 tokens 796 / 708, asymmetric grid 877 / 785; 512 of
     // 1024 x 4096, 4000 tokens 623 / 592; 128 of 1024 x 4096, 1100 tokens 236 / 219; 256 of 2080 x 6144 with 1-32 tokens each
     // 966 / 926.  Not so: 1500 of 600 x 1600, 4000 tokens 331 / 371; 2048 of 2080 x 6144, 2048 tokens 828 / 836; 128 of 768 x 3072,
     // 4001 tokens, Zipf 207 / 210.
-    const bool six = n_tokens >= 4LL * n_experts && n_tokens < 24LL * n_experts;
-    mp->min_tokens = tu.mfma_min_tokens > 0 ? tu.mfma_min_tokens : (six ? kMmMinTokensCrowded : kMmMinTokensDefault);
+    // From six / from five tokens on: 200 of 2080 x 6144, 1024 tokens, asymmetric grid 816 / 750; 256 of 1024 x 4096, 1536 tokens
+    // 308 / 292; of 52 layers with 4 to 7 tokens per expert (six shapes, uniform and Zipf routing) 0.97 of the time on average and 1.01 at
+    // worst.  Not so: 512 of 1024 x 4096, 4000 tokens 527 / 537; 256 of 2080 x 6144 with 1-32 tokens each 812 / 834; on one stream, 200 of
+    // 2080 x 6144, 1000 tokens, Zipf 446 / 458.
+    mp->min_tokens = kMmMinTokensDefault;
+    if (n_tokens >= 4LL * n_experts && n_tokens < 24LL * n_experts)
+        mp->min_tokens = !mp->one_stream && n_tokens < 7LL * n_experts ? kMmMinTokensMostly : kMmMinTokensCrowded;
+    if (tu.mfma_min_tokens > 0) mp->min_tokens = tu.mfma_min_tokens;
     mp->grid = di.cus;
     mp->smem = mm_lds_bytes(n_order);
     return QMOE_OK;
