@@ -506,15 +506,15 @@ __device__ __forceinline__ void mm_item(const ProductArgs &a, const qmoe_matrix 
 #pragma unroll
         for (int nb = 0; nb < 4; nb++) acc[mb][nb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 
-    // asymmetric grid, tiles of up to 32 tokens: a second sum under |weight|, the grid points are applied when a row is written; larger ones (no registers for
+    // asymmetric grid, tiles of up to 32 tokens: a sum for each sign, the grid points are applied when a row is written; larger ones (no registers for
     // that): the grid points of the four rows whose weights this lane feeds to the matrix cores
     constexpr bool kTwoSums = ASYM && MB <= 2;
-    f32x4 acc_abs[kTwoSums ? MB : 1][4];
+    f32x4 acc_neg[kTwoSums ? MB : 1][4];
     if constexpr (kTwoSums) {
 #pragma unroll
         for (int mb = 0; mb < MB; mb++)
 #pragma unroll
-            for (int nb = 0; nb < 4; nb++) acc_abs[mb][nb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            for (int nb = 0; nb < 4; nb++) acc_neg[mb][nb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     }
     uint32_t g_hi[4] = {0u, 0u, 0u, 0u}, g_lo[4] = {0u, 0u, 0u, 0u};
     if constexpr (ASYM && !kTwoSums) {
@@ -587,7 +587,7 @@ __device__ __forceinline__ void mm_item(const ProductArgs &a, const qmoe_matrix 
                 if constexpr (ASYM && !kTwoSums)
                     bw[nb] = mm_expand_minmax(wd[ks][nb], g_hi[nb], g_lo[nb]);
                 else
-                    bw[nb] = mm_expand(wd[ks][nb]);
+                    bw[nb] = mm_expand(kTwoSums ? wd[ks][nb] & ~(wd[ks][nb] >> 1) & 0x44444444u : wd[ks][nb]);
             }
 #pragma unroll
             for (int mb = 0; mb < MB; mb++) __builtin_memcpy(&ax[mb], &xa[X][mb][ks], 16);
@@ -598,17 +598,12 @@ __device__ __forceinline__ void mm_item(const ProductArgs &a, const qmoe_matrix 
                     acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bw[nb], ax[mb], acc[mb][nb], 0, 0, 0);
             if constexpr (kTwoSums) {
 #pragma unroll
-                for (int nb = 0; nb < 4; nb++) {
-                    u32x4 m;
-                    __builtin_memcpy(&m, &bw[nb], 16);
-                    m &= 0x7FFF7FFFu;
-                    __builtin_memcpy(&bw[nb], &m, 16);
-                }
+                for (int nb = 0; nb < 4; nb++) bw[nb] = mm_expand(wd[ks][nb] & (wd[ks][nb] >> 1) & 0x44444444u);
 #pragma unroll
                 for (int mb = 0; mb < MB; mb++)
 #pragma unroll
                     for (int nb = 0; nb < 4; nb++)
-                        acc_abs[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bw[nb], ax[mb], acc_abs[mb][nb], 0, 0, 0);
+                        acc_neg[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bw[nb], ax[mb], acc_neg[mb][nb], 0, 0, 0);
             }
             if (ks == 0) {
                 group = ring_look_up(tab, four);
@@ -640,8 +635,8 @@ __device__ __forceinline__ void mm_item(const ProductArgs &a, const qmoe_matrix 
             uint32_t raw = 0u;
             if constexpr (kTwoSums || !ASYM) raw = (uint32_t)__shfl((int)scale_own, 16 * nb + 4 * lg + v, 64);
             if constexpr (kTwoSums) {
-                scale[nb][v] = 0.25f * __uint_as_float(raw & 0xFFFF0000u);  // w_max
-                scale_neg[nb][v] = 0.25f * __uint_as_float(raw << 16);      // w_min
+                scale[nb][v] = 0.5f * __uint_as_float(raw & 0xFFFF0000u);  // w_max
+                scale_neg[nb][v] = 0.5f * __uint_as_float(raw << 16);      // w_min
             } else if constexpr (!ASYM) {
                 scale[nb][v] = 0.5f * half_bits_to_float((uint16_t)raw);
             } else {
@@ -677,13 +672,18 @@ __device__ __forceinline__ void mm_item(const ProductArgs &a, const qmoe_matrix 
 #pragma unroll
                 for (int v = 0; v < 4; v++) {
                     if constexpr (kTwoSums) {
-                        // Twice the activations under positive and under negative weights: exactly zero where a row has none of them,
-                        // so that a grid point that it does not use, which may be large or infinite, has no part in it.
-                        // (Half the sum and the difference of the grid points times the two sums: that point's rounding stays in the result.
-                        // A sum of its own for each sign in the matrix cores: 256 experts of 2080 x 6144 with 16 tokens each 880 -> 971 us.)
-                        const float pos = acc_abs[mb][nb][v] + acc[mb][nb][v], neg = acc_abs[mb][nb][v] - acc[mb][nb][v];
-                        const float of_pos = pos != 0.0f ? pos * scale[nb][v] : 0.0f;
-                        val[v] = neg != 0.0f ? fmaf(neg, scale_neg[nb][v], of_pos) : of_pos;
+                        // A grid point meets the sum of its own sign only, whose rounding it scales, and none at all where that is
+                        // zero: one that the row does not use may be large or infinite.  The two often nearly cancel: the rounding of the
+                        // first product is added back.
+                        // (A signed sum and one under |weight|, their sum and difference taken here, save 24 instructions a step:
+                        // 884 us instead of 964 for 256 experts of 2080 x 6144 with 16 tokens each, 962 / 1010 with 1-32, 217 / 217 for 4001
+                        // tokens on 128 of 768 x 3072.  But each grid point then scales the rounding of both signs' sum: rows with two
+                        // weights of one sign whose grid point is 100 / 2^14 times the other's were off by up to 9e-6 / 1.5e-3 of
+                        // sum |w x|, 1.8e-7 this way.  A grid point picked per weight, as in larger tiles: 975, 998, 217 us, 6e-7.)
+                        const float pos = acc[mb][nb][v], neg = acc_neg[mb][nb][v], s_pos = pos != 0.0f ? scale[nb][v] : 0.0f;
+                        const float of_pos = pos * s_pos, rest = fmaf(pos, s_pos, -of_pos);
+                        const float sum = neg != 0.0f ? fmaf(neg, scale_neg[nb][v], of_pos) : of_pos;
+                        val[v] = fabsf(sum) < INFINITY ? sum + rest : sum;
                     } else {
                         val[v] = acc[mb][nb][v] * scale[nb][v];
                     }

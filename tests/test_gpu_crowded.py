@@ -108,3 +108,41 @@ def test_grid_points_far_apart(oracle_dict, batch):
     for _, x, y in _matvec(oracle_dict, tern, None, mm, (batch,)):
         y_ref, bound = oracle.matvec(tern, None, x, with_bound=True, minmax_bf16=mm)
         assert (np.abs(y - y_ref) <= cols * 2.0 ** -24 * bound).all()
+
+
+@pytest.mark.parametrize("ratio", [100.0, 2.0 ** 14])
+def test_a_large_grid_point_leaves_the_other_signs_sum_alone(oracle_dict, ratio):
+    """Rows of one sign but for two weights, whose grid point is far the larger and whose activations are as much smaller: it scales the
+    rounding of their own sum only.  Products are exact in float32, so a row's error is below one rounding (2^-24) of sum |w x| for
+    each of its weights."""
+    rows, cols = 70, 6144
+    tern = -np.abs(synth.ternary(69, rows, cols, 0.9)).astype(np.int8)
+    for r in range(rows):
+        tern[r, [r % 7, 8 + r % 5]] = 1
+    tern[1::2] *= -1
+    mm = synth.minmax_bf16(70, rows, 0.01, 0.1).view(np.uint16).copy().reshape(rows, 2)
+    small = torch.from_numpy(mm[:, 0].astype(np.uint16).view(np.int16).copy()).view(torch.bfloat16)
+    large = (-small.float() * ratio).to(torch.bfloat16)  # |w_max| of the rows whose two weights are positive, |w_min| of the others
+    neg, pos = small.clone(), large.clone()
+    neg[1::2], pos[1::2] = -large[1::2], -small[1::2]
+    mm[:, 0], mm[:, 1] = neg.view(torch.int16).numpy().view(np.uint16), pos.view(torch.int16).numpy().view(np.uint16)
+    gpu = "cuda:0"
+    codes, row_off = oracle.encode(oracle_dict, tern)
+    dd = dev.DeviceDict(q.qmoe_dict_from_words(oracle_dict.words), gpu)
+    M = dev.DeviceMatrix(codes, row_off, None, rows, cols, device=gpu, device_order_of=dd, minmax_bf16=mm)
+    q.qmoe_set_tuning("mfma_min_tokens", 1)
+    try:
+        for batch in (5, 32, 64):
+            x = torch.randn((batch, cols), generator=torch.Generator().manual_seed(71 + batch)).clamp(min=0)  # (one sign: no cancellation)
+            x[:, :16] /= ratio
+            x = x.to(torch.bfloat16).view(torch.int16)
+            y = torch.full((batch, rows), float("nan"), dtype=torch.float32, device=gpu)
+            q.qmoe_decode_matvec(dd.handle, M.desc, x.to(gpu), y)
+            torch.cuda.synchronize()
+            y_ref, bound = oracle.matvec(tern, None, x.numpy().view(np.uint16), with_bound=True, minmax_bf16=mm)
+            err = np.abs(y.cpu().numpy().astype(np.float64) - y_ref)
+            print(batch, (err / bound).max())
+            assert (err <= (tern != 0).sum(1) * 2.0 ** -24 * bound).all(), batch
+    finally:
+        q.qmoe_set_tuning("mfma_min_tokens", 0)
+        dd.close()
