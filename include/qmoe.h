@@ -359,6 +359,8 @@ size_t qmoe_moe_layer_workspace(int n_experts, int d_model, int d_ff, int n_toke
  * wi, wo: device arrays [n_experts] of qmoe_matrix (wi[e]: d_ff x d_model,
  * wo[e]: d_model x d_ff).  x: device bf16 [n_tokens][d_model].  expert_idx:
  * device int32 [n_tokens].  gate: device fp32 [n_tokens] or NULL (= 1).
+ * Activations should be finite: one that is not spoils results of its own token and, where its
+ * expert is given to a few-token kernel (below), may spoil the other tokens' of its tile of up to four.
  * y: device fp32 [n_tokens][d_model], overwritten; a token whose expert index
  * is outside [0, n_experts) gets a zero row.  workspace: device, 256-byte
  * aligned, >= qmoe_moe_layer_workspace(...) bytes (32 KiB less will do, for half a microsecond

@@ -420,9 +420,10 @@ __device__ __forceinline__ void ring_decode_step(RingDecoder &d, const RingTable
 // behind the last step, 728 -> 717.)
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
+// Returns the tile's tokens (a bit each) whose results it has not written: mm_again.
 template <int MB, int EPI, int ASYM>
-__device__ __forceinline__ void mm_item(const ProductArgs &a, const qmoe_matrix &M, int rblk, int slot0, int ntok,
-                                        uint32_t wt, uint32_t win)
+__device__ __forceinline__ unsigned long long mm_item(const ProductArgs &a, const qmoe_matrix &M, int rblk, int slot0, int ntok,
+                                                      uint32_t wt, uint32_t win)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l16 = lane & 15, lg = lane >> 4;
@@ -644,6 +645,11 @@ __device__ __forceinline__ void mm_item(const ProductArgs &a, const qmoe_matrix 
             }
         }
     }
+    // (an activation that is not finite makes every row's sum so, one without weights too: one row's tells)
+    unsigned long long again = 0;
+#pragma unroll
+    for (int mb = 0; mb < MB; mb++) again |= (__ballot(acc[mb][0][0] * 0.0f != 0.0f) & 0xFFFFull) << (16 * mb);
+    again &= ~0ull >> (64 - ntok);
 #pragma unroll
     for (int mb = 0; mb < MB; mb++) {
         const int t = 16 * mb + l16;
@@ -664,7 +670,7 @@ __device__ __forceinline__ void mm_item(const ProductArgs &a, const qmoe_matrix 
         } else {
             to = reinterpret_cast<uintptr_t>(a.out) + 2 * ((size_t)(slot0 + t) * a.ld_out + (size_t)(r0 + 4 * lg));
         }
-        if (t < ntok) {
+        if (t < ntok && !((again >> t) & 1u)) {
 #pragma unroll
             for (int nb = 0; nb < 4; nb++) {
                 const int r = r0 + 16 * nb + 4 * lg;
@@ -712,6 +718,90 @@ __device__ __forceinline__ void mm_item(const ProductArgs &a, const qmoe_matrix 
                             if (r + v < a.rows) ((gw_u16)at)[v] = (uint16_t)h[v];
                     }
                 }
+            }
+        }
+    }
+    return again;
+}
+
+// The given tokens of a unit without the matrix cores, which multiply weights of zero too: an activation that is infinite or no number would
+// make NaN of its token's results in every row, and of the hidden vector zeros (the ReLU), where only rows with a weight there have a
+// part in it.  One lane = one row, four tokens at a time, straight from the stream; four trips to memory a codeword bound it.  256 experts
+// of 2080 x 6144 with 1-32 tokens each, a first call, us: 958 with finite activations, 1625 with one that is not, 14900 with none that is.
+template <int EPI, int ASYM>
+__device__ __forceinline__ void mm_again(const ProductArgs &a, const qmoe_matrix &M, int rblk, int slot0, int ntok, unsigned long long tokens)
+{
+    const int row = rblk * 64 + ((int)threadIdx.x & 63);
+    const bool row_live = row < a.rows;
+    const RowStream rst = row_stream(M, row, row_live);
+    const uint32_t left = min(rst.left, (uint32_t)a.cols);  // (no codeword stands for fewer than two columns)
+    float scale = 0.0f, w_neg = -1.0f, w_pos = 1.0f;
+    if (row_live) {
+        if constexpr (ASYM) {
+            const uint32_t pair = M.minmax_bf16 ? ((gp_u32)M.minmax_bf16)[row] : 0u;
+            w_neg = __uint_as_float(pair << 16);
+            w_pos = __uint_as_float(pair & 0xFFFF0000u);
+            scale = 1.0f;
+        } else {
+            scale = half_bits_to_float(((gp_u16)M.scale_f16)[row]);
+        }
+    }
+    while (tokens) {
+        constexpr int kAtOnce = 4;
+        int slot[kAtOnce], tok[kAtOnce], n = 0;
+        uintptr_t x[kAtOnce];
+        uint32_t next8[kAtOnce];  // bytes from one column to the one eight columns on
+        float sum[kAtOnce];
+#pragma unroll
+        for (int k = 0; k < kAtOnce; k++) {
+            const int t = __builtin_ctzll(tokens ? tokens : 1ull << (slot[0] - slot0));  // (none left: the first again)
+            n += tokens != 0;
+            tokens &= tokens - (tokens != 0);
+            slot[k] = slot0 + t;
+            tok[k] = a.perm ? a.perm[slot[k]] : slot[k];
+            if (EPI == 0 && a.x_tiled) {  // (see mm_item)
+                const int b = t & ~15;
+                x[k] = reinterpret_cast<uintptr_t>(a.x) + 2 * ((size_t)(slot0 + b) * a.ldx + (size_t)(8 * (t & 15)));
+                next8[k] = 16u * (uint32_t)min(16, ntok - b);
+            } else {
+                x[k] = reinterpret_cast<uintptr_t>(a.x) + 2 * ((size_t)(a.x_by_slot ? slot[k] : tok[k]) * a.ldx);
+                next8[k] = 16u;
+            }
+            sum[k] = 0.0f;
+        }
+        uint32_t col = 0;
+        for (uint32_t i = 0; i < left && col < (uint32_t)a.cols; i++) {
+            const uint32_t at = rst.sub + i, code = ((gp_u16)min(rst.pp + rst.pstride * (uintptr_t)(at >> 3), rst.last))[at & 7u];
+            const uint32_t groups3 = 3u * (uint32_t)a.n_groups, single = code > groups3 ? code - groups3 : 0u;
+            const uint32_t e = *(lp_u32)(uintptr_t)(4u * min(max(code >> 2, single), (uint32_t)(a.n_order - 1)));
+            const uint32_t weights = (e & kMmWeights) ^ (((code & 0xFFu) * kMmFlipMul) & kMmFlips), places = e & kMmPlaces;
+#pragma unroll
+            for (int z = 0; z < 3; z++) {
+                const uint32_t w = byte_of(weights, z), c = col + (byte_of(places, z) >> 2);
+                if ((w & 1u) && c < (uint32_t)a.cols) {
+                    const float g = w & 2u ? w_neg : w_pos;
+#pragma unroll
+                    for (int k = 0; k < kAtOnce; k++)
+                        sum[k] = fmaf(g, __uint_as_float((uint32_t)*(gp_u16)(x[k] + (uintptr_t)((c >> 3) * next8[k] + 2u * (c & 7u))) << 16), sum[k]);
+                }
+            }
+            col += places >> 26;
+        }
+        if (!row_live) continue;
+#pragma unroll
+        for (int k = 0; k < kAtOnce; k++) {
+            if (k >= n) break;
+            float val = sum[k] * scale;
+            if constexpr (EPI == 0) {
+                if (a.gate) val *= a.gate[tok[k]];
+                reinterpret_cast<float *>(a.out)[(size_t)tok[k] * a.ld_out + row] = val;
+            } else {
+                size_t to = (size_t)slot[k] * a.ld_out + row;
+                if (a.out_tiled) {
+                    const int b = (slot[k] - slot0) & ~15, j = (slot[k] - slot0) & 15;
+                    to = (size_t)(slot0 + b) * a.ld_out + ((size_t)(row >> 3) * min(16, ntok - b) + j) * 8 + (row & 7);
+                }
+                reinterpret_cast<uint16_t *>(a.out)[to] = float_to_bf16_bits(val > 0.0f ? val : 0.0f);
             }
         }
     }
@@ -816,12 +906,14 @@ __global__ __launch_bounds__(kMmThreads) void k_product_mm(const ProductArgs a)
         const int ntok = min(it.ntok, kMmTokens);
         if (expert < 0 || expert >= a.n_experts || ntok < 1) continue;
         const qmoe_matrix M = matrix_of(a, expert);
+        unsigned long long again;
         if (ntok <= 16)
-            mm_item<1, EPI, ASYM>(a, M, rblk, slot0, ntok, wt_addr, win_addr);
+            again = mm_item<1, EPI, ASYM>(a, M, rblk, slot0, ntok, wt_addr, win_addr);
         else if (ntok <= 32)
-            mm_item<2, EPI, ASYM>(a, M, rblk, slot0, ntok, wt_addr, win_addr);
+            again = mm_item<2, EPI, ASYM>(a, M, rblk, slot0, ntok, wt_addr, win_addr);
         else
-            mm_item<4, EPI, ASYM>(a, M, rblk, slot0, ntok, wt_addr, win_addr);
+            again = mm_item<4, EPI, ASYM>(a, M, rblk, slot0, ntok, wt_addr, win_addr);
+        if (again) mm_again<EPI, ASYM>(a, M, rblk, slot0, ntok, again);
     }
 }
 

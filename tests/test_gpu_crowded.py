@@ -146,3 +146,99 @@ def test_a_large_grid_point_leaves_the_other_signs_sum_alone(oracle_dict, ratio)
     finally:
         q.qmoe_set_tuning("mfma_min_tokens", 0)
         dd.close()
+
+
+def _of_weights(tern, grid, x):
+    """sum of w x over a row's weights only (no weight, no part), in float64: [tokens, rows]; `grid` float64 [rows, 2] (under -1, under +1)."""
+    y = np.zeros((x.shape[0], tern.shape[0]))
+    with np.errstate(invalid="ignore"):
+        for r in range(tern.shape[0]):
+            at = np.flatnonzero(tern[r])
+            y[:, r] = (np.where(tern[r, at] > 0, grid[r, 1], grid[r, 0]) * x[:, at]).sum(1)
+    return y
+
+
+def _same(got, ref, tol):
+    """Equal where the reference is infinite or no number, within the tolerance elsewhere."""
+    odd = ~np.isfinite(ref)
+    assert np.array_equal(got[odd], ref[odd], equal_nan=True)
+    assert (np.abs(got[~odd] - ref[~odd]) <= np.broadcast_to(tol, ref.shape)[~odd]).all()
+    return odd
+
+
+@pytest.mark.parametrize("cols", [72, 1000])
+@pytest.mark.parametrize("minmax", [False, True])
+def test_activations_that_are_not_finite(oracle_dict, cols, minmax):
+    """An infinite activation, or one that is no number, counts in the rows that have a weight there and in no others, and for its own
+    token only; a sum of doubled weights that overflows is no infinity."""
+    rows = 70
+    tern = synth.ternary(81, rows, cols, 0.7)
+    scale = None if minmax else synth.uniform_f16(82, (rows,), 0.01, 0.1)
+    mm = synth.minmax_bf16(83, rows, 0.01, 0.1) if minmax else None
+    grid = synth.bf16_to_f64(mm) if minmax else np.stack([-scale.view(np.float16), scale.view(np.float16)], 1).astype(np.float64)
+    gpu = "cuda:0"
+    codes, row_off = oracle.encode(oracle_dict, tern)
+    dd = dev.DeviceDict(q.qmoe_dict_from_words(oracle_dict.words), gpu)
+    M = dev.DeviceMatrix(codes, row_off, scale, rows, cols, device=gpu, device_order_of=dd, minmax_bf16=mm)
+    q.qmoe_set_tuning("mfma_min_tokens", 1)
+    try:
+        for batch in (1, 5, 17, 40, 64, 70):
+            x = synth.normal_bf16(84 + batch, (batch, cols)).copy()
+            x[0, 3] = 0x7F80                                 # +inf
+            x[batch // 2, cols - 1] = 0xFF80                 # -inf
+            x[batch - 1, 5], x[batch - 1, 6] = 0x7FC0, 0x7F80  # NaN, +inf
+            y = torch.full((batch, rows), 7.0, dtype=torch.float32, device=gpu)
+            q.qmoe_decode_matvec(dd.handle, M.desc, torch.from_numpy(x.view(np.int16)).to(gpu), y)
+            torch.cuda.synchronize()
+            xf = synth.bf16_to_f64(x).reshape(batch, cols)
+            with np.errstate(invalid="ignore"):
+                bound = _of_weights(np.abs(tern), np.abs(grid).max(1, keepdims=True).repeat(2, 1), np.abs(xf))
+            odd = _same(y.cpu().numpy().astype(np.float64), _of_weights(tern, grid, xf), cols * 2.0 ** -24 * bound)
+            assert odd.any() and not odd.all(), batch
+    finally:
+        q.qmoe_set_tuning("mfma_min_tokens", 0)
+        dd.close()
+
+
+@pytest.mark.parametrize("minmax", [False, True])
+@pytest.mark.parametrize("n", [8, 30, 150])
+def test_layers_of_activations_that_are_not_finite(oracle_dict, n, minmax):
+    """The same in a layer: hidden vectors by blocks of tokens, results by gates.  A token whose first product meets an infinity in a
+    few rows has finite results in the rows of the second product without a weight there."""
+    gpu, E, d_model, d_ff = "cuda:0", 2, 136, 264
+    dd = dev.DeviceDict(q.qmoe_dict_from_words(oracle_dict.words), gpu)
+    layer = dev.DeviceLayer(E, d_model, d_ff, gpu, minmax=minmax)
+    tern, grid = {}, {}
+    for e in range(E):
+        for which, rows, cols in (("wi", d_ff, d_model), ("wo", d_model, d_ff)):
+            t = synth.ternary(90 + 2 * e + (which == "wo"), rows, cols, 0.9)
+            g = synth.minmax_bf16(95 + e, rows, 0.01, 0.1) if minmax else synth.uniform_f16(95 + e, (rows,), 0.01, 0.1)
+            layer.set_expert(e, which, *oracle.encode(oracle_dict, t), g)
+            tern[e, which] = t
+            grid[e, which] = synth.bf16_to_f64(g) if minmax else np.stack([-g.view(np.float16), g.view(np.float16)], 1).astype(np.float64)
+    layer.finalize(device_order_of=dd)
+    idx = np.arange(n, dtype=np.int32) % E
+    x = synth.normal_bf16(99, (n, d_model)).copy()
+    x[0, 7], x[1, 0], x[n // 2, 135], x[n - 1, 64] = 0x7F80, 0xFF80, 0x7F80, 0xFF80
+    gate = (0.5 + np.arange(n) % 3).astype(np.float32)
+    y, ws = torch.empty((n, d_model), dtype=torch.float32, device=gpu), layer.workspace(n)
+    q.qmoe_set_tuning("mfma_min_tokens", 1)
+    try:
+        layer.forward(dd, torch.from_numpy(x.view(np.int16)).to(gpu), torch.from_numpy(idx).to(gpu), y, ws, torch.from_numpy(gate).to(gpu))
+        torch.cuda.synchronize()
+        out = dev.read_workspace(ws, E, d_model, d_ff, n)
+    finally:
+        q.qmoe_set_tuning("mfma_min_tokens", 0)
+        dd.close()
+    assert out["counters"][7] > 0
+    slot = np.empty(n, dtype=np.int64)
+    slot[out["perm"][:n]] = np.arange(n)
+    hidden = synth.bf16_to_f64(np.ascontiguousarray(out["hidden"][slot])).reshape(n, d_ff)
+    for e in range(E):
+        own = np.flatnonzero(idx == e)
+        ref = np.maximum(_of_weights(tern[e, "wi"], grid[e, "wi"], synth.bf16_to_f64(x[own]).reshape(own.size, d_model)), 0.0)
+        odd = _same(hidden[own], ref, 2.0 ** -8 * ref + 1e-5)  # (bf16)
+        assert odd.any() and not odd.all()
+        ref = _of_weights(tern[e, "wo"], grid[e, "wo"], hidden[own]) * gate[own, None]
+        odd = _same(y.cpu().numpy().astype(np.float64)[own], ref, d_ff * 2.0 ** -24 * 3 * np.nansum(np.where(np.isfinite(hidden[own]), hidden[own], 0), 1)[:, None])
+        assert odd.any() and not odd[odd.any(1)].all()
