@@ -307,29 +307,30 @@ qmoe_status plan_dense(int rows, int cols, long long max_passes_hint, ProductPla
 
 // Tokens from which on a call of fewer than four per compute unit has its crowded experts multiplied on the matrix cores.
 //
-// The few-token kernels decode a matrix again for every four tokens: 0.18 us a pass and million weights of a matrix (both
-// products), behind a start of 15 us.  The matrix-core kernel decodes it once for 64, but a tile is walked column step by column step by one
-// wavefront per 64 rows, a chain of 1.1 us a step behind a start of 45, or, where that is more, 0.24 us an expert and million weights; and
-// experts with few tokens, left to the other kernel, come on top (70 us), unless there are hardly any.  Experts of the same size, few
-// tokens / matrix cores, us: 4 of 2080 x 6144, 200 tokens 196 / 195, 400 256 / 175, 1000 563 / 180; 64, 700 tokens 426 / 255; 8 of 1024 x
-// 4096, 700 tokens 154 / 125; 128 of 1024 x 4096, 700 tokens 167 / 205; 4 of 768 x 3072, 700 tokens 101 / 105.  Of 330 calls with 4 experts
-// to 130, 220 tokens to 990, six shapes, uniform and Zipf routing, 80 to 90 % zeros, this takes 112 to the matrix cores, in 0.59 of the
-// time on average and 0.97 at worst.
+// The few-token kernels decode a matrix again for every four tokens: 0.036 us a token and million weights of a matrix (both products)
+// at 92 % zeros, 0.062 at 80 %, a tenth more on the asymmetric grid.  The matrix-core kernel decodes it once for 64, but a tile is walked
+// column step by column step by one wavefront per 64 rows (0.8 to 1.1 us a step), and experts with few tokens, left to the other kernel, come on
+// top.  The host sees neither the streams nor the routing: the line is drawn for 92 % zeros, where the few-token kernels are at their
+// best, and 8 % further out, for what the routing scatters.  Few tokens / matrix cores, 92 % zeros, us: 4 experts of 2080 x 6144 (line at 333
+// tokens), 309 tokens 182 / 173, 386 219 / 173, 679 351 / 177; 64 (582) 410 242 / 256, 656 369 / 259; 9 of 1536 x 6144 (441) 389 171 / 160, Zipf
+// 174 / 190, 486 199 / 168; asymmetric grid, 64 of 2080 x 6144 (605) 512 305 / 313, 656 379 / 320.  Of 5528 calls measured on both
+// kernels (4 experts to 250, some 800 shapes, 80 to 92 % zeros, both grids, uniform and Zipf routing, 256 compute units) this gives 2655
+// to the matrix cores, in 0.64 of the time on average and 1.003 at worst; of 500 others at the line or up to a fifth above it, 90 and 92 %
+// zeros, 0.84 on average and 1.04 at worst.  (A line fitted on the symmetric grid at 80 to 90 %
+// zeros alone: up to 1.25 on the asymmetric one at 92 %.)
 // (On one stream: the two chains side by side, on two, were 7 % slower here.)
-int mm_from_tokens(int n_experts, int d_model, int d_ff)
+int mm_from_tokens(int n_experts, int d_model, int d_ff, bool minmax)
 {
-    const double weights = 1e-6 * d_model * d_ff, steps = (d_model + d_ff) / 64.0;
-    const double chain = std::max(45.0 + 1.1 * steps, 25.0 + 0.24 * n_experts * weights);
-    // passes of four tokens, and for every expert three eighths of one that is not full
-    auto tokens = [&](double us) { return 4.0 * ((1.05 * us - 15.0) / (0.18 * weights) - 0.375 * n_experts); };
-    const double from = std::min(tokens(chain + 70.0), std::max(tokens(chain), 32.0 * n_experts));
+    const double weights = 1e-6 * d_model * d_ff, all = n_experts * weights, steps_wi = d_model / 64.0, steps_wo = d_ff / 64.0;
+    const double from = minmax ? (14.0 + 1.10 * steps_wi + 1.00 * steps_wo + 0.11 * all + 1.50 * std::sqrt(all)) / (0.0360 * weights)
+                               : (17.0 + 1.12 * steps_wi + 0.77 * steps_wo + 0.10 * all + 1.35 * std::sqrt(all)) / (0.0333 * weights);
     return (int)std::min(std::max(from, 4.0 * n_experts), 2e9) + 1;
 }
 
 constexpr int kMmMinTokensMostly = 5;  // (see kMmMinTokensDefault) in layers whose experts mostly have a few tokens
 
-qmoe_status plan_mm(const qmoe_dict *d, int code_order, int n_experts, int d_model, int d_ff, int n_tokens, bool x_aligned,
-                    MmPlan *mp)
+qmoe_status plan_mm(const qmoe_dict *d, int code_order, int n_experts, int d_model, int d_ff, int n_tokens, bool minmax,
+                    bool x_aligned, MmPlan *mp)
 {
     *mp = MmPlan{};
     DeviceInfo di;
@@ -343,7 +344,7 @@ qmoe_status plan_mm(const qmoe_dict *d, int code_order, int n_experts, int d_mod
         (d_ff % 8) || !x_aligned || tu.mfma_min_tokens < 0)
         return QMOE_OK;
     if (tu.mfma_min_tokens == 0 && n_tokens < 4 * di.cus) {
-        mp->from_tokens = mm_from_tokens(n_experts, d_model, d_ff);
+        mp->from_tokens = mm_from_tokens(n_experts, d_model, d_ff, minmax);
         mp->one_stream = true;
         if (n_tokens < mp->from_tokens) return QMOE_OK;
     }
@@ -800,7 +801,7 @@ qmoe_status qmoe_moe_dispatch(const qmoe_dict *d, int code_order, const int32_t 
                            tuning().blocks_second > 0 ? tuning().blocks_second : spread,
                            (d_model % 8 == 0 && tuning().stage_out >= 0) ? 4 : 0, minmax, lanes_wo)) != QMOE_OK)
         return st;
-    if ((st = plan_mm(d, code_order, n_experts, d_model, d_ff, n_tokens, true, &mp)) != QMOE_OK) return st;
+    if ((st = plan_mm(d, code_order, n_experts, d_model, d_ff, n_tokens, minmax, true, &mp)) != QMOE_OK) return st;
     return launch_dispatch(dispatch_args(expert_idx, n_tokens, n_experts, d_model, layer_ptrs(workspace, l), pwi.tb_max,
                                          pwo.tb_max, mp, nullptr), static_cast<hipStream_t>(stream));
 }
@@ -838,7 +839,7 @@ qmoe_status layer_forward(const qmoe_dict *d, const qmoe_matrix *wi, const qmoe_
                            (d_model % 8 == 0 && tuning().stage_out >= 0) ? 4 : 0, minmax, lanes_wo)) != QMOE_OK)
         return st;
     MmPlan mp;
-    if ((st = plan_mm(d, code_order, n_experts, d_model, d_ff, n_tokens, reinterpret_cast<uintptr_t>(x_bf16) % 16 == 0, &mp)) != QMOE_OK)
+    if ((st = plan_mm(d, code_order, n_experts, d_model, d_ff, n_tokens, minmax, reinterpret_cast<uintptr_t>(x_bf16) % 16 == 0, &mp)) != QMOE_OK)
         return st;
     const bool mm = mp.min_tokens <= n_tokens;  // otherwise no expert can reach the threshold
     hipStream_t s = static_cast<hipStream_t>(stream);

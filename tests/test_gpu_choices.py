@@ -257,23 +257,24 @@ def test_many_tokens_without_the_matrix_cores(gpu, ddict, oracle_dict, loaded_fo
     assert np.isfinite(y).all() and not y[[5, 12345]].any() and (y != 0).any(axis=1).sum() == T - 2
 
 
-# Calls of fewer than 1024 tokens, on both sides of the line from which on their crowded experts take the matrix cores: 599 tokens for
-# four experts of 1504 x 2600, 974 for 32.  Tokens without an expert do not count.
-@pytest.mark.parametrize("E,T,lost,crowded", [(4, 598, 0, False), (4, 599, 0, True), (4, 599, 1, False), (4, 610, 11, True),
-                                              (32, 973, 0, False), (32, 974, 0, True), (32, 1023, 300, False)])
-def test_small_calls_on_crowded_experts(gpu, ddict, oracle_dict, E, T, lost, crowded):
+# Calls of fewer than 1024 tokens, on both sides of the line from which on their crowded experts take the matrix cores: 626 tokens for
+# four experts of 1504 x 2600 (627 on the asymmetric grid), 785 for 32.  Tokens without an expert do not count.
+@pytest.mark.parametrize("E,T,lost,crowded,minmax", [
+    (4, 625, 0, False, False), (4, 626, 0, True, False), (4, 626, 1, False, False), (4, 637, 11, True, False), (4, 626, 0, False, True),
+    (4, 627, 0, True, True), (32, 784, 0, False, False), (32, 785, 0, True, False), (32, 1023, 300, False, False)])
+def test_small_calls_on_crowded_experts(gpu, ddict, oracle_dict, E, T, lost, crowded, minmax):
     w = synth.WORKLOADS["switch_base128"].scaled(n_experts=E, d_model=1504, d_ff=2600, n_tokens=T)
     x = w.tokens()
     idx = np.random.default_rng(T).choice(np.array([0, E - 1], dtype=np.int32), T)
     idx[:3], idx[3:3 + lost] = 1, -1  # one expert with few tokens
-    layer = _build_layer(w, oracle_dict, gpu, order_of=ddict, experts=[0, 1, E - 1])
-    print(f"{E} experts, {T} tokens, {lost} without", flush=True)
+    layer = _build_layer(w, oracle_dict, gpu, order_of=ddict, experts=[0, 1, E - 1], minmax=minmax)
+    print(f"{E} experts, {T} tokens, {lost} without, asymmetric grid {minmax}", flush=True)
     y, wsout = _run_layer(layer, ddict, x, idx, gpu)
     assert (wsout["counters"][7] > 0) == crowded
     kept = [t for t in range(T) if idx[t] >= 0]
     tok_off, perm = oracle.dispatch(idx, E)
     assert np.array_equal(wsout["tok_off"], tok_off) and np.array_equal(wsout["perm"][:len(kept)], perm)
-    _check_layer(w, idx, x, y, wsout, kept[:2] + kept[-4:])
+    _check_layer(w, idx, x, y, wsout, kept[:2] + kept[-4:], asym=minmax)
     assert not y[idx < 0].any()
 
 
