@@ -327,7 +327,25 @@ int mm_from_tokens(int n_experts, int d_model, int d_ff, bool minmax)
     return (int)std::min(std::max(from, 4.0 * n_experts), 2e9) + 1;
 }
 
-constexpr int kMmMinTokensMostly = 5;  // (see kMmMinTokensDefault) in layers whose experts mostly have a few tokens
+// Tokens from which on an expert takes the matrix cores.  A tile of eight or more is better there anyhow, one of five to seven where
+// most experts are crowded or nearly so (the few-token kernels need two passes for it).  "Per expert" is the average over all experts of the
+// layer, which is all the host knows.  Layers whose experts have fewer than four keep those on the few-token kernels, which are their long chain; with 24
+// and more only skewed routing has such experts, and the crowded are the long chain; and small layers are one partly filled round, as long as
+// its longest chain, which five to seven tokens should not have.
+//
+// Us, from eight / six / five tokens on, 90 % zeros, uniform routing, where nothing else is said:
+// 4 to 7 per expert: 600 experts of 600 x 1600, 3000 tokens 254 / 248 / 225; 256 of 2080 x 6144, 1500 tokens 783 / 674 / 671 (asymmetric grid 860 /
+// 789 / 806); 256 of 1024 x 4096, 1536 tokens 349 / 308 / 302; 200 of 2080 x 6144, 1024 tokens, asymmetric, 80 % 950 / 827 / 789.
+// 7 to 24: 512 of 1024 x 4096, 4000 tokens 584 / 535 / 552; 128, 1100 tokens 230 / 222 / 214; 256 of 2080 x 6144 with 1-32 tokens each 856 / 814 / 842.
+// Fewer than 4: 1500 of 600 x 1600, 4000 tokens 315 / 347 / 360; 2048 of 2080 x 6144, 2048 tokens, Zipf 822 / 834 / 835.  24 and more: 128 of 768 x
+// 3072, 4001 tokens, Zipf 196 / 196 / 196.
+// Small layers: 275 of 400 x 1112, 1344 tokens 112 / 141 / 132; 174 of 848 x 1128, 1275 tokens, asymmetric 145 / 163 / 150.  Of 465 layers with 4 to 24
+// tokens per expert, those below 4 * 10^8 weights a projection lose up to a fifth with six (five) and gain 1 % on average, those above lose 7 % at
+// worst (Zipf, fewer than seven tokens per expert) and gain 5 %.
+constexpr int kMmMinTokens = 8;
+constexpr int kMmMinTokensMostly = 5;        // 4 to 7 tokens per expert; not on one stream (200 of 2080 x 6144, 1000 tokens, Zipf: 446, with six 458)
+constexpr int kMmMinTokensCrowded = 6;       // up to 24 per expert
+constexpr double kMmCrowdedWeights = 4e8;    // of all experts, a projection
 
 qmoe_status plan_mm(const qmoe_dict *d, int code_order, int n_experts, int d_model, int d_ff, int n_tokens, bool minmax,
                     bool x_aligned, MmPlan *mp)
@@ -348,19 +366,8 @@ qmoe_status plan_mm(const qmoe_dict *d, int code_order, int n_experts, int d_mod
         mp->one_stream = true;
         if (n_tokens < mp->from_tokens) return QMOE_OK;
     }
-    // A tile of eight or more tokens is better here anyhow, one of five to seven where most experts are crowded or nearly so (the
-    // few-token kernels need two passes for it).  Layers whose experts have few tokens keep those on the few-token kernels, which
-    // are their long chain, and so do very crowded ones, where only skewed routing has such experts and the crowded are the long chain.
-    // From eight / from six tokens on, us: 256 experts of 2080 x 6144, 1500 tokens 796 / 708, asymmetric grid 877 / 785; 512 of
-    // 1024 x 4096, 4000 tokens 623 / 592; 128 of 1024 x 4096, 1100 tokens 236 / 219; 256 of 2080 x 6144 with 1-32 tokens each
-    // 966 / 926.  Not so: 1500 of 600 x 1600, 4000 tokens 331 / 371; 2048 of 2080 x 6144, 2048 tokens 828 / 836; 128 of 768 x 3072,
-    // 4001 tokens, Zipf 207 / 210.
-    // From six / from five tokens on: 200 of 2080 x 6144, 1024 tokens, asymmetric grid 816 / 750; 256 of 1024 x 4096, 1536 tokens
-    // 308 / 292; of 52 layers with 4 to 7 tokens per expert (six shapes, uniform and Zipf routing) 0.97 of the time on average and 1.01 at
-    // worst.  Not so: 512 of 1024 x 4096, 4000 tokens 527 / 537; 256 of 2080 x 6144 with 1-32 tokens each 812 / 834; on one stream, 200 of
-    // 2080 x 6144, 1000 tokens, Zipf 446 / 458.
-    mp->min_tokens = kMmMinTokensDefault;
-    if (n_tokens >= 4LL * n_experts && n_tokens < 24LL * n_experts)
+    mp->min_tokens = kMmMinTokens;
+    if (n_tokens >= 4LL * n_experts && n_tokens < 24LL * n_experts && (double)n_experts * d_model * d_ff >= kMmCrowdedWeights)
         mp->min_tokens = !mp->one_stream && n_tokens < 7LL * n_experts ? kMmMinTokensMostly : kMmMinTokensCrowded;
     if (tu.mfma_min_tokens > 0) mp->min_tokens = tu.mfma_min_tokens;
     mp->grid = di.cus;

@@ -163,8 +163,6 @@ constexpr int kRowsMaxGrid = 512;        // workgroups of k_rows that a workspac
 constexpr size_t kRowsShareBytes = 64;   // a record
 constexpr int kMmThreads = 512;
 constexpr int kMmTokens = 64;                  // tokens per tile
-constexpr int kMmMinTokensDefault = 8;         // experts with fewer tokens stay on the scalar kernel, ...
-constexpr int kMmMinTokensCrowded = 6;         // ... in layers with many tokens per expert these
 
 // ---------------------------------------------------------------- launch functions (one per kernel family)
 // Each enqueues on `s` and returns QMOE_OK or QMOE_E_HIP; the callers have checked the arguments.

@@ -278,16 +278,17 @@ def test_small_calls_on_crowded_experts(gpu, ddict, oracle_dict, E, T, lost, cro
     assert not y[idx < 0].any()
 
 
-# 1100 tokens, from how many of them on an expert takes the matrix cores: both sides of 4, 7 and 24 tokens per expert
-@pytest.mark.parametrize("E,least", [(276, 8), (275, 5), (158, 5), (157, 6), (46, 6), (45, 8)])
-def test_crowded_from(gpu, ddict, oracle_dict, E, least):
-    w = synth.WORKLOADS["switch_base128"].scaled(n_experts=E, d_model=136, d_ff=264, n_tokens=1100)
+# 1100 tokens, from how many of them on an expert takes the matrix cores: both sides of 4, 7 and 24 tokens per expert and of 4e8 weights
+@pytest.mark.parametrize("E,d_model,d_ff,least", [(276, 544, 2680, 8), (275, 544, 2680, 5), (275, 544, 2672, 8), (158, 632, 4008, 5),
+                                                  (157, 640, 3984, 6), (157, 640, 3976, 8), (46, 1456, 5976, 6), (45, 1456, 6144, 8)])
+def test_crowded_from(gpu, ddict, oracle_dict, E, d_model, d_ff, least):
+    w = synth.WORKLOADS["switch_base128"].scaled(n_experts=E, d_model=d_model, d_ff=d_ff, n_tokens=1100)
     x, few = w.tokens(), np.repeat(np.arange(5, dtype=np.int32), np.arange(4, 9))
     idx = np.full(1100, E - 1, dtype=np.int32)
     at = np.random.default_rng(E).permutation(1100)[:few.size]
     idx[at] = few
     layer = _build_layer(w, oracle_dict, gpu, order_of=ddict, experts=[0, 1, 2, 3, 4, E - 1])
-    print(f"{E} experts", flush=True)
+    print(f"{E} experts of {d_model} x {d_ff}", flush=True)
     y, wsout = _run_layer(layer, ddict, x, idx, gpu)
     assert wsout["counters"][7] == (9 - least) + -(-(1100 - few.size) // 64)
     _check_layer(w, idx, x, y, wsout, list(at) + [t for t in (0, 1, 1098, 1099) if idx[t] == E - 1])
