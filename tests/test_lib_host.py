@@ -108,8 +108,7 @@ def test_encoder_thread_count_does_not_change_the_stream(lib_dict):
 
 @pytest.mark.parametrize("rows,threads", [(1, 1), (3, 5), (64, 2), (65, 2), (257, 5), (1023, 16), (4099, 3)])
 def test_encoder_pieces(lib_dict, rows, threads):
-    """The pieces that the threads take: the stream is one thread's, the error is that of the matrix's first bad row, a
-    buffer that is too small is left alone."""
+    """The pieces that the threads take: the stream is one thread's, a bad row is found, a buffer that is too small is left alone."""
     t = synth.ternary(209, rows, 66, 0.85)
     L, n = q.lib(), ctypes.c_size_t(0)
     try:
@@ -129,6 +128,36 @@ def test_encoder_pieces(lib_dict, rows, threads):
         assert call(bad, codes.size) == -3
     finally:
         q.qmoe_set_tuning("host_threads", 0)
+
+
+@pytest.mark.parametrize("threads", [1, 2, 5, 16])
+def test_encoder_error_is_the_first_bad_rows(threads):
+    """Two bad rows in different pieces, one of a phrase that the dictionary lacks, one of a symbol that is none: the error is the
+    earlier row's, whichever piece was parsed first."""
+    d = q.qmoe_dict_create(0.5, 1, 8)  # eight of the nine pairs
+    words = q.qmoe_dict_words(d)
+    have = {(int(w[0]) >> 4 & 3, int(w[0]) >> 6 & 3) for w in words}
+    lacks = next(p for p in np.ndindex(3, 3) if p not in have)
+    symbol = {0: 0, 1: -1, 2: 1}
+    rows, cols, L = 1030, 64, q.lib()
+    good = np.zeros((rows, cols), dtype=np.int8)
+    codes, row_off, n = np.empty(good.size, dtype=np.uint16), np.empty(rows + 1, dtype=np.uint32), ctypes.c_size_t(0)
+    call = lambda m: L.qmoe_encode_host(d, m.ctypes.data, rows, cols, codes.ctypes.data, codes.size, row_off.ctypes.data,  # noqa: E731
+                                        ctypes.byref(n))
+    try:
+        q.qmoe_set_tuning("host_threads", threads)
+        assert call(good) == 0
+        for first, second in ((0, rows - 1), (3, 4), (500, 600), (rows - 2, rows - 1)):
+            for _ in range(3):
+                t = good.copy()
+                t[first, 10:12], t[second, 20] = [symbol[k] for k in lacks], 2
+                assert call(t) == -7, (first, second)  # UNENCODABLE
+                t = good.copy()
+                t[first, 20], t[second, 10:12] = 2, [symbol[k] for k in lacks]
+                assert call(t) == -3, (first, second)  # BAD_SYMBOL
+    finally:
+        q.qmoe_set_tuning("host_threads", 0)
+        q.qmoe_dict_destroy(d)
 
 
 def test_encoder_with_small_dictionaries_equals_oracle():
