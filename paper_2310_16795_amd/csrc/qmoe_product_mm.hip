@@ -29,7 +29,7 @@ namespace {
 //
 // (Four codewords a round and four bits a column: with one codeword a round and a byte a column, three byte stores a codeword and the
 // ring cleared by stores, the same layer took 449 / 420 us with the units handed out by tickets, 430 / 361 this way; rows of mixed sparsity
-// 498 / 475 and 493 / 435; on the asymmetric grid 495 / 469 and 480 / 419.  Slower or no different, measured: the trips to memory of the
+// 498 / 475 and 493 / 435.  As it stands: 370 / 337, on the asymmetric grid 447 / 436.  Slower or no different, measured: the trips to memory of the
 // next unit during the present one, 905 -> 930 us for 256 experts with 1 to 32 tokens; the activations of 64-token tiles a step ahead, 765 -> 785.)
 
 constexpr int kMmKc = 64;                      // columns per step
@@ -420,7 +420,7 @@ __device__ __forceinline__ void ring_decode_step(RingDecoder &d, const RingTable
 // behind the last step, 728 -> 717.)
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// Returns the tile's tokens (a bit each) whose results it has not written: mm_again.
+// Returns the tile's tokens (a bit each) whose results want mm_again.
 template <int MB, int EPI, int ASYM>
 __device__ __forceinline__ unsigned long long mm_item(const ProductArgs &a, const qmoe_matrix &M, int rblk, int slot0, int ntok,
                                                       uint32_t wt, uint32_t win)
@@ -645,11 +645,6 @@ __device__ __forceinline__ unsigned long long mm_item(const ProductArgs &a, cons
             }
         }
     }
-    // (an activation that is not finite makes every row's sum so, one without weights too: one row's tells)
-    unsigned long long again = 0;
-#pragma unroll
-    for (int mb = 0; mb < MB; mb++) again |= (__ballot(acc[mb][0][0] * 0.0f != 0.0f) & 0xFFFFull) << (16 * mb);
-    again &= ~0ull >> (64 - ntok);
 #pragma unroll
     for (int mb = 0; mb < MB; mb++) {
         const int t = 16 * mb + l16;
@@ -670,7 +665,7 @@ __device__ __forceinline__ unsigned long long mm_item(const ProductArgs &a, cons
         } else {
             to = reinterpret_cast<uintptr_t>(a.out) + 2 * ((size_t)(slot0 + t) * a.ld_out + (size_t)(r0 + 4 * lg));
         }
-        if (t < ntok && !((again >> t) & 1u)) {
+        if (t < ntok) {
 #pragma unroll
             for (int nb = 0; nb < 4; nb++) {
                 const int r = r0 + 16 * nb + 4 * lg;
@@ -721,6 +716,12 @@ __device__ __forceinline__ unsigned long long mm_item(const ProductArgs &a, cons
             }
         }
     }
+    // (An activation that is not finite makes every row's sum so, one without weights too: one row's tells.  Behind the stores: ahead of them,
+    // and the stores left out for such tokens, the compiler's order of the rows' ends cost the second product 346 -> 365 us.)
+    unsigned long long again = 0;
+#pragma unroll
+    for (int mb = 0; mb < MB; mb++) again |= (__ballot(acc[mb][0][0] * 0.0f != 0.0f) & 0xFFFFull) << (16 * mb);
+    again &= ~0ull >> (64 - ntok);
     return again;
 }
 
@@ -820,9 +821,9 @@ __global__ __launch_bounds__(kMmThreads) void k_product_mm(const ProductArgs a)
     // the table is staged the wavefronts of a workgroup share nothing and meet at no barrier, so one
     // wavefront's set-up (a chain of trips to memory) runs under the others' arithmetic, a matrix
     // whose rows are no multiple of 512 leaves no wavefront idle, and the units are small enough to
-    // pack well.  A layer call brings a list of items and a device counter that hands the units out;
-    // the single-matrix call has neither: its items are the tiles of 64 consecutive tokens of
-    // `single`, its units dealt out round robin.
+    // pack well.  A layer call brings a list of items, most of whose units are dealt out in advance, and a device
+    // counter for the rest, or for all of them where a workgroup's wavefronts go in step (both below); the single-matrix call
+    // has neither: its items are the tiles of 64 consecutive tokens of `single`, its units dealt out round robin.
     const bool listed = a.items != nullptr;
     const int n_items = listed ? min(*a.n_items_dev, a.max_items) : (a.batch + kMmTokens - 1) / kMmTokens;
     const int total = (int)min((long long)n_items * a.mm_row_blocks, 0x7FFFFFFFLL);
@@ -913,7 +914,10 @@ __global__ __launch_bounds__(kMmThreads) void k_product_mm(const ProductArgs a)
             again = mm_item<2, EPI, ASYM>(a, M, rblk, slot0, ntok, wt_addr, win_addr);
         else
             again = mm_item<4, EPI, ASYM>(a, M, rblk, slot0, ntok, wt_addr, win_addr);
-        if (again) mm_again<EPI, ASYM>(a, M, rblk, slot0, ntok, again);
+        if (again) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (other lanes write the same places again)
+            mm_again<EPI, ASYM>(a, M, rblk, slot0, ntok, again);
+        }
     }
 }
 
