@@ -370,14 +370,16 @@ size_t qmoe_moe_layer_workspace(int n_experts, int d_model, int d_ff, int n_toke
  * (QMOE_FORMAT_GRID_MINMAX; the descriptors live in device memory, so the host is told).
  * A call of fewer tokens than four per compute unit on experts of at least 2^18 weights
  * (device order) enqueues one kernel per product, in which several lanes share a row; the first
- * groups the tokens itself where it can (up to 512 tokens).  Otherwise:
+ * groups the tokens itself where it can (up to 512 tokens).  The exception are calls with enough tokens
+ * for their experts to be crowded (by experts, widths and grid: 582 tokens on 64 experts of 2080 x 6144,
+ * 333 on four), which go like larger ones but on `stream` alone.  Otherwise:
  * Enqueues a dispatch kernel and, per product, the scalar kernel for experts with few
  * tokens (by the experts that the call can reach, their widths and the layout: the one in which several
  * lanes share a row, or the one with a row range per lane) and (device-order streams, widths divisible by 8, x 16-byte aligned) the
  * matrix-core kernel for crowded ones: an expert's matrix is decoded once per tile of up
  * to 64 tokens there, instead of once per 4.  When both kinds of experts are present the
- * two kernels of one kind run on a second stream that forks from `stream` after the dispatch and
- * joins it again before the call's work ends (two library-owned events per device), so that
+ * two kernels of one kind run, in calls of at least four tokens per compute unit, on a second stream that
+ * forks from `stream` after the dispatch and joins it again before the call's work ends (two library-owned events per device), so that
  * later work on `stream` sees y complete as usual.  side_stream: that second stream, owned
  * by the caller like `stream` (default priority; it must not be `stream` itself); NULL = a
  * stream the library creates once per device and keeps.  Calls on one device must not be
