@@ -371,8 +371,8 @@ size_t qmoe_moe_layer_workspace(int n_experts, int d_model, int d_ff, int n_toke
  * A call of fewer tokens than four per compute unit on experts of at least 2^18 weights
  * (device order) enqueues one kernel per product, in which several lanes share a row; the first
  * groups the tokens itself where it can (up to 512 tokens).  The exception are calls with enough tokens
- * for their experts to be crowded (by experts, widths and grid: 582 tokens on 64 experts of 2080 x 6144,
- * 333 on four), which go like larger ones but on `stream` alone.  Otherwise:
+ * for their experts to be crowded (by experts, widths and grid: 583 tokens on 64 experts of 2080 x 6144,
+ * 334 on four), which go like larger ones but on `stream` alone.  Otherwise:
  * Enqueues a dispatch kernel and, per product, the scalar kernel for experts with few
  * tokens (by the experts that the call can reach, their widths and the layout: the one in which several
  * lanes share a row, or the one with a row range per lane) and (device-order streams, widths divisible by 8, x 16-byte aligned) the

@@ -311,9 +311,9 @@ qmoe_status plan_dense(int rows, int cols, long long max_passes_hint, ProductPla
 // at 92 % zeros, 0.062 at 80 %, a tenth more on the asymmetric grid.  The matrix-core kernel decodes it once for 64, but a tile is walked
 // column step by column step by one wavefront per 64 rows (0.8 to 1.1 us a step), and experts with few tokens, left to the other kernel, come on
 // top.  The host sees neither the streams nor the routing: the line is drawn for 92 % zeros, where the few-token kernels are at their
-// best, and 8 % further out, for what the routing scatters.  Few tokens / matrix cores, 92 % zeros, us: 4 experts of 2080 x 6144 (line at 333
-// tokens), 309 tokens 182 / 173, 386 219 / 173, 679 351 / 177; 64 (582) 410 242 / 256, 656 369 / 259; 9 of 1536 x 6144 (441) 389 171 / 160, Zipf
-// 174 / 190, 486 199 / 168; asymmetric grid, 64 of 2080 x 6144 (605) 512 305 / 313, 656 379 / 320.  Of 5528 calls measured on both
+// best, and 8 % further out, for what the routing scatters.  Few tokens / matrix cores, 92 % zeros, us: 4 experts of 2080 x 6144 (line at 334
+// tokens), 309 tokens 182 / 173, 386 219 / 173, 679 351 / 177; 64 (583) 410 242 / 256, 656 369 / 259; 9 of 1536 x 6144 (442) 389 171 / 160, Zipf
+// 174 / 190, 486 199 / 168; asymmetric grid, 64 of 2080 x 6144 (606) 512 305 / 313, 656 379 / 320.  Of 5528 calls measured on both
 // kernels (4 experts to 250, some 800 shapes, 80 to 92 % zeros, both grids, uniform and Zipf routing, 256 compute units) this gives 2655
 // to the matrix cores, in 0.64 of the time on average and 1.003 at worst; of 500 others at the line or up to a fifth above it, 90 and 92 %
 // zeros, 0.84 on average and 1.04 at worst.  (A line fitted on the symmetric grid at 80 to 90 %
