@@ -928,6 +928,7 @@ qmoe_status layer_forward(const qmoe_dict *d, const qmoe_matrix *wi, const qmoe_
         // the hidden vectors of the crowded experts are kept in blocks of 16 tokens (see ProductArgs); only the two
         // matrix-core kernels touch those slots (needs whole 8-column groups on the hidden side: d_ff % 8 == 0)
         am.out_tiled = 1;
+        am.mm_spread = !overlap || !mm_first;  // (the shorter chain leaves compute units to the longer one)
         am.mm_in_step = 1;  // its activations come by token rows: the wavefronts of a workgroup read the same lines together
         if (phases & 8)
             if ((st = launch_product_mm(am, mp, s_mm)) != QMOE_OK) return st;
@@ -936,6 +937,7 @@ qmoe_status layer_forward(const qmoe_dict *d, const qmoe_matrix *wi, const qmoe_
         am.n_items_dev = lp.counters + 7;
         am.work_counter = lp.counters + 9;
         am.x_tiled = 1;
+        am.mm_spread = !overlap || !mm_first;
         if (phases & 16)
             if ((st = launch_product_mm(am, mp, s_mm)) != QMOE_OK) return st;
     }

@@ -83,6 +83,7 @@ struct ProductArgs {
     int n_groups, n_order;
     int code_order;           // numbering of the streams (decode_dense only; the product picks its kernel)
     int mm_row_blocks;  // matrix-core kernel: blocks of 64 rows per matrix (a wavefront's unit of work)
+    int mm_spread;      // matrix-core kernel: fewer units than wavefronts are spread over all compute units
     int mm_in_step;     // matrix-core kernel: a workgroup's wavefronts may take eight consecutive units at a time, together
     int minmax;               // rows on the grid {w_min, 0, w_max} (host side: which kernel to launch)
     // matrix-core kernel, layer calls: the hidden vectors of a tile are kept in blocks of 16 tokens,

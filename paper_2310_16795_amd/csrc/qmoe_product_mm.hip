@@ -808,6 +808,24 @@ __device__ __forceinline__ void mm_again(const ProductArgs &a, const qmoe_matrix
     }
 }
 
+// A ticket of the device counter for a wavefront, out of the `some` that its workgroup has drawn last.  pool: lock, next ticket, end of the
+// drawn ones (in LDS, zeros at first).  Nobody draws again when the counter has given all `n` tickets.
+__device__ __forceinline__ int pool_draw(int *pool, int *counter, int some, int n)
+{
+    int got = 0;
+    if ((threadIdx.x & 63) == 0) {
+        while (__hip_atomic_exchange(pool, 1, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP)) __builtin_amdgcn_s_sleep(1);
+        got = pool[1];
+        if (got >= pool[2] && got < n) {
+            got = atomicAdd(counter, some);
+            pool[2] = got + some;
+        }
+        pool[1] = got + 1;
+        __hip_atomic_store(pool, 0, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    return min(__builtin_amdgcn_readfirstlane(got), n);
+}
+
 template <int EPI, int ASYM>
 __global__ __launch_bounds__(kMmThreads) void k_product_mm(const ProductArgs a)
 {
@@ -828,19 +846,25 @@ __global__ __launch_bounds__(kMmThreads) void k_product_mm(const ProductArgs a)
     const int n_items = listed ? min(*a.n_items_dev, a.max_items) : (a.batch + kMmTokens - 1) / kMmTokens;
     const int total = (int)min((long long)n_items * a.mm_row_blocks, 0x7FFFFFFFLL);
     const int wave = (int)threadIdx.x >> 6, lane = (int)threadIdx.x & 63, waves = kMmThreads / 64;
+    const int all_waves = (int)gridDim.x * waves;
     // No more workgroups than fill all their wavefronts stay (a workgroup holds its compute unit's LDS whole,
     // so one that runs half empty keeps the other kernels of a layer call off that compute unit); the
-    // single-matrix call, which is after latency, spreads its units over as many compute units as it can.
-    if (total <= 0 || (int)blockIdx.x >= (listed ? (total + waves - 1) / waves : total)) return;
+    // single-matrix call, which is after latency, spreads its units over as many compute units as it can, and so does a layer call
+    // whose few-token kernels run before or after these or need little (mm_spread): 64 experts of 768 x 3072 with 16 tokens each, second
+    // product, 768 units on 96 compute units 51, on all of them 34 us.
+    const bool spread = listed && a.mm_spread && total < all_waves;
+    const int wgs = listed && !spread ? (total + waves - 1) / waves : min(total, (int)gridDim.x);
+    if ((int)blockIdx.x >= wgs) return;
     int *next_base = reinterpret_cast<int *>(win + (size_t)kMmThreads * kMmWindowBytes);  // [1], in-step hand-out only
     int *tok_sums = next_base + 1;                                                      // [2]
-    if (threadIdx.x < 2) tok_sums[threadIdx.x] = 0;
+    int *pool = next_base + 3;                                                          // [3], see pool_draw
+    if (threadIdx.x < 5) tok_sums[threadIdx.x] = 0;
     stage_words(table_w, a.order_table, a.n_order, ring_entry_bytes);
     __syncthreads();
     // In step or each wavefront for itself (see the loop)?  In step when most of the tokens sit in tiles of
     // more than 32: those read 4-8 KB of activations per wavefront and step.
     bool in_step = false;
-    if (listed && a.mm_in_step) {
+    if (listed && a.mm_in_step && total > all_waves) {
         int big = 0, all = 0;
         for (int i = threadIdx.x; i < n_items; i += kMmThreads) {
             const int n = max(0, min(a.items[i].ntok, kMmTokens));
@@ -856,36 +880,46 @@ __global__ __launch_bounds__(kMmThreads) void k_product_mm(const ProductArgs a)
     }
 
     const uint32_t wt_addr = (uint32_t)(uintptr_t)(lw_u8)wt, win_addr = (uint32_t)(uintptr_t)(lw_u8)win;
-    // Which units: in a layer call seven eighths of them are dealt out, a workgroup's wavefronts taking consecutive ones (of
-    // the same tile, as a rule), and the rest handed out by the device counter.  (A ticket for every unit, and the counter bounds the
-    // kernel: it gives one in 13 ns, whoever asks, and 256 experts of 2080 x 6144 with 16 tokens each have 24576 units in the first
-    // product.  That product 436 -> 394 us; fifteen sixteenths, two thirds: no difference.)
+    // Which units: in a layer call the first one of every wavefront and seven eighths of all are dealt out, consecutive ones (of the
+    // same tile, as a rule) to a workgroup; the others are drawn from the device counter, `some` at a time for the whole workgroup.
+    // The counter gives a ticket in 13 ns, whoever asks, those that find nothing left too: 2048 wavefronts whose units take 12 to 16 steps
+    // wait for it, and a call of one round took 27 us for its tickets and as much again for the empty ones.  Tickets for all units but the whole
+    // rounds among the first seven eighths / this, first and second product, us: 170 experts of 768 x 3072 with 16 tokens each 88.7 and
+    // 76.9 / 66.4 and 44.4, 128 of 1024 x 4096 with 8 97.6 and 84.0 / 76.0 and 52.9, 63 of 2080 x 6144 with 1-32 100 and 116 / 95.7
+    // and 96.9, 252 of them with 16 378 and 361 / 380 and 362.  Long units are drawn one at a time, since the end waits for the longest: 252 of 2080 x 6144 with
+    // 1-32 tokens, second product, 357 by eights, 310 one by one.  More dealt out: fifteen sixteenths 378.
     // The single-matrix call deals all of them out, round robin over the workgroups first, then over their wavefronts: few units spread
     // over many compute units.
-    const int all_waves = (int)gridDim.x * waves;
-    const int dealt = listed ? (total - total / 8) / all_waves * all_waves : total;
-    int g_dealt = listed ? (int)blockIdx.x * waves + wave : wave * (int)gridDim.x + (int)blockIdx.x;
-    for (;;) {
-        int g = g_dealt;
-        if (in_step) {
-            // The wavefronts of a workgroup take eight consecutive units together and start them together:
-            // where the activations are not stored by token blocks (the first product of a layer) their
-            // operand loads touch a line per token, and eight wavefronts that ask for the same lines at the
-            // same time are served by one fetch.  (Measured both ways: a layer with few, crowded experts is
-            // 3 % faster in step, one with many experts of 8-32 tokens 7 % faster without.)
-            __syncthreads();
-            if (threadIdx.x == 0) *next_base = atomicAdd(a.work_counter, waves);
-            __syncthreads();
-            const int base = *next_base;
-            if (base >= total) break;
-            g = base + wave;
-            if (g >= total) continue;
-        } else if (listed && g >= dealt) {
-            int got = 0;
-            if (lane == 0) got = atomicAdd(a.work_counter, 1);
-            g = dealt + __builtin_amdgcn_readfirstlane(got);
-        } else {
-            g_dealt += all_waves;
+    const int grid = (int)gridDim.x, wg = (int)blockIdx.x;
+    const int dealt = !listed || total <= all_waves ? total : (in_step ? all_waves : max((total - total / 8) / all_waves, 1) * all_waves);
+    const int some = max(min((total - dealt) / (2 * grid), min(96 * kMmKc / a.cols, waves)), 1);
+    int g = wave * grid + wg;
+    if (listed) g = wg * waves + wave;
+    if (spread) {
+        const int from = (int)((long long)wg * total / wgs), to = (int)((long long)(wg + 1) * total / wgs);
+        g = from + wave < to ? from + wave : total;
+    }
+    for (bool first = true;; first = false) {
+        if (!first) {
+            if (in_step) {
+                // The wavefronts of a workgroup take eight consecutive units together and start them together:
+                // where the activations are not stored by token blocks (the first product of a layer) their
+                // operand loads touch a line per token, and eight wavefronts that ask for the same lines at the
+                // same time are served by one fetch.  (Measured both ways: a layer with few, crowded experts is
+                // 3 % faster in step, one with many experts of 8-32 tokens 7 % faster without.)
+                __syncthreads();
+                if (threadIdx.x == 0) *next_base = dealt + atomicAdd(a.work_counter, waves);
+                __syncthreads();
+                if (*next_base >= total) break;
+                g = *next_base + wave;
+                if (g >= total) continue;
+            } else {
+                g += g < dealt ? all_waves : 0;
+                if (g >= dealt) {
+                    if (dealt >= total) break;
+                    g = dealt + pool_draw(pool, a.work_counter, some, total - dealt);
+                }
+            }
         }
         if (g >= total) break;
         const int idx = g / a.mm_row_blocks;
@@ -925,7 +959,7 @@ __global__ __launch_bounds__(kMmThreads) void k_product_mm(const ProductArgs a)
 
 size_t mm_lds_bytes(int n_order)
 {
-    return mm_table_bytes(n_order) + (size_t)kMmThreads * (kMmRowBytes + kMmWindowBytes) + 16;
+    return mm_table_bytes(n_order) + (size_t)kMmThreads * (kMmRowBytes + kMmWindowBytes) + 32;
 }
 
 qmoe_status launch_product_mm(ProductArgs a, const MmPlan &mp, hipStream_t s)

@@ -292,3 +292,23 @@ def test_crowded_from(gpu, ddict, oracle_dict, E, d_model, d_ff, least):
     y, wsout = _run_layer(layer, ddict, x, idx, gpu)
     assert wsout["counters"][7] == (9 - least) + -(-(1100 - few.size) // 64)
     _check_layer(w, idx, x, y, wsout, list(at) + [t for t in (0, 1, 1098, 1099) if idx[t] == E - 1])
+
+
+# The matrix-core kernel's units (64 rows of a tile) against its 2048 wavefronts: fewer, spread over the compute units or eight to a workgroup
+# (`experts` many more than those with tokens), one round and its edges, units that are drawn, and workgroups whose wavefronts go in step.
+@pytest.mark.parametrize("experts,used,n,d_model,d_ff", [
+    (3, 3, 350, 72, 64), (683, 683, 8, 64, 192), (682, 682, 8, 192, 200), (4000, 683, 8, 64, 200), (4000, 256, 8, 512, 520), (900, 585, 8, 256, 224),
+    (1000, 1000, 8, 320, 312), (90, 90, 33, 2056, 1544), (200, 64, 33, 2056, 2104)])
+def test_units_of_the_matrix_cores(gpu, ddict, oracle_dict, experts, used, n, d_model, d_ff):
+    w = synth.WORKLOADS["switch_base128"].scaled(n_experts=experts, d_model=d_model, d_ff=d_ff, n_tokens=used * n)
+    x, some = w.tokens(), np.random.default_rng(used).permutation(experts)[:used].astype(np.int32)
+    idx = np.random.default_rng(n).permutation(np.repeat(some, n))
+    layer = _build_layer(w, oracle_dict, gpu, encoder="library", lib_dict=ddict.handle, experts=[int(e) for e in some], order_of=ddict)
+    units = [used * -(-n // 64) * -(-rows // 64) for rows in (d_ff, d_model)]
+    print(f"{used} of {experts} experts of {d_model} x {d_ff}, {n} tokens each: {units} units", flush=True)
+    y, wsout = _run_layer(layer, ddict, x, idx, gpu)
+    assert wsout["counters"][7] == used * -(-n // 64) and np.isfinite(y).all()
+    first = {int(e): t for t, e in reversed(list(enumerate(idx)))}
+    _check_layer(w, idx, x, y, wsout, [first[int(e)] for e in sorted(some)[::max(1, used // 40)]] + [first[int(max(some))]])
+    again, _ = _run_layer(layer, ddict, x, idx, gpu)  # (which wavefront takes a unit does not show)
+    assert np.array_equal(y, again)
