@@ -347,6 +347,17 @@ constexpr int kMmMinTokensMostly = 5;        // 4 to 7 tokens per expert; not on
 constexpr int kMmMinTokensCrowded = 6;       // up to 24 per expert
 constexpr double kMmCrowdedWeights = 4e8;    // of all experts, a projection
 
+// Layers whose experts all take the matrix cores, those with one token too: small ones from 2.5 tokens per expert on, others from 25 on, in calls
+// that are not small.  Next to the matrix-core kernel the few experts that are left to the few-token kernels cost those kernels' starts and a second
+// stream's fork and join, some 20 us in all, as much as a tile for each of them; larger layers with fewer tokens have so many experts of one or two that
+// tiles of sixteen are the dearer way.  Both ways, us, from eight tokens on (larger layers: see above) / all: 128 experts of 768 x 3072, 4001 tokens, Zipf
+// 188 / 159, 1088 tokens, uniform 150 / 106; 256 of 512 x 2048, 80 % zeros, 1152 tokens 167 / 109, Zipf 129 / 104; 100 of 2080 x 6144, 3000 tokens 406 / 386;
+// 45, 2048 tokens, Zipf 282 / 250; not so 200, 4100 tokens, Zipf 690 / 723.  Of 119 layers below 3.5 * 10^8 weights a projection (1024 to 4100 tokens, 2 to 60 per
+// expert, 80 to 92 % zeros, both grids and routings): 0.81 of the time on average, 0.95 at worst; of 25 larger ones with 25 tokens per expert or more 0.88 and
+// 0.99; of larger ones with 10 to 25 0.94 and 1.11, with fewer up to 1.6.
+constexpr double kMmAllWeights = 3.5e8, kMmAllPerExpert = 2.5, kMmAllPerExpertLarge = 25.0;
+constexpr long long kMmAllMatrix = 1 << 18;  // (a matrix; smaller ones, which do without k_rows, are launch latency either way)
+
 qmoe_status plan_mm(const qmoe_dict *d, int code_order, int n_experts, int d_model, int d_ff, int n_tokens, bool minmax,
                     bool x_aligned, MmPlan *mp)
 {
@@ -367,8 +378,16 @@ qmoe_status plan_mm(const qmoe_dict *d, int code_order, int n_experts, int d_mod
         if (n_tokens < mp->from_tokens) return QMOE_OK;
     }
     mp->min_tokens = kMmMinTokens;
-    if (n_tokens >= 4LL * n_experts && n_tokens < 24LL * n_experts && (double)n_experts * d_model * d_ff >= kMmCrowdedWeights)
+    const double weights = (double)n_experts * d_model * d_ff;
+    if (n_tokens >= 4LL * n_experts && n_tokens < 24LL * n_experts && weights >= kMmCrowdedWeights)
         mp->min_tokens = !mp->one_stream && n_tokens < 7LL * n_experts ? kMmMinTokensMostly : kMmMinTokensCrowded;
+    const double all_from = (weights < kMmAllWeights ? kMmAllPerExpert : kMmAllPerExpertLarge) * n_experts;
+    if (tu.mfma_min_tokens == 0 && n_tokens >= 4 * di.cus && n_tokens >= all_from && (long long)d_model * d_ff >= kMmAllMatrix) {
+        mp->otherwise = mp->min_tokens;  // (tokens without an expert do not count)
+        mp->min_tokens = 1;
+        mp->from_tokens = (int)std::max(std::ceil(all_from), 4.0 * di.cus);
+        mp->one_stream = true;
+    }
     if (tu.mfma_min_tokens > 0) mp->min_tokens = tu.mfma_min_tokens;
     mp->grid = di.cus;
     mp->smem = mm_lds_bytes(n_order);
@@ -548,6 +567,7 @@ DispatchArgs dispatch_args(const int32_t *expert_idx, int n_tokens, int n_expert
     da.tb_wo = tb_wo;
     da.mm_min = mp.min_tokens;
     da.mm_from = mp.from_tokens;
+    da.mm_else = mp.otherwise;
     da.y = y;
     da.d_model = d_model;
     return da;

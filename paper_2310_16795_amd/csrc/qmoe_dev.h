@@ -115,6 +115,7 @@ struct DispatchArgs {
     int tb_wi, tb_wo;
     int mm_min;     // experts with at least this many tokens go to the matrix-core kernel (tiles of 64)
     int mm_from;    // ... if so many tokens of the call have an expert
+    int mm_else;    // ... and with at least this many if not
     float *y;       // rows of dropped tokens are zeroed (may be nullptr)
     int d_model;
 };
@@ -151,8 +152,9 @@ struct ProductPlan {
 // Which experts of a layer go to the matrix-core kernel, and its launch shape.
 struct MmPlan {
     int min_tokens = 0x7FFFFFFF;  // experts with at least this many tokens; INT_MAX = path off
-    int from_tokens = 0;          // ... in calls in which so many tokens have an expert (small calls: see mm_from_tokens)
-    bool one_stream = false;      // small calls: no second stream
+    int from_tokens = 0;          // ... in calls in which so many tokens have an expert (small calls: see mm_from_tokens; kMmAllWeights)
+    int otherwise = 0x7FFFFFFF;   // ... and experts with at least this many in calls in which fewer have
+    bool one_stream = false;      // no second stream: small calls, and those that leave no expert to the few-token kernels
     int grid = 0;
     size_t smem = 0;
 };

@@ -96,7 +96,7 @@ __global__ __launch_bounds__(1024) void k_dispatch(const DispatchArgs a)
     }
     if (dropped) atomicAdd(lost, dropped);
     __syncthreads();
-    const int mm_min = T - *lost >= a.mm_from ? a.mm_min : 0x7FFFFFFF;
+    const int mm_min = T - *lost >= a.mm_from ? a.mm_min : a.mm_else;
 
     // each thread owns a contiguous chunk of experts
     const int chunk = (E + nthr - 1) / nthr;

@@ -312,3 +312,23 @@ def test_units_of_the_matrix_cores(gpu, ddict, oracle_dict, experts, used, n, d_
     _check_layer(w, idx, x, y, wsout, [first[int(e)] for e in sorted(some)[::max(1, used // 40)]] + [first[int(max(some))]])
     again, _ = _run_layer(layer, ddict, x, idx, gpu)  # (which wavefront takes a unit does not show)
     assert np.array_equal(y, again)
+
+
+# Calls whose experts all take the matrix cores, those with one token too: both sides of 1024 tokens, of 2^18 weights a matrix, of 2.5 tokens per expert below 3.5e8 weights
+# and of 25 above; tokens without an expert do not count.  `least`: tokens from which on an expert takes them.
+@pytest.mark.parametrize("E,d_model,d_ff,T,lost,least", [
+    (400, 512, 512, 1024, 0, 1), (400, 512, 512, 1024, 1, 8), (400, 512, 504, 1024, 0, 8), (409, 264, 1000, 1024, 0, 1), (410, 264, 1000, 1024, 0, 8), (437, 296, 2704, 1093, 0, 1),
+    (437, 296, 2712, 1093, 0, 8), (41, 2080, 4104, 1025, 0, 1), (41, 2080, 4104, 1025, 5, 8), (42, 2080, 4008, 1049, 0, 8)])
+def test_all_experts_on_the_matrix_cores(gpu, ddict, oracle_dict, E, d_model, d_ff, T, lost, least):
+    w = synth.WORKLOADS["switch_base128"].scaled(n_experts=E, d_model=d_model, d_ff=d_ff, n_tokens=T)
+    x, few = w.tokens(), np.repeat(np.arange(5, dtype=np.int32), [1, 2, 5, 7, 8])
+    idx = np.full(T, E - 1, dtype=np.int32)
+    order = np.random.default_rng(E).permutation(T)
+    at = order[:few.size]
+    idx[at], idx[order[few.size:few.size + lost]] = few, -1
+    layer = _build_layer(w, oracle_dict, gpu, order_of=ddict, experts=[0, 1, 2, 3, 4, E - 1])
+    print(f"{E} experts of {d_model} x {d_ff}, {T} tokens, {lost} without", flush=True)
+    y, wsout = _run_layer(layer, ddict, x, idx, gpu)
+    assert wsout["counters"][7] == sum(n >= least for n in (1, 2, 5, 7, 8)) + -(-(T - lost - few.size) // 64)
+    _check_layer(w, idx, x, y, wsout, list(at) + [int(t) for t in np.flatnonzero(idx == E - 1)[[0, 1, -2, -1]]])
+    assert np.isfinite(y).all() and not y[idx < 0].any()
