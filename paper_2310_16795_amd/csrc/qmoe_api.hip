@@ -358,6 +358,18 @@ constexpr double kMmCrowdedWeights = 4e8;    // of all experts, a projection
 constexpr double kMmAllWeights = 3.5e8, kMmAllPerExpert = 2.5, kMmAllPerExpertLarge = 25.0;
 constexpr long long kMmAllMatrix = 1 << 18;  // (a matrix; smaller ones, which do without k_rows, are launch latency either way)
 
+// Calls that give all experts to the matrix cores bring the activations to the first product in blocks of 16 tokens (k_tile_x), if that has more units than
+// there are wavefronts.  Read by token rows, a quarter of a wavefront's operand load touches sixteen lines, in blocks two: a step of 64 tokens took
+// 3.1 to 4.2 thousand cycles in the first product and 1.8 to 2.1 in the second.  The copy costs 3 to 4 us, which one partly filled round of
+// units does not win back.  Rows / blocks, us, 90 % zeros, uniform routing where nothing else is said: 128 experts of 768 x 3072, 64 tokens each 171 / 147, 16 each
+// 107 / 107, 4001 tokens, Zipf 165 / 149.5; 64 of 1024 x 4096, 64 each 156 / 133; 64 of 2080 x 6144, 64 each 344 / 315 (asymmetric grid 380 / 387), 32 each
+// 254 / 258; 18 of 1920 x 2496, 3996 tokens, Zipf, asymmetric 220 / 190; below the line 64 of 512 x 2048, 24 each 59 / 62; 24 of 2088 x 1176, 1684
+// tokens, Zipf 80 / 84.  (The tiles are estimated: whole ones, and half a tile an expert.)
+bool mm_tiles_x(int n_experts, int d_ff, int n_tokens, const DeviceInfo &di)
+{
+    return ((double)n_tokens / kMmTokens + 0.5 * n_experts) * ((d_ff + 63) / 64) >= (double)(kMmThreads / 64) * di.cus;
+}
+
 qmoe_status plan_mm(const qmoe_dict *d, int code_order, int n_experts, int d_model, int d_ff, int n_tokens, bool minmax,
                     bool x_aligned, MmPlan *mp)
 {
@@ -387,6 +399,7 @@ qmoe_status plan_mm(const qmoe_dict *d, int code_order, int n_experts, int d_mod
         mp->min_tokens = 1;
         mp->from_tokens = (int)std::max(std::ceil(all_from), 4.0 * di.cus);
         mp->one_stream = true;
+        mp->tile_x = mm_tiles_x(n_experts, d_ff, n_tokens, di);
     }
     if (tu.mfma_min_tokens > 0) mp->min_tokens = tu.mfma_min_tokens;
     mp->grid = di.cus;
@@ -880,7 +893,15 @@ qmoe_status layer_forward(const qmoe_dict *d, const qmoe_matrix *wi, const qmoe_
     }
     // In a small call the kernel with several lanes per row groups the tokens itself.
     const bool grouping = rp.on && !mm && rows_can_dispatch(n_experts, n_tokens, rp.grid, n_order, rp.max_lds);
-    const DispatchArgs da = dispatch_args(expert_idx, n_tokens, n_experts, d_model, lp, pwi.tb_max, pwo.tb_max, mp, y);
+    // The blocks of the activations go into the output's memory, which nobody writes before the second product does, behind the first one on the
+    // same stream; that product clears the rows of tokens without an expert, too, then.
+    auto apart = [&](const void *p, size_t bytes) {
+        const uintptr_t q = reinterpret_cast<uintptr_t>(p), o = reinterpret_cast<uintptr_t>(y);
+        return q + bytes <= o || o + sizeof(float) * (size_t)n_tokens * (size_t)d_model <= q;
+    };
+    const bool tile_x = mp.tile_x && mm && mp.one_stream && reinterpret_cast<uintptr_t>(y) % 16 == 0 && apart(x_bf16, sizeof(uint16_t) * (size_t)n_tokens * (size_t)d_model) &&
+                        apart(expert_idx, sizeof(int32_t) * (size_t)n_tokens);
+    const DispatchArgs da = dispatch_args(expert_idx, n_tokens, n_experts, d_model, lp, pwi.tb_max, pwo.tb_max, mp, tile_x ? nullptr : y);
     if ((phases & 1) && !grouping)
         if ((st = launch_dispatch(da, s)) != QMOE_OK) return st;
 
@@ -949,7 +970,14 @@ qmoe_status layer_forward(const qmoe_dict *d, const qmoe_matrix *wi, const qmoe_
         // matrix-core kernels touch those slots (needs whole 8-column groups on the hidden side: d_ff % 8 == 0)
         am.out_tiled = 1;
         am.mm_spread = !overlap || !mm_first;  // (the shorter chain leaves compute units to the longer one)
-        am.mm_in_step = 1;  // its activations come by token rows: the wavefronts of a workgroup read the same lines together
+        // activations by token rows: the wavefronts of a workgroup read the same lines together (in blocks: 4001 tokens on 128 experts of 768 x 3072,
+        // Zipf, 155 us in step, 149.5 each for itself)
+        am.mm_in_step = !tile_x;
+        if (tile_x && (phases & 8)) {
+            if ((st = launch_tile_x(am, reinterpret_cast<uint16_t *>(y), mp.grid, s_mm)) != QMOE_OK) return st;
+            am.x = reinterpret_cast<const uint16_t *>(y);
+            am.x_tiled = 1;
+        }
         if (phases & 8)
             if ((st = launch_product_mm(am, mp, s_mm)) != QMOE_OK) return st;
         am = a2;
@@ -958,6 +986,11 @@ qmoe_status layer_forward(const qmoe_dict *d, const qmoe_matrix *wi, const qmoe_
         am.work_counter = lp.counters + 9;
         am.x_tiled = 1;
         am.mm_spread = !overlap || !mm_first;
+        if (tile_x) {
+            am.clear_idx = expert_idx;
+            am.clear_count = lp.counters + 1;
+            am.n_tokens = n_tokens;
+        }
         if (phases & 16)
             if ((st = launch_product_mm(am, mp, s_mm)) != QMOE_OK) return st;
     }

@@ -89,8 +89,12 @@ struct ProductArgs {
     // matrix-core kernel, layer calls: the hidden vectors of a tile are kept in blocks of 16 tokens,
     // [8-column group][token of the block][8 columns] (a partial last block: its own token count),
     // in the same bytes the plain [slot][column] rows would take, so that the 16-byte operand
-    // loads of the second product are consecutive over the 64 lanes of a wavefront
+    // loads of the second product are consecutive over the 64 lanes of a wavefront; and so are the activations of
+    // calls that k_tile_x copies into such blocks
     int x_tiled, out_tiled;
+    const int32_t *clear_idx;  // second product: experts of the n_tokens tokens, whose rows of the output are cleared where they have none,
+    const int *clear_count;    // so many of them (device); nullptr: cleared by the dispatch kernel
+    int n_tokens;
 };
 
 
@@ -155,6 +159,7 @@ struct MmPlan {
     int from_tokens = 0;          // ... in calls in which so many tokens have an expert (small calls: see mm_from_tokens; kMmAllWeights)
     int otherwise = 0x7FFFFFFF;   // ... and experts with at least this many in calls in which fewer have
     bool one_stream = false;      // no second stream: small calls, and those that leave no expert to the few-token kernels
+    bool tile_x = false;          // activations go to the first product in blocks of 16 tokens, too (launch_tile_x)
     int grid = 0;
     size_t smem = 0;
 };
@@ -181,6 +186,7 @@ qmoe_status launch_product_sym(const ProductArgs &a, const ProductPlan &p, bool 
 qmoe_status launch_product_asym(const ProductArgs &a, const ProductPlan &p, bool run, hipStream_t s);
 size_t mm_lds_bytes(int n_order);                                                                   // qmoe_product_mm.hip
 qmoe_status launch_product_mm(ProductArgs a, const MmPlan &mp, hipStream_t s);
+qmoe_status launch_tile_x(const ProductArgs &a, uint16_t *out, int cus, hipStream_t s);
 qmoe_status launch_decompress(const DecompressArgs &a, int out_kind, bool minmax, int cus, int max_lds, hipStream_t s);  // qmoe_decompress.hip
 size_t decompress_lds_bytes(int n_order, int n_mats);  // table, rings, one bit per matrix
 qmoe_status launch_matvec_rows(const ProductArgs &a, bool run, bool minmax, int grid, int threads, size_t smem,

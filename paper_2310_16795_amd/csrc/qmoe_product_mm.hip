@@ -457,7 +457,7 @@ __device__ __forceinline__ unsigned long long mm_item(const ProductArgs &a, cons
         // (a lane whose columns do not exist -- fewer than 8 * lg + 8 columns -- reads column 0 and drops it;
         // a lane without a token reads the block's first token, or the tile's last)
         const size_t col0 = x_col ? 8 * (size_t)lg : (size_t)0;
-        if (EPI == 0 && a.x_tiled) {
+        if (a.x_tiled) {
             const int tb = min(16, ntok - 16 * mb);  // tokens in this block (<= 0: no such block)
             const size_t block0 = tb > 0 ? (size_t)(slot0 + 16 * mb) : (size_t)slot0;
             const size_t j = t < ntok ? (size_t)l16 : (size_t)0;
@@ -760,7 +760,7 @@ __device__ __forceinline__ void mm_again(const ProductArgs &a, const qmoe_matrix
             tokens &= tokens - (tokens != 0);
             slot[k] = slot0 + t;
             tok[k] = a.perm ? a.perm[slot[k]] : slot[k];
-            if (EPI == 0 && a.x_tiled) {  // (see mm_item)
+            if (a.x_tiled) {  // (see mm_item)
                 const int b = t & ~15;
                 x[k] = reinterpret_cast<uintptr_t>(a.x) + 2 * ((size_t)(slot0 + b) * a.ldx + (size_t)(8 * (t & 15)));
                 next8[k] = 16u * (uint32_t)min(16, ntok - b);
@@ -843,6 +843,15 @@ __global__ __launch_bounds__(kMmThreads) void k_product_mm(const ProductArgs a)
     // counter for the rest, or for all of them where a workgroup's wavefronts go in step (both below); the single-matrix call
     // has neither: its items are the tiles of 64 consecutive tokens of `single`, its units dealt out round robin.
     const bool listed = a.items != nullptr;
+    if constexpr (EPI == 0) {  // (ahead of the return: all workgroups)
+        if (a.clear_idx && *a.clear_count > 0) {
+            for (int t = ((int)blockIdx.x * kMmThreads + (int)threadIdx.x) >> 6; t < a.n_tokens; t += (int)gridDim.x * (kMmThreads / 64)) {
+                const int e = a.clear_idx[t];
+                if (e >= 0 && e < a.n_experts) continue;
+                for (int c = (int)threadIdx.x & 63; c < a.rows; c += 64) ((float *)a.out)[(size_t)t * a.ld_out + c] = 0.0f;
+            }
+        }
+    }
     const int n_items = listed ? min(*a.n_items_dev, a.max_items) : (a.batch + kMmTokens - 1) / kMmTokens;
     const int total = (int)min((long long)n_items * a.mm_row_blocks, 0x7FFFFFFFLL);
     const int wave = (int)threadIdx.x >> 6, lane = (int)threadIdx.x & 63, waves = kMmThreads / 64;
@@ -955,7 +964,51 @@ __global__ __launch_bounds__(kMmThreads) void k_product_mm(const ProductArgs a)
     }
 }
 
+// The activations of the listed tiles in blocks of 16 tokens (see ProductArgs): a block stands in `out` where its slots' plain rows would.
+// A wavefront takes 128 columns of a block; eight lanes read 128 bytes of a token in a run and write 128 bytes of a column group with eight others.
+// What bounds it is its launch and two dependent trips to memory: 3 to 4 us in a layer call, 4001 x 768 activations.
+constexpr int kTileCols = 128;
+__global__ __launch_bounds__(256) void k_tile_x(const ProductArgs a, uint16_t *out)
+{
+    const int lane = threadIdx.x & 63, piece = lane & 7;
+    const int chunks = (a.cols + kTileCols - 1) / kTileCols, per_item = (kMmTokens / 16) * chunks;
+    const int n_items = min(*a.n_items_dev, a.max_items);
+    const long long total = (long long)n_items * per_item;
+    for (long long u = (long long)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6); u < total; u += 4LL * gridDim.x) {
+        const int idx = (int)(u / per_item), in_item = (int)(u - (long long)idx * per_item), block = in_item / chunks;
+        const Item it = a.items[idx];
+        const int tb = min(16, min(it.ntok, kMmTokens) - 16 * block), slot0 = it.slot0 + 16 * block;
+        if (tb < 1) continue;
+        const int col = (in_item - block * chunks) * kTileCols + 8 * piece;
+        u32x4 v[2][2];
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+            const int j = min(8 * h + (lane >> 3), tb - 1);
+            const uint16_t *row = a.x + (size_t)a.perm[slot0 + j] * a.ldx;
+#pragma unroll
+            for (int c = 0; c < 2; c++) v[h][c] = *(gp_u32x4)(row + min(col + 64 * c, a.cols - 8));
+        }
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+            const int j = 8 * h + (lane >> 3);
+#pragma unroll
+            for (int c = 0; c < 2; c++) {
+                const int k = col + 64 * c;
+                if (j < tb && k < a.cols)
+                    *(__attribute__((address_space(1))) u32x4 *)(out + (size_t)slot0 * a.ldx + ((size_t)(k >> 3) * tb + j) * 8) = v[h][c];
+            }
+        }
+    }
+}
+
 }  // namespace
+
+qmoe_status launch_tile_x(const ProductArgs &a, uint16_t *out, int cus, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_tile_x, dim3(4 * cus), dim3(256), 0, s, a, out);
+    QMOE_HIP_TRY(hipGetLastError());
+    return QMOE_OK;
+}
 
 size_t mm_lds_bytes(int n_order)
 {

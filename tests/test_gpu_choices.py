@@ -332,3 +332,34 @@ def test_all_experts_on_the_matrix_cores(gpu, ddict, oracle_dict, E, d_model, d_
     assert wsout["counters"][7] == sum(n >= least for n in (1, 2, 5, 7, 8)) + -(-(T - lost - few.size) // 64)
     _check_layer(w, idx, x, y, wsout, list(at) + [int(t) for t in np.flatnonzero(idx == E - 1)[[0, 1, -2, -1]]])
     assert np.isfinite(y).all() and not y[idx < 0].any()
+
+
+# Calls whose activations go to the first product in blocks of 16 tokens, in the output's memory, against the same call with an output that such
+# blocks cannot go to (4 bytes off): the same bits.  Full and partial blocks of every tile size, widths with partial steps and partial pieces of 128
+# columns, tokens without an expert (so many that few-token experts go to their own kernels: 1023 of 1100 left), an infinite activation.
+@pytest.mark.parametrize("E,d_model,d_ff,lost,minmax,inf", [
+    (100, 136, 2056, 0, False, False), (100, 136, 2056, 7, True, False), (100, 264, 2056, 76, False, True), (100, 264, 2056, 77, False, False),
+    (96, 456, 2600, 3, False, True), (96, 200, 4104, 3, True, True)])
+def test_activations_in_blocks(gpu, ddict, oracle_dict, E, d_model, d_ff, lost, minmax, inf):
+    T = 1100
+    w = synth.WORKLOADS["switch_base128"].scaled(n_experts=E, d_model=d_model, d_ff=d_ff, n_tokens=T)
+    x, sizes = w.tokens(), [1, 8, 15, 16, 17, 31, 32, 33, 48, 63, 64, 65, 130]
+    idx = np.full(T, E - 1, dtype=np.int32)
+    order = np.random.default_rng(d_model).permutation(T)
+    idx[order[:sum(sizes)]] = np.repeat(np.arange(len(sizes), dtype=np.int32), sizes)
+    none = order[sum(sizes):sum(sizes) + lost]
+    idx[none] = np.where(np.arange(lost) % 2, E, -1)
+    at = [int(np.flatnonzero(idx == e)[k]) for e in list(range(len(sizes))) + [E - 1] for k in (0, -1)]
+    if inf:
+        x[order[-1], 5] = 0x7F80
+        at = [t for t in at if t != order[-1]]
+    layer = _build_layer(w, oracle_dict, gpu, order_of=ddict, experts=list(range(len(sizes))) + [E - 1], minmax=minmax)
+    print(f"{E} experts of {d_model} x {d_ff}, {lost} without, asymmetric grid {minmax}, infinite {inf}", flush=True)
+    y, wsout = _run_layer(layer, ddict, x, idx, gpu)
+    assert wsout["counters"][7] == sum(-(-n // 64) for n in sizes if n >= (8 if T - lost < 1024 else 1)) + -(-(T - lost - sum(sizes)) // 64)
+    _check_layer(w, idx, x, y, wsout, at, asym=minmax)
+    assert not y[none].any() and np.isfinite(np.delete(y, order[-1:] if inf else [], axis=0)).all()
+    other = torch.full((T * d_model + 1,), float("nan"), dtype=torch.float32, device=gpu)[1:].view(T, d_model)
+    layer.forward(ddict, _to_dev16(x, gpu), torch.from_numpy(idx).to(gpu), other, layer.workspace(T))
+    torch.cuda.synchronize()
+    assert np.array_equal(y, other.cpu().numpy(), equal_nan=True)
