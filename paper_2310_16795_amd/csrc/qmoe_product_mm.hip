@@ -867,7 +867,8 @@ __global__ __launch_bounds__(kMmThreads) void k_product_mm(const ProductArgs a)
     int *next_base = reinterpret_cast<int *>(win + (size_t)kMmThreads * kMmWindowBytes);  // [1], in-step hand-out only
     int *tok_sums = next_base + 1;                                                      // [2]
     int *pool = next_base + 3;                                                          // [3], see pool_draw
-    if (threadIdx.x < 5) tok_sums[threadIdx.x] = 0;
+    int *taken = pool + 3;                                                              // [1] units of the workgroup's share that are taken
+    if (threadIdx.x < 6) tok_sums[threadIdx.x] = 0;
     stage_words(table_w, a.order_table, a.n_order, ring_entry_bytes);
     __syncthreads();
     // In step or each wavefront for itself (see the loop)?  In step when most of the tokens sit in tiles of
@@ -889,7 +890,7 @@ __global__ __launch_bounds__(kMmThreads) void k_product_mm(const ProductArgs a)
     }
 
     const uint32_t wt_addr = (uint32_t)(uintptr_t)(lw_u8)wt, win_addr = (uint32_t)(uintptr_t)(lw_u8)win;
-    // Which units: in a layer call the first one of every wavefront and seven eighths of all are dealt out, consecutive ones (of the
+    // Which units: in a layer call of more than two rounds the first one of every wavefront and seven eighths of all are dealt out, consecutive ones (of the
     // same tile, as a rule) to a workgroup; the others are drawn from the device counter, `some` at a time for the whole workgroup.
     // The counter gives a ticket in 13 ns, whoever asks, those that find nothing left too: 2048 wavefronts whose units take 12 to 16 steps
     // wait for it, and a call of one round took 27 us for its tickets and as much again for the empty ones.  Tickets for all units but the whole
@@ -897,13 +898,23 @@ __global__ __launch_bounds__(kMmThreads) void k_product_mm(const ProductArgs a)
     // 76.9 / 66.4 and 44.4, 128 of 1024 x 4096 with 8 97.6 and 84.0 / 76.0 and 52.9, 63 of 2080 x 6144 with 1-32 100 and 116 / 95.7
     // and 96.9, 252 of them with 16 378 and 361 / 380 and 362.  Long units are drawn one at a time, since the end waits for the longest: 252 of 2080 x 6144 with
     // 1-32 tokens, second product, 357 by eights, 310 one by one.  More dealt out: fifteen sixteenths 378.
+    // Between an eighth more than one round and two rounds all are dealt out, in fours over the workgroups, whose wavefronts take them as they come free: the
+    // tickets of such a second round, one each or several at a time, cost more than they even out.  Layers of two products, tickets / this, us: 173 experts
+    // of 736 x 1056, 1301 tokens 85 / 73; 122 of 1600 x 2576, 3441 tokens 193 / 181; 18 of 1920 x 2496, 3996 tokens, Zipf, asymmetric grid 189 / 173;
+    // 128 of 768 x 3072 with 100 tokens each 241 / 232; of 44 layers of all shapes 1.02 on average, 1.18 and 0.98 at the ends.  A few units more than one round
+    // are better drawn: 30 of 1896 x 2320, 2687 tokens, Zipf 153 / 158.  (One by one over the workgroups: 128 of 768 x 3072 with 100 257.  More
+    // rounds this way, and tickets for the last eighth: 170 of 768 x 3072 with 16 141 / 150.)  Beside a longer chain (mm_spread not set) workgroups start
+    // late, and the others have to be able to take their units.
     // The single-matrix call deals all of them out, round robin over the workgroups first, then over their wavefronts: few units spread
     // over many compute units.
     const int grid = (int)gridDim.x, wg = (int)blockIdx.x;
-    const int dealt = !listed || total <= all_waves ? total : (in_step ? all_waves : max((total - total / 8) / all_waves, 1) * all_waves);
+    const bool evenly = listed && a.mm_spread && !in_step && total >= all_waves + all_waves / 8 && total <= 2 * all_waves;
+    const int dealt = !listed || total <= all_waves ? total : (in_step || evenly ? all_waves : max((total - total / 8) / all_waves, 1) * all_waves);
     const int some = max(min((total - dealt) / (2 * grid), min(96 * kMmKc / a.cols, waves)), 1);
     int g = wave * grid + wg;
     if (listed) g = wg * waves + wave;
+    auto in_fours = [&](int j) { return ((j >> 2) * grid + wg) * 4 + (j & 3); };  // unit j of the workgroup
+    if (evenly) g = in_fours(wave);
     if (spread) {
         const int from = (int)((long long)wg * total / wgs), to = (int)((long long)(wg + 1) * total / wgs);
         g = from + wave < to ? from + wave : total;
@@ -924,7 +935,11 @@ __global__ __launch_bounds__(kMmThreads) void k_product_mm(const ProductArgs a)
                 if (g >= total) continue;
             } else {
                 g += g < dealt ? all_waves : 0;
-                if (g >= dealt) {
+                if (evenly) {
+                    int j = 0;
+                    if (lane == 0) j = atomicAdd(taken, 1);
+                    g = in_fours(waves + __builtin_amdgcn_readfirstlane(j));
+                } else if (g >= dealt) {
                     if (dealt >= total) break;
                     g = dealt + pool_draw(pool, a.work_counter, some, total - dealt);
                 }

@@ -295,10 +295,10 @@ def test_crowded_from(gpu, ddict, oracle_dict, E, d_model, d_ff, least):
 
 
 # The matrix-core kernel's units (64 rows of a tile) against its 2048 wavefronts: fewer, spread over the compute units or eight to a workgroup
-# (`experts` many more than those with tokens), one round and its edges, units that are drawn, and workgroups whose wavefronts go in step.
+# (`experts` many more than those with tokens), one round, two and their edges, units that are drawn, and workgroups whose wavefronts go in step.
 @pytest.mark.parametrize("experts,used,n,d_model,d_ff", [
     (3, 3, 350, 72, 64), (683, 683, 8, 64, 192), (682, 682, 8, 192, 200), (4000, 683, 8, 64, 200), (4000, 256, 8, 512, 520), (900, 585, 8, 256, 224),
-    (1000, 1000, 8, 320, 312), (90, 90, 33, 2056, 1544), (200, 64, 33, 2056, 2104)])
+    (1000, 1000, 8, 320, 312), (1365, 1365, 8, 64, 192), (1024, 1024, 8, 136, 256), (1025, 1025, 8, 136, 256), (90, 90, 33, 2056, 1544), (200, 64, 33, 2056, 2104)])
 def test_units_of_the_matrix_cores(gpu, ddict, oracle_dict, experts, used, n, d_model, d_ff):
     w = synth.WORKLOADS["switch_base128"].scaled(n_experts=experts, d_model=d_model, d_ff=d_ff, n_tokens=used * n)
     x, some = w.tokens(), np.random.default_rng(used).permutation(experts)[:used].astype(np.int32)
