@@ -186,7 +186,6 @@ qmoe_status launch_product_sym(const ProductArgs &a, const ProductPlan &p, bool 
 qmoe_status launch_product_asym(const ProductArgs &a, const ProductPlan &p, bool run, hipStream_t s);
 size_t mm_lds_bytes(int n_order);                                                                   // qmoe_product_mm.hip
 qmoe_status launch_product_mm(ProductArgs a, const MmPlan &mp, hipStream_t s);
-qmoe_status launch_tile_x(const ProductArgs &a, uint16_t *out, int cus, hipStream_t s);
 qmoe_status launch_decompress(const DecompressArgs &a, int out_kind, bool minmax, int cus, int max_lds, hipStream_t s);  // qmoe_decompress.hip
 size_t decompress_lds_bytes(int n_order, int n_mats);  // table, rings, one bit per matrix
 qmoe_status launch_matvec_rows(const ProductArgs &a, bool run, bool minmax, int grid, int threads, size_t smem,
@@ -199,6 +198,7 @@ qmoe_status launch_rows(const ProductArgs &a, int x_slots, const DispatchArgs *d
                         hipStream_t s);
 qmoe_status launch_decode_dense(const ProductArgs &a, bool run, int8_t *out, int grid, hipStream_t s);
 qmoe_status launch_dispatch_kernel(const DispatchArgs &da, int max_lds, hipStream_t s);             // qmoe_dispatch.hip
+qmoe_status launch_tile_x(const ProductArgs &a, uint16_t *out, int cus, hipStream_t s);
 qmoe_status launch_dense_bf16(const DenseArgs &a, const ProductPlan &p, hipStream_t s);             // qmoe_misc.hip
 qmoe_status launch_stream_copy(void *dst, const void *src, size_t n16, int grid, hipStream_t s);
 qmoe_status launch_renumber(uint16_t *codes, size_t n, const uint16_t *map, int grid, hipStream_t s);

@@ -983,51 +983,7 @@ __global__ __launch_bounds__(kMmThreads) void k_product_mm(const ProductArgs a)
     }
 }
 
-// The activations of the listed tiles in blocks of 16 tokens (see ProductArgs): a block stands in `out` where its slots' plain rows would.
-// A wavefront takes 128 columns of a block; eight lanes read 128 bytes of a token in a run and write 128 bytes of a column group with eight others.
-// What bounds it is its launch and two dependent trips to memory: 3 to 4 us in a layer call, 4001 x 768 activations.
-constexpr int kTileCols = 128;
-__global__ __launch_bounds__(256) void k_tile_x(const ProductArgs a, uint16_t *out)
-{
-    const int lane = threadIdx.x & 63, piece = lane & 7;
-    const int chunks = (a.cols + kTileCols - 1) / kTileCols, per_item = (kMmTokens / 16) * chunks;
-    const int n_items = min(*a.n_items_dev, a.max_items);
-    const long long total = (long long)n_items * per_item;
-    for (long long u = (long long)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6); u < total; u += 4LL * gridDim.x) {
-        const int idx = (int)(u / per_item), in_item = (int)(u - (long long)idx * per_item), block = in_item / chunks;
-        const Item it = a.items[idx];
-        const int tb = min(16, min(it.ntok, kMmTokens) - 16 * block), slot0 = it.slot0 + 16 * block;
-        if (tb < 1) continue;
-        const int col = (in_item - block * chunks) * kTileCols + 8 * piece;
-        u32x4 v[2][2];
-#pragma unroll
-        for (int h = 0; h < 2; h++) {
-            const int j = min(8 * h + (lane >> 3), tb - 1);
-            const uint16_t *row = a.x + (size_t)a.perm[slot0 + j] * a.ldx;
-#pragma unroll
-            for (int c = 0; c < 2; c++) v[h][c] = *(gp_u32x4)(row + min(col + 64 * c, a.cols - 8));
-        }
-#pragma unroll
-        for (int h = 0; h < 2; h++) {
-            const int j = 8 * h + (lane >> 3);
-#pragma unroll
-            for (int c = 0; c < 2; c++) {
-                const int k = col + 64 * c;
-                if (j < tb && k < a.cols)
-                    *(__attribute__((address_space(1))) u32x4 *)(out + (size_t)slot0 * a.ldx + ((size_t)(k >> 3) * tb + j) * 8) = v[h][c];
-            }
-        }
-    }
-}
-
 }  // namespace
-
-qmoe_status launch_tile_x(const ProductArgs &a, uint16_t *out, int cus, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_tile_x, dim3(4 * cus), dim3(256), 0, s, a, out);
-    QMOE_HIP_TRY(hipGetLastError());
-    return QMOE_OK;
-}
 
 size_t mm_lds_bytes(int n_order)
 {
