@@ -17,7 +17,9 @@ extern "C" {
  * Keys:
  *  "phases"    bit mask of the kernels qmoe_moe_layer_forward / qmoe_bf16_layer_forward enqueue:
  *              1 dispatch, 2 / 4 scalar kernel of the first / second product, 8 / 16
- *              matrix-core kernel of the first / second product; 0 = all (the default)
+ *              matrix-core kernel of the first / second product (in calls that bring the activations
+ *              in blocks: 8 with the copy, into y, and 16 clears the rows of tokens without an
+ *              expert); 0 = all (the default)
  *  "stage_out" -1 = the products write their results straight to global memory instead of
  *              staging a block's results in LDS; 0 = default
  *  "rows"      1 = layer calls and single matrices use the kernel with several lanes per row
