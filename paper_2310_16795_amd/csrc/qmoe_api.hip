@@ -355,7 +355,11 @@ constexpr double kMmCrowdedWeights = 4e8;    // of all experts, a projection
 // 45, 2048 tokens, Zipf 282 / 250; not so 200, 4100 tokens, Zipf 690 / 723.  Of 119 layers below 3.5 * 10^8 weights a projection (1024 to 4100 tokens, 2 to 60 per
 // expert, 80 to 92 % zeros, both grids and routings): 0.81 of the time on average, 0.95 at worst; of 25 larger ones with 25 tokens per expert or more 0.88 and
 // 0.99; of larger ones with 10 to 25 0.94 and 1.11, with fewer up to 1.6.
-constexpr double kMmAllWeights = 3.5e8, kMmAllPerExpert = 2.5, kMmAllPerExpertLarge = 25.0;
+// Up to 7 * 10^8 weights, calls of five tokens per compute unit or more with 14 per expert: 56 of 1752 x 6144, 1366 tokens, Zipf 264 / 219; 64 of 1264 x 4368,
+// 1507, Zipf 199 / 157; 129 of 1112 x 4112, 2035, uniform 207 / 190; 103 of 1680 x 2680, 2318, Zipf, asymmetric grid 230 / 233; of 34 such layers 0.92 of the time
+// on average, 1.015 at worst.  With fewer per expert (302 of 792 x 2064, 3349 tokens, Zipf, asymmetric 195 / 218) or more weights (212 of 1240 x 5496, 3421, Zipf,
+// asymmetric 468 / 515) not.
+constexpr double kMmAllWeights = 3.5e8, kMmAllPerExpert = 2.5, kMmMiddleWeights = 7e8, kMmAllPerExpertMiddle = 14.0, kMmAllPerExpertLarge = 25.0;
 constexpr long long kMmAllMatrix = 1 << 18;  // (a matrix; smaller ones, which do without k_rows, are launch latency either way)
 
 // Calls that give all experts to the matrix cores bring the activations to the first product in blocks of 16 tokens (k_tile_x), if that has more units than
@@ -393,7 +397,8 @@ qmoe_status plan_mm(const qmoe_dict *d, int code_order, int n_experts, int d_mod
     const double weights = (double)n_experts * d_model * d_ff;
     if (n_tokens >= 4LL * n_experts && n_tokens < 24LL * n_experts && weights >= kMmCrowdedWeights)
         mp->min_tokens = !mp->one_stream && n_tokens < 7LL * n_experts ? kMmMinTokensMostly : kMmMinTokensCrowded;
-    const double all_from = (weights < kMmAllWeights ? kMmAllPerExpert : kMmAllPerExpertLarge) * n_experts;
+    const bool middle = weights < kMmMiddleWeights && n_tokens >= 5 * di.cus;
+    const double all_from = (weights < kMmAllWeights ? kMmAllPerExpert : (middle ? kMmAllPerExpertMiddle : kMmAllPerExpertLarge)) * n_experts;
     if (tu.mfma_min_tokens == 0 && n_tokens >= 4 * di.cus && n_tokens >= all_from && (long long)d_model * d_ff >= kMmAllMatrix) {
         mp->otherwise = mp->min_tokens;  // (tokens without an expert do not count)
         mp->min_tokens = 1;

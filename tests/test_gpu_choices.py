@@ -315,10 +315,12 @@ def test_units_of_the_matrix_cores(gpu, ddict, oracle_dict, experts, used, n, d_
 
 
 # Calls whose experts all take the matrix cores, those with one token too: both sides of 1024 tokens, of 2^18 weights a matrix, of 2.5 tokens per expert below 3.5e8 weights
-# and of 25 above; tokens without an expert do not count.  `least`: tokens from which on an expert takes them.
+# and of 25 above, from 1280 tokens on of 14 up to 7e8 weights; tokens without an expert do not count.  `least`: tokens from which on an expert takes them.
 @pytest.mark.parametrize("E,d_model,d_ff,T,lost,least", [
     (400, 512, 512, 1024, 0, 1), (400, 512, 512, 1024, 1, 8), (400, 512, 504, 1024, 0, 8), (409, 264, 1000, 1024, 0, 1), (410, 264, 1000, 1024, 0, 8), (437, 296, 2704, 1093, 0, 1),
-    (437, 296, 2712, 1093, 0, 8), (41, 2080, 4104, 1025, 0, 1), (41, 2080, 4104, 1025, 5, 8), (42, 2080, 4008, 1049, 0, 8)])
+    (437, 296, 2712, 1093, 0, 8), (41, 2080, 4104, 1025, 0, 1), (41, 2080, 4104, 1025, 5, 8), (42, 2080, 4008, 1049, 0, 8),
+    (91, 1024, 4000, 1280, 6, 1), (91, 1024, 4000, 1280, 7, 8), (91, 1024, 4000, 1279, 0, 8), (92, 1024, 4000, 1280, 0, 8), (91, 1024, 7512, 1280, 0, 1),
+    (91, 1024, 7520, 1280, 0, 6)])
 def test_all_experts_on_the_matrix_cores(gpu, ddict, oracle_dict, E, d_model, d_ff, T, lost, least):
     w = synth.WORKLOADS["switch_base128"].scaled(n_experts=E, d_model=d_model, d_ff=d_ff, n_tokens=T)
     x, few = w.tokens(), np.repeat(np.arange(5, dtype=np.int32), [1, 2, 5, 7, 8])
