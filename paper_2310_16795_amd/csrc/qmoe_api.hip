@@ -406,6 +406,12 @@ qmoe_status plan_mm(const qmoe_dict *d, int code_order, int n_experts, int d_mod
         mp->one_stream = true;
         mp->tile_x = mm_tiles_x(n_experts, d_ff, n_tokens, di);
     }
+    // Small calls, too, from 14 tokens per expert on: the few-token kernels would come before or after, on the same stream.  From eight tokens on / all, us: 44
+    // experts of 1624 x 2456, 926 tokens, Zipf 147 / 112; 29 of 1760 x 3112, 730 tokens, Zipf 143 / 113; 16 of 1032 x 5592, 661 tokens, Zipf 130 / 116; 8 of 1704 x
+    // 2616, 997 tokens, Zipf 83 / 83; of 40 such calls 0.93 of the time on average, 1.00 at worst, but for one with fewer per expert (55 of 2048 x 3904, 655
+    // tokens, Zipf 168 / 179).
+    if (tu.mfma_min_tokens == 0 && n_tokens < 4 * di.cus && n_tokens >= kMmAllPerExpertMiddle * n_experts && (long long)d_model * d_ff >= kMmAllMatrix)
+        mp->min_tokens = 1;
     if (tu.mfma_min_tokens > 0) mp->min_tokens = tu.mfma_min_tokens;
     mp->grid = di.cus;
     mp->smem = mm_lds_bytes(n_order);

@@ -336,6 +336,23 @@ def test_all_experts_on_the_matrix_cores(gpu, ddict, oracle_dict, E, d_model, d_
     assert np.isfinite(y).all() and not y[idx < 0].any()
 
 
+# Calls of fewer than 1024 tokens that take the matrix cores: all experts from 14 tokens per expert on, below from eight tokens on.
+@pytest.mark.parametrize("E,T,lost,least", [(68, 952, 0, 1), (68, 951, 0, 8), (4, 700, 0, 1), (68, 1023, 20, 1)])
+def test_small_calls_give_all_experts(gpu, ddict, oracle_dict, E, T, lost, least):
+    w = synth.WORKLOADS["switch_base128"].scaled(n_experts=E, d_model=1504, d_ff=2600, n_tokens=T)
+    x, few = w.tokens(), np.repeat(np.arange(3, dtype=np.int32), [1, 7, 8])
+    idx = np.full(T, E - 1, dtype=np.int32)
+    order = np.random.default_rng(T).permutation(T)
+    idx[order[:few.size]] = few
+    idx[order[few.size:few.size + lost]] = -1
+    layer = _build_layer(w, oracle_dict, gpu, order_of=ddict, experts=[0, 1, 2, E - 1])
+    print(f"{E} experts, {T} tokens, {lost} without", flush=True)
+    y, wsout = _run_layer(layer, ddict, x, idx, gpu)
+    assert wsout["counters"][7] == sum(n >= least for n in (1, 7, 8)) + -(-(T - lost - few.size) // 64)
+    _check_layer(w, idx, x, y, wsout, [int(t) for t in order[:few.size]] + [int(t) for t in order[-3:]])
+    assert not y[idx < 0].any() and np.isfinite(y).all()
+
+
 # Calls whose activations go to the first product in blocks of 16 tokens, in the output's memory, against the same call with an output that such
 # blocks cannot go to (4 bytes off): the same bits.  Full and partial blocks of every tile size, widths with partial steps and partial pieces of 128
 # columns, tokens without an expert (so many that few-token experts go to their own kernels: 1023 of 1100 left), an infinite activation.
