@@ -973,14 +973,16 @@ qmoe_status layer_forward(const qmoe_dict *d, const qmoe_matrix *wi, const qmoe_
     a2.cols = d_ff;
     // crowded experts (matrix cores): their tiles are the long items
     if (mm) {
+        // (the shorter chain leaves compute units to the longer one)
+        const int mm_spread = !overlap ? kMmSpread : (mm_first ? 0 : kMmSpread | kMmBeside | (rp.on ? 0 : kMmBesideHolds));
         ProductArgs am = a1;
         am.items = lp.items_mm;
-        am.n_items_dev = lp.counters + 7;
+        am.n_items_dev = lp.counters + kCounterMm;
         am.work_counter = lp.counters + 8;
         // the hidden vectors of the crowded experts are kept in blocks of 16 tokens (see ProductArgs); only the two
         // matrix-core kernels touch those slots (needs whole 8-column groups on the hidden side: d_ff % 8 == 0)
         am.out_tiled = 1;
-        am.mm_spread = !overlap || !mm_first;  // (the shorter chain leaves compute units to the longer one)
+        am.mm_spread = mm_spread;
         // activations by token rows: the wavefronts of a workgroup read the same lines together (in blocks: 4001 tokens on 128 experts of 768 x 3072,
         // Zipf, 155 us in step, 149.5 each for itself)
         am.mm_in_step = !tile_x;
@@ -993,10 +995,10 @@ qmoe_status layer_forward(const qmoe_dict *d, const qmoe_matrix *wi, const qmoe_
             if ((st = launch_product_mm(am, mp, s_mm)) != QMOE_OK) return st;
         am = a2;
         am.items = lp.items_mm;
-        am.n_items_dev = lp.counters + 7;
+        am.n_items_dev = lp.counters + kCounterMm;
         am.work_counter = lp.counters + 9;
         am.x_tiled = 1;
-        am.mm_spread = !overlap || !mm_first;
+        am.mm_spread = mm_spread;
         if (tile_x) {
             am.clear_idx = expert_idx;
             am.clear_count = lp.counters + 1;
@@ -1007,7 +1009,7 @@ qmoe_status layer_forward(const qmoe_dict *d, const qmoe_matrix *wi, const qmoe_
     }
     // experts with few tokens (scalar kernels)
     a1.items = lp.items_wi;
-    a1.n_items_dev = lp.counters + 3;
+    a1.n_items_dev = lp.counters + kCounterFew;
     a1.rows_per_item = pwi.rows_per_item;
     a1.blocks_per_pass = pwi.blocks_per_pass;
     a1.tb_max = pwi.tb_max;

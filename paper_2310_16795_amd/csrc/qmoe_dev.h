@@ -52,6 +52,13 @@ struct Item {  // one (expert, token tile) unit of work; row blocks are enumerat
     int expert, slot0, ntok, pad;
 };
 
+// How the matrix-core kernel of a layer call may hand its units out (one word: every word more in ProductArgs, which each kernel reads at its start, cost a
+// call some 0.3 us a launch).
+constexpr int kMmSpread = 1;       // up to two rounds of units may be dealt out over all compute units
+constexpr int kMmBeside = 2;       // the few-token kernels start first and run beside it, on another stream
+constexpr int kMmBesideHolds = 4;  // ... with workgroups that hold their compute units
+constexpr int kCounterFew = 3, kCounterMm = 7;  // of a layer call's counters: items of the first few-token product, of both matrix-core ones
+
 struct ProductArgs {
     const qmoe_matrix *mats;  // device array indexed by expert, or nullptr -> `single`
     qmoe_matrix single;
@@ -83,7 +90,7 @@ struct ProductArgs {
     int n_groups, n_order;
     int code_order;           // numbering of the streams (decode_dense only; the product picks its kernel)
     int mm_row_blocks;  // matrix-core kernel: blocks of 64 rows per matrix (a wavefront's unit of work)
-    int mm_spread;      // matrix-core kernel: fewer units than wavefronts are spread over all compute units
+    int mm_spread;      // matrix-core kernel, layer calls: kMmSpread and the others
     int mm_in_step;     // matrix-core kernel: a workgroup's wavefronts may take eight consecutive units at a time, together
     int minmax;               // rows on the grid {w_min, 0, w_max} (host side: which kernel to launch)
     // matrix-core kernel, layer calls: the hidden vectors of a tile are kept in blocks of 16 tokens,

@@ -859,9 +859,17 @@ __global__ __launch_bounds__(kMmThreads) void k_product_mm(const ProductArgs a)
     // No more workgroups than fill all their wavefronts stay (a workgroup holds its compute unit's LDS whole,
     // so one that runs half empty keeps the other kernels of a layer call off that compute unit); the
     // single-matrix call, which is after latency, spreads its units over as many compute units as it can, and so does a layer call
-    // whose few-token kernels run before or after these or need little (mm_spread): 64 experts of 768 x 3072 with 16 tokens each, second
+    // whose few-token kernels run before or after these or need little (kMmSpread): 64 experts of 768 x 3072 with 16 tokens each, second
     // product, 768 units on 96 compute units 51, on all of them 34 us.
-    const bool spread = listed && a.mm_spread && total < all_waves;
+    // `late`: the few-token chain beside this one holds whole compute units (k_product's workgroups stay for the launch) and has items.  Workgroups of
+    // this kernel start late there, and those that run have to be able to take any unit: tickets for all but the whole rounds among the first seven
+    // eighths, no more workgroups than needed, wavefronts in step also where one round does.  Units dealt out and spread / this, us: 427 experts of
+    // 1688 x 4664, 1803 tokens, Zipf, asymmetric grid 626 / 583; 336 of 1320 x 3400, 1573, the same 366 / 329; 200 of 256 x 1000, 4000, Zipf 147 / 128; without few-token
+    // items, 17 of 160 x 1456, 2864 tokens, uniform, asymmetric 77 / 98.  The kernel with several lanes per row is beside it for less of the time: 285 of 768 x 4576,
+    // 1923 tokens, Zipf 233 / 253.
+    const int few = a.mm_spread & kMmBeside ? a.n_items_dev[kCounterFew - kCounterMm] : 0;  // items of that chain
+    const bool late = (a.mm_spread & kMmBesideHolds) && few > 0;
+    const bool spread = listed && (a.mm_spread & kMmSpread) && !late && total < all_waves;
     const int wgs = listed && !spread ? (total + waves - 1) / waves : min(total, (int)gridDim.x);
     if ((int)blockIdx.x >= wgs) return;
     int *next_base = reinterpret_cast<int *>(win + (size_t)kMmThreads * kMmWindowBytes);  // [1], in-step hand-out only
@@ -874,7 +882,7 @@ __global__ __launch_bounds__(kMmThreads) void k_product_mm(const ProductArgs a)
     // In step or each wavefront for itself (see the loop)?  In step when most of the tokens sit in tiles of
     // more than 32: those read 4-8 KB of activations per wavefront and step.
     bool in_step = false;
-    if (listed && a.mm_in_step && total > all_waves) {
+    if (listed && a.mm_in_step && (late || total > all_waves)) {
         int big = 0, all = 0;
         for (int i = threadIdx.x; i < n_items; i += kMmThreads) {
             const int n = max(0, min(a.items[i].ntok, kMmTokens));
@@ -903,13 +911,24 @@ __global__ __launch_bounds__(kMmThreads) void k_product_mm(const ProductArgs a)
     // of 736 x 1056, 1301 tokens 85 / 73; 122 of 1600 x 2576, 3441 tokens 193 / 181; 18 of 1920 x 2496, 3996 tokens, Zipf, asymmetric grid 189 / 173;
     // 128 of 768 x 3072 with 100 tokens each 241 / 232; of 44 layers of all shapes 1.02 on average, 1.18 and 0.98 at the ends.  A few units more than one round
     // are better drawn: 30 of 1896 x 2320, 2687 tokens, Zipf 153 / 158.  (One by one over the workgroups: 128 of 768 x 3072 with 100 257.  More
-    // rounds this way, and tickets for the last eighth: 170 of 768 x 3072 with 16 141 / 150.)  Beside a longer chain (mm_spread not set) workgroups start
-    // late, and the others have to be able to take their units.
+    // rounds this way, and tickets for the last eighth: 170 of 768 x 3072 with 16 141 / 150.)  Not beside a longer chain, where workgroups start
+    // late and the others have to be able to take their units: kMmSpread is not set, or the few-token kernel has more than half an item for every tile
+    // (309 of 1776 x 2696, 3022 tokens, Zipf 326 / 312; with fewer, 216 of 1248 x 4352, 1335 tokens, uniform, asymmetric 323 / 331).  Nor where the fours leave
+    // wavefronts without a unit for longer than the tickets cost, some 28 steps: 82 of 1808 x 6192, 3361 tokens, Zipf, asymmetric, 0.43 of a round of 97 steps
+    // 524 / 479; 65 of 2000 x 4912, 3986, Zipf, 80 % zeros, 0.38 of 77 404 / 389; not so 98 of 1792 x 3696, 2110, Zipf, 0.44 of 58 227 / 239.
     // The single-matrix call deals all of them out, round robin over the workgroups first, then over their wavefronts: few units spread
     // over many compute units.
     const int grid = (int)gridDim.x, wg = (int)blockIdx.x;
-    const bool evenly = listed && a.mm_spread && !in_step && total >= all_waves + all_waves / 8 && total <= 2 * all_waves;
-    const int dealt = !listed || total <= all_waves ? total : (in_step || evenly ? all_waves : max((total - total / 8) / all_waves, 1) * all_waves);
+    bool evenly = listed && (a.mm_spread & kMmSpread) && !late && 2 * few <= n_items && !in_step && total >= all_waves + all_waves / 8 && total <= 2 * all_waves;
+    if (evenly) {
+        const int places = 2 * total <= 3 * all_waves ? all_waves + all_waves / 2 : 2 * all_waves;  // (three or four fours a workgroup)
+        evenly = (places - total) * (a.cols / kMmKc) <= 28 * all_waves;
+    }
+    int dealt = total;
+    if (late || (listed && total > all_waves)) {
+        dealt = late ? 0 : all_waves;
+        if (!in_step && !evenly) dealt = max((total - total / 8) / all_waves * all_waves, dealt);
+    }
     const int some = max(min((total - dealt) / (2 * grid), min(96 * kMmKc / a.cols, waves)), 1);
     int g = wave * grid + wg;
     if (listed) g = wg * waves + wave;
@@ -923,7 +942,7 @@ __global__ __launch_bounds__(kMmThreads) void k_product_mm(const ProductArgs a)
         const int most = (total + wgs - 1) / wgs, twos = (total + 2 * wgs - 1) / (2 * wgs);
         g = 2 * twos == most ? ((wave >> 1) * wgs + wg) * 2 + (wave & 1) : wave * wgs + wg;
     }
-    for (bool first = true;; first = false) {
+    for (bool first = g < dealt;; first = false) {
         if (!first) {
             if (in_step) {
                 // The wavefronts of a workgroup take eight consecutive units together and start them together:

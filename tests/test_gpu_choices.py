@@ -314,6 +314,49 @@ def test_units_of_the_matrix_cores(gpu, ddict, oracle_dict, experts, used, n, d_
     assert np.array_equal(y, again)
 
 
+class _Repeated:
+    """A workload of many experts whose matrices are those of the first few."""
+
+    def __init__(self, w, distinct):
+        self.w, self.distinct = w, distinct
+
+    def __getattr__(self, name):
+        a = getattr(self.w, name)
+        return (lambda e: a(e % self.distinct)) if name[:3] in ("wi_", "wo_") else a
+
+    def layer(self, gpu, ddict, minmax):
+        layer = dev.DeviceLayer(self.w.n_experts, self.w.d_model, self.w.d_ff, gpu, minmax=minmax)
+        for which in ("wi", "wo"):
+            coded = [q.qmoe_encode_host(ddict.handle, getattr(self.w, which + "_ternary")(e)) for e in range(self.distinct)]
+            for e in range(self.w.n_experts):
+                layer.set_expert(e, which, *coded[e % self.distinct], getattr(self, which + ("_minmax" if minmax else "_scale"))(e))
+        return layer.finalize(device_order_of=ddict)
+
+
+# The matrix-core kernel's units in calls on two streams whose few-token kernels run beside it, and have items.  Matrices below 2^18 weights (kernel with a row range per lane
+# beside it: tickets, from the first unit on in up to 8/7 of a round; in step, also in one round), larger ones (several lanes per row: a second round from the counter where
+# the few-token items are many), and without few-token items a second round that would leave too many long units' places empty.  The same bits as on one stream.
+@pytest.mark.parametrize("crowded,n,few,m,d_model,d_ff,minmax", [
+    (60, 40, 30, 3, 256, 1000, False), (140, 40, 30, 2, 256, 1000, True), (130, 16, 30, 2, 256, 1000, False), (300, 16, 40, 3, 256, 1000, True), (20, 70, 9, 7, 104, 520, False),
+    (270, 9, 1050, 3, 512, 520, False), (576, 16, 0, 0, 4800, 256, False)])
+def test_units_beside_few_tokens(gpu, ddict, oracle_dict, crowded, n, few, m, d_model, d_ff, minmax):
+    E = crowded + few
+    w = _Repeated(synth.WORKLOADS["switch_base128"].scaled(n_experts=E, d_model=d_model, d_ff=d_ff, n_tokens=crowded * n + few * m), 5)
+    x, experts = w.tokens(), np.random.default_rng(E).permutation(E).astype(np.int32)
+    idx = np.random.default_rng(n).permutation(np.concatenate([np.repeat(experts[:crowded], n), np.repeat(experts[crowded:], m)]))
+    layer = w.layer(gpu, ddict, minmax)
+    print(f"{crowded} experts of {d_model} x {d_ff} with {n} tokens, {few} with {m}, asymmetric grid {minmax}", flush=True)
+    y, wsout = _run_layer(layer, ddict, x, idx, gpu)
+    assert wsout["counters"][7] == crowded * -(-n // 64) and wsout["counters"][3] == few * -(-m // 4) and np.isfinite(y).all()
+    _check_layer(w, idx, x, y, wsout, [int(np.flatnonzero(idx == e)[k]) for e in experts[[0, 1, crowded - 1, -1]] for k in (0, -1)], asym=minmax)
+    q.qmoe_set_tuning("overlap", -1)
+    try:
+        alone, _ = _run_layer(layer, ddict, x, idx, gpu)
+    finally:
+        q.qmoe_set_tuning("overlap", 0)
+    assert np.array_equal(y, alone)
+
+
 # Calls whose experts all take the matrix cores, those with one token too: both sides of 1024 tokens, of 2^18 weights a matrix, of 2.5 tokens per expert below 3.5e8 weights
 # and of 25 above, from 1280 tokens on of 14 up to 7e8 weights; tokens without an expert do not count.  `least`: tokens from which on an expert takes them.
 @pytest.mark.parametrize("E,d_model,d_ff,T,lost,least", [
