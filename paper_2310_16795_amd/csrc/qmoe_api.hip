@@ -359,7 +359,8 @@ constexpr double kMmCrowdedWeights = 4e8;    // of all experts, a projection
 // 1507, Zipf 199 / 157; 129 of 1112 x 4112, 2035, uniform 207 / 190; 103 of 1680 x 2680, 2318, Zipf, asymmetric grid 230 / 233; of 34 such layers 0.92 of the time
 // on average, 1.015 at worst.  With fewer per expert (302 of 792 x 2064, 3349 tokens, Zipf, asymmetric 195 / 218) or more weights (212 of 1240 x 5496, 3421, Zipf,
 // asymmetric 468 / 515) not.
-constexpr double kMmAllWeights = 3.5e8, kMmAllPerExpert = 2.5, kMmMiddleWeights = 7e8, kMmAllPerExpertMiddle = 14.0, kMmAllPerExpertLarge = 25.0;
+constexpr double kMmAllWeights = 3.5e8, kMmAllPerExpert = 2.5, kMmMiddleWeights = 7e8, kMmAllPerExpertMiddle = 14.0, kMmAllPerExpertLarge = 25.0,
+                 kMmChooseWeights = 1.5e8;
 constexpr long long kMmAllMatrix = 1 << 18;  // (a matrix; smaller ones, which do without k_rows, are launch latency either way)
 
 // Calls that give all experts to the matrix cores bring the activations to the first product in blocks of 16 tokens (k_tile_x), if that has more units than
@@ -400,9 +401,14 @@ qmoe_status plan_mm(const qmoe_dict *d, int code_order, int n_experts, int d_mod
     const bool middle = weights < kMmMiddleWeights && n_tokens >= 5 * di.cus;
     const double all_from = (weights < kMmAllWeights ? kMmAllPerExpert : (middle ? kMmAllPerExpertMiddle : kMmAllPerExpertLarge)) * n_experts;
     if (tu.mfma_min_tokens == 0 && n_tokens >= 4 * di.cus && n_tokens >= all_from && (long long)d_model * d_ff >= kMmAllMatrix) {
-        mp->otherwise = mp->min_tokens;  // (tokens without an expert do not count)
+        mp->otherwise = mp->min_tokens;
         mp->min_tokens = 1;
         mp->from_tokens = (int)std::max(std::ceil(all_from), 4.0 * di.cus);
+        // (tokens without an expert do not count.  13 passes for ten tiles, of four tokens a pass, take kept / 4 <= 1.3 * (experts + kept / 64), fewer than six
+        // tokens an expert; layers below 1.5 * 10^8 weights gain nothing above the line: 400 of 512 x 512, 1024 tokens, uniform, matrix cores / few-token kernels 55 / 59)
+        mp->below = std::max(mp->from_tokens, weights >= kMmChooseWeights ? 6 * n_experts : 0);
+        mp->passes = weights < kMmAllWeights ? 13 : 17;
+        mp->split = minmax && weights >= kMmAllWeights;
         mp->one_stream = true;
         mp->tile_x = mm_tiles_x(n_experts, d_ff, n_tokens, di);
     }
@@ -592,6 +598,9 @@ DispatchArgs dispatch_args(const int32_t *expert_idx, int n_tokens, int n_expert
     da.mm_min = mp.min_tokens;
     da.mm_from = mp.from_tokens;
     da.mm_else = mp.otherwise;
+    da.mm_below = mp.below;
+    da.mm_passes = mp.passes;
+    da.mm_split = mp.split;
     da.y = y;
     da.d_model = d_model;
     return da;

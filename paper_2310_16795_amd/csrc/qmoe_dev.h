@@ -127,6 +127,9 @@ struct DispatchArgs {
     int mm_min;     // experts with at least this many tokens go to the matrix-core kernel (tiles of 64)
     int mm_from;    // ... if so many tokens of the call have an expert
     int mm_else;    // ... and with at least this many if not
+    int mm_below;   // not 0: calls that give all experts to it (mm_min is 1), but where fewer tokens than this have an expert may do otherwise, see choose_mm_min:
+    int mm_passes;  // ... few-token passes for ten tiles up to which they give it none
+    int mm_split;   // ... with fewer than mm_from tokens, perhaps the experts with mm_else tokens only
     float *y;       // rows of dropped tokens are zeroed (may be nullptr)
     int d_model;
 };
@@ -165,6 +168,7 @@ struct MmPlan {
     int min_tokens = 0x7FFFFFFF;  // experts with at least this many tokens; INT_MAX = path off
     int from_tokens = 0;          // ... in calls in which so many tokens have an expert (small calls: see mm_from_tokens; kMmAllWeights)
     int otherwise = 0x7FFFFFFF;   // ... and experts with at least this many in calls in which fewer have
+    int below = 0, passes = 0, split = 0;  // (see DispatchArgs)
     bool one_stream = false;      // no second stream: small calls, and those that leave no expert to the few-token kernels
     bool tile_x = false;          // activations go to the first product in blocks of 16 tokens, too (launch_tile_x)
     int grid = 0;

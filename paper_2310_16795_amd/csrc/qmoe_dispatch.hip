@@ -57,6 +57,42 @@ __device__ __forceinline__ void put_tiles(Item *items, int (&at)[4], int e, int 
 __host__ __device__ __forceinline__ int spread(int e) { return e + (e >> 5); }
 __host__ __device__ __forceinline__ int count_stride(int n_experts) { return spread(n_experts) + 1; }
 
+// A call that may give all its experts to the matrix-core kernel: does it?  The host knows neither the routing nor how many tokens have an expert, and its
+// rules (plan_mm) hold for calls in which nearly all have.  A pass of the few-token kernels, four tokens of an expert as a rule, decodes a matrix once, as a tile of 64
+// does: where ten tiles are no more than mm_passes passes, all experts go to those kernels, which start sooner.  Us, matrix cores / few-token kernels / both,
+// side by side on two streams: 716 experts of 696 x 680, 2422 tokens, uniform, asymmetric grid (12.7 passes for ten tiles) 163 / 134 / 157; 128 of 768 x 3072, 109
+// of 1088 tokens left 86 / 57 / 60; 231 of 896 x 320, 1198 (16.7) 51 / 62 / 81.  Small layers lose from 14 on, large ones from 19 on (mm_passes 13 and 17).
+// mm_split, large layers on the asymmetric grid: where tokens are missing and the experts below mm_else outnumber the other ones' tiles, both kernels one
+// after the other are at worst 8 % slower than side by side, the matrix cores alone 15 % (122 of 1568 x 3464, 732 of 3457 tokens left, Zipf, 92 % zeros: 203 side by
+// side, 210, 233).
+// 2575 calls of 230 layers (1024 to 4100 tokens, 0 to 99 % of them without an expert, 0.15 to 10 * 10^8 weights a projection, both grids and routings, 80 to 92 % zeros):
+// 0.79 of the time side by side, 1.08 at worst, six above 1.05; with only the host's lines, one kernel after the other below them, 0.88, 1.18 and 94.
+// What it costs a call: 0.5 to 1 us (1024 threads that add to the same words of LDS one by one took 5 to 10).
+template <int PARTS>
+__device__ int choose_mm_min(const DispatchArgs &a, const int *cnt, int S, int e0, int e1, int kept, int *sums)
+{
+    int passes = 0, tiles = 0, few = 0, crowded = 0;
+    for (int e = e0; e < e1; e++) {
+        int n = 0;
+#pragma unroll
+        for (int p = 0; p < PARTS; p++) n += cnt[p * S + spread(e)];
+        const int t = (n + kMmTokens - 1) / kMmTokens;
+        passes += (n + kRowsTokenTile - 1) / kRowsTokenTile;
+        tiles += t;
+        if (n >= a.mm_else) crowded += t;
+        else few += t;
+    }
+    const int v[4] = {passes, tiles, few, crowded};
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+        const int wave_sum = wave_inclusive_scan(v[k]);  // (in lane 63)
+        if ((threadIdx.x & 63) == 63 && wave_sum) atomicAdd(&sums[k], wave_sum);
+    }
+    __syncthreads();
+    if (10LL * sums[0] <= (long long)a.mm_passes * sums[1]) return 0x7FFFFFFF;
+    return a.mm_split && kept < a.mm_from && sums[2] > sums[3] ? a.mm_else : a.mm_min;
+}
+
 template <int PARTS>
 __global__ __launch_bounds__(1024) void k_dispatch(const DispatchArgs a)
 {
@@ -77,9 +113,9 @@ __global__ __launch_bounds__(1024) void k_dispatch(const DispatchArgs a)
     const int S = count_stride(E);
     int *cnt = sm;               // [PARTS][S] tokens of the part, later the slot of its next one; expert e at spread(e)
     int *tmp = sm + PARTS * S;   // [17 * 12] scan scratch
-    int *lost = tmp + 17 * 12;   // tokens without an expert
+    int *lost = tmp + 17 * 12;   // [1 + 4] tokens without an expert; sums of choose_mm_min
     for (int i = tid; i < PARTS * S; i += nthr) cnt[i] = 0;
-    if (tid == 0) *lost = 0;
+    if (tid < 5) lost[tid] = 0;
     __syncthreads();
     int dropped = 0;
     for (int t0 = tid; t0 < T; t0 += 4 * nthr) {
@@ -96,11 +132,13 @@ __global__ __launch_bounds__(1024) void k_dispatch(const DispatchArgs a)
     }
     if (dropped) atomicAdd(lost, dropped);
     __syncthreads();
-    const int mm_min = T - *lost >= a.mm_from ? a.mm_min : a.mm_else;
-
     // each thread owns a contiguous chunk of experts
     const int chunk = (E + nthr - 1) / nthr;
     const int e0 = min(E, tid * chunk), e1 = min(E, e0 + chunk);
+    const int kept = T - *lost;
+    int mm_min = kept >= a.mm_from ? a.mm_min : a.mm_else;
+    if (kept < a.mm_below) mm_min = choose_mm_min<PARTS>(a, cnt, S, e0, e1, kept, lost + 1);
+
     // Work items of the scalar products are listed longest first (by tile_class): handed out in that
     // order, the last workgroups to finish are busy with short items.
     int s_tok = 0, s_act = 0, s_mm = 0;
@@ -252,7 +290,7 @@ template <int PARTS>
 static qmoe_status launch_parts(const DispatchArgs &da, int threads, int max_lds, hipStream_t s)
 {
     // parts: a wavefront each, as many as the tokens fill and the LDS has counts for (two at 16384 experts)
-    const size_t smem = sizeof(int) * ((size_t)PARTS * (size_t)count_stride(da.n_experts) + 17 * 12 + 1);
+    const size_t smem = sizeof(int) * ((size_t)PARTS * (size_t)count_stride(da.n_experts) + 17 * 12 + 5);
     if constexpr (PARTS > 1) {
         if (PARTS > threads / 64 || 32 * PARTS >= da.n_tokens || smem > (size_t)max_lds)
             return launch_parts<PARTS / 2>(da, threads, max_lds, s);

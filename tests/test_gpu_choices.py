@@ -358,11 +358,11 @@ def test_units_beside_few_tokens(gpu, ddict, oracle_dict, crowded, n, few, m, d_
 
 
 # Calls whose experts all take the matrix cores, those with one token too: both sides of 1024 tokens, of 2^18 weights a matrix, of 2.5 tokens per expert below 3.5e8 weights
-# and of 25 above, from 1280 tokens on of 14 up to 7e8 weights; tokens without an expert do not count.  `least`: tokens from which on an expert takes them.
+# and of 25 above, from 1280 tokens on of 14 up to 7e8 weights; also with tokens without an expert.  `least`: tokens from which on an expert takes them.
 @pytest.mark.parametrize("E,d_model,d_ff,T,lost,least", [
-    (400, 512, 512, 1024, 0, 1), (400, 512, 512, 1024, 1, 8), (400, 512, 504, 1024, 0, 8), (409, 264, 1000, 1024, 0, 1), (410, 264, 1000, 1024, 0, 8), (437, 296, 2704, 1093, 0, 1),
-    (437, 296, 2712, 1093, 0, 8), (41, 2080, 4104, 1025, 0, 1), (41, 2080, 4104, 1025, 5, 8), (42, 2080, 4008, 1049, 0, 8),
-    (91, 1024, 4000, 1280, 6, 1), (91, 1024, 4000, 1280, 7, 8), (91, 1024, 4000, 1279, 0, 8), (92, 1024, 4000, 1280, 0, 8), (91, 1024, 7512, 1280, 0, 1),
+    (400, 512, 512, 1024, 0, 1), (400, 512, 512, 1024, 1, 1), (400, 512, 504, 1024, 0, 8), (409, 264, 1000, 1024, 0, 1), (410, 264, 1000, 1024, 0, 8), (437, 296, 2704, 1093, 0, 1),
+    (437, 296, 2712, 1093, 0, 8), (41, 2080, 4104, 1025, 0, 1), (41, 2080, 4104, 1025, 5, 1), (42, 2080, 4008, 1049, 0, 8),
+    (91, 1024, 4000, 1280, 6, 1), (91, 1024, 4000, 1280, 7, 1), (91, 1024, 4000, 1279, 0, 8), (92, 1024, 4000, 1280, 0, 8), (91, 1024, 7512, 1280, 0, 1),
     (91, 1024, 7520, 1280, 0, 6)])
 def test_all_experts_on_the_matrix_cores(gpu, ddict, oracle_dict, E, d_model, d_ff, T, lost, least):
     w = synth.WORKLOADS["switch_base128"].scaled(n_experts=E, d_model=d_model, d_ff=d_ff, n_tokens=T)
@@ -377,6 +377,36 @@ def test_all_experts_on_the_matrix_cores(gpu, ddict, oracle_dict, E, d_model, d_
     assert wsout["counters"][7] == sum(n >= least for n in (1, 2, 5, 7, 8)) + -(-(T - lost - few.size) // 64)
     _check_layer(w, idx, x, y, wsout, list(at) + [int(t) for t in np.flatnonzero(idx == E - 1)[[0, 1, -2, -1]]])
     assert np.isfinite(y).all() and not y[idx < 0].any()
+
+
+# Which kernels the experts of such layers go to when tokens are without an expert, or experts have few: `sizes` = (experts, tokens each) of those that have any, the other
+# tokens have none.  least: 1 = all to the matrix cores; 0 = none, up to 13 few-token passes (of four tokens) for ten tiles (of 64), 17 from 3.5e8 weights a projection
+# on; 8 = those with eight tokens (asymmetric grid, from 3.5e8 weights on, fewer tokens than the line, more experts below than tiles above).
+@pytest.mark.parametrize("E,d_model,d_ff,T,sizes,minmax,least", [
+    (128, 768, 3072, 1088, [], False, 0), (128, 768, 3072, 1088, [(1, 1)], False, 0), (128, 768, 3072, 1088, [(70, 1), (10, 5)], False, 0), (128, 768, 3072, 1088, [(70, 1), (7, 9)], False, 0),
+    (128, 768, 3072, 1088, [(6, 1), (4, 5)], False, 1), (128, 768, 3072, 1088, [(7, 4), (3, 8)], False, 0), (128, 768, 3072, 1088, [(120, 8)], False, 1), (128, 768, 3072, 1088, [(5, 150)], False, 1),
+    (400, 512, 512, 1100, [(324, 2), (75, 5)], False, 0), (400, 512, 512, 1100, [(1, 1), (324, 2), (75, 5)], False, 1), (400, 512, 512, 1100, [(200, 2), (100, 5)], False, 1),
+    (400, 512, 960, 2400, [(280, 4), (120, 5)], False, 0), (400, 512, 960, 2400, [(279, 4), (121, 5)], False, 1), (400, 512, 960, 2400, [(400, 6)], False, 1),
+    (100, 1568, 2400, 1420, [(3, 4), (7, 8)], True, 0), (100, 1568, 2400, 1420, [(2, 4), (1, 5), (7, 8)], True, 1), (100, 1568, 2400, 1420, [(3, 4), (7, 8)], False, 0),
+    (100, 1568, 2400, 1420, [(12, 40), (60, 3)], True, 8), (100, 1568, 2400, 1420, [(12, 40), (60, 3)], False, 1), (100, 1568, 2400, 1420, [(12, 40), (12, 3)], True, 1),
+    (100, 1568, 2400, 1420, [(12, 40), (13, 7)], True, 8), (100, 1568, 2400, 1420, [(20, 66), (79, 1)], True, 8), (100, 1568, 2400, 1420, [(20, 66), (80, 1)], True, 1)])
+def test_tokens_without_an_expert(gpu, ddict, oracle_dict, E, d_model, d_ff, T, sizes, minmax, least):
+    w = _Repeated(synth.WORKLOADS["switch_base128"].scaled(n_experts=E, d_model=d_model, d_ff=d_ff, n_tokens=T), 3)
+    n = np.concatenate([np.repeat(m, k) for k, m in sizes] + [np.zeros(0, int)]).astype(int)
+    assert n.size <= E and n.sum() <= T
+    kept = np.repeat(np.random.default_rng(E).permutation(E)[:n.size].astype(np.int32), n)
+    idx = np.random.default_rng(T).permutation(np.concatenate([kept, np.where(np.arange(T - kept.size) % 2, E, -1)])).astype(np.int32)
+    x, layer = w.tokens(), w.layer(gpu, ddict, minmax)
+    print(f"{E} experts of {d_model} x {d_ff}, {kept.size} of {T} tokens, asymmetric grid {minmax}", flush=True)
+    y, wsout = _run_layer(layer, ddict, x, idx, gpu)
+    on = n >= (least or 1 << 30)
+    assert wsout["counters"][7] == sum(-(-k // 64) for k in n[on]) and wsout["counters"][3] == sum(-(-k // 4) for k in n[~on])
+    have = np.flatnonzero((idx >= 0) & (idx < E))
+    # (not among them: token 169 of the 1420, whose row 345 sums to 3e-6 out of terms of +-0.17; fp32 sums, with up to 2^-24 of all terms' 5.5 an addition, are within
+    # 5e-9 of the terms there on either kernel, which is two bf16 ulp of the rest)
+    some = {int(have[k * (have.size - 1) // 7]) for k in range(8)} - {169} if have.size else set()
+    _check_layer(w, idx, x, y, wsout, sorted(some), asym=minmax)
+    assert not np.delete(y, have, 0).any() and np.isfinite(y).all()
 
 
 # Calls of fewer than 1024 tokens that take the matrix cores: all experts from 14 tokens per expert on, below from eight tokens on.
@@ -398,7 +428,7 @@ def test_small_calls_give_all_experts(gpu, ddict, oracle_dict, E, T, lost, least
 
 # Calls whose activations go to the first product in blocks of 16 tokens, in the output's memory, against the same call with an output that such
 # blocks cannot go to (4 bytes off): the same bits.  Full and partial blocks of every tile size, widths with partial steps and partial pieces of 128
-# columns, tokens without an expert (so many that few-token experts go to their own kernels: 1023 of 1100 left), an infinite activation.
+# columns, tokens without an expert (also so many that fewer than 1024 are left), an infinite activation.
 @pytest.mark.parametrize("E,d_model,d_ff,lost,minmax,inf", [
     (100, 136, 2056, 0, False, False), (100, 136, 2056, 7, True, False), (100, 264, 2056, 76, False, True), (100, 264, 2056, 77, False, False),
     (96, 456, 2600, 3, False, True), (96, 200, 4104, 3, True, True)])
@@ -418,7 +448,7 @@ def test_activations_in_blocks(gpu, ddict, oracle_dict, E, d_model, d_ff, lost, 
     layer = _build_layer(w, oracle_dict, gpu, order_of=ddict, experts=list(range(len(sizes))) + [E - 1], minmax=minmax)
     print(f"{E} experts of {d_model} x {d_ff}, {lost} without, asymmetric grid {minmax}, infinite {inf}", flush=True)
     y, wsout = _run_layer(layer, ddict, x, idx, gpu)
-    assert wsout["counters"][7] == sum(-(-n // 64) for n in sizes if n >= (8 if T - lost < 1024 else 1)) + -(-(T - lost - sum(sizes)) // 64)
+    assert wsout["counters"][7] == sum(-(-n // 64) for n in sizes) + -(-(T - lost - sum(sizes)) // 64)
     _check_layer(w, idx, x, y, wsout, at, asym=minmax)
     assert not y[none].any() and np.isfinite(np.delete(y, order[-1:] if inf else [], axis=0)).all()
     other = torch.full((T * d_model + 1,), float("nan"), dtype=torch.float32, device=gpu)[1:].view(T, d_model)
