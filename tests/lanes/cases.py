@@ -15,6 +15,8 @@ from paper_2310_16795_amd import synth  # noqa: E402
 L = q.lib()
 L.lanes_alloc.restype, L.lanes_alloc.argtypes = ctypes.c_void_p, [ctypes.c_size_t, ctypes.c_int, ctypes.c_size_t]
 L.lanes_reports.restype = ctypes.c_long
+P, N = ctypes.c_void_p, ctypes.c_int
+L.lanes_tile_x.argtypes, L.lanes_dispatch.argtypes = [P, P, N, P, P, N, P, N], [P, N, N, *[P] * 8, N, N]
 OD = oracle.Dictionary()
 D = q.qmoe_dict_from_words(OD.words)
 
@@ -153,13 +155,67 @@ def encode(rng, i, bad):
     return status == [0, 0] and np.array_equal(read(at_off, rows + 1, np.uint32), off) and np.array_equal(read(at, codes.size, np.uint16), codes)
 
 
+def blocks(rng, i):
+    """The copy of activations into blocks of 16 tokens."""
+    cols, cus = int(rng.choice([8, 16, 120, 128, 136, 264])), int(rng.choice([1, 6]))
+    sizes = rng.choice([1, 2, 15, 16, 17, 31, 33, 48, 63, 64], int(rng.integers(0, 6)))
+    more, skipped = int(rng.integers(0, 9)), int(rng.integers(0, 5))  # tokens of no listed tile; slots of one, ahead of the others
+    slots = int(sizes.sum()) + skipped
+    T = slots + more
+    print(f"blocks {i}: {sizes.tolist()} of {T} tokens, {cols} columns, {cus} compute units", flush=True)
+    m = Memory(i % 2)
+    x, perm = synth.normal_bf16(int(rng.integers(1 << 20)), (T + 1, cols))[:T], rng.permutation(T).astype(np.int32)
+    at = skipped + np.concatenate([[0], np.cumsum(sizes)])[:len(sizes)].astype(int)
+    items = np.array([[0, s, n, 0] for s, n in zip(at, sizes)], dtype=np.int32).reshape(-1, 4)
+    order = rng.permutation(len(items))
+    out = m.new(max(1, 2 * slots * cols), 16)
+    assert L.lanes_tile_x(m.put(items[order]) if len(items) else None, m.put(np.array([len(items)], dtype=np.int32)), max(1, len(items)), m.put(perm[:max(1, slots)]), m.put(x, 16), cols, out, cus) == 0
+    got, want = read(out, slots * cols, np.uint16).reshape(slots, cols), np.full((slots, cols), 0xFFFF, dtype=np.uint16)
+    for s, n in zip(at, sizes):
+        for b in range(0, n, 16):
+            t = x[perm[s + b:s + min(n, b + 16)]]
+            want[s + b:s + b + len(t)] = t.reshape(len(t), cols // 8, 8).transpose(1, 0, 2).reshape(len(t), cols)
+    return np.array_equal(got, want)
+
+
+def dispatch(rng, i):
+    """The dispatch of calls whose experts may all take the matrix cores."""
+    E, T = int(rng.choice([1, 5, 40, 130, 300])), int(np.exp(rng.uniform(0, np.log(1500))))
+    idx = rng.integers(0, E, T)
+    if rng.random() < 0.5:
+        idx = np.minimum((E * rng.random(T) ** 4).astype(int), E - 1)
+    idx[rng.random(T) < rng.choice([0.0, 0.1, 0.7, 1.0])] = rng.choice([-1, E, 1 << 30])
+    idx = idx.astype(np.int32)
+    n = np.bincount(idx[(idx >= 0) & (idx < E)], minlength=E)
+    kept = int(n.sum())
+    passes, tiles = int((-(-n // 4)).sum()), int((-(-n // 64)).sum())
+    edge = 10 * passes // max(1, tiles)
+    lines = [1, int(rng.choice([kept, kept + 1, 1, T])), int(rng.choice([5, 8])), int(rng.choice([0, kept, kept + 1, T + 1])), int(rng.choice([13, 17, edge, edge + 1])), int(rng.integers(0, 2))]
+    least = lines[0] if kept >= lines[1] else lines[2]
+    if kept < lines[3]:
+        few, crowded = int(((n > 0) & (n < lines[2])).sum()), int((-(-n[n >= lines[2]] // 64)).sum())
+        least = 1 << 30 if 10 * passes <= lines[4] * tiles else (lines[2] if lines[5] and kept < lines[1] and few > crowded else 1)
+    print(f"dispatch {i}: {E} experts, {kept} of {T} tokens, lines {lines}", flush=True)
+    m = Memory(i % 2)
+    lists, off, perm, counters, y = [m.new(16 * T, 16) for _ in range(3)], m.new(4 * (E + 1)), m.new(4 * T), m.new(64), m.new(4 * T * 3)
+    assert L.lanes_dispatch(m.put(idx), T, E, off, perm, counters, *lists, m.put(np.array(lines, dtype=np.int32)), y, 3, 160 << 10) == 0
+    c, ref_off, ref_perm = read(counters, 16, np.int32), *oracle.dispatch(idx, E)
+    right = np.array_equal(read(off, E + 1, np.int32), ref_off) and np.array_equal(read(perm, kept, np.int32), ref_perm)
+    for list_at, count, tile, experts in ((lists[0], c[3], 4, n < least), (lists[1], c[4], 4, n < least), (lists[2], c[7], 64, n >= least)):
+        got = read(list_at, 4 * count, np.int32).reshape(count, 4).tolist()
+        right &= sorted(got) == [[e, ref_off[e] + b, min(tile, n[e] - b), 0] for e in np.flatnonzero(experts) for b in range(0, n[e], tile)]
+    none = (idx < 0) | (idx >= E)
+    return right and c[0] == kept and c[1] == none.sum() and not read(y, 3 * T, np.float32).reshape(T, 3)[none].any()
+
+
 if __name__ == "__main__":
     kind, seed, count = sys.argv[1], int(sys.argv[2]), int(sys.argv[3])
     rng, ok = np.random.default_rng(seed), True
     for i in range(count):
         before = L.lanes_reports()
         right = {"layer": lambda: layer(rng, i, 0), "layer_corrupt": lambda: layer(rng, i, 1 + i % 3), "single": lambda: single(rng, i, 0),
-                 "single_corrupt": lambda: single(rng, i, 1 + i % 4 % 3), "encode": lambda: encode(rng, i, i % 4 % 3)}[kind]()
+                 "single_corrupt": lambda: single(rng, i, 1 + i % 4 % 3), "encode": lambda: encode(rng, i, i % 4 % 3),
+                 "blocks": lambda: blocks(rng, i), "dispatch": lambda: dispatch(rng, i)}[kind]()
         out = L.lanes_reports() - before
         ok &= bool(right) and out == 0
         if not right or out:

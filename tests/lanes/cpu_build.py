@@ -1,7 +1,8 @@
 """A CPU build of the library's kernels, for the tests: every lane a fibre, every access checked (lanes.cpp).
 
 The sources are taken as they are but for pointers with an address space, which become objects that check what they point
-at, and two instructions that are written in assembly.  The matrix-core kernel, whose loop is in assembly, is left out.
+at, and two instructions that are written in assembly.  The matrix-core kernel, whose loop is in assembly, is left out; the dispatch for it and
+the copy of activations into its blocks, which a layer call without it does not reach, have entries here.
 """
 import os
 import re
@@ -16,6 +17,26 @@ NO_MATRIX_CORES = """#include "qmoe_dev.h"
 namespace qmoe {
 size_t mm_lds_bytes(int) { return (size_t)1 << 40; }
 qmoe_status launch_product_mm(ProductArgs, const MmPlan &, hipStream_t) { return QMOE_E_LIMIT; }
+}
+using namespace qmoe;
+extern "C" int lanes_tile_x(const int *items, const int *n_items, int max_items, const int *perm, const uint16_t *x, int cols, uint16_t *out, int cus)
+{
+    ProductArgs a{};
+    a.items = reinterpret_cast<const Item *>(items);
+    a.n_items_dev = n_items;
+    a.max_items = max_items;
+    a.perm = perm;
+    a.x = x;
+    a.cols = a.ldx = cols;
+    return launch_tile_x(a, out, cus, nullptr);
+}
+extern "C" int lanes_dispatch(const int32_t *expert_idx, int n_tokens, int n_experts, int *tok_off, int *perm, int *counters, int *items_wi, int *items_wo,
+                              int *items_mm, const int *lines /*mm_min, mm_from, mm_else, mm_below, mm_passes, mm_split*/, float *y, int d_model, int max_lds)
+{
+    auto list = [](int *p) { return reinterpret_cast<Item *>(p); };
+    const DispatchArgs d{expert_idx, n_tokens, n_experts, tok_off, perm, counters, list(items_wi), list(items_wo), list(items_mm), 4, 4,
+                         lines[0], lines[1], lines[2], lines[3], lines[4], lines[5], y, d_model};
+    return launch_dispatch_kernel(d, max_lds, nullptr);
 }
 """
 

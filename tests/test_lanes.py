@@ -1,5 +1,5 @@
 """The kernels in a CPU build that checks every access to memory and LDS (tests/lanes), against the oracle: layers, single
-matrices, decompression and the device encoder at small odd sizes, every layout, numbering, grid and tile; and streams that are none,
+matrices, decompression, the device encoder and what goes before the matrix-core kernel at small odd sizes, every layout, numbering, grid and tile; and streams that are none,
 which must stay inside their buffers whatever they decode to."""
 import os
 import subprocess
@@ -18,7 +18,7 @@ def library(tmp_path_factory):
     return build(str(tmp_path_factory.mktemp("lanes")))
 
 
-@pytest.mark.parametrize("kind,count", [("layer", 60), ("layer_corrupt", 24), ("single", 60), ("single_corrupt", 18), ("encode", 60)])
+@pytest.mark.parametrize("kind,count", [("layer", 60), ("layer_corrupt", 24), ("single", 60), ("single_corrupt", 18), ("encode", 60), ("blocks", 60), ("dispatch", 80)])
 def test_every_access_is_inside(library, kind, count):
     cmd = [sys.executable, os.path.join(HERE, "lanes", "cases.py"), kind, "1", str(count)]
     r = subprocess.run(cmd, env={**os.environ, "QMOE_LIBRARY": library}, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300)
