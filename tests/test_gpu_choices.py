@@ -455,3 +455,82 @@ def test_activations_in_blocks(gpu, ddict, oracle_dict, E, d_model, d_ff, lost, 
     layer.forward(ddict, _to_dev16(x, gpu), torch.from_numpy(idx).to(gpu), other, layer.workspace(T))
     torch.cuda.synchronize()
     assert np.array_equal(y, other.cpu().numpy(), equal_nan=True)
+
+
+def _blocks(x, items, perm):
+    """Activations of the listed tiles as the copy leaves them in the output, by slot."""
+    out = np.zeros((perm.size, x.shape[1]), dtype=np.uint16)
+    for _, slot0, ntok, _ in items:
+        for s in range(slot0, slot0 + ntok, 16):
+            t = x[perm[s:min(slot0 + ntok, s + 16)]]
+            out[s:s + len(t)] = t.reshape(len(t), -1, 8).transpose(1, 0, 2).reshape(len(t), -1)
+    return out
+
+
+# Where those blocks are taken, seen after the dispatch and the first product alone: calls from 2048 units of the first product on (by the plan's estimate: 90 experts, not
+# 89), with an output that is aligned and apart from the activations and from the experts' numbers.  Elsewhere the output is untouched by then.  Complete calls give the same
+# bits, with a gate, from the entry without a workspace, and from a graph that is replayed between other work.
+def test_where_blocks_are_taken(gpu, ddict, oracle_dict):
+    T, d_model, d_ff = 1100, 136, 2056
+    for E in (90, 89):
+        w = _Repeated(synth.WORKLOADS["switch_base128"].scaled(n_experts=E, d_model=d_model, d_ff=d_ff, n_tokens=T), 3)
+        x, idx = w.tokens(), np.random.default_rng(E).integers(0, E, T).astype(np.int32)
+        idx[:400] = 7
+        layer = w.layer(gpu, ddict, False)
+        gate = torch.linspace(0.2, 1.0, T, device=gpu)
+        room = torch.empty(4 * T * d_model + 64, dtype=torch.uint8, device=gpu)
+
+        def buffers(where):
+            """x, experts' numbers and output, the first two inside the third where it says so."""
+            room.fill_(0xFF)
+            at = 4 if where == "misaligned" else 0
+            y = room[at:at + 4 * T * d_model].view(torch.float32).view(T, d_model)
+            bits, numbers = _to_dev16(x, gpu), torch.from_numpy(idx).to(gpu)
+            if where == "x inside":
+                bits = room[2 * T * d_model:4 * T * d_model].view(torch.int16).view(T, d_model).copy_(bits)
+            if where == "numbers inside":
+                numbers = room[:4 * T].view(torch.int32).copy_(numbers)
+            return bits, numbers, y
+
+        results = {}
+        for where in ("apart", "misaligned", "x inside", "numbers inside"):
+            print(f"{E} experts, {where}", flush=True)
+            bits, numbers, y = buffers(where)
+            before, ws = y.clone(), layer.workspace(T)
+            q.qmoe_hook_set("phases", 1 | 8)
+            try:
+                layer.forward(ddict, bits, numbers, y, ws, gate)
+                torch.cuda.synchronize()
+            finally:
+                q.qmoe_hook_set("phases", 0)
+            out = dev.read_workspace(ws, E, d_model, d_ff, T)
+            items = out["items_mm"][:out["counters"][7]]
+            assert items[:, 2].sum() == T
+            if E == 90 and where == "apart":
+                held = y.view(torch.int16).cpu().numpy().view(np.uint16).reshape(-1)[:T * d_model].reshape(T, d_model)
+                assert np.array_equal(held, _blocks(x, items, out["perm"]))
+            else:
+                assert torch.equal(y.view(torch.int32), before.view(torch.int32))
+            bits, numbers, y = buffers(where)
+            layer.forward(ddict, bits, numbers, y, ws, gate)
+            torch.cuda.synchronize()
+            results[where] = y.cpu().numpy().copy()
+            if where == "apart":
+                _check_layer(w, idx, x, results[where], dev.read_workspace(ws, E, d_model, d_ff, T), [0, 1, 399, 400, 1098, 1099], gate=gate.cpu().numpy())
+        bits, numbers, y = buffers("apart")
+        layer.forward_static(ddict, bits, numbers, y, gate)
+        torch.cuda.synchronize()
+        results["static"] = y.cpu().numpy().copy()
+        stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            layer.forward(ddict, bits, numbers, y, ws, gate, stream=torch.cuda.current_stream().cuda_stream)
+        for k in range(3):
+            other = torch.empty_like(y)
+            layer.forward(ddict, bits, numbers, other, layer.workspace(T), gate)
+            y.fill_(float("nan"))
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            results[f"replay {k}"] = y.cpu().numpy().copy()
+        for what, y in results.items():
+            assert np.array_equal(y, results["apart"]), what
