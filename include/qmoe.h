@@ -337,8 +337,8 @@ qmoe_status qmoe_decompress(const qmoe_dict *d, const qmoe_matrix *mats /*device
  *   counters int32 [16]           [0] tokens kept, [1] tokens dropped (expert index
  *                                 outside [0,n_experts)), [2] experts with tokens,
  *                                 [3] work items of the first product, [4] of the second,
- *                                 [7] token tiles of crowded experts (items_mm, up to 64
- *                                 tokens each, both products, matrix-core kernel)
+ *                                 [7] token tiles of the experts on the matrix-core kernel (items_mm,
+ *                                 up to 64 tokens each, both products)
  *   items_*  int32 [n_tokens][4]  {expert, first slot, tokens, 0}; every kept token is in
  *                                 exactly one item of items_wi or items_mm, and one of
  *                                 items_wo or items_mm
@@ -360,9 +360,12 @@ size_t qmoe_moe_layer_workspace(int n_experts, int d_model, int d_ff, int n_toke
  * wo[e]: d_model x d_ff).  x: device bf16 [n_tokens][d_model].  expert_idx:
  * device int32 [n_tokens].  gate: device fp32 [n_tokens] or NULL (= 1).
  * Activations should be finite: one that is not spoils results of its own token and, where its
- * expert is given to a few-token kernel (below), may spoil the other tokens' of its tile of up to four.
+ * expert is given to a few-token kernel (below), may spoil the other tokens' of its tile of up to four.  On the matrix-core
+ * kernel it costs time: its rows are summed again weight by weight (one such token among 4001 on 128 experts of 768 x 3072: 148 us, 410 with it).
  * y: device fp32 [n_tokens][d_model], overwritten; a token whose expert index
- * is outside [0, n_experts) gets a zero row.  workspace: device, 256-byte
+ * is outside [0, n_experts) gets a zero row.  Until the call's work ends y may hold anything: a call may keep the activations in it, in
+ * another order, if it is 16-byte aligned and apart from x and expert_idx, so it should be memory that this GPU reads as fast as
+ * it writes.  expert_idx is read until then, too.  workspace: device, 256-byte
  * aligned, >= qmoe_moe_layer_workspace(...) bytes (32 KiB less will do, for half a microsecond
  * more in small calls), contents need not be initialised.  Experts without tokens are never
  * touched (their qmoe_matrix may hold anything).  code_order: QMOE_FORMAT_* bits: the numbering of every expert's
@@ -376,9 +379,14 @@ size_t qmoe_moe_layer_workspace(int n_experts, int d_model, int d_ff, int n_toke
  * Enqueues a dispatch kernel and, per product, the scalar kernel for experts with few
  * tokens (by the experts that the call can reach, their widths and the layout: the one in which several
  * lanes share a row, or the one with a row range per lane) and (device-order streams, widths divisible by 8, x 16-byte aligned) the
- * matrix-core kernel for crowded ones: an expert's matrix is decoded once per tile of up
- * to 64 tokens there, instead of once per 4.  When both kinds of experts are present the
- * two kernels of one kind run, in calls of at least four tokens per compute unit, on a second stream that
+ * matrix-core kernel for the others: an expert's matrix is decoded once per tile of up
+ * to 64 tokens there, instead of once per 4.  Which experts are the others goes by the layer and the tokens per expert: those with eight tokens
+ * (in some layers five or six), or all of them: in calls of four tokens per compute unit and more with 2.5 tokens per expert where all experts
+ * have fewer than 3.5e8 weights a projection, with 14 where they have fewer than 7e8 (and the call five tokens per compute unit), else with 25; in smaller
+ * ones that use that kernel at all, with 14.  (The larger of these leave that to the dispatch kernel where tokens without an expert, or experts with few, would make
+ * the few-token kernels the faster way for all or, on the asymmetric grid, some.)  Calls that may give it all experts run on `stream` alone, kernel
+ * after kernel.  In the others of at least four tokens per compute unit the
+ * two kernels of one kind run on a second stream that
  * forks from `stream` after the dispatch and joins it again before the call's work ends (two library-owned events per device), so that
  * later work on `stream` sees y complete as usual.  side_stream: that second stream, owned
  * by the caller like `stream` (default priority; it must not be `stream` itself); NULL = a

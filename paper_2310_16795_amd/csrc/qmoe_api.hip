@@ -350,26 +350,27 @@ constexpr double kMmCrowdedWeights = 4e8;    // of all experts, a projection
 // Layers whose experts all take the matrix cores, those with one token too: small ones from 2.5 tokens per expert on, others from 25 on, in calls
 // that are not small.  Next to the matrix-core kernel the few experts that are left to the few-token kernels cost those kernels' starts and a second
 // stream's fork and join, some 20 us in all, as much as a tile for each of them; larger layers with fewer tokens have so many experts of one or two that
-// tiles of sixteen are the dearer way.  Both ways, us, from eight tokens on (larger layers: see above) / all: 128 experts of 768 x 3072, 4001 tokens, Zipf
-// 188 / 159, 1088 tokens, uniform 150 / 106; 256 of 512 x 2048, 80 % zeros, 1152 tokens 167 / 109, Zipf 129 / 104; 100 of 2080 x 6144, 3000 tokens 406 / 386;
-// 45, 2048 tokens, Zipf 282 / 250; not so 200, 4100 tokens, Zipf 690 / 723.  Of 119 layers below 3.5 * 10^8 weights a projection (1024 to 4100 tokens, 2 to 60 per
+// tiles of sixteen are the dearer way.  Both ways, us, from eight tokens on (larger layers: see above), on two streams / all: 128 experts of 768 x 3072, 4001
+// tokens, Zipf 192 / 147, 1088 tokens, uniform 145 / 107; 256 of 512 x 2048, 1152 tokens, 80 % zeros 167 / 116, 90 %, Zipf 107 / 96; 100 of 2080 x 6144, 3000 tokens
+// 402 / 384; 45, 2048 tokens, Zipf 283 / 242; not so 200, 4100 tokens, Zipf 705 / 707.  Of 119 layers below 3.5 * 10^8 weights a projection (1024 to 4100 tokens, 2 to 60 per
 // expert, 80 to 92 % zeros, both grids and routings): 0.81 of the time on average, 0.95 at worst; of 25 larger ones with 25 tokens per expert or more 0.88 and
 // 0.99; of larger ones with 10 to 25 0.94 and 1.11, with fewer up to 1.6.
-// Up to 7 * 10^8 weights, calls of five tokens per compute unit or more with 14 per expert: 56 of 1752 x 6144, 1366 tokens, Zipf 264 / 219; 64 of 1264 x 4368,
-// 1507, Zipf 199 / 157; 129 of 1112 x 4112, 2035, uniform 207 / 190; 103 of 1680 x 2680, 2318, Zipf, asymmetric grid 230 / 233; of 34 such layers 0.92 of the time
-// on average, 1.015 at worst.  With fewer per expert (302 of 792 x 2064, 3349 tokens, Zipf, asymmetric 195 / 218) or more weights (212 of 1240 x 5496, 3421, Zipf,
-// asymmetric 468 / 515) not.
+// Up to 7 * 10^8 weights, calls of five tokens per compute unit or more with 14 per expert: 56 of 1752 x 6144, 1366 tokens, Zipf 258 / 212; 64 of 1264 x 4368,
+// 1507, Zipf 198 / 155; 129 of 1112 x 4112, 2035, uniform 209 / 194; of 34 such layers 0.92 of the time on average.  The asymmetric grid has the few that lose, with
+// Zipf routing: 103 of 1680 x 2680, 2318 224 / 231; 132 of 1504 x 3384, 2444 284 / 296.  With fewer per expert (302 of 792 x 2064, 3349 tokens, Zipf, asymmetric
+// 192 / 219) or more weights (212 of 1240 x 5496, 3421, Zipf, asymmetric 468 / 515) not.
 constexpr double kMmAllWeights = 3.5e8, kMmAllPerExpert = 2.5, kMmMiddleWeights = 7e8, kMmAllPerExpertMiddle = 14.0, kMmAllPerExpertLarge = 25.0,
                  kMmChooseWeights = 1.5e8;
-constexpr long long kMmAllMatrix = 1 << 18;  // (a matrix; smaller ones, which do without k_rows, are launch latency either way)
+constexpr long long kMmAllMatrix = 1 << 18;  // (a matrix; the line of k_rows.  Smaller ones were not measured with all experts here)
 
 // Calls that give all experts to the matrix cores bring the activations to the first product in blocks of 16 tokens (k_tile_x), if that has more units than
 // there are wavefronts.  Read by token rows, a quarter of a wavefront's operand load touches sixteen lines, in blocks two: a step of 64 tokens took
-// 3.1 to 4.2 thousand cycles in the first product and 1.8 to 2.1 in the second.  The copy costs 3 to 4 us, which one partly filled round of
-// units does not win back.  Rows / blocks, us, 90 % zeros, uniform routing where nothing else is said: 128 experts of 768 x 3072, 64 tokens each 171 / 147, 16 each
-// 107 / 107, 4001 tokens, Zipf 165 / 149.5; 64 of 1024 x 4096, 64 each 156 / 133; 64 of 2080 x 6144, 64 each 344 / 315 (asymmetric grid 380 / 387), 32 each
-// 254 / 258; 18 of 1920 x 2496, 3996 tokens, Zipf, asymmetric 220 / 190; below the line 64 of 512 x 2048, 24 each 59 / 62; 24 of 2088 x 1176, 1684
-// tokens, Zipf 80 / 84.  (The tiles are estimated: whole ones, and half a tile an expert.)
+// 3.1 to 4.2 thousand cycles in the first product and 1.8 to 2.1 in the second.  The copy (k_tile_x) costs more than one partly filled round of
+// units wins back.  Rows / blocks, us, 90 % zeros, uniform routing where nothing else is said: 128 experts of 768 x 3072, 8192 tokens 234 / 201, 2048
+// 115 / 114, 4001 tokens, Zipf 164 / 149; 64 of 1024 x 4096, 4096 tokens 198 / 165; 64 of 2080 x 6144, 4096 432 / 383 (asymmetric grid 499 / 468), 2048
+// 288 / 279; 18 of 1920 x 2496, 3996 tokens, Zipf, asymmetric 224 / 180; below the line 64 of 512 x 2048, 1536 65 / 67; 24 of 2088 x 1176, 1684
+// tokens, Zipf 80 / 85.  On the asymmetric grid some above it lose up to 3 %: 71 of 1832 x 5328, 2459 tokens 315 / 326.  (The tiles are estimated: whole
+// ones, and half a tile an expert.)
 bool mm_tiles_x(int n_experts, int d_ff, int n_tokens, const DeviceInfo &di)
 {
     return ((double)n_tokens / kMmTokens + 0.5 * n_experts) * ((d_ff + 63) / 64) >= (double)(kMmThreads / 64) * di.cus;
@@ -913,7 +914,7 @@ qmoe_status layer_forward(const qmoe_dict *d, const qmoe_matrix *wi, const qmoe_
     }
     // In a small call the kernel with several lanes per row groups the tokens itself.
     const bool grouping = rp.on && !mm && rows_can_dispatch(n_experts, n_tokens, rp.grid, n_order, rp.max_lds);
-    // The blocks of the activations go into the output's memory, which nobody writes before the second product does, behind the first one on the
+    // The blocks of the activations go into the output's memory, which nobody writes before the second products do, behind the first one on the
     // same stream; that product clears the rows of tokens without an expert, too, then.
     auto apart = [&](const void *p, size_t bytes) {
         const uintptr_t q = reinterpret_cast<uintptr_t>(p), o = reinterpret_cast<uintptr_t>(y);
@@ -993,7 +994,7 @@ qmoe_status layer_forward(const qmoe_dict *d, const qmoe_matrix *wi, const qmoe_
         am.out_tiled = 1;
         am.mm_spread = mm_spread;
         // activations by token rows: the wavefronts of a workgroup read the same lines together (in blocks: 4001 tokens on 128 experts of 768 x 3072,
-        // Zipf, 155 us in step, 149.5 each for itself)
+        // Zipf, 153 us in step, 149 each for itself)
         am.mm_in_step = !tile_x;
         if (tile_x && (phases & 8)) {
             if ((st = launch_tile_x(am, reinterpret_cast<uint16_t *>(y), mp.grid, s_mm)) != QMOE_OK) return st;

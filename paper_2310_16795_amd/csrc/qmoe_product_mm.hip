@@ -835,13 +835,14 @@ __global__ __launch_bounds__(kMmThreads) void k_product_mm(const ProductArgs a)
     unsigned char *wt = smem + table_bytes;                           // [512][kMmRowBytes] rings
     unsigned char *win = wt + (size_t)kMmThreads * kMmRowBytes;       // codeword windows: [wavefront][group][lane][4]
 
-    // A unit of work is 64 rows of one (expert, token tile) item, and a wavefront takes it alone: after
-    // the table is staged the wavefronts of a workgroup share nothing and meet at no barrier, so one
-    // wavefront's set-up (a chain of trips to memory) runs under the others' arithmetic, a matrix
+    // A unit of work is 64 rows of one (expert, token tile) item, and a wavefront takes it alone: once
+    // the table is staged the wavefronts of a workgroup share the table and how they come by their units, and meet at no barrier (but
+    // in step), so one wavefront's set-up (a chain of trips to memory) runs under the others' arithmetic, a matrix
     // whose rows are no multiple of 512 leaves no wavefront idle, and the units are small enough to
-    // pack well.  A layer call brings a list of items, most of whose units are dealt out in advance, and a device
-    // counter for the rest, or for all of them where a workgroup's wavefronts go in step (both below); the single-matrix call
-    // has neither: its items are the tiles of 64 consecutive tokens of `single`, its units dealt out round robin.
+    // pack well.  A layer call brings a list of items, some or all of whose units are dealt out in advance, and a device counter for the rest, which a
+    // workgroup's wavefronts draw from through a lock and a small stock in LDS (pool_draw), or, in step, eight at a time; where two rounds are dealt
+    // out, they count in LDS what is taken of their workgroup's share.  All of that is below.  The single-matrix call
+    // has neither list nor counter: its items are the tiles of 64 consecutive tokens of `single`, its units dealt out round robin.
     const bool listed = a.items != nullptr;
     if constexpr (EPI == 0) {  // (ahead of the return: all workgroups)
         if (a.clear_idx && *a.clear_count > 0) {
