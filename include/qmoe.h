@@ -381,7 +381,7 @@ size_t qmoe_moe_layer_workspace(int n_experts, int d_model, int d_ff, int n_toke
  * lanes share a row, or the one with a row range per lane) and (device-order streams, widths divisible by 8, x 16-byte aligned) the
  * matrix-core kernel for the others: an expert's matrix is decoded once per tile of up
  * to 64 tokens there, instead of once per 4.  Which experts are the others goes by the layer and the tokens per expert: those with eight tokens
- * (in some layers five or six), or all of them: in calls of four tokens per compute unit and more with 2.5 tokens per expert where all experts
+ * (in some layers five or six), or, where a matrix has at least 2^18 weights, all of them: in calls of four tokens per compute unit and more with 2.5 tokens per expert where all experts
  * have fewer than 3.5e8 weights a projection, with 14 where they have fewer than 7e8 (and the call five tokens per compute unit), else with 25; in smaller
  * ones that use that kernel at all, with 14.  (The larger of these leave that to the dispatch kernel where tokens without an expert, or experts with few, would make
  * the few-token kernels the faster way for all or, on the asymmetric grid, some.)  Calls that may give it all experts run on `stream` alone, kernel
